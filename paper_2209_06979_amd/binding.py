@@ -1,8 +1,11 @@
 """Thin Python binding over the C ABI of libmagicube.so (see include/magicube.h).
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.
-PyTorch supplies device memory (tensors) and the current stream, nothing else.  If the
-shared library is missing the import fails -- there is no fallback implementation.
+PyTorch supplies device memory (tensors) and the current stream, nothing else.  The format
+builders, options and measurement aids go through ctypes; the compute calls, where the time of
+a call counts, are the functions of the extension module ``_native`` (csrc/python_calls.cpp).
+If the shared library or the extension is missing the import fails -- there is no fallback
+implementation.
 """
 from __future__ import annotations
 
@@ -151,6 +154,15 @@ def _load() -> ctypes.CDLL:
 
 lib = _load()
 
+try:  # after the library, which it links to
+    from . import _native
+except ImportError as e:
+    raise ImportError(f"the extension module _native cannot be loaded ({e}): build it first "
+                      "(python -m paper_2209_06979_amd.build); there is no other implementation of the compute calls") from e
+
+
+_native._set_error_class(MagicubeError)
+
 
 def _check(status: int, where: str) -> None:
     if status != MC_OK:
@@ -248,7 +260,16 @@ def unpack_host(M, K, V, lhs_bits, panel_ptr, slot_idx, slot_vals):
 
 
 # ---------------------------------------------------------------- device objects ----
-class SparseMatrix:
+# Compute calls (see their docstrings); SparseMatrix.set_values comes from the same module.
+spmm, spmm_dequant = _native.spmm, _native.spmm_dequant
+sddmm, sddmm_dequant, sddmm_to_mat = _native.sddmm, _native.sddmm_dequant, _native.sddmm_to_mat
+absmax, quantize = _native.absmax, _native.quantize
+sparse_softmax, sparse_softmax_to_mat = _native.sparse_softmax, _native.sparse_softmax_to_mat
+sparse_attention, sparse_attention_static = _native.sparse_attention, _native.sparse_attention_static
+OUT_TYPE = {torch.float32: 0, torch.float16: 1}
+
+
+class SparseMatrix(_native.Matrix):
     """Device-resident vector-sparse matrix or mask (owns an mc_mat handle)."""
 
     def __init__(self, M, K, V, row_ptr, col_idx, values=None, lhs_bits=0):
@@ -272,15 +293,11 @@ class SparseMatrix:
         grp, mnvec = c_int(), c_int64()
         _check(lib.mc_mat_merged_info(h, ctypes.byref(grp), ctypes.byref(mnvec)), "mc_mat_merged_info")
         self.merge_group, self.merged_nvec = grp.value, mnvec.value   # 0: the operand has no merged copy
-
-    def set_values(self, values_dev) -> None:
-        """values_dev: device tensor, nvec*V elements in interchange (vector-major) order."""
-        assert values_dev.is_cuda and values_dev.is_contiguous()
-        assert values_dev.numel() * values_dev.element_size() == self.nvec * self.V * _container_bits(self.lhs_bits) // 8
-        _check(lib.mc_mat_set_values_device(self.handle, values_dev.data_ptr(), _stream()), "mc_mat_set_values_device")
+        self._attach(h.value, M, V, self.nvec, self.lhs_bits)         # for the compute calls
 
     def close(self) -> None:
         if getattr(self, "handle", None):
+            self._detach()
             lib.mc_mat_destroy(self.handle)
             self.handle = None
 
@@ -326,31 +343,6 @@ def set_attention_mode(mode: int = 0) -> None:
     _check(lib.mc_set_attention_mode(mode), "mc_set_attention_mode")
 
 
-def spmm(A: SparseMatrix, B, prec: str, out=None, lhs_unsigned: bool = False, rhs_unsigned: bool = False,
-         options: Options | None = None):
-    """C = A * B (int32, M x N).  B: device tensor (K, N) int8, (K, N/2) uint8 for R4, (K, N) int16 for R16.
-    lhs_unsigned / rhs_unsigned: read the 8- or 4-bit operand as non-negative values.
-    options: kernel-variant choices of this call (None: the calling thread's defaults)."""
-    assert B.is_cuda and B.dim() == 2 and B.stride(1) == 1
-    rbits = RHS_BITS[prec]
-    N = B.shape[1] * B.element_size() * 8 // rbits
-    ldb = B.stride(0) * B.element_size() * 8 // rbits
-    if out is None:
-        out = torch.empty((A.M, N), dtype=torch.int32, device=B.device)
-    assert out.is_cuda and out.dtype == torch.int32 and out.shape == (A.M, N) and out.stride(1) == 1
-    flags = (1 if lhs_unsigned else 0) | (2 if rhs_unsigned else 0)
-    if options is not None:
-        _check(lib.mc_spmm_ex(A.handle, B.data_ptr(), N, ldb, PREC[prec], flags, ctypes.byref(options), out.data_ptr(),
-                              out.stride(0), _stream()), "mc_spmm_ex")
-        return out
-    _check(lib.mc_spmm_flags(A.handle, B.data_ptr(), N, ldb, PREC[prec], flags, out.data_ptr(), out.stride(0), _stream()),
-           "mc_spmm_flags")
-    return out
-
-
-OUT_TYPE = {torch.float32: 0, torch.float16: 1}
-
-
 def spmm_form(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> str:
     """The form mc_spmm_ex would take for this operand: "gather" or "lds" (K-blocks of B resident in LDS)."""
     r = lib.mc_spmm_form(A.handle, N, PREC[prec], ctypes.byref(options) if options is not None else None)
@@ -365,22 +357,6 @@ def spmm_on_merged(A: SparseMatrix, N: int, prec: str, options: Options | None =
     if r < 0:
         _check(r, "mc_spmm_form")
     return bool(r & 2)
-
-
-def spmm_dequant(A: SparseMatrix, B, prec: str, scale: float, out_dtype=torch.float32, out=None,
-                 lhs_unsigned: bool = False, rhs_unsigned: bool = False):  # kernel variants: the thread's options
-    """C = scale * (A * B) as fp32 or fp16 (M x N): SpMM with the dequantisation fused into the kernel."""
-    assert B.is_cuda and B.dim() == 2 and B.stride(1) == 1
-    rbits = RHS_BITS[prec]
-    N = B.shape[1] * B.element_size() * 8 // rbits
-    ldb = B.stride(0) * B.element_size() * 8 // rbits
-    if out is None:
-        out = torch.empty((A.M, N), dtype=out_dtype, device=B.device)
-    assert out.is_cuda and out.dtype == out_dtype and out.shape == (A.M, N) and out.stride(1) == 1
-    flags = (1 if lhs_unsigned else 0) | (2 if rhs_unsigned else 0)
-    _check(lib.mc_spmm_dequant(A.handle, B.data_ptr(), N, ldb, PREC[prec], flags, float(scale), OUT_TYPE[out_dtype],
-                               out.data_ptr(), out.stride(0), _stream()), "mc_spmm_dequant")
-    return out
 
 
 def probe_gather(A: SparseMatrix, B, prec: str, sink=None):
@@ -417,105 +393,6 @@ def probe_mfma(workgroups: int, iters: int, sink=None):
     return sink
 
 
-def sddmm(Q, Kmat, mask: SparseMatrix, prec: str, out=None, lhs_unsigned: bool = False, rhs_unsigned: bool = False,
-          options: Options | None = None):
-    """S (nvec*V int32, interchange order) = (Q * Kmat^T) at the mask's stored vectors."""
-    assert Q.is_cuda and Kmat.is_cuda and Q.dim() == 2 and Kmat.dim() == 2
-    assert Q.stride(1) == 1 and Kmat.stride(1) == 1 and Q.shape[1] == Kmat.shape[1]
-    bits = LHS_BITS[prec]
-    Kd = Q.shape[1] * Q.element_size() * 8 // bits
-    assert Q.element_size() == Kmat.element_size()
-    if out is None:
-        out = torch.empty(mask.nvec * mask.V, dtype=torch.int32, device=Q.device)
-    assert out.is_cuda and out.dtype == torch.int32 and out.numel() == mask.nvec * mask.V and out.is_contiguous()
-    flags = (1 if lhs_unsigned else 0) | (2 if rhs_unsigned else 0)
-    if options is not None:
-        _check(lib.mc_sddmm_ex(Q.data_ptr(), Q.stride(0) * Q.element_size() * 8 // bits, Kmat.data_ptr(),
-                               Kmat.stride(0) * Kmat.element_size() * 8 // bits, Kd, mask.handle, PREC[prec], flags,
-                               ctypes.byref(options), out.data_ptr(), _stream()), "mc_sddmm_ex")
-        return out
-    _check(lib.mc_sddmm_flags(Q.data_ptr(), Q.stride(0) * Q.element_size() * 8 // bits, Kmat.data_ptr(),
-                              Kmat.stride(0) * Kmat.element_size() * 8 // bits, Kd,
-                              mask.handle, PREC[prec], flags, out.data_ptr(), _stream()), "mc_sddmm_flags")
-    return out
-
-
-def sddmm_dequant(Q, Kmat, mask: SparseMatrix, prec: str, scale: float, out_dtype=torch.float32, out=None,
-                  lhs_unsigned: bool = False, rhs_unsigned: bool = False):
-    """scale * (Q * Kmat^T) at the mask's stored vectors as nvec*V fp32 or fp16 values (interchange order)."""
-    assert Q.is_cuda and Kmat.is_cuda and Q.dim() == 2 and Kmat.dim() == 2
-    assert Q.stride(1) == 1 and Kmat.stride(1) == 1 and Q.shape[1] == Kmat.shape[1]
-    bits = LHS_BITS[prec]
-    Kd = Q.shape[1] * Q.element_size() * 8 // bits
-    assert Q.element_size() == Kmat.element_size()
-    if out is None:
-        out = torch.empty(mask.nvec * mask.V, dtype=out_dtype, device=Q.device)
-    assert out.is_cuda and out.dtype == out_dtype and out.numel() == mask.nvec * mask.V and out.is_contiguous()
-    flags = (1 if lhs_unsigned else 0) | (2 if rhs_unsigned else 0)
-    _check(lib.mc_sddmm_dequant(Q.data_ptr(), Q.stride(0) * Q.element_size() * 8 // bits, Kmat.data_ptr(),
-                                Kmat.stride(0) * Kmat.element_size() * 8 // bits, Kd, mask.handle, PREC[prec], flags,
-                                float(scale), OUT_TYPE[out_dtype], out.data_ptr(), _stream()), "mc_sddmm_dequant")
-    return out
-
-
-def sddmm_to_mat(Q, Kmat, P: SparseMatrix, prec: str, scale: float) -> None:
-    """(Q * Kmat^T) at P's pattern, re-quantised to P's 8- or 16-bit integers and written into P's device values."""
-    assert Q.is_cuda and Kmat.is_cuda and Q.dim() == 2 and Kmat.dim() == 2
-    assert Q.stride(1) == 1 and Kmat.stride(1) == 1 and Q.shape[1] == Kmat.shape[1] and Q.element_size() == Kmat.element_size()
-    bits = LHS_BITS[prec]
-    Kd = Q.shape[1] * Q.element_size() * 8 // bits
-    _check(lib.mc_sddmm_to_mat(Q.data_ptr(), Q.stride(0) * Q.element_size() * 8 // bits, Kmat.data_ptr(),
-                               Kmat.stride(0) * Kmat.element_size() * 8 // bits, Kd, PREC[prec], float(scale), P.handle,
-                               _stream()), "mc_sddmm_to_mat")
-
-
-def absmax(x, out=None):
-    """max |x| of a contiguous fp32 device tensor, as a one-element device tensor."""
-    assert x.is_cuda and x.dtype == torch.float32 and x.is_contiguous()
-    if out is None:
-        out = torch.empty(1, dtype=torch.float32, device=x.device)
-    _check(lib.mc_absmax(x.data_ptr(), x.numel(), out.data_ptr(), _stream()), "mc_absmax")
-    return out
-
-
-def quantize(x, scale: float, bits: int = 8, out=None):
-    """Symmetric quantisation of a contiguous fp32 device tensor: int8 codes of the same shape, or
-    (bits=4) uint8 with half the last dimension, two codes per byte."""
-    assert x.is_cuda and x.dtype == torch.float32 and x.is_contiguous()
-    if out is None:
-        if bits == 4:
-            out = torch.empty(x.shape[:-1] + (x.shape[-1] // 2,), dtype=torch.uint8, device=x.device)
-        else:
-            out = torch.empty(x.shape, dtype=torch.int8, device=x.device)
-    assert out.is_cuda and out.is_contiguous()
-    if out.numel() * (2 if bits == 4 else 1) != x.numel() and bits in (4, 8):
-        raise MagicubeError(MC_EINVAL, "quantize(out size)")
-    _check(lib.mc_quantize(x.data_ptr(), x.numel(), float(scale), bits, out.data_ptr(), _stream()), "mc_quantize")
-    return out
-
-
-def sparse_softmax(mask: SparseMatrix, S, score_scale: float, inv_s_p: float, out=None, code_bits: int = 8):
-    """Integer codes (int8, or int16 for code_bits=16) of the row softmax over the stored
-    entries; S: (batch, nvec*V) int32."""
-    assert S.is_cuda and S.dtype == torch.int32 and S.is_contiguous()
-    n = mask.nvec * mask.V
-    S2 = S.reshape(-1, n) if n else S.reshape(S.shape[0] if S.dim() > 1 else 1, 0)
-    dt = torch.int16 if code_bits == 16 else torch.int8
-    if out is None:
-        out = torch.empty(S2.shape, dtype=dt, device=S.device)
-    assert out.is_cuda and out.dtype == dt and out.is_contiguous() and out.numel() == S2.numel()
-    _check(lib.mc_sparse_softmax_bits(mask.handle, S2.shape[0], S2.data_ptr(), score_scale, inv_s_p, code_bits,
-                                      out.data_ptr(), _stream()), "mc_sparse_softmax_bits")
-    return out.reshape(S.shape)
-
-
-def sparse_softmax_to_mat(P: SparseMatrix, S, score_scale: float, inv_s_p: float) -> None:
-    """Softmax of one score set (nvec*V int32) written as integer codes straight into P's device values."""
-    assert S.is_cuda and S.dtype == torch.int32 and S.is_contiguous() and S.numel() == P.nvec * P.V
-    _check(lib.mc_sparse_softmax_to_mat(P.handle, S.data_ptr(), float(score_scale), float(inv_s_p), _stream()),
-           "mc_sparse_softmax_to_mat")
-
-
 def attention_workspace_bytes(heads: int, mask: SparseMatrix, p_bits: int = 8) -> int:
     return int(lib.mc_attention_workspace_bytes_bits(heads, mask.handle, p_bits))
 
@@ -529,64 +406,3 @@ def attention_workspace_needed(heads: int, dk: int, mask: SparseMatrix, p_bits: 
 STATIC_SCRATCH_BYTES = 16 << 20
 
 
-def sparse_attention_static(Q8, K8, V8, mask: SparseMatrix, s_q, s_k, s_v, s_p, out, p_bits: int = 8, qkv_bits: int = 8,
-                            options: Options | None = None):
-    """sparse_attention for callers that cannot allocate: no workspace argument (the library's own per-GPU array
-    holds the intermediates) and a caller-provided ``out``.  This wrapper allocates nothing on the device either."""
-    epb = 8 // qkv_bits
-    batched = Q8.dim() == 4
-    batch = Q8.shape[0] if batched else 1
-    heads, L, dkb = Q8.shape[-3:]
-    dk = dkb * epb
-    st = tuple(x * epb for x in Q8.stride()[:-1])
-    bs, hs, ts = (st if batched else (0,) + st)
-    for t in (Q8, K8, V8):
-        assert t.is_cuda and t.element_size() == 1 and t.shape == Q8.shape and t.stride() == Q8.stride() and t.stride(-1) == 1
-    assert out.is_cuda and out.dtype in OUT_TYPE and out.shape == tuple(Q8.shape[:-1]) + (dk,) and out.stride() == st + (1,)
-    _check(lib.mc_sparse_attention_static(Q8.data_ptr(), K8.data_ptr(), V8.data_ptr(), batch, heads, L, dk, bs, hs, ts,
-                                          mask.handle, p_bits, qkv_bits, float(s_q), float(s_k), float(s_v), float(s_p),
-                                          OUT_TYPE[out.dtype], None if options is None else ctypes.byref(options),
-                                          out.data_ptr(), _stream()), "mc_sparse_attention_static")
-    return out
-
-
-def sparse_attention(Q8, K8, V8, mask: SparseMatrix, s_q, s_k, s_v, s_p, out=None, workspace=None,
-                     p_bits: int = 8, qkv_bits: int = 8, out_dtype=torch.float32, options: Options | None = None):
-    """Quantized sparse self-attention; Q8/K8/V8: (heads, L, dk) or (batch, heads, L, dk) int8
-    device tensors, or for qkv_bits=4 uint8 tensors of half the last dimension with two 4-bit
-    values per byte.  p_bits is the width of the re-quantised softmax output (8 or 16);
-    out_dtype is torch.float32 or torch.float16.
-
-    Any layout with unit stride along dk is accepted as long as the three tensors (and
-    ``out``) share it; a (heads, L, dk) view of a token-major (L, heads, dk) buffer, i.e.
-    ``x.permute(1, 0, 2)``, selects the fast two-heads-per-request path.
-    """
-    epb = 8 // qkv_bits                       # elements per byte
-    batched = Q8.dim() == 4
-    batch = Q8.shape[0] if batched else 1
-    heads, L, dkb = Q8.shape[-3:]
-    dk = dkb * epb
-    st = tuple(x * epb for x in Q8.stride()[:-1])     # strides in elements
-    bs, hs, ts = (st if batched else (0,) + st)
-    for t in (Q8, K8, V8):
-        assert t.is_cuda and t.element_size() == 1 and t.shape == Q8.shape and t.stride() == Q8.stride() and t.stride(-1) == 1
-    oshape = tuple(Q8.shape[:-1]) + (dk,)
-    if out is None:
-        out = torch.empty_strided(oshape, st + (1,), dtype=out_dtype, device=Q8.device)   # the inputs' layout
-    assert out.is_cuda and out.dtype == out_dtype and out.shape == oshape and out.stride() == st + (1,)
-    if workspace is None:
-        need = attention_workspace_needed(heads, dk, mask, p_bits, options)
-        workspace = torch.empty(need, dtype=torch.uint8, device=Q8.device) if need else None
-    ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.numel() * workspace.element_size())
-    assert workspace is None or (workspace.is_cuda and workspace.is_contiguous())
-    if options is not None:
-        _check(lib.mc_sparse_attention_ex(Q8.data_ptr(), K8.data_ptr(), V8.data_ptr(), batch, heads, L, dk, bs, hs, ts,
-                                          mask.handle, p_bits, qkv_bits, float(s_q), float(s_k), float(s_v), float(s_p),
-                                          OUT_TYPE[out_dtype], ctypes.byref(options), out.data_ptr(), ws_ptr, ws_bytes,
-                                          _stream()), "mc_sparse_attention_ex")
-        return out
-    _check(lib.mc_sparse_attention_out(Q8.data_ptr(), K8.data_ptr(), V8.data_ptr(), batch, heads, L, dk, bs, hs, ts,
-                                       mask.handle, p_bits, qkv_bits, float(s_q), float(s_k), float(s_v), float(s_p),
-                                       OUT_TYPE[out_dtype], out.data_ptr(), ws_ptr, ws_bytes, _stream()),
-           "mc_sparse_attention_out")
-    return out

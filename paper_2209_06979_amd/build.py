@@ -1,4 +1,5 @@
-"""Builds libmagicube.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc."""
+"""Builds libmagicube.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc, and the extension module _native (the
+Python binding's compute calls, host code) with the host compiler."""
 from __future__ import annotations
 
 import hashlib
@@ -65,6 +66,25 @@ def build_library(verbose: bool = False, jobs: int = 4) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     return LIB
+
+
+def build_extension(verbose: bool = False) -> str:
+    """Compiles csrc/python_calls.cpp against torch and the library (which must have been built)."""
+    import sysconfig
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    out = os.path.join(PKG, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           *(f"-I{d}" for d in (os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+                                sysconfig.get_paths()["include"], "/opt/rocm/include")),
+           os.path.join(CSRC, "python_calls.cpp"), "-o", out,
+           # torch's own libraries are in the process before this module is; libmagicube.so sits beside it
+           "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip",
+           "-L" + PKG, "-lmagicube", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return out
 
 
 _REMARK = re.compile(r"remark:\s+(.*?)\s*\[-Rpass-analysis=kernel-resource-usage\]")
@@ -174,6 +194,7 @@ def _wait(procs, verbose, table):
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_extension(verbose=True))
     if len(sys.argv) == 3 and sys.argv[1] == "--resources":
         # a copy of the per-kernel resource table (registers, scratch, LDS, occupancy) for the records
         with open(os.path.join(PKG, "_build", "kernel_resources_summary.txt")) as f, open(sys.argv[2], "w") as g:
