@@ -522,7 +522,7 @@ int mc_set_spmm_splitting(int enable);
  * pieces short enough to make 256 of them, again at least 8 chunks.) */
 /* SDDMM variant: -1 = automatic, 0 = the kernel that loads operands straight from memory
  * (any row length), 1, 2, 4 or 8 = waves per panel of the kernel that stages Kmat rows in
- * LDS (used when a row has 64, 128, 256, 512 or 1024 bytes, or 32 bytes of 4-bit values, else
+ * LDS (used for rows of up to 1024 bytes, else
  * ignored). */
 int mc_set_sddmm_variant(int waves);
 /* Softmax variant: 0 = automatic (panels of up to 4096 scores, padding included, are kept in

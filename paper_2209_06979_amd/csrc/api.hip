@@ -116,17 +116,19 @@ void free_device(mc_mat *A)
     }
 }
 
-// Waves per panel for SDDMM: enough to put about 2048 waves on the chip (4096 of the light ones
-// that stage rows of 32 bytes, or 64 bytes of nibbles), fewer than twice the chunks of an average panel.
+// Waves per panel for SDDMM: enough to put about 3200 waves on the chip (4096 of the light ones that stage rows of 32
+// bytes, or 64 bytes of nibbles), and no more than a panel has units of rows (64 of up to 128 bytes, 32 of 256, 16 beyond).
+// On 35 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count, 8 % once.
 int choose_sddmm_waves(const mc_mat *mask, int batch, int row_bytes, int bits, const mc_options &o)
 {
     if (o.sddmm_waves != 0) return o.sddmm_waves < 0 ? 0 : o.sddmm_waves; // 0 selects the direct-load kernel in launch_sddmm
     const double avg = mask->P ? (double)(mask->nslots / MC_CHUNK) / mask->P : 0.0;
+    const double units = avg * (row_bytes <= 128 ? 1 : (row_bytes <= 256 ? 2 : 4));
     const double groups = (double)mask->P * (batch > 0 ? batch : 1);
-    const double target = (row_bytes <= 32 || (bits == 4 && row_bytes <= 64)) ? 4096.0 : 2048.0;
+    const double target = (row_bytes <= 32 || (bits == 4 && row_bytes <= 64)) ? 4096.0 : 3200.0;
     int w = 1;
-    // (down to one chunk per wave, e.g. 32 panels of 7 chunks: 2.8 us with 4 waves, 2.4 us with 8)
-    while (w < 8 && groups * w * 2 <= target && w < avg) w *= 2;
+    // (down to one unit per wave, e.g. 32 panels of 7 chunks: 2.8 us with 4 waves, 2.4 us with 8)
+    while (w < 8 && groups * w * 2 <= target && w < units) w *= 2;
     return w;
 }
 

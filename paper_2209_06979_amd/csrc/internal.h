@@ -211,7 +211,7 @@ hipError_t launch_gather_probe(const SpmmArgs &a, int bnb, int waves, int32_t *s
 // `workgroups` x 4 waves x `iters` x 8 MFMAs (16x16x64 i8); sink: workgroups * 256 int32
 hipError_t launch_mfma_probe(int workgroups, int iters, int32_t *sink, hipStream_t s);
 // waves: 0 = the direct-load kernel; 1, 2, 4, 8 = waves per panel of the LDS-staged kernel
-// (used when a row has 64, 128, 256, 512 or 1024 bytes)
+// (used for rows of up to 1024 bytes)
 hipError_t launch_sddmm(int bits, const SddmmArgs &a, int waves, hipStream_t s);
 hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s);
 // waves: 2 or 4 per (panel, head); the longest padded panel must not exceed scores_softmax_max_npad(row_bytes, waves)

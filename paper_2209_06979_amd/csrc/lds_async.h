@@ -51,6 +51,13 @@ __device__ __forceinline__ void copy16_to_lds(const void *gbase_uniform, unsigne
                  : "memory", "m0");
 }
 
+// The same with a 64-bit address per lane (operands that may span 4 GiB and more).
+__device__ __forceinline__ void copy16_to_lds(const void *lane_address, unsigned lds_base)
+{
+    const unsigned base = __builtin_amdgcn_readfirstlane(lds_base);
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(lane_address), "s"(base) : "memory", "m0");
+}
+
 // Transposing 64-bit LDS read of 8-bit elements: inside each group of 16 lanes, lane l
 // receives byte (l % 8) of the 8-byte pieces addressed by lanes 2*t + l/8, t = 0..7.
 // With lanes 2t and 2t+1 pointing at the two 8-byte halves of a 16-byte row piece, lane l

@@ -9,18 +9,17 @@
 // both sides.  The waves of a workgroup take the panel's chunks of 64 vectors round-robin
 // and never have to meet: every chunk produces its own outputs.
 // Two kernels:
-//   sddmm_lds_kernel   rows of 64, 128, 256, 512 or 1024 bytes (sddmm_nib32_kernel: 32 bytes of nibbles): the 64 Kmat rows of a chunk are copied
+//   sddmm_staged_kernel rows of up to 1024 bytes (sddmm_nib32_kernel: 32 bytes of nibbles): Kmat rows are copied
 //                      from global memory straight into LDS with coalesced 16-byte pieces
 //                      (global_load_lds), then read as 128-bit MFMA operands; the
-//                      16-byte segments are XOR-swizzled against bank conflicts.  Rows longer
-//                      than 256 bytes pass through the stage 256 bytes at a time.
-//   sddmm_direct_kernel any row length: each lane loads its 16 operand bytes from memory.
+//                      16-byte segments are XOR-swizzled against bank conflicts.
+//   sddmm_direct_kernel longer rows: each lane loads its 16 operand bytes from memory.
 // int4 operands are widened in registers; int16 operands (L16-R16, Section 4.4) are split in
 // registers into signed byte planes, the two Q planes stacked in the MFMA rows 0..7 / 8..15.
 // The output is written in interchange (BCRS) order: V consecutive int32 per vector, or with the
 // fused dequantisation of Section 5.3 V consecutive fp32 / fp16 values.
 #include "internal.h"
-
+#include "lds_async.h"
 #include "sddmm_tile.h"
 
 namespace {
@@ -87,132 +86,179 @@ __device__ __forceinline__ void store_scores(const SddmmArgs &a, int64_t out0, i
 }
 
 
-// RB: bytes of a Kmat row staged per pass (64, 128, 256, 512; 16-bit operands: from 128); SEGS: passes
-// per chunk, a row has RB * SEGS bytes (the tiles' accumulators live across the passes, so long
-// rows need no more LDS than short ones).  WK: waves per workgroup.
+// LPR: 16-byte pieces (lanes) of a staged Kmat row: 4, 8, 16, 32 or 64; a row has at most that many and is always
+// fetched whole.  Pieces beyond its end are fetched from its start instead (a line that is on its way anyway), and the Q
+// operand is zero there, so they add nothing.
 // U: 8- or 4-bit operands of which one or both are read as non-negative values (Section 4.4.1); the
 // scheme is the one described at sddmm_unsigned_kernel below, here on rows staged in LDS.
-template <int PB, int RB, int SEGS, int WK, bool DQ, bool U>
-__global__ __launch_bounds__(64 * WK) void sddmm_lds_kernel(SddmmArgs a)
+//
+// The unit of work of a wave is 8 KB of rows: 64 vectors of up to 128 bytes, 32 of 256, 16 of 512 (4 KB for rows of 64
+// bytes, 16 KB for 1024).  What bounds the kernel on large masks is the number of 128-byte lines the gather asks L2 for
+// (about 3 clocks per line and compute unit), so a row is read in one go by neighbouring lanes: cut into pieces of 128 or
+// 256 bytes, a row that is not aligned to lines costs one more line per piece.  On small masks it is the chain row
+// numbers -> rows -> MFMA -> stores.  A unit's rows are copied straight into the wave's one stage of LDS; its operands
+// are then taken into registers, which frees the stage for the next unit's rows while the MFMAs and stores of this one
+// run (a second stage would halve the waves of a compute unit, staging through registers costs LDS writes: 2 - 8 % slower).
+// L8-R8, 4096 x 4096, V = 8, 90 % sparse, Kd = 256: 6.2 -> 5.9 us; 1224 x 7932, V = 4, 80 %, Kd = 464 58.7 -> 21.7 us, L16-R16,
+// 2000 x 3100, V = 4, 90 %, Kd = 200 13.6 -> 9.6 us (row lengths that the direct kernel used to take: there the lanes that read
+// one row are 16 apart and their requests are not combined, 9 TB/s of rows from L2 against 25 coalesced).
+template <int PB, int LPR, bool DQ, bool U>
+__global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
 {
-    constexpr int LPR = RB / 16, NI = LPR, RPI = 64 / LPR, KC = RB / StepBytes<PB>::value;
+    constexpr int RB = LPR * 16, NI = (LPR == 4) ? 4 : (LPR == 64 ? 16 : 8), RPI = 64 / LPR, UNIT = NI * RPI, TILES = UNIT / 16;
+    constexpr int KC = RB / StepBytes<PB>::value;
+    constexpr int SW = (LPR < 16) ? LPR : 16;       // pieces of a row that the swizzle permutes
     static_assert(KC >= 1, "a row must fill at least one MFMA step");
     static_assert(!U || PB == 8 || PB == 4, "unsigned operands: 4 and 8 bits");
     constexpr int QR = (U && PB == 4) ? 2 : 1; // registers per step of the Q operand (unsigned nibbles are widened once, up front)
-    __shared__ __attribute__((aligned(16))) char lds[WK * 64 * RB];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
     const int batch = blockIdx.y;
-    // a unit of work: a whole panel, or (masks with very unequal panels) a range of its chunks
-    int panel = blockIdx.x, cb = 0, ce = -1;
+    // a share of the mask: a whole panel, or (masks with very unequal panels) a range of its chunks
+    int panel = blockIdx.x, cb = 0, ce = INT32_MAX / MC_CHUNK;
     if (a.items) {
         const v4i it = *reinterpret_cast<const v4i *>(a.items + 4 * blockIdx.x);
         panel = it.x; cb = it.y; ce = it.z;
     }
-    const int s0 = a.panel_ptr[2 * panel], n = a.panel_ptr[2 * panel + 1] - s0;
-    if (ce < 0) ce = (n + MC_CHUNK - 1) / MC_CHUNK;
-    const int nch = ce - cb;
-    const int32_t *idx = a.slot_idx + s0 + cb * MC_CHUNK;
+    const v2i pp = *reinterpret_cast<const v2i *>(a.panel_ptr + 2 * panel);
+    const int s0 = pp.x, n = pp.y - s0;
+    // slots of the share (codes written into an operand's device format also cover the padded ones, with zeros)
+    const int n_all = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK : n;
+    const int first = cb * MC_CHUNK, end = min(n_all, ce * MC_CHUNK);
+    const int nunits = (end - first + UNIT - 1) / UNIT;
+    const int nmy = (nunits > w) ? (nunits - w + nw - 1) / nw : 0;
+    if (nmy == 0) return;
+    // piece i of a unit: lane (rg, seg) fetches piece seg of the row in slot rg*NI + i
+    const int32_t *idx = a.slot_idx + s0 + first + rg * NI;
+    v4i ixn[NI / 4];
+    auto load_idx = [&](int u) {
+#pragma unroll
+        for (int t = 0; t < NI / 4; ++t) ixn[t] = *reinterpret_cast<const v4i *>(idx + u * UNIT + 4 * t);
+    };
+    load_idx(w);
     const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)a.row_ptr[panel] * a.V;
     const uint8_t *Km = a.Kmat + (int64_t)batch * a.K_batch_stride;
-    char *stage = lds + w * (64 * RB);
 
-    v4i qf[KC * SEGS * QR];
+    v4i qf[KC * QR];
     const uint8_t *Qpanel = a.Q + (int64_t)batch * a.Q_batch_stride + (int64_t)panel * a.V * a.ldq_bytes;
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
     const v4i nib = {NIBBLE_HI, NIBBLE_HI, NIBBLE_HI, NIBBLE_HI};
     const int qx1 = (U && a.lhs_unsigned) ? (int)0x80808080 : 0, kx1 = (U && a.rhs_unsigned) ? (int)0x80808080 : 0;
     const v4i qx = {qx1, qx1, qx1, qx1}, kx = {kx1, kx1, kx1, kx1};
+    v4i raw_q[KC];
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) raw_q[kc] = load_q<PB>(Qpanel, a.ldq_bytes, a.V, a.row_bytes, kc, j, g);
+
+    // LDS: the row of slot s at byte (s % NI) * 1024 + (s / NI) * RB, its piece p at position p ^ swz(s): the 16 rows of a
+    // tile, read at one piece number by 16 lanes, spread over all banks
+    char *stage = lds + w * (UNIT * RB);
+    const unsigned stage_u = mcu::lds_addr_uniform(stage);
+    auto swz = [](int s) { return LPR < 16 ? (s ^ (s >> 3)) & (SW - 1) : s & 15; };
+    int off[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int p = seg ^ swz(rg * NI + i);
+        off[i] = p * 16 < a.row_bytes ? p * 16 : 0;
+    }
+    auto request = [&]() {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km + ((int64_t)ixn[i >> 2][i & 3] * a.ldk_bytes + off[i]), stage_u + i * 1024);
+    };
+    request();
+    if (nmy > 1) load_idx(w + nw);
+
     v4i rq = {0, 0, 0, 0}; // U: rows 4g .. 4g+3: sum over the reduction of the Q operand bytes
 #pragma unroll
-    for (int kc = 0; kc < KC * SEGS; ++kc) {
-        const v4i raw = load_q<PB>(Qpanel, a.ldq_bytes, a.V, RB * SEGS, kc, j, g);
+    for (int kc = 0; kc < KC; ++kc) {
         if (!U) {
-            qf[kc] = raw;
+            qf[kc] = raw_q[kc];
         } else {
             // rows of the panel: the operand bytes; MFMA row 8: all ones (it collects the sums of the Kmat
-            // operand bytes of every output column); other rows: zero
+            // operand bytes of every output column); other rows, and everything beyond the row end: zero
+            const bool in_row = kc * 64 + g * 16 < a.row_bytes;
 #pragma unroll
             for (int t = 0; t < QR; ++t) {
-                v4i q = (PB == 8) ? (raw ^ qx) : (((t == 0 ? (raw << 4) : raw) & nib) ^ qx);
+                v4i q = (PB == 8) ? (raw_q[kc] ^ qx) : (((t == 0 ? (raw_q[kc] << 4) : raw_q[kc]) & nib) ^ qx);
                 if (j >= a.V) q = (j == 8) ? ones : (v4i){0, 0, 0, 0};
+                if (!in_row) q = (v4i){0, 0, 0, 0};
                 qf[kc * QR + t] = q;
                 rq = __builtin_amdgcn_mfma_i32_16x16x64_i8(q, ones, rq, 0, 0, 0);
             }
         }
     }
-    const int nred = RB * SEGS * (PB == 4 ? 2 : 1);                      // reduction elements
+    const int nred = a.row_bytes * (PB == 4 ? 2 : 1);                    // reduction elements
     const int cqck = (U && a.lhs_unsigned && a.rhs_unsigned) ? (PB == 4 ? 64 : 16384) * nred : 0;
-    // load instruction i: lane (rg, seg) copies segment seg ^ i of the row (piece) in slot rg*NI + i
-    // to LDS row i*RPI + rg (byte i*1024 + lane*16 of the stage)
-    const int nmy = (nch > w) ? (nch - w + WK - 1) / WK : 0;
-    v4i idxv[NI / 4];
-    auto load_idx = [&](int c) {
-#pragma unroll
-        for (int t = 0; t < NI / 4; ++t) idxv[t] = *reinterpret_cast<const v4i *>(idx + c * MC_CHUNK + rg * NI + 4 * t);
-    };
-    if (nmy > 0) load_idx(w);
+
     for (int k = 0; k < nmy; ++k) {
-        const int c = w + k * WK;
-        v4i acc[4], acc2[4];
+        const int u = w + k * nw;
+        // This unit's rows have landed.  (Integer outputs: the TILES stores of the unit before were issued after this
+        // unit's copies -- only the last unit can have tiles without a store -- and need not be waited for.)
+        if (k == 0 || DQ) mcu::vm_wait<0>();
+        else mcu::vm_wait<TILES>();
+        // The operands of the whole unit first, so that the stage is free for the next unit's rows before the MFMAs (rows
+        // of 1024 bytes: their operands are more than the registers hold, they are read one by one).
+        constexpr int OPS = (PB == 16) ? 2 * KC : KC;
+        constexpr bool EARLY = LPR < 64;
+        v4i kt[TILES][OPS];
+        auto read_op = [&](int tl, int kc) -> v4i {
+            const int s = tl * 16 + j, i = s % NI;
+            const char *rowp = stage + i * 1024 + (s / NI) * RB;
+            const int p = (PB == 16) ? (kc >> 1) * 8 + 2 * g + (kc & 1) : kc * 4 + g;
+            return *reinterpret_cast<const v4i *>(rowp + (p ^ swz(s)) * 16);
+        };
+        auto next_unit = [&]() {
+            mcu::lgkm_wait();                       // the reads have returned: the stage may be overwritten
+            if (k + 1 < nmy) {
+                request();
+                if (k + 2 < nmy) load_idx(u + 2 * nw);
+            }
+        };
+        if (EARLY) {
 #pragma unroll
-        for (int h = 0; h < SEGS; ++h) {
-            if (h > 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the previous pass has been read
-            // (the column indices of this chunk are still needed by the later passes: the next
-            // chunk's may only be requested after the last pass has issued its copies)
+            for (int tl = 0; tl < TILES; ++tl)
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
-                __builtin_amdgcn_global_load_lds((gptr_t *)(Km + (int64_t)idxv[i >> 2][i & 3] * a.ldk_bytes + h * RB + ((seg ^ i) * 16)),
-                                                 (lptr_t *)(stage + i * 1024), 16, 0, 0);
-            const bool more = (h == SEGS - 1) && (k + 1 < nmy);
-            if (more) load_idx(c + WK);
-            if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI / 4) : "memory"); // rows landed, indices may still fly
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                for (int kc = 0; kc < OPS; ++kc) kt[tl][kc] = read_op(tl, kc);
+            next_unit();
+        }
 #pragma unroll
-            for (int tl = 0; tl < 4; ++tl) {
-                const int s = tl * 16 + j;              // slot within the chunk
-                const int i = s % NI, r = s / NI;       // its load instruction and row group
-                const char *rowp = stage + i * 1024 + r * RB;
-                if (h == 0) acc[tl] = acc2[tl] = (v4i){0, 0, 0, 0};
+        for (int tl = 0; tl < TILES; ++tl) {
+            v4i acc = {0, 0, 0, 0}, acc2 = {0, 0, 0, 0};
 #pragma unroll
-                for (int kc = 0; kc < KC; ++kc) {
-                    if (PB == 16) {
-                        const v4i x = *reinterpret_cast<const v4i *>(rowp + (((kc * 8 + 2 * g) ^ i) * 16));
-                        const v4i y = *reinterpret_cast<const v4i *>(rowp + (((kc * 8 + 2 * g + 1) ^ i) * 16));
-                        v4i kh, kl;
-                        split16(x, y, kh, kl);
-                        mma_step<PB>(qf[h * KC + kc], kh, kl, acc[tl], acc2[tl]);
-                    } else {
-                        const v4i kf = *reinterpret_cast<const v4i *>(rowp + (((kc * 4 + g) ^ i) * 16));
-                        if (!U) {
-                            mma_step<PB>(qf[h * KC + kc], kf, kf, acc[tl], acc2[tl]);
-                        } else if (PB == 8) {
-                            acc[tl] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[h * KC + kc], kf ^ kx, acc[tl], 0, 0, 0);
-                        } else {
-                            acc[tl] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[(h * KC + kc) * 2], ((kf << 4) & nib) ^ kx, acc[tl], 0, 0, 0);
-                            acc[tl] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[(h * KC + kc) * 2 + 1], (kf & nib) ^ kx, acc[tl], 0, 0, 0);
-                        }
-                    }
-                }
-                if (h == SEGS - 1) {
+            for (int kc = 0; kc < KC; ++kc) {
+                if (PB == 16) {
+                    v4i kh, kl;
+                    if (EARLY) split16(kt[tl][2 * kc], kt[tl][2 * kc + 1], kh, kl);
+                    else split16(read_op(tl, 2 * kc), read_op(tl, 2 * kc + 1), kh, kl);
+                    mma_step<PB>(qf[kc], kh, kl, acc, acc2);
+                } else {
+                    const v4i kf = EARLY ? kt[tl][kc] : read_op(tl, kc);
                     if (!U) {
-                        store_scores<DQ>(a, out0, s0, (cb + c) * MC_CHUNK + s, n, g, finish_tile<PB>(acc[tl], acc2[tl]));
+                        mma_step<PB>(qf[kc], kf, kf, acc, acc2);
+                    } else if (PB == 8) {
+                        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[kc], kf ^ kx, acc, 0, 0, 0);
                     } else {
-                        // sum (q'+cq)(k'+ck) = sum q'k' + ck sum q' + cq sum k' + cq ck n, with cq = ck = 128 in the
-                        // scale the operand bytes carry (nibbles: 16 x their value)
-                        v4i r = acc[tl];
-                        const int cs = __shfl(r[0], 32 + j); // MFMA row 8 (lane group 2, register 0) of this lane's column
-                        if (a.rhs_unsigned) r += rq << 7;
-                        if (a.lhs_unsigned) r += (v4i){cs << 7, cs << 7, cs << 7, cs << 7};
-                        if (PB == 4) r = r >> 8;
-                        r += (v4i){cqck, cqck, cqck, cqck};
-                        store_scores<DQ>(a, out0, s0, (cb + c) * MC_CHUNK + s, n, g, r);
+                        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[kc * 2], ((kf << 4) & nib) ^ kx, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[kc * 2 + 1], (kf & nib) ^ kx, acc, 0, 0, 0);
                     }
                 }
             }
+            if (!EARLY) next_unit();                // (a unit of these is one tile)
+            const int slot = first + u * UNIT + tl * 16 + j;
+            if (!U) {
+                store_scores<DQ>(a, out0, s0, slot, n, g, finish_tile<PB>(acc, acc2));
+            } else {
+                // sum (q'+cq)(k'+ck) = sum q'k' + ck sum q' + cq sum k' + cq ck n, with cq = ck = 128 in the
+                // scale the operand bytes carry (nibbles: 16 x their value)
+                const int cs = __shfl(acc[0], 32 + j); // MFMA row 8 (lane group 2, register 0) of this lane's column
+                if (a.rhs_unsigned) acc += rq << 7;
+                if (a.lhs_unsigned) acc += (v4i){cs << 7, cs << 7, cs << 7, cs << 7};
+                if (PB == 4) acc = acc >> 8;
+                acc += (v4i){cqck, cqck, cqck, cqck};
+                store_scores<DQ>(a, out0, s0, slot, n, g, acc);
+            }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // reads done before the rows are overwritten
     }
 }
 
@@ -220,7 +266,7 @@ __global__ __launch_bounds__(64 * WK) void sddmm_lds_kernel(SddmmArgs a)
 // reduction elements of a row fill the step exactly when lane groups 0 and 1 take the even elements
 // of the two 16-byte pieces (low nibbles, shifted up) and groups 2 and 3 the odd ones (high nibbles),
 // on both operand sides: sums do not depend on the order of their terms.  Both operands carry a
-// factor 16.  Staging as in sddmm_lds_kernel: copy instruction i (of 2) brings the rows of the
+// factor 16.  Staging as in sddmm_staged_kernel: copy instruction i (of 2) brings the rows of the
 // slots 2*rg + i, rg = lane / 2, into LDS rows i*32 + rg, pieces XOR-swizzled with i.
 template <int WK, bool DQ, bool U>
 __global__ __launch_bounds__(64 * WK) void sddmm_nib32_kernel(SddmmArgs a)
@@ -495,17 +541,12 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs a)
 
 } // namespace
 
-template <int PB, int RB, int SEGS, bool DQ, bool U> hipError_t launch_sddmm_lds(const SddmmArgs &a, int waves, hipStream_t s)
+template <int PB, int LPR, bool DQ, bool U> hipError_t launch_staged(const SddmmArgs &a, int waves, hipStream_t s)
 {
     dim3 grid((unsigned)(a.items ? a.n_units : a.P), (unsigned)a.batch);
-    constexpr int MAXW = (64 * RB * 8 <= 65536) ? 8 : ((64 * RB * 4 <= 65536) ? 4 : 2); // 64 KB of stages per workgroup
-    if (waves > MAXW) waves = MAXW;
-    switch (waves) {
-    case 1: hipLaunchKernelGGL((sddmm_lds_kernel<PB, RB, SEGS, 1, DQ, U>), grid, dim3(64), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((sddmm_lds_kernel<PB, RB, SEGS, 2, DQ, U>), grid, dim3(128), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((sddmm_lds_kernel<PB, RB, SEGS, (MAXW < 4 ? MAXW : 4), DQ, U>), grid, dim3(64 * (MAXW < 4 ? MAXW : 4)), 0, s, a); break;
-    default: hipLaunchKernelGGL((sddmm_lds_kernel<PB, RB, SEGS, MAXW, DQ, U>), grid, dim3(64 * MAXW), 0, s, a); break;
-    }
+    constexpr int STAGE = (LPR == 4) ? 4096 : (LPR == 64 ? 16384 : 8192);
+    if (LPR == 64 && waves > 4) waves = 4;      // 64 KB of stages per workgroup
+    hipLaunchKernelGGL((sddmm_staged_kernel<PB, LPR, DQ, U>), grid, dim3(64 * waves), waves * STAGE, s, a);
     return hipGetLastError();
 }
 
@@ -524,13 +565,12 @@ template <int PB, bool DQ, bool U> hipError_t launch_sddmm_bits(const SddmmArgs 
                 return hipGetLastError();
             }
         }
-        if (a.row_bytes == 64 && PB != 16) return launch_sddmm_lds<(PB == 16 ? 8 : PB), 64, 1, DQ, U>(a, waves, s);
-        if (a.row_bytes == 128) return launch_sddmm_lds<PB, 128, 1, DQ, U>(a, waves, s);
-        if (a.row_bytes == 256) return launch_sddmm_lds<PB, 256, 1, DQ, U>(a, waves, s);
-        // longer rows go through the stage in passes of 256 bytes: four waves per workgroup still fit
-        // (a 512-byte stage leaves room for two; measured 15.6 -> 12.0 us for 16-bit operands at Kd = 256)
-        if (a.row_bytes == 512) return launch_sddmm_lds<PB, 256, 2, DQ, U>(a, waves, s);
-        if (a.row_bytes == 1024) return launch_sddmm_lds<PB, 256, 4, DQ, U>(a, waves, s);
+        // the narrowest stage that holds the row
+        if (a.row_bytes <= 64 && PB != 16) return launch_staged<(PB == 16 ? 8 : PB), 4, DQ, U>(a, waves, s);
+        if (a.row_bytes <= 128) return launch_staged<PB, 8, DQ, U>(a, waves, s);
+        if (a.row_bytes <= 256) return launch_staged<PB, 16, DQ, U>(a, waves, s);
+        if (a.row_bytes <= 512) return launch_staged<PB, 32, DQ, U>(a, waves, s);
+        if (a.row_bytes <= 1024) return launch_staged<PB, 64, DQ, U>(a, waves, s);
     }
     dim3 grid((unsigned)(a.items ? a.n_units : a.P), (unsigned)a.batch), block(64 * SDDMM_WAVES);
     if constexpr (U) {
