@@ -145,7 +145,8 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
     const uint8_t *Qpanel = a.Q + (int64_t)batch * a.Q_batch_stride + (int64_t)panel * a.V * a.ldq_bytes;
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
     const v4i nib = {NIBBLE_HI, NIBBLE_HI, NIBBLE_HI, NIBBLE_HI};
-    const int qx1 = (U && a.lhs_unsigned) ? (int)0x80808080 : 0, kx1 = (U && a.rhs_unsigned) ? (int)0x80808080 : 0;
+    int qx1 = (U && a.lhs_unsigned) ? (int)0x80808080 : 0, kx1 = (U && a.rhs_unsigned) ? (int)0x80808080 : 0;
+    if (U) asm("" : "+v"(qx1), "+v"(kx1));
     const v4i qx = {qx1, qx1, qx1, qx1}, kx = {kx1, kx1, kx1, kx1};
     v4i raw_q[KC];
 #pragma unroll
@@ -163,13 +164,17 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
         off[i] = p * 16 < a.row_bytes ? p * 16 : 0;
     }
     auto request = [&]() {
+        unsigned to = stage_u;
+        if (U && LPR == 64) asm("" : "+s"(to)); // (sixteen places kept in scalar registers would be spilled)
 #pragma unroll
-        for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km + ((int64_t)ixn[i >> 2][i & 3] * a.ldk_bytes + off[i]), stage_u + i * 1024);
+        for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km + ((int64_t)ixn[i >> 2][i & 3] * a.ldk_bytes + off[i]), to + i * 1024);
     };
     request();
     if (nmy > 1) load_idx(w + nw);
 
     v4i rq = {0, 0, 0, 0}; // U: rows 4g .. 4g+3: sum over the reduction of the Q operand bytes
+    int ones8 = (j == 8) ? 0x01010101 : 0, of_panel = (j < a.V) ? -1 : 0;
+    asm("" : "+v"(ones8), "+v"(of_panel));
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
         if (!U) {
@@ -177,19 +182,22 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
         } else {
             // rows of the panel: the operand bytes; MFMA row 8: all ones (it collects the sums of the Kmat
             // operand bytes of every output column); other rows, and everything beyond the row end: zero
-            const bool in_row = kc * 64 + g * 16 < a.row_bytes;
+            // (bit masks in vector registers: as conditions they would take two scalar registers per step)
+            int row1 = (kc * 64 + g * 16 - a.row_bytes) >> 31;
+            asm("" : "+v"(row1));
+            const int keep1 = row1 & of_panel, one1 = row1 & ones8;
+            const v4i keep = {keep1, keep1, keep1, keep1}, one = {one1, one1, one1, one1};
 #pragma unroll
             for (int t = 0; t < QR; ++t) {
-                v4i q = (PB == 8) ? (raw_q[kc] ^ qx) : (((t == 0 ? (raw_q[kc] << 4) : raw_q[kc]) & nib) ^ qx);
-                if (j >= a.V) q = (j == 8) ? ones : (v4i){0, 0, 0, 0};
-                if (!in_row) q = (v4i){0, 0, 0, 0};
+                const v4i q = (((PB == 8) ? (raw_q[kc] ^ qx) : (((t == 0 ? (raw_q[kc] << 4) : raw_q[kc]) & nib) ^ qx)) & keep) | one;
                 qf[kc * QR + t] = q;
                 rq = __builtin_amdgcn_mfma_i32_16x16x64_i8(q, ones, rq, 0, 0, 0);
             }
         }
     }
     const int nred = a.row_bytes * (PB == 4 ? 2 : 1);                    // reduction elements
-    const int cqck = (U && a.lhs_unsigned && a.rhs_unsigned) ? (PB == 4 ? 64 : 16384) * nred : 0;
+    int cqck = (U && a.lhs_unsigned && a.rhs_unsigned) ? (PB == 4 ? 64 : 16384) * nred : 0;
+    if (U) asm("" : "+v"(cqck)); // (scalar registers are scarce here)
 
     for (int k = 0; k < nmy; ++k) {
         const int u = w + k * nw;
