@@ -95,14 +95,15 @@ typedef struct mc_options {
     int spmm_splitting;      /* 0 automatic (very unequal panels are cut into work items, see
                                 mc_set_spmm_splitting), -1 never, 1 as 0 and also in the last SpMM of the
                                 attention layer's kernel pipeline (see mc_attention_workspace_needed)      */
-    int spmm_slab;           /* the SpMM form that keeps blocks of B resident in LDS and reads the gathered
-                                rows from there: 0 automatic (when it is expected to be faster: dense
-                                matrices), -1 never (also: mc_mat_create on this thread does not build the
-                                K-blocked copy of the operand that form needs), 1 whenever the operand has
-                                that copy and the precision has an 8- or 4-bit B without unsigned flags    */
-    int spmm_slab_waves;     /* that form's computing waves per workgroup: 0 automatic, else 1 .. 15           */
-    int spmm_slab_panels;    /* that form's panels per computing wave: 0 automatic, else 1, 2 or 4 (4 only with
-                                an 8-bit B)                                                                */
+    int spmm_slab;           /* the SpMM form that keeps rows of B resident in LDS and reads the gathered
+                                rows from there: 0 automatic (when it is expected to be faster: many stored
+                                vectors per row of B), -1 never (also: mc_mat_create on this thread does not
+                                build the LDS-ordered copy of the operand that form needs), 1 whenever the
+                                operand has that copy and the precision has an 8- or 4-bit B without
+                                unsigned flags                                                             */
+    int spmm_slab_waves;     /* that form's waves per workgroup: 0 automatic, else 1 .. 15                     */
+    int spmm_slab_panels;    /* 0, 1, 2 or 4: accepted, without effect (a wave keeps as many panels in flight
+                                as the operand's number of columns asks for)                               */
     int sddmm_waves;         /* 0 automatic, -1 the kernel that loads operands straight from memory,
                                 1, 2, 4 or 8 waves per panel of the kernel that stages Kmat rows in LDS   */
     int softmax_variant;     /* 0 automatic, 1 a workgroup per panel also for short panels, 2 always the
@@ -271,7 +272,7 @@ int mc_spmm_flags(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec pr
 int mc_spmm_ex(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, unsigned flags,
                const mc_options *options, int32_t *C_dev, int ldc, void *stream);
 /* Which form mc_spmm_ex would run for this operand, width and options (host only, launches nothing):
- * bit 0: 0 = rows of B gathered per stored vector, 1 = K-blocks of B resident in LDS; bit 1 (value 2): on the
+ * bit 0: 0 = rows of B gathered per stored vector, 1 = rows of B resident in LDS; bit 1 (value 2): on the
  * operand's merged copy (see mc_merge_host).  Negative: an error code. */
 int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_options *options);
 

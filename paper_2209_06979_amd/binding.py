@@ -344,7 +344,7 @@ def set_attention_mode(mode: int = 0) -> None:
 
 
 def spmm_form(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> str:
-    """The form mc_spmm_ex would take for this operand: "gather" or "lds" (K-blocks of B resident in LDS)."""
+    """The form mc_spmm_ex would take for this operand: "gather" or "lds" (rows of B resident in LDS)."""
     r = lib.mc_spmm_form(A.handle, N, PREC[prec], ctypes.byref(options) if options is not None else None)
     if r < 0:
         _check(r, "mc_spmm_form")

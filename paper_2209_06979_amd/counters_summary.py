@@ -26,7 +26,7 @@ def bench_name(kernel: str):
     m = re.search(r"spmm_kernel<\s*\d+,\s*\d+,\s*(\d+),\s*(\d+)", kernel)
     if m:
         return f"spmm_L{m.group(1)}R{m.group(2)}"
-    m = re.search(r"spmm_slab_kernel<\s*\d+,\s*(\d+),\s*(true|false|0|1)", kernel)
+    m = re.search(r"spmm_resident_kernel<\s*(\d+),\s*(true|false|0|1)", kernel)
     if m:
         return f"spmm_L{m.group(1)}R{'4' if m.group(2) in ('true', '1') else '8'}"
     m = re.search(r"sddmm_\w*kernel<\s*(\d+)", kernel)

@@ -103,9 +103,11 @@ void free_device(mc_mat *A)
     if (A->d_items) (void)hipFree(A->d_items);
     if (A->d_split_panels) (void)hipFree(A->d_split_panels);
     if (A->d_blk_ptr) (void)hipFree(A->d_blk_ptr);
-    if (A->d_blk_rows) (void)hipFree(A->d_blk_rows);
-    if (A->d_blk_vals) (void)hipFree(A->d_blk_vals);
+    if (A->d_blk_recs) (void)hipFree(A->d_blk_recs);
+    if (A->d_blk_ends) (void)hipFree(A->d_blk_ends);
     if (A->d_blk_src) (void)hipFree(A->d_blk_src);
+    if (A->d_order) (void)hipFree(A->d_order);
+    if (A->d_splits) (void)hipFree(A->d_splits);
     if (A->d_class_panels) (void)hipFree(A->d_class_panels);
     if (A->d_merge_src) (void)hipFree(A->d_merge_src);
     if (A->d_merge_vals) (void)hipFree(A->d_merge_vals);
@@ -280,6 +282,90 @@ extern "C" int mc_set_attention_mode(int mode)
 }
 
 namespace {
+// Work split of the SpMM that keeps rows of B resident in LDS, and its expected time.
+struct SlabPlan { int nt, ntiles, groups, wpp, waves; double us; };
+
+int resident_end_words(const mc_mat *A) { return (int)((A->blk_chunks + 31) / 32 + 2); }
+int resident_rec_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V * (A->lhs_bits == 12 ? 16 : A->lhs_bits) / 8; }
+
+// Expected times in us of the two forms of the SpMM, fitted (least squares on the logarithm) to 470 drawn operands: all
+// precisions but 16 x 16 bits, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B of 32 .. 1024
+// bytes, half to 97 % empty, a quarter of them with panels of unequal length.  They are good to 15 %; picking the form
+// by them costs 3 % over always picking the best of the four (merged or not, resident or gathered).
+// Resident: launch and start; per K-block and pass the fill, a line of B per row; per step of a wave (16 waves a unit,
+// each as slow as the SIMD's issue makes it, see the kernel) a fixed part and one per MFMA; the epilogues; the stores.
+// (A: the operand's layout figures are enough, its copies need not exist yet)
+void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_options &o, SlabPlan *pl)
+{
+    pl->us = 1e30;
+    const double lists = (double)A->blk_chunks / A->P;               // chunks of a panel over all its blocks
+    const double store_us = (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes * 0.15e-6;
+    for (int nt = A->nblk == 1 ? A->blk_nt : 2; nt >= 2; nt -= 2) {
+        SlabPlan q;
+        q.nt = nt;
+        q.ntiles = (row_bytes + 16 * nt - 1) / (16 * nt);
+        // one workgroup per compute unit; the tiles of a group share an XCD (32 compute units)
+        q.groups = 8 * std::max(1, 32 / q.ntiles);
+        if (q.groups > A->P) q.groups = A->P;
+        const int in_group = (A->P + q.groups - 1) / q.groups;
+        q.waves = o.spmm_slab_waves ? o.spmm_slab_waves : 16;
+        q.wpp = 1;
+        if (A->nblk == 1 && !o.spmm_slab_waves)
+            while (q.wpp < 8 && in_group * q.wpp * 2 <= q.waves && q.wpp * 2 <= lists) q.wpp *= 2;
+        const int rounds = ((q.groups + 7) / 8 * q.ntiles + 31) / 32;
+        const int passes = A->nblk == 1 ? 1 : (in_group + q.waves * (r4 ? 4 : 8) - 1) / (q.waves * (r4 ? 4 : 8));
+        // steps of the busiest wave: whole panels, or, where panels are unequal, a fair share
+        double steps;
+        if (A->nblk > 1) steps = (in_group + q.waves - 1) / q.waves * std::max(lists, 2.0 * A->nblk);
+        else if (A->uniform_chunks && in_group >= q.waves) steps = (in_group + q.waves - 1) / q.waves * lists;
+        else if (in_group >= q.waves) steps = in_group * lists / q.waves;
+        else steps = lists / q.wpp;
+        const int mfma = nt * (r4 ? 2 : 1);
+        const double fill_us = passes * A->nblk * (2.1 + A->block_rows * 0.65e-3);
+        // (in blocks: a step waits for its own reads, and every panel of a wave costs a start in each block)
+        const double walk_us = A->nblk > 1 ? steps * (r4 ? 0.17 : 0.21) + (in_group + q.waves - 1) / q.waves * 3.2
+                                           : steps * (0.105 + (r4 ? 0.039 : 0.028) * mfma) + in_group * mfma * (0.13 / 16);
+        q.us = 3.1 + rounds * (fill_us + walk_us) + store_us;
+        if (q.us < pl->us) *pl = q;
+    }
+}
+
+// Gathered: launch and start; the gathered bytes (a row that is no whole number of 128-byte lines touches more of them);
+// the stores; the chain of the longest unit of work; the launch that clears rows when panels are cut into items.
+double gather_us(const mc_mat *A, int row_bytes, bool r4, int out_bytes)
+{
+    const bool items = A->n_items && out_bytes == 4;
+    const double gathered = (double)A->nvec * (row_bytes + (row_bytes % 128 ? 14 : 0)) * (r4 ? 0.102e-6 : 0.0754e-6);
+    return 3.15 + gathered + (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes * 0.18e-6 +
+           0.059 * (items ? A->max_item_chunks : A->max_panel_chunks) + (items ? 3.1 : 0.0);
+}
+
+// Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines.
+bool resident_worth_building(const mc_mat *A)
+{
+    const mc_options automatic = {};
+    for (int row_bytes : {1024, 512, 256, 128}) {
+        for (int r4 = (A->lhs_bits == 4); r4 < 2; ++r4) {
+            SlabPlan pl;
+            plan_slab(A, row_bytes, r4, 4, automatic, &pl);
+            double best = gather_us(A, row_bytes, r4, 4);
+            if (A->merged) {
+                best = std::min(best, gather_us(A->merged, row_bytes, r4, 4));
+                if (A->merged->d_blk_recs) {
+                    SlabPlan m;
+                    plan_slab(A->merged, row_bytes, r4, 4, automatic, &m);
+                    best = std::min(best, m.us);
+                }
+            }
+            if (pl.us < 0.98 * best) return true;
+        }
+    }
+    return false;
+}
+
+} // namespace
+
+namespace {
 // Whether mc_mat_create builds the merged copy (lay: the operand, ml: its merged form).  The copy holds
 // ml.nvec * rows values; which of the two a call uses is decided per call (merged_pays).
 bool merged_worth_building(const mc_layout &lay, const mc_merged_layout &ml, int V)
@@ -330,8 +416,8 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     A->d_items = A->d_split_panels = nullptr;
     A->n_items = A->n_split = 0;
     A->max_item_chunks = 0;
-    A->nblk = 0; A->blk_chunks = 0; A->blk_valid = false;
-    A->d_blk_ptr = nullptr; A->d_blk_rows = nullptr; A->d_blk_vals = nullptr; A->d_blk_src = nullptr;
+    A->blk_nt = A->block_rows = A->nblk = 0; A->blk_chunks = 0; A->blk_valid = false; A->d_order = A->d_splits = nullptr;
+    A->d_blk_ptr = nullptr; A->d_blk_recs = nullptr; A->d_blk_ends = nullptr; A->d_blk_src = nullptr;
     A->d_class_panels = nullptr;
     A->merged = nullptr; A->merge_group = 0; A->d_merge_src = nullptr; A->d_merge_vals = nullptr; A->merged_valid = false;
     // Length classes of the panels (V = 8: the attention kernel gives a panel 1, 2, 4 or 8 waves)
@@ -406,76 +492,6 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             for (size_t i = 0; i < items.size(); i += 4) A->max_item_chunks = std::max(A->max_item_chunks, items[i + 2] - items[i + 1]);
         }
     }
-    // K-blocked copy for the SpMM that keeps blocks of B resident in LDS: for operands with values whose
-    // panels are about equally long and dense enough that the per-(panel, block) padding stays moderate
-    // (at most half as many slots again as there are vectors), unless the thread's options rule that kernel out.
-    std::vector<int32_t> blk_ptr, blk_src;
-    std::vector<uint16_t> blk_rows;
-    std::vector<uint8_t> blk_vals;
-    if (lhs_bits != 0 && lay.nvec > 0 && (A->n_items == 0 || t_options.spmm_slab == 1) && t_options.spmm_slab != -1) {
-        mc_blocked_layout bl;
-        // (spmm_slab == 1 on the creating thread: built whatever the shape, so that the form can be forced)
-        const bool forced = t_options.spmm_slab == 1;
-        if (mc_blocked_query_wide(M, K, V, lhs_bits, row_ptr, col_idx, &bl) == MC_OK && bl.nblk <= 63 && bl.nchunks > 0 &&
-            (forced || ((double)lay.nvec >= 160.0 * lay.P * bl.nblk && // (below about 160 vectors per list the form never won)
-                        bl.nchunks * MC_CHUNK <= lay.nvec + lay.nvec / 2 &&
-                        A->max_panel_chunks <= 2.0 * (double)(lay.nslots / MC_CHUNK) / lay.P + 1.0))) {
-            try {
-                blk_ptr.resize((size_t)lay.P * bl.nblk + 1);
-                blk_rows.resize((size_t)bl.nchunks * MC_CHUNK);
-                blk_src.resize((size_t)bl.nchunks * MC_CHUNK);
-                blk_vals.resize((size_t)bl.vals_bytes);
-            } catch (const std::bad_alloc &) {
-                delete A;
-                return MC_ENOMEM;
-            }
-            rc = mc_pack_blocked_host_wide(M, K, V, lhs_bits, row_ptr, col_idx, values, blk_ptr.data(), blk_rows.data(),
-                                           blk_vals.data(), blk_src.data());
-            if (rc != MC_OK) {
-                delete A;
-                return rc;
-            }
-            A->nblk = bl.nblk;
-            A->blk_chunks = bl.nchunks;
-        }
-    }
-    hipStream_t s = static_cast<hipStream_t>(stream);
-#define MC_TRY(call) (ok = ok && hip_ok((call), #call))
-    bool ok = true;
-    MC_TRY(hipGetDevice(&A->device));
-    // the index array gets one spare chunk so that 16-byte index reads never leave it
-    MC_TRY(hipMalloc(&A->d_panel_ptr, sizeof(int32_t) * 2 * (size_t)(lay.P + 1)));
-    MC_TRY(hipMalloc(&A->d_row_ptr, sizeof(int32_t) * (size_t)(lay.P + 1)));
-    MC_TRY(hipMalloc(&A->d_slot_idx, sizeof(int32_t) * (size_t)(lay.nslots + MC_CHUNK)));
-    if (lay.vals_bytes) MC_TRY(hipMalloc(&A->d_vals, (size_t)lay.vals_bytes));
-    MC_TRY(hipMemcpyAsync(A->d_panel_ptr, panel_ptr.data(), sizeof(int32_t) * 2 * (size_t)lay.P, hipMemcpyHostToDevice, s));
-    MC_TRY(hipMemcpyAsync(A->d_row_ptr, row_ptr, sizeof(int32_t) * (size_t)(lay.P + 1), hipMemcpyHostToDevice, s));
-    if (lay.nslots)
-        MC_TRY(hipMemcpyAsync(A->d_slot_idx, slot_idx.data(), sizeof(int32_t) * (size_t)lay.nslots, hipMemcpyHostToDevice, s));
-    if (lay.vals_bytes)
-        MC_TRY(hipMemcpyAsync(A->d_vals, vals.data(), (size_t)lay.vals_bytes, hipMemcpyHostToDevice, s));
-    if (A->n_items) {
-        MC_TRY(hipMalloc(&A->d_items, sizeof(int32_t) * items.size()));
-        MC_TRY(hipMalloc(&A->d_split_panels, sizeof(int32_t) * split_panels.size()));
-        MC_TRY(hipMemcpyAsync(A->d_items, items.data(), sizeof(int32_t) * items.size(), hipMemcpyHostToDevice, s));
-        MC_TRY(hipMemcpyAsync(A->d_split_panels, split_panels.data(), sizeof(int32_t) * split_panels.size(),
-                              hipMemcpyHostToDevice, s));
-    }
-    if (A->blk_chunks) {
-        MC_TRY(hipMalloc(&A->d_blk_ptr, sizeof(int32_t) * blk_ptr.size()));
-        MC_TRY(hipMalloc(&A->d_blk_rows, sizeof(uint16_t) * blk_rows.size()));
-        MC_TRY(hipMalloc(&A->d_blk_src, sizeof(int32_t) * blk_src.size()));
-        MC_TRY(hipMalloc(&A->d_blk_vals, blk_vals.size()));
-        MC_TRY(hipMemcpyAsync(A->d_blk_ptr, blk_ptr.data(), sizeof(int32_t) * blk_ptr.size(), hipMemcpyHostToDevice, s));
-        MC_TRY(hipMemcpyAsync(A->d_blk_rows, blk_rows.data(), sizeof(uint16_t) * blk_rows.size(), hipMemcpyHostToDevice, s));
-        MC_TRY(hipMemcpyAsync(A->d_blk_src, blk_src.data(), sizeof(int32_t) * blk_src.size(), hipMemcpyHostToDevice, s));
-        MC_TRY(hipMemcpyAsync(A->d_blk_vals, blk_vals.data(), blk_vals.size(), hipMemcpyHostToDevice, s));
-        A->blk_valid = true;
-    }
-    if (!class_panels.empty()) {
-        MC_TRY(hipMalloc(&A->d_class_panels, sizeof(int32_t) * class_panels.size()));
-        MC_TRY(hipMemcpyAsync(A->d_class_panels, class_panels.data(), sizeof(int32_t) * class_panels.size(), hipMemcpyHostToDevice, s));
-    }
     // Merged copy for the SpMM: panels of fewer rows than the matrix unit takes share one panel of 16 rows (4- and
     // 8-bit values) or 8 rows (two byte planes), see mc_merge_host.  Not for operands without vectors, and not
     // when the thread's options rule it out.
@@ -512,6 +528,95 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             A->merge_group = group;
             m_vals_bytes = (int64_t)m_values.size();
         }
+    }
+    // LDS-ordered copy for the SpMM that keeps rows of B resident in LDS, where that form is expected to be the fastest one
+    // for some width of B (the merged copy's forms included), unless the thread's options rule that kernel out (1: built whatever the shape, so that the
+    // form can be forced).
+    std::vector<int32_t> blk_ptr, blk_src, order, splits;
+    std::vector<uint8_t> blk_recs;
+    std::vector<uint32_t> blk_ends;
+    if (lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_slab != -1) {
+        ResidentLayout rl;
+        mc_resident_query(K, lay.P, row_ptr, col_idx, &rl);
+        A->blk_nt = rl.nt; A->block_rows = rl.block_rows; A->nblk = rl.nblk; A->blk_chunks = rl.nchunks;
+        if (rl.nchunks * MC_CHUNK <= INT32_MAX && (t_options.spmm_slab == 1 || resident_worth_building(A))) {
+            try {
+                blk_ptr.resize((size_t)lay.P * rl.nblk + 1);
+                blk_src.resize((size_t)rl.nchunks * MC_CHUNK);
+                blk_ends.resize((size_t)resident_end_words(A));
+                blk_recs.resize((size_t)((rl.nchunks + RESIDENT_AHEAD) * resident_rec_bytes(A))); // (readers run ahead of the end)
+                if (A->uniform_chunks == 0 && rl.nblk > 1) {
+                    order.resize((size_t)lay.P);
+                    for (int p = 0; p < lay.P; ++p) order[(size_t)p] = p;
+                    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return row_ptr[x + 1] - row_ptr[x] > row_ptr[y + 1] - row_ptr[y]; });
+                }
+                rc = mc_resident_pack(K, V, lhs_bits, lay.P, row_ptr, col_idx, values, rl, blk_ptr.data(), blk_recs.data(), blk_src.data(), blk_ends.data());
+                if (A->uniform_chunks == 0 && rl.nblk == 1) {
+                    splits.resize(RESIDENT_SPLITS + 1);
+                    for (int i = 0, p = 0; i <= RESIDENT_SPLITS; ++i) {
+                        const int64_t want = rl.nchunks * i / RESIDENT_SPLITS;
+                        while (p < lay.P && (blk_ptr[(size_t)p] < want || (i == RESIDENT_SPLITS))) ++p;
+                        splits[(size_t)i] = p;
+                    }
+                }
+            } catch (const std::bad_alloc &) {
+                free_device(A);
+                delete A;
+                return MC_ENOMEM;
+            }
+            if (rc != MC_OK) {
+                free_device(A);
+                delete A;
+                return rc;
+            }
+        } else {
+            A->nblk = 0; A->blk_chunks = 0;
+        }
+    }
+    hipStream_t s = static_cast<hipStream_t>(stream);
+#define MC_TRY(call) (ok = ok && hip_ok((call), #call))
+    bool ok = true;
+    MC_TRY(hipGetDevice(&A->device));
+    // the index array gets one spare chunk so that 16-byte index reads never leave it
+    MC_TRY(hipMalloc(&A->d_panel_ptr, sizeof(int32_t) * 2 * (size_t)(lay.P + 1)));
+    MC_TRY(hipMalloc(&A->d_row_ptr, sizeof(int32_t) * (size_t)(lay.P + 1)));
+    MC_TRY(hipMalloc(&A->d_slot_idx, sizeof(int32_t) * (size_t)(lay.nslots + MC_CHUNK)));
+    if (lay.vals_bytes) MC_TRY(hipMalloc(&A->d_vals, (size_t)lay.vals_bytes));
+    MC_TRY(hipMemcpyAsync(A->d_panel_ptr, panel_ptr.data(), sizeof(int32_t) * 2 * (size_t)lay.P, hipMemcpyHostToDevice, s));
+    MC_TRY(hipMemcpyAsync(A->d_row_ptr, row_ptr, sizeof(int32_t) * (size_t)(lay.P + 1), hipMemcpyHostToDevice, s));
+    if (lay.nslots)
+        MC_TRY(hipMemcpyAsync(A->d_slot_idx, slot_idx.data(), sizeof(int32_t) * (size_t)lay.nslots, hipMemcpyHostToDevice, s));
+    if (lay.vals_bytes)
+        MC_TRY(hipMemcpyAsync(A->d_vals, vals.data(), (size_t)lay.vals_bytes, hipMemcpyHostToDevice, s));
+    if (A->n_items) {
+        MC_TRY(hipMalloc(&A->d_items, sizeof(int32_t) * items.size()));
+        MC_TRY(hipMalloc(&A->d_split_panels, sizeof(int32_t) * split_panels.size()));
+        MC_TRY(hipMemcpyAsync(A->d_items, items.data(), sizeof(int32_t) * items.size(), hipMemcpyHostToDevice, s));
+        MC_TRY(hipMemcpyAsync(A->d_split_panels, split_panels.data(), sizeof(int32_t) * split_panels.size(),
+                              hipMemcpyHostToDevice, s));
+    }
+    if (A->blk_chunks) {
+        MC_TRY(hipMalloc(&A->d_blk_ptr, sizeof(int32_t) * blk_ptr.size()));
+        MC_TRY(hipMalloc(&A->d_blk_recs, blk_recs.size()));
+        MC_TRY(hipMalloc(&A->d_blk_ends, sizeof(uint32_t) * blk_ends.size()));
+        MC_TRY(hipMemcpyAsync(A->d_blk_ends, blk_ends.data(), sizeof(uint32_t) * blk_ends.size(), hipMemcpyHostToDevice, s));
+        MC_TRY(hipMalloc(&A->d_blk_src, sizeof(int32_t) * blk_src.size()));
+        MC_TRY(hipMemcpyAsync(A->d_blk_ptr, blk_ptr.data(), sizeof(int32_t) * blk_ptr.size(), hipMemcpyHostToDevice, s));
+        MC_TRY(hipMemcpyAsync(A->d_blk_recs, blk_recs.data(), blk_recs.size(), hipMemcpyHostToDevice, s));
+        MC_TRY(hipMemcpyAsync(A->d_blk_src, blk_src.data(), sizeof(int32_t) * blk_src.size(), hipMemcpyHostToDevice, s));
+        if (!order.empty()) {
+            MC_TRY(hipMalloc(&A->d_order, sizeof(int32_t) * order.size()));
+            MC_TRY(hipMemcpyAsync(A->d_order, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice, s));
+        }
+        if (!splits.empty()) {
+            MC_TRY(hipMalloc(&A->d_splits, sizeof(int32_t) * splits.size()));
+            MC_TRY(hipMemcpyAsync(A->d_splits, splits.data(), sizeof(int32_t) * splits.size(), hipMemcpyHostToDevice, s));
+        }
+        A->blk_valid = true;
+    }
+    if (!class_panels.empty()) {
+        MC_TRY(hipMalloc(&A->d_class_panels, sizeof(int32_t) * class_panels.size()));
+        MC_TRY(hipMemcpyAsync(A->d_class_panels, class_panels.data(), sizeof(int32_t) * class_panels.size(), hipMemcpyHostToDevice, s));
     }
     if (A->merged) {
         MC_TRY(hipMalloc(&A->d_merge_src, sizeof(int32_t) * m_src.size()));
@@ -577,8 +682,8 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
     r.dst = A->d_vals; r.dst_batch_stride = 0;
     r.P = A->P; r.V = A->V; r.bits = (A->lhs_bits == 12) ? 16 : A->lhs_bits; r.batch = 1;
     MC_HIP(launch_repack(r, static_cast<hipStream_t>(stream)));
-    if (A->d_blk_vals) { // the K-blocked copy follows
-        MC_HIP(launch_repack_blocked(A->d_blk_src, r.src, A->d_blk_vals, A->blk_chunks, A->V, r.bits, static_cast<hipStream_t>(stream)));
+    if (A->d_blk_recs) { // the LDS-ordered copy follows
+        MC_HIP(launch_repack_blocked(A->d_blk_src, r.src, A->d_blk_recs, A->blk_chunks, A->V, r.bits, static_cast<hipStream_t>(stream)));
         A->blk_valid = true;
     }
     if (A->merged) { // and the merged copy: its values in interchange order first, then its own formats
@@ -600,90 +705,32 @@ inline int spmm_stages_for(const mc_options &o, int K, int64_t ldb_bytes, int ro
             ldb_bytes < (1 << 24)) ? 2 : 1;
 }
 
-// Work split of the SpMM that keeps K-blocks of B resident in LDS: one workgroup per (64-byte column
-// tile, group of ppg consecutive panels); about one workgroup per compute unit (each takes 128 KB of
-// LDS), more groups when a wave would otherwise own more panels than its registers hold.
-struct SlabPlan { int groups, ppg, wpp, nc, ppw, passes; int64_t workgroups; };
-bool plan_slab(const mc_mat *A, int row_bytes, bool r4, int batch, const mc_options &o, SlabPlan *pl)
-{
-    const int T = (row_bytes + 63) / 64, max_ppw = r4 ? 2 : 4;
-    int64_t G = (256 + (int64_t)T * batch - 1) / ((int64_t)T * batch);
-    if (G > A->P) G = A->P;
-    if (G < 1) G = 1;
-    const int ppg = (int)((A->P + G - 1) / G);
-    G = (A->P + ppg - 1) / ppg;
-    pl->groups = (int)G;
-    pl->ppg = ppg;
-    pl->workgroups = G * T * batch;
-    // Twelve computing waves and four filling ones (one filling wave alone is bound by the latency of its own
-    // copies: 3.3 against 1.6 us per 64 KB block).  More panels than waves: two panels per wave and as many
-    // passes over K as it takes (measured against 8 x 2, 8 x 4, 12 x 1 and 15 x 1/2/4: 12 x 2 is the fastest or
-    // within 5 % of it from 13 panels per workgroup on).  Fewer panels than waves: several waves share a panel's
-    // chunks, at most four and no more than a (panel, block) list has chunks on average.
-    if (ppg > 12) {
-        pl->nc = 12; pl->wpp = 1; pl->ppw = 2; pl->passes = (ppg + 23) / 24;
-    } else {
-        const double per_list = (double)A->blk_chunks / ((double)A->P * A->nblk);
-        int wpp = 12 / ppg;
-        if (wpp > 4) wpp = 4;
-        while (wpp > 1 && wpp > per_list) --wpp;
-        pl->nc = ppg * wpp; pl->wpp = wpp; pl->ppw = 1; pl->passes = 1;
-    }
-    if (o.spmm_slab_waves || o.spmm_slab_panels) {
-        // a pinned shape: one wave per panel, as many passes as it takes
-        pl->nc = o.spmm_slab_waves ? o.spmm_slab_waves : pl->nc;
-        pl->ppw = o.spmm_slab_panels ? o.spmm_slab_panels : pl->ppw;
-        pl->wpp = 1;
-        pl->passes = (ppg + pl->nc * pl->ppw - 1) / (pl->nc * pl->ppw);
-    }
-    return pl->ppw <= max_ppw;
-}
+// The form one SpMM call takes: the operand or its merged copy, and whether rows of B are resident in LDS (then plan is
+// the work split).
+struct SpmmForm { const mc_mat *A; bool slab; SlabPlan plan; };
 
-// Whether the LDS-resident form is expected to beat the gather form.  Both times (microseconds) are least-squares
-// fits to measurements on MI355X over V in {2, 4, 8}, six sparsities and N in {128, 256, 512} at 4096 x 4096, for
-// byte and for nibble rows of B apart (nibble rows take two MFMA steps per 64 bytes).  Gather form: a start-up
-// term plus its gathered bytes at 22 (nibbles: 14) TB/s.  LDS-resident form: a start-up term, about 2 us per
-// K-block and pass for the fill it cannot hide, and 16 (nibbles: 42) ns per chunk step of a compute unit.  Picking
-// by these fits is on average 0.03 % and at worst 4 % slower than the better form over the points of that sweep
-// where both exist.
-bool slab_pays(const mc_mat *A, int row_bytes, bool r4, int batch, const SlabPlan &pl)
+SpmmForm spmm_form(const mc_mat *A, int row_bytes, int rb, int out_bytes, unsigned flags, const mc_options &o)
 {
-    const double T = (double)((row_bytes + 63) / 64);
-    double t_gather = (r4 ? 3.88 : 3.96) + (double)A->nvec * row_bytes * batch / (r4 ? 13.99e6 : 22.13e6);
-    if (A->V == 16) {
-        // merged copies (16-row panels, fewer and longer): the gather form fitted on the merged operands of the same sweep
-        const double t0 = r4 ? 3.9 : (row_bytes >= 512 ? 4.4 : 3.3);
-        const double rate = r4 ? (row_bytes == 128 ? 10.0e6 : 12.5e6) : (row_bytes >= 512 ? 20.5e6 : 17.7e6);
-        t_gather = t0 + (double)A->nvec * row_bytes * batch / rate;
+    const bool r4 = rb == 4;
+    const bool slab_possible = o.spmm_slab != -1 && flags == 0 && rb != 16 && o.spmm_row_tile_bytes == 0 && o.spmm_waves == 0;
+    // a 16-row panel leaves no MFMA row for the column sums that unsigned operands need
+    const bool merged_possible = A->merged && A->merged_valid && o.spmm_merge != -1 && !(flags != 0 && A->merged->V > 8);
+    SpmmForm f = {A, false, {}};
+    double best = 1e30;
+    for (int m = (merged_possible && o.spmm_merge == 1) ? 1 : 0; m <= (merged_possible ? 1 : 0); ++m) {
+        const mc_mat *X = m ? A->merged : A;
+        const bool slab = slab_possible && X->d_blk_recs && X->blk_valid;
+        if (!slab && !merged_possible) return f;                    // nothing to choose
+        SlabPlan pl;
+        pl.us = 1e30;
+        if (slab) plan_slab(X, row_bytes, r4, out_bytes, o, &pl);
+        const double gather = (slab && o.spmm_slab == 1) ? 1e30 : gather_us(X, row_bytes, r4, out_bytes);
+        if (std::min(gather, pl.us) < best) {
+            best = std::min(gather, pl.us);
+            f.A = X; f.slab = pl.us < gather; f.plan = pl;
+        }
     }
-    const double steps = (double)A->blk_chunks * T * batch / 256.0;
-    const double rounds = std::max(1.0, std::ceil((double)pl.workgroups / 256.0) / ((double)pl.workgroups / 256.0));
-    const double t_slab = (r4 ? 0.47 : 2.05) + (pl.passes * (r4 ? 2.12 : 1.98) * A->nblk + (r4 ? 0.0417 : 0.01565) * steps) * rounds;
-    return t_slab < t_gather;
-}
-
-// The form one SpMM call takes: true = K-blocks of B resident in LDS (then *pl is its work split).
-bool slab_chosen(const mc_mat *A, int row_bytes, int rb, unsigned flags, const mc_options &o, SlabPlan *pl)
-{
-    if (o.spmm_slab == -1 || !A->d_blk_vals || !A->blk_valid || flags != 0 || rb == 16 || o.spmm_row_tile_bytes != 0 ||
-        o.spmm_waves != 0)
-        return false;
-    return plan_slab(A, row_bytes, rb == 4, 1, o, pl) && (o.spmm_slab == 1 || slab_pays(A, row_bytes, rb == 4, 1, *pl));
-}
-
-// Whether an SpMM call runs on the operand's merged copy.
-bool merged_chosen(const mc_mat *A, int row_bytes, unsigned flags, const mc_options &o)
-{
-    if (!A->merged || !A->merged_valid || o.spmm_merge == -1) return false;
-    if (flags != 0 && A->merged->V > 8) return false;
-    if (o.spmm_merge == 1) return true;
-    // Merged panels of 8 rows (two-plane values) run in the same kernel shape as unmerged ones with fewer gathered
-    // rows, fewer padded slots and fewer panels: faster at 34 of 36 points of a 4096 x 4096 sweep (V = 2 / 4, six
-    // sparsities, N = 128 .. 512), at worst 9 % slower.
-    if (A->merged->V <= 8) return true;
-    // Merged panels of 16 rows gather fewer rows (padded slots included) but run fewer, longer panels with 16-row
-    // tiles; in the same sweep (V = 2 / 4 / 8) they are the faster form once they save about 24 MB of gathered rows.
-    return (double)(A->nslots - A->merged->nslots) * row_bytes >= 24e6;
+    return f;
 }
 
 // out_mode 0: int32 results; 1 / 2: scale * result as fp32 / fp16 (fused dequantisation)
@@ -707,10 +754,10 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
     if (out_mode && !std::isfinite(scale)) return MC_EINVAL;
     if (!on_device_of(A)) return MC_EINVAL;
 
-    // the operand's merged copy (panels of 8 or 16 rows at the union of their columns) where it is expected to be faster;
-    // a 16-row panel leaves no MFMA row for the column sums that unsigned operands need
+    // the operand's merged copy (panels of 8 or 16 rows at the union of their columns) where it is expected to be faster
     const int rows = A->M;
-    if (merged_chosen(A, N * rb / 8, flags, o)) A = A->merged;
+    const SpmmForm form = spmm_form(A, N * rb / 8, rb, out_mode == 2 ? 2 : 4, flags, o);
+    A = form.A;
 
     SpmmArgs a = {};
     a.rows = rows;
@@ -721,21 +768,19 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
     a.row_bytes = N * rb / 8;
     a.C = C_dev; a.ldc = ldc; a.C_batch_stride = 0;
     a.P = A->P; a.V = A->V; a.batch = 1; a.float_out = out_mode; a.out_scale = out_mode ? scale : 1.f;
-    // dense matrices: blocks of B resident in LDS instead of a gather per stored vector
-    {
-        SlabPlan pl;
-        if (slab_chosen(A, a.row_bytes, rb, flags, o, &pl)) {
-            SlabArgs sa = {};
-            sa.blk_ptr = A->d_blk_ptr; sa.blk_rows = A->d_blk_rows; sa.vals = A->d_blk_vals; sa.vals_batch_stride = 0;
-            sa.B = a.B; sa.ldb_bytes = a.ldb_bytes; sa.B_batch_stride = 0; sa.row_bytes = a.row_bytes; sa.K = A->K;
-            sa.C = C_dev; sa.ldc = ldc; sa.C_batch_stride = 0;
-            sa.P = A->P; sa.V = A->V; sa.batch = 1; sa.nblk = A->nblk; sa.rows = rows;
-            sa.float_out = out_mode; sa.out_scale = a.out_scale;
-            sa.groups = pl.groups; sa.ppg = pl.ppg; sa.wpp = pl.wpp; sa.nc = pl.nc;
-            sa.nf = 16 - sa.nc < 4 ? 16 - sa.nc : 4;
-            MC_HIP(launch_spmm_slab(prec, sa, pl.ppw, static_cast<hipStream_t>(stream)));
-            return MC_OK;
-        }
+    if (form.slab) {
+        const SlabPlan &pl = form.plan;
+        SlabArgs sa = {};
+        sa.blk_ptr = A->d_blk_ptr; sa.recs = A->d_blk_recs; sa.ends = A->d_blk_ends; sa.end_words = resident_end_words(A);
+        sa.order = A->d_order; sa.splits = A->d_splits;
+        sa.uniform_chunks = A->uniform_chunks; sa.rec_bytes = resident_rec_bytes(A); sa.nchunks = A->blk_chunks;
+        sa.B = a.B; sa.ldb_bytes = a.ldb_bytes; sa.row_bytes = a.row_bytes; sa.K = A->K;
+        sa.C = C_dev; sa.ldc = ldc;
+        sa.P = A->P; sa.V = A->V; sa.nblk = A->nblk; sa.block_rows = A->block_rows; sa.nt = A->blk_nt; sa.rows = rows;
+        sa.float_out = out_mode; sa.out_scale = a.out_scale;
+        sa.ntiles = pl.ntiles; sa.groups = pl.groups; sa.wpp = pl.wpp; sa.waves = pl.waves;
+        MC_HIP(launch_spmm_slab(prec, sa, pl.nt, static_cast<hipStream_t>(stream)));
+        return MC_OK;
     }
     a.stages = spmm_stages_for(o, A->K, a.ldb_bytes, a.row_bytes);
     a.uniform_chunks = A->uniform_chunks;
@@ -781,11 +826,9 @@ extern "C" int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_optio
     const mc_options automatic = {};
     mc_options o;
     if (resolve_options(options ? options : &automatic, &o) != MC_OK) return MC_EINVAL;
-    SlabPlan pl;
     const int rb = rhs_bits_of(prec);
-    const bool merged = merged_chosen(A, N * rb / 8, 0u, o);
-    if (merged) A = A->merged;
-    return (slab_chosen(A, N * rb / 8, rb, 0u, o, &pl) ? 1 : 0) | (merged ? 2 : 0);
+    const SpmmForm form = spmm_form(A, N * rb / 8, rb, 4, 0u, o);
+    return (form.slab ? 1 : 0) | (form.A != A ? 2 : 0);
 }
 
 extern "C" int mc_spmm_dequant(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, unsigned flags,

@@ -210,14 +210,8 @@ extern "C" int mc_unpack_host(int M, int K, int V, int lhs_bits, const int32_t *
 extern "C" int mc_blocked_query(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
                                 mc_blocked_layout *out)
 {
-    return V == 16 ? MC_EINVAL : mc_blocked_query_wide(M, K, V, lhs_bits, row_ptr, col_idx, out);
-}
-
-int mc_blocked_query_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
-                          mc_blocked_layout *out)
-{
     mc_layout lay;
-    int rc = mc_layout_query_wide(M, K, V, lhs_bits, row_ptr, &lay);
+    int rc = mc_layout_query(M, K, V, lhs_bits, row_ptr, &lay);
     if (rc != MC_OK) return rc;
     if (!out || (lay.nvec && !col_idx)) return MC_EINVAL;
     const int nblk = (K + MC_KBLOCK - 1) / MC_KBLOCK;
@@ -248,14 +242,8 @@ extern "C" int mc_pack_blocked_host(int M, int K, int V, int lhs_bits, const int
                                     const void *values, int32_t *blk_ptr, uint16_t *blk_rows, void *blk_vals,
                                     int32_t *blk_src)
 {
-    return V == 16 ? MC_EINVAL : mc_pack_blocked_host_wide(M, K, V, lhs_bits, row_ptr, col_idx, values, blk_ptr, blk_rows, blk_vals, blk_src);
-}
-
-int mc_pack_blocked_host_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
-                              const void *values, int32_t *blk_ptr, uint16_t *blk_rows, void *blk_vals, int32_t *blk_src)
-{
     mc_blocked_layout bl;
-    int rc = mc_blocked_query_wide(M, K, V, lhs_bits, row_ptr, col_idx, &bl);
+    int rc = mc_blocked_query(M, K, V, lhs_bits, row_ptr, col_idx, &bl);
     if (rc != MC_OK) return rc;
     if (!blk_ptr || (bl.nchunks && (!blk_rows || !blk_src))) return MC_EINVAL;
     const bool with_vals = lhs_bits != 0 && values != nullptr;
@@ -292,6 +280,100 @@ int mc_pack_blocked_host_wide(int M, int K, int V, int lhs_bits, const int32_t *
         }
     }
     blk_ptr[(int64_t)P * bl.nblk] = (int32_t)chunk;
+    return MC_OK;
+}
+
+// ---- LDS-ordered copy ------------------------------------------------------------------------
+// For the kernel that keeps whole rows of a column tile of the dense operand in LDS (internal.h has the layout).
+// 160 KB hold 2560 rows of 64 bytes or 5120 of 32; more rows than that come in equal blocks.
+void mc_resident_query(int K, int P, const int32_t *row_ptr, const int32_t *col_idx, ResidentLayout *out)
+{
+    out->nt = K <= 2560 ? 4 : 2;
+    const int most = 10240 / out->nt;
+    out->nblk = (K + most - 1) / most;
+    out->block_rows = ((K + out->nblk - 1) / out->nblk + 15) / 16 * 16;
+    int64_t nchunks = 0;
+    for (int p = 0; p < P; ++p) {
+        if (out->nblk == 1) {
+            nchunks += std::max(1, (row_ptr[p + 1] - row_ptr[p] + MC_CHUNK - 1) / MC_CHUNK);
+            continue;
+        }
+        const int32_t *i = col_idx + row_ptr[p], *end = col_idx + row_ptr[p + 1];
+        for (int b = 0; b < out->nblk; ++b) {
+            const int32_t *e = std::lower_bound(i, end, (b + 1) * out->block_rows);
+            nchunks += std::max<int64_t>(1, (e - i + MC_CHUNK - 1) / MC_CHUNK);
+            i = e;
+        }
+    }
+    out->nchunks = nchunks;
+}
+
+int mc_resident_pack(int K, int V, int lhs_bits, int P, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
+                     const ResidentLayout &lay, int32_t *ptr, uint8_t *recs, int32_t *src, uint32_t *ends)
+{
+    const int64_t rbytes = 2 * MC_CHUNK + chunk_value_bytes(V, lhs_bits);
+    std::vector<int32_t> place;                 // interchange vector of each place of a list, -1: empty
+    std::vector<int32_t> extra[16];             // vectors whose residue has more of them than the list has sets
+    int64_t chunk = 0;
+    for (int p = 0; p < P; ++p) {
+        const int32_t *i = col_idx + row_ptr[p], *end = col_idx + row_ptr[p + 1];
+        for (int b = 0; b < lay.nblk; ++b) {
+            ptr[(int64_t)p * lay.nblk + b] = (int32_t)chunk;
+            const int32_t *e = lay.nblk == 1 ? end : std::lower_bound(i, end, (b + 1) * lay.block_rows);
+            const int row0 = b * lay.block_rows, nrows = std::min(K - row0, lay.block_rows);
+            const int nch = std::max(1, (int)((e - i + MC_CHUNK - 1) / MC_CHUNK)), nsets = nch * 4;
+            // A set is the 16 rows that half a wave reads at once; place 16*set + residue.  The k-th row of a residue
+            // goes to set k; what exceeds the number of sets fills the places left over, one of a residue per set.
+            place.assign((size_t)nsets * 16, -1);
+            int count[16] = {0};
+            for (const int32_t *c = i; c < e; ++c) {
+                const int res = (*c - row0) & 15, at = count[res]++;
+                if (at < nsets) place[(size_t)at * 16 + res] = (int32_t)(c - col_idx);
+                else extra[res].push_back((int32_t)(c - col_idx));
+            }
+            for (int st = 0; st < nsets; ++st) {
+                int res = 0;
+                for (int t = 0; t < 16; ++t) {
+                    if (place[(size_t)st * 16 + t] >= 0) continue;
+                    while (res < 16 && extra[res].empty()) ++res;
+                    if (res == 16) break;
+                    place[(size_t)st * 16 + t] = extra[res].back();
+                    extra[res].pop_back();
+                    ++res;
+                }
+            }
+            for (int st = 0; st < nsets; ++st) {    // (a last resort: several of one residue in a set)
+                for (int t = 0; t < 16; ++t) {
+                    if (place[(size_t)st * 16 + t] >= 0) continue;
+                    int res = 0;
+                    while (res < 16 && extra[res].empty()) ++res;
+                    if (res == 16) break;
+                    place[(size_t)st * 16 + t] = extra[res].back();
+                    extra[res].pop_back();
+                }
+            }
+            for (int st = 0; st < nsets; ++st) {
+                const int64_t c = chunk + st / 4;
+                const int pair = (st % 4) / 2, h = st % 2;   // lane groups 2*pair, 2*pair + 1; slots 8h .. 8h + 7 of each
+                for (int t = 0; t < 16; ++t) {
+                    const int slot = (2 * pair + t / 8) * 16 + 8 * h + t % 8;
+                    const int32_t from = place[(size_t)st * 16 + t];
+                    const int row = from >= 0 ? col_idx[from] - row0 : (t < nrows ? t : 0);
+                    uint8_t *rec = recs + c * rbytes;
+                    reinterpret_cast<uint16_t *>(rec)[row_position(slot)] = (uint16_t)((row >> 4) * 16 * lay.nt + (row & 15));
+                    src[c * MC_CHUNK + slot] = from;
+                    if (from >= 0) {
+                        const int rc = put_vector(rec + 2 * MC_CHUNK, V, lhs_bits, slot, values, from);
+                        if (rc != MC_OK) return rc;
+                    }
+                }
+            }
+            chunk += nch;
+            if (lay.nblk == 1) ends[(chunk - 1) / 32] |= 1u << ((chunk - 1) % 32);
+            i = e;
+        }
+    }
+    ptr[(int64_t)P * lay.nblk] = (int32_t)chunk;
     return MC_OK;
 }
 

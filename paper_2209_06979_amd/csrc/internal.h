@@ -23,14 +23,19 @@ struct mc_mat {
     int32_t *d_split_panels;   // n_split: the panels that have several items
     int n_items, n_split;
     int max_item_chunks;       // chunks of the longest item
-    // K-blocked copy of the operand for the SpMM that keeps blocks of B resident in LDS (null when not
-    // built: pattern-only masks, very sparse or very unequal matrices, more than 63 K-blocks)
-    int nblk;                  // K-blocks of MC_KBLOCK rows
+    // LDS-ordered copy of the operand for the SpMM that keeps rows of B resident in LDS (see mc_resident_pack; null when
+    // not built: pattern-only masks, operands too sparse or small for it)
+    int blk_nt;                // 16-byte segments of a row in the LDS image the codes are made for (2 or 4)
+    int block_rows;            // rows of B per K-block
+    int nblk;                  // K-blocks
     int64_t blk_chunks;        // chunks over all (panel, block) lists
     int32_t *d_blk_ptr;        // P*nblk + 1
-    uint16_t *d_blk_rows;      // blk_chunks * 64
-    uint8_t *d_blk_vals;       // blk_chunks * chunk bytes
+    uint8_t *d_blk_recs;       // blk_chunks records (and RESIDENT_AHEAD of zeros)
+    uint32_t *d_blk_ends;      // nblk == 1: a bit per chunk, set where a panel ends (and two words of zeros)
     int32_t *d_blk_src;        // blk_chunks * 64: interchange vector of each slot, -1 for padding
+    int32_t *d_order;          // nblk > 1: P panel numbers by falling length (null: all panels have the same number of chunks)
+    int32_t *d_splits;         // nblk == 1: RESIDENT_SPLITS + 1 panel numbers, the first that starts at or after i/4096 of the
+                               // chunks (null: all panels have the same number of chunks)
     bool blk_valid;            // false once the values were replaced in the panel format only
     // Panels sorted by length class for kernels that give a panel 1, 2, 4 or 8 waves (V = 8 only; null when every
     // panel falls into one class): class b holds the panels of at most 8 << b chunks that class b - 1 does not
@@ -52,9 +57,21 @@ struct mc_mat {
 int mc_layout_query_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, mc_layout *out);
 int mc_pack_host_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                       int32_t *panel_ptr, int32_t *slot_idx, void *slot_vals);
-int mc_blocked_query_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx, mc_blocked_layout *out);
-int mc_pack_blocked_host_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
-                              int32_t *blk_ptr, uint16_t *blk_rows, void *blk_vals, int32_t *blk_src);
+
+// The LDS-ordered copy of an operand (spmm_resident_kernels.hip).  Rows of B are resident in LDS in blocks of block_rows,
+// a block's image being [row / 16][segment of 16 bytes][row % 16] with nt segments; the vectors of a (panel, block) list
+// (never empty: at least one chunk) are dealt into chunks of 64 such that the 16 rows which one LDS read addresses differ modulo 16 where possible.
+//   ptr    P*nblk + 1: first chunk of (panel p, block b) at [p*nblk + b]
+//   recs   nchunks records: 64 codes (uint16: (row / 16)*16*nt + row % 16, the place of the row's segment 0 in 16 bytes; the
+//          code of slot s at position (s/16)*16 + (s%8)*2 + (s%16)/8; padded slots name some row of the block), then the values in the layout of a chunk of mc_pack_host's slot_vals.  Zeroed by the caller.
+//   src    nchunks*64: interchange vector of each slot, -1 for padding
+constexpr int RESIDENT_AHEAD = 8;     // chunks of padding after the copy's device arrays (its readers run ahead)
+constexpr int RESIDENT_SPLITS = 4096; // an operand with unequal panels has the first panel of every 1/4096 of its chunks listed
+struct ResidentLayout { int nt, block_rows, nblk; int64_t nchunks; };
+void mc_resident_query(int K, int P, const int32_t *row_ptr, const int32_t *col_idx, ResidentLayout *out);
+// bit i of ends: chunk i is the last of its panel (nblk 1 only; (nchunks + 31) / 32 + 2 words)
+int mc_resident_pack(int K, int V, int lhs_bits, int P, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
+                     const ResidentLayout &lay, int32_t *ptr, uint8_t *recs, int32_t *src, uint32_t *ends);
 
 // One SpMM launch (optionally a batch of problems sharing the sparsity pattern).
 struct SpmmArgs {
@@ -89,26 +106,30 @@ struct SpmmArgs {
     long long *trace;          // measurement aid (launch_spmm_phase_probe only): time stamps per wave
 };
 
-// One launch of the SpMM that keeps K-blocks of B resident in LDS (see spmm_slab_kernels.hip).
+// One launch of the SpMM that keeps rows of B resident in LDS (see spmm_resident_kernels.hip).
 struct SlabArgs {
     const int32_t *blk_ptr;
-    const uint16_t *blk_rows;
-    const uint8_t *vals;
-    int64_t vals_batch_stride; // bytes
+    const uint8_t *recs;
+    const uint32_t *ends;
+    int end_words;
+    const int32_t *order, *splits; // see mc_mat
+    int uniform_chunks;        // > 0: every panel has this many chunks (nblk == 1)
+    int rec_bytes;             // bytes of a record
+    int64_t nchunks;           // records (RESIDENT_AHEAD more follow)
     const uint8_t *B;
-    int64_t ldb_bytes, B_batch_stride;
+    int64_t ldb_bytes;
     int row_bytes, K;
     void *C;
-    int64_t ldc, C_batch_stride;
-    int P, V, batch, nblk;
+    int64_t ldc;
+    int P, V, nblk, block_rows;
+    int nt;                    // segments per row of the LDS image (the operand's copy is made for it)
     int rows;                  // rows of C (see SpmmArgs)
     int float_out;
     float out_scale;
+    int ntiles;                // column tiles
     int groups;                // panel groups (workgroups per column tile)
-    int ppg;                   // consecutive panels per workgroup (taken in passes of (nc / wpp) * panels-per-wave)
-    int wpp;                   // waves sharing a panel (its chunks dealt round-robin)
-    int nc;                    // computing waves per workgroup; nc / wpp panels at a time
-    int nf;                    // filling waves (after the computing ones); nc + nf <= 16
+    int wpp;                   // waves sharing a panel (its chunks dealt round-robin); above 1 only if every wave has one panel
+    int waves;                 // per workgroup, a multiple of wpp
 };
 
 struct SddmmArgs {
@@ -196,9 +217,9 @@ hipError_t launch_spmm(mc_prec prec, const SpmmArgs &a, int bnb, int waves, hipS
 // the L8-R8 SpMM (128-byte tiles, 2 waves per panel, two chunks in flight; every panel at most 8 chunks, whole panels,
 // B below 4 GiB) with 10 time stamps per wave written to a.trace
 hipError_t launch_spmm_phase_probe(const SpmmArgs &a, hipStream_t s);
-// ppw: panels per computing wave (1, 2 or 4; 4 only with an 8-bit B).  Precisions with a 16-bit B are not built.
-hipError_t launch_spmm_slab(mc_prec prec, const SlabArgs &a, int ppw, hipStream_t s);
-hipError_t launch_repack_blocked(const int32_t *blk_src, const uint8_t *src, uint8_t *dst, int64_t nchunks, int V, int bits,
+// nt: segments (16 bytes) of a column tile, 2 or 4, at most a.nt.  Precisions with a 16-bit B are not built.
+hipError_t launch_spmm_slab(mc_prec prec, const SlabArgs &a, int nt, hipStream_t s);
+hipError_t launch_repack_blocked(const int32_t *blk_src, const uint8_t *src, uint8_t *recs, int64_t nchunks, int V, int bits,
                                  hipStream_t s);
 // clears the C rows (int32, n columns) of the listed panels
 hipError_t launch_zero_rows(int32_t *C, int64_t ldc, int n, int V, const int32_t *panels, int n_panels, hipStream_t s);
