@@ -1236,7 +1236,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
 
     if (attention_is_fused(mask, dk, qkv_bits, o)) {
         const int tile = dk <= 64 ? 64 : 128;     // the kernel's head dimension
-        AttnArgs f;
+        AttnArgs f = {};
         f.real_pieces = dk * qkv_bits / 8 / 16; f.out_cols = dk;
         f.panel_ptr = mask->d_panel_ptr; f.slot_idx = mask->d_slot_idx;
         f.Q = static_cast<const uint8_t *>(Q_dev); f.Km = static_cast<const uint8_t *>(Km_dev);

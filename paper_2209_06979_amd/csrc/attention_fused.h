@@ -35,6 +35,7 @@
 #pragma once
 #include "internal.h"
 #include "lds_async.h"
+#include <type_traits>
 
 namespace {
 
@@ -123,7 +124,7 @@ void attention_fused_kernel(AttnArgs a)
     static_assert(!SMALLP || OTILE <= STG, "with two heads per workgroup a wave's output tile is staged in one gather stage");
     __shared__ __attribute__((aligned(16))) char stage_all[NST * STG * KS];  // chunks of gathered rows (KS > 1: one stage per wave)
     __shared__ __attribute__((aligned(16))) char Pl_all[NW * PLB]; // codes, [plane][slot][8 rows], per wave
-    __shared__ __attribute__((aligned(8))) char zeros[8];                      // row operand of the MFMA rows that carry no codes
+    __shared__ __attribute__((aligned(8))) char zeros[72];                     // row operand of the MFMA rows that carry no codes
     __shared__ int xch[2][HPW][KS][8];                                        // row maxima / row sums of the KS waves of a head
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -132,27 +133,34 @@ void attention_fused_kernel(AttnArgs a)
     char *stage = stage_all + ks * (NST * STG);
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
-    // Workgroups are handed to the 8 XCDs round-robin by linear id.  With id = panel * groups +
-    // head group, an XCD only ever sees the head groups congruent to its number, so its L2 has
-    // to hold the Kmat and V rows of those heads only.
+    // Workgroups are handed to the 8 XCDs round-robin by linear id.  1, 2, 4 or 8 (head group, batch item) pairs are worked on
+    // at a time, a row of the grid: the most that divide their number.  An XCD then sees one pair at a time, its L2
+    // holds the Kmat and V rows of that pair and fetches them once.  (With all XCDs on one batch item at a time each fetched every
+    // item's rows: 2 heads x 4096, batch 32, 90 % empty 112 -> 105 us.)
     const int groups = a.heads / HPW;
-    const int hgrp = blockIdx.x % groups;
-    const int panel = a.panel_list ? a.panel_list[blockIdx.x / groups] : (int)(blockIdx.x / groups);
+    const int pair = ((int)(blockIdx.z * gridDim.y + blockIdx.y) << a.pair_shift) + (int)(blockIdx.x & ((1u << a.pair_shift) - 1));
+    if (pair >= groups * a.batch) return;
+    int hgrp = pair, item = 0;
+    if (a.batch > 1) {
+        item = pair / groups;
+        hgrp = pair - item * groups;
+    }
+    const int panel = a.panel_list ? a.panel_list[blockIdx.x >> a.pair_shift] : (int)(blockIdx.x >> a.pair_shift);
     const int head = hgrp * HPW + w;
     const int s0 = a.panel_ptr[2 * panel], n = a.panel_ptr[2 * panel + 1] - s0;
     const int nch = (n + MC_CHUNK - 1) / MC_CHUNK;
     const int32_t *idx = a.slot_idx + s0;
     const int64_t goff = (int64_t)hgrp * HPW * a.in_head_stride; // first head of the group
-    const int64_t boff = (int64_t)blockIdx.y * a.in_batch_stride; // batch item
+    const int64_t boff = (int64_t)item * a.in_batch_stride; // batch item
     const uint8_t *Kg = a.Km + boff + goff, *Vg = a.Vm + boff + goff;
-    float *Oh = a.O + (int64_t)blockIdx.y * a.batch_stride + (int64_t)head * a.head_stride + (int64_t)panel * 8 * a.token_stride;
+    float *Oh = a.O + (int64_t)item * a.batch_stride + (int64_t)head * a.head_stride + (int64_t)panel * 8 * a.token_stride;
     char *Pl = Pl_all + wave * PLB;
     const int nloc = (nch > ks) ? (nch - ks + KS - 1) / KS : 0; // chunks of this wave: ks, ks + KS, ...
     // Waves that meet at a workgroup barrier per chunk all make as many passes as the busiest of them
     // (a pass without a chunk of its own is the barrier alone).
     constexpr bool LOCKSTEP = (HPW > 1 && KS > 1);
     const int npass = LOCKSTEP ? (nch + KS - 1) / KS : nloc;
-    if (PB == 8 && lane < 2) reinterpret_cast<int *>(zeros)[lane] = 0; // every wave writes the same zeros: no race that matters
+    if (PB == 8 && lane < 18) reinterpret_cast<int *>(zeros)[lane] = 0; // every wave writes the same zeros: no race that matters
     if (PAD) {
         // the places of the pieces a row does not have: zero once, never written again
         for (int i = threadIdx.x; i < NST * STG * KS / 16; i += 64 * NW) reinterpret_cast<v4i *>(stage_all)[i] = (v4i){0, 0, 0, 0};
@@ -179,7 +187,9 @@ void attention_fused_kernel(AttnArgs a)
     // Copy instruction i of a chunk: lane (rg, seg) fetches segment seg ^ i of the row in slot
     // rg*NIT + i; it lands in LDS row i*(64/NIT) + rg.  Wave w issues instructions NITW*w .. +NITW-1,
     // whose column indices are consecutive slots: one 128-bit (64-bit) index load per chunk.
-    typedef int ixv_t __attribute__((ext_vector_type(NITW)));
+    constexpr int SHARE = NITW >= 4 ? 4 : 2, NIX = NITW / SHARE;  // lanes that share their indices; indices a lane loads per chunk
+    static_assert(SHARE <= LPR, "only lanes of one row share");
+    typedef int ixv_t __attribute__((ext_vector_type(NIX)));
     unsigned segoff[NITW];
     bool live[NITW]; // PAD: whether the row has the piece this lane would fetch in instruction i
 #pragma unroll
@@ -188,42 +198,53 @@ void attention_fused_kernel(AttnArgs a)
         live[i] = !PAD || (int)(seg ^ ((NITW * w + i) & SWZ)) < a.real_pieces;
     }
     const unsigned stage_u = lds_addr_uniform(stage);  // this wave's stage(s)
-    const int32_t *myidx = idx + rg * NIT + NITW * w;
+    // A lane's copies take NITW indices, the same for all lanes of a row.  Loaded by each lane they would be a fifth of
+    // all bytes that L1 returns: a lane loads NIX of them and takes the others from its neighbours.
+    // (a chunk's place is wave-uniform: a scalar base and the lane's constant offset)
+    const unsigned lane_idx = (rg * NIT + NITW * w + (lane % SHARE) * NIX) * 4;
+    auto index_of = [&](auto I, const ixv_t &ix) -> unsigned { // index of copy instruction i
+        constexpr int i = decltype(I)::value, q = i / NIX, ctrl = SHARE == 4 ? q * 0x55 : (q == 0 ? 0xA0 : 0xF5); // quad_perm [q,q,q,q] / [0,0,2,2], [1,1,3,3]
+        return (unsigned)__builtin_amdgcn_mov_dpp(ix[i % NIX], ctrl, 0xF, 0xF, true);
+    };
+    auto load_idx = [&](int c) -> ixv_t {
+        return *reinterpret_cast<const ixv_t *>(reinterpret_cast<const char *>(idx + c * MC_CHUNK) + lane_idx);
+    };
     const unsigned tstride = (unsigned)a.in_token_stride;
-    // issue(c): this wave's copies of chunk c into stage c % NST, from the column indices held
+    // issue(c, st): this wave's copies of chunk c into stage st, from the column indices held
     // in ixn; then the indices of the following chunk are requested (an ordinary load that has
     // long arrived by the time they are needed: a vm_wait<0>() lies in between).
     ixv_t ixn = {};
-    auto issue = [&](const uint8_t *base, int c) {
-#pragma unroll
-        for (int i = 0; i < NITW; ++i)
-            if (!PAD || live[i])
-                copy16_to_lds(base, __umul24(ixn[i], tstride) + segoff[i], stage_u + ((c / KS) % NST) * STG + (NITW * w + i) * 1024);
-        ixn = *reinterpret_cast<const ixv_t *>(myidx + ((c + KS < nch) ? c + KS : c) * MC_CHUNK);
+    auto issue = [&](const uint8_t *base, int c, int st) {
+        static_for<NITW>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            const unsigned at = __umul24(index_of(I, ixn), tstride) + segoff[i]; // (the exchange with all lanes active)
+            if (!PAD || live[i]) copy16_to_lds(base, at, stage_u + st * STG + (NITW * w + i) * 1024);
+        });
+        ixn = load_idx((c + KS < nch) ? c + KS : c);
     };
     auto start_pipeline = [&](const uint8_t *base) {
         lgkm_wait();                               // no read of the stage is still in flight
         if (HPW > 1) __builtin_amdgcn_s_barrier(); // both waves are done with the stages
         if (nloc > 0) {
-            ixn = *reinterpret_cast<const ixv_t *>(myidx + ks * MC_CHUNK);
-            issue(base, ks);
+            ixn = load_idx(ks);
+            issue(base, ks, 0);
         }
     };
     // Makes chunk c readable.  HPW 1: the next chunk is issued by release() once this one has
     // been read.  HPW 2: both halves have landed after the barrier, which also tells that
     // everybody is done reading the pair's previous chunk, so its next chunk can go into the other
-    // stage now.  (c may lie beyond the panel's last chunk in a pass of waiting only.)
-    auto acquire = [&](const uint8_t *base, int c) {
+    // stage st now.  (c may lie beyond the panel's last chunk in a pass of waiting only.)
+    auto acquire = [&](const uint8_t *base, int c, int st) {
         vm_wait<0>();
         if (HPW > 1) {
             __builtin_amdgcn_s_barrier();
-            if (c + KS < nch) issue(base, c + KS);
+            if (c + KS < nch) issue(base, c + KS, st);
         }
     };
     auto release = [&](const uint8_t *base, int c) { // the reads of chunk c have been issued
         if (HPW == 1 && c + KS < nch) {
             lgkm_wait(); // ... and have returned: the one stage may be overwritten
-            issue(base, c + KS);
+            issue(base, c + KS, 0);
         }
     };
 
@@ -254,7 +275,7 @@ void attention_fused_kernel(AttnArgs a)
         constexpr int c = C, ST = (c % NST) * STG;
         const int gc = ks + c * KS;
         if (c < npass) {
-            acquire(Kg, gc);
+            acquire(Kg, gc, (c + 1) % NST);
             if (LOCKSTEP && c >= nloc) return;
             v4i kt[KK][4]; // tiles 0..3 of the chunk
 #pragma unroll
@@ -355,62 +376,77 @@ void attention_fused_kernel(AttnArgs a)
     v4i o[NO];
 #pragma unroll
     for (int ct = 0; ct < NO; ++ct) o[ct] = (v4i){0, 0, 0, 0};
-    const int src = lane & 15, ii = src >> 1;
-    int vbase[2];
-    const char *paddr[2];
+    // Lane (g, src) supplies the V rows of the chunk's slots s = g*16 + ii and s + 8, and their codes.  (8 slots on is
+    // 8 / NIT rows of the stage on, 64 bytes of codes on: instruction offsets; the swizzled places of the column tiles
+    // are worked out once.)
+    const int src = lane & 15, ii = src >> 1, slot0 = g * 16 + ii;
+    constexpr int ROWS8 = 8 / NIT * ROWB;
+    const char *vaddr[NITW];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int s = g * 16 + 8 * h + ii;   // slot within the chunk supplied by this lane
-        const int i = s % NIT, r = s / NIT;
-        vbase[h] = i * 1024 + r * ROWB + (((NITW * w) ^ i) * 16) + 8 * (src & 1);
-        // lanes 2t and 2t+1 supply the 8-byte pieces that end up in MFMA rows 0..7 and 8..15: the
-        // codes and 8 zero bytes (PB 8), or the high and the low plane of the codes (PB 16)
-        if (PB == 16) paddr[h] = Pl + s * 8 + (src & 1) * PSTRIDE;
-        else paddr[h] = (src & 1) ? zeros : Pl + s * 8;
-    }
+    for (int ct = 0; ct < NITW; ++ct)
+        vaddr[ct] = stage + (slot0 % NIT) * 1024 + (slot0 / NIT) * ROWB + (((NITW * w + ct) ^ (slot0 % NIT)) * 16) + 8 * (src & 1);
+    // lanes 2t and 2t+1 supply the 8-byte pieces that end up in MFMA rows 0..7 and 8..15: the
+    // codes and 8 zero bytes (PB 8; they do not move from chunk to chunk), or the high and the low plane of the codes (PB 16)
+    const char *paddr = (PB == 8 && (src & 1)) ? zeros : Pl + slot0 * 8 + (src & 1) * PSTRIDE;
+    const int pstep = (SMALLP || (PB == 8 && (src & 1))) ? 0 : 512;
+    char *const code_at = Pl + ((g >> 1) * 16 + j) * 8 + 4 * (g & 1); // codes of tile pair pr: 256 * pr on
+    // p / s_p stays within the largest code unless s_p is below its reciprocal
+    const bool cap = a.inv_s_p > (PB == 8 ? 127.f : 32639.f);
     static_for<MAXCH>([&](auto C) {
         constexpr int c = C;
         const int gc = ks + c * KS;
         if (LOCKSTEP && c >= nloc) { // a pass of waiting only
-            if (c < npass) acquire(Vg, gc);
+            if (c < npass) acquire(Vg, gc, (c + 1) % NST);
             return;
         }
         if (c < nloc) {
             // Codes of this chunk's slots (tile*16 + j), rows 4*(g&1) .. +3: one 32-bit LDS write
-            // per tile.  v_cvt_pk_u8_f32 rounds to nearest even and drops the byte into place; the
-            // largest code is 127 (p / s_p exceeds it when s_p < 1/127), hence the minimum.
-            // Done here, chunk by chunk, so that this ALU work overlaps the V copies in flight.
+            // per tile and plane.  Done here, chunk by chunk, so that this ALU work overlaps the V copies in flight.
+            auto make_codes = [&](auto Cap) {
+                constexpr bool CAP = decltype(Cap)::value;
 #pragma unroll
-            for (int pr = 0; pr < 2; ++pr) {
-                const int slot = (SMALLP ? 0 : c * MC_CHUNK) + (2 * pr + (g >> 1)) * 16 + j;
-                if (PB == 8) {
-                    unsigned packed = 0;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) packed = __builtin_amdgcn_cvt_pk_u8_f32(fminf(x[2 * c + pr][r] * rinv[r], 127.f), r, packed);
-                    *reinterpret_cast<unsigned *>(Pl + slot * 8 + 4 * (g & 1)) = packed;
-                } else {
-                    // code = clamp(rint(e * rinv), 0, 32639) (ties to even), hi = (code + 128) >> 8 in
-                    // [0, 127], lo = code - 256 * hi in [-128, 127]: its low byte as it is
-                    unsigned hi = 0, lo = 0;
+                for (int pr = 0; pr < 2; ++pr) {
+                    float y[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int code = (int)__builtin_rintf(fminf(x[2 * c + pr][r] * rinv[r], 32639.f));
-                        hi |= (unsigned)((code + 128) >> 8) << (8 * r);
-                        lo |= (unsigned)(code & 255) << (8 * r);
+                        y[r] = x[2 * c + pr][r] * rinv[r];
+                        if (CAP) y[r] = fminf(y[r], PB == 8 ? 127.f : 32639.f);
                     }
-                    *reinterpret_cast<unsigned *>(Pl + slot * 8 + 4 * (g & 1)) = hi;
-                    *reinterpret_cast<unsigned *>(Pl + PSTRIDE + slot * 8 + 4 * (g & 1)) = lo;
+                    char *to = code_at + (SMALLP ? 0 : c * 512) + pr * 256;
+                    if (PB == 8) {
+                        // v_cvt_pk_u8_f32 rounds to nearest even and drops the byte into place
+                        unsigned packed = 0;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) packed = __builtin_amdgcn_cvt_pk_u8_f32(y[r], r, packed);
+                        *reinterpret_cast<unsigned *>(to) = packed;
+                    } else {
+                        // code = rint(y), ties to even, hi = (code + 128) >> 8 in [0, 127], lo = code - 256 * hi in [-128, 127]:
+                        // the code's low byte as it is.  Adding 1.5 * 2^23 rounds to an integer and leaves it in the low
+                        // half of the word; four codes are then split two at a time.  (18 instructions for four codes, it
+                        // was 36: 8 heads x 4096, batch 8, 16-bit codes 107 -> 99 us.)
+                        unsigned u[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            asm("" : "+v"(y[r])); // (the product is rounded before the sum is)
+                            u[r] = __builtin_bit_cast(unsigned, y[r] + 12582912.f);
+                        }
+                        const unsigned c01 = __builtin_amdgcn_perm(u[1], u[0], 0x05040100), c23 = __builtin_amdgcn_perm(u[3], u[2], 0x05040100);
+                        *reinterpret_cast<unsigned *>(to) = __builtin_amdgcn_perm(c23 + 0x00800080u, c01 + 0x00800080u, 0x07050301);
+                        *reinterpret_cast<unsigned *>(to + PSTRIDE) = __builtin_amdgcn_perm(c23, c01, 0x06040200);
+                    }
                 }
-            }
-            acquire(Vg, gc);
+            };
+            if (cap) make_codes(std::true_type{});
+            else make_codes(std::false_type{});
+            acquire(Vg, gc, (c + 1) % NST);
             // the codes, transposed to the MFMA row operand: row j < 8, slots g*16 .. +15
-            const int pstep = (SMALLP || (PB == 8 && (src & 1))) ? 0 : c * 512; // the zero bytes do not move
-            const v2i p0 = lds_read_tr8(paddr[0] + pstep), p1 = lds_read_tr8(paddr[1] + pstep);
+            const char *pa = paddr + c * pstep;
+            const v2i p0 = lds_read_tr8(pa), p1 = lds_read_tr8(pa + 64);
             v2i d[NITW][2];
 #pragma unroll
             for (int ct = 0; ct < NITW; ++ct) {
-                d[ct][0] = lds_read_tr8(stage + (c % NST) * STG + (vbase[0] ^ (ct * 16)));
-                d[ct][1] = lds_read_tr8(stage + (c % NST) * STG + (vbase[1] ^ (ct * 16)));
+                d[ct][0] = lds_read_tr8(vaddr[ct] + (c % NST) * STG);
+                d[ct][1] = lds_read_tr8(vaddr[ct] + (c % NST) * STG + ROWS8);
             }
             release(Vg, gc);
             const v4i aop = {p0.x, p0.y, p1.x, p1.y};
@@ -500,5 +536,15 @@ void attention_fused_kernel(AttnArgs a)
     }
 }
 
+
+template <int HPW, int PB, int QB, int KS, int DK, bool PAD> hipError_t launch_pairs(AttnArgs a, hipStream_t s)
+{
+    const unsigned pairs = (unsigned)(a.heads / HPW) * (unsigned)a.batch;
+    a.pair_shift = pairs % 8 == 0 ? 3 : (pairs % 4 == 0 ? 2 : (pairs % 2 == 0 ? 1 : 0));
+    const unsigned rows = pairs >> a.pair_shift, y = rows < 32768 ? rows : 32768;
+    hipLaunchKernelGGL((attention_fused_kernel<8, HPW, PB, QB, KS, DK, PAD>), dim3((unsigned)a.P << a.pair_shift, y, (rows + y - 1) / y),
+                       dim3(64 * HPW * KS), 0, s, a);
+    return hipGetLastError();
+}
 
 } // namespace

@@ -11,21 +11,17 @@ template <int PB, int QB, int DK> hipError_t launch_pq(const AttnArgs &a, int he
         // bytes: one head per workgroup)
         if constexpr ((PB == 16 && QB == 4) || (DK == 128 && QB == 8)) return hipErrorInvalidValue;
         else {
-            const dim3 grid((unsigned)a.P * (unsigned)(a.heads / 2), (unsigned)a.batch);
-            if (waves_per_panel == 4) hipLaunchKernelGGL((attention_fused_kernel<8, 2, PB, QB, 4, DK>), grid, dim3(512), 0, s, a);
-            else if (waves_per_panel == 2) hipLaunchKernelGGL((attention_fused_kernel<8, 2, PB, QB, 2, DK>), grid, dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((attention_fused_kernel<8, 2, PB, QB, 1, DK>), grid, dim3(128), 0, s, a);
+            if (waves_per_panel == 4) return launch_pairs<2, PB, QB, 4, DK, false>(a, s);
+            if (waves_per_panel == 2) return launch_pairs<2, PB, QB, 2, DK, false>(a, s);
+            return launch_pairs<2, PB, QB, 1, DK, false>(a, s);
         }
-    } else if (waves_per_panel == 8) {
-        hipLaunchKernelGGL((attention_fused_kernel<8, 1, PB, QB, 8, DK>), dim3((unsigned)a.P * (unsigned)a.heads, (unsigned)a.batch), dim3(512), 0, s, a);
-    } else if (waves_per_panel == 4) {
-        hipLaunchKernelGGL((attention_fused_kernel<8, 1, PB, QB, 4, DK>), dim3((unsigned)a.P * (unsigned)a.heads, (unsigned)a.batch), dim3(256), 0, s, a);
-    } else if (waves_per_panel == 2) {
-        hipLaunchKernelGGL((attention_fused_kernel<8, 1, PB, QB, 2, DK>), dim3((unsigned)a.P * (unsigned)a.heads, (unsigned)a.batch), dim3(128), 0, s, a);
-    } else {
-        hipLaunchKernelGGL((attention_fused_kernel<8, 1, PB, QB, 1, DK>), dim3((unsigned)a.P * (unsigned)a.heads, (unsigned)a.batch), dim3(64), 0, s, a);
     }
-    return hipGetLastError();
+    switch (waves_per_panel) {
+    case 8: return launch_pairs<1, PB, QB, 8, DK, false>(a, s);
+    case 4: return launch_pairs<1, PB, QB, 4, DK, false>(a, s);
+    case 2: return launch_pairs<1, PB, QB, 2, DK, false>(a, s);
+    default: return launch_pairs<1, PB, QB, 1, DK, false>(a, s);
+    }
 }
 
 // waves_per_panel: 1, 2, 4 or 8 waves share the chunks of one (panel, head) (8: one head per workgroup only); a wave
