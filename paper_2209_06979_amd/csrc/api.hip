@@ -110,7 +110,7 @@ void free_device(mc_mat *A)
     if (A->d_splits) (void)hipFree(A->d_splits);
     if (A->d_class_panels) (void)hipFree(A->d_class_panels);
     if (A->d_merge_src) (void)hipFree(A->d_merge_src);
-    if (A->d_merge_vals) (void)hipFree(A->d_merge_vals);
+    if (A->d_chunk_panel) (void)hipFree(A->d_chunk_panel);
     if (A->merged) {
         free_device(A->merged);
         delete A->merged;
@@ -419,7 +419,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     A->blk_nt = A->block_rows = A->nblk = 0; A->blk_chunks = 0; A->blk_valid = false; A->d_order = A->d_splits = nullptr;
     A->d_blk_ptr = nullptr; A->d_blk_recs = nullptr; A->d_blk_ends = nullptr; A->d_blk_src = nullptr;
     A->d_class_panels = nullptr;
-    A->merged = nullptr; A->merge_group = 0; A->d_merge_src = nullptr; A->d_merge_vals = nullptr; A->merged_valid = false;
+    A->merged = nullptr; A->merge_group = 0; A->d_merge_src = nullptr; A->d_chunk_panel = nullptr; A->merged_valid = false;
     // Length classes of the panels (V = 8: the attention kernel gives a panel 1, 2, 4 or 8 waves)
     std::vector<int32_t> class_panels;
     for (int b = 0; b <= 4; ++b) A->class_start[b] = 0;
@@ -496,7 +496,6 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     // 8-bit values) or 8 rows (two byte planes), see mc_merge_host.  Not for operands without vectors, and not
     // when the thread's options rule it out.
     std::vector<int32_t> m_src;
-    int64_t m_vals_bytes = 0;
     if (!child && lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_merge != -1) {
         const int rows = (lhs_bits == 4 || lhs_bits == 8) ? 16 : 8, group = rows / V;
         mc_merged_layout ml;
@@ -526,7 +525,6 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
                 return rc;
             }
             A->merge_group = group;
-            m_vals_bytes = (int64_t)m_values.size();
         }
     }
     // LDS-ordered copy for the SpMM that keeps rows of B resident in LDS, where that form is expected to be the fastest one
@@ -588,6 +586,20 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         MC_TRY(hipMemcpyAsync(A->d_slot_idx, slot_idx.data(), sizeof(int32_t) * (size_t)lay.nslots, hipMemcpyHostToDevice, s));
     if (lay.vals_bytes)
         MC_TRY(hipMemcpyAsync(A->d_vals, vals.data(), (size_t)lay.vals_bytes, hipMemcpyHostToDevice, s));
+    std::vector<int32_t> chunk_panel;
+    if (lhs_bits != 0 && lay.nslots) {
+        try {
+            chunk_panel.resize((size_t)(lay.nslots / MC_CHUNK));
+        } catch (const std::bad_alloc &) {
+            free_device(A);
+            delete A;
+            return MC_ENOMEM;
+        }
+        for (int p = 0; p < lay.P; ++p)
+            for (int c = panel_ptr[2 * (size_t)p] / MC_CHUNK, e = (panel_ptr[2 * (size_t)p + 1] + MC_CHUNK - 1) / MC_CHUNK; c < e; ++c) chunk_panel[(size_t)c] = p;
+        MC_TRY(hipMalloc(&A->d_chunk_panel, sizeof(int32_t) * chunk_panel.size()));
+        MC_TRY(hipMemcpyAsync(A->d_chunk_panel, chunk_panel.data(), sizeof(int32_t) * chunk_panel.size(), hipMemcpyHostToDevice, s));
+    }
     if (A->n_items) {
         MC_TRY(hipMalloc(&A->d_items, sizeof(int32_t) * items.size()));
         MC_TRY(hipMalloc(&A->d_split_panels, sizeof(int32_t) * split_panels.size()));
@@ -620,7 +632,6 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     }
     if (A->merged) {
         MC_TRY(hipMalloc(&A->d_merge_src, sizeof(int32_t) * m_src.size()));
-        MC_TRY(hipMalloc(&A->d_merge_vals, (size_t)m_vals_bytes));
         MC_TRY(hipMemcpyAsync(A->d_merge_src, m_src.data(), sizeof(int32_t) * m_src.size(), hipMemcpyHostToDevice, s));
         A->merged_valid = true;
     }
@@ -676,22 +687,25 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
     if (A->nslots == 0) return MC_OK;              // no stored vector: nothing to replace
     if (!values_dev) return MC_EINVAL;
     if (!on_device_of(A)) return MC_EINVAL;
-    RepackArgs r;
-    r.panel_ptr = A->d_panel_ptr; r.row_ptr = A->d_row_ptr;
-    r.src = static_cast<const uint8_t *>(values_dev); r.src_batch_stride = 0;
-    r.dst = A->d_vals; r.dst_batch_stride = 0;
-    r.P = A->P; r.V = A->V; r.bits = (A->lhs_bits == 12) ? 16 : A->lhs_bits; r.batch = 1;
-    MC_HIP(launch_repack(r, static_cast<hipStream_t>(stream)));
-    if (A->d_blk_recs) { // the LDS-ordered copy follows
-        MC_HIP(launch_repack_blocked(A->d_blk_src, r.src, A->d_blk_recs, A->blk_chunks, A->V, r.bits, static_cast<hipStream_t>(stream)));
-        A->blk_valid = true;
+    ValuesArgs a = {};
+    a.src = static_cast<const uint8_t *>(values_dev);
+    a.V = A->V; a.bits = (A->lhs_bits == 12) ? 16 : A->lhs_bits;
+    for (mc_mat *X : {A, A->merged}) {
+        if (!X) continue;
+        const int32_t *merge_src = X == A ? nullptr : A->d_merge_src;
+        const int chunk_bytes = MC_CHUNK * X->V * a.bits / 8;
+        ValuesJob &panels = a.job[a.njobs++];
+        panels = {X->d_chunk_panel, X->d_panel_ptr, X->d_row_ptr, nullptr, merge_src, static_cast<uint8_t *>(X->d_vals), X->nslots / MC_CHUNK,
+                  chunk_bytes, 0, X->V, 0};
+        if (X->d_blk_recs) { // the LDS-ordered copy follows
+            ValuesJob &copy = a.job[a.njobs++];
+            copy = {nullptr, nullptr, nullptr, X->d_blk_src, merge_src, X->d_blk_recs, X->blk_chunks, resident_rec_bytes(X), 2 * MC_CHUNK, X->V, 0};
+        }
     }
-    if (A->merged) { // and the merged copy: its values in interchange order first, then its own formats
-        const int vb = A->V * r.bits / 8;
-        MC_HIP(launch_merge_values(A->d_merge_src, r.src, A->d_merge_vals, A->merged->nvec * A->merge_group, vb,
-                                   static_cast<hipStream_t>(stream)));
-        const int rc = mc_mat_set_values_device(A->merged, A->d_merge_vals, stream);
-        if (rc != MC_OK) return rc;
+    MC_HIP(launch_set_values(a, static_cast<hipStream_t>(stream)));
+    A->blk_valid = A->d_blk_recs != nullptr;
+    if (A->merged) {
+        A->merged->blk_valid = A->merged->d_blk_recs != nullptr;
         A->merged_valid = true;
     }
     return MC_OK;

@@ -49,7 +49,7 @@ struct mc_mat {
     mc_mat *merged;
     int merge_group;
     int32_t *d_merge_src;      // merged nvec * merge_group: interchange vector of each panel's share, -1 = zeros
-    uint8_t *d_merge_vals;     // staging for mc_mat_set_values_device: the merged operand's values in interchange order
+    int32_t *d_chunk_panel;    // panel of each chunk of the panel format (operands with values)
     bool merged_valid;         // false once the values were replaced in the panel format only
 };
 
@@ -184,14 +184,19 @@ struct SoftmaxArgs {
     int variant;               // 0: automatic; 1: a workgroup per panel even for short panels; 2: the any-length kernel
 };
 
-struct RepackArgs {
-    const int32_t *panel_ptr;
-    const int32_t *row_ptr;
-    const uint8_t *src;        // interchange order values
-    int64_t src_batch_stride;  // bytes
-    uint8_t *dst;              // device-format values
-    int64_t dst_batch_stride;  // bytes
-    int P, V, bits, batch;
+// One device format that receives an operand's new values.
+struct ValuesJob {
+    const int32_t *chunk_panel, *panel_ptr, *row_ptr; // panels: the panel of each chunk, its slots, its first stored vector
+    const int32_t *blk_src;    // LDS-ordered copy (else null): the stored vector of each slot, -1 for padding
+    const int32_t *merge_src;  // merged copy (else null): the operand's own vector behind each share of a merged vector, -1: zeros
+    uint8_t *dst;              // chunk c's values at c * rec_bytes + head_bytes
+    int64_t nchunks;
+    int rec_bytes, head_bytes, V, first_block;
+};
+struct ValuesArgs {
+    const uint8_t *src;        // interchange order, V values of `bits` per vector
+    int V, bits, njobs;
+    ValuesJob job[4];
 };
 
 // Fused attention for head dimension 64.  Element (head h, token l, d) of Q, Km, Vm (int8)
@@ -220,8 +225,7 @@ hipError_t launch_spmm(mc_prec prec, const SpmmArgs &a, int bnb, int waves, hipS
 hipError_t launch_spmm_phase_probe(const SpmmArgs &a, hipStream_t s);
 // nt: segments (16 bytes) of a column tile, 2 or 4, at most a.nt.  Precisions with a 16-bit B are not built.
 hipError_t launch_spmm_slab(mc_prec prec, const SlabArgs &a, int nt, hipStream_t s);
-hipError_t launch_repack_blocked(const int32_t *blk_src, const uint8_t *src, uint8_t *recs, int64_t nchunks, int V, int bits,
-                                 hipStream_t s);
+hipError_t launch_set_values(ValuesArgs a, hipStream_t s);
 // clears the C rows (int32, n columns) of the listed panels
 hipError_t launch_zero_rows(int32_t *C, int64_t ldc, int n, int V, const int32_t *panels, int n_panels, hipStream_t s);
 hipError_t launch_zero_ints(int32_t *p, int64_t n, hipStream_t s); // n a multiple of 4, p 16-byte aligned
@@ -241,10 +245,8 @@ hipError_t launch_scores_softmax(const ScoresArgs &a, int qkv_bits, int code_bit
 int scores_softmax_max_npad(int row_bytes, int waves);
 hipError_t launch_absmax(const float *x, int64_t n, float *result, hipStream_t s);
 hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uint8_t *q, hipStream_t s);
-hipError_t launch_repack(const RepackArgs &a, hipStream_t s);
 // values of a merged operand in interchange order from the original operand's: share (i, g) of vb bytes = vector
 // merge_src[i * group + g] of src, or zeros
-hipError_t launch_merge_values(const int32_t *merge_src, const uint8_t *src, uint8_t *dst, int64_t shares, int vb, hipStream_t s);
 // dk is 64 or 128.  heads_per_group 2 needs head_stride == dk (token-major layout), rows of at most 64
 // bytes and an even head count, and is not available for 16-bit codes with 4-bit inputs
 hipError_t launch_attention_fused(const AttnArgs &a, int heads_per_group, int waves_per_panel, int p_bits, int qkv_bits,

@@ -497,56 +497,6 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_unsigned_kernel(SddmmA
     }
 }
 
-// ---- interchange-order values -> device panel format -------------------------------
-// One workgroup per (panel, batch); a thread handles one padded slot (8/16 bit) or the
-// slot pair (b, b+8) that shares bytes (4 bit).
-__global__ __launch_bounds__(256) void repack_kernel(RepackArgs a)
-{
-    const int panel = blockIdx.x, batch = blockIdx.y, V = a.V;
-    const int s0 = a.panel_ptr[2 * panel], n = a.panel_ptr[2 * panel + 1] - s0;
-    const int npad = (n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK;
-    const uint8_t *src = a.src + (int64_t)batch * a.src_batch_stride;
-    uint8_t *dst = a.dst + (int64_t)batch * a.dst_batch_stride;
-    const int64_t vec0 = a.row_ptr[panel];
-    if (a.bits == 8 || a.bits == 16) {
-        const int cbytes = MC_CHUNK * V * a.bits / 8;
-        for (int i = threadIdx.x; i < npad; i += 256) {
-            const int s = s0 + i, g = (i % MC_CHUNK) / 16, b = i % 16;
-            uint8_t *chunk = dst + (int64_t)(s / MC_CHUNK) * cbytes;
-            for (int v = 0; v < V; ++v) {
-                if (a.bits == 8) {
-                    chunk[g * (16 * V) + v * 16 + b] = (i < n) ? src[(vec0 + i) * V + v] : (uint8_t)0;
-                } else {
-                    const int x = (i < n) ? reinterpret_cast<const int16_t *>(src)[(vec0 + i) * V + v] : 0;
-                    const int hi = (x + 128) >> 8, lo = x - hi * 256;
-                    chunk[g * (32 * V) + v * 16 + b] = (uint8_t)hi;
-                    chunk[g * (32 * V) + 16 * V + v * 16 + b] = (uint8_t)lo;
-                }
-            }
-        }
-    } else { // 4 bits
-        const int cbytes = MC_CHUNK * V / 2;
-        for (int i2 = threadIdx.x; i2 < npad / 2; i2 += 256) {
-            // pair index i2 -> (chunk, g, b < 8): slots i_lo = .. + b and i_hi = i_lo + 8
-            const int ch = i2 / 32, g = (i2 % 32) / 8, b = i2 % 8;
-            const int i_lo = ch * MC_CHUNK + g * 16 + b, i_hi = i_lo + 8;
-            uint8_t *chunk = dst + (int64_t)(s0 / MC_CHUNK + ch) * cbytes;
-            for (int v = 0; v < V; ++v) {
-                int nl = 0, nh = 0;
-                if (i_lo < n) {
-                    const int64_t e = (vec0 + i_lo) * V + v;
-                    nl = (src[e >> 1] >> ((e & 1) * 4)) & 15;
-                }
-                if (i_hi < n) {
-                    const int64_t e = (vec0 + i_hi) * V + v;
-                    nh = (src[e >> 1] >> ((e & 1) * 4)) & 15;
-                }
-                chunk[g * (8 * V) + v * 8 + b] = (uint8_t)(nl | (nh << 4));
-            }
-        }
-    }
-}
-
 } // namespace
 
 template <int PB, int LPR, bool DQ, bool U> hipError_t launch_staged(const SddmmArgs &a, int waves, hipStream_t s)
@@ -609,30 +559,4 @@ hipError_t launch_sddmm(int bits, const SddmmArgs &a, int waves, hipStream_t s)
 {
     if (a.P == 0 || a.batch == 0) return hipSuccess;
     return a.float_out ? launch_sddmm_out<true>(bits, a, waves, s) : launch_sddmm_out<false>(bits, a, waves, s);
-}
-
-hipError_t launch_repack(const RepackArgs &a, hipStream_t s)
-{
-    if (a.P == 0 || a.batch == 0) return hipSuccess;
-    dim3 grid((unsigned)a.P, (unsigned)a.batch), block(256);
-    hipLaunchKernelGGL(repack_kernel, grid, block, 0, s, a);
-    return hipGetLastError();
-}
-
-namespace {
-// One thread per share (merged vector i, panel g of its group): vb bytes copied from the vector that fills it, or zeros.
-__global__ __launch_bounds__(256) void merge_values_kernel(const int32_t *merge_src, const uint8_t *src, uint8_t *dst, int64_t shares, int vb)
-{
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= shares) return;
-    const int64_t from = merge_src[t];
-    for (int b = 0; b < vb; ++b) dst[t * vb + b] = (from >= 0) ? src[from * vb + b] : (uint8_t)0;
-}
-} // namespace
-
-hipError_t launch_merge_values(const int32_t *merge_src, const uint8_t *src, uint8_t *dst, int64_t shares, int vb, hipStream_t s)
-{
-    if (shares == 0) return hipSuccess;
-    hipLaunchKernelGGL(merge_values_kernel, dim3((unsigned)((shares + 255) / 256)), dim3(256), 0, s, merge_src, src, dst, shares, vb);
-    return hipGetLastError();
 }

@@ -410,43 +410,6 @@ template <int LB, bool R4> hipError_t launch_nt(const SlabArgs &a, int nt, hipSt
     return launch_walk<LB, R4, 2>(a, s);
 }
 
-// values in interchange order -> the values of the copy's records, one thread per slot (8 / 16 bits) or per pair of
-// slots (b, b + 8) that share bytes (4 bits)
-__global__ __launch_bounds__(256) void repack_blocked_kernel(const int32_t *blk_src, const uint8_t *src, uint8_t *recs, int64_t nchunks,
-                                                             int V, int bits)
-{
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int rec_bytes = 2 * MC_CHUNK + MC_CHUNK * V * bits / 8;
-    if (bits == 8 || bits == 16) {
-        if (t >= nchunks * MC_CHUNK) return;
-        const int i = (int)(t % MC_CHUNK), g = i / 16, b = i % 16;
-        const int64_t vec = blk_src[t];
-        uint8_t *chunk = recs + (t / MC_CHUNK) * rec_bytes + 2 * MC_CHUNK;
-        for (int v = 0; v < V; ++v) {
-            if (bits == 8) {
-                chunk[g * (16 * V) + v * 16 + b] = (vec >= 0) ? src[vec * V + v] : (uint8_t)0;
-            } else {
-                const int x = (vec >= 0) ? reinterpret_cast<const int16_t *>(src)[vec * V + v] : 0;
-                const int hi = (x + 128) >> 8, lo = x - hi * 256;
-                chunk[g * (32 * V) + v * 16 + b] = (uint8_t)hi;
-                chunk[g * (32 * V) + 16 * V + v * 16 + b] = (uint8_t)lo;
-            }
-        }
-    } else {
-        if (t >= nchunks * (MC_CHUNK / 2)) return;
-        const int64_t ch = t / 32;
-        const int g = (int)(t % 32) / 8, b = (int)(t % 8);
-        const int64_t v_lo = blk_src[ch * MC_CHUNK + g * 16 + b], v_hi = blk_src[ch * MC_CHUNK + g * 16 + b + 8];
-        uint8_t *chunk = recs + ch * rec_bytes + 2 * MC_CHUNK;
-        for (int v = 0; v < V; ++v) {
-            int nl = 0, nh = 0;
-            if (v_lo >= 0) { const int64_t e = v_lo * V + v; nl = (src[e >> 1] >> ((e & 1) * 4)) & 15; }
-            if (v_hi >= 0) { const int64_t e = v_hi * V + v; nh = (src[e >> 1] >> ((e & 1) * 4)) & 15; }
-            chunk[g * (8 * V) + v * 8 + b] = (uint8_t)(nl | (nh << 4));
-        }
-    }
-}
-
 } // namespace
 
 hipError_t launch_spmm_slab(mc_prec prec, const SlabArgs &a, int nt, hipStream_t s)
@@ -461,13 +424,4 @@ hipError_t launch_spmm_slab(mc_prec prec, const SlabArgs &a, int nt, hipStream_t
     case MC_L12R4: return launch_nt<16, true>(a, nt, s);
     default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_repack_blocked(const int32_t *blk_src, const uint8_t *src, uint8_t *recs, int64_t nchunks, int V, int bits,
-                                 hipStream_t s)
-{
-    if (nchunks == 0) return hipSuccess;
-    const int64_t threads = nchunks * (bits == 4 ? MC_CHUNK / 2 : MC_CHUNK);
-    hipLaunchKernelGGL(repack_blocked_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, blk_src, src, recs, nchunks, V, bits);
-    return hipGetLastError();
 }
