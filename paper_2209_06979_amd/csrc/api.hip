@@ -1248,8 +1248,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
     if (!on_device_of(mask)) return MC_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    if (attention_is_fused(mask, dk, qkv_bits, o)) {
-        const int tile = dk <= 64 ? 64 : 128;     // the kernel's head dimension
+    auto fused = [&](int tile) -> int {           // tile: the kernel's head dimension
         AttnArgs f = {};
         f.real_pieces = dk * qkv_bits / 8 / 16; f.out_cols = dk;
         f.panel_ptr = mask->d_panel_ptr; f.slot_idx = mask->d_slot_idx;
@@ -1264,7 +1263,8 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         // gather 128 bytes per token (not for 16-bit codes with 4-bit inputs, whose output tile does not fit
         // that kernel's stages)
         const bool short_rows = dk == 64 || qkv_bits == 4;
-        const bool pairs = dk == tile && short_rows && head_stride == dk && heads % 2 == 0 && !(p_bits == 16 && qkv_bits == 4);
+        const bool fills = dk == tile && tile <= 128; // (the tile of 192 is a padded one)
+        const bool pairs = fills && short_rows && head_stride == dk && heads % 2 == 0 && !(p_bits == 16 && qkv_bits == 4);
         const double avg = mask->P ? (double)(mask->nslots / MC_CHUNK) / mask->P : 0.0;
         // One launch for the panels in `list` (null: all), none of which has more than max_chunks chunks.
         auto launch = [&](const int32_t *list, int n_panels, int max_chunks) -> hipError_t {
@@ -1279,13 +1279,15 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 // has a chunk (256 units of 7 chunks: 5.9 us with one wave each, 4.5 us with four).
                 const int64_t units = (int64_t)n_panels * heads * batch;
                 hpg = (pairs && units >= 2048 && wpp < 8) ? 2 : 1;
-                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp * 2 <= avg) wpp *= 2;
+                // (rows of 256 bytes: four waves' stages take half a compute unit's LDS)
+                const int64_t in_flight = tile == 192 && qkv_bits == 8 ? 1024 : 2048;
+                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= in_flight && wpp * 2 <= avg) wpp *= 2;
             } else {
                 if (o.attention_mode == 3 && wpp < 2) wpp = 2;
                 if (o.attention_mode == 4 && wpp < 4) wpp = 4;
                 hpg = (o.attention_mode != 2 && pairs && wpp < 8) ? 2 : 1;
             }
-            if (dk == tile) return launch_attention_fused(f, hpg, wpp, p_bits, qkv_bits, dk, s);
+            if (fills) return launch_attention_fused(f, hpg, wpp, p_bits, qkv_bits, dk, s);
             return launch_attention_fused_padded(f, wpp, p_bits, qkv_bits, tile, s);
         };
         // Panels of very different lengths (the longest at least twice the average and more than one wave's
@@ -1300,7 +1302,8 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
             MC_HIP(launch(nullptr, mask->P, mask->max_panel_chunks));
         }
         return MC_OK;
-    }
+    };
+    if (attention_is_fused(mask, dk, qkv_bits, o)) return fused(dk <= 64 ? 64 : 128);
     // the kernel pipeline keeps its intermediates in a workspace (none are needed when nothing is stored)
     const bool with_scores = scores_kernel_waves(mask, heads, dk, qkv_bits, o) == 0;
     const size_t need = attn_layout(heads, mask, p_bits, with_scores).total;
@@ -1320,6 +1323,10 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         if ((reinterpret_cast<uintptr_t>(workspace_dev) & 255u) != 0) return MC_EALIGN;
         if (workspace_bytes < need) return MC_ENOMEM;
     }
+    // Head dimensions up to 192 have a fused form, too, for panels that four waves can share; it needs no workspace, but what
+    // callers give is what the pipeline needs, and the layer of callers without memory of their own stays the pipeline.  One
+    // launch for all batch items against two for each: batch 8, 8 heads x 616, dk = 160, 87 % empty: 98 -> 25 us.
+    if (!use_static && o.attention_mode == 0 && dk <= 192 && (dk * qkv_bits / 8) % 16 == 0 && mask->max_panel_chunks <= 32) return fused(192);
     // the batch items run one after the other through the same workspace
     for (int b = 0; b < batch; ++b) {
         const int64_t ib = (int64_t)b * batch_stride * qkv_bits / 8;

@@ -1,5 +1,5 @@
 // Launchers of the fused attention kernel for head dimensions that do not fill its tile of 64 or 128
-// elements (any multiple of 16; of 32 for 4-bit inputs): one head per workgroup, the missing pieces of
+// elements, and of up to 192 (any multiple of 16; of 32 for 4-bit inputs): one head per workgroup, the missing pieces of
 // every row read as zeros (see PAD in attention_fused.h).
 #include "attention_fused.h"
 
@@ -7,7 +7,9 @@ namespace {
 template <int PB, int QB, int DK> hipError_t launch_padded(const AttnArgs &a, int waves_per_panel, hipStream_t s)
 {
     switch (waves_per_panel) {
-    case 8: return launch_pairs<1, PB, QB, 8, DK, true>(a, s);
+    case 8:
+        if constexpr (DK == 192) return hipErrorInvalidValue; // (its eight stages and code areas would not fit LDS)
+        else return launch_pairs<1, PB, QB, 8, DK, true>(a, s);
     case 4: return launch_pairs<1, PB, QB, 4, DK, true>(a, s);
     case 2: return launch_pairs<1, PB, QB, 2, DK, true>(a, s);
     default: return launch_pairs<1, PB, QB, 1, DK, true>(a, s);
@@ -15,12 +17,19 @@ template <int PB, int QB, int DK> hipError_t launch_padded(const AttnArgs &a, in
 }
 } // namespace
 
-// tile: 64 or 128, the kernel's head dimension; a.real_pieces * 16 bytes is what a row really has
-// (fewer than tile * qkv_bits / 8), a.out_cols the real head dimension.
+// tile: 64, 128 or 192, the kernel's head dimension; a.real_pieces * 16 bytes is what a row really has
+// (fewer, with 192 at most, than tile * qkv_bits / 8), a.out_cols the real head dimension.
 hipError_t launch_attention_fused_padded(const AttnArgs &a, int waves_per_panel, int p_bits, int qkv_bits, int tile, hipStream_t s)
 {
     if (a.P == 0 || a.heads == 0 || a.batch == 0) return hipSuccess;
-    if (a.real_pieces <= 0 || a.real_pieces * 16 >= tile * qkv_bits / 8 || a.out_cols <= 0 || a.out_cols >= tile) return hipErrorInvalidValue;
+    if (a.real_pieces <= 0 || a.out_cols <= 0) return hipErrorInvalidValue;
+    if (tile == 192 ? (a.real_pieces * 16 > tile * qkv_bits / 8 || a.out_cols > tile)
+                    : (a.real_pieces * 16 >= tile * qkv_bits / 8 || a.out_cols >= tile))
+        return hipErrorInvalidValue;
+    if (tile == 192) {
+        if (p_bits == 16) return (qkv_bits == 4) ? launch_padded<16, 4, 192>(a, waves_per_panel, s) : launch_padded<16, 8, 192>(a, waves_per_panel, s);
+        return (qkv_bits == 4) ? launch_padded<8, 4, 192>(a, waves_per_panel, s) : launch_padded<8, 8, 192>(a, waves_per_panel, s);
+    }
     if (tile == 128) {
         if (p_bits == 16) return (qkv_bits == 4) ? launch_padded<16, 4, 128>(a, waves_per_panel, s) : launch_padded<16, 8, 128>(a, waves_per_panel, s);
         return (qkv_bits == 4) ? launch_padded<8, 4, 128>(a, waves_per_panel, s) : launch_padded<8, 8, 128>(a, waves_per_panel, s);
