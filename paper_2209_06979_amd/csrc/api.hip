@@ -542,7 +542,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
                 blk_ptr.resize((size_t)lay.P * rl.nblk + 1);
                 blk_src.resize((size_t)rl.nchunks * MC_CHUNK);
                 blk_ends.resize((size_t)resident_end_words(A));
-                blk_recs.resize((size_t)((rl.nchunks + RESIDENT_AHEAD) * resident_rec_bytes(A))); // (readers run ahead of the end)
+                blk_recs.resize((size_t)((rl.nchunks + RESIDENT_PADDING) * resident_rec_bytes(A))); // (readers run ahead of the end)
                 if (A->uniform_chunks == 0 && rl.nblk > 1) {
                     order.resize((size_t)lay.P);
                     for (int p = 0; p < lay.P; ++p) order[(size_t)p] = p;

@@ -30,7 +30,7 @@ struct mc_mat {
     int nblk;                  // K-blocks
     int64_t blk_chunks;        // chunks over all (panel, block) lists
     int32_t *d_blk_ptr;        // P*nblk + 1
-    uint8_t *d_blk_recs;       // blk_chunks records (and RESIDENT_AHEAD of zeros)
+    uint8_t *d_blk_recs;       // blk_chunks records (and RESIDENT_PADDING of zeros)
     uint32_t *d_blk_ends;      // nblk == 1: a bit per chunk, set where a panel ends (and two words of zeros)
     int32_t *d_blk_src;        // blk_chunks * 64: interchange vector of each slot, -1 for padding
     int32_t *d_order;          // nblk > 1: P panel numbers by falling length (null: all panels have the same number of chunks)
@@ -65,7 +65,19 @@ int mc_pack_host_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr,
 //   recs   nchunks records: 64 codes (uint16: (row / 16)*16*nt + row % 16, the place of the row's segment 0 in 16 bytes; the
 //          code of slot s at position (s/16)*16 + (s%8)*2 + (s%16)/8; padded slots name some row of the block), then the values in the layout of a chunk of mc_pack_host's slot_vals.  Zeroed by the caller.
 //   src    nchunks*64: interchange vector of each slot, -1 for padding
-constexpr int RESIDENT_AHEAD = 8;     // chunks of padding after the copy's device arrays (its readers run ahead)
+constexpr int RESIDENT_AHEAD = 8;     // records that a reader has requested ahead of its step, at most
+// A reader of n records requests `ahead` of them before its first step and one in every step, and takes whole turns of `ahead`
+// steps: this many in all, the surplus ones from what follows (the next reader's records, or the padding).
+constexpr int64_t resident_requests(int64_t n, int ahead) { return ahead + (n + ahead - 1) / ahead * ahead; }
+// Records of zeros after the copy: what the reader of its last records requests beyond them (most where one record is left
+// for the last turn).
+constexpr int RESIDENT_PADDING = 2 * RESIDENT_AHEAD - 1;
+constexpr bool resident_padding_suffices(int ahead)
+{
+    for (int n = 0; n <= 4 * ahead; ++n)
+        if (resident_requests(n, ahead) > n + RESIDENT_PADDING) return false;
+    return true;
+}
 constexpr int RESIDENT_SPLITS = 4096; // an operand with unequal panels has the first panel of every 1/4096 of its chunks listed
 struct ResidentLayout { int nt, block_rows, nblk; int64_t nchunks; };
 void mc_resident_query(int K, int P, const int32_t *row_ptr, const int32_t *col_idx, ResidentLayout *out);
@@ -115,7 +127,7 @@ struct SlabArgs {
     const int32_t *order, *splits; // see mc_mat
     int uniform_chunks;        // > 0: every panel has this many chunks (nblk == 1)
     int rec_bytes;             // bytes of a record
-    int64_t nchunks;           // records (RESIDENT_AHEAD more follow)
+    int64_t nchunks;           // records (RESIDENT_PADDING more follow)
     const uint8_t *B;
     int64_t ldb_bytes;
     int row_bytes, K;

@@ -44,7 +44,8 @@ typedef __attribute__((address_space(3))) void lptr_t;
 
 // Operands of a chunk (A values and row codes) are requested this many chunks ahead: they come from L2 or beyond, one
 // chunk step is far shorter than that latency, and the stores of a finished panel, which a wave's later loads queue up
-// behind, take longer still.  (As many as the registers allow; at most RESIDENT_AHEAD chunks of padding follow the copy.)
+// behind, take longer still.  (As many as the registers allow.  The last turn's surplus requests go beyond the wave's chunks,
+// at the end of the copy into its padding: resident_requests in internal.h counts them.)
 template <int LB, bool R4, int NT> constexpr int ahead = (R4 && NT == 4) ? (LB == 16 ? 2 : 4) : RESIDENT_AHEAD;
 constexpr int PFB = 3; // in the K-blocked form, whose accumulators need the registers
 
@@ -63,6 +64,7 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
     constexpr int NACC = NT * (R4 ? 2 : 1);              // accumulators (v4i) of one panel
     constexpr int SH = R4 ? (LB == 4 ? 8 : 4) : 0;       // scale carried by widened nibbles
     constexpr int PF = ahead<LB, R4, NT>, PPW = R4 ? 4 : 8;
+    static_assert(resident_padding_suffices(PF), "the walk stays inside the copy and its padding");
     const int float_out = OUT < 0 ? a.float_out : OUT;
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
@@ -103,12 +105,13 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
     // A record of the copy is a chunk's codes followed by its values.  A lane's word of codes: the LDS places (in 16 bytes)
     // of the rows in slots g*16 + ii (low half) and g*16 + 8 + ii.
     // Records are read through a buffer descriptor: a scalar offset moves from record to record, the lanes' offsets stay.
+    // (The descriptor's range check leaves the scalar offset out: what keeps a stream inside the copy is its padding.)
     const unsigned lane_r = (g * 8 + ii) * 4;
     const int v_of_j = (L16 ? (j & 7) : j) < a.V ? (L16 ? (j & 7) : j) : 0; // (columns beyond the panel's rows get a copy of row 0)
     const unsigned lane_a = 2 * MC_CHUNK + (L16 ? g * 32 * a.V + (j >> 3) * 16 * a.V + v_of_j * 16
                                                 : (LB == 4 ? g * 8 * a.V + v_of_j * 8 : g * 16 * a.V + v_of_j * 16));
     auto records_from = [&](int64_t chunk) {              // descriptor of the records from this one on
-        const int64_t left = (a.nchunks + RESIDENT_AHEAD - chunk) * a.rec_bytes;
+        const int64_t left = (a.nchunks + RESIDENT_PADDING - chunk) * a.rec_bytes;
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.recs) + chunk * a.rec_bytes, 0, (int)(left < 0x7fffffff ? left : 0x7fffffff),
                                                  0x00020000);
     };
