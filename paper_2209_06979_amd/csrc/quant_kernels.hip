@@ -15,81 +15,107 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 __global__ void absmax_init_kernel(float *result) { *result = 0.f; }
 
-// Scratch of a launch whose workgroups find their maximum together; the counters are zero between launches.  Each workgroup
-// leaves its maximum at a place of its own and counts itself in one of 16 counters, on lines of their own; the last of a
-// counter counts in the common one, and the last of all gathers.  (All at one address: 20 - 50 ns a workgroup, one after the other.)
-constexpr int ABSMAX_CELLS = 32, ABSMAX_GROUPS = 256, ABSMAX_COUNTERS = 16;
-struct AbsmaxCell {
-    unsigned max[ABSMAX_GROUPS];
-    unsigned done[ABSMAX_COUNTERS + 1][32];
-};
-__device__ AbsmaxCell absmax_cells[ABSMAX_CELLS];
+// Where the workgroups of a launch leave their maxima for the first one to gather: a row of words that hold the launch's number
+// above the 31 bits of a non-negative float.  A word only grows, and value and number arrive together, so that nothing else
+// has to be ordered: a word with this launch's number is this launch's maximum, a smaller one is still to come, and a larger one says
+// that a later launch has been given the same row (rows go round; launches of many streams can overtake each other).  The first
+// workgroup then reduces the whole tensor by itself, and so it does if the others have not run for a long while: it
+// never waits for good.  Nothing is tied to a stream, nothing has to be given back.
+constexpr int ABSMAX_ROWS = 64, ABSMAX_GROUPS = 256, ABSMAX_POLLS = 1 << 16;
+__device__ unsigned long long absmax_words[ABSMAX_ROWS][ABSMAX_GROUPS];
 
 // Workgroups of 1024 threads with four independent 16-byte loads in flight per lane, 64 KB a workgroup and turn; each
-// streams one contiguous span.  The loads are non-temporal (the tensor is read once).
-// ALONE: one workgroup has the whole tensor and writes the result.  Otherwise with cell >= 0 the workgroups
-// meet in absmax_cells[cell] and the last one writes the result; with cell < 0 they meet in the result
-// itself, which a kernel before this one has set to zero.
-// 8 MB: two launches, 15.2 -> one launch, 5.0 us; 1 MB: 9.4 -> 3.8 us; 64 MB 26 -> 14.5 us; 512 MB 80 -> 79 us (calls back to back).
-template <bool ALONE> __global__ __launch_bounds__(1024) void absmax_kernel(const float *x, int64_t n, float *result, int cell)
+// streams one contiguous span.  The loads are non-temporal.
+// ALONE: one workgroup has the whole tensor and writes the result.  Otherwise with a number the first workgroup
+// gathers what the others left in the number's row; without one (0) they meet in the result itself, which a kernel before this
+// one has set to zero.
+// Calls back to back: 1 MB 9.4 us as two launches, 4.1 in one; 8 MB 15.2 and 4.2; 24 MB 4.9, 64 MB 26 and 10.4; 512 MB 80 and 78 (6.9 TB/s).  With counters
+// of the workgroups that had left their maximum, ordered by waits, one launch took 4.3, 4.9, 6.1, 11.7 and 78.5 us, and with agent-scope
+// fences around the counting 5.4, 7.6, 9.6, 15.2 and 82.6.
+template <bool ALONE> __global__ __launch_bounds__(1024) void absmax_kernel(const float *x, int64_t n, float *result, unsigned long long number)
 {
     constexpr int U = 4;
     const v4f *xv = reinterpret_cast<const v4f *>(x);
     const int64_t nv = n / 4, per = ((nv + gridDim.x - 1) / gridDim.x + 63) & ~(int64_t)63; // (whole kilobytes)
-    const int64_t b = (int64_t)blockIdx.x * per, e = (b + per < nv) ? b + per : nv;
+    __shared__ float red[16];
+    __shared__ bool gathered;
     float m = 0.f;
     auto take = [&](v4f v) { m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)))); };
-    int64_t i = b + threadIdx.x;
-    for (; i + (U - 1) * 1024 < e; i += U * 1024) {
-        v4f v[U];
+    auto stream = [&](int64_t b, int64_t e) {
+        int64_t i = b + threadIdx.x;
+        for (; i + (U - 1) * 1024 < e; i += U * 1024) {
+            v4f v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(&xv[i + u * 1024]);
+            for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(&xv[i + u * 1024]);
 #pragma unroll
-        for (int u = 0; u < U; ++u) take(v[u]);
-    }
-    if (i < e) { // (the rest at once, too: what is beyond the end repeats the first element of this lane)
-        v4f v[U];
+            for (int u = 0; u < U; ++u) take(v[u]);
+        }
+        if (i < e) { // (the rest at once, too: what is beyond the end repeats the first element of this lane)
+            v4f v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(&xv[i + u * 1024 < e ? i + u * 1024 : i]);
+            for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(&xv[i + u * 1024 < e ? i + u * 1024 : i]);
 #pragma unroll
-        for (int u = 0; u < U; ++u) take(v[u]);
-    }
-    if (blockIdx.x == 0 && threadIdx.x < (unsigned)(n - nv * 4)) m = fmaxf(m, fabsf(x[nv * 4 + threadIdx.x]));
+            for (int u = 0; u < U; ++u) take(v[u]);
+        }
+    };
+    auto reduce = [&]() { // the workgroup's maximum, in its first wave
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    __shared__ float red[16];
-    __shared__ bool last;
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    if (threadIdx.x == 0) last = false;
-    __syncthreads();
-    AbsmaxCell &c = absmax_cells[cell < 0 ? 0 : cell];
-    if (threadIdx.x == 0) {
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+        __syncthreads();
 #pragma unroll
         for (int w = 0; w < 16; ++w) m = fmaxf(m, red[w]);
-        // non-negative floats order like their bit patterns
-        if (ALONE) {
-            *result = m;
-        } else if (cell < 0) {
-            unsigned *to = reinterpret_cast<unsigned *>(result);
-            if (__float_as_uint(m) > __atomic_load_n(to, __ATOMIC_RELAXED)) atomicMax(to, __float_as_uint(m));
-        } else {
-            // (atomics are carried out where all compute units see them; one has been when its wait has ended)
-            atomicExch(&c.max[blockIdx.x], __float_as_uint(m));
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            // (a counter starts again at zero by itself; up to 32 workgroups count in the common one at once)
-            const unsigned counters = ABSMAX_COUNTERS, k = blockIdx.x % counters, members = (gridDim.x - k + counters - 1) / counters;
-            if (gridDim.x <= 32) last = atomicInc(&c.done[counters][0], gridDim.x - 1) == gridDim.x - 1;
-            else last = atomicInc(&c.done[k][0], members - 1) == members - 1 && atomicInc(&c.done[counters][0], counters - 1) == counters - 1;
+    };
+    const int64_t b = (int64_t)blockIdx.x * per;
+    stream(b, (b + per < nv) ? b + per : nv);
+    if (blockIdx.x == 0 && threadIdx.x < (unsigned)(n - nv * 4)) m = fmaxf(m, fabsf(x[nv * 4 + threadIdx.x]));
+    reduce();
+    if (ALONE) {
+        if (threadIdx.x == 0) *result = m;
+        return;
+    }
+    // (non-negative floats order like their bit patterns)
+    if (number == 0) {
+        unsigned *to = reinterpret_cast<unsigned *>(result);
+        if (threadIdx.x == 0 && __float_as_uint(m) > __atomic_load_n(to, __ATOMIC_RELAXED)) atomicMax(to, __float_as_uint(m));
+        return;
+    }
+    unsigned long long *row = absmax_words[number % ABSMAX_ROWS];
+    if (blockIdx.x != 0) {
+        if (threadIdx.x == 0) (void)__hip_atomic_fetch_max(&row[blockIdx.x], number << 31 | __float_as_uint(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    if (threadIdx.x < 64) {
+        bool all = false, mine = true;
+        for (int poll = 0; poll < ABSMAX_POLLS && !all; ++poll) {
+            bool there = true;
+            unsigned long long w[ABSMAX_GROUPS / 64];
+#pragma unroll
+            for (int q = 0; q < ABSMAX_GROUPS / 64; ++q) {
+                const unsigned g = threadIdx.x + 64 * q;
+                w[q] = (g == 0 || g >= gridDim.x) ? number << 31 : __hip_atomic_load(&row[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int q = 0; q < ABSMAX_GROUPS / 64; ++q) {
+                there = there && (w[q] >> 31) >= number;
+                mine = mine && (w[q] >> 31) <= number;
+                if ((w[q] >> 31) == number) m = fmaxf(m, __uint_as_float((unsigned)w[q] & 0x7fffffffu));
+            }
+            all = __all(there);
+        }
+        const bool ok = __all(all && mine);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        if (threadIdx.x == 0) {
+            gathered = ok;
+            if (ok) *result = m;
         }
     }
-    if (ALONE || cell < 0) return;
     __syncthreads();
-    if (!last || threadIdx.x >= 64) return;
-    unsigned top = 0;
-    for (unsigned g = threadIdx.x; g < gridDim.x; g += 64) top = max(top, __hip_atomic_load(&c.max[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, o, 64));
-    if (threadIdx.x == 0) *result = __uint_as_float(top);
+    if (gathered) return;
+    stream(0, nv);
+    reduce();
+    if (threadIdx.x == 0) *result = m;
 }
 
 // inv = 1 / scale rounded to fp32.  x * inv is within 1.5 units in the last place of x / scale,
@@ -167,23 +193,21 @@ inline unsigned grid_for(int64_t units, int64_t cap)
 
 } // namespace
 
-// The cell of a stream: launches on one stream run one after the other, so that a cell has one user at a time.  -1: none
-// is left, or the launch may run beside others of its stream's name (while a graph is captured; the per-thread default stream).
-static int absmax_cell(hipStream_t s)
+// The number of a launch on the stream's device (they count from 1).  0: the launch may run several times under its number (while a
+// graph is captured), the device is not known, or the numbers' 33 bits are used up.
+static unsigned long long absmax_number(hipStream_t s)
 {
-    static std::atomic<uintptr_t> owner[ABSMAX_CELLS];
+    constexpr int DEVICES = 64;
+    static std::atomic<unsigned long long> launches[DEVICES];
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (s == hipStreamPerThread || hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    int dev = -1;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+        (s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess || dev < 0 || dev >= DEVICES) {
         (void)hipGetLastError();
-        return -1;
+        return 0;
     }
-    const uintptr_t key = reinterpret_cast<uintptr_t>(s) + 1;
-    for (int c = 0; c < ABSMAX_CELLS; ++c) {
-        uintptr_t seen = owner[c].load(std::memory_order_relaxed);
-        if (seen == 0 && owner[c].compare_exchange_strong(seen, key, std::memory_order_relaxed)) return c;
-        if (seen == key) return c;
-    }
-    return -1;
+    const unsigned long long number = launches[dev].fetch_add(1, std::memory_order_relaxed) + 1;
+    return number >> 33 ? 0 : number;
 }
 
 hipError_t launch_absmax(const float *x, int64_t n, float *result, hipStream_t s)
@@ -192,12 +216,12 @@ hipError_t launch_absmax(const float *x, int64_t n, float *result, hipStream_t s
     // one alone reads 128 KB sooner than two have met
     const int64_t groups = (n + 16383) / 16384;
     if (groups <= 2) { // (also an empty tensor)
-        hipLaunchKernelGGL((absmax_kernel<true>), dim3(1), dim3(1024), 0, s, x, n, result, -1);
+        hipLaunchKernelGGL((absmax_kernel<true>), dim3(1), dim3(1024), 0, s, x, n, result, 0ull);
         return hipGetLastError();
     }
-    const int cell = absmax_cell(s);
-    if (cell < 0) hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, s, result);
-    hipLaunchKernelGGL((absmax_kernel<false>), dim3((unsigned)(groups < ABSMAX_GROUPS ? groups : ABSMAX_GROUPS)), dim3(1024), 0, s, x, n, result, cell);
+    const unsigned long long number = absmax_number(s);
+    if (number == 0) hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, s, result);
+    hipLaunchKernelGGL((absmax_kernel<false>), dim3((unsigned)(groups < ABSMAX_GROUPS ? groups : ABSMAX_GROUPS)), dim3(1024), 0, s, x, n, result, number);
     return hipGetLastError();
 }
 

@@ -64,3 +64,32 @@ def test_absmax_of_interleaved_streams(n):
         half = xs[i][:max(1, n // 2 // 4 * 4)]
         for k in range(6):
             assert float(outs[i][k]) == float((xs[i] if k % 2 == 0 else half).abs().max()), (i, k)
+
+
+@pytest.mark.parametrize("n", [3 * 16384, 70 * 16384 + 5])
+def test_absmax_that_is_overtaken(n):
+    """Many streams at once, and a launch that waits on its stream until the 64 later ones after which rows come round again have
+    run: its first workgroup finds their numbers in its row."""
+    import torch
+    from paper_2209_06979_amd import binding as mc
+    x = torch.randn(n, device="cuda")
+    tops = torch.rand(140, device="cuda") + 50.0
+    xs = [x.clone() for _ in range(4)]
+    late, want_late = torch.full((1,), -1.0, device="cuda"), float(x.abs().max())
+    out = torch.full((140,), -1.0, device="cuda")
+    torch.cuda.synchronize()
+    held = torch.cuda.Stream()
+    with torch.cuda.stream(held):
+        torch.cuda._sleep(20_000_000)                          # some ten milliseconds
+        mc.absmax(x, out=late)
+    streams = [torch.cuda.Stream() for _ in range(35)]
+    for k in range(140):
+        s = streams[k % 35]
+        with torch.cuda.stream(s):
+            y = xs[k % 4] * (tops[k] / want_late)
+            mc.absmax(y, out=out[k:k + 1])
+            y.record_stream(s)
+    torch.cuda.synchronize()
+    assert float(late) == want_late
+    for k in range(140):
+        assert float(out[k]) == float((xs[k % 4] * (tops[k] / want_late)).abs().max()), k
