@@ -1258,7 +1258,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         f.in_head_stride = head_stride * qkv_bits / 8; f.in_token_stride = token_stride * qkv_bits / 8;
         f.in_batch_stride = batch_stride * qkv_bits / 8;
         f.score_scale = s_q * s_k / std::sqrt((float)dk); f.inv_s_p = 1.f / s_p; f.out_scale = s_p * s_v;
-        f.heads = heads; f.batch = batch;
+        f.heads = heads; f.batch = batch; f.tokens = L;
         // neighbouring heads contiguous inside a token, rows of at most 64 bytes: two heads per workgroup can
         // gather 128 bytes per token (not for 16-bit codes with 4-bit inputs, whose output tile does not fit
         // that kernel's stages)
@@ -1269,6 +1269,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         // One launch for the panels in `list` (null: all), none of which has more than max_chunks chunks.
         auto launch = [&](const int32_t *list, int n_panels, int max_chunks) -> hipError_t {
             f.panel_list = list; f.P = n_panels;
+            f.index_bytes = 4 * std::min(mask->nslots, (int64_t)n_panels * max_chunks * MC_CHUNK);
             // a wave keeps at most 8 chunks of scores in registers: longer panels are shared by 2, 4 or 8 waves
             int wpp = max_chunks > 32 ? 8 : (max_chunks > 16 ? 4 : (max_chunks > 8 ? 2 : 1));
             int hpg;

@@ -137,9 +137,7 @@ void attention_fused_kernel(AttnArgs a)
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
     // Workgroups are handed to the 8 XCDs round-robin by linear id.  1, 2, 4 or 8 (head group, batch item) pairs are worked on
-    // at a time, a row of the grid: the most that divide their number.  An XCD then sees one pair at a time, its L2
-    // holds the Kmat and V rows of that pair and fetches them once.  (With all XCDs on one batch item at a time each fetched every
-    // item's rows: 2 heads x 4096, batch 32, 90 % empty 112 -> 105 us.)
+    // at a time, a row of the grid (pairs_at_a_time): an XCD then sees one pair at a time.
     const int groups = a.heads / HPW;
     const int pair = ((int)(blockIdx.z * gridDim.y + blockIdx.y) << a.pair_shift) + (int)(blockIdx.x & ((1u << a.pair_shift) - 1));
     if (pair >= groups * a.batch) return;
@@ -202,7 +200,8 @@ void attention_fused_kernel(AttnArgs a)
     }
     const unsigned stage_u = lds_addr_uniform(stage);  // this wave's stage(s)
     // A lane's copies take NITW indices, the same for all lanes of a row.  Loaded by each lane they would be a fifth of
-    // all bytes that L1 returns: a lane loads NIX of them and takes the others from its neighbours.
+    // all bytes that L1 returns: a lane loads NIX of them and takes the others from its neighbours.  (By itself: 8 x 4 heads x 8192,
+    // (L, heads, dk), 181 -> 177 us; 8 heads x 4096 x 128 22.6 -> 22.1; (heads, L, dk) tensors of dk = 64 0 - 1 %.)
     // (a chunk's place is wave-uniform: a scalar base and the lane's constant offset)
     const unsigned lane_idx = (rg * NIT + NITW * w + (lane % SHARE) * NIX) * 4;
     auto index_of = [&](auto I, const ixv_t &ix) -> unsigned { // index of copy instruction i
@@ -429,7 +428,7 @@ void attention_fused_kernel(AttnArgs a)
                         // code = rint(y), ties to even, hi = (code + 128) >> 8 in [0, 127], lo = code - 256 * hi in [-128, 127]:
                         // the code's low byte as it is.  Adding 1.5 * 2^23 rounds to an integer and leaves it in the low
                         // half of the word; four codes are then split two at a time.  (18 instructions for four codes, it
-                        // was 36: 8 heads x 4096, batch 8, 16-bit codes 107 -> 99 us.)
+                        // was 36.  By itself: 8 x 4 heads x 8192, (L, heads, dk), 190.5 -> 184.5 us, (heads, L, dk) 227.5 -> 225.5.)
                         unsigned u[4];
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
@@ -543,11 +542,34 @@ void attention_fused_kernel(AttnArgs a)
     }
 }
 
+// log2 of the pairs worked on at a time, 2^s of them: the s at which the XCDs fetch least from beyond their L2s.  The 8 >> s XCDs of
+// a pair fetch its K and V rows (row_bytes), and each its share of the column indices; the share is still there for
+// the XCD's next pair if it fits beside a pair's rows into three of L2's four megabytes, or is fetched again for every pair.
+// 2^s must divide the number of pairs.  Measured at 1, 2, 4, 8 pairs at a time, 90 % empty, dk = 64, 8-bit codes and inputs:
+//   8 x 4 heads x 8192, (heads, L, dk)   217  213  212 (taken)  215 us        16-bit codes 227  219  220 (taken)  226; 4-bit inputs 194  193  191 (taken)  197
+//   8 x 4 heads x 8192, (L, heads, dk)   180  179  178.5        177.5 (taken)     4-bit inputs 165  170  168  167.5 (taken)
+//   8 x 8 heads x 4096, (heads, L, dk)   122  112  109          108 (taken)   (L, heads, dk) 95.5  92.5  91.5  90 (taken)
+//   2 heads x 4096, batch 32             122  113  108          108 (taken)   8 heads x 4096 x 128  27  25  22.1  22.1 (taken)
+inline int pairs_at_a_time(int64_t pairs, double row_bytes, double index_bytes)
+{
+    int best = 0;
+    double least = 0.0;
+    for (int s = 0; s <= 3 && pairs % (1 << s) == 0; ++s) {
+        const double share = index_bytes * (1 << s) / 8;
+        const double fetched = pairs * row_bytes * (8 >> s) + (row_bytes + share <= 3.0 * (1 << 20) ? 8 * share : pairs * index_bytes);
+        if (s == 0 || fetched <= least) {
+            best = s;
+            least = fetched;
+        }
+    }
+    return best;
+}
 
 template <int HPW, int PB, int QB, int KS, int DK, bool PAD> hipError_t launch_pairs(AttnArgs a, hipStream_t s)
 {
     const unsigned pairs = (unsigned)(a.heads / HPW) * (unsigned)a.batch;
-    a.pair_shift = pairs % 8 == 0 ? 3 : (pairs % 4 == 0 ? 2 : (pairs % 2 == 0 ? 1 : 0));
+    const int row = HPW * (PAD ? a.real_pieces * 16 : DK * QB / 8), lines = (row + 127) / 128 * 128; // (the L2 holds lines of 128 bytes)
+    a.pair_shift = pairs_at_a_time(pairs, 2.0 * a.tokens * (a.in_token_stride < lines ? (double)a.in_token_stride : lines), (double)a.index_bytes);
     const unsigned rows = pairs >> a.pair_shift, y = rows < 32768 ? rows : 32768;
     hipLaunchKernelGGL((attention_fused_kernel<8, HPW, PB, QB, KS, DK, PAD>), dim3((unsigned)a.P << a.pair_shift, y, (rows + y - 1) / y),
                        dim3(64 * HPW * KS), 0, s, a);

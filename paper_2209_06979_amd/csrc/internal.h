@@ -225,6 +225,8 @@ struct AttnArgs {
     int P, heads, batch;                     // P: panels of this launch
     const int32_t *panel_list;               // their numbers (null: 0 .. P-1)
     int out_f16;                             // 1: O holds fp16 (the fp32 result rounded to nearest even)
+    int tokens;                              // rows of Km and Vm
+    int64_t index_bytes;                     // column indices of this launch's panels
     int pair_shift;                          // log2 of the (head group, batch item) pairs of a grid row (set by the launcher)
     // head dimensions below the kernel's tile (launch_attention_fused_padded): 16-byte pieces a Q / Kmat / V row
     // really has, and columns of O

@@ -32,3 +32,24 @@ def test_batched_layers_equal_item_by_item(B, heads, dk, p_bits, token_major):
             assert torch.equal(O[b], mc.sparse_attention(qd[b], kd[b], vd[b], mask, s_q, s_k, s_v, s_p, p_bits=p_bits)), b
     finally:
         mc.set_attention_mode(0)
+
+
+@pytest.mark.parametrize("batch", [4, 8])
+def test_fewer_pairs_at_a_time(batch):
+    """A mask whose column indices do not fit an XCD's L2 beside a pair's rows: fewer pairs are worked on at a time."""
+    import torch
+    from paper_2209_06979_amd import binding as mc
+    L, V, dk = 8192, 8, 64
+    rp, ci = wl.vector_sparse_pattern(L, L, V, 0.9, 4790)
+    mask = mc.SparseMatrix(L, L, V, rp, ci)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4791)
+    q, k, v = (torch.randint(-127, 128, (batch, 1, L, dk), generator=g, device="cuda", dtype=torch.int8) for _ in range(3))
+    O = mc.sparse_attention(q, k, v, mask, 0.01, 0.01, 0.01, 1 / 127)
+    mc.set_attention_mode(2)                                  # the same number of waves per (panel, head), by panel length alone
+    try:
+        for b in range(batch):
+            assert torch.equal(O[b], mc.sparse_attention(q[b], k[b], v[b], mask, 0.01, 0.01, 0.01, 1 / 127)), b
+    finally:
+        mc.set_attention_mode(0)
+    mask.close()
