@@ -94,7 +94,8 @@ typedef struct mc_options {
                                 less than 4 GiB and no wave has more than 4 chunks), 1 or 2               */
     int spmm_splitting;      /* 0 automatic (very unequal panels are cut into work items, see
                                 mc_set_spmm_splitting), -1 never, 1 as 0 and also in the last SpMM of the
-                                attention layer's kernel pipeline (see mc_attention_workspace_needed)      */
+                                attention layer's kernel pipeline (see mc_attention_workspace_needed), which
+                                layers of head dimensions above 128 then run in where the mask has such panels */
     int spmm_slab;           /* the SpMM form that keeps rows of B resident in LDS and reads the gathered
                                 rows from there: 0 automatic (when it is expected to be faster: many stored
                                 vectors per row of B), -1 never (also: mc_mat_create on this thread does not
@@ -411,12 +412,14 @@ int mc_sparse_softmax_to_mat(mc_mat *P, const int32_t *S_dev, float score_scale,
  * are; MC_EINVAL otherwise).  Entries excluded by the mask do not take part in the softmax.
  * Empty rows give zeros.  The workspace is only needed, checked and touched when the layer
  * runs as the pipeline of separate kernels (see mc_set_attention_mode): NULL / 0 is accepted
- * whenever mc_attention_workspace_needed(...) is 0 -- the fused kernel takes the layer, or the
- * mask stores nothing.
+ * whenever mc_attention_form(...) is 0 -- the fused kernel takes the layer -- or
+ * mc_attention_workspace_needed(...) is 0.
  * ---------------------------------------------------------------------------------- */
 size_t mc_attention_workspace_bytes(int heads, const mc_mat *mask);
 /* Bytes of workspace the layer makes use of for this head dimension and these options (NULL: the
- * calling thread's defaults): 0 when the fused kernel runs; else the codes of all heads, plus the
+ * calling thread's defaults): 0 when the fused kernel runs (head dimensions above 128: the figure is that
+ * of the kernel pipeline, also where mc_attention_form says that the fused kernel takes the layer and a
+ * workspace is not looked at); else the codes of all heads, plus the
  * int32 scores when they travel through memory (three kernels), plus -- for a mask with panels many
  * times longer than the average and with spmm_splitting = 1 -- int32 output rows of those panels,
  * which several workgroups of the last SpMM then share (exact partial sums, scaled and rounded by a
@@ -424,6 +427,10 @@ size_t mc_attention_workspace_bytes(int heads, const mc_mat *mask);
  * and scores) is always enough to run; with less than the figure returned here the long panels are
  * simply not shared (same results, a longer tail). */
 size_t mc_attention_workspace_needed(int heads, int dk, const mc_mat *mask, int p_bits, const mc_options *options);
+/* Which form the layer runs in for this mask, head dimension, input width and these options (NULL: the calling
+ * thread's defaults; host only, launches nothing): 0 the fused kernel, 1 the pipeline with scores and softmax in one
+ * kernel, 2 the pipeline of three kernels.  Negative: an error code. */
+int mc_attention_form(const mc_mat *mask, int dk, int qkv_bits, const mc_options *options);
 /* The same layer for any regular layout: element (head h, token l, d) of Q, Km, Vm (int8)
  * and of O (fp32) sits at h*head_stride + l*token_stride + d (strides in elements, both
  * multiples of 16).  mc_sparse_attention is the case head_stride = L*dk, token_stride = dk.
@@ -445,9 +452,8 @@ int mc_sparse_attention(const int8_t *Q_dev, const int8_t *Km_dev, const int8_t 
  * packed two per byte along dk).  Strides are in ELEMENTS for all four tensors and must make
  * whole 16-byte pieces (multiples of 16 for 8-bit, of 32 for 4-bit inputs); dk likewise.
  * p_bits = 8, qkv_bits = 8 is mc_sparse_attention_strided.  Every combination has the fused
- * kernel (dk == 64 or dk == 128; panels of at most 2048 vectors) and the
- * kernel pipeline behind it, as selected by mc_set_attention_mode; the workspace must hold
- * mc_attention_workspace_bytes_bits(heads, mask, p_bits) bytes.
+ * kernel and the kernel pipeline behind it, as selected by mc_set_attention_mode; the workspace, where one is needed,
+ * must hold mc_attention_workspace_bytes_bits(heads, mask, p_bits) bytes.
  * Unsupported widths: MC_EUNSUPPORTED. */
 size_t mc_attention_workspace_bytes_bits(int heads, const mc_mat *mask, int p_bits);
 int mc_sparse_attention_bits(const void *Q_dev, const void *Km_dev, const void *Vm_dev, int heads, int L, int dk,
@@ -531,11 +537,12 @@ int mc_set_sddmm_variant(int waves);
  * 1 = a workgroup per panel also for short panels, 2 = always the kernel for panels of any
  * length (three passes).  Same codes up to fp32 summation order. */
 int mc_set_softmax_variant(int variant);
-/* Attention path: 0 = automatic (a single fused kernel when dk is 64 or 128 and no panel holds
- * more than 2048 vectors -- one, two or four waves per (panel, head) for panels of up to 512,
- * 1024, 2048 vectors, more waves than that when the launch is small; two neighbouring heads per
- * workgroup for token-major tensors once the launch has 2048 (panel, head) units -- else the
- * pipeline of kernels), 1 = always the pipeline: one kernel that computes the scores of a panel,
+/* Attention path: 0 = automatic (a single fused kernel when dk is at most 128 and no panel holds
+ * more than 4096 vectors -- one, two, four or eight waves per (panel, head) for panels of up to 512,
+ * 1024, 2048, 4096 vectors, more waves than that when the launch is small; two neighbouring heads per
+ * workgroup for token-major tensors once the launch has 2048 (panel, head) units -- or when dk is at
+ * most 192, no panel holds more than 2048 vectors and spmm_splitting does not ask for the sharing of
+ * long panels, which only the pipeline has; else the pipeline of kernels), 1 = always the pipeline: one kernel that computes the scores of a panel,
  * keeps them in on-chip memory, takes the softmax and writes the integer codes in the SpMM's operand
  * format, then the SpMM (rows of Q / Km of up to 256 bytes and panels of up to about 4700 vectors;
  * beyond that, or with 6 = always, three kernels: SDDMM, softmax, SpMM, with the int32 scores in the

@@ -134,6 +134,7 @@ def _load() -> ctypes.CDLL:
                                              POINTER(Options), c_void_p, c_void_p]
     L.mc_attention_workspace_needed.argtypes = [c_int, c_int, c_void_p, c_int, POINTER(Options)]
     L.mc_attention_workspace_needed.restype = c_size_t
+    L.mc_attention_form.argtypes = [c_void_p, c_int, c_int, POINTER(Options)]
     L.mc_set_spmm_variant.argtypes = [c_int, c_int]
     L.mc_set_attention_mode.argtypes = [c_int]
     L.mc_set_spmm_splitting.argtypes = [c_int]
@@ -147,7 +148,7 @@ def _load() -> ctypes.CDLL:
                  "mc_set_spmm_variant", "mc_set_attention_mode", "mc_set_sddmm_variant", "mc_set_spmm_splitting", "mc_set_spmm_stages",
                  "mc_set_softmax_variant", "mc_set_thread_options", "mc_get_thread_options", "mc_spmm_ex", "mc_sddmm_ex",
                  "mc_sparse_attention_ex", "mc_sparse_attention_static", "mc_blocked_query", "mc_pack_blocked_host", "mc_sddmm_to_mat", "mc_probe_mfma", "mc_spmm_form",
-                 "mc_mat_merged_info", "mc_merged_query", "mc_merge_host", "mc_probe_spmm_phases"):
+                 "mc_attention_form", "mc_mat_merged_info", "mc_merged_query", "mc_merge_host", "mc_probe_spmm_phases"):
         getattr(L, name).restype = c_int
     return L
 
@@ -398,9 +399,17 @@ def attention_workspace_bytes(heads: int, mask: SparseMatrix, p_bits: int = 8) -
 
 
 def attention_workspace_needed(heads: int, dk: int, mask: SparseMatrix, p_bits: int = 8, options: Options | None = None) -> int:
-    """Bytes of workspace the layer will really use (0 when the fused kernel takes it)."""
+    """Bytes of workspace the layer uses (0 when the fused kernel takes it; head dimensions above 128: what the kernel
+    pipeline would use)."""
     return int(lib.mc_attention_workspace_needed(heads, dk, mask.handle, p_bits,
                                                  None if options is None else ctypes.byref(options)))
+
+
+def attention_form(mask: SparseMatrix, dk: int, qkv_bits: int = 8, options: Options | None = None) -> str:
+    """'fused' (no workspace), 'scores+spmm' or 'three kernels': the form sparse_attention runs in."""
+    rc = lib.mc_attention_form(mask.handle, dk, qkv_bits, None if options is None else ctypes.byref(options))
+    _check(min(rc, 0), "mc_attention_form")
+    return ("fused", "scores+spmm", "three kernels")[rc]
 
 
 STATIC_SCRATCH_BYTES = 16 << 20

@@ -1188,13 +1188,16 @@ int attention_pipeline(const uint8_t *Q, const uint8_t *Km, const uint8_t *Vm, i
     return MC_OK;
 }
 
-// Whether the single fused kernel takes this layer (else the pipeline of separate kernels, which needs a workspace).
-// (Head dimensions up to 128 whose rows are whole 16-byte pieces; those below 64 or between 64 and 128 run in the
-// next larger tile with the missing pieces read as zeros.)
-bool attention_is_fused(const mc_mat *mask, int dk, int qkv_bits, const mc_options &o)
+// The head dimension of the fused kernel that takes this layer; 0: the pipeline of separate kernels does.
+// (Rows of whole 16-byte pieces; dimensions below 64, between 64 and 128 and above run in the next larger tile with the
+// missing pieces read as zeros.  Above 128: panels that four waves can share, and not where the caller pins a mode or asks
+// for the pipeline's sharing of long panels.  One launch for all batch items against two for each: batch 8, 8 heads x 616, dk = 160,
+// 87 % empty: 98 -> 25 us.)
+int fused_tile(const mc_mat *mask, int dk, int qkv_bits, const mc_options &o)
 {
-    return o.attention_mode != 1 && o.attention_mode != 6 && dk <= 128 && (dk * qkv_bits / 8) % 16 == 0 &&
-           mask->max_panel_chunks * MC_CHUNK <= attention_fused_max_vectors();
+    if (o.attention_mode == 1 || o.attention_mode == 6 || (dk * qkv_bits / 8) % 16 != 0) return 0;
+    if (dk <= 128) return mask->max_panel_chunks * MC_CHUNK <= attention_fused_max_vectors() ? (dk <= 64 ? 64 : 128) : 0;
+    return o.attention_mode == 0 && dk <= 192 && mask->max_panel_chunks <= 32 && !pipeline_splits(mask, o) ? 192 : 0;
 }
 
 // Memory the library itself provides to callers that cannot allocate (mc_sparse_attention_static):
@@ -1304,7 +1307,8 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         }
         return MC_OK;
     };
-    if (attention_is_fused(mask, dk, qkv_bits, o)) return fused(dk <= 64 ? 64 : 128);
+    const int tile = fused_tile(mask, dk, qkv_bits, o);
+    if (tile && (tile <= 128 || !use_static)) return fused(tile);
     // the kernel pipeline keeps its intermediates in a workspace (none are needed when nothing is stored)
     const bool with_scores = scores_kernel_waves(mask, heads, dk, qkv_bits, o) == 0;
     const size_t need = attn_layout(heads, mask, p_bits, with_scores).total;
@@ -1312,11 +1316,12 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
     const size_t need_split = attn_layout(heads, mask, p_bits, with_scores, dk).total;
     const bool split_panels = pipeline_splits(mask, o) && (use_static ? need_split <= STATIC_SCRATCH_BYTES : workspace_bytes >= need_split);
     if (use_static) {
-        if (need > STATIC_SCRATCH_BYTES) {
+        if (need > STATIC_SCRATCH_BYTES) { // (above 128, too, where the fused kernel would do without: the limit is the layer's, not the form's)
             snprintf(g_detail, sizeof g_detail, "the layer's intermediates need %zu bytes, the library's own array holds %zu",
                      need, STATIC_SCRATCH_BYTES);
             return MC_ENOMEM;
         }
+        if (tile) return fused(tile);
         const int rc = static_scratch(&workspace_dev);
         if (rc != MC_OK) return rc;
     } else if (need > 0) {
@@ -1324,10 +1329,6 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         if ((reinterpret_cast<uintptr_t>(workspace_dev) & 255u) != 0) return MC_EALIGN;
         if (workspace_bytes < need) return MC_ENOMEM;
     }
-    // Head dimensions up to 192 have a fused form, too, for panels that four waves can share; it needs no workspace, but what
-    // callers give is what the pipeline needs, and the layer of callers without memory of their own stays the pipeline.  One
-    // launch for all batch items against two for each: batch 8, 8 heads x 616, dk = 160, 87 % empty: 98 -> 25 us.
-    if (!use_static && o.attention_mode == 0 && dk <= 192 && (dk * qkv_bits / 8) % 16 == 0 && mask->max_panel_chunks <= 32) return fused(192);
     // the batch items run one after the other through the same workspace
     for (int b = 0; b < batch; ++b) {
         const int64_t ib = (int64_t)b * batch_stride * qkv_bits / 8;
@@ -1354,13 +1355,23 @@ extern "C" size_t mc_attention_workspace_bytes(int heads, const mc_mat *mask)
     return mc_attention_workspace_bytes_bits(heads, mask, 8);
 }
 
+extern "C" int mc_attention_form(const mc_mat *mask, int dk, int qkv_bits, const mc_options *options)
+{
+    if (!mask || mask->V != 8 || (qkv_bits != 8 && qkv_bits != 4) || dk <= 0 || dk % (128 / qkv_bits) != 0) return MC_EINVAL;
+    mc_options o;
+    if (resolve_options(options, &o) != MC_OK) return MC_EINVAL;
+    if (fused_tile(mask, dk, qkv_bits, o)) return 0;
+    return scores_kernel_waves(mask, 1, dk, qkv_bits, o) ? 1 : 2;
+}
+
 extern "C" size_t mc_attention_workspace_needed(int heads, int dk, const mc_mat *mask, int p_bits, const mc_options *options)
 {
     if (!mask || heads <= 0 || (p_bits != 8 && p_bits != 16)) return 0;
     mc_options o;
     if (resolve_options(options, &o) != MC_OK) return 0;
-    // (8-bit inputs decide here; a 4-bit layer whose rows are not whole pieces then needs what is returned)
-    if (attention_is_fused(mask, dk, 8, o)) return 0;
+    // (8-bit inputs decide here; a 4-bit layer whose rows are not whole pieces then needs what is returned.  Above 128 the figure is
+    // the pipeline's whatever the form.)
+    if (dk <= 128 && fused_tile(mask, dk, 8, o)) return 0;
     // (the narrowest inputs the layer takes give the smallest rows: whether the scores stay on chip is decided
     // for 8-bit inputs here, which never asks for less than a 4-bit layer needs)
     return attn_layout(heads, mask, p_bits, scores_kernel_waves(mask, heads, dk, 8, o) == 0, pipeline_splits(mask, o) ? dk : 0).total;

@@ -638,7 +638,8 @@ PyObject *sparse_attention(PyObject *, PyObject *const *args, Py_ssize_t nargs, 
         if (ws) {
             w = ws->data_ptr();
             wbytes = (size_t)ws->numel() * ws->element_size();
-        } else if ((wbytes = mc_attention_workspace_needed(in.heads, in.dk, mask->mat, in.p_bits, opts.ptr)) > 0) {
+        } else if (mc_attention_form(mask->mat, in.dk, in.qkv_bits, opts.ptr) != 0 &&
+                   (wbytes = mc_attention_workspace_needed(in.heads, in.dk, mask->mat, in.p_bits, opts.ptr)) > 0) {
             scratch = empty({(int64_t)wbytes}, at::kByte, *in.q);
             w = scratch.data_ptr();
         }

@@ -48,3 +48,51 @@ def test_head_dimensions_up_to_192(dk, L, sparsity, p_bits, qkv_bits, token_majo
         want = oracle.attention(*r, c["row_ptr"], c["col_idx"], V, s_q, s_k, s_v, s_p, p_bits=p_bits, qkv_bits=qkv_bits)[0]
         bad = np.abs(O[1].float().cpu().numpy() - want) > 1e-3 + np.abs(want) * 2.0 ** -10
         assert bad.mean() < 0.02
+
+
+@pytest.mark.parametrize("dk,p_bits,qkv_bits", [(160, 8, 8), (160, 16, 8), (192, 16, 4), (144, 16, 8)])
+def test_entry_points_agree_and_no_workspace_is_taken(dk, p_bits, qkv_bits):
+    """The entry point without a workspace runs the same kernel, code for code, and the other one neither asks for a workspace
+    nor, through the binding, allocates one."""
+    import torch
+    from paper_2209_06979_amd import binding as mc
+    heads, L = 3, 1024
+    rp, ci = wl.vector_sparse_pattern(L, L, 8, 0.6, 4990, keep_diagonal=True)
+    mask = mc.SparseMatrix(L, L, 8, rp, ci)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4991)
+    q, k, v = (torch.randint(0, 256, (heads, L, dk * qkv_bits // 8), generator=g, device="cuda", dtype=torch.uint8) for _ in range(3))
+    if qkv_bits == 8:
+        q, k, v = (t.view(torch.int8) for t in (q, k, v))
+    s_p = np.float32(1.0 / oracle.P_CODE_MAX[p_bits])
+    args = (q, k, v, mask, 0.002, 0.02 if qkv_bits == 8 else 2.0, 0.01, s_p)
+    assert mc.attention_form(mask, dk, qkv_bits) == "fused" and mc.attention_form(mask, dk, qkv_bits, mc.Options(attention_mode=1)) == "scores+spmm"
+    mc.sparse_attention(*args, p_bits=p_bits, qkv_bits=qkv_bits)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    O = mc.sparse_attention(*args, p_bits=p_bits, qkv_bits=qkv_bits)
+    assert mc.attention_workspace_needed(heads, dk, mask, p_bits) > 1 << 20                # (what the pipeline would use)
+    assert torch.cuda.max_memory_allocated() - before <= O.numel() * 4 + 4096
+    S = torch.full_like(O, float("nan"))
+    mc.sparse_attention_static(*args, S, p_bits=p_bits, qkv_bits=qkv_bits)
+    assert torch.equal(O, S)
+    mask.close()
+
+
+def test_sharing_of_long_panels_is_the_pipelines():
+    """spmm_splitting = 1 on a mask with panels far above the average: the pipeline runs, with its output rows shared."""
+    import torch
+    from paper_2209_06979_amd import binding as mc
+    heads, L, dk = 2, 2048, 160
+    counts = np.full(L // 8, 40)
+    counts[[3, 77]] = 2000
+    rp, ci = wl.ragged_pattern(L, L, 8, counts, 4995)
+    mask = mc.SparseMatrix(L, L, 8, rp, ci)
+    x = torch.randint(-127, 128, (heads, L, dk), device="cuda", dtype=torch.int8)
+    args = (x, x, x, mask, 0.001, 0.02, 0.01, 1 / 127)
+    share, piped = mc.Options(spmm_splitting=1), mc.Options(spmm_splitting=1, attention_mode=1)
+    assert mc.attention_form(mask, dk, 8) == "fused" and mc.attention_form(mask, dk, 8, share) == "scores+spmm"
+    assert torch.equal(mc.sparse_attention(*args, options=share), mc.sparse_attention(*args, options=piped))
+    mask.close()
