@@ -91,3 +91,27 @@ def test_pattern_only_and_empty_operands():
     assert np.array_equal(m_ci[m_rp[0]:m_rp[1]], np.flatnonzero(flags[0] | flags[1]))
     assert np.array_equal(m_ci[m_rp[1]:m_rp[2]], np.flatnonzero(flags[2]))
     assert (m_src.reshape(-1, 2)[m_rp[1]:, 1] == -1).all()                       # the ragged group's missing panel
+
+
+@pytest.mark.parametrize("K", [1, 63, 64, 65, 4095, 4096, 4097, 262145])
+def test_union_at_the_edges_of_its_words(K):
+    """Columns at both ends and around every multiple of 64 and of 4096 that the matrix has."""
+    V, group = 4, 4
+    edges = sorted({c for b in (0, 64, 128, 4096, 8192, 262144, K) for c in (b - 1, b, b + 1) if 0 <= c < K})
+    panels = [edges, edges[::2], [], edges[1::3], [K - 1], [0]]
+    rp = np.concatenate([[0], np.cumsum([len(p) for p in panels])]).astype(np.int32)
+    ci = np.array([c for p in panels for c in p], np.int32)
+    vals = wl.uniform_int8((len(ci), V), 77)
+    m_rp, m_ci, m_vals, m_src = mc.merge_host(V * len(panels), K, V, 8, rp, ci, vals, group)
+    for sp in range(2):
+        mine = panels[sp * group:(sp + 1) * group]
+        want = sorted(set().union(*mine))
+        assert list(m_ci[m_rp[sp]:m_rp[sp + 1]]) == want
+        for i, c in enumerate(want, m_rp[sp]):
+            for g in range(group):
+                at = m_src[i * group + g]
+                share = m_vals.reshape(-1, group, V)[i, g]
+                if g < len(mine) and c in mine[g]:
+                    assert at == rp[sp * group + g] + mine[g].index(c) and np.array_equal(share, vals[at].view(np.uint8))
+                else:
+                    assert at == -1 and not share.any()
