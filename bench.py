@@ -17,7 +17,8 @@ beforehand (the paper builds its format offline as well).
 
 Other modes, each printing ONE JSON object: --sweep (the SpMM / SDDMM grids, for the SpMM with the gather form,
 the LDS-resident form and the automatic choice side by side), --skew (panels of log-normal length), --shapes
-(matrices with few panels: the automatic kernel variant against every pinned one).
+(matrices with few panels: the automatic kernel variant against every pinned one), --forms N (drawn operands in every form of
+the SpMM, beside the expected times that the choice of form rests on), --waves (the SDDMM's waves per panel).
 
 `cpu_baseline` is the CPU oracle timed on this host.
 """
@@ -129,8 +130,13 @@ def main():
     ap.add_argument("--shapes", action="store_true",
                     help="instead of the step: matrices with few panels or short panels; the automatic kernel variant "
                          "against every pinned tile / wave variant")
+    ap.add_argument("--forms", type=int, default=0, metavar="N",
+                    help="instead of the step: the SpMM on N drawn operands (all precisions but 16 x 16 bits, all sizes, equal and "
+                         "unequal panels) in each of its four forms, beside the time that the library's choice expects of it")
+    ap.add_argument("--waves", action="store_true",
+                    help="instead of the step: the SDDMM's automatic number of waves per panel against every pinned one")
     ap.add_argument("--table", action="store_true",
-                    help="with --sweep / --skew / --shapes: print a plain-text table instead of the JSON object")
+                    help="with --sweep / --skew / --shapes / --forms / --waves: print a plain-text table instead of the JSON object")
     ap.add_argument("--point", default="",
                     help="instead of the step: one SpMM configuration 'prec:V:sparsity:N:form' (form: gather, lds, merged, merged-lds or auto) at "
                          "4096 x 4096, launched --steps times one by one (for counter and trace collection), e.g. L8R8:2:0.5:512:lds")
@@ -153,9 +159,10 @@ def main():
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
 
-    if args.sweep or args.skew or args.shapes or args.phases:
+    if args.sweep or args.skew or args.shapes or args.phases or args.forms or args.waves:
         result = (run_sweep(mc, torch) if args.sweep else run_skew(mc, torch) if args.skew else
-                  run_shapes(mc, torch) if args.shapes else run_phases(mc, torch))
+                  run_shapes(mc, torch) if args.shapes else run_forms(mc, torch, args.forms) if args.forms else
+                  run_waves(mc, torch) if args.waves else run_phases(mc, torch))
         print(as_table(result) if args.table else json.dumps(result))
         return
     if args.point:
@@ -609,6 +616,128 @@ def run_shapes(mc, torch):
     return {"shapes": "SpMM, V=8, warm caches, 50 back-to-back launches (median of 3); pinned = tile bytes x waves",
             "library": mc.lib.mc_version().decode(), "points": len(rows), "within_5_percent_of_best": within5,
             "worst_auto_over_best": worst, "rows": rows}
+
+
+def draw_operand(rng):
+    """Sizes of one operand of run_forms: at most 2^22 stored vectors, 800 MB of gathered rows."""
+    while True:
+        prec = ("L8R8", "L8R4", "L4R4", "L16R8", "L16R4", "L12R4")[rng.integers(6)]
+        Vv = (2, 4, 8, 8)[rng.integers(4)]
+        Ms = max(1, int(np.exp(rng.uniform(np.log(256), np.log(16000)))) // Vv) * Vv
+        Ks = int(np.exp(rng.uniform(np.log(512), np.log(8192))))
+        row_bytes = max(2, int(np.exp(rng.uniform(np.log(32), np.log(1024)))) // 16) * 16
+        s = round(float(rng.uniform(0.5, 0.97)), 3)
+        sigma = round(float(rng.uniform(0.2, 1.2)), 2) if rng.integers(4) == 0 else 0.0
+        nvec = Ms // Vv * Ks * (1 - s)
+        if nvec <= 1 << 22 and nvec * row_bytes <= 800e6:
+            return prec, Vv, Ms, Ks, row_bytes, s, sigma, (4, 2)[rng.integers(2)]
+
+
+def run_forms(mc, torch, count):
+    """The SpMM on drawn operands: each of its four forms -- rows of B gathered per stored vector or resident in LDS, on
+    the operand as given or on its merged copy -- timed beside the time that the library's choice expects of it, and what the
+    choice loses over the fastest.  `chunks` / `longest` and their merged counterparts are the operand's chunks of 64 vectors
+    and those of its longest panel."""
+    from paper_2209_06979_amd import workloads as wl
+    rng = np.random.default_rng(470)
+    stream = torch.cuda.Stream()
+    pins = {"gather": mc.Options(spmm_slab=-1, spmm_merge=-1), "lds": mc.Options(spmm_slab=1, spmm_merge=-1),
+            "m_gather": mc.Options(spmm_slab=-1, spmm_merge=1), "m_lds": mc.Options(spmm_slab=1, spmm_merge=1)}
+    rows = []
+    chunks = lambda rp: (np.diff(rp) + 63) // 64
+    with torch.cuda.stream(stream):
+        for i in range(count):
+            prec, Vv, Ms, Ks, row_bytes, s, sigma, out = draw_operand(rng)
+            P, lhs, rhs = Ms // Vv, mc.LHS_BITS[prec], mc.RHS_BITS[prec]
+            N = row_bytes * 8 // rhs
+            lengths = np.maximum(1, lognormal_counts(P, max(8, round(Ks * (1 - s))), sigma, Ks, rng))
+            score = rng.random((P, Ks), dtype=np.float32)
+            rank = np.argsort(score, axis=1) if sigma else np.argpartition(score, int(lengths[0]) - 1, axis=1)
+            rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+            ci = np.concatenate([np.sort(rank[p, :lengths[p]]) for p in range(P)]).astype(np.int32)
+            n = len(ci)
+            vals = (wl.uniform_packed_int4((n, Vv // 2), i) if lhs == 4 else wl.uniform_int8((n, Vv), i) if lhs == 8 else
+                    wl.uniform_int16((n, Vv), i, -2048, 2047))
+            mc.set_thread_options(mc.Options(spmm_slab=1, spmm_merge=1))   # (all copies, whether they would be built or not)
+            A = mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs)
+            mc.set_thread_options(None)
+            own = mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs)           # (the copies that are built by themselves)
+            B = torch.randint(0, 256, (Ks, row_bytes), device="cuda", dtype=torch.uint8)
+            B = B if rhs == 4 else B.view(torch.int8)
+            dtype = torch.int32 if out == 4 else torch.float16
+            C = torch.empty((Ms, N), dtype=dtype, device="cuda")
+
+            def launch(X, o):
+                if out == 4:
+                    return lambda: mc.spmm(X, B, prec, out=C, options=o)
+
+                def dequant():                                             # (takes the thread's options)
+                    mc.set_thread_options(o)
+                    mc.spmm_dequant(X, B, prec, 1e-4, dtype, out=C)
+                    mc.set_thread_options(None)
+                return dequant
+            reps = 50 if n * row_bytes < 100e6 else 20
+            us, want = {}, {}
+            for k, (f, o) in enumerate(pins.items()):
+                if f[0] == "m" and not A.merge_group:
+                    continue
+                us[f] = time_graph(torch, stream, [launch(A, o)] * reps, rounds=3, warm_ms=0.0 if k else 15.0)
+                want[f] = mc.spmm_form_us(A, N, prec, out, o)
+            auto = ("m_" if mc.spmm_on_merged(own, N, prec) else "") + mc.spmm_form(own, N, prec)
+            merged = mc.merge_host(Ms, Ks, Vv, lhs, rp, ci, None, A.merge_group)[0] if A.merge_group else None
+            rows.append(dict(prec=prec, V=Vv, M=Ms, K=Ks, row_bytes=row_bytes, out=out, empty=s, sigma=sigma, nvec=n, chunks=int(chunks(rp).sum()),
+                             longest=int(chunks(rp).max()), m_nvec=int(merged[-1]) if merged is not None else None,
+                             m_chunks=int(chunks(merged).sum()) if merged is not None else None,
+                             m_longest=int(chunks(merged).max()) if merged is not None else None,
+                             **{k: round(us[f], 2) if f in us else None for f in pins for k in [f]},
+                             **{f"{f}_exp": round(want[f], 2) if f in want else None for f in pins},
+                             auto=auto, auto_over_best=round(us[auto] / min(us.values()), 3)))
+            A.close()
+            own.close()
+            if i % 20 == 19:
+                print(f"{i + 1} of {count} operands", file=sys.stderr, flush=True)
+
+    def summary(some):
+        r = dict(operands=len(some))
+        for f in pins:
+            e = np.sort([abs(np.log(x[f + "_exp"] / x[f])) for x in some if x[f] is not None])
+            if len(e):
+                r[f + "_error"] = " / ".join(f"{100 * (np.exp(e[int(q * (len(e) - 1))]) - 1):.0f}" for q in (0.5, 0.9, 1.0))
+        a = np.sort([x["auto_over_best"] for x in some])
+        r["auto_over_best"] = f"{a.mean():.3f} / {a[int(0.9 * (len(a) - 1))]:.3f} / {a[-1]:.3f}"
+        return r
+    groups = {"all": rows, "equal panels": [x for x in rows if not x["sigma"]], "unequal panels": [x for x in rows if x["sigma"]]}
+    return {"forms": "SpMM on drawn operands, warm caches, back-to-back launches in a graph (median of 3), us",
+            "library": mc.lib.mc_version().decode(),
+            "columns": "<form>_error: median / 9 in 10 / largest error of the expected time, per cent; auto_over_best: mean / 9 in 10 / largest",
+            "summary": [dict(panels=k, **summary(v)) for k, v in groups.items() if v], "rows": rows}
+
+
+def run_waves(mc, torch):
+    """The SDDMM with the library's number of waves per panel against every pinned one."""
+    from paper_2209_06979_amd import workloads as wl
+    stream = torch.cuda.Stream()
+    rows = []
+    with torch.cuda.stream(stream):
+        for Ms, Ks, Vv, s in [(4096, 4096, 8, 0.9), (4096, 4096, 8, 0.7), (4096, 4096, 2, 0.95), (2048, 2048, 4, 0.9), (1000, 3100, 4, 0.9),
+                              (256, 2304, 8, 0.7), (128, 4096, 8, 0.5), (16384, 4096, 8, 0.98), (512, 512, 8, 0.8), (2000, 5000, 8, 0.5)]:
+            for prec, Kd in (("L8R8", 64), ("L8R8", 256), ("L8R8", 544), ("L4R4", 64), ("L4R4", 256), ("L16R16", 64), ("L16R16", 200)):
+                c = wl.sddmm_case(Ms, Ks, Kd, Vv, s, prec, 1)
+                m = mc.SparseMatrix(Ms, Ks, Vv, c["row_ptr"], c["col_idx"])
+                Q, Km = torch.from_numpy(c["Q"]).cuda(), torch.from_numpy(c["Kmat"]).cuda()
+                S = torch.empty(m.nvec * Vv, dtype=torch.int32, device="cuda")
+                auto = time_graph(torch, stream, [lambda: mc.sddmm(Q, Km, m, prec, out=S)] * 50, rounds=3, warm_ms=15.0)
+                us = {}
+                for w in (1, 2, 4, 8):
+                    o = mc.Options(sddmm_waves=w)
+                    us[w] = time_graph(torch, stream, [lambda: mc.sddmm(Q, Km, m, prec, out=S, options=o)] * 50, rounds=3)
+                rows.append(dict(prec=prec, M=Ms, K=Ks, V=Vv, empty=s, row_bytes=Kd * mc.LHS_BITS[prec] // 8, auto_us=round(auto, 2),
+                                 **{f"w{w}_us": round(us[w], 2) for w in us}, auto_over_best=round(auto / min(us.values()), 3)))
+                m.close()
+    over = sorted(r["auto_over_best"] for r in rows)
+    return {"waves": "SDDMM, warm caches, 50 back-to-back launches in a graph (median of 3)", "library": mc.lib.mc_version().decode(),
+            "points": len(rows), "within_5_percent_of_best": sum(x <= 1.05 for x in over), "within_8_percent": sum(x <= 1.08 for x in over),
+            "worst": over[-1], "rows": rows}
 
 
 def time_graph(torch, stream, launches, rounds=5, warm_ms=0.0):

@@ -224,7 +224,13 @@ int mc_merge_host(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, con
 /* Builds the device format from HOST interchange arrays and uploads it on `stream`
  * (the call returns after the upload has completed).  values == NULL or lhs_bits == 0
  * gives a pattern-only mask (for SDDMM / attention).  *out is owned by the caller
- * until mc_mat_destroy.  Errors as mc_pack_host, plus MC_EHIP / MC_ENOMEM. */
+ * until mc_mat_destroy.  Errors as mc_pack_host, plus MC_EHIP / MC_ENOMEM.
+ * An operand with values is stored up to four times, in the forms that mc_spmm chooses from, and building it takes as
+ * long as writing them: the panel format (its values, padded, and 4 bytes per slot); the merged copy (see mc_merge_host: the
+ * panel format of the merged operand and 4 bytes per merged vector and panel of its group) unless it would hold more vectors
+ * than the operand; and an LDS-ordered copy (the values, and 6 bytes per slot) of either where the SpMM form that needs
+ * it is expected to be the fastest for some width of B.  spmm_merge = -1 and spmm_slab = -1 in the creating
+ * thread's options leave them out.  (4096 x 4096, V = 8, 90 % empty, 8 bits: 1.8 MB of values, 13 MB on the device.) */
 int mc_mat_create(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
                   const void *values, void *stream, mc_mat **out);
 /* Replaces the values from a DEVICE array in interchange order (nvec*V elements of the
@@ -276,6 +282,9 @@ int mc_spmm_ex(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec,
  * bit 0: 0 = rows of B gathered per stored vector, 1 = rows of B resident in LDS; bit 1 (value 2): on the
  * operand's merged copy (see mc_merge_host).  Negative: an error code. */
 int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_options *options);
+/* Measurement aid: the time in us that this choice expects of the form it takes (results of out_bytes = 2 or 4
+ * bytes; the options can pin each form in turn).  Negative: an error code. */
+double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_bytes, const mc_options *options);
 
 /* SpMM with fused dequantisation (Section 5.3: the integer product is turned into real values
  * in the kernel's epilogue): C = scale * (A * B), each element computed as float(int32 result) *

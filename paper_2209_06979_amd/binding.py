@@ -134,6 +134,8 @@ def _load() -> ctypes.CDLL:
                                              POINTER(Options), c_void_p, c_void_p]
     L.mc_attention_workspace_needed.argtypes = [c_int, c_int, c_void_p, c_int, POINTER(Options)]
     L.mc_attention_workspace_needed.restype = c_size_t
+    L.mc_spmm_form_us.argtypes = [c_void_p, c_int, c_int, c_int, POINTER(Options)]
+    L.mc_spmm_form_us.restype = ctypes.c_double
     L.mc_attention_form.argtypes = [c_void_p, c_int, c_int, POINTER(Options)]
     L.mc_set_spmm_variant.argtypes = [c_int, c_int]
     L.mc_set_attention_mode.argtypes = [c_int]
@@ -350,6 +352,14 @@ def spmm_form(A: SparseMatrix, N: int, prec: str, options: Options | None = None
     if r < 0:
         _check(r, "mc_spmm_form")
     return "lds" if r & 1 else "gather"
+
+
+def spmm_form_us(A: SparseMatrix, N: int, prec: str, out_bytes: int = 4, options: Options | None = None) -> float:
+    """The time that the library's choice of form expects of the form it takes (a measurement aid)."""
+    us = lib.mc_spmm_form_us(A.handle, N, PREC[prec], out_bytes, ctypes.byref(options) if options is not None else None)
+    if us < 0:
+        _check(int(us), "mc_spmm_form_us")
+    return us
 
 
 def spmm_on_merged(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> bool:

@@ -120,7 +120,8 @@ void free_device(mc_mat *A)
 
 // Waves per panel for SDDMM: enough to put about 3200 waves on the chip (4096 of the light ones that stage rows of 32
 // bytes, or 64 bytes of nibbles), and no more than a panel has units of rows (64 of up to 128 bytes, 32 of 256, 16 beyond).
-// On 35 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count, 8 % once.
+// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at 67, 6 % at worst
+// (profiles/sddmm_waves.txt).
 int choose_sddmm_waves(const mc_mat *mask, int batch, int row_bytes, int bits, const mc_options &o)
 {
     if (o.sddmm_waves != 0) return o.sddmm_waves < 0 ? 0 : o.sddmm_waves; // 0 selects the direct-load kernel in launch_sddmm
@@ -288,10 +289,13 @@ struct SlabPlan { int nt, ntiles, groups, wpp, waves; double us; };
 int resident_end_words(const mc_mat *A) { return (int)((A->blk_chunks + 31) / 32 + 2); }
 int resident_rec_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V * (A->lhs_bits == 12 ? 16 : A->lhs_bits) / 8; }
 
-// Expected times in us of the two forms of the SpMM, fitted (least squares on the logarithm) to 470 drawn operands: all
-// precisions but 16 x 16 bits, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B of 32 .. 1024
-// bytes, half to 97 % empty, a quarter of them with panels of unequal length.  They are good to 15 %; picking the form
-// by them costs 3 % over always picking the best of the four (merged or not, resident or gathered).
+// Expected times in us of the two forms of the SpMM, fitted (least squares on the logarithm) to drawn operands as in
+// profiles/spmm_forms.txt: all precisions but 16 x 16 bits, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B
+// of 32 .. 1024 bytes, half to 97 % empty, a quarter of them with panels of unequal length.  There an expected time is off by 10 - 13 % in
+// the median and by up to a third in nine cases of ten, and the form picked is slower than the fastest of the four (merged or not,
+// resident or gathered) by 2.4 % on average, by 7 % or less in nine cases of ten, by 46 % at worst (rows of nibbles of no round
+// length); on unequal panels 3.3 %, 11 %, 46 %.  The resident form has no term for its longest panel: with one, and the other terms as they
+// are, the choice on unequal panels loses 6 %.
 // Resident: launch and start; per K-block and pass the fill, a line of B per row; per step of a wave (16 waves a unit,
 // each as slow as the SIMD's issue makes it, see the kernel) a fixed part and one per MFMA; the epilogues; the stores.
 // (A: the operand's layout figures are enough, its copies need not exist yet)
@@ -340,7 +344,9 @@ double gather_us(const mc_mat *A, int row_bytes, bool r4, int out_bytes)
            0.059 * (items ? A->max_item_chunks : A->max_panel_chunks) + (items ? 3.1 : 0.0);
 }
 
-// Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines.
+// Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines; by a
+// tenth at least where the merged copy has such a copy already.  (Of 400 drawn operands 8 then have both, with 2 % 14; the
+// forms they run in lose the same 2.4 % over the best on average.)
 bool resident_worth_building(const mc_mat *A)
 {
     const mc_options automatic = {};
@@ -348,16 +354,16 @@ bool resident_worth_building(const mc_mat *A)
         for (int r4 = (A->lhs_bits == 4); r4 < 2; ++r4) {
             SlabPlan pl;
             plan_slab(A, row_bytes, r4, 4, automatic, &pl);
-            double best = gather_us(A, row_bytes, r4, 4);
+            double best = 0.98 * gather_us(A, row_bytes, r4, 4);
             if (A->merged) {
-                best = std::min(best, gather_us(A->merged, row_bytes, r4, 4));
+                best = std::min(best, 0.98 * gather_us(A->merged, row_bytes, r4, 4));
                 if (A->merged->d_blk_recs) {
                     SlabPlan m;
                     plan_slab(A->merged, row_bytes, r4, 4, automatic, &m);
-                    best = std::min(best, m.us);
+                    best = std::min(best, 0.9 * m.us);
                 }
             }
-            if (pl.us < 0.98 * best) return true;
+            if (pl.us < best) return true;
         }
     }
     return false;
@@ -843,6 +849,17 @@ extern "C" int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_optio
     const int rb = rhs_bits_of(prec);
     const SpmmForm form = spmm_form(A, N * rb / 8, rb, 4, 0u, o);
     return (form.slab ? 1 : 0) | (form.A != A ? 2 : 0);
+}
+
+extern "C" double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_bytes, const mc_options *options)
+{
+    if (!A || N <= 0 || !valid_prec((int)prec) || A->lhs_bits != lhs_bits_of(prec) || (out_bytes != 2 && out_bytes != 4)) return MC_EINVAL;
+    const mc_options automatic = {};
+    mc_options o;
+    if (resolve_options(options ? options : &automatic, &o) != MC_OK) return MC_EINVAL;
+    const int rb = rhs_bits_of(prec);
+    const SpmmForm form = spmm_form(A, N * rb / 8, rb, out_bytes, 0u, o);
+    return form.slab ? form.plan.us : gather_us(form.A, N * rb / 8, rb == 4, out_bytes);
 }
 
 extern "C" int mc_spmm_dequant(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, unsigned flags,
