@@ -378,8 +378,8 @@ def main():
 def run_sweep(mc, torch):
     """The grids of the SpMM and SDDMM precision sweeps (Section 5.2 figures' shapes: vector lengths, sparsities,
     widths of the dense operand, precisions) on seeded synthetic 4096 x 4096 patterns, warm caches.  Every SpMM point
-    is timed on the operand as given -- rows of B gathered per stored vector (`gather_us`), K-blocks of B resident in
-    LDS (`lds_us`, null where that form does not exist: two-plane right operands, more than 63 K-blocks) -- on its
+    is timed on the operand as given -- rows of B gathered per stored vector (`gather_us`), a tile of B resident in
+    LDS (`lds_us`, null where that form does not exist: two-plane right operands) -- on its
     merged copy (`merged_gather_us`, `merged_lds_us`: consecutive panels sharing one panel of 16 or 8 rows; null
     where there is nothing to merge) and as the library picks by itself (`us`, `form`, `merged`);
     `auto_over_best` = us / the fastest of the pinned forms."""
@@ -397,7 +397,7 @@ def run_sweep(mc, torch):
                             continue     # the mixed-precision configuration: V = 8, N = 256
                         c = wl.spmm_case(M, K, N, Vv, s, prec, wl.seed_for(2, 1))
                         A = mc.SparseMatrix(M, K, Vv, c["row_ptr"], c["col_idx"], c["values"], mc.LHS_BITS[prec])
-                        mc.set_thread_options(build_all)       # the creating thread's options: build the K-blocked and merged copies anyway
+                        mc.set_thread_options(build_all)       # the creating thread's options: build the LDS-ordered and merged copies anyway
                         Af = mc.SparseMatrix(M, K, Vv, c["row_ptr"], c["col_idx"], c["values"], mc.LHS_BITS[prec])
                         mc.set_thread_options(None)
                         B = torch.from_numpy(c["B"]).cuda()

@@ -102,7 +102,7 @@ typedef struct mc_options {
                                 build the LDS-ordered copy of the operand that form needs), 1 whenever the
                                 operand has that copy and the precision has an 8- or 4-bit B without
                                 unsigned flags                                                             */
-    int spmm_slab_waves;     /* that form's waves per workgroup: 0 automatic, else 1 .. 15                     */
+    int spmm_slab_waves;     /* that form's waves per workgroup: 0 automatic (16), else 1 .. 15                */
     int spmm_slab_panels;    /* 0, 1, 2 or 4: accepted, without effect (a wave keeps as many panels in flight
                                 as the operand's number of columns asks for)                               */
     int sddmm_waves;         /* 0 automatic, -1 the kernel that loads operands straight from memory,
@@ -161,18 +161,17 @@ int mc_pack_host(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, cons
 int mc_unpack_host(int M, int K, int V, int lhs_bits, const int32_t *panel_ptr, const int32_t *slot_idx,
                    const void *slot_vals, int32_t *row_ptr, int32_t *col_idx, void *values);
 
-/* K-blocked variant of the device format (Section 4.1 leaves the stride to the kernel; Section 4.2
- * notes that rows of the dense operand have no reuse in on-chip memory when every panel gathers
- * them anew -- this layout is what lets a workgroup keep a block of rows resident instead): the
+/* K-blocked variant of the format (Section 4.1 leaves the stride to the kernel): the
  * vectors of a panel are also grouped by the block of MC_KBLOCK consecutive columns they fall in,
  * each (panel, block) list zero-padded to whole chunks of 64, so that a chunk only names rows of
- * one block.  nblk = ceil(K / MC_KBLOCK).
+ * one block.  nblk = ceil(K / MC_KBLOCK).  For callers with kernels of their own: no kernel of this library reads
+ * it (the SpMM that keeps rows of B in on-chip memory has an internal format, made by mc_mat_create).
  *   blk_ptr   P*nblk + 1 int32: first chunk of (panel p, block b) at [p*nblk + b]; the chunks of a
  *             panel are consecutive over its blocks
  *   blk_rows  nchunks*64 uint16: row of each slot inside its block (column - b*MC_KBLOCK); padded
  *             slots repeat the list's last real row.  Inside a chunk, slot s sits at position
  *             (s/16)*16 + (s%8)*2 + (s%16)/8: slots s and s+8 of a sub-stride of 16 are neighbours
- *             (one lane of the kernel addresses exactly these two and reads them as one word)
+ *             (one lane of a kernel can read the two it addresses as one word)
  *   blk_vals  vals_bytes bytes, chunk by chunk in the layout of mc_pack_host's slot_vals
  *   blk_src   nchunks*64 int32: interchange index of the vector in each slot, -1 for padding
  * Same validation and error codes as mc_pack_host.  Pure host code. */

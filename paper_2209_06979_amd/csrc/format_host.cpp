@@ -93,7 +93,7 @@ template <class F> int with_put_vector(int V, int bits, F &&f)
     }
 }
 
-// Position of slot s (0..63) of a chunk in the K-blocked format's row array: the two slots one lane of the
+// Position of slot s (0..63) of a chunk in the row arrays of the formats below: the two slots one lane of the
 // kernel addresses (s and s + 8 inside a sub-stride of 16) are neighbours, so that they travel as one 32-bit word.
 inline int64_t chunk_base(int64_t slot) { return slot / MC_CHUNK * MC_CHUNK; }
 inline int row_position(int s) { return (s / 16) * 16 + (s % 8) * 2 + (s % 16) / 8; }
@@ -232,8 +232,8 @@ extern "C" int mc_unpack_host(int M, int K, int V, int lhs_bits, const int32_t *
 }
 
 // ---- K-blocked variant of the format -------------------------------------------------------
-// For kernels that keep a block of MC_KBLOCK consecutive rows of the dense operand resident in
-// on-chip memory: the vectors of a panel are additionally grouped by the K-block their column
+// A host-side format of the public interface that no kernel here reads (the resident SpMM has its own, see mc_resident_pack):
+// blocks of MC_KBLOCK consecutive rows of the dense operand; the vectors of a panel are additionally grouped by the K-block their column
 // falls in, and each (panel, block) list is padded to whole chunks on its own, so that every
 // chunk only names rows of one block (as 16-bit row numbers inside that block).
 extern "C" int mc_blocked_query(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,

@@ -44,7 +44,7 @@ struct mc_mat {
     int class_start[5];        // first entry of each class in d_class_panels; [4] = P
     // Merged copy for the SpMM (null when not built): `merge_group` consecutive panels as one panel of
     // V * merge_group rows at the union of their columns (see mc_merge_host); a complete operand of its own
-    // (work items, K-blocked copy), never merged again.  Its rows may run past M: launches on it pass M as the
+    // (work items, LDS-ordered copy), never merged again.  Its rows may run past M: launches on it pass M as the
     // number of output rows.
     mc_mat *merged;
     int merge_group;
@@ -211,7 +211,7 @@ struct ValuesArgs {
     ValuesJob job[4];
 };
 
-// Fused attention for head dimension 64.  Element (head h, token l, d) of Q, Km, Vm (int8)
+// Fused attention (attention_fused.h).  Element (head h, token l, d) of Q, Km, Vm (8- or 4-bit)
 // and O (fp32) sits at h*head_stride + l*token_stride + d.
 struct AttnArgs {
     const int32_t *panel_ptr;
@@ -259,12 +259,10 @@ hipError_t launch_scores_softmax(const ScoresArgs &a, int qkv_bits, int code_bit
 int scores_softmax_max_npad(int row_bytes, int waves);
 hipError_t launch_absmax(const float *x, int64_t n, float *result, hipStream_t s);
 hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uint8_t *q, hipStream_t s);
-// values of a merged operand in interchange order from the original operand's: share (i, g) of vb bytes = vector
-// merge_src[i * group + g] of src, or zeros
 // dk is 64 or 128.  heads_per_group 2 needs head_stride == dk (token-major layout), rows of at most 64
 // bytes and an even head count, and is not available for 16-bit codes with 4-bit inputs
 hipError_t launch_attention_fused(const AttnArgs &a, int heads_per_group, int waves_per_panel, int p_bits, int qkv_bits,
                                   int dk, hipStream_t s);
-// the same kernel for head dimensions below its tile (64 or 128): one head per workgroup; a.real_pieces, a.out_cols set
+// the same kernel for head dimensions below its tile (64 or 128), and up to its tile of 192: one head per workgroup; a.real_pieces, a.out_cols set
 hipError_t launch_attention_fused_padded(const AttnArgs &a, int waves_per_panel, int p_bits, int qkv_bits, int tile, hipStream_t s);
 int attention_fused_max_vectors(); // longest panel (in vectors) the fused kernel accepts

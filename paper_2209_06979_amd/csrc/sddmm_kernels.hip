@@ -1,4 +1,4 @@
-// SDDMM and value-repack kernels for gfx950 (the sparse softmax lives in softmax_kernels.hip).
+// SDDMM kernels for gfx950.
 //
 // SDDMM (paper, Section 4.3): a workgroup owns one row panel of the mask.  The panel's
 // V rows of Q are the row operand of v_mfma_i32_16x16x64_i8 and stay in registers for
