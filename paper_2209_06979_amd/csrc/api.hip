@@ -373,12 +373,8 @@ bool resident_worth_building(const mc_mat *A)
 
 namespace {
 // Whether mc_mat_create builds the merged copy (lay: the operand, ml: its merged form).  The copy holds
-// ml.nvec * rows values; which of the two a call uses is decided per call (merged_pays).
-bool merged_worth_building(const mc_layout &lay, const mc_merged_layout &ml, int V)
-{
-    (void)V;
-    return ml.nvec <= lay.nvec;
-}
+// ml.nvec * rows values; which of the two a call uses is decided per call (spmm_form).
+bool merged_worth_building(const mc_layout &lay, const mc_merged_layout &ml) { return ml.nvec <= lay.nvec; }
 
 // child: the merged copy of another operand (V up to 16, never merged again)
 int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
@@ -476,12 +472,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
                         for (int b = 0; b < c; b += per) items.insert(items.end(), {p, b, std::min(c, b + per), (int)split_panels.size()});
                     }
                 }
-            } catch (const std::bad_alloc &) {
-                delete A;
-                return MC_ENOMEM;
-            }
-            // longest first: workgroups start in this order, so the long items do not form the tail
-            {
+                // longest first: workgroups start in this order, so the long items do not form the tail
                 const size_t ni = items.size() / 4;
                 std::vector<size_t> order(ni);
                 for (size_t i = 0; i < ni; ++i) order[i] = i;
@@ -491,6 +482,9 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
                 std::vector<int32_t> sorted(items.size());
                 for (size_t i = 0; i < ni; ++i) std::copy(items.begin() + 4 * order[i], items.begin() + 4 * order[i] + 4, sorted.begin() + 4 * i);
                 items.swap(sorted);
+            } catch (const std::bad_alloc &) {
+                delete A;
+                return MC_ENOMEM;
             }
             A->n_items = (int)(items.size() / 4);
             A->n_split = (int)split_panels.size();
@@ -506,7 +500,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         const int rows = (lhs_bits == 4 || lhs_bits == 8) ? 16 : 8, group = rows / V;
         mc_merged_layout ml;
         if (group >= 2 && mc_merged_query(M, K, V, lhs_bits, row_ptr, col_idx, group, &ml) == MC_OK && ml.nvec > 0 &&
-            (t_options.spmm_merge == 1 || merged_worth_building(lay, ml, V))) {
+            (t_options.spmm_merge == 1 || merged_worth_building(lay, ml))) {
             std::vector<int32_t> m_row_ptr, m_col_idx;
             std::vector<uint8_t> m_values;
             const int64_t vb = (int64_t)V * (lhs_bits == 12 ? 16 : lhs_bits) / 8;
