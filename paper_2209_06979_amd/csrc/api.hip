@@ -291,10 +291,10 @@ int resident_rec_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V 
 
 // Expected times in us of the two forms of the SpMM, fitted (least squares on the logarithm) to drawn operands as in
 // profiles/spmm_forms.txt: all precisions but 16 x 16 bits, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B
-// of 32 .. 1024 bytes, half to 97 % empty, a quarter of them with panels of unequal length.  There an expected time is off by 10 - 13 % in
+// of 32 .. 1024 bytes, half to 97 % empty, a quarter of them with panels of unequal length.  There an expected time is off by 9 - 13 % in
 // the median and by up to a third in nine cases of ten, and the form picked is slower than the fastest of the four (merged or not,
-// resident or gathered) by 2.4 % on average, by 7 % or less in nine cases of ten, by 46 % at worst (rows of nibbles of no round
-// length); on unequal panels 3.3 %, 11 %, 46 %.  The resident form has no term for its longest panel: with one, and the other terms as they
+// resident or gathered) by 2.4 % on average, by 7 % or less in nine cases of ten, by nearly half at worst (rows of nibbles of no round
+// length); on unequal panels by 3 % and 9 %.  The resident form has no term for its longest panel: with one, and the other terms as they
 // are, the choice on unequal panels loses 6 %.
 // Resident: launch and start; per K-block and pass the fill, a line of B per row; per step of a wave (16 waves a unit,
 // each as slow as the SIMD's issue makes it, see the kernel) a fixed part and one per MFMA; the epilogues; the stores.
