@@ -131,7 +131,7 @@ def main():
                     help="instead of the step: matrices with few panels or short panels; the automatic kernel variant "
                          "against every pinned tile / wave variant")
     ap.add_argument("--forms", type=int, default=0, metavar="N",
-                    help="instead of the step: the SpMM on N drawn operands (all precisions but 16 x 16 bits, all sizes, equal and "
+                    help="instead of the step: the SpMM on N drawn operands (all precisions, all sizes, equal and "
                          "unequal panels) in each of its four forms, beside the time that the library's choice expects of it")
     ap.add_argument("--waves", action="store_true",
                     help="instead of the step: the SDDMM's automatic number of waves per panel against every pinned one")
@@ -621,11 +621,12 @@ def run_shapes(mc, torch):
 def draw_operand(rng):
     """Sizes of one operand of run_forms: at most 2^22 stored vectors, 800 MB of gathered rows."""
     while True:
-        prec = ("L8R8", "L8R4", "L4R4", "L16R8", "L16R4", "L12R4")[rng.integers(6)]
+        prec = ("L8R8", "L8R4", "L4R4", "L16R8", "L16R4", "L12R4", "L16R16")[rng.integers(7)]
         Vv = (2, 4, 8, 8)[rng.integers(4)]
         Ms = max(1, int(np.exp(rng.uniform(np.log(256), np.log(16000)))) // Vv) * Vv
         Ks = int(np.exp(rng.uniform(np.log(512), np.log(8192))))
-        row_bytes = max(2, int(np.exp(rng.uniform(np.log(32), np.log(1024)))) // 16) * 16
+        row_bytes = (max(2, int(np.exp(rng.uniform(np.log(32), np.log(1024)))) // 16) * 16 if rng.integers(3) == 0 else
+                     (32, 64, 128, 128, 256, 256, 384, 512, 512, 768, 1024)[rng.integers(11)])      # (two in three of round length)
         s = round(float(rng.uniform(0.5, 0.97)), 3)
         sigma = round(float(rng.uniform(0.2, 1.2)), 2) if rng.integers(4) == 0 else 0.0
         nvec = Ms // Vv * Ks * (1 - s)
@@ -636,7 +637,8 @@ def draw_operand(rng):
 def run_forms(mc, torch, count):
     """The SpMM on drawn operands: each of its four forms -- rows of B gathered per stored vector or resident in LDS, on
     the operand as given or on its merged copy -- timed beside the time that the library's choice expects of it, and what the
-    choice loses over the fastest.  `chunks` / `longest` and their merged counterparts are the operand's chunks of 64 vectors
+    choice loses over the fastest.  Three copies of everything are visited in turn, as a program's operands alternate (an XCD's L2
+    then holds small ones only).  `chunks` / `longest` and their merged counterparts are the operand's chunks of 64 vectors
     and those of its longest panel."""
     from paper_2209_06979_amd import workloads as wl
     rng = np.random.default_rng(470)
@@ -659,29 +661,30 @@ def run_forms(mc, torch, count):
             vals = (wl.uniform_packed_int4((n, Vv // 2), i) if lhs == 4 else wl.uniform_int8((n, Vv), i) if lhs == 8 else
                     wl.uniform_int16((n, Vv), i, -2048, 2047))
             mc.set_thread_options(mc.Options(spmm_slab=1, spmm_merge=1))   # (all copies, whether they would be built or not)
-            A = mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs)
+            As = [mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs) for _ in range(3)]
+            A = As[0]
             mc.set_thread_options(None)
             own = mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs)           # (the copies that are built by themselves)
-            B = torch.randint(0, 256, (Ks, row_bytes), device="cuda", dtype=torch.uint8)
-            B = B if rhs == 4 else B.view(torch.int8)
+            Bs = [torch.randint(0, 256, (Ks, row_bytes), device="cuda", dtype=torch.uint8) for _ in As]
+            Bs = Bs if rhs == 4 else [B.view(torch.int8 if rhs == 8 else torch.int16) for B in Bs]
             dtype = torch.int32 if out == 4 else torch.float16
-            C = torch.empty((Ms, N), dtype=dtype, device="cuda")
+            Cs = [torch.empty((Ms, N), dtype=dtype, device="cuda") for _ in As]
 
-            def launch(X, o):
+            def launch(k, o):
                 if out == 4:
-                    return lambda: mc.spmm(X, B, prec, out=C, options=o)
+                    return lambda: mc.spmm(As[k], Bs[k], prec, out=Cs[k], options=o)
 
                 def dequant():                                             # (takes the thread's options)
                     mc.set_thread_options(o)
-                    mc.spmm_dequant(X, B, prec, 1e-4, dtype, out=C)
+                    mc.spmm_dequant(As[k], Bs[k], prec, 1e-4, dtype, out=Cs[k])
                     mc.set_thread_options(None)
                 return dequant
-            reps = 50 if n * row_bytes < 100e6 else 20
+            reps = 45 if n * row_bytes < 100e6 else 18
             us, want = {}, {}
             for k, (f, o) in enumerate(pins.items()):
-                if f[0] == "m" and not A.merge_group:
+                if (f[0] == "m" and not A.merge_group) or (rhs == 16 and f[-3:] == "lds"):
                     continue
-                us[f] = time_graph(torch, stream, [launch(A, o)] * reps, rounds=3, warm_ms=0.0 if k else 15.0)
+                us[f] = time_graph(torch, stream, [launch(r % 3, o) for r in range(reps)], rounds=3, warm_ms=0.0 if k else 15.0)
                 want[f] = mc.spmm_form_us(A, N, prec, out, o)
             auto = ("m_" if mc.spmm_on_merged(own, N, prec) else "") + mc.spmm_form(own, N, prec)
             merged = mc.merge_host(Ms, Ks, Vv, lhs, rp, ci, None, A.merge_group)[0] if A.merge_group else None
@@ -692,8 +695,8 @@ def run_forms(mc, torch, count):
                              **{k: round(us[f], 2) if f in us else None for f in pins for k in [f]},
                              **{f"{f}_exp": round(want[f], 2) if f in want else None for f in pins},
                              auto=auto, auto_over_best=round(us[auto] / min(us.values()), 3)))
-            A.close()
-            own.close()
+            for X in (*As, own):
+                X.close()
             if i % 20 == 19:
                 print(f"{i + 1} of {count} operands", file=sys.stderr, flush=True)
 
@@ -707,7 +710,7 @@ def run_forms(mc, torch, count):
         r["auto_over_best"] = f"{a.mean():.3f} / {a[int(0.9 * (len(a) - 1))]:.3f} / {a[-1]:.3f}"
         return r
     groups = {"all": rows, "equal panels": [x for x in rows if not x["sigma"]], "unequal panels": [x for x in rows if x["sigma"]]}
-    return {"forms": "SpMM on drawn operands, warm caches, back-to-back launches in a graph (median of 3), us",
+    return {"forms": "SpMM on drawn operands, three copies in turn, back-to-back launches in a graph (median of 3), us",
             "library": mc.lib.mc_version().decode(),
             "columns": "<form>_error: median / 9 in 10 / largest error of the expected time, per cent; auto_over_best: mean / 9 in 10 / largest",
             "summary": [dict(panels=k, **summary(v)) for k, v in groups.items() if v], "rows": rows}

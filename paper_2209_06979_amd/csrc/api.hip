@@ -289,21 +289,24 @@ struct SlabPlan { int nt, ntiles, groups, wpp, waves; double us; };
 int resident_end_words(const mc_mat *A) { return (int)((A->blk_chunks + 31) / 32 + 2); }
 int resident_rec_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V * (A->lhs_bits == 12 ? 16 : A->lhs_bits) / 8; }
 
-// Expected times in us of the two forms of the SpMM, fitted (least squares on the logarithm) to drawn operands as in
-// profiles/spmm_forms.txt: all precisions but 16 x 16 bits, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B
-// of 32 .. 1024 bytes, half to 97 % empty, a quarter of them with panels of unequal length.  There an expected time is off by 9 - 13 % in
-// the median and by up to a third in nine cases of ten, and the form picked is slower than the fastest of the four (merged or not,
-// resident or gathered) by 2.4 % on average, by 7 % or less in nine cases of ten, by nearly half at worst (rows of nibbles of no round
-// length); on unequal panels by 3 % and 9 %.  The resident form has no term for its longest panel: with one, and the other terms as they
-// are, the choice on unequal panels loses 6 %.
-// Resident: launch and start; per K-block and pass the fill, a line of B per row; per step of a wave (16 waves a unit,
-// each as slow as the SIMD's issue makes it, see the kernel) a fixed part and one per MFMA; the epilogues; the stores.
+// Expected times in us of the two forms of the SpMM, fitted (non-negative least squares on the relative error) to 1600 operands drawn
+// as in profiles/spmm_forms.txt, which holds the first of them: all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192
+// columns, rows of B of 32 .. 1024 bytes, two in three of them of round length, half to 97 % empty, a quarter with panels of unequal length.
+// Timed with three copies of everything in turn, as a program's operands alternate.  An expected time is off by 8 - 10 % in the median and by
+// up to 28 % in nine cases of ten; the form picked is slower than the fastest of the four (merged or not, resident or gathered) by 1.5 % on
+// average, by 6 % or less in nine cases of ten, by half at worst, on equal and on unequal panels alike (with the constants before:
+// 2.8 %, 11 %, 62 %, and on the 168 points of profiles/sweep_spmm_sddmm_grid.txt, one operand over and over, 5.5 % and 54 % against
+// 2.3 % and 30 %).
+// Resident, all of B's rows at once: launch and start; the fill, a line of B per row, by how many workgroups there are to fill; per
+// step of a wave one part per MFMA and one per byte of a record, both by how many of the sixteen waves have panels; the epilogues; the stores;
+// waves that share a panel meet; and the steps that the longest panel's waves still have when an even share would be done.
+// In blocks: per block and pass the fill, per step of a wave its own reads, and per panel of a wave a start in each block.
 // (A: the operand's layout figures are enough, its copies need not exist yet)
 void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_options &o, SlabPlan *pl)
 {
     pl->us = 1e30;
     const double lists = (double)A->blk_chunks / A->P;               // chunks of a panel over all its blocks
-    const double store_us = (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes * 0.15e-6;
+    const double store = (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes;
     for (int nt = A->nblk == 1 ? A->blk_nt : 2; nt >= 2; nt -= 2) {
         SlabPlan q;
         q.nt = nt;
@@ -325,28 +328,54 @@ void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_
         else if (in_group >= q.waves) steps = in_group * lists / q.waves;
         else steps = lists / q.wpp;
         const int mfma = nt * (r4 ? 2 : 1);
-        const double fill_us = passes * A->nblk * (2.1 + A->block_rows * 0.65e-3);
-        // (in blocks: a step waits for its own reads, and every panel of a wave costs a start in each block)
-        const double walk_us = A->nblk > 1 ? steps * (r4 ? 0.17 : 0.21) + (in_group + q.waves - 1) / q.waves * 3.2
-                                           : steps * (0.105 + (r4 ? 0.039 : 0.028) * mfma) + in_group * mfma * (0.13 / 16);
-        q.us = 3.1 + rounds * (fill_us + walk_us) + store_us;
+        if (A->nblk == 1) {
+            const double filling = std::min(256, q.groups * q.ntiles) / 256.0, busy = std::min(1.0, (double)in_group * q.wpp / q.waves);
+            const double late = std::max(0.0, (double)A->max_panel_chunks / q.wpp - steps);
+            q.us = (r4 ? 4.7 : 4.55) + store * (r4 ? 9.1e-8 : 1.2e-7) + (q.wpp > 1 ? (r4 ? 0.39 : 0.22) : 0.0) +
+                   rounds * (A->block_rows * filling * (r4 ? 8.6e-4 : 9.9e-4) + steps * busy * mfma * (r4 ? 0.072 : 0.056) +
+                             steps * busy * filling * resident_rec_bytes(A) * (r4 ? 7.8e-5 : 1.04e-4) + in_group * mfma * (r4 ? 0.0042 : 0.0038) +
+                             late * (r4 ? 0.16 : 0.067));
+        } else {
+            q.us = 3.1 + store * 1.5e-7 + rounds * (passes * A->nblk * (2.1 + A->block_rows * 0.65e-3) + steps * (r4 ? 0.17 : 0.21) +
+                                                    (in_group + q.waves - 1) / q.waves * 3.2);
+        }
         if (q.us < pl->us) *pl = q;
     }
 }
 
-// Gathered: launch and start; the gathered bytes (a row that is no whole number of 128-byte lines touches more of them);
-// the stores; the chain of the longest unit of work; the launch that clears rows when panels are cut into items.
-double gather_us(const mc_mat *A, int row_bytes, bool r4, int out_bytes)
+// Gathered, in the tiles and waves that choose_variant and the launcher give it: launch and start; the staged bytes (padded slots and
+// the unused part of a last tile included); the 128-byte lines that rows touch, each tile by itself, with rows at all multiples of their
+// length; the stores; the waves; the launch that clears rows when panels are cut into items; the chunks of a wave, one after the other,
+// at an even share; and those that the longest unit's waves still have then.  The constants go by the width of B and by the rows of the
+// MFMA's result that a panel fills (merged panels and two planes of V = 8: all sixteen).
+double gather_us(const mc_mat *A, int row_bytes, int rb, int out_bytes, const mc_options &o)
 {
+    struct Cost { double start, byte, line, store, wave, chunk, late; };
+    static const Cost cost[3][2] = {{{2.55, 7.9e-8, 0.0, 9.8e-8, 5.5e-5, 0.30, 0.48}, {2.65, 6.3e-8, 6.3e-7, 1.0e-7, 1.75e-4, 0.50, 0.45}},
+                                    {{2.37, 4.8e-8, 7.5e-7, 4.7e-8, 5.6e-5, 0.21, 0.29}, {2.22, 4.6e-8, 1.3e-6, 4.5e-8, 1.23e-4, 0.44, 0.26}},
+                                    {{2.40, 5.2e-8, 3.7e-7, 0.0, 2.3e-4, 0.23, 0.33}, {2.40, 4.1e-8, 2.2e-6, 1.3e-7, 0.0, 0.41, 0.42}}};
+    constexpr double second_launch = 3.1;
+    const Cost &c = cost[rb == 4 ? 0 : rb == 8 ? 1 : 2][A->V == 16 || (A->V == 8 && A->lhs_bits > 8)];
     const bool items = A->n_items && out_bytes == 4;
-    const double gathered = (double)A->nvec * (row_bytes + (row_bytes % 128 ? 14 : 0)) * (r4 ? 0.102e-6 : 0.0754e-6);
-    return 3.15 + gathered + (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes * 0.18e-6 +
-           0.059 * (items ? A->max_item_chunks : A->max_panel_chunks) + (items ? 3.1 : 0.0);
+    const int longest = items ? A->max_item_chunks : A->max_panel_chunks;
+    int bnb, waves;
+    choose_variant(A, A->lhs_bits, row_bytes, rb == 4, 1, longest, o, &bnb, &waves);
+    const int wave_lds = std::max(MC_CHUNK * bnb, (A->lhs_bits > 8 ? 16 : 8) * ((rb == 4 ? 2 * bnb : bnb) + 4) * 4); // (as in SpmmCfg)
+    while (waves > 1 && waves * wave_lds > 65536) waves /= 2;
+    int unit = bnb;                                       // rows start at multiples of this, tiles too
+    while (row_bytes % unit || unit > 128) unit /= 2;
+    const double tiles = (row_bytes + bnb - 1) / bnb, chunks = (double)(A->nslots / MC_CHUNK), groups = A->P * tiles;
+    const double lines = (row_bytes + tiles * (128 - unit)) / 128;
+    const double at_once = 256.0 * std::max(1, std::min(163840 / (waves * wave_lds), 32 / waves)); // workgroups, by LDS and wave slots
+    const double share = chunks * tiles / (std::min(groups, at_once) * waves), longest_share = (double)longest / waves;
+    return c.start + chunks * MC_CHUNK * tiles * bnb * c.byte + A->nvec * lines * c.line +
+           (double)A->M * (row_bytes * 8.0 / rb) * out_bytes * c.store + groups * waves * c.wave + (items ? second_launch : 0.0) +
+           share * c.chunk + std::max(0.0, longest_share - share) * bnb / 64 * c.late;
 }
 
 // Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines; by a
-// tenth at least where the merged copy has such a copy already.  (Of 400 drawn operands 8 then have both, with 2 % 14; the
-// forms they run in lose the same 2.4 % over the best on average.)
+// tenth at least where the merged copy has such a copy already.  (Of 1385 drawn operands 33 then have both, with 2 %
+// 106; the forms they run in lose the same 2.0 % over the best on average.)
 bool resident_worth_building(const mc_mat *A)
 {
     const mc_options automatic = {};
@@ -354,9 +383,9 @@ bool resident_worth_building(const mc_mat *A)
         for (int r4 = (A->lhs_bits == 4); r4 < 2; ++r4) {
             SlabPlan pl;
             plan_slab(A, row_bytes, r4, 4, automatic, &pl);
-            double best = 0.98 * gather_us(A, row_bytes, r4, 4);
+            double best = 0.98 * gather_us(A, row_bytes, r4 ? 4 : 8, 4, automatic);
             if (A->merged) {
-                best = std::min(best, 0.98 * gather_us(A->merged, row_bytes, r4, 4));
+                best = std::min(best, 0.98 * gather_us(A->merged, row_bytes, r4 ? 4 : 8, 4, automatic));
                 if (A->merged->d_blk_recs) {
                     SlabPlan m;
                     plan_slab(A->merged, row_bytes, r4, 4, automatic, &m);
@@ -738,7 +767,7 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int rb, int out_bytes, unsign
         SlabPlan pl;
         pl.us = 1e30;
         if (slab) plan_slab(X, row_bytes, r4, out_bytes, o, &pl);
-        const double gather = (slab && o.spmm_slab == 1) ? 1e30 : gather_us(X, row_bytes, r4, out_bytes);
+        const double gather = (slab && o.spmm_slab == 1) ? 1e30 : gather_us(X, row_bytes, rb, out_bytes, o);
         if (std::min(gather, pl.us) < best) {
             best = std::min(gather, pl.us);
             f.A = X; f.slab = pl.us < gather; f.plan = pl;
@@ -853,7 +882,7 @@ extern "C" double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_
     if (resolve_options(options ? options : &automatic, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
     const SpmmForm form = spmm_form(A, N * rb / 8, rb, out_bytes, 0u, o);
-    return form.slab ? form.plan.us : gather_us(form.A, N * rb / 8, rb == 4, out_bytes);
+    return form.slab ? form.plan.us : gather_us(form.A, N * rb / 8, rb, out_bytes, o);
 }
 
 extern "C" int mc_spmm_dequant(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, unsigned flags,
