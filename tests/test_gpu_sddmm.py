@@ -173,8 +173,7 @@ def test_attention_small(mode, token_major):
 @pytest.mark.parametrize("token_major", [False, True])
 @pytest.mark.parametrize("mode", [1, 6])   # 1: scores and softmax in one kernel, then the SpMM; 6: three kernels
 def test_attention_pipeline_head_dimensions_and_long_panels(mode, token_major):
-    """Head dimensions the single fused kernel does not take (16, 32, 96, 160, 256) and panels beyond its 2048
-    vectors, through both forms of the kernel pipeline."""
+    """Head dimensions from 16 to 320 and panels of up to 4096 vectors, through both forms of the kernel pipeline."""
     _attention_check(2, 256, 16, 0.5, 1260, mode, token_major)     # rows of 16 bytes: one copy segment real, three repeated
     _attention_check(3, 512, 32, 0.9, 1261, mode, token_major)
     _attention_check(2, 512, 96, 0.8, 1262, mode, token_major)     # 96 bytes in a 128-byte stage

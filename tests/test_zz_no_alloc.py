@@ -39,23 +39,27 @@ def _both(mc, heads, L, dk, sparsity, seed, p_bits=8, qkv_bits=8, options=None, 
     return got.cpu().numpy(), want.cpu().numpy(), c, (q, k, v, s_q, s_k, s_v, s_p)
 
 
-def test_two_calls_second_smaller_equal_the_workspace_entry_point():
-    """dk = 160 always runs as the kernel pipeline, whose codes (and scores) live in the library's array.  Both entry
-    points launch the same kernels on the same inputs, so the outputs must be identical bit for bit."""
+@pytest.mark.parametrize("mode", [0, 1, 6])
+def test_two_calls_second_smaller_equal_the_workspace_entry_point(mode):
+    """Automatic (the fused kernel) and as the kernel pipeline, whose codes (and scores, with three kernels) live in the
+    library's array.  Both entry points launch the same kernels on the same inputs, so the outputs must be identical bit for bit."""
     from paper_2209_06979_amd import binding as mc
-    print("no-alloc: 3 heads x 512 x 160, then 2 heads x 256 x 160", flush=True)
-    got, want, _, _ = _both(mc, 3, 512, 160, 0.8, 7001)
+    o = mc.Options(attention_mode=mode)
+    print(f"no-alloc: 3 heads x 512 x 160, then 2 heads x 256 x 160, mode {mode}", flush=True)
+    got, want, _, _ = _both(mc, 3, 512, 160, 0.8, 7001, options=o)
     assert not np.isnan(got).any() and np.array_equal(got, want)
-    got, want, _, _ = _both(mc, 2, 256, 160, 0.75, 7002)       # smaller: the array still holds the first call's data
+    got, want, _, _ = _both(mc, 2, 256, 160, 0.75, 7002, options=o)       # smaller: the array still holds the first call's data
     assert not np.isnan(got).any() and np.array_equal(got, want)
 
 
-def test_against_the_oracle_after_a_larger_call():
+@pytest.mark.parametrize("mode", [0, 1, 6])
+def test_against_the_oracle_after_a_larger_call(mode):
     """The second, smaller call also agrees with the CPU oracle (so stale contents of the shared array are not read)."""
     import oracle
     from paper_2209_06979_amd import binding as mc
-    _both(mc, 4, 1024, 160, 0.8, 7003)
-    got, want, c, (q, k, v, s_q, s_k, s_v, s_p) = _both(mc, 2, 256, 160, 0.75, 7004)
+    o = mc.Options(attention_mode=mode)
+    _both(mc, 4, 1024 if mode < 6 else 512, 160, 0.8, 7003, options=o)   # (three kernels: the scores have to fit, too)
+    got, want, c, (q, k, v, s_q, s_k, s_v, s_p) = _both(mc, 2, 256, 160, 0.75, 7004, options=o)
     ref, _, probs, _ = oracle.attention(q.cpu().numpy(), k.cpu().numpy(), v.cpu().numpy(), c["row_ptr"], c["col_idx"], 8,
                                         s_q, s_k, s_v, s_p)
     x = probs / np.float64(s_p)
