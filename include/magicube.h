@@ -35,7 +35,8 @@
  *     along a row (same nibble order as above); leading dimensions are in ELEMENTS.
  *   - A compute call must be made with the device current on which its mc_mat was created
  *     (MC_EINVAL otherwise; mc_last_error_detail() names both devices).
- *   - The library keeps no process-wide mutable state.  Kernel-variant choices are automatic;
+ *   - The library keeps no process-wide mutable state that a result depends on (mc_absmax
+ *     numbers its launches on each device).  Kernel-variant choices are automatic;
  *     a caller that wants to pin them passes an mc_options to an ..._ex entry point, or sets
  *     defaults for its own thread (mc_set_thread_options).  Calls from different host threads
  *     never influence each other.
@@ -390,7 +391,8 @@ int mc_sparse_softmax_bits(const mc_mat *mask, int batch, const int32_t *S_dev, 
 /* ------------------------------------------------------------------------------------
  * Quantisation of the layer's inputs (Section 5.3, first step): symmetric, one scale per tensor.
  *   mc_absmax    *result_dev (device float) = max |x_dev[i]|, i < n; the caller takes
- *                scale = max / 127 (8 bits) or max / 7 (4 bits), or uses a calibrated constant
+ *                scale = max / 127 (8 bits) or max / 7 (4 bits), or uses a calibrated constant.
+ *                Calls from any number of streams and threads may overlap
  *   mc_quantize  q[i] = clamp(rint(x[i] / scale), -qmax, qmax), ties to even, decided as in double
  *                precision; bits = 8: int8 codes; bits = 4: two codes per byte (element 2j in bits
  *                3:0 of byte j), n even.  x_dev 16-byte aligned, q_dev 8-byte aligned.

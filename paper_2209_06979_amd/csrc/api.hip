@@ -120,8 +120,8 @@ void free_device(mc_mat *A)
 
 // Waves per panel for SDDMM: enough to put about 3200 waves on the chip (4096 of the light ones that stage rows of 32
 // bytes, or 64 bytes of nibbles), and no more than a panel has units of rows (64 of up to 128 bytes, 32 of 256, 16 beyond).
-// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at 67, 6 % at worst
-// (profiles/sddmm_waves.txt).
+// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at nine in ten, 10 % at
+// worst (profiles/sddmm_waves.txt; which points lie between 3 and 8 % changes from run to run).
 int choose_sddmm_waves(const mc_mat *mask, int batch, int row_bytes, int bits, const mc_options &o)
 {
     if (o.sddmm_waves != 0) return o.sddmm_waves < 0 ? 0 : o.sddmm_waves; // 0 selects the direct-load kernel in launch_sddmm
@@ -296,7 +296,7 @@ int resident_rec_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V 
 // up to 28 % in nine cases of ten; the form picked is slower than the fastest of the four (merged or not, resident or gathered) by 1.5 % on
 // average, by 6 % or less in nine cases of ten, by half at worst, on equal and on unequal panels alike (with the constants before:
 // 2.8 %, 11 %, 62 %, and on the 168 points of profiles/sweep_spmm_sddmm_grid.txt, one operand over and over, 5.5 % and 54 % against
-// 2.3 % and 30 %).
+// 2 % and 30 %).
 // Resident, all of B's rows at once: launch and start; the fill, a line of B per row, by how many workgroups there are to fill; per
 // step of a wave one part per MFMA and one per byte of a record, both by how many of the sixteen waves have panels; the epilogues; the stores;
 // waves that share a panel meet; and the steps that the longest panel's waves still have when an even share would be done.
