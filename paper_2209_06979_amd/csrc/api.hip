@@ -120,8 +120,8 @@ void free_device(mc_mat *A)
 
 // Waves per panel for SDDMM: enough to put about 3200 waves on the chip (4096 of the light ones that stage rows of 32
 // bytes, or 64 bytes of nibbles), and no more than a panel has units of rows (64 of up to 128 bytes, 32 of 256, 16 beyond).
-// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at nine in ten, 10 % at
-// worst (profiles/sddmm_waves.txt; which points lie between 3 and 8 % changes from run to run).
+// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at nine in ten, about
+// 11 % at worst: two byte planes, 512 panels of 20 chunks, 10.9 us with 4 waves, 10.0 with 8 (profiles/sddmm_waves.txt).
 int choose_sddmm_waves(const mc_mat *mask, int batch, int row_bytes, int bits, const mc_options &o)
 {
     if (o.sddmm_waves != 0) return o.sddmm_waves < 0 ? 0 : o.sddmm_waves; // 0 selects the direct-load kernel in launch_sddmm
