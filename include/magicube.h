@@ -225,11 +225,11 @@ int mc_merge_host(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, con
  * (the call returns after the upload has completed).  values == NULL or lhs_bits == 0
  * gives a pattern-only mask (for SDDMM / attention).  *out is owned by the caller
  * until mc_mat_destroy.  Errors as mc_pack_host, plus MC_EHIP / MC_ENOMEM.
- * An operand with values is stored up to four times, in the forms that mc_spmm chooses from, and building it takes as
+ * An operand with values is stored up to five times, in the forms that mc_spmm chooses from, and building it takes as
  * long as writing them: the panel format (its values, padded, and 4 bytes per slot); the merged copy (see mc_merge_host: the
  * panel format of the merged operand and 4 bytes per merged vector and panel of its group) unless it would hold more vectors
- * than the operand; and an LDS-ordered copy (the values, and 6 bytes per slot) of either where the SpMM form that needs
- * it is expected to be the fastest for some width of B.  spmm_merge = -1 and spmm_slab = -1 in the creating
+ * than the operand; and an LDS-ordered copy (the values, and 6 bytes per slot) of either, and a copy with all
+ * columns (see mc_set_spmm_dense), where the SpMM form that needs it is expected to be the fastest for some width of B.  spmm_merge = -1 and spmm_slab = -1 in the creating
  * thread's options leave them out.  (4096 x 4096, V = 8, 90 % empty, 8 bits: 1.8 MB of values, 13 MB on the device.) */
 int mc_mat_create(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
                   const void *values, void *stream, mc_mat **out);
@@ -279,8 +279,9 @@ int mc_spmm_flags(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec pr
 int mc_spmm_ex(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, unsigned flags,
                const mc_options *options, int32_t *C_dev, int ldc, void *stream);
 /* Which form mc_spmm_ex would run for this operand, width and options (host only, launches nothing):
- * bit 0: 0 = rows of B gathered per stored vector, 1 = rows of B resident in LDS; bit 1 (value 2): on the
- * operand's merged copy (see mc_merge_host).  Negative: an error code. */
+ * bit 0: 0 = rows of B gathered per stored vector, 1 = rows of B resident in LDS; bit 1 (value 2): on merged
+ * panels (see mc_merge_host); bit 2 (value 4, and value 2 where the operand has merged panels): on the copy that
+ * holds blocks of 16 rows with all their columns (see mc_set_spmm_dense).  Negative: an error code. */
 int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_options *options);
 /* Measurement aid: the time in us that this choice expects of the form it takes (results of out_bytes = 2 or 4
  * bytes; the options can pin each form in turn).  Negative: an error code. */
@@ -533,6 +534,13 @@ int mc_set_spmm_stages(int stages);
  * (first cleared) rows of such panels.  enable = 0 turns this off (one workgroup per panel and
  * row tile, as for regular matrices); the result is the same either way. */
 int mc_set_spmm_splitting(int enable);
+/* The SpMM form for patterns whose blocks of 16 rows name nearly every column: mc_mat_create then also stores
+ * the operand with all its columns (M * K bytes, twice that for 16- and 12-bit values), zeros where nothing is
+ * stored, and calls without unsigned flags, with an 8- or 4-bit B and no other option pinned choose that form
+ * where it is expected to be the fastest.  For the calling thread, tests and measurements: mode 0 automatic,
+ * -1 never (nor built by mc_mat_create on this thread), 1 wherever it exists (and built whatever the pattern);
+ * tile -1 automatic, 0 .. 5 one of the kernel's tile shapes, largest first.  MC_EINVAL otherwise. */
+int mc_set_spmm_dense(int mode, int tile);
 /* (The switch also governs the work items of mc_sddmm.  There every item writes its own outputs,
  * so a pattern-only mask is cut finer: into pieces of at most the average panel length, at least
  * 8 chunks, as soon as one panel is longer than that; a mask with fewer than 256 panels into

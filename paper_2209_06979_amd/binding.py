@@ -141,13 +141,14 @@ def _load() -> ctypes.CDLL:
     L.mc_set_attention_mode.argtypes = [c_int]
     L.mc_set_spmm_splitting.argtypes = [c_int]
     L.mc_set_spmm_stages.argtypes = [c_int]
+    L.mc_set_spmm_dense.argtypes = [c_int, c_int]
     L.mc_set_sddmm_variant.argtypes = [c_int]
     L.mc_set_softmax_variant.argtypes = [c_int]
     for name in ("mc_layout_query", "mc_pack_host", "mc_unpack_host", "mc_mat_create", "mc_mat_set_values_device",
                  "mc_mat_info", "mc_spmm", "mc_spmm_flags", "mc_sddmm", "mc_sddmm_flags", "mc_sparse_softmax", "mc_sparse_softmax_bits", "mc_sparse_attention",
                  "mc_sparse_attention_strided", "mc_sparse_attention_bits", "mc_sparse_attention_batched", "mc_probe_gather",
                  "mc_absmax", "mc_quantize", "mc_sparse_attention_out", "mc_spmm_dequant", "mc_sddmm_dequant", "mc_sparse_softmax_to_mat",
-                 "mc_set_spmm_variant", "mc_set_attention_mode", "mc_set_sddmm_variant", "mc_set_spmm_splitting", "mc_set_spmm_stages",
+                 "mc_set_spmm_variant", "mc_set_attention_mode", "mc_set_sddmm_variant", "mc_set_spmm_splitting", "mc_set_spmm_stages", "mc_set_spmm_dense",
                  "mc_set_softmax_variant", "mc_set_thread_options", "mc_get_thread_options", "mc_spmm_ex", "mc_sddmm_ex",
                  "mc_sparse_attention_ex", "mc_sparse_attention_static", "mc_blocked_query", "mc_pack_blocked_host", "mc_sddmm_to_mat", "mc_probe_mfma", "mc_spmm_form",
                  "mc_attention_form", "mc_mat_merged_info", "mc_merged_query", "mc_merge_host", "mc_probe_spmm_phases"):
@@ -334,6 +335,10 @@ def set_spmm_splitting(enable: bool = True) -> None:
     _check(lib.mc_set_spmm_splitting(1 if enable else 0), "mc_set_spmm_splitting")
 
 
+def set_spmm_dense(mode: int = 0, tile: int = -1) -> None:
+    _check(lib.mc_set_spmm_dense(mode, tile), "mc_set_spmm_dense")
+
+
 def set_sddmm_variant(waves: int = -1) -> None:
     _check(lib.mc_set_sddmm_variant(waves), "mc_set_sddmm_variant")
 
@@ -347,11 +352,12 @@ def set_attention_mode(mode: int = 0) -> None:
 
 
 def spmm_form(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> str:
-    """The form mc_spmm_ex would take for this operand: "gather" or "lds" (rows of B resident in LDS)."""
+    """The form mc_spmm_ex would take for this operand: "gather", "lds" (rows of B resident in LDS) or
+    "dense" (the operand held with all its columns)."""
     r = lib.mc_spmm_form(A.handle, N, PREC[prec], ctypes.byref(options) if options is not None else None)
     if r < 0:
         _check(r, "mc_spmm_form")
-    return "lds" if r & 1 else "gather"
+    return "dense" if r & 4 else "lds" if r & 1 else "gather"
 
 
 def spmm_form_us(A: SparseMatrix, N: int, prec: str, out_bytes: int = 4, options: Options | None = None) -> float:

@@ -16,6 +16,10 @@ namespace {
 // options it was handed or these once, at entry, and never looks at shared state afterwards.
 thread_local mc_options t_options = {};
 
+// The calling thread's choice for the SpMM form that holds an operand with all its columns (mc_set_spmm_dense).
+struct DenseChoice { int mode, tile; }; // mode 0 automatic, -1 never, 1 wherever it exists; tile -1 automatic
+thread_local DenseChoice t_dense = {0, -1};
+
 bool valid_options(const mc_options &o)
 {
     const int b = o.spmm_row_tile_bytes, w = o.spmm_waves, d = o.sddmm_waves;
@@ -111,6 +115,7 @@ void free_device(mc_mat *A)
     if (A->d_class_panels) (void)hipFree(A->d_class_panels);
     if (A->d_merge_src) (void)hipFree(A->d_merge_src);
     if (A->d_chunk_panel) (void)hipFree(A->d_chunk_panel);
+    if (A->d_dense) (void)hipFree(A->d_dense);
     if (A->merged) {
         free_device(A->merged);
         delete A->merged;
@@ -265,6 +270,13 @@ extern "C" int mc_set_spmm_splitting(int enable)
     return set_field([&](mc_options &o) { o.spmm_splitting = enable ? 0 : -1; });
 }
 
+extern "C" int mc_set_spmm_dense(int mode, int tile)
+{
+    if (mode < -1 || mode > 1 || tile < -1 || tile >= DENSE_TILES) return MC_EINVAL;
+    t_dense = {mode, tile};
+    return MC_OK;
+}
+
 extern "C" int mc_set_sddmm_variant(int waves)
 {
     // this setter's own convention: -1 automatic, 0 the direct-load kernel
@@ -373,10 +385,51 @@ double gather_us(const mc_mat *A, int row_bytes, int rb, int out_bytes, const mc
            share * c.chunk + std::max(0.0, longest_share - share) * bnb / 64 * c.late;
 }
 
+// With all columns: the tile shape and the expected time.
+struct DensePlan { int tile; double us; };
+
+int64_t dense_bytes(int M, int K, int bits) { return (int64_t)((M + 15) / 16) * ((K + MC_CHUNK - 1) / MC_CHUNK) * 1024 * (bits > 8 ? 2 : 1); }
+
+bool dense_possible(int M, int K, int bits)
+{
+    return M > 0 && K > 0 && bits != 0 && dense_bytes(M, K, bits) <= INT32_MAX;
+}
+
+// Expected time: launch and start; then the longer of a workgroup's steps one after the other (as many turns as its compute unit cannot
+// hold of them at once) and of all steps of a compute unit at the rate at which it takes in operands, each with what starting and
+// finishing a tile costs; and the stores.  Fitted per tile, planes and width of B to 900 drawn operands, three copies in turn (256 .. 16000
+// rows, 512 .. 8192 columns, rows of B of 32 .. 1024 bytes): off by 2 - 7 % in the median and by 6 - 24 % in nine cases of ten; the tile
+// picked is 0.5 % slower than the best on average, 25 % at worst, and where the time expected is 3 % below the measured one of the other
+// forms (237 of the 900) the call is 1.2 times as fast in the mean.
+DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_bytes)
+{
+    struct Cost { double start, step, stream, store, tile; };
+    static const Cost cost[2][2][DENSE_TILES] =
+       {{{{1.54e-06, 0.328, 0.562, 1.2e-07, 6.31}, {2.92e-08, 0.424, 0.1, 2.1e-07, 5.62}, {3.45, 0.308, 0.404, 1.5e-07, 0}, {2.91, 0.219, 0.302, 7.4e-08, 0.155}, {1.58, 0.379, 0.401, 5.6e-07, 1.03}, {2.16, 0.0648, 0.176, 2.1e-09, 1.11}},
+         {{2.63, 0.357, 0.569, 1e-07, 4.22}, {5.04e-07, 0.443, 0.603, 9.6e-08, 6.34}, {3.41, 0.258, 0.377, 1.3e-07, 0.677}, {2.96, 0.197, 0.26, 1.2e-07, 0.695}, {1.97, 0.297, 0.359, 3.5e-07, 1.87}, {3.05, 0.119, 0.145, 3.4e-08, 0}}},
+        {{{3.16, 0.355, 0.527, 9.1e-08, 1.69}, {1.15, 0.417, 0.57, 7.1e-09, 4.42}, {0.703, 0.467, 0.225, 2e-07, 3.61}, {3.16, 0.283, 0.405, 2.1e-07, 0.311}, {1.81, 0.468, 0.512, 3.9e-07, 1.82}, {2.76, 0.16, 0.22, 7.6e-08, 0}},
+         {{0.314, 0.415, 0.542, 7.7e-08, 4.75}, {1.02, 0.513, 0.0347, 1.4e-07, 4.19}, {1.36, 0.437, 0.514, 1.2e-07, 3.63}, {3.65, 0.285, 0.354, 2e-07, 0.353}, {2.12, 0.412, 0.479, 6.1e-07, 2.05}, {3.09, 0.157, 0.184, 4e-07, 0}}}};
+    const int planes = bits > 8 ? 2 : 1, cols = row_bytes * (r4 ? 2 : 1), chunks = (K + MC_CHUNK - 1) / MC_CHUNK;
+    DensePlan best = {-1, 1e30};
+    for (int tile = 0; tile < DENSE_TILES; ++tile) {
+        if (t_dense.tile >= 0 && tile != t_dense.tile) continue;
+        const Cost &c = cost[planes - 1][r4][tile];
+        const int rows = dense_tile_rows(tile, planes), turn = dense_tile_turn(tile), share = dense_tile_share(tile);
+        const int at_once = tile == 5 ? 4 : tile == 3 || (tile == 2 && planes == 1) ? 2 : 1; // workgroups of a compute unit
+        const int steps = ((chunks + share - 1) / share + turn - 1) / turn * turn;
+        const int64_t tiles = (int64_t)((M + rows - 1) / rows) * ((cols + dense_tile_cols(tile) - 1) / dense_tile_cols(tile));
+        const double turns = (double)((tiles + 256 * at_once - 1) / (256 * at_once)), mean = tiles / 256.0, most = (double)((tiles + 255) / 256);
+        const double us = c.start + std::max(turns * (steps * c.step + c.tile), 0.5 * (mean + most) * (steps * c.stream + c.tile / at_once)) +
+                          (double)M * cols * out_bytes * c.store;
+        if (us < best.us) best = {tile, us};
+    }
+    return best;
+}
+
 // Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines; by a
 // tenth at least where the merged copy has such a copy already.  (Of 1385 drawn operands 33 then have both, with 2 %
 // 106; the forms they run in lose the same 2.0 % over the best on average.)
-bool resident_worth_building(const mc_mat *A)
+bool resident_worth_building(const mc_mat *A, bool dense_rival)
 {
     const mc_options automatic = {};
     for (int row_bytes : {1024, 512, 256, 128}) {
@@ -384,6 +437,7 @@ bool resident_worth_building(const mc_mat *A)
             SlabPlan pl;
             plan_slab(A, row_bytes, r4, 4, automatic, &pl);
             double best = 0.98 * gather_us(A, row_bytes, r4 ? 4 : 8, 4, automatic);
+            if (dense_rival) best = std::min(best, plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, 4).us);
             if (A->merged) {
                 best = std::min(best, 0.98 * gather_us(A->merged, row_bytes, r4 ? 4 : 8, 4, automatic));
                 if (A->merged->d_blk_recs) {
@@ -401,6 +455,35 @@ bool resident_worth_building(const mc_mat *A)
 } // namespace
 
 namespace {
+// Whether the copy with all columns is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines.
+bool dense_worth_building(const mc_mat *A)
+{
+    const mc_options automatic = {};
+    for (int row_bytes : {1024, 512, 256, 128}) {
+        for (int r4 = (A->lhs_bits == 4); r4 < 2; ++r4) {
+            double best = 1e30;
+            for (const mc_mat *X : {A, (const mc_mat *)A->merged}) {
+                if (!X) continue;
+                best = std::min(best, gather_us(X, row_bytes, r4 ? 4 : 8, 4, automatic));
+                if (!X->blk_chunks) continue;
+                SlabPlan pl;
+                plan_slab(X, row_bytes, r4, 4, automatic, &pl);
+                best = std::min(best, pl.us);
+            }
+            if (plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, 4).us < 0.98 * best) return true;
+        }
+    }
+    return false;
+}
+
+DenseFillArgs dense_fill_args(const mc_mat *A)
+{
+    DenseFillArgs f = {};
+    f.panel_ptr = A->d_panel_ptr; f.slot_idx = A->d_slot_idx; f.vals = A->d_vals; f.dst = A->d_dense;
+    f.P = A->P; f.V = A->V; f.bits = A->lhs_bits == 12 ? 16 : A->lhs_bits; f.nch = (A->K + MC_CHUNK - 1) / MC_CHUNK;
+    return f;
+}
+
 // Whether mc_mat_create builds the merged copy (lay: the operand, ml: its merged form).  The copy holds
 // ml.nvec * rows values; which of the two a call uses is decided per call (spmm_form).
 bool merged_worth_building(const mc_layout &lay, const mc_merged_layout &ml) { return ml.nvec <= lay.nvec; }
@@ -451,6 +534,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     A->d_blk_ptr = nullptr; A->d_blk_recs = nullptr; A->d_blk_ends = nullptr; A->d_blk_src = nullptr;
     A->d_class_panels = nullptr;
     A->merged = nullptr; A->merge_group = 0; A->d_merge_src = nullptr; A->d_chunk_panel = nullptr; A->merged_valid = false;
+    A->d_dense = nullptr; A->dense_valid = false;
     // Length classes of the panels (V = 8: the attention kernel gives a panel 1, 2, 4 or 8 waves)
     std::vector<int32_t> class_panels;
     for (int b = 0; b <= 4; ++b) A->class_start[b] = 0;
@@ -556,6 +640,9 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             A->merge_group = group;
         }
     }
+    // (a thread that pins or forbids the other copies gets those and no others)
+    const bool dense_allowed = t_dense.mode == 1 || (t_dense.mode == 0 && t_options.spmm_merge == 0 && t_options.spmm_slab == 0);
+    const bool dense_rival = dense_allowed && dense_possible(M, K, lhs_bits);
     // LDS-ordered copy for the SpMM that keeps rows of B resident in LDS, where that form is expected to be the fastest one
     // for some width of B (the merged copy's forms included), unless the thread's options rule that kernel out (1: built whatever the shape, so that the
     // form can be forced).
@@ -566,7 +653,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         ResidentLayout rl;
         mc_resident_query(K, lay.P, row_ptr, col_idx, &rl);
         A->blk_nt = rl.nt; A->block_rows = rl.block_rows; A->nblk = rl.nblk; A->blk_chunks = rl.nchunks;
-        if (rl.nchunks * MC_CHUNK <= INT32_MAX && (t_options.spmm_slab == 1 || resident_worth_building(A))) {
+        if (rl.nchunks * MC_CHUNK <= INT32_MAX && (t_options.spmm_slab == 1 || resident_worth_building(A, dense_rival))) {
             try {
                 blk_ptr.resize((size_t)lay.P * rl.nblk + 1);
                 blk_src.resize((size_t)rl.nchunks * MC_CHUNK);
@@ -600,6 +687,8 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             A->nblk = 0; A->blk_chunks = 0;
         }
     }
+    // The operand with all its columns, where that form is expected to be the fastest for some width of B
+    const bool dense = !child && dense_rival && lay.nvec > 0 && (t_dense.mode == 1 || dense_worth_building(A));
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define MC_TRY(call) (ok = ok && hip_ok((call), #call))
     bool ok = true;
@@ -658,6 +747,11 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     if (!class_panels.empty()) {
         MC_TRY(hipMalloc(&A->d_class_panels, sizeof(int32_t) * class_panels.size()));
         MC_TRY(hipMemcpyAsync(A->d_class_panels, class_panels.data(), sizeof(int32_t) * class_panels.size(), hipMemcpyHostToDevice, s));
+    }
+    if (dense) {
+        MC_TRY(hipMalloc(&A->d_dense, (size_t)dense_bytes(M, K, lhs_bits)));
+        if (ok) MC_TRY(launch_dense_fill(dense_fill_args(A), s));
+        A->dense_valid = true;
     }
     if (A->merged) {
         MC_TRY(hipMalloc(&A->d_merge_src, sizeof(int32_t) * m_src.size()));
@@ -732,6 +826,10 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
         }
     }
     MC_HIP(launch_set_values(a, static_cast<hipStream_t>(stream)));
+    if (A->d_dense) {
+        MC_HIP(launch_dense_fill(dense_fill_args(A), static_cast<hipStream_t>(stream)));
+        A->dense_valid = true;
+    }
     A->blk_valid = A->d_blk_recs != nullptr;
     if (A->merged) {
         A->merged->blk_valid = A->merged->d_blk_recs != nullptr;
@@ -749,28 +847,41 @@ inline int spmm_stages_for(const mc_options &o, int K, int64_t ldb_bytes, int ro
 }
 
 // The form one SpMM call takes: the operand or its merged copy, and whether rows of B are resident in LDS (then plan is
-// the work split).
-struct SpmmForm { const mc_mat *A; bool slab; SlabPlan plan; };
+// the work split), or the operand with all its columns (dense: the tile shape, else -1).
+struct SpmmForm { const mc_mat *A; bool slab; SlabPlan plan; int dense; };
 
-SpmmForm spmm_form(const mc_mat *A, int row_bytes, int rb, int out_bytes, unsigned flags, const mc_options &o)
+// ldb_bytes: from row to row of B
+SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, int out_bytes, unsigned flags, const mc_options &o)
 {
     const bool r4 = rb == 4;
     const bool slab_possible = o.spmm_slab != -1 && flags == 0 && rb != 16 && o.spmm_row_tile_bytes == 0 && o.spmm_waves == 0;
     // a 16-row panel leaves no MFMA row for the column sums that unsigned operands need
     const bool merged_possible = A->merged && A->merged_valid && o.spmm_merge != -1 && !(flags != 0 && A->merged->V > 8);
-    SpmmForm f = {A, false, {}};
+    SpmmForm f = {A, false, {}, -1};
     double best = 1e30;
+    if (A->d_dense && A->dense_valid && t_dense.mode != -1 && flags == 0 && rb != 16 && o.spmm_slab == 0 && o.spmm_merge == 0 &&
+        o.spmm_row_tile_bytes == 0 && o.spmm_waves == 0 && (A->K - 1) * ldb_bytes + row_bytes <= INT32_MAX && (A->K + 8192) * ldb_bytes <= UINT32_MAX) {
+        const DensePlan d = plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, out_bytes);
+        if (d.tile >= 0) {
+            f.dense = d.tile;
+            // (its expected times and the others' were fitted apart.  Taken by 3 % or more: of 400 drawn operands 73 change their form and
+            // run 1.22 times as fast in the mean, one in twenty of them 4 - 5 % slower; rows of less than 64 bytes by 15 %: their gather
+            // is expected up to a fifth too slow)
+            f.plan.us = d.us;
+            best = t_dense.mode == 1 ? 0.0 : d.us * (row_bytes < 64 ? 1.15 : 1.03);
+        }
+    }
     for (int m = (merged_possible && o.spmm_merge == 1) ? 1 : 0; m <= (merged_possible ? 1 : 0); ++m) {
         const mc_mat *X = m ? A->merged : A;
         const bool slab = slab_possible && X->d_blk_recs && X->blk_valid;
-        if (!slab && !merged_possible) return f;                    // nothing to choose
+        if (!slab && !merged_possible && f.dense < 0) return f;     // nothing to choose
         SlabPlan pl;
         pl.us = 1e30;
         if (slab) plan_slab(X, row_bytes, r4, out_bytes, o, &pl);
         const double gather = (slab && o.spmm_slab == 1) ? 1e30 : gather_us(X, row_bytes, rb, out_bytes, o);
         if (std::min(gather, pl.us) < best) {
             best = std::min(gather, pl.us);
-            f.A = X; f.slab = pl.us < gather; f.plan = pl;
+            f.A = X; f.slab = pl.us < gather; f.plan = pl; f.dense = -1;
         }
     }
     return f;
@@ -799,7 +910,7 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
 
     // the operand's merged copy (panels of 8 or 16 rows at the union of their columns) where it is expected to be faster
     const int rows = A->M;
-    const SpmmForm form = spmm_form(A, N * rb / 8, rb, out_mode == 2 ? 2 : 4, flags, o);
+    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)ldb * rb / 8, rb, out_mode == 2 ? 2 : 4, flags, o);
     A = form.A;
 
     SpmmArgs a = {};
@@ -811,6 +922,15 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
     a.row_bytes = N * rb / 8;
     a.C = C_dev; a.ldc = ldc; a.C_batch_stride = 0;
     a.P = A->P; a.V = A->V; a.batch = 1; a.float_out = out_mode; a.out_scale = out_mode ? scale : 1.f;
+    if (form.dense >= 0) {
+        DenseArgs da = {};
+        da.A = A->d_dense; da.a_bytes = (int)dense_bytes(A->M, A->K, A->lhs_bits);
+        da.nrb = (A->M + 15) / 16; da.nch = (A->K + MC_CHUNK - 1) / MC_CHUNK;
+        da.B = a.B; da.ldb_bytes = a.ldb_bytes; da.b_bytes = (int)((A->K - 1) * a.ldb_bytes + a.row_bytes); da.cols = N;
+        da.C = C_dev; da.ldc = ldc; da.rows = rows; da.float_out = out_mode; da.out_scale = a.out_scale;
+        MC_HIP(launch_spmm_dense(prec, da, form.dense, static_cast<hipStream_t>(stream)));
+        return MC_OK;
+    }
     if (form.slab) {
         const SlabPlan &pl = form.plan;
         SlabArgs sa = {};
@@ -870,8 +990,8 @@ extern "C" int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_optio
     mc_options o;
     if (resolve_options(options ? options : &automatic, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
-    const SpmmForm form = spmm_form(A, N * rb / 8, rb, 4, 0u, o);
-    return (form.slab ? 1 : 0) | (form.A != A ? 2 : 0);
+    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, 4, 0u, o);
+    return form.dense >= 0 ? 4 | (A->merged ? 2 : 0) : (form.slab ? 1 : 0) | (form.A != A ? 2 : 0);
 }
 
 extern "C" double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_bytes, const mc_options *options)
@@ -881,8 +1001,8 @@ extern "C" double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_
     mc_options o;
     if (resolve_options(options ? options : &automatic, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
-    const SpmmForm form = spmm_form(A, N * rb / 8, rb, out_bytes, 0u, o);
-    return form.slab ? form.plan.us : gather_us(form.A, N * rb / 8, rb, out_bytes, o);
+    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, out_bytes, 0u, o);
+    return form.slab || form.dense >= 0 ? form.plan.us : gather_us(form.A, N * rb / 8, rb, out_bytes, o);
 }
 
 extern "C" int mc_spmm_dequant(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, unsigned flags,
@@ -1049,6 +1169,7 @@ extern "C" int mc_sddmm_to_mat(const void *Q_dev, int ldq, const void *Kmat_dev,
     if (P->n_items && o.spmm_splitting != -1) { a.items = P->d_items; a.n_units = P->n_items; }
     P->blk_valid = false; // only the panel format receives the new values
     P->merged_valid = false;
+    P->dense_valid = false;
     MC_HIP(launch_sddmm(bits, a, choose_sddmm_waves(P, 1, a.row_bytes, bits, o), static_cast<hipStream_t>(stream)));
     return MC_OK;
 }
@@ -1109,6 +1230,7 @@ extern "C" int mc_sparse_softmax_to_mat(mc_mat *P, const int32_t *S_dev, float s
     a.max_panel_chunks = P->max_panel_chunks; a.variant = o.softmax_variant;
     P->blk_valid = false; // only the panel format receives the new values
     P->merged_valid = false;
+    P->dense_valid = false;
     MC_HIP(launch_softmax(a, static_cast<hipStream_t>(stream)));
     return MC_OK;
 }

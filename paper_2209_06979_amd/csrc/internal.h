@@ -51,6 +51,9 @@ struct mc_mat {
     int32_t *d_merge_src;      // merged nvec * merge_group: interchange vector of each panel's share, -1 = zeros
     int32_t *d_chunk_panel;    // panel of each chunk of the panel format (operands with values)
     bool merged_valid;         // false once the values were replaced in the panel format only
+    // The operand with all its columns (null when not built; see spmm_dense_kernels.hip).
+    uint8_t *d_dense;
+    bool dense_valid;          // false once the values were replaced in the panel format only
 };
 
 // Builders that also take V = 16 (4- and 8-bit values): the library's merged copies only.
@@ -142,6 +145,35 @@ struct SlabArgs {
     int groups;                // panel groups (workgroups per column tile)
     int wpp;                   // waves sharing a panel (its chunks dealt round-robin); above 1 only if every wave has one panel
     int waves;                 // per workgroup, a multiple of wpp
+};
+
+// One launch of the SpMM on an operand held with all its columns (see spmm_dense_kernels.hip).
+struct DenseArgs {
+    const uint8_t *A;          // [block of 16 rows][chunk of 64 columns][plane] fragments of 1 KB: 16 bytes of lane j + 16 g = row j, columns 16 g ..
+    int a_bytes;               // its size
+    int nrb, nch;              // row blocks, chunks
+    const uint8_t *B;
+    int64_t ldb_bytes;
+    int b_bytes;               // from B's first byte to the end of the last row's part that takes part
+    void *C;
+    int64_t ldc;
+    int rows, cols;            // of C
+    int float_out;             // as in SpmmArgs
+    float out_scale;
+    int tm, tn;                // filled by the launcher: row and column tiles
+};
+constexpr int DENSE_TILES = 6; // tile shapes of that kernel, numbered from the largest: rows and columns
+constexpr int dense_tile_rows(int tile, int planes) { return tile < 2 ? (planes == 1 ? 256 : 128) >> tile : tile == 2 ? 128 : tile == 3 ? 64 : 32; }
+constexpr int dense_tile_cols(int tile) { return tile < 2 ? 128 : tile == 5 ? 32 : 64; }
+// groups of waves that take turns at its chunks, and the steps that its loop runs as one
+constexpr int dense_tile_share(int tile) { return tile == 0 ? 1 : tile == 4 ? 4 : 2; }
+constexpr int dense_tile_turn(int tile) { return tile < 4 ? 4 : 8; }
+// The copy that kernel reads, written from the panel format.
+struct DenseFillArgs {
+    const int32_t *panel_ptr, *slot_idx;
+    const uint8_t *vals;
+    uint8_t *dst;
+    int P, V, bits, nch;       // bits 4, 8 or 16
 };
 
 struct SddmmArgs {
@@ -239,6 +271,10 @@ hipError_t launch_spmm(mc_prec prec, const SpmmArgs &a, int bnb, int waves, hipS
 hipError_t launch_spmm_phase_probe(const SpmmArgs &a, hipStream_t s);
 // nt: segments (16 bytes) of a column tile, 2 or 4, at most a.nt.  Precisions with a 16-bit B are not built.
 hipError_t launch_spmm_slab(mc_prec prec, const SlabArgs &a, int nt, hipStream_t s);
+// tile: 0 .. DENSE_TILES - 1.  Precisions with a 16-bit B are not built.  A and B span less than 2 GiB each, and
+// 8192 rows more of B less than 4 GiB (the kernel's offsets run ahead of the last row, to where its loads return zeros).
+hipError_t launch_spmm_dense(mc_prec prec, const DenseArgs &a, int tile, hipStream_t s);
+hipError_t launch_dense_fill(const DenseFillArgs &a, hipStream_t s);
 hipError_t launch_set_values(ValuesArgs a, hipStream_t s);
 // clears the C rows (int32, n columns) of the listed panels
 hipError_t launch_zero_rows(int32_t *C, int64_t ldc, int n, int V, const int32_t *panels, int n_panels, hipStream_t s);
