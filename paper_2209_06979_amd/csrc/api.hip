@@ -105,6 +105,7 @@ void free_device(mc_mat *A)
     if (A->d_slot_idx) (void)hipFree(A->d_slot_idx);
     if (A->d_vals) (void)hipFree(A->d_vals);
     if (A->d_items) (void)hipFree(A->d_items);
+    if (A->d_shares) (void)hipFree(A->d_shares);
     if (A->d_split_panels) (void)hipFree(A->d_split_panels);
     if (A->d_blk_ptr) (void)hipFree(A->d_blk_ptr);
     if (A->d_blk_recs) (void)hipFree(A->d_blk_recs);
@@ -123,20 +124,22 @@ void free_device(mc_mat *A)
     }
 }
 
-// Waves per panel for SDDMM: enough to put about 3200 waves on the chip (4096 of the light ones that stage rows of 32
-// bytes, or 64 bytes of nibbles), and no more than a panel has units of rows (64 of up to 128 bytes, 32 of 256, 16 beyond).
-// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at nine in ten, about
-// 11 % at worst: two byte planes, 512 panels of 20 chunks, 10.9 us with 4 waves, 10.0 with 8 (profiles/sddmm_waves.txt).
-int choose_sddmm_waves(const mc_mat *mask, int batch, int row_bytes, int bits, const mc_options &o)
+// Waves per share of the mask for SDDMM: enough to put about 3200 waves on the chip (4096 of the light ones that stage rows of 32
+// bytes, or 64 bytes of nibbles), no more than a share has units of rows (64 of up to 128 bytes, 32 of 256, 16 beyond), and
+// so many that no wave has more than 24 units.
+// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at 66, 9 % off at
+// worst (profiles/sddmm_waves.txt).
+int choose_sddmm_waves(const mc_mat *mask, int shares, int batch, int row_bytes, int bits, const mc_options &o)
 {
     if (o.sddmm_waves != 0) return o.sddmm_waves < 0 ? 0 : o.sddmm_waves; // 0 selects the direct-load kernel in launch_sddmm
-    const double avg = mask->P ? (double)(mask->nslots / MC_CHUNK) / mask->P : 0.0;
+    const double avg = shares ? (double)(mask->nslots / MC_CHUNK) / shares : 0.0;
     const double units = avg * (row_bytes <= 128 ? 1 : (row_bytes <= 256 ? 2 : 4));
-    const double groups = (double)mask->P * (batch > 0 ? batch : 1);
+    const double groups = (double)shares * (batch > 0 ? batch : 1);
     const double target = (row_bytes <= 32 || (bits == 4 && row_bytes <= 64)) ? 4096.0 : 3200.0;
     int w = 1;
     // (down to one unit per wave, e.g. 32 panels of 7 chunks: 2.8 us with 4 waves, 2.4 us with 8)
     while (w < 8 && groups * w * 2 <= target && w < units) w *= 2;
+    while (w < 8 && units > 24 * w) w *= 2;
     return w;
 }
 
@@ -476,6 +479,40 @@ bool dense_worth_building(const mc_mat *A)
     return false;
 }
 
+// Appends the panels in pieces to `shares` (see mc_mat) if any is cut; returns their number.
+int cut_shares(const mc_mat *A, const int32_t *row_ptr, const int32_t *panel_ptr, std::vector<int32_t> &shares)
+{
+    // Pieces of the average panel's chunks; of fewer than 256 panels, of as few (two at least) as make 512 of them.  Whole calls, us, against
+    // pieces of 8 chunks at least, 256 of them at least:  L16-R16, 2000 x 3100, V = 4, 90 % empty, unequal (sigma = 0.5), Kd = 200
+    // 9.5 -> 8.6;  L8-R8, 4096 x 4096, V = 8, 90 %, unequal (1), Kd = 256 7.2 -> 6.6;  512 x 4096, half empty 5.6 -> 4.5.  Equal panels of
+    // 256 and more are better whole (681 of 4 chunks 4.9, halved 5.4) or gain nothing to rely on (512 of 7 chunks 6.0,
+    // in pieces of 4 / 3 / 2 chunks 6.0 / 5.7 / 6.3).
+    const double total = (double)(A->nslots / MC_CHUNK);
+    const int cap = std::max(2, (int)std::ceil(A->P >= 256 ? total / A->P : std::min(total / A->P, total / 512)));
+    if (A->max_panel_chunks <= cap) return 0;
+    std::vector<std::vector<int32_t>> by_length((size_t)cap + 1); // longest first: they start first and do not form the tail
+    for (int p = 0; p < A->P; ++p) {
+        const int n = row_ptr[p + 1] - row_ptr[p], c = (n + MC_CHUNK - 1) / MC_CHUNK, pieces = (c + cap - 1) / cap, per = pieces ? (c + pieces - 1) / pieces : 0;
+        for (int b = 0; b < c; b += per) {
+            const int e = std::min(c, b + per);
+            auto &to = by_length[(size_t)(e - b)];
+            to.insert(to.end(), {panel_ptr[2 * (size_t)p] + b * MC_CHUNK, std::min(n, e * MC_CHUNK) - b * MC_CHUNK, p, row_ptr[p] + b * MC_CHUNK});
+        }
+    }
+    const size_t before = shares.size();
+    for (size_t l = by_length.size(); l-- > 0;) shares.insert(shares.end(), by_length[l].begin(), by_length[l].end());
+    return (int)((shares.size() - before) / 4);
+}
+
+// The shares of one SDDMM launch (cut: panels of unequal length in pieces)
+void take_shares(const mc_mat *A, bool cut, SddmmArgs *a)
+{
+    const bool pieces = cut && A->n_cut > 0;
+    a->shares = A->d_shares + (pieces ? 4 * (int64_t)A->P : 0);
+    a->n_shares = pieces ? A->n_cut : A->P;
+    a->kmat_rows = A->K;
+}
+
 DenseFillArgs dense_fill_args(const mc_mat *A)
 {
     DenseFillArgs f = {};
@@ -529,6 +566,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     A->d_vals = nullptr;
     A->d_items = A->d_split_panels = nullptr;
     A->n_items = A->n_split = 0;
+    A->d_shares = nullptr; A->n_cut = 0;
     A->max_item_chunks = 0;
     A->blk_nt = A->block_rows = A->nblk = 0; A->blk_chunks = 0; A->blk_valid = false; A->d_order = A->d_splits = nullptr;
     A->d_blk_ptr = nullptr; A->d_blk_recs = nullptr; A->d_blk_ends = nullptr; A->d_blk_src = nullptr;
@@ -564,7 +602,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     std::vector<int32_t> items, split_panels;
     {
         const double avg = lay.P ? (double)(lay.nslots / MC_CHUNK) / lay.P : 0.0;
-        // A pattern-only mask (SDDMM: every item writes its own outputs, nothing to add up) is cut
+        // A pattern-only mask (its items serve the last SpMM of the attention layer's pipeline, on request) is cut
         // as soon as a panel exceeds the average rounded up to 8 chunks.
         // With fewer than 256 panels the pieces also get short enough to make 256 of them.
         const bool mask_only = (lhs_bits == 0);
@@ -603,6 +641,18 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             A->n_split = (int)split_panels.size();
             A->max_item_chunks = 0;
             for (size_t i = 0; i < items.size(); i += 4) A->max_item_chunks = std::max(A->max_item_chunks, items[i + 2] - items[i + 1]);
+        }
+    }
+    // Shares of the SDDMM: every share writes its own outputs, nothing is added up
+    std::vector<int32_t> shares;
+    if (!child && lay.P > 0) {
+        try {
+            shares.reserve((size_t)lay.P * 4);
+            for (int p = 0; p < lay.P; ++p) shares.insert(shares.end(), {panel_ptr[2 * (size_t)p], row_ptr[p + 1] - row_ptr[p], p, row_ptr[p]});
+            A->n_cut = cut_shares(A, row_ptr, panel_ptr.data(), shares);
+        } catch (const std::bad_alloc &) {
+            delete A;
+            return MC_ENOMEM;
         }
     }
     // Merged copy for the SpMM: panels of fewer rows than the matrix unit takes share one panel of 16 rows (4- and
@@ -717,6 +767,10 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             for (int c = panel_ptr[2 * (size_t)p] / MC_CHUNK, e = (panel_ptr[2 * (size_t)p + 1] + MC_CHUNK - 1) / MC_CHUNK; c < e; ++c) chunk_panel[(size_t)c] = p;
         MC_TRY(hipMalloc(&A->d_chunk_panel, sizeof(int32_t) * chunk_panel.size()));
         MC_TRY(hipMemcpyAsync(A->d_chunk_panel, chunk_panel.data(), sizeof(int32_t) * chunk_panel.size(), hipMemcpyHostToDevice, s));
+    }
+    if (!shares.empty()) {
+        MC_TRY(hipMalloc(&A->d_shares, sizeof(int32_t) * shares.size()));
+        MC_TRY(hipMemcpyAsync(A->d_shares, shares.data(), sizeof(int32_t) * shares.size(), hipMemcpyHostToDevice, s));
     }
     if (A->n_items) {
         MC_TRY(hipMalloc(&A->d_items, sizeof(int32_t) * items.size()));
@@ -1100,15 +1154,15 @@ int sddmm_impl(const void *Q_dev, int ldq, const void *Kmat_dev, int ldk, int Kd
 
     SddmmArgs a = {};
     a.float_out = out_mode; a.out_scale = out_mode ? scale : 1.f;
-    a.panel_ptr = mask->d_panel_ptr; a.row_ptr = mask->d_row_ptr; a.slot_idx = mask->d_slot_idx;
+    a.slot_idx = mask->d_slot_idx;
     a.Q = static_cast<const uint8_t *>(Q_dev); a.ldq_bytes = (int64_t)ldq * bits / 8; a.Q_batch_stride = 0;
     a.Kmat = static_cast<const uint8_t *>(Kmat_dev); a.ldk_bytes = (int64_t)ldk * bits / 8; a.K_batch_stride = 0;
     a.row_bytes = Kd * bits / 8;
     a.S = S_dev; a.S_batch_stride = 0;
-    a.P = mask->P; a.V = mask->V; a.batch = 1;
+    a.V = mask->V; a.batch = 1;
     a.lhs_unsigned = (flags & MC_LHS_UNSIGNED) ? 1 : 0; a.rhs_unsigned = (flags & MC_RHS_UNSIGNED) ? 1 : 0;
-    if (mask->n_items && o.spmm_splitting != -1) { a.items = mask->d_items; a.n_units = mask->n_items; } // very unequal panels
-    MC_HIP(launch_sddmm(bits, a, choose_sddmm_waves(mask, 1, a.row_bytes, bits, o), static_cast<hipStream_t>(stream)));
+    take_shares(mask, o.spmm_splitting != -1, &a);
+    MC_HIP(launch_sddmm(bits, a, choose_sddmm_waves(mask, a.n_shares, 1, a.row_bytes, bits, o), static_cast<hipStream_t>(stream)));
     return MC_OK;
 }
 } // namespace
@@ -1160,17 +1214,17 @@ extern "C" int mc_sddmm_to_mat(const void *Q_dev, int ldq, const void *Kmat_dev,
     SddmmArgs a = {};
     a.float_out = 3; a.out_scale = scale;
     a.dev_vals = P->d_vals; a.dev_batch_stride = 0; a.code_bits = P->lhs_bits;
-    a.panel_ptr = P->d_panel_ptr; a.row_ptr = P->d_row_ptr; a.slot_idx = P->d_slot_idx;
+    a.slot_idx = P->d_slot_idx;
     a.Q = static_cast<const uint8_t *>(Q_dev); a.ldq_bytes = (int64_t)ldq * bits / 8; a.Q_batch_stride = 0;
     a.Kmat = static_cast<const uint8_t *>(Kmat_dev); a.ldk_bytes = (int64_t)ldk * bits / 8; a.K_batch_stride = 0;
     a.row_bytes = Kd * bits / 8;
     a.S = nullptr; a.S_batch_stride = 0;
-    a.P = P->P; a.V = P->V; a.batch = 1;
-    if (P->n_items && o.spmm_splitting != -1) { a.items = P->d_items; a.n_units = P->n_items; }
+    a.V = P->V; a.batch = 1;
+    take_shares(P, o.spmm_splitting != -1, &a);
     P->blk_valid = false; // only the panel format receives the new values
     P->merged_valid = false;
     P->dense_valid = false;
-    MC_HIP(launch_sddmm(bits, a, choose_sddmm_waves(P, 1, a.row_bytes, bits, o), static_cast<hipStream_t>(stream)));
+    MC_HIP(launch_sddmm(bits, a, choose_sddmm_waves(P, a.n_shares, 1, a.row_bytes, bits, o), static_cast<hipStream_t>(stream)));
     return MC_OK;
 }
 
@@ -1305,13 +1359,13 @@ int attention_pipeline(const uint8_t *Q, const uint8_t *Km, const uint8_t *Vm, i
         MC_HIP(launch_scores_softmax(c, qkv_bits, p_bits, sw, s));
     } else {
         SddmmArgs d = {};
-        d.panel_ptr = mask->d_panel_ptr; d.row_ptr = mask->d_row_ptr; d.slot_idx = mask->d_slot_idx;
+        d.slot_idx = mask->d_slot_idx;
         d.Q = Q; d.ldq_bytes = token_stride_bytes; d.Q_batch_stride = head_stride_bytes;
         d.Kmat = Km; d.ldk_bytes = token_stride_bytes; d.K_batch_stride = head_stride_bytes;
         d.row_bytes = row_bytes; d.S = scores; d.S_batch_stride = nnz;
-        d.P = mask->P; d.V = 8; d.batch = heads;
-        if (mask->n_items && o.spmm_splitting != -1) { d.items = mask->d_items; d.n_units = mask->n_items; } // very unequal panels
-        MC_HIP(launch_sddmm(qkv_bits, d, choose_sddmm_waves(mask, heads, row_bytes, qkv_bits, o), s));
+        d.V = 8; d.batch = heads;
+        take_shares(mask, o.spmm_splitting != -1, &d);
+        MC_HIP(launch_sddmm(qkv_bits, d, choose_sddmm_waves(mask, d.n_shares, heads, row_bytes, qkv_bits, o), s));
 
         // the softmax writes its codes in the layout the SpMM reads
         SoftmaxArgs f = {};

@@ -23,6 +23,11 @@ struct mc_mat {
     int32_t *d_split_panels;   // n_split: the panels that have several items
     int n_items, n_split;
     int max_item_chunks;       // chunks of the longest item
+    // Shares of the SDDMM, one workgroup each: first slot (a multiple of 64), stored vectors, panel, first stored vector's number.  First
+    // one per panel, then, where panels are cut (n_cut > 0), that many more: the panels in pieces of at most max_cut_chunks
+    // chunks, longest first.
+    int32_t *d_shares;         // (P + n_cut) x 4
+    int n_cut;
     // LDS-ordered copy of the operand for the SpMM that keeps rows of B resident in LDS (see mc_resident_pack; null when
     // not built: pattern-only masks, operands too sparse or small for it)
     int blk_nt;                // 16-byte segments of a row in the LDS image the codes are made for (2 or 4)
@@ -177,8 +182,8 @@ struct DenseFillArgs {
 };
 
 struct SddmmArgs {
-    const int32_t *panel_ptr;
-    const int32_t *row_ptr;
+    const int32_t *shares;     // n_shares x 4 (see mc_mat)
+    int n_shares;
     const int32_t *slot_idx;
     const uint8_t *Q;
     int64_t ldq_bytes, Q_batch_stride;
@@ -193,10 +198,9 @@ struct SddmmArgs {
     uint8_t *dev_vals;         // float_out 3: the operand's value array, its bytes per batch item, its code width (8 / 16)
     int64_t dev_batch_stride;
     int code_bits;
-    int P, V, batch;
+    int V, batch;
     int lhs_unsigned, rhs_unsigned; // 4- and 8-bit operands read as non-negative values
-    const int32_t *items;      // optional work items (see mc_mat): null = one workgroup per panel
-    int n_units;               // items, or P
+    int kmat_rows;
 };
 
 // Scores + softmax of the attention layer in one kernel (attention_scores_kernels.hip): V = 8, one mask for all heads.

@@ -86,6 +86,69 @@ __device__ __forceinline__ void store_scores(const SddmmArgs &a, int64_t out0, i
 }
 
 
+// Two int16 operands: the tile's accumulators hold Qh.Kh (rows 0 .. 7) and Ql.Kh (rows 8 .. 15, 32 lanes further up) in acc, the same with
+// Kl in acc2; S = (QhKh << 16) + ((QhKl + QlKh) << 8) + QlKl.  Each half of the wave adds up the two terms that it has after one
+// exchange of halves (lower lanes those of acc, upper lanes those of acc2), a second exchange brings the halves' sums together and leaves
+// lane (j, g) rows 4 (g & 1) + 2 (g >> 1) and the next of vector j: every lane has a pair of rows to store.
+__device__ __forceinline__ v2i combine16(v4i acc, v4i acc2, int lower_shift)
+{
+    v4i z;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const auto s = __builtin_amdgcn_permlane32_swap((unsigned)acc[r], (unsigned)acc2[r], false, false);
+        z[r] = (int)(((s[0] << 8) + s[1]) << lower_shift);   // lower: QhKh << 16 + QlKh << 8; upper: QhKl << 8 + QlKl
+    }
+    v2i out;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const auto s = __builtin_amdgcn_permlane32_swap((unsigned)z[r], (unsigned)z[r + 2], false, false);
+        out[r] = (int)(s[0] + s[1]);
+    }
+    return out;
+}
+
+// store_scores for the pair of rows that combine16 leaves in a lane
+template <bool DQ>
+__device__ __forceinline__ void store_pair(const SddmmArgs &a, int64_t out0, int s0, int slot, int n, int g, v2i s)
+{
+    const int row = 4 * (g & 1) + 2 * (g >> 1);
+    if (DQ && a.float_out == 3) {
+        if (row >= a.V) return;
+        const int64_t gs = (int64_t)s0 + slot;
+        const int sub = (int)(gs % MC_CHUNK) / 16, b = (int)(gs % 16);
+        const float qmax = (a.code_bits == 16) ? 32639.f : 127.f;
+        uint8_t *chunk = a.dev_vals + (int64_t)blockIdx.y * a.dev_batch_stride + (gs / MC_CHUNK) * (MC_CHUNK * a.V * a.code_bits / 8);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const float x = __builtin_rintf((float)s[r] * a.out_scale);
+            const int code = (slot < n) ? (int)__builtin_fminf(__builtin_fmaxf(x, -qmax), qmax) : 0;
+            if (a.code_bits == 8) {
+                chunk[sub * (16 * a.V) + (row + r) * 16 + b] = (uint8_t)code;
+            } else {
+                const int hi = (code + 128) >> 8, lo = code - hi * 256;
+                chunk[sub * (32 * a.V) + (row + r) * 16 + b] = (uint8_t)hi;
+                chunk[sub * (32 * a.V) + 16 * a.V + (row + r) * 16 + b] = (uint8_t)lo;
+            }
+        }
+        return;
+    }
+    if (slot < n && row < a.V) {
+        const int64_t off = out0 + (int64_t)slot * a.V + row;
+        if (!DQ) {
+            __builtin_nontemporal_store(s, reinterpret_cast<v2i *>(static_cast<int32_t *>(a.S) + off));
+        } else {
+            const float f0 = s.x * a.out_scale, f1 = s.y * a.out_scale;
+            if (a.float_out == 1) {
+                float *o = static_cast<float *>(a.S) + off;
+                o[0] = f0; o[1] = f1;
+            } else {
+                const v4h h = to_half4((v4f){f0, f1, 0.f, 0.f});
+                *reinterpret_cast<v2h *>(static_cast<_Float16 *>(a.S) + off) = (v2h){h.x, h.y};
+            }
+        }
+    }
+}
+
 // LPR: 16-byte pieces (lanes) of a staged Kmat row: 4, 8, 16, 32 or 64; a row has at most that many and is always
 // fetched whole.  Pieces beyond its end are fetched from its start instead (a line that is on its way anyway), and the Q
 // operand is zero there, so they add nothing.
@@ -100,9 +163,13 @@ __device__ __forceinline__ void store_scores(const SddmmArgs &a, int64_t out0, i
 // are then taken into registers, which frees the stage for the next unit's rows while the MFMAs and stores of this one
 // run (a second stage would halve the waves of a compute unit, staging through registers costs LDS writes: 2 - 8 % slower).
 // L8-R8, 4096 x 4096, V = 8, 90 % sparse, Kd = 256: 6.2 -> 5.9 us; 1224 x 7932, V = 4, 80 %, Kd = 464 58.7 -> 21.7 us, L16-R16,
-// 2000 x 3100, V = 4, 90 %, Kd = 200 13.6 -> 9.6 us (row lengths that the direct kernel used to take: there the lanes that read
+// 2000 x 3100, V = 4, 90 %, Kd = 200 13.6 -> 8.6 us (row lengths that the direct kernel used to take: there the lanes that read
 // one row are 16 apart and their requests are not combined, 9 TB/s of rows from L2 against 25 coalesced).
-template <int PB, int LPR, bool DQ, bool U>
+// With int16 operands it is the instructions, too (the same rows as int8: 6.9 us where int16 took 8.9, equal panels): Kmat's bytes
+// are taken apart without a carry, halves of the wave combine a tile's four sums by two exchanges in registers, and offsets are 32
+// bits wide where they can be: 8.9 -> 7.9; with rows above 512 bytes (5760 x 2546, V = 8, 71 %, Kd = 280) 43.6 -> 32.7.
+// SHORT: Kmat spans less than 4 GiB, its rows and their length fit 24 bits.
+template <int PB, int LPR, bool DQ, bool U, bool SHORT>
 __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
 {
     constexpr int RB = LPR * 16, NI = (LPR == 4) ? 4 : (LPR == 64 ? 16 : 8), RPI = 64 / LPR, UNIT = NI * RPI, TILES = UNIT / 16;
@@ -116,29 +183,22 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
     const int batch = blockIdx.y;
-    // a share of the mask: a whole panel, or (masks with very unequal panels) a range of its chunks
-    int panel = blockIdx.x, cb = 0, ce = INT32_MAX / MC_CHUNK;
-    if (a.items) {
-        const v4i it = *reinterpret_cast<const v4i *>(a.items + 4 * blockIdx.x);
-        panel = it.x; cb = it.y; ce = it.z;
-    }
-    const v2i pp = *reinterpret_cast<const v2i *>(a.panel_ptr + 2 * panel);
-    const int s0 = pp.x, n = pp.y - s0;
-    // slots of the share (codes written into an operand's device format also cover the padded ones, with zeros)
+    const v4i share = *reinterpret_cast<const v4i *>(a.shares + 4 * blockIdx.x);
+    const int s0 = share.x, n = share.y, panel = share.z;
+    // (codes written into an operand's device format also cover the padded slots, with zeros)
     const int n_all = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK : n;
-    const int first = cb * MC_CHUNK, end = min(n_all, ce * MC_CHUNK);
-    const int nunits = (end - first + UNIT - 1) / UNIT;
+    const int nunits = (n_all + UNIT - 1) / UNIT;
     const int nmy = (nunits > w) ? (nunits - w + nw - 1) / nw : 0;
     if (nmy == 0) return;
     // piece i of a unit: lane (rg, seg) fetches piece seg of the row in slot rg*NI + i
-    const int32_t *idx = a.slot_idx + s0 + first + rg * NI;
+    const int32_t *idx = a.slot_idx + s0 + rg * NI;
     v4i ixn[NI / 4];
     auto load_idx = [&](int u) {
 #pragma unroll
         for (int t = 0; t < NI / 4; ++t) ixn[t] = *reinterpret_cast<const v4i *>(idx + u * UNIT + 4 * t);
     };
     load_idx(w);
-    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)a.row_ptr[panel] * a.V;
+    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)share.w * a.V;
     const uint8_t *Km = a.Kmat + (int64_t)batch * a.K_batch_stride;
 
     v4i qf[KC * QR];
@@ -166,19 +226,27 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
     auto request = [&]() {
         unsigned to = stage_u;
         if (U && LPR == 64) asm("" : "+s"(to)); // (sixteen places kept in scalar registers would be spilled)
+        if constexpr (SHORT) { // one multiply-add per piece, and eight registers less
 #pragma unroll
-        for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km + ((int64_t)ixn[i >> 2][i & 3] * a.ldk_bytes + off[i]), to + i * 1024);
+            for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km, __umul24(ixn[i >> 2][i & 3], (unsigned)a.ldk_bytes) + off[i], to + i * 1024);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km + ((int64_t)ixn[i >> 2][i & 3] * a.ldk_bytes + off[i]), to + i * 1024);
+        }
     };
     request();
     if (nmy > 1) load_idx(w + nw);
 
-    v4i rq = {0, 0, 0, 0}; // U: rows 4g .. 4g+3: sum over the reduction of the Q operand bytes
+    // sum over the reduction of the Q operand bytes, of rows 4g .. 4g+3 (U, and int16)
+    v4i rq = {0, 0, 0, 0};
+    const int lower_shift = lane < 32 ? 8 : 0;
     int ones8 = (j == 8) ? 0x01010101 : 0, of_panel = (j < a.V) ? -1 : 0;
     asm("" : "+v"(ones8), "+v"(of_panel));
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
         if (!U) {
             qf[kc] = raw_q[kc];
+            if (PB == 16) rq = __builtin_amdgcn_mfma_i32_16x16x64_i8(raw_q[kc], ones, rq, 0, 0, 0);
         } else {
             // rows of the panel: the operand bytes; MFMA row 8: all ones (it collects the sums of the Kmat
             // operand bytes of every output column); other rows, and everything beyond the row end: zero
@@ -232,13 +300,14 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
         }
 #pragma unroll
         for (int tl = 0; tl < TILES; ++tl) {
-            v4i acc = {0, 0, 0, 0}, acc2 = {0, 0, 0, 0};
+            // (int16: the low bytes of Kmat enter as u - 128, and 128 times the sum of Q goes in here)
+            v4i acc = {0, 0, 0, 0}, acc2 = (PB == 16) ? rq << 7 : (v4i){0, 0, 0, 0};
 #pragma unroll
             for (int kc = 0; kc < KC; ++kc) {
                 if (PB == 16) {
                     v4i kh, kl;
-                    if (EARLY) split16(kt[tl][2 * kc], kt[tl][2 * kc + 1], kh, kl);
-                    else split16(read_op(tl, 2 * kc), read_op(tl, 2 * kc + 1), kh, kl);
+                    if (EARLY) bytes16(kt[tl][2 * kc], kt[tl][2 * kc + 1], kh, kl);
+                    else bytes16(read_op(tl, 2 * kc), read_op(tl, 2 * kc + 1), kh, kl);
                     mma_step<PB>(qf[kc], kh, kl, acc, acc2);
                 } else {
                     const v4i kf = EARLY ? kt[tl][kc] : read_op(tl, kc);
@@ -253,8 +322,10 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
                 }
             }
             if (!EARLY) next_unit();                // (a unit of these is one tile)
-            const int slot = first + u * UNIT + tl * 16 + j;
-            if (!U) {
+            const int slot = u * UNIT + tl * 16 + j;
+            if (PB == 16) {
+                store_pair<DQ>(a, out0, s0, slot, n, g, combine16(acc, acc2, lower_shift));
+            } else if (!U) {
                 store_scores<DQ>(a, out0, s0, slot, n, g, finish_tile<PB>(acc, acc2));
             } else {
                 // sum (q'+cq)(k'+ck) = sum q'k' + ck sum q' + cq sum k' + cq ck n, with cq = ck = 128 in the
@@ -285,16 +356,11 @@ __global__ __launch_bounds__(64 * WK) void sddmm_nib32_kernel(SddmmArgs a)
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane >> 1, seg = lane & 1;
     const int batch = blockIdx.y;
-    int panel = blockIdx.x, cb = 0, ce = -1;
-    if (a.items) {
-        const v4i it = *reinterpret_cast<const v4i *>(a.items + 4 * blockIdx.x);
-        panel = it.x; cb = it.y; ce = it.z;
-    }
-    const int s0 = a.panel_ptr[2 * panel], n = a.panel_ptr[2 * panel + 1] - s0;
-    if (ce < 0) ce = (n + MC_CHUNK - 1) / MC_CHUNK;
-    const int nch = ce - cb;
-    const int32_t *idx = a.slot_idx + s0 + cb * MC_CHUNK;
-    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)a.row_ptr[panel] * a.V;
+    const v4i share = *reinterpret_cast<const v4i *>(a.shares + 4 * blockIdx.x);
+    const int s0 = share.x, n = share.y, panel = share.z;
+    const int nch = (n + MC_CHUNK - 1) / MC_CHUNK;
+    const int32_t *idx = a.slot_idx + s0;
+    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)share.w * a.V;
     const uint8_t *Km = a.Kmat + (int64_t)batch * a.K_batch_stride;
     char *stage = lds + w * (64 * RB);
 
@@ -345,7 +411,7 @@ __global__ __launch_bounds__(64 * WK) void sddmm_nib32_kernel(SddmmArgs a)
             }
             acc = acc >> 8; // both operands carried a factor 16
             if (U) acc += (v4i){cqck, cqck, cqck, cqck};
-            store_scores<DQ>(a, out0, s0, (cb + c) * MC_CHUNK + s, n, g, acc);
+            store_scores<DQ>(a, out0, s0, c * MC_CHUNK + s, n, g, acc);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // reads done before the rows are overwritten
     }
@@ -359,16 +425,11 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_direct_kernel(SddmmArg
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, g = lane >> 4;
     const int batch = blockIdx.y;
-    int panel = blockIdx.x, cb = 0, ce = -1; // unit of work: a panel or a range of its chunks
-    if (a.items) {
-        const v4i it = *reinterpret_cast<const v4i *>(a.items + 4 * blockIdx.x);
-        panel = it.x; cb = it.y; ce = it.z;
-    }
-    const int s0 = a.panel_ptr[2 * panel], n = a.panel_ptr[2 * panel + 1] - s0;
+    const v4i share = *reinterpret_cast<const v4i *>(a.shares + 4 * blockIdx.x);
+    const int s0 = share.x, n = share.y, panel = share.z;
     // (codes written into an operand's device format also cover the padded slots of the last chunk, with zeros)
-    const int tiles_all = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * 4 : (n + 15) / 16;
-    const int tile0 = 4 * cb, ntile = (ce < 0) ? tiles_all : min(tiles_all, 4 * ce);
-    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)a.row_ptr[panel] * a.V;
+    const int ntile = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * 4 : (n + 15) / 16;
+    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)share.w * a.V;
     const uint8_t *Qpanel = a.Q + (int64_t)batch * a.Q_batch_stride + (int64_t)panel * a.V * a.ldq_bytes;
     const uint8_t *Km = a.Kmat + (int64_t)batch * a.K_batch_stride + g * LANEB;
     const int kc_n = (a.row_bytes + STEP - 1) / STEP;
@@ -395,7 +456,7 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_direct_kernel(SddmmArg
         for (int kc = 0; kc < KC; ++kc) qf[kc] = load_q<PB>(Qpanel, a.ldq_bytes, a.V, a.row_bytes, kc, j, g);
     }
 
-    for (int t = tile0 + w; t < ntile; t += SDDMM_WAVES) {
+    for (int t = w; t < ntile; t += SDDMM_WAVES) {
         const int slot = t * 16 + j;
         const int row = a.slot_idx[s0 + slot]; // padded slots name a valid row
         const uint8_t *kr = Km + (int64_t)row * a.ldk_bytes;
@@ -432,16 +493,11 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_unsigned_kernel(SddmmA
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, g = lane >> 4;
     const int batch = blockIdx.y;
-    int panel = blockIdx.x, cb = 0, ce = -1; // unit of work: a panel or a range of its chunks
-    if (a.items) {
-        const v4i it = *reinterpret_cast<const v4i *>(a.items + 4 * blockIdx.x);
-        panel = it.x; cb = it.y; ce = it.z;
-    }
-    const int s0 = a.panel_ptr[2 * panel], n = a.panel_ptr[2 * panel + 1] - s0;
+    const v4i share = *reinterpret_cast<const v4i *>(a.shares + 4 * blockIdx.x);
+    const int s0 = share.x, n = share.y, panel = share.z;
     // (codes written into an operand's device format also cover the padded slots of the last chunk, with zeros)
-    const int tiles_all = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * 4 : (n + 15) / 16;
-    const int tile0 = 4 * cb, ntile = (ce < 0) ? tiles_all : min(tiles_all, 4 * ce);
-    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)a.row_ptr[panel] * a.V;
+    const int ntile = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * 4 : (n + 15) / 16;
+    const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)share.w * a.V;
     const uint8_t *Qrow = a.Q + (int64_t)batch * a.Q_batch_stride + (int64_t)(panel * a.V + (j < a.V ? j : 0)) * a.ldq_bytes + g * 16;
     const uint8_t *Km = a.Kmat + (int64_t)batch * a.K_batch_stride + g * 16;
     const int kc_n = (a.row_bytes + 63) / 64;
@@ -476,7 +532,7 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_unsigned_kernel(SddmmA
     const int nred = kc_n * (PB == 4 ? 128 : 64);                       // reduction elements, padding included
     const int cqck = (a.lhs_unsigned && a.rhs_unsigned) ? (PB == 4 ? 64 : 16384) * nred : 0;
 
-    for (int t = tile0 + w; t < ntile; t += SDDMM_WAVES) {
+    for (int t = w; t < ntile; t += SDDMM_WAVES) {
         const int slot = t * 16 + j;
         const int row = a.slot_idx[s0 + slot]; // padded slots name a valid row
         const uint8_t *kr = Km + (int64_t)row * a.ldk_bytes;
@@ -501,10 +557,16 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_unsigned_kernel(SddmmA
 
 template <int PB, int LPR, bool DQ, bool U> hipError_t launch_staged(const SddmmArgs &a, int waves, hipStream_t s)
 {
-    dim3 grid((unsigned)(a.items ? a.n_units : a.P), (unsigned)a.batch);
+    dim3 grid((unsigned)a.n_shares, (unsigned)a.batch);
     constexpr int STAGE = (LPR == 4) ? 4096 : (LPR == 64 ? 16384 : 8192);
     if (LPR == 64 && waves > 4) waves = 4;      // 64 KB of stages per workgroup
-    hipLaunchKernelGGL((sddmm_staged_kernel<PB, LPR, DQ, U>), grid, dim3(64 * waves), waves * STAGE, s, a);
+    if constexpr (!U) {
+        if (a.kmat_rows <= (1 << 24) && a.ldk_bytes < (1 << 24) && (a.kmat_rows - 1) * a.ldk_bytes + a.row_bytes < ((int64_t)1 << 32)) {
+            hipLaunchKernelGGL((sddmm_staged_kernel<PB, LPR, DQ, U, true>), grid, dim3(64 * waves), waves * STAGE, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((sddmm_staged_kernel<PB, LPR, DQ, U, false>), grid, dim3(64 * waves), waves * STAGE, s, a);
     return hipGetLastError();
 }
 
@@ -513,7 +575,7 @@ template <int PB, bool DQ, bool U> hipError_t launch_sddmm_bits(const SddmmArgs 
     if (waves > 0) {
         if constexpr (PB == 4) {
             if (a.row_bytes == 32) { // 64 nibbles: one MFMA step
-                dim3 grid((unsigned)(a.items ? a.n_units : a.P), (unsigned)a.batch);
+                dim3 grid((unsigned)a.n_shares, (unsigned)a.batch);
                 switch (waves) {
                 case 1: hipLaunchKernelGGL((sddmm_nib32_kernel<1, DQ, U>), grid, dim3(64), 0, s, a); break;
                 case 2: hipLaunchKernelGGL((sddmm_nib32_kernel<2, DQ, U>), grid, dim3(128), 0, s, a); break;
@@ -530,7 +592,7 @@ template <int PB, bool DQ, bool U> hipError_t launch_sddmm_bits(const SddmmArgs 
         if (a.row_bytes <= 512) return launch_staged<PB, 32, DQ, U>(a, waves, s);
         if (a.row_bytes <= 1024) return launch_staged<PB, 64, DQ, U>(a, waves, s);
     }
-    dim3 grid((unsigned)(a.items ? a.n_units : a.P), (unsigned)a.batch), block(64 * SDDMM_WAVES);
+    dim3 grid((unsigned)a.n_shares, (unsigned)a.batch), block(64 * SDDMM_WAVES);
     if constexpr (U) {
         hipLaunchKernelGGL((sddmm_unsigned_kernel<PB, DQ>), grid, block, 0, s, a); // any row length, operands straight from memory
     } else {
@@ -557,6 +619,6 @@ template <bool DQ> hipError_t launch_sddmm_out(int bits, const SddmmArgs &a, int
 
 hipError_t launch_sddmm(int bits, const SddmmArgs &a, int waves, hipStream_t s)
 {
-    if (a.P == 0 || a.batch == 0) return hipSuccess;
+    if (a.n_shares == 0 || a.batch == 0) return hipSuccess;
     return a.float_out ? launch_sddmm_out<true>(bits, a, waves, s) : launch_sddmm_out<false>(bits, a, waves, s);
 }

@@ -44,6 +44,18 @@ __device__ __forceinline__ void split16(v4i x, v4i y, v4i &hi, v4i &lo)
                (int)__builtin_amdgcn_perm(yr.y, yr.x, ODD), (int)__builtin_amdgcn_perm(yr.w, yr.z, ODD)};
 }
 
+// The same elements as their bytes: e = 256 * hi + lo + 128 with hi the high byte, lo the low byte less 128 (any e; no carry, a
+// quarter of the instructions less, for a side whose counterpart's sums are known).
+__device__ __forceinline__ void bytes16(v4i x, v4i y, v4i &hi, v4i &lo)
+{
+    constexpr unsigned EVEN = 0x06040200u, ODD = 0x07050301u;
+    const v4i flip = {(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
+    lo = (v4i){(int)__builtin_amdgcn_perm(x.y, x.x, EVEN), (int)__builtin_amdgcn_perm(x.w, x.z, EVEN),
+               (int)__builtin_amdgcn_perm(y.y, y.x, EVEN), (int)__builtin_amdgcn_perm(y.w, y.z, EVEN)} ^ flip;
+    hi = (v4i){(int)__builtin_amdgcn_perm(x.y, x.x, ODD), (int)__builtin_amdgcn_perm(x.w, x.z, ODD),
+               (int)__builtin_amdgcn_perm(y.y, y.x, ODD), (int)__builtin_amdgcn_perm(y.w, y.z, ODD)};
+}
+
 // One reduction step of a 16-vector tile.  PB = operand width in bits.
 //   8:  q, k are the operands.
 //   4:  q, k hold packed nibbles; both are widened (16 x value) and multiplied pairwise.
