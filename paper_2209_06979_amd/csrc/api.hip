@@ -100,12 +100,10 @@ bool on_device_of(const mc_mat *A)
 
 void free_device(mc_mat *A)
 {
-    if (A->d_panel_ptr) (void)hipFree(A->d_panel_ptr);
-    if (A->d_row_ptr) (void)hipFree(A->d_row_ptr);
+    if (A->d_panel_ptr) (void)hipFree(A->d_panel_ptr); // (d_row_ptr and d_shares lie behind it)
     if (A->d_slot_idx) (void)hipFree(A->d_slot_idx);
     if (A->d_vals) (void)hipFree(A->d_vals);
     if (A->d_items) (void)hipFree(A->d_items);
-    if (A->d_shares) (void)hipFree(A->d_shares);
     if (A->d_split_panels) (void)hipFree(A->d_split_panels);
     if (A->d_blk_ptr) (void)hipFree(A->d_blk_ptr);
     if (A->d_blk_recs) (void)hipFree(A->d_blk_recs);
@@ -473,7 +471,7 @@ bool dense_worth_building(const mc_mat *A)
                 plan_slab(X, row_bytes, r4, 4, automatic, &pl);
                 best = std::min(best, pl.us);
             }
-            if (plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, 4).us < 0.98 * best) return true;
+            if (plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, 4).us < 0.95 * best) return true;
         }
     }
     return false;
@@ -744,12 +742,22 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     bool ok = true;
     MC_TRY(hipGetDevice(&A->device));
     // the index array gets one spare chunk so that 16-byte index reads never leave it
-    MC_TRY(hipMalloc(&A->d_panel_ptr, sizeof(int32_t) * 2 * (size_t)(lay.P + 1)));
-    MC_TRY(hipMalloc(&A->d_row_ptr, sizeof(int32_t) * (size_t)(lay.P + 1)));
+    // panel pointers, shares and row pointers in one allocation and one copy
+    const size_t at_shares = (2 * (size_t)(lay.P + 1) + 3) / 4 * 4, at_rows = at_shares + shares.size();
+    try {
+        panel_ptr.resize(at_rows + (size_t)lay.P + 1);
+    } catch (const std::bad_alloc &) {
+        free_device(A);
+        delete A;
+        return MC_ENOMEM;
+    }
+    std::copy(shares.begin(), shares.end(), panel_ptr.begin() + at_shares);
+    std::copy(row_ptr, row_ptr + lay.P + 1, panel_ptr.begin() + at_rows);
+    MC_TRY(hipMalloc(&A->d_panel_ptr, sizeof(int32_t) * panel_ptr.size()));
+    A->d_shares = A->d_panel_ptr + at_shares; A->d_row_ptr = A->d_panel_ptr + at_rows;
     MC_TRY(hipMalloc(&A->d_slot_idx, sizeof(int32_t) * (size_t)(lay.nslots + MC_CHUNK)));
     if (lay.vals_bytes) MC_TRY(hipMalloc(&A->d_vals, (size_t)lay.vals_bytes));
-    MC_TRY(hipMemcpyAsync(A->d_panel_ptr, panel_ptr.data(), sizeof(int32_t) * 2 * (size_t)lay.P, hipMemcpyHostToDevice, s));
-    MC_TRY(hipMemcpyAsync(A->d_row_ptr, row_ptr, sizeof(int32_t) * (size_t)(lay.P + 1), hipMemcpyHostToDevice, s));
+    MC_TRY(hipMemcpyAsync(A->d_panel_ptr, panel_ptr.data(), sizeof(int32_t) * panel_ptr.size(), hipMemcpyHostToDevice, s));
     if (lay.nslots)
         MC_TRY(hipMemcpyAsync(A->d_slot_idx, slot_idx.data(), sizeof(int32_t) * (size_t)lay.nslots, hipMemcpyHostToDevice, s));
     if (lay.vals_bytes)
@@ -767,10 +775,6 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             for (int c = panel_ptr[2 * (size_t)p] / MC_CHUNK, e = (panel_ptr[2 * (size_t)p + 1] + MC_CHUNK - 1) / MC_CHUNK; c < e; ++c) chunk_panel[(size_t)c] = p;
         MC_TRY(hipMalloc(&A->d_chunk_panel, sizeof(int32_t) * chunk_panel.size()));
         MC_TRY(hipMemcpyAsync(A->d_chunk_panel, chunk_panel.data(), sizeof(int32_t) * chunk_panel.size(), hipMemcpyHostToDevice, s));
-    }
-    if (!shares.empty()) {
-        MC_TRY(hipMalloc(&A->d_shares, sizeof(int32_t) * shares.size()));
-        MC_TRY(hipMemcpyAsync(A->d_shares, shares.data(), sizeof(int32_t) * shares.size(), hipMemcpyHostToDevice, s));
     }
     if (A->n_items) {
         MC_TRY(hipMalloc(&A->d_items, sizeof(int32_t) * items.size()));

@@ -571,9 +571,8 @@ template <int HPW, int PB, int QB, int KS, int DK, bool PAD> hipError_t launch_p
     const int row = HPW * (PAD ? a.real_pieces * 16 : DK * QB / 8), lines = (row + 127) / 128 * 128; // (the L2 holds lines of 128 bytes)
     a.pair_shift = pairs_at_a_time(pairs, 2.0 * a.tokens * (a.in_token_stride < lines ? (double)a.in_token_stride : lines), (double)a.index_bytes);
     const unsigned rows = pairs >> a.pair_shift, y = rows < 32768 ? rows : 32768;
-    hipLaunchKernelGGL((attention_fused_kernel<8, HPW, PB, QB, KS, DK, PAD>), dim3((unsigned)a.P << a.pair_shift, y, (rows + y - 1) / y),
+    return launch_kernel((attention_fused_kernel<8, HPW, PB, QB, KS, DK, PAD>), dim3((unsigned)a.P << a.pair_shift, y, (rows + y - 1) / y),
                        dim3(64 * HPW * KS), 0, s, a);
-    return hipGetLastError();
 }
 
 } // namespace

@@ -175,8 +175,7 @@ template <int PB, int RB, int WK, bool C16> hipError_t launch_one(const ScoresAr
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.P, (unsigned)a.heads), dim3(64 * WK), lds, s, a);
-    return hipGetLastError();
+    return launch_kernel(kern, dim3((unsigned)a.P, (unsigned)a.heads), dim3(64 * WK), lds, s, a);
 }
 
 template <int PB, int RB, bool C16> hipError_t launch_wk(const ScoresArgs &a, int waves, hipStream_t s)

@@ -70,12 +70,11 @@ template <int BNB> hipError_t launch_bnb(const SpmmArgs &a, int waves, int32_t *
     constexpr int MAXW = (64 * BNB * 8 <= 65536) ? 8 : 4;
     if (waves > MAXW) waves = MAXW;
     switch (waves) {
-    case 1: hipLaunchKernelGGL((gather_probe_kernel<BNB, 1>), grid, dim3(64), 0, s, a, sink); break;
-    case 2: hipLaunchKernelGGL((gather_probe_kernel<BNB, 2>), grid, dim3(128), 0, s, a, sink); break;
-    case 4: hipLaunchKernelGGL((gather_probe_kernel<BNB, 4>), grid, dim3(256), 0, s, a, sink); break;
-    default: hipLaunchKernelGGL((gather_probe_kernel<BNB, MAXW>), grid, dim3(64 * MAXW), 0, s, a, sink); break;
+    case 1: return launch_kernel((gather_probe_kernel<BNB, 1>), grid, dim3(64), 0, s, a, sink);
+    case 2: return launch_kernel((gather_probe_kernel<BNB, 2>), grid, dim3(128), 0, s, a, sink);
+    case 4: return launch_kernel((gather_probe_kernel<BNB, 4>), grid, dim3(256), 0, s, a, sink);
+    default: return launch_kernel((gather_probe_kernel<BNB, MAXW>), grid, dim3(64 * MAXW), 0, s, a, sink);
     }
-    return hipGetLastError();
 }
 
 // The matrix unit alone: every wave issues `iters` rounds of eight independent v_mfma_i32_16x16x64_i8 on
@@ -107,8 +106,7 @@ __global__ __launch_bounds__(256) void mfma_probe_kernel(int iters, int32_t *sin
 
 hipError_t launch_mfma_probe(int workgroups, int iters, int32_t *sink, hipStream_t s)
 {
-    hipLaunchKernelGGL(mfma_probe_kernel, dim3((unsigned)workgroups), dim3(256), 0, s, iters, sink);
-    return hipGetLastError();
+    return launch_kernel(mfma_probe_kernel, dim3((unsigned)workgroups), dim3(256), 0, s, iters, sink);
 }
 
 hipError_t launch_gather_probe(const SpmmArgs &a, int bnb, int waves, int32_t *sink, hipStream_t s)

@@ -230,13 +230,14 @@ hipError_t launch_absmax(const float *x, int64_t n, float *result, hipStream_t s
     // one alone reads 128 KB sooner than two have met
     const int64_t groups = (n + 16383) / 16384;
     if (groups <= 2) { // (also an empty tensor)
-        hipLaunchKernelGGL((absmax_kernel<true>), dim3(1), dim3(1024), 0, s, x, n, result, 0ull);
-        return hipGetLastError();
+        return launch_kernel((absmax_kernel<true>), dim3(1), dim3(1024), 0, s, x, n, result, 0ull);
     }
     const unsigned long long number = absmax_number(s);
-    if (number == 0) hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, s, result);
-    hipLaunchKernelGGL((absmax_kernel<false>), dim3((unsigned)(groups < ABSMAX_GROUPS ? groups : ABSMAX_GROUPS)), dim3(1024), 0, s, x, n, result, number);
-    return hipGetLastError();
+    if (number == 0) {
+        const hipError_t e = launch_kernel(absmax_init_kernel, dim3(1), dim3(1), 0, s, result);
+        if (e != hipSuccess) return e;
+    }
+    return launch_kernel((absmax_kernel<false>), dim3((unsigned)(groups < ABSMAX_GROUPS ? groups : ABSMAX_GROUPS)), dim3(1024), 0, s, x, n, result, number);
 }
 
 hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uint8_t *q, hipStream_t s)
@@ -246,9 +247,8 @@ hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uin
     const int64_t loads = n / 4 / 256;
     const dim3 grid(grid_for(n / 4, loads <= 2048 ? 2048 : loads / 8 < 2048 ? 2048 : loads / 8 < 16384 ? loads / 8 : 16384)), block(256);
     const bool stream = n * bits / 8 > QUANTIZE_CACHED;
-    if (bits == 8 && stream) hipLaunchKernelGGL((quantize_kernel<8, true>), grid, block, 0, s, x, n, scale, q);
-    else if (bits == 8) hipLaunchKernelGGL((quantize_kernel<8, false>), grid, block, 0, s, x, n, scale, q);
-    else if (stream) hipLaunchKernelGGL((quantize_kernel<4, true>), grid, block, 0, s, x, n, scale, q);
-    else hipLaunchKernelGGL((quantize_kernel<4, false>), grid, block, 0, s, x, n, scale, q);
-    return hipGetLastError();
+    if (bits == 8 && stream) return launch_kernel((quantize_kernel<8, true>), grid, block, 0, s, x, n, scale, q);
+    if (bits == 8) return launch_kernel((quantize_kernel<8, false>), grid, block, 0, s, x, n, scale, q);
+    if (stream) return launch_kernel((quantize_kernel<4, true>), grid, block, 0, s, x, n, scale, q);
+    return launch_kernel((quantize_kernel<4, false>), grid, block, 0, s, x, n, scale, q);
 }

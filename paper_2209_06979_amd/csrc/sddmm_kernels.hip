@@ -562,12 +562,10 @@ template <int PB, int LPR, bool DQ, bool U> hipError_t launch_staged(const Sddmm
     if (LPR == 64 && waves > 4) waves = 4;      // 64 KB of stages per workgroup
     if constexpr (!U) {
         if (a.kmat_rows <= (1 << 24) && a.ldk_bytes < (1 << 24) && (a.kmat_rows - 1) * a.ldk_bytes + a.row_bytes < ((int64_t)1 << 32)) {
-            hipLaunchKernelGGL((sddmm_staged_kernel<PB, LPR, DQ, U, true>), grid, dim3(64 * waves), waves * STAGE, s, a);
-            return hipGetLastError();
+            return launch_kernel((sddmm_staged_kernel<PB, LPR, DQ, U, true>), grid, dim3(64 * waves), waves * STAGE, s, a);
         }
     }
-    hipLaunchKernelGGL((sddmm_staged_kernel<PB, LPR, DQ, U, false>), grid, dim3(64 * waves), waves * STAGE, s, a);
-    return hipGetLastError();
+    return launch_kernel((sddmm_staged_kernel<PB, LPR, DQ, U, false>), grid, dim3(64 * waves), waves * STAGE, s, a);
 }
 
 template <int PB, bool DQ, bool U> hipError_t launch_sddmm_bits(const SddmmArgs &a, int waves, hipStream_t s)
@@ -577,12 +575,11 @@ template <int PB, bool DQ, bool U> hipError_t launch_sddmm_bits(const SddmmArgs 
             if (a.row_bytes == 32) { // 64 nibbles: one MFMA step
                 dim3 grid((unsigned)a.n_shares, (unsigned)a.batch);
                 switch (waves) {
-                case 1: hipLaunchKernelGGL((sddmm_nib32_kernel<1, DQ, U>), grid, dim3(64), 0, s, a); break;
-                case 2: hipLaunchKernelGGL((sddmm_nib32_kernel<2, DQ, U>), grid, dim3(128), 0, s, a); break;
-                case 4: hipLaunchKernelGGL((sddmm_nib32_kernel<4, DQ, U>), grid, dim3(256), 0, s, a); break;
-                default: hipLaunchKernelGGL((sddmm_nib32_kernel<8, DQ, U>), grid, dim3(512), 0, s, a); break;
+                case 1: return launch_kernel((sddmm_nib32_kernel<1, DQ, U>), grid, dim3(64), 0, s, a);
+                case 2: return launch_kernel((sddmm_nib32_kernel<2, DQ, U>), grid, dim3(128), 0, s, a);
+                case 4: return launch_kernel((sddmm_nib32_kernel<4, DQ, U>), grid, dim3(256), 0, s, a);
+                default: return launch_kernel((sddmm_nib32_kernel<8, DQ, U>), grid, dim3(512), 0, s, a);
                 }
-                return hipGetLastError();
             }
         }
         // the narrowest stage that holds the row
@@ -594,15 +591,14 @@ template <int PB, bool DQ, bool U> hipError_t launch_sddmm_bits(const SddmmArgs 
     }
     dim3 grid((unsigned)a.n_shares, (unsigned)a.batch), block(64 * SDDMM_WAVES);
     if constexpr (U) {
-        hipLaunchKernelGGL((sddmm_unsigned_kernel<PB, DQ>), grid, block, 0, s, a); // any row length, operands straight from memory
+        return launch_kernel((sddmm_unsigned_kernel<PB, DQ>), grid, block, 0, s, a); // any row length, operands straight from memory
     } else {
         const int kc = (a.row_bytes + StepBytes<PB>::value - 1) / StepBytes<PB>::value;
-        if (kc == 1) hipLaunchKernelGGL((sddmm_direct_kernel<PB, 1, DQ>), grid, block, 0, s, a);
-        else if (kc == 2) hipLaunchKernelGGL((sddmm_direct_kernel<PB, 2, DQ>), grid, block, 0, s, a);
-        else if (kc <= 4) hipLaunchKernelGGL((sddmm_direct_kernel<PB, 4, DQ>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((sddmm_direct_kernel<PB, 0, DQ>), grid, block, 0, s, a);
+        if (kc == 1) return launch_kernel((sddmm_direct_kernel<PB, 1, DQ>), grid, block, 0, s, a);
+        if (kc == 2) return launch_kernel((sddmm_direct_kernel<PB, 2, DQ>), grid, block, 0, s, a);
+        if (kc <= 4) return launch_kernel((sddmm_direct_kernel<PB, 4, DQ>), grid, block, 0, s, a);
+        return launch_kernel((sddmm_direct_kernel<PB, 0, DQ>), grid, block, 0, s, a);
     }
-    return hipGetLastError();
 }
 
 template <bool DQ> hipError_t launch_sddmm_out(int bits, const SddmmArgs &a, int waves, hipStream_t s)

@@ -358,14 +358,13 @@ template <bool C16, bool DEV> hipError_t launch_softmax_mode(const SoftmaxArgs &
     if (a.variant == 0 && longest <= 16 * 256) {
         // few panels: two waves per panel halve the time of the launch (5.9 -> 5.2 us for 512 panels of 3280
         // scores); many: one wave per panel (15.0 against 17.4 us for 4096 of them)
-        if (units <= 1024) hipLaunchKernelGGL((softmax_group_kernel<8, 2, C16, DEV>), grid, dim3(128), 0, s, a);
-        else hipLaunchKernelGGL((softmax_wave_kernel<16, C16, DEV>), grid4, dim3(256), 0, s, a);
+        if (units <= 1024) return launch_kernel((softmax_group_kernel<8, 2, C16, DEV>), grid, dim3(128), 0, s, a);
+        return launch_kernel((softmax_wave_kernel<16, C16, DEV>), grid4, dim3(256), 0, s, a);
     } else if (a.variant != 2 && longest <= 16 * 1024) {
-        hipLaunchKernelGGL((softmax_group_kernel<16, 4, C16, DEV>), grid, dim3(256), 0, s, a);
+        return launch_kernel((softmax_group_kernel<16, 4, C16, DEV>), grid, dim3(256), 0, s, a);
     } else {
-        hipLaunchKernelGGL(softmax_general_kernel, grid, dim3(256), 0, s, a);
+        return launch_kernel(softmax_general_kernel, grid, dim3(256), 0, s, a);
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s)

@@ -243,8 +243,7 @@ template <int TILE, int PL, bool R4, int NT, int RF, int WR, int W> hipError_t l
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)((a.tm * a.tn + 7) / 8 * 8)), dim3(64 * W), LDS, s, a);
-    return hipGetLastError();
+    return launch_kernel(kern, dim3((unsigned)((a.tm * a.tn + 7) / 8 * 8)), dim3(64 * W), LDS, s, a);
 }
 
 template <int PL, bool R4> hipError_t launch_tile(const DenseArgs &a, int tile, hipStream_t s)
@@ -322,6 +321,5 @@ hipError_t launch_dense_fill(const DenseFillArgs &a, hipStream_t s)
 {
     const int blocks = (a.P * a.V + 15) / 16;
     if (blocks == 0 || a.nch == 0) return hipSuccess;
-    hipLaunchKernelGGL(dense_fill_kernel, dim3((unsigned)blocks, (unsigned)((a.nch + FILL_CHUNKS - 1) / FILL_CHUNKS)), dim3(256), 0, s, a);
-    return hipGetLastError();
+    return launch_kernel(dense_fill_kernel, dim3((unsigned)blocks, (unsigned)((a.nch + FILL_CHUNKS - 1) / FILL_CHUNKS)), dim3(256), 0, s, a);
 }

@@ -436,8 +436,7 @@ template <int BNB, int WK, int LB, int RB, bool U, int NS> hipError_t launch_one
     for (int sh = 0; sh < 31; ++sh)
         if ((1 << sh) == a.ntiles) a.tile_shift = sh;
     dim3 grid((unsigned)((a.items ? a.n_units : a.P) * a.ntiles), (unsigned)a.batch), block(64 * WK);
-    hipLaunchKernelGGL((spmm_kernel<BNB, WK, LB, RB, U, NS>), grid, block, 0, s, a);
-    return hipGetLastError();
+    return launch_kernel((spmm_kernel<BNB, WK, LB, RB, U, NS>), grid, block, 0, s, a);
 }
 
 template <int BNB, int LB, int RB, bool U, int NS> hipError_t launch_ns(const SpmmArgs &a, int waves, hipStream_t s)
@@ -518,24 +517,21 @@ hipError_t launch_zero_ints(int32_t *p, int64_t n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     const int64_t n4 = n / 4;
-    hipLaunchKernelGGL(zero_ints_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, p, n4);
-    return hipGetLastError();
+    return launch_kernel(zero_ints_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, p, n4);
 }
 
 hipError_t launch_finish_split_rows(const int32_t *acc, int n, int n_split, int V, int batch, const int32_t *panels, void *C,
                                     int64_t ldc, int64_t C_batch_stride, int float_out, float scale, hipStream_t s)
 {
     if (n_split == 0 || batch == 0 || n == 0) return hipSuccess;
-    hipLaunchKernelGGL(finish_split_rows_kernel, dim3((unsigned)n_split, (unsigned)batch), dim3(256), 0, s, acc, n, n_split, V, panels,
+    return launch_kernel(finish_split_rows_kernel, dim3((unsigned)n_split, (unsigned)batch), dim3(256), 0, s, acc, n, n_split, V, panels,
                        C, ldc, C_batch_stride, float_out, scale);
-    return hipGetLastError();
 }
 
 hipError_t launch_zero_rows(int32_t *C, int64_t ldc, int n, int V, const int32_t *panels, int n_panels, hipStream_t s)
 {
     if (n_panels == 0 || n == 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_rows_kernel, dim3((unsigned)n_panels), dim3(256), 0, s, C, ldc, n, V, panels);
-    return hipGetLastError();
+    return launch_kernel(zero_rows_kernel, dim3((unsigned)n_panels), dim3(256), 0, s, C, ldc, n, V, panels);
 }
 
 // The L8-R8 kernel on 128-byte tiles with two waves per panel and two chunks in flight, instrumented with time stamps
@@ -548,8 +544,7 @@ hipError_t launch_spmm_phase_probe(const SpmmArgs &a, hipStream_t s)
     b.tile_shift = -1;
     for (int sh = 0; sh < 31; ++sh)
         if ((1 << sh) == b.ntiles) b.tile_shift = sh;
-    hipLaunchKernelGGL((spmm_kernel<128, 2, 8, 8, false, 2, true>), dim3((unsigned)(a.P * b.ntiles)), dim3(128), 0, s, b);
-    return hipGetLastError();
+    return launch_kernel((spmm_kernel<128, 2, 8, 8, false, 2, true>), dim3((unsigned)(a.P * b.ntiles)), dim3(128), 0, s, b);
 }
 
 hipError_t launch_spmm(mc_prec prec, const SpmmArgs &a, int bnb, int waves, hipStream_t s)

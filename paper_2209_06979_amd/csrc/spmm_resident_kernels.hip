@@ -394,8 +394,7 @@ template <int LB, bool R4, int NT, Walk WALK, int OUT> hipError_t launch_one(con
     }
     // ids of the same panel group are equal modulo 8 (see the kernel): groups are rounded up to a multiple of 8
     dim3 grid((unsigned)((a.groups + 7) / 8 * 8 * a.ntiles)), block(64 * a.waves);
-    hipLaunchKernelGGL(kern, grid, block, lds, s, a);
-    return hipGetLastError();
+    return launch_kernel(kern, grid, block, lds, s, a);
 }
 
 template <int LB, bool R4, int NT> hipError_t launch_walk(const SlabArgs &a, hipStream_t s)

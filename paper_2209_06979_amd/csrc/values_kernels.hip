@@ -87,6 +87,5 @@ hipError_t launch_set_values(ValuesArgs a, hipStream_t s)
         blocks += (a.job[k].nchunks + 3) / 4;
     }
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(set_values_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
-    return hipGetLastError();
+    return launch_kernel(set_values_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
 }
