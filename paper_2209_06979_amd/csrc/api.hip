@@ -113,7 +113,7 @@ void free_device(mc_mat *A)
     if (A->d_splits) (void)hipFree(A->d_splits);
     if (A->d_class_panels) (void)hipFree(A->d_class_panels);
     if (A->d_merge_src) (void)hipFree(A->d_merge_src);
-    if (A->d_chunk_panel) (void)hipFree(A->d_chunk_panel);
+    if (A->d_chunk_vec) (void)hipFree(A->d_chunk_vec);
     if (A->d_dense) (void)hipFree(A->d_dense);
     if (A->merged) {
         free_device(A->merged);
@@ -569,7 +569,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     A->blk_nt = A->block_rows = A->nblk = 0; A->blk_chunks = 0; A->blk_valid = false; A->d_order = A->d_splits = nullptr;
     A->d_blk_ptr = nullptr; A->d_blk_recs = nullptr; A->d_blk_ends = nullptr; A->d_blk_src = nullptr;
     A->d_class_panels = nullptr;
-    A->merged = nullptr; A->merge_group = 0; A->d_merge_src = nullptr; A->d_chunk_panel = nullptr; A->merged_valid = false;
+    A->merged = nullptr; A->merge_group = 0; A->d_merge_src = nullptr; A->d_chunk_vec = nullptr; A->merged_valid = false;
     A->d_dense = nullptr; A->dense_valid = false;
     // Length classes of the panels (V = 8: the attention kernel gives a panel 1, 2, 4 or 8 waves)
     std::vector<int32_t> class_panels;
@@ -762,19 +762,22 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         MC_TRY(hipMemcpyAsync(A->d_slot_idx, slot_idx.data(), sizeof(int32_t) * (size_t)lay.nslots, hipMemcpyHostToDevice, s));
     if (lay.vals_bytes)
         MC_TRY(hipMemcpyAsync(A->d_vals, vals.data(), (size_t)lay.vals_bytes, hipMemcpyHostToDevice, s));
-    std::vector<int32_t> chunk_panel;
+    std::vector<int32_t> chunk_vec;
     if (lhs_bits != 0 && lay.nslots) {
         try {
-            chunk_panel.resize((size_t)(lay.nslots / MC_CHUNK));
+            chunk_vec.resize(2 * (size_t)(lay.nslots / MC_CHUNK));
         } catch (const std::bad_alloc &) {
             free_device(A);
             delete A;
             return MC_ENOMEM;
         }
         for (int p = 0; p < lay.P; ++p)
-            for (int c = panel_ptr[2 * (size_t)p] / MC_CHUNK, e = (panel_ptr[2 * (size_t)p + 1] + MC_CHUNK - 1) / MC_CHUNK; c < e; ++c) chunk_panel[(size_t)c] = p;
-        MC_TRY(hipMalloc(&A->d_chunk_panel, sizeof(int32_t) * chunk_panel.size()));
-        MC_TRY(hipMemcpyAsync(A->d_chunk_panel, chunk_panel.data(), sizeof(int32_t) * chunk_panel.size(), hipMemcpyHostToDevice, s));
+            for (int v = row_ptr[p], c = panel_ptr[2 * (size_t)p] / MC_CHUNK; v < row_ptr[p + 1]; v += MC_CHUNK, ++c) {
+                chunk_vec[2 * (size_t)c] = v;
+                chunk_vec[2 * (size_t)c + 1] = std::min(MC_CHUNK, row_ptr[p + 1] - v);
+            }
+        MC_TRY(hipMalloc(&A->d_chunk_vec, sizeof(int32_t) * chunk_vec.size()));
+        MC_TRY(hipMemcpyAsync(A->d_chunk_vec, chunk_vec.data(), sizeof(int32_t) * chunk_vec.size(), hipMemcpyHostToDevice, s));
     }
     if (A->n_items) {
         MC_TRY(hipMalloc(&A->d_items, sizeof(int32_t) * items.size()));
@@ -876,11 +879,10 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
         const int32_t *merge_src = X == A ? nullptr : A->d_merge_src;
         const int chunk_bytes = MC_CHUNK * X->V * a.bits / 8;
         ValuesJob &panels = a.job[a.njobs++];
-        panels = {X->d_chunk_panel, X->d_panel_ptr, X->d_row_ptr, nullptr, merge_src, static_cast<uint8_t *>(X->d_vals), X->nslots / MC_CHUNK,
-                  chunk_bytes, 0, X->V, 0};
+        panels = {X->d_chunk_vec, nullptr, merge_src, static_cast<uint8_t *>(X->d_vals), X->nslots / MC_CHUNK, chunk_bytes, 0, X->V, 0};
         if (X->d_blk_recs) { // the LDS-ordered copy follows
             ValuesJob &copy = a.job[a.njobs++];
-            copy = {nullptr, nullptr, nullptr, X->d_blk_src, merge_src, X->d_blk_recs, X->blk_chunks, resident_rec_bytes(X), 2 * MC_CHUNK, X->V, 0};
+            copy = {nullptr, X->d_blk_src, merge_src, X->d_blk_recs, X->blk_chunks, resident_rec_bytes(X), 2 * MC_CHUNK, X->V, 0};
         }
     }
     MC_HIP(launch_set_values(a, static_cast<hipStream_t>(stream)));

@@ -67,7 +67,7 @@ struct mc_mat {
     mc_mat *merged;
     int merge_group;
     int32_t *d_merge_src;      // merged nvec * merge_group: interchange vector of each panel's share, -1 = zeros
-    int32_t *d_chunk_panel;    // panel of each chunk of the panel format (operands with values)
+    int32_t *d_chunk_vec;      // operands with values: first stored vector of each chunk of the panel format, and how many it has
     bool merged_valid;         // false once the values were replaced in the panel format only
     // The operand with all its columns (null when not built; see spmm_dense_kernels.hip).
     uint8_t *d_dense;
@@ -247,7 +247,7 @@ struct SoftmaxArgs {
 
 // One device format that receives an operand's new values.
 struct ValuesJob {
-    const int32_t *chunk_panel, *panel_ptr, *row_ptr; // panels: the panel of each chunk, its slots, its first stored vector
+    const int32_t *chunk_vec;  // panels: first stored vector and number of vectors of each chunk
     const int32_t *blk_src;    // LDS-ordered copy (else null): the stored vector of each slot, -1 for padding
     const int32_t *merge_src;  // merged copy (else null): the operand's own vector behind each share of a merged vector, -1: zeros
     uint8_t *dst;              // chunk c's values at c * rec_bytes + head_bytes

@@ -2,78 +2,111 @@
 // LDS-ordered copy, and the same two of its merged copy.  (It was a launch per format and one for the merged values in
 // interchange order: with the first kernels of a layer's steps that is what a small layer waits for.)
 //
-// What bounds it: latency -- the formats of 100,000 vectors are a few megabytes -- and, written byte by byte as the formats
-// ask for it (the values of a vector lie 16 or 8 bytes apart), the number of stores.  A workgroup therefore takes four chunks of
-// one format, a thread reads one slot's vector in one or two loads, the bytes are put into place in LDS, and the finished
-// chunks are copied out 16 bytes at a time.
-// 2048 x 2048, 90 % empty, V = 8 (panels, merged panels and their LDS-ordered copy): 4 launches, 18 us -> 1 launch, 5.8 us
-// under the profiler; the layer's steps with it 28.7 -> 16.3 us.
+// What bounds it: latency -- the formats of 100,000 vectors are a few megabytes -- so a wave takes one chunk of one format, and
+// its chain is short: the chunk's first vector (one scalar load), for a merged panel the vectors behind its shares, their values, one
+// trip through LDS.  A lane has one slot: the bytes of up to eight of its rows are one 64-bit LDS write, the transposing read gives
+// a lane eight slots of one row, and those 8 bytes are the format's.  Waves never meet.
+// 2048 x 2048, 90 % empty, V = 8 (panels, merged panels and their LDS-ordered copy), under the profiler: a launch per format 18 us;
+// one launch, the panel looked up, bytes put into place one by one and workgroups that meet 5.1; as it is 4.1.
 #include "internal.h"
+#include "lds_async.h"
 
 namespace {
 
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
+using mcu::v2i;
 // (a caller's values have no particular alignment)
 struct __attribute__((packed, aligned(1))) u16_any { uint16_t x; };
 struct __attribute__((packed, aligned(1))) u32_any { uint32_t x; };
 struct __attribute__((packed, aligned(1))) u64_any { uint64_t x; };
 
-__global__ __launch_bounds__(256) void set_values_kernel(ValuesArgs a)
+// byte 0 .. 3 of x and of y in turn: the first two of each, the last two
+__device__ __forceinline__ uint64_t interleaved(uint32_t x, uint32_t y)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t tile[4 * MC_CHUNK * 16];       // four chunks: 64 slots x 16 rows of a byte, or 8 of two planes
+    return (uint64_t)__builtin_amdgcn_perm(y, x, 0x07030602) << 32 | __builtin_amdgcn_perm(y, x, 0x05010400);
+}
+
+// V values of `bits` each from s
+template <int BYTES> __device__ __forceinline__ void load_vector(const uint8_t *s, uint64_t &x, uint64_t &y)
+{
+    y = 0;
+    if constexpr (BYTES == 1) x = *s;
+    else if constexpr (BYTES == 2) x = reinterpret_cast<const u16_any *>(s)->x;
+    else if constexpr (BYTES == 4) x = reinterpret_cast<const u32_any *>(s)->x;
+    else x = reinterpret_cast<const u64_any *>(s)->x;
+    if constexpr (BYTES == 16) y = reinterpret_cast<const u64_any *>(s + 8)->x;
+}
+
+// V: rows of a stored vector
+template <int BITS, int V> __global__ __launch_bounds__(256) void set_values_kernel(ValuesArgs a)
+{
+    constexpr int PL = BITS == 16 ? 2 : 1;                       // byte planes
+    constexpr int VB = V * BITS / 8, MOST = 8 / V;               // bytes of a vector; vectors that eight rows come from, at most
+    __shared__ __attribute__((aligned(16))) uint64_t stage[4][PL][MC_CHUNK];
     int k = 0;
     while (k + 1 < a.njobs && (int)blockIdx.x >= a.job[k + 1].first_block) ++k;
     const ValuesJob &job = a.job[k];
-    const int64_t chunk0 = (int64_t)(blockIdx.x - job.first_block) * 4;
-    const int tid = threadIdx.x, i = tid & 63, g = i >> 4, b = i & 15;
-    const int64_t chunk = chunk0 + (tid >> 6);
-    const int rows = job.V, cbytes = MC_CHUNK * rows * a.bits / 8;
-    // the stored vector of this slot, -1: padding
-    int64_t vec = -1;
-    if (chunk < job.nchunks) {
-        if (job.blk_src) {
-            vec = job.blk_src[chunk * MC_CHUNK + i];
-        } else {
-            const int p = job.chunk_panel[chunk], s0 = job.panel_ptr[2 * p];
-            const int64_t at = chunk * MC_CHUNK + i - s0;
-            if (at < job.panel_ptr[2 * p + 1] - s0) vec = job.row_ptr[p] + at;
-        }
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, l = lane & 15;
+    const int64_t chunk = (int64_t)(blockIdx.x - job.first_block) * 4 + w;
+    if (chunk >= job.nchunks) return;
+    int64_t vec = -1;                                            // the stored vector of this lane's slot, -1: padding
+    if (job.blk_src) {
+        vec = job.blk_src[chunk * MC_CHUNK + lane];
+    } else {
+        const v2i c = *reinterpret_cast<const v2i *>(job.chunk_vec + 2 * chunk);
+        if (lane < c.y) vec = c.x + lane;
     }
-    uint8_t *mine = tile + (tid >> 6) * cbytes;
-    const int shares = rows / a.V, vb = a.V * a.bits / 8;         // a merged vector's rows come from that many vectors
-    for (int q = 0; q < shares; ++q) {
-        const int64_t from = (job.merge_src && vec >= 0) ? job.merge_src[vec * shares + q] : vec;
-        uint64_t lo = 0, hi = 0;
-        if (from >= 0) {
-            const uint8_t *s = a.src + from * vb;
-            switch (vb) {
-            case 1: lo = *s; break;
-            case 2: lo = reinterpret_cast<const u16_any *>(s)->x; break;
-            case 4: lo = reinterpret_cast<const u32_any *>(s)->x; break;
-            case 8: lo = reinterpret_cast<const u64_any *>(s)->x; break;
-            default: lo = reinterpret_cast<const u64_any *>(s)->x; hi = reinterpret_cast<const u64_any *>(s + 8)->x; break;
+    const int rows = job.V, shares = rows / V;                   // a merged vector's rows come from `shares` vectors
+    const int octets = rows > 8 ? 2 : 1, per = shares / octets;  // rows are handled eight at a time
+    uint8_t *const dst = job.dst + chunk * job.rec_bytes + job.head_bytes;
+    for (int o = 0; o < octets; ++o) {
+        // all sources, then all values: each a round trip to memory
+        int64_t from[MOST];
+#pragma unroll
+        for (int q = 0; q < MOST; ++q) from[q] = q == 0 ? vec : -1;
+        if (job.merge_src) {
+#pragma unroll
+            for (int q = 0; q < MOST; ++q) from[q] = (q < per && vec >= 0) ? job.merge_src[vec * shares + o * per + q] : -1;
+        }
+        uint64_t x[MOST], y[MOST], bytes[PL] = {};               // row r of the eight in byte r
+#pragma unroll
+        for (int q = 0; q < MOST; ++q) load_vector<VB>(a.src + (from[q] < 0 ? 0 : from[q]) * VB, x[q], y[q]);
+#pragma unroll
+        for (int q = 0; q < MOST; ++q) {
+            if (from[q] < 0) x[q] = y[q] = 0;
+            constexpr uint32_t NIB = 0x0F0F0F0Fu;
+            const int at = 8 * V * q;
+            if constexpr (BITS == 8) {
+                bytes[0] |= x[q] << at;
+            } else if constexpr (BITS == 4) {
+                bytes[0] |= interleaved((uint32_t)x[q] & NIB, (uint32_t)(x[q] >> 4) & NIB) << at;
+            } else { // value = 256 * high + low, both signed: the low byte as it is, the high byte of the value + 128
+                const uint32_t w4[4] = {(uint32_t)x[q], (uint32_t)(x[q] >> 32), (uint32_t)y[q], (uint32_t)(y[q] >> 32)};
+                uint32_t r4[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) r4[t] = ((w4[t] & 0x7FFF7FFFu) + 0x00800080u) ^ (w4[t] & 0x80008000u);
+                bytes[PL - 1] |= ((uint64_t)__builtin_amdgcn_perm(w4[3], w4[2], 0x06040200) << 32 | __builtin_amdgcn_perm(w4[1], w4[0], 0x06040200)) << at;
+                bytes[0] |= ((uint64_t)__builtin_amdgcn_perm(r4[3], r4[2], 0x07050301) << 32 | __builtin_amdgcn_perm(r4[1], r4[0], 0x07050301)) << at;
             }
         }
-        const int v0 = q * a.V;
-        if (a.bits == 8) {
-            for (int v = 0; v < a.V; ++v) mine[g * (16 * rows) + (v0 + v) * 16 + b] = (uint8_t)((v < 8 ? lo : hi) >> (8 * (v & 7)));
-        } else if (a.bits == 16) {
-            for (int v = 0; v < a.V; ++v) {
-                const int x = (int16_t)((v < 4 ? lo : hi) >> (16 * (v & 3))), h = (x + 128) >> 8, l = x - h * 256;
-                mine[g * (32 * rows) + (v0 + v) * 16 + b] = (uint8_t)h;
-                mine[g * (32 * rows) + 16 * rows + (v0 + v) * 16 + b] = (uint8_t)l;
+#pragma unroll
+        for (int p = 0; p < PL; ++p) stage[w][p][lane] = bytes[p];
+        mcu::lgkm_wait();                                        // (LDS executes a wave's instructions in order: for the compiler)
+        __builtin_amdgcn_wave_barrier();
+        // lane l of a group of 16 slots: row l % 8 of the octet, slots 0 .. 7 (l < 8) or 8 .. 15
+        const int row = o * 8 + (l & 7), half = l >> 3;
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+            v2i d = mcu::lds_read_tr8(&stage[w][p][g * 16 + (l >> 1) + 8 * (l & 1)]);
+            if constexpr (BITS == 4) {                           // byte b: slots b and b + 8
+                const v2i up = {__builtin_amdgcn_update_dpp(0, d.x, 0x128, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, d.y, 0x128, 0xF, 0xF, false)};
+                d = (v2i){d.x | up.x << 4, d.y | up.y << 4};
+                if (row < rows && half == 0) *reinterpret_cast<v2i *>(dst + (g * rows + row) * 8) = d;
+            } else if (row < rows) {
+                *reinterpret_cast<v2i *>(dst + ((g * PL + p) * rows + row) * 16 + half * 8) = d;
             }
-        } else { // slots b and b + 8 share bytes
-            const uint64_t other = __shfl_xor((unsigned long long)lo, 8, 64);
-            if (b < 8)
-                for (int v = 0; v < a.V; ++v) mine[g * (8 * rows) + (v0 + v) * 8 + b] = (uint8_t)(((lo >> (4 * v)) & 15) | (((other >> (4 * v)) & 15) << 4));
         }
-    }
-    __syncthreads();
-    const int per = cbytes / 16;
-    for (int u = tid; u < 4 * per; u += 256) {
-        const int64_t c = chunk0 + u / per;
-        if (c < job.nchunks) *reinterpret_cast<v4u *>(job.dst + c * job.rec_bytes + job.head_bytes + (u % per) * 16) = reinterpret_cast<const v4u *>(tile)[u];
+        mcu::lgkm_wait();                                        // the next octet goes to the same place
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -87,5 +120,17 @@ hipError_t launch_set_values(ValuesArgs a, hipStream_t s)
         blocks += (a.job[k].nchunks + 3) / 4;
     }
     if (blocks == 0) return hipSuccess;
-    return launch_kernel(set_values_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    const dim3 grid((unsigned)blocks), block(256);
+    switch (a.bits * 16 + a.V) {
+    case 4 * 16 + 2: return launch_kernel(set_values_kernel<4, 2>, grid, block, 0, s, a);
+    case 4 * 16 + 4: return launch_kernel(set_values_kernel<4, 4>, grid, block, 0, s, a);
+    case 4 * 16 + 8: return launch_kernel(set_values_kernel<4, 8>, grid, block, 0, s, a);
+    case 8 * 16 + 2: return launch_kernel(set_values_kernel<8, 2>, grid, block, 0, s, a);
+    case 8 * 16 + 4: return launch_kernel(set_values_kernel<8, 4>, grid, block, 0, s, a);
+    case 8 * 16 + 8: return launch_kernel(set_values_kernel<8, 8>, grid, block, 0, s, a);
+    case 16 * 16 + 2: return launch_kernel(set_values_kernel<16, 2>, grid, block, 0, s, a);
+    case 16 * 16 + 4: return launch_kernel(set_values_kernel<16, 4>, grid, block, 0, s, a);
+    case 16 * 16 + 8: return launch_kernel(set_values_kernel<16, 8>, grid, block, 0, s, a);
+    default: return hipErrorInvalidValue;
+    }
 }
