@@ -1,9 +1,8 @@
 // Sparse softmax with fused dequantisation of the scores and re-quantisation of the
 // probabilities (Section 5.3) for gfx950.
 //
-// One workgroup of 256 threads per (panel, score set).  A panel's scores are one contiguous block
-// of nvec_p * V int32 in interchange order (V consecutive values per stored vector), and every
-// row of the panel has the same number of entries, so the rows of a panel are reduced together.
+// A panel's scores are one contiguous block of nvec_p * V int32 in interchange order (V consecutive values per stored
+// vector), and every row of the panel has the same number of entries, so the rows of a panel are reduced together.
 //
 //   softmax_wave_kernel<R>    panels of up to R * 256 scores: ONE WAVE per panel (four panels per
 //                             workgroup), each lane keeps R pieces of four consecutive scores in
@@ -12,6 +11,10 @@
 //   softmax_group_kernel<R,NW> panels of up to R * NW * 256 scores: the same with the NW waves of a
 //                             workgroup sharing one panel (reductions finish through LDS).
 //   softmax_general_kernel    any panel length: three passes over the scores in memory.
+//
+// What bounds them: one read and one write per score where there are many panels (5 bytes a score: 5.8 TB/s at 32768 panels
+// of 4096 scores), the chain load - reduce - exponentials - reduce - store where there are few, and in between the
+// instructions for pieces that a panel does not have: R is no larger than the longest panel needs.
 //
 // The integer codes go out either in interchange order (int8 / int16) or straight in the device
 // panel format that the SpMM kernels read (Section 4.3 lets the producer pick the format by its
@@ -45,6 +48,23 @@ __device__ __forceinline__ int dev_offset(int e, int vs, int pb)
 // r % 2 for V = 2 (then components 0/2 and 1/3 belong together).  MAX: maximum, else sum.
 template <bool MAX> __device__ __forceinline__ float comb(float x, float y) { return MAX ? fmaxf(x, y) : x + y; }
 
+// the value of the lane N lanes on in its row of 16 (cyclic)
+template <int N> __device__ __forceinline__ float rotated(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF, false));
+}
+
+// v and what the lanes of the other half (HALF: of 32 lanes, else of each pair of rows of 16) hold, combined
+template <bool MAX, bool HALF> __device__ __forceinline__ float exchanged(float v)
+{
+    const unsigned b = __builtin_bit_cast(unsigned, v);
+    const auto s = HALF ? __builtin_amdgcn_permlane32_swap(b, b, false, false) : __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    const unsigned x = s[0], y = s[1];   // (the cast of a vector's element itself would take the first for every one)
+    return comb<MAX>(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y));
+}
+
+// All in registers: rotations by 2, 4 and 8 in a row of 16 lanes (they keep a lane's parity), then exchanges of rows and of halves.
+// Through LDS, as shuffles, the five dependent steps of both reductions took 0.7 us of a launch.
 template <bool MAX> __device__ __forceinline__ v4f reduce_lanes(v4f x, int V)
 {
     if (V == 2) {
@@ -54,10 +74,11 @@ template <bool MAX> __device__ __forceinline__ v4f reduce_lanes(v4f x, int V)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         float v = x[r];
-        if (V < 8) v = comb<MAX>(v, __shfl_xor(v, 1, 64));
-#pragma unroll
-        for (int d = 2; d < 64; d <<= 1) v = comb<MAX>(v, __shfl_xor(v, d, 64));
-        x[r] = v;
+        if (V < 8) v = comb<MAX>(v, rotated<1>(v));
+        v = comb<MAX>(v, rotated<2>(v));
+        v = comb<MAX>(v, rotated<4>(v));
+        v = comb<MAX>(v, rotated<8>(v));
+        x[r] = exchanged<MAX, true>(exchanged<MAX, false>(v));
     }
     return x;
 }
@@ -251,9 +272,9 @@ __device__ __forceinline__ void softmax_panel(const SoftmaxArgs &a, int panel, i
     }
 }
 
-// four waves per SIMD: every panel of a 4096-panel launch is resident at once
+// at least four waves per SIMD: every panel of a 4096-panel launch is resident at once
 template <int R, bool C16, bool DEV>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void softmax_wave_kernel(SoftmaxArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void softmax_wave_kernel(SoftmaxArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint8_t stage[4][DEV ? R * 256 * (C16 ? 2 : 1) : 16]; // device-format codes, per wave
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -352,19 +373,28 @@ __global__ __launch_bounds__(256) void softmax_general_kernel(SoftmaxArgs a)
 
 template <bool C16, bool DEV> hipError_t launch_softmax_mode(const SoftmaxArgs &a, hipStream_t s)
 {
-    dim3 grid((unsigned)a.P, (unsigned)a.batch), grid4((unsigned)((a.P + 3) / 4), (unsigned)a.batch);
+    const dim3 grid((unsigned)a.P, (unsigned)a.batch), grid4((unsigned)((a.P + 3) / 4), (unsigned)a.batch);
     const int64_t longest = (int64_t)a.max_panel_chunks * MC_CHUNK * a.V; // scores of the longest panel, padding included
     const int64_t units = (int64_t)a.P * a.batch;
-    if (a.variant == 0 && longest <= 16 * 256) {
-        // few panels: two waves per panel halve the time of the launch (5.9 -> 5.2 us for 512 panels of 3280
-        // scores); many: one wave per panel (15.0 against 17.4 us for 4096 of them)
-        if (units <= 1024) return launch_kernel((softmax_group_kernel<8, 2, C16, DEV>), grid, dim3(128), 0, s, a);
-        return launch_kernel((softmax_wave_kernel<16, C16, DEV>), grid4, dim3(256), 0, s, a);
-    } else if (a.variant != 2 && longest <= 16 * 1024) {
-        return launch_kernel((softmax_group_kernel<16, 4, C16, DEV>), grid, dim3(256), 0, s, a);
-    } else {
-        return launch_kernel(softmax_general_kernel, grid, dim3(256), 0, s, a);
-    }
+    // One wave per panel up to 2048 scores, with the smallest R; workgroups of four or eight waves beyond, and from 1025 scores on
+    // also for few panels, whose launch is one chain.  us, V = 8, int8 codes, replayed from a graph, before (8 x 2 waves up to 1024
+    // panels, 16 x 1 wave beyond, 16 x 4 from 4097 scores on, all with shuffles through LDS) and as it is:
+    //   scores   256 panels   1024         4096         32768
+    //      512   4.1   2.7    4.6   2.7     6.5   4.1    35    17
+    //     1024   4.2   3.1    4.7   3.3     8.5   6.7    42    32
+    //     2048   4.4   3.2    5.0   4.0    11.1   9.9    62    63   (256 panels by single waves: 3.8; 1024 by workgroups: 4.7)
+    //     4096   4.8   3.7    8.0   7.6    17.5  15.8   124   120   (1024 panels by 8 x 2 waves: 7.4, 4096: 16.4)
+    //     8192   5.8   4.5   12.0  11.2    34.1  33.2   233   235   (by 8 x 4 waves 4.4, 10.8, 34.2, 248)
+    //    16384   8.6   7.3   18.2  17.2    68.0  68.2
+    const bool few = units <= 512;
+    if (a.variant == 2 || longest > 16384) return launch_kernel(softmax_general_kernel, grid, dim3(256), 0, s, a);
+    if (longest > 8192) return launch_kernel((softmax_group_kernel<8, 8, C16, DEV>), grid, dim3(512), 0, s, a);
+    if (longest > 4096) return launch_kernel((softmax_group_kernel<4, 8, C16, DEV>), grid, dim3(512), 0, s, a);
+    if (longest > 2048) return launch_kernel((softmax_group_kernel<4, 4, C16, DEV>), grid, dim3(256), 0, s, a);
+    if (a.variant == 1 || (few && longest > 1024)) return launch_kernel((softmax_group_kernel<2, 4, C16, DEV>), grid, dim3(256), 0, s, a);
+    if (longest > 1024) return launch_kernel((softmax_wave_kernel<8, C16, DEV>), grid4, dim3(256), 0, s, a);
+    if (longest > 512) return launch_kernel((softmax_wave_kernel<4, C16, DEV>), grid4, dim3(256), 0, s, a);
+    return launch_kernel((softmax_wave_kernel<2, C16, DEV>), grid4, dim3(256), 0, s, a);
 }
 
 hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s)
