@@ -48,10 +48,19 @@ __device__ __forceinline__ int dev_offset(int e, int vs, int pb)
 // r % 2 for V = 2 (then components 0/2 and 1/3 belong together).  MAX: maximum, else sum.
 template <bool MAX> __device__ __forceinline__ float comb(float x, float y) { return MAX ? fmaxf(x, y) : x + y; }
 
-// the value of the lane N lanes on in its row of 16 (cyclic)
-template <int N> __device__ __forceinline__ float rotated(float v)
+// the value of the lane whose number differs in bit D (1, 2, 4 or 8), in registers
+template <int D> __device__ __forceinline__ float partner(float v)
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF, false));
+    const int b = __builtin_bit_cast(int, v);
+    int r;
+    if (D == 1) r = __builtin_amdgcn_update_dpp(0, b, 0xB1, 0xF, 0xF, false);      // quad_perm [1,0,3,2]
+    else if (D == 2) r = __builtin_amdgcn_update_dpp(0, b, 0x4E, 0xF, 0xF, false); // quad_perm [2,3,0,1]
+    else if (D == 8) r = __builtin_amdgcn_update_dpp(0, b, 0x128, 0xF, 0xF, false); // row_ror:8
+    else { // the even quads of a row from four lanes on, the odd ones from four lanes back
+        r = __builtin_amdgcn_update_dpp(b, b, 0x104, 0xF, 0x5, false);
+        r = __builtin_amdgcn_update_dpp(r, b, 0x114, 0xF, 0xA, false);
+    }
+    return __builtin_bit_cast(float, r);
 }
 
 // v and what the lanes of the other half (HALF: of 32 lanes, else of each pair of rows of 16) hold, combined
@@ -63,8 +72,8 @@ template <bool MAX, bool HALF> __device__ __forceinline__ float exchanged(float 
     return comb<MAX>(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y));
 }
 
-// All in registers: rotations by 2, 4 and 8 in a row of 16 lanes (they keep a lane's parity), then exchanges of rows and of halves.
-// Through LDS, as shuffles, the five dependent steps of both reductions took 0.7 us of a launch.
+// All in registers, partner by partner, so that all lanes come to the same sum.  Through LDS, as shuffles, the five dependent
+// steps of both reductions took 0.7 us of a launch.
 template <bool MAX> __device__ __forceinline__ v4f reduce_lanes(v4f x, int V)
 {
     if (V == 2) {
@@ -74,10 +83,10 @@ template <bool MAX> __device__ __forceinline__ v4f reduce_lanes(v4f x, int V)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         float v = x[r];
-        if (V < 8) v = comb<MAX>(v, rotated<1>(v));
-        v = comb<MAX>(v, rotated<2>(v));
-        v = comb<MAX>(v, rotated<4>(v));
-        v = comb<MAX>(v, rotated<8>(v));
+        if (V < 8) v = comb<MAX>(v, partner<1>(v));
+        v = comb<MAX>(v, partner<2>(v));
+        v = comb<MAX>(v, partner<4>(v));
+        v = comb<MAX>(v, partner<8>(v));
         x[r] = exchanged<MAX, true>(exchanged<MAX, false>(v));
     }
     return x;
@@ -385,10 +394,10 @@ template <bool C16, bool DEV> hipError_t launch_softmax_mode(const SoftmaxArgs &
     //     2048   4.4   3.2    5.0   4.0    11.1   9.9    62    63   (256 panels by single waves: 3.8; 1024 by workgroups: 4.7)
     //     4096   4.8   3.7    8.0   7.6    17.5  15.8   124   120   (1024 panels by 8 x 2 waves: 7.4, 4096: 16.4)
     //     8192   5.8   4.5   12.0  11.2    34.1  33.2   233   235   (by 8 x 4 waves 4.4, 10.8, 34.2, 248)
-    //    16384   8.6   7.3   18.2  17.2    68.0  68.2
+    //    16384   8.6   8.0   18.2  17.8    68.0  68.1
     const bool few = units <= 512;
     if (a.variant == 2 || longest > 16384) return launch_kernel(softmax_general_kernel, grid, dim3(256), 0, s, a);
-    if (longest > 8192) return launch_kernel((softmax_group_kernel<8, 8, C16, DEV>), grid, dim3(512), 0, s, a);
+    if (longest > 8192) return launch_kernel((softmax_group_kernel<16, 4, C16, DEV>), grid, dim3(256), 0, s, a);
     if (longest > 4096) return launch_kernel((softmax_group_kernel<4, 8, C16, DEV>), grid, dim3(512), 0, s, a);
     if (longest > 2048) return launch_kernel((softmax_group_kernel<4, 4, C16, DEV>), grid, dim3(256), 0, s, a);
     if (a.variant == 1 || (few && longest > 1024)) return launch_kernel((softmax_group_kernel<2, 4, C16, DEV>), grid, dim3(256), 0, s, a);
