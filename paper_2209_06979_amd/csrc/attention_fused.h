@@ -75,10 +75,15 @@ __device__ __forceinline__ float row16_sum(float v)
 // PB: bits of the re-quantised softmax output.  16 ("16b-8b" layer): the code c <= 32639 is split
 // into signed bytes c = 256*hi + lo (Section 4.4); the hi codes feed MFMA rows 0..7 and the lo
 // codes rows 8..15 of the same instruction, and the output is (O_hi << 8) + O_lo.
-// QB: bits of Q, Kmat and V.  4 ("8b-4b" layer): rows are 32 bytes of packed nibbles.  A nibble is
-// widened in registers to an int8 worth 16 x its value (Section 4.4 without an int4 matrix unit):
-// the even elements of a 16-byte piece in lane groups 0 and 1, the odd ones in groups 2 and 3, so
-// the scores carry a factor 256 and the output a factor 16, removed by exact shifts.
+// QB: bits of Q, Kmat and V.  4 ("8b-4b" layer): rows are 32 bytes of packed nibbles, whose bytes are widened in registers (Section 4.4
+// without an int4 matrix unit): the even elements of a 16-byte piece in lane groups 0 and 1, the odd ones in groups 2 and 3.  An
+// odd element stays in the upper half of its byte, worth 16 x its value; an even one in the lower half as value + 8, which one
+// three-input logic operation makes of it, where a shift to the upper half took two (and a select between the two kinds of lane a third).
+// The scores come out 16-fold and the 8s as a constant per row of Q, with which the sums start; in the output the 8s are 8 times the sum of
+// the codes, which one more MFMA per chunk adds up.  Short of the largest launches, which wait for L2 (a request per row whatever its
+// length), these layers are bound by the VALU: a chunk took 64 + 32 + 45 instructions, now 24 + 32 + 37.  By itself, 8-bit codes:
+// 8 heads x 1752, dk = 128, 73 % empty 14.3 -> 12.0 us; 12 x 4064, dk = 128, 80 % 60.4 -> 54.3; 8 x 12 x 1712, dk = 96, 72 % 110.6 -> 99.6;
+// 8 x 12 x 5432, dk = 64, 92 % 199 both.
 // KS: waves that share one (panel, head) when a panel is longer than MAXCH chunks: wave ks takes
 // chunks ks, ks + KS, ...; the waves exchange their row maxima and row sums through LDS and add up
 // their partial output tiles at the end (three workgroup barriers in total).  With HPW 2 the
@@ -177,9 +182,9 @@ void attention_fused_kernel(AttnArgs a)
         if (!PAD || (QB == 8 ? 4 * kk + g : 2 * kk + (g & 1)) < a.real_pieces) { // (a piece the row does not have stays zero)
             if (QB == 8) {
                 qv = *reinterpret_cast<const v4i *>(qrow + kk * 64 + g * 16);
-            } else {
+            } else { // 16 x the even elements; the odd ones as they are, sign-extended from the upper half
                 const v4i raw = *reinterpret_cast<const v4i *>(qrow + kk * 32 + (g & 1) * 16);
-                qv = (g < 2) ? ((raw << 4) & NIB) : (raw & NIB);
+                qv = (g < 2) ? ((raw << 4) & NIB) : ((((((raw >> 4) & ~NIB) ^ 0x08080808) | (int)0x80808080) - 0x08080808) ^ (int)0x80808080);
             }
         }
         q_lo[kk] = (j < 8) ? qv : (v4i){0, 0, 0, 0};
@@ -263,10 +268,20 @@ void attention_fused_kernel(AttnArgs a)
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
         kaddr[kk] = stage + (j % NIT) * 1024 + (j / NIT) * ROWB + (((NITW * w + (QB == 8 ? 4 * kk + g : 2 * kk + (g & 1))) ^ (j % NIT)) * 16);
+    const int flip = g < 2 ? 0x08080808 : 0, half = g < 2 ? ~NIB : NIB;
     auto kop = [&](v4i raw) -> v4i {
         if (QB == 8) return raw;
-        return (g < 2) ? ((raw << 4) & NIB) : (raw & NIB);
+        return (raw ^ flip) & half;
     };
+    v4i first = {0, 0, 0, 0};                  // what the sums start with: -8 x 16 x the row's even elements
+    if (QB == 4) {
+        const int minus8 = g < 2 ? (int)0xF8F8F8F8 : 0;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            first = __builtin_amdgcn_mfma_i32_16x16x64_i8(q_lo[kk], (v4i){minus8, minus8, minus8, minus8}, first, 0, 0, 0);
+            first = __builtin_amdgcn_mfma_i32_16x16x64_i8(q_hi[kk], (v4i){minus8, minus8, minus8, minus8}, first, 0, 0, 0);
+        }
+    }
     v4i sc[NPR];
     int imax[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
     const int tail = n - (nch - 1) * MC_CHUNK; // real vectors in the last chunk
@@ -287,18 +302,14 @@ void attention_fused_kernel(AttnArgs a)
 #pragma unroll
                 for (int tl = 0; tl < 4; ++tl) kt[kk][tl] = *reinterpret_cast<const v4i *>(kaddr[kk] + ST + tl * 256);
             release(Kg, gc);
-            sc[2 * c] = (v4i){0, 0, 0, 0};
-            sc[2 * c + 1] = (v4i){0, 0, 0, 0};
+            sc[2 * c] = first;
+            sc[2 * c + 1] = first;
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 sc[2 * c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q_lo[kk], kop(kt[kk][0]), sc[2 * c], 0, 0, 0);
                 sc[2 * c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q_hi[kk], kop(kt[kk][1]), sc[2 * c], 0, 0, 0);
                 sc[2 * c + 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q_lo[kk], kop(kt[kk][2]), sc[2 * c + 1], 0, 0, 0);
                 sc[2 * c + 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q_hi[kk], kop(kt[kk][3]), sc[2 * c + 1], 0, 0, 0);
-            }
-            if (QB == 4) { // both operands carried a factor 16
-                sc[2 * c] = sc[2 * c] >> 8;
-                sc[2 * c + 1] = sc[2 * c + 1] >> 8;
             }
             // a padded slot repeats the panel's last real column, so its score duplicates a real
             // one and cannot change the row maximum: no masking here
@@ -311,7 +322,7 @@ void attention_fused_kernel(AttnArgs a)
 
     // ---- softmax over row 4*(g&1) + r, in base 2: exp(x - max) = 2^((s - smax) * scale2) -----
     constexpr float LOG2E = 1.4426950408889634f;
-    const float scale2 = a.score_scale * LOG2E;
+    const float scale2 = a.score_scale * LOG2E * (QB == 4 ? 0.0625f : 1.f);
     float m2[4], srow[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -380,6 +391,7 @@ void attention_fused_kernel(AttnArgs a)
     v4i o[NO];
 #pragma unroll
     for (int ct = 0; ct < NO; ++ct) o[ct] = (v4i){0, 0, 0, 0};
+    v4i ocodes = {0, 0, 0, 0};                 // 4 bit: sums of the codes
     // Lane (g, src) supplies the V rows of the chunk's slots s = g*16 + ii and s + 8, and their codes.  (8 slots on is
     // 8 / NIT rows of the stage on, 64 bytes of codes on: instruction offsets; the swizzled places of the column tiles
     // are worked out once.)
@@ -462,11 +474,11 @@ void attention_fused_kernel(AttnArgs a)
                 if (QB == 8) {
                     o[ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop, bop, o[ct], 0, 0, 0);
                 } else { // byte j of the piece holds columns 32*ct + 2j (low nibble) and 2j + 1 (high nibble)
-                    const v4i msk = {NIB, NIB, NIB, NIB};
-                    o[2 * ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop, (bop << 4) & msk, o[2 * ct], 0, 0, 0);
-                    o[2 * ct + 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop, bop & msk, o[2 * ct + 1], 0, 0, 0);
+                    o[2 * ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop, (bop ^ 0x08080808) & ~NIB, o[2 * ct], 0, 0, 0);
+                    o[2 * ct + 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop, bop & NIB, o[2 * ct + 1], 0, 0, 0);
                 }
             }
+            if (QB == 4) ocodes = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop, (v4i){0x01010101, 0x01010101, 0x01010101, 0x01010101}, ocodes, 0, 0, 0);
         }
     });
 
@@ -482,9 +494,9 @@ void attention_fused_kernel(AttnArgs a)
         for (int ct = 0; ct < NO; ++ct)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                // the nibble products carry a factor 16; each plane's sum is shifted on its own
+                // nibbles: low ones were 8 too large, high ones carry a factor 16; each plane's sum for itself
                 if (QB == 8) Ol[(4 * g + r) * (DK + 4) + ct * 16 + j] = o[ct][r];
-                else Ol[(4 * g + r) * (DK + 4) + (ct >> 1) * 32 + 2 * j + (ct & 1)] = o[ct][r] >> 4;
+                else Ol[(4 * g + r) * (DK + 4) + (ct >> 1) * 32 + 2 * j + (ct & 1)] = (ct & 1) ? o[ct][r] >> 4 : o[ct][r] - 8 * ocodes[r];
             }
     }
     lgkm_wait();
