@@ -142,10 +142,14 @@ void attention_fused_kernel(AttnArgs a)
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
     // Workgroups are handed to the 8 XCDs round-robin by linear id.  1, 2, 4 or 8 (head group, batch item) pairs are worked on
-    // at a time, a row of the grid (pairs_at_a_time): an XCD then sees one pair at a time.
+    // at a time, a row of the grid (pairs_at_a_time): an XCD then sees one pair at a time, and neighbouring ones one after the other.
+    // In (L, heads, dk) tensors neighbouring heads share lines unless their rows are whole ones: an XCD finds in its L2 what it would
+    // otherwise fetch while another XCD fetches it, too.  (By itself, neighbouring pairs at the same time and as it is: 8 x 8 heads x 1800, 87 %
+    // empty, 8-bit codes and inputs, dk = 32 36.6 -> 33.9 us, 48 60.2 -> 41.6, 80 61.8 -> 55.4, 96 63.1 -> 59.0, 128 52.4 -> 50.3.)
     const int groups = a.heads / HPW;
-    const int pair = ((int)(blockIdx.z * gridDim.y + blockIdx.y) << a.pair_shift) + (int)(blockIdx.x & ((1u << a.pair_shift) - 1));
-    if (pair >= groups * a.batch) return;
+    const int grid_row = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+    if (grid_row >= a.pair_rows) return;
+    const int pair = (int)(blockIdx.x & ((1u << a.pair_shift) - 1)) * a.pair_rows + grid_row;
     int hgrp = pair, item = 0;
     if (a.batch > 1) {
         item = pair / groups;
@@ -582,7 +586,8 @@ template <int HPW, int PB, int QB, int KS, int DK, bool PAD> hipError_t launch_p
     const unsigned pairs = (unsigned)(a.heads / HPW) * (unsigned)a.batch;
     const int row = HPW * (PAD ? a.real_pieces * 16 : DK * QB / 8), lines = (row + 127) / 128 * 128; // (the L2 holds lines of 128 bytes)
     a.pair_shift = pairs_at_a_time(pairs, 2.0 * a.tokens * (a.in_token_stride < lines ? (double)a.in_token_stride : lines), (double)a.index_bytes);
-    const unsigned rows = pairs >> a.pair_shift, y = rows < 32768 ? rows : 32768;
+    a.pair_rows = (int)(pairs >> a.pair_shift);
+    const unsigned rows = (unsigned)a.pair_rows, y = rows < 32768 ? rows : 32768;
     return launch_kernel((attention_fused_kernel<8, HPW, PB, QB, KS, DK, PAD>), dim3((unsigned)a.P << a.pair_shift, y, (rows + y - 1) / y),
                        dim3(64 * HPW * KS), 0, s, a);
 }

@@ -277,6 +277,7 @@ struct AttnArgs {
     int tokens;                              // rows of Km and Vm
     int64_t index_bytes;                     // column indices of this launch's panels
     int pair_shift;                          // log2 of the (head group, batch item) pairs of a grid row (set by the launcher)
+    int pair_rows;             // filled by the launcher: rows of the grid, pairs >> pair_shift
     // head dimensions below the kernel's tile (launch_attention_fused_padded): 16-byte pieces a Q / Kmat / V row
     // really has, and columns of O
     int real_pieces, out_cols;
