@@ -1484,12 +1484,12 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         f.in_batch_stride = batch_stride * qkv_bits / 8;
         f.score_scale = s_q * s_k / std::sqrt((float)dk); f.inv_s_p = 1.f / s_p; f.out_scale = s_p * s_v;
         f.heads = heads; f.batch = batch; f.tokens = L;
-        // neighbouring heads contiguous inside a token, rows of at most 64 bytes: two heads per workgroup can
-        // gather 128 bytes per token (not for 16-bit codes with 4-bit inputs, whose output tile does not fit
+        // neighbouring heads contiguous inside a token, rows of at most 64 bytes (less than 64 elements where they do not fill the tile): two
+        // heads per workgroup can gather 128 bytes per token (not for 16-bit codes with 4-bit inputs, whose output tile does not fit
         // that kernel's stages)
         const bool short_rows = dk == 64 || qkv_bits == 4;
         const bool fills = dk == tile && tile <= 128; // (the tile of 192 is a padded one)
-        const bool pairs = fills && short_rows && head_stride == dk && heads % 2 == 0 && !(p_bits == 16 && qkv_bits == 4);
+        const bool pairs = ((fills && short_rows) || tile == 64) && head_stride == dk && heads % 2 == 0 && !(p_bits == 16 && qkv_bits == 4);
         const double avg = mask->P ? (double)(mask->nslots / MC_CHUNK) / mask->P : 0.0;
         // One launch for the panels in `list` (null: all), none of which has more than max_chunks chunks.
         auto launch = [&](const int32_t *list, int n_panels, int max_chunks) -> hipError_t {
@@ -1504,7 +1504,9 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 // more waves per unit instead, until about 2048 waves are in flight and while every wave still
                 // has a chunk (256 units of 7 chunks: 5.9 us with one wave each, 4.5 us with four).
                 const int64_t units = (int64_t)n_panels * heads * batch;
-                hpg = (pairs && units >= 2048 && wpp < 8) ? 2 : 1;
+                // (Shorter heads from 4096 units on: 8 x 8 heads x 1584, dk = 48, 84 % empty 40.9 -> 33.7 us, 8 heads x 4896, 83 % 72.1 -> 46.4,
+                // 8 x 8 x 1888, dk = 32 48.1 -> 43.0; 2048 to 4096 units 0.94 - 1.2 times as fast.)
+                hpg = (pairs && units >= (fills ? 2048 : 4096) && wpp < 8) ? 2 : 1;
                 // (rows of 256 bytes: four waves' stages take half a compute unit's LDS)
                 const int64_t in_flight = tile == 192 && qkv_bits == 8 ? 1024 : 2048;
                 if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= in_flight && wpp * 2 <= avg) wpp *= 2;
@@ -1514,7 +1516,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 hpg = (o.attention_mode != 2 && pairs && wpp < 8) ? 2 : 1;
             }
             if (fills) return launch_attention_fused(f, hpg, wpp, p_bits, qkv_bits, dk, s);
-            return launch_attention_fused_padded(f, wpp, p_bits, qkv_bits, tile, s);
+            return launch_attention_fused_padded(f, hpg, wpp, p_bits, qkv_bits, tile, s);
         };
         // Panels of very different lengths (the longest at least twice the average and more than one wave's
         // worth), automatic mode: one launch per length class, so that short panels are not given the many waves

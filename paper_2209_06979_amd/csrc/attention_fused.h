@@ -97,12 +97,13 @@ __device__ __forceinline__ float row16_sum(float v)
 // a.real_pieces 16-byte pieces.  The copies of the missing pieces are left out, so the places they would
 // land in keep the zeros written once at the start (place p of an LDS row always receives the same piece
 // number, see the copy layout below); the Q registers of those pieces are zero as well.  Zero columns add
-// nothing to a score and give zero output columns, which are not stored.  One head per workgroup only.
+// nothing to a score and give zero output columns, which are not stored.  Two heads per workgroup (DK 64 only): the places of both heads' pieces,
+// which are contiguous in memory, side by side as if the rows were full.
 template <int MAXCH, int HPW, int PB, int QB, int KS, int DK, bool PAD = false>
 __global__ __launch_bounds__(64 * HPW * KS, (((HPW == 1 && PB == 8 && KS == 1 && DK == 64) || (HPW == 2 && DK == 64 && QB == 8)) ? 4 : ((KS == 8 || DK == 192) ? 2 : 3)))
 void attention_fused_kernel(AttnArgs a)
 {
-    static_assert(!PAD || HPW == 1, "shorter rows: one head per workgroup");
+    static_assert(!PAD || HPW == 1 || DK == 64, "shorter rows of more than 64 elements: one head per workgroup");
     static_assert(PB == 8 || PB == 16, "8- or 16-bit codes");
     static_assert(QB == 8 || QB == 4, "Q, K, V are 8-bit or packed 4-bit");
     static_assert(DK == 64 || (DK == 128 && (QB == 4 || HPW == 1)) || (DK == 192 && PAD), "rows of 128 bytes: one head per workgroup");
@@ -203,9 +204,13 @@ void attention_fused_kernel(AttnArgs a)
     unsigned segoff[NITW];
 #pragma unroll
     for (int i = 0; i < NITW; ++i) {
-        segoff[i] = (seg ^ ((NITW * w + i) & SWZ)) * 16;
-        // PAD: a piece that the row does not have is not fetched (the sign says so)
-        if (PAD && (int)(seg ^ ((NITW * w + i) & SWZ)) >= a.real_pieces) segoff[i] |= 1u << 31;
+        const int place = seg ^ ((NITW * w + i) & SWZ);
+        segoff[i] = place * 16;
+        if (PAD) { // a piece that the row does not have is not fetched (the sign says so)
+            const int piece = HPW == 1 ? place : place % NITW;
+            segoff[i] = (HPW == 1 ? place : place / NITW * a.real_pieces + piece) * 16;
+            if (piece >= a.real_pieces) segoff[i] |= 1u << 31;
+        }
     }
     const unsigned stage_u = lds_addr_uniform(stage);  // this wave's stage(s)
     // A lane's copies take NITW indices, the same for all lanes of a row.  Loaded by each lane they would be a fifth of

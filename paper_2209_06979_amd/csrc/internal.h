@@ -318,5 +318,5 @@ hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uin
 hipError_t launch_attention_fused(const AttnArgs &a, int heads_per_group, int waves_per_panel, int p_bits, int qkv_bits,
                                   int dk, hipStream_t s);
 // the same kernel for head dimensions below its tile (64 or 128), and up to its tile of 192: one head per workgroup; a.real_pieces, a.out_cols set
-hipError_t launch_attention_fused_padded(const AttnArgs &a, int waves_per_panel, int p_bits, int qkv_bits, int tile, hipStream_t s);
+hipError_t launch_attention_fused_padded(const AttnArgs &a, int heads_per_group, int waves_per_panel, int p_bits, int qkv_bits, int tile, hipStream_t s);
 int attention_fused_max_vectors(); // longest panel (in vectors) the fused kernel accepts
