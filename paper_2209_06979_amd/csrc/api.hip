@@ -1507,9 +1507,9 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 // (Shorter heads from 4096 units on: 8 x 8 heads x 1584, dk = 48, 84 % empty 40.9 -> 33.7 us, 8 heads x 4896, 83 % 72.1 -> 46.4,
                 // 8 x 8 x 1888, dk = 32 48.1 -> 43.0; 2048 to 4096 units 0.94 - 1.2 times as fast.)
                 hpg = (pairs && units >= (fills ? 2048 : 4096) && wpp < 8) ? 2 : 1;
-                // (rows of 256 bytes: four waves' stages take half a compute unit's LDS)
-                const int64_t in_flight = tile == 192 && qkv_bits == 8 ? 1024 : 2048;
-                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= in_flight && wpp * 2 <= avg) wpp *= 2;
+                // (Rows of 256 bytes, too, where four waves' stages take half a compute unit's LDS: against 1024 waves in flight 46 drawn layers of
+                // dk = 144 - 192 1.03 times as fast in the mean, up to 1.23.  4096 waves: 0.98, down to 0.73.)
+                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp * 2 <= avg) wpp *= 2;
             } else {
                 if (o.attention_mode == 3 && wpp < 2) wpp = 2;
                 if (o.attention_mode == 4 && wpp < 4) wpp = 4;

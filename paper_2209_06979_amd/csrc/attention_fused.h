@@ -21,7 +21,7 @@
 //
 // Two variants (HPW = heads per workgroup):
 //   HPW 1  any layout: the wave gathers the rows of its own head (64 bytes; 128 bytes for head
-//          dimension 128 with 8-bit inputs) into its one LDS stage (8 KB of LDS per wave and
+//          dimension 128 with 8-bit inputs) into its one LDS stage (5 KB of LDS per wave and
 //          16 waves per CU for 64-byte rows).
 //   HPW 2  token-major layout (the heads of a token are contiguous, as a QKV projection
 //          writes them): two waves own two neighbouring heads and gather their 128 bytes of
@@ -108,13 +108,13 @@ void attention_fused_kernel(AttnArgs a)
     static_assert(QB == 8 || QB == 4, "Q, K, V are 8-bit or packed 4-bit");
     static_assert(DK == 64 || (DK == 128 && (QB == 4 || HPW == 1)) || (DK == 192 && PAD), "rows of 128 bytes: one head per workgroup");
     constexpr int NW = HPW * KS;         // waves per workgroup
-    constexpr int PLANE = MAXCH * 512;   // bytes of one plane of codes, [slot][8 rows]
-    constexpr int OTILE = (PB == 16 ? 16 : 8) * (DK + 4) * 4;                       // a wave's output tile, staged in the same area
-    // HPW 2: the code area holds ONE chunk (codes are written right before they are read) and the
-    // output tile is staged in the gather stages, which keeps a workgroup below 20 KB of LDS:
-    // eight of them, i.e. all 2048 of a 8 x 4096 layer, are resident at once.
-    constexpr bool SMALLP = (HPW == 2);
-    constexpr int PSTRIDE = SMALLP ? 512 : PLANE;                                   // from the high to the low plane of the codes
+    constexpr int OTILE = (PB == 16 ? 16 : 8) * (DK + 4) * 4;                       // a wave's output tile, staged where the gathered rows were
+    // The code area holds ONE chunk, [plane][slot][8 rows] (codes are written right before they are read; an area for all chunks and
+    // the output tile took 3.5 - 14 KB more of LDS per wave): a workgroup of two heads stays below 20 KB, eight of them, i.e. all 2048 of a 8 x 4096
+    // layer, are resident at once; four waves of a dk of 144 - 192 take 68 KB instead of 82, two workgroups a compute unit instead of
+    // one (12 heads x 5568, dk = 144, 77 % empty 489 -> 296 us, 3 x 2264, dk = 160 28.5 -> 19.1); with 16-bit codes 16 waves are resident instead of
+    // 13 (8 heads x 5008, dk = 96, 95 % 29.1 -> 25.3; 12 x 2 x 2336, dk = 64, 4-bit inputs 35.8 -> 33.7).
+    constexpr int PSTRIDE = 512, PLB = 512 * (PB / 8);                              // from the high to the low plane of the codes; bytes of that area
     constexpr int DKB = DK * QB / 8; // bytes of one head's row
     constexpr int KK = DK / 64;      // MFMA steps along the head dimension
     constexpr int NO = DK / 16;      // column tiles of the output
@@ -127,11 +127,10 @@ void attention_fused_kernel(AttnArgs a)
     constexpr int SWZ = LPR - 1;
     constexpr int NIB = (int)0xF0F0F0F0;
     constexpr int STG = 64 * ROWB;   // bytes of one stage
-    constexpr bool OSTAGE = SMALLP || (DK == 192 && OTILE <= STG);                  // the output tile is staged in a gather stage
-    constexpr int PLB = SMALLP ? 512 * (PB / 8) : ((OSTAGE || PLANE * (PB / 8) > OTILE) ? PLANE * (PB / 8) : OTILE); // bytes of that area
     constexpr int NST = HPW;         // stages: one for a lone wave, two when two waves share the chunks
-    static_assert(!SMALLP || OTILE <= STG, "with two heads per workgroup a wave's output tile is staged in one gather stage");
-    __shared__ __attribute__((aligned(16))) char stage_all[NST * STG * KS];  // chunks of gathered rows (KS > 1: one stage per wave)
+    constexpr int WSTG = (HPW == 1 && OTILE > STG) ? OTILE : NST * STG;               // ... of the stages of one share of the chunks
+    static_assert(HPW == 1 || OTILE <= STG, "with two heads per workgroup a wave's output tile is staged in one gather stage");
+    __shared__ __attribute__((aligned(16))) char stage_all[WSTG * KS];       // chunks of gathered rows (KS > 1: one stage per wave)
     __shared__ __attribute__((aligned(16))) char Pl_all[NW * PLB]; // codes, [plane][slot][8 rows], per wave
     __shared__ __attribute__((aligned(8))) char zeros[72];                     // row operand of the MFMA rows that carry no codes
     __shared__ int xch[2][HPW][KS][8];                                        // row maxima / row sums of the KS waves of a head
@@ -139,7 +138,7 @@ void attention_fused_kernel(AttnArgs a)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = (HPW > 1) ? wave % HPW : 0;  // head within the workgroup
     const int ks = (KS > 1) ? wave / HPW : 0;  // share of the panel's chunks
-    char *stage = stage_all + ks * (NST * STG);
+    char *stage = stage_all + ks * WSTG;
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
     // Workgroups are handed to the 8 XCDs round-robin by linear id.  1, 2, 4 or 8 (head group, batch item) pairs are worked on
@@ -174,7 +173,7 @@ void attention_fused_kernel(AttnArgs a)
     if (PB == 8 && lane < 18) reinterpret_cast<int *>(zeros)[lane] = 0; // every wave writes the same zeros: no race that matters
     if (PAD) {
         // the places of the pieces a row does not have: zero once, never written again
-        for (int i = threadIdx.x; i < NST * STG * KS / 16; i += 64 * NW) reinterpret_cast<v4i *>(stage_all)[i] = (v4i){0, 0, 0, 0};
+        for (int i = threadIdx.x; i < WSTG * KS / 16; i += 64 * NW) reinterpret_cast<v4i *>(stage_all)[i] = (v4i){0, 0, 0, 0};
         __syncthreads(); // (waits for the writes, too: the copies below must land after them)
     }
 
@@ -414,7 +413,6 @@ void attention_fused_kernel(AttnArgs a)
     // lanes 2t and 2t+1 supply the 8-byte pieces that end up in MFMA rows 0..7 and 8..15: the
     // codes and 8 zero bytes (PB 8; they do not move from chunk to chunk), or the high and the low plane of the codes (PB 16)
     const char *paddr = (PB == 8 && (src & 1)) ? zeros : Pl + slot0 * 8 + (src & 1) * PSTRIDE;
-    const int pstep = (SMALLP || (PB == 8 && (src & 1))) ? 0 : 512;
     char *const code_at = Pl + ((g >> 1) * 16 + j) * 8 + 4 * (g & 1); // codes of tile pair pr: 256 * pr on
     // p / s_p stays within the largest code unless s_p is below its reciprocal
     const bool cap = a.inv_s_p > (PB == 8 ? 127.f : 32639.f);
@@ -438,7 +436,7 @@ void attention_fused_kernel(AttnArgs a)
                         y[r] = x[2 * c + pr][r] * rinv[r];
                         if (CAP) y[r] = fminf(y[r], PB == 8 ? 127.f : 32639.f);
                     }
-                    char *to = code_at + (SMALLP ? 0 : c * 512) + pr * 256;
+                    char *to = code_at + pr * 256;
                     if (PB == 8) {
                         // v_cvt_pk_u8_f32 rounds to nearest even and drops the byte into place
                         unsigned packed = 0;
@@ -466,8 +464,7 @@ void attention_fused_kernel(AttnArgs a)
             else make_codes(std::false_type{});
             acquire(Vg, gc, (c + 1) % NST);
             // the codes, transposed to the MFMA row operand: row j < 8, slots g*16 .. +15
-            const char *pa = paddr + c * pstep;
-            const v2i p0 = lds_read_tr8(pa), p1 = lds_read_tr8(pa + 64);
+            const v2i p0 = lds_read_tr8(paddr), p1 = lds_read_tr8(paddr + 64);
             v2i d[NCT][2];
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
@@ -476,6 +473,7 @@ void attention_fused_kernel(AttnArgs a)
                 else d[ct][1] = lds_read_tr8(vaddr[ct] + (c % NST) * STG + ROWS8);
             }
             release(Vg, gc);
+            if (HPW == 1) asm volatile("" ::: "memory"); // (the next chunk's codes go where this one's were read)
             const v4i aop = {p0.x, p0.y, p1.x, p1.y};
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
@@ -491,13 +489,13 @@ void attention_fused_kernel(AttnArgs a)
         }
     });
 
-    // ---- output: 8 x DK tile through this wave's code area, scaled, 16-byte stores -------------
+    // ---- output: 8 x DK tile through this wave's stage, scaled, 16-byte stores -------------
     vm_wait<0>();
-    if (OSTAGE) lgkm_wait();
-    if (SMALLP) {
+    lgkm_wait();
+    if (HPW == 2) {
         __builtin_amdgcn_s_barrier(); // nobody reads the stages any more: each wave takes one for its tile
     }
-    int *Ol = reinterpret_cast<int *>(OSTAGE ? stage_all + (ks * NST + w) * STG : Pl); // SMALLP: NST == HPW stages per pair
+    int *Ol = reinterpret_cast<int *>(stage_all + ks * WSTG + w * STG); // (HPW 2: as many stages as waves)
     if (g < 2 || PB == 16) {
 #pragma unroll
         for (int ct = 0; ct < NO; ++ct)
@@ -512,7 +510,7 @@ void attention_fused_kernel(AttnArgs a)
     if (KS > 1) __syncthreads(); else __builtin_amdgcn_wave_barrier();
     // the tile of wave k of this wave's head, and this thread's number among the 64 * KS threads of the head
     auto partial_tile = [&](int k) -> const int * {
-        return reinterpret_cast<const int *>(OSTAGE ? stage_all + (k * NST + w) * STG : Pl_all + k * PLB);
+        return reinterpret_cast<const int *>(stage_all + k * WSTG + w * STG);
     };
     const int tih = ks * 64 + lane;
     if (a.out_f16) {

@@ -8,7 +8,7 @@ template <int PB, int QB, int DK> hipError_t launch_padded(const AttnArgs &a, in
 {
     switch (waves_per_panel) {
     case 8:
-        if constexpr (DK == 192) return hipErrorInvalidValue; // (its eight stages and code areas would not fit LDS)
+        if constexpr (DK == 192) return hipErrorInvalidValue; // (such panels go to the pipeline)
         else return launch_pairs<1, PB, QB, 8, DK, true>(a, s);
     case 4: return launch_pairs<1, PB, QB, 4, DK, true>(a, s);
     case 2: return launch_pairs<1, PB, QB, 2, DK, true>(a, s);
