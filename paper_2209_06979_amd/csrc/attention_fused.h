@@ -239,11 +239,13 @@ void attention_fused_kernel(AttnArgs a)
         });
         ixn = load_idx((c + KS < nch) ? c + KS : c);
     };
+    ixv_t ix_first = {};                           // the first chunk's indices, for K and V
+    if (nloc > 0) ix_first = load_idx(ks);
     auto start_pipeline = [&](const uint8_t *base) {
         lgkm_wait();                               // no read of the stage is still in flight
         if (HPW > 1) __builtin_amdgcn_s_barrier(); // both waves are done with the stages
         if (nloc > 0) {
-            ixn = load_idx(ks);
+            ixn = ix_first;
             issue(base, ks, 0);
         }
     };
