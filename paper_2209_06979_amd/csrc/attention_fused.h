@@ -71,6 +71,14 @@ __device__ __forceinline__ float row16_sum(float v)
     return v;
 }
 
+// the values that lanes l and l + 32 hold, in both (in registers; through LDS the two exchanges of the softmax cost a round trip each)
+__device__ __forceinline__ void both_halves(unsigned v, unsigned &lo, unsigned &hi)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    lo = s[0];
+    hi = s[1];
+}
+
 // MAXCH: longest panel in chunks of 64 vectors.  HPW: heads (= waves) per workgroup.
 // PB: bits of the re-quantised softmax output.  16 ("16b-8b" layer): the code c <= 32639 is split
 // into signed bytes c = 256*hi + lo (Section 4.4); the hi codes feed MFMA rows 0..7 and the lo
@@ -336,8 +344,9 @@ void attention_fused_kernel(AttnArgs a)
     float m2[4], srow[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        imax[r] = row16_imax(imax[r]);
-        imax[r] = max(imax[r], __shfl_xor(imax[r], 32, 64));
+        unsigned lo, hi;
+        both_halves((unsigned)row16_imax(imax[r]), lo, hi);
+        imax[r] = max((int)lo, (int)hi);
     }
     if (KS > 1) { // row 4*(g&1) + r: lanes 0 and 16 publish, everybody reads all waves
         if (lane == 0 || lane == 16) {
@@ -379,8 +388,9 @@ void attention_fused_kernel(AttnArgs a)
     float rinv[4]; // p / s_p = e * (1 / (sum * s_p)): one division per row instead of one per entry
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        srow[r] = row16_sum(srow[r]);
-        srow[r] += __shfl_xor(srow[r], 32, 64);
+        unsigned lo, hi;
+        both_halves(__builtin_bit_cast(unsigned, row16_sum(srow[r])), lo, hi);
+        srow[r] = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
     }
     if (KS > 1) { // every wave adds the partial sums in the same order: identical totals everywhere
         if (lane == 0 || lane == 16) {
@@ -395,8 +405,14 @@ void attention_fused_kernel(AttnArgs a)
             for (int k = 0; k < KS; ++k) srow[r] += __builtin_bit_cast(float, xch[1][w][k][4 * (g & 1) + r]);
         }
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) rinv[r] = a.inv_s_p / srow[r];
+    {   // one division per lane, of the row that its place in a group of four names
+        const float s01 = (lane & 1) ? srow[1] : srow[0], s23 = (lane & 1) ? srow[3] : srow[2];
+        const int q = __builtin_bit_cast(int, a.inv_s_p / ((lane & 2) ? s23 : s01));
+        rinv[0] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, q, 0x00, 0xF, 0xF, false)); // quad_perm [0,0,0,0]
+        rinv[1] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, q, 0x55, 0xF, 0xF, false));
+        rinv[2] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, q, 0xAA, 0xF, 0xF, false));
+        rinv[3] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, q, 0xFF, 0xF, 0xF, false));
+    }
     // ---- phase V: O = codes * V ------------------------------------------------------------------
     v4i o[NO];
 #pragma unroll
