@@ -79,6 +79,8 @@ __device__ __forceinline__ void both_halves(unsigned v, unsigned &lo, unsigned &
     hi = s[1];
 }
 
+constexpr unsigned PAIR_ROWS_Y = 32768; // rows of the grid along y, the rest of them along z
+
 // MAXCH: longest panel in chunks of 64 vectors.  HPW: heads (= waves) per workgroup.
 // PB: bits of the re-quantised softmax output.  16 ("16b-8b" layer): the code c <= 32639 is split
 // into signed bytes c = 256*hi + lo (Section 4.4); the hi codes feed MFMA rows 0..7 and the lo
@@ -155,7 +157,10 @@ void attention_fused_kernel(AttnArgs a)
     // otherwise fetch while another XCD fetches it, too.  (By itself, neighbouring pairs at the same time and as it is: 8 x 8 heads x 1800, 87 %
     // empty, 8-bit codes and inputs, dk = 32 36.6 -> 33.9 us, 48 60.2 -> 41.6, 80 61.8 -> 55.4, 96 63.1 -> 59.0, 128 52.4 -> 50.3.)
     const int groups = a.heads / HPW;
-    const int grid_row = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+    // (all of the first line of arguments in one round trip, not one by one as they come to be needed)
+    asm volatile("" ::"s"(a.panel_ptr), "s"(a.slot_idx), "s"(a.panel_list), "s"(a.heads), "s"(a.batch), "s"(a.pair_shift), "s"(a.pair_rows),
+                 "s"(a.Km), "s"(a.in_token_stride), "s"(a.in_head_stride), "s"(a.Q));
+    const int grid_row = (int)(blockIdx.z * PAIR_ROWS_Y + blockIdx.y);
     if (grid_row >= a.pair_rows) return;
     const int pair = (int)(blockIdx.x & ((1u << a.pair_shift) - 1)) * a.pair_rows + grid_row;
     int hgrp = pair, item = 0;
@@ -608,7 +613,7 @@ template <int HPW, int PB, int QB, int KS, int DK, bool PAD> hipError_t launch_p
     const int row = HPW * (PAD ? a.real_pieces * 16 : DK * QB / 8), lines = (row + 127) / 128 * 128; // (the L2 holds lines of 128 bytes)
     a.pair_shift = pairs_at_a_time(pairs, 2.0 * a.tokens * (a.in_token_stride < lines ? (double)a.in_token_stride : lines), (double)a.index_bytes);
     a.pair_rows = (int)(pairs >> a.pair_shift);
-    const unsigned rows = (unsigned)a.pair_rows, y = rows < 32768 ? rows : 32768;
+    const unsigned rows = (unsigned)a.pair_rows, y = rows < PAIR_ROWS_Y ? rows : PAIR_ROWS_Y;
     return launch_kernel((attention_fused_kernel<8, HPW, PB, QB, KS, DK, PAD>), dim3((unsigned)a.P << a.pair_shift, y, (rows + y - 1) / y),
                        dim3(64 * HPW * KS), 0, s, a);
 }

@@ -263,24 +263,27 @@ struct ValuesArgs {
 // Fused attention (attention_fused.h).  Element (head h, token l, d) of Q, Km, Vm (8- or 4-bit)
 // and O (fp32) sits at h*head_stride + l*token_stride + d.
 struct AttnArgs {
+    // what a wave needs first, in one line of 64 bytes
     const int32_t *panel_ptr;
     const int32_t *slot_idx;
-    const uint8_t *Q, *Km, *Vm;
+    const int32_t *panel_list;               // the panels of this launch (null: 0 .. P-1)
+    int heads, batch;
+    int pair_shift, pair_rows;               // set by the launcher: log2 of the (head group, batch item) pairs of a grid row; rows of the grid
+    const uint8_t *Km;
+    int64_t in_token_stride, in_head_stride; // bytes of Q, Km, Vm
+    const uint8_t *Q, *Vm;
+    int64_t in_batch_stride;                 // between batch items: bytes of Q, Km, Vm
     float *O;                                // fp32, or half when out_f16 is set
     int64_t head_stride, token_stride;       // elements of O
-    int64_t in_head_stride, in_token_stride; // bytes of Q, Km, Vm
-    int64_t batch_stride, in_batch_stride;   // between batch items: elements of O, bytes of Q, Km, Vm
+    int64_t batch_stride;
     float score_scale, inv_s_p, out_scale;
-    int P, heads, batch;                     // P: panels of this launch
-    const int32_t *panel_list;               // their numbers (null: 0 .. P-1)
     int out_f16;                             // 1: O holds fp16 (the fp32 result rounded to nearest even)
-    int tokens;                              // rows of Km and Vm
-    int64_t index_bytes;                     // column indices of this launch's panels
-    int pair_shift;                          // log2 of the (head group, batch item) pairs of a grid row (set by the launcher)
-    int pair_rows;             // filled by the launcher: rows of the grid, pairs >> pair_shift
     // head dimensions below the kernel's tile (launch_attention_fused_padded): 16-byte pieces a Q / Kmat / V row
     // really has, and columns of O
     int real_pieces, out_cols;
+    // for the launcher: panels, rows of Km and Vm, column indices of this launch's panels
+    int P, tokens;
+    int64_t index_bytes;
 };
 
 hipError_t launch_spmm(mc_prec prec, const SpmmArgs &a, int bnb, int waves, hipStream_t s);
