@@ -172,6 +172,7 @@ __device__ __forceinline__ void store_pair(const SddmmArgs &a, int64_t out0, int
 template <int PB, int LPR, bool DQ, bool U, bool SHORT>
 __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
 {
+    mcu::request_arguments(a);
     constexpr int RB = LPR * 16, NI = (LPR == 4) ? 4 : (LPR == 64 ? 16 : 8), RPI = 64 / LPR, UNIT = NI * RPI, TILES = UNIT / 16;
     constexpr int KC = RB / StepBytes<PB>::value;
     constexpr int SW = (LPR < 16) ? LPR : 16;       // pieces of a row that the swizzle permutes
@@ -350,6 +351,7 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
 template <int WK, bool DQ, bool U>
 __global__ __launch_bounds__(64 * WK) void sddmm_nib32_kernel(SddmmArgs a)
 {
+    mcu::request_arguments(a);
     constexpr int RB = 32;
     __shared__ __attribute__((aligned(16))) char lds[WK * 64 * RB];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -421,6 +423,7 @@ __global__ __launch_bounds__(64 * WK) void sddmm_nib32_kernel(SddmmArgs a)
 template <int PB, int KC, bool DQ>
 __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_direct_kernel(SddmmArgs a)
 {
+    mcu::request_arguments(a);
     constexpr int STEP = StepBytes<PB>::value, LANEB = STEP / 4; // bytes per step / per lane and step
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, g = lane >> 4;

@@ -44,6 +44,7 @@ constexpr int STAGES = 4;
 template <int PL, bool R4, int NT, int RF, int WR, int W, int AH>
 __global__ __launch_bounds__(64 * W, PL == 1 && NT == 4 && RF == 2 ? 4 : 1) void spmm_dense_kernel(DenseArgs a)
 {
+    mcu::request_arguments(a);
     constexpr int WK = W / WR, NP = WK * NT / W, STAGE = WK * NT * 1024, OWN = RF * NT / WK;
     static_assert(NP >= 1 && NP * W == WK * NT && OWN >= 1 && OWN * WK == RF * NT, "whole pieces per thread, whole tiles per wave");
     static_assert(AH % STAGES == 0, "stage numbers repeat with the unrolled loop");

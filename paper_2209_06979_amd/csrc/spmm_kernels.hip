@@ -110,6 +110,7 @@ template <bool TR> struct PhaseClock {
 template <int BNB, int WK, int LB, int RB, bool U = false, int NS = 1, bool TR = false>
 __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
 {
+    mcu::request_arguments(a);
     using Cfg = SpmmCfg<BNB, WK, LB, RB, U, NS>;
     PhaseClock<TR> clk;
     clk.stamp(0);                                        // the wave has started
