@@ -15,7 +15,8 @@
 // Whole calls, against the faster of the gather form and of the form with blocks of 1024 rows and separate filling waves that
 // this one replaced, and the kernel by itself in its two and the gather form on the operand as given / merged:
 //   16384 x 4096, 90 % empty, V = 8, N = 1024, fp16 out   58.0 -> 33.3 us    34.4 / 33.9 against 57.8 / 55.9
-//   4096 x 4096, half empty, V = 2, N = 512               22.6 -> 20.5       50.6 / 20.3 against 103.8 / 30.1
+//   4096 x 4096, half empty, V = 2, N = 512               22.6 -> 20.5       50.6 / 20.3 against 103.8 / 30.1   (calls now take the form of
+//                                                         spmm_dense_kernels.hip there, 15.4)
 //   3004 x 2900, 85 % empty, unequal panels, 16 x 8 bit   16.2 -> 10.3       10.1 - 11.1 / 10.1 - 10.6 against 11.9 / 12.2
 // Three things keep the LDS reads at their full rate (190 bytes per clock and compute
 // unit measured, random rows reach 81):

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("many", [False, True])              # at most 512 panels in all score sets, or more
-@pytest.mark.parametrize("scores", [512, 1024, 2048, 4096, 8192, 16384])
+@pytest.mark.parametrize("scores", [512, 1024, 2048, 3072, 4096, 8192, 16384])
 @pytest.mark.parametrize("V", [2, 4, 8])
 def test_lengths_where_the_kernel_changes(V, scores, many):
     """The longest panel at a limit and one vector beyond it (a panel is padded to 64 vectors)."""
@@ -25,7 +25,7 @@ def test_lengths_where_the_kernel_changes(V, scores, many):
 
 
 @pytest.mark.parametrize("bits", [8, 16])
-@pytest.mark.parametrize("scores", [512, 1024, 2048, 4096, 8192, 16384, 16385])
+@pytest.mark.parametrize("scores", [512, 1024, 2048, 3072, 4096, 8192, 16384, 16385])
 @pytest.mark.parametrize("V,P", [(2, 64), (4, 600), (8, 64), (8, 600)])
 def test_device_format_of_every_kernel(V, P, scores, bits):
     import torch
