@@ -132,7 +132,7 @@ def main():
                          "against every pinned tile / wave variant")
     ap.add_argument("--forms", type=int, default=0, metavar="N",
                     help="instead of the step: the SpMM on N drawn operands (all precisions, all sizes, equal and "
-                         "unequal panels) in each of its four forms, beside the time that the library's choice expects of it")
+                         "unequal panels) in each of its five forms, beside the time that the library's choice expects of it")
     ap.add_argument("--waves", action="store_true",
                     help="instead of the step: the SDDMM's automatic number of waves per panel against every pinned one")
     ap.add_argument("--table", action="store_true",
@@ -635,8 +635,8 @@ def draw_operand(rng):
 
 
 def run_forms(mc, torch, count):
-    """The SpMM on drawn operands: each of its four forms -- rows of B gathered per stored vector or resident in LDS, on
-    the operand as given or on its merged copy -- timed beside the time that the library's choice expects of it, and what the
+    """The SpMM on drawn operands: each of its five forms -- rows of B gathered per stored vector or resident in LDS, on
+    the operand as given or on its merged copy, and the operand with all its columns -- timed beside the time that the library's choice expects of it, and what the
     choice loses over the fastest.  Three copies of everything are visited in turn, as a program's operands alternate (an XCD's L2
     then holds small ones only).  `chunks` / `longest` and their merged counterparts are the operand's chunks of 64 vectors
     and those of its longest panel."""
