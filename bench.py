@@ -645,7 +645,7 @@ def run_forms(mc, torch, count):
     stream = torch.cuda.Stream()
     pins = {"gather": mc.Options(spmm_slab=-1, spmm_merge=-1), "lds": mc.Options(spmm_slab=1, spmm_merge=-1),
             "m_gather": mc.Options(spmm_slab=-1, spmm_merge=1), "m_lds": mc.Options(spmm_slab=1, spmm_merge=1),
-            "dense": mc.Options()}
+            "dense": mc.Options(spmm_merge=mc.SPMM_DENSE)}
     rows = []
     chunks = lambda rp: (np.diff(rp) + 63) // 64
     with torch.cuda.stream(stream):
@@ -661,12 +661,10 @@ def run_forms(mc, torch, count):
             n = len(ci)
             vals = (wl.uniform_packed_int4((n, Vv // 2), i) if lhs == 4 else wl.uniform_int8((n, Vv), i) if lhs == 8 else
                     wl.uniform_int16((n, Vv), i, -2048, 2047))
-            mc.set_thread_options(mc.Options(spmm_slab=1, spmm_merge=1))   # (all copies, whether they would be built or not)
-            mc.set_spmm_dense(1)
+            mc.set_thread_options(mc.Options(spmm_slab=1, spmm_merge=mc.SPMM_DENSE)) # (all copies, whether they would be built or not)
             As = [mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs) for _ in range(3)]
             A = As[0]
             mc.set_thread_options(None)
-            mc.set_spmm_dense(0)
             own = mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs)           # (the copies that are built by themselves)
             Bs = [torch.randint(0, 256, (Ks, row_bytes), device="cuda", dtype=torch.uint8) for _ in As]
             Bs = Bs if rhs == 4 else [B.view(torch.int8 if rhs == 8 else torch.int16) for B in Bs]
@@ -687,10 +685,8 @@ def run_forms(mc, torch, count):
             for k, (f, o) in enumerate(pins.items()):
                 if (f[0] == "m" and not A.merge_group) or (rhs == 16 and f[-3:] in ("lds", "nse")):
                     continue
-                mc.set_spmm_dense(1 if f == "dense" else -1)
                 us[f] = time_graph(torch, stream, [launch(r % 3, o) for r in range(reps)], rounds=3, warm_ms=0.0 if k else 15.0)
                 want[f] = mc.spmm_form_us(A, N, prec, out, o)
-                mc.set_spmm_dense(0)
             auto = mc.spmm_form(own, N, prec)
             auto = ("m_" if mc.spmm_on_merged(own, N, prec) and auto != "dense" else "") + auto
             merged = mc.merge_host(Ms, Ks, Vv, lhs, rp, ci, None, A.merge_group)[0] if A.merge_group else None

@@ -114,8 +114,14 @@ typedef struct mc_options {
     int spmm_merge;          /* the SpMM on the operand's merged copy (see mc_merge_host): 0 automatic (when
                                 the copy exists and is expected to be faster), -1 never (also: mc_mat_create on
                                 this thread does not build the copy), 1 whenever the copy exists (and
-                                mc_mat_create on this thread builds it whatever the shape)                  */
+                                mc_mat_create on this thread builds it whatever the shape); 1 and -1 also leave
+                                out the copy with all columns (see mc_set_spmm_dense).  MC_SPMM_DENSE: the
+                                latter wherever it exists and the call can use it, MC_SPMM_DENSE + 1 + t in the
+                                kernel's tile shape t = 0 .. 5, largest first (mc_mat_create on this thread builds both
+                                copies whatever the shape); -MC_SPMM_DENSE: never (nor built), the other
+                                forms automatic                                                            */
 } mc_options;
+#define MC_SPMM_DENSE 16
 /* Sets every field to automatic. */
 void mc_options_init(mc_options *o);
 /* Defaults of the CALLING THREAD for entry points that take no options argument (NULL: back to
@@ -281,7 +287,8 @@ int mc_spmm_ex(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec,
 /* Which form mc_spmm_ex would run for this operand, width and options (host only, launches nothing):
  * bit 0: 0 = rows of B gathered per stored vector, 1 = rows of B resident in LDS; bit 1 (value 2): on merged
  * panels (see mc_merge_host); bit 2 (value 4, and value 2 where the operand has merged panels): on the copy that
- * holds blocks of 16 rows with all their columns (see mc_set_spmm_dense).  Negative: an error code. */
+ * holds blocks of 16 rows with all their columns (see mc_set_spmm_dense).  options == NULL: the calling thread's
+ * defaults, as mc_spmm takes them.  Negative: an error code. */
 int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_options *options);
 /* Measurement aid: the time in us that this choice expects of the form it takes (results of out_bytes = 2 or 4
  * bytes; the options can pin each form in turn).  Negative: an error code. */
@@ -537,9 +544,9 @@ int mc_set_spmm_splitting(int enable);
 /* The SpMM form for patterns whose blocks of 16 rows name nearly every column: mc_mat_create then also stores
  * the operand with all its columns (M * K bytes, twice that for 16- and 12-bit values), zeros where nothing is
  * stored, and calls without unsigned flags, with an 8- or 4-bit B and no other option pinned choose that form
- * where it is expected to be the fastest.  For the calling thread, tests and measurements: mode 0 automatic,
- * -1 never (nor built by mc_mat_create on this thread), 1 wherever it exists (and built whatever the pattern);
- * tile -1 automatic, 0 .. 5 one of the kernel's tile shapes, largest first.  MC_EINVAL otherwise. */
+ * where it is expected to be the fastest.  Sets spmm_merge of the thread's options: mode 1 to MC_SPMM_DENSE (tile -1)
+ * or MC_SPMM_DENSE + 1 + tile (0 .. 5); -1 to -MC_SPMM_DENSE and 0 to 0, where it does not pin the merged copy or its
+ * absence (the tile counts with mode 1 only).  MC_EINVAL otherwise. */
 int mc_set_spmm_dense(int mode, int tile);
 /* (The switch also governs the work items of mc_sddmm.  There every item writes its own outputs,
  * so a pattern-only mask is cut finer: into pieces of at most the average panel length, at least

@@ -46,6 +46,9 @@ class MergedLayout(ctypes.Structure):
     _fields_ = [("group", c_int32), ("P", c_int32), ("nvec", c_int64)]
 
 
+SPMM_DENSE = 16  # spmm_merge: the copy with all columns (+ 1 + t: in tile shape t; negative: never)
+
+
 class Options(ctypes.Structure):
     """mc_options: kernel-variant choices of one call; all zero = automatic."""
     _fields_ = [("spmm_row_tile_bytes", c_int), ("spmm_waves", c_int), ("spmm_stages", c_int), ("spmm_splitting", c_int),
@@ -352,8 +355,8 @@ def set_attention_mode(mode: int = 0) -> None:
 
 
 def spmm_form(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> str:
-    """The form mc_spmm_ex would take for this operand: "gather", "lds" (rows of B resident in LDS) or
-    "dense" (the operand held with all its columns)."""
+    """The form spmm would take for this operand and these options (None: the calling thread's): "gather", "lds" (rows of B
+    resident in LDS) or "dense" (the operand held with all its columns)."""
     r = lib.mc_spmm_form(A.handle, N, PREC[prec], ctypes.byref(options) if options is not None else None)
     if r < 0:
         _check(r, "mc_spmm_form")
@@ -369,7 +372,7 @@ def spmm_form_us(A: SparseMatrix, N: int, prec: str, out_bytes: int = 4, options
 
 
 def spmm_on_merged(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> bool:
-    """Whether mc_spmm_ex would run on the operand's merged copy (panels sharing the MFMA's 16 rows)."""
+    """Whether spmm would run on the operand's merged copy (panels sharing the MFMA's 16 rows)."""
     r = lib.mc_spmm_form(A.handle, N, PREC[prec], ctypes.byref(options) if options is not None else None)
     if r < 0:
         _check(r, "mc_spmm_form")

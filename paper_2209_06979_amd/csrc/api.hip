@@ -16,9 +16,10 @@ namespace {
 // options it was handed or these once, at entry, and never looks at shared state afterwards.
 thread_local mc_options t_options = {};
 
-// The calling thread's choice for the SpMM form that holds an operand with all its columns (mc_set_spmm_dense).
-struct DenseChoice { int mode, tile; }; // mode 0 automatic, -1 never, 1 wherever it exists; tile -1 automatic
-thread_local DenseChoice t_dense = {0, -1};
+// The SpMM form that holds an operand with all its columns, as spmm_merge asks for it: 0 automatic, -1 never (also where another
+// copy is pinned), 1 wherever it exists; then the tile shape, or -1.
+int dense_mode(const mc_options &o) { return o.spmm_merge >= MC_SPMM_DENSE ? 1 : o.spmm_merge == 0 ? 0 : -1; }
+int dense_tile(const mc_options &o) { return o.spmm_merge > MC_SPMM_DENSE ? o.spmm_merge - MC_SPMM_DENSE - 1 : -1; }
 
 bool valid_options(const mc_options &o)
 {
@@ -33,7 +34,8 @@ bool valid_options(const mc_options &o)
     if (d != 0 && d != -1 && d != 1 && d != 2 && d != 4 && d != 8) return false;
     if (o.softmax_variant < 0 || o.softmax_variant > 2) return false;
     if (o.attention_mode < 0 || o.attention_mode > 6) return false;
-    if (o.spmm_merge < -1 || o.spmm_merge > 1) return false;
+    const int m = o.spmm_merge;
+    if ((m < -1 || m > 1) && m != -MC_SPMM_DENSE && (m < MC_SPMM_DENSE || m > MC_SPMM_DENSE + DENSE_TILES)) return false;
     return true;
 }
 
@@ -274,8 +276,10 @@ extern "C" int mc_set_spmm_splitting(int enable)
 extern "C" int mc_set_spmm_dense(int mode, int tile)
 {
     if (mode < -1 || mode > 1 || tile < -1 || tile >= DENSE_TILES) return MC_EINVAL;
-    t_dense = {mode, tile};
-    return MC_OK;
+    return set_field([&](mc_options &o) {
+        if (mode == 1) o.spmm_merge = MC_SPMM_DENSE + 1 + tile;
+        else if (o.spmm_merge != -1 && o.spmm_merge != 1) o.spmm_merge = mode == -1 ? -MC_SPMM_DENSE : 0; // (a pin of the other copies stays)
+    });
 }
 
 extern "C" int mc_set_sddmm_variant(int waves)
@@ -402,7 +406,7 @@ bool dense_possible(int M, int K, int bits)
 // rows, 512 .. 8192 columns, rows of B of 32 .. 1024 bytes): off by 2 - 7 % in the median and by 6 - 24 % in nine cases of ten; the tile
 // picked is 0.5 % slower than the best on average, 25 % at worst, and where the time expected is 3 % below the measured one of the other
 // forms (237 of the 900) the call is 1.2 times as fast in the mean.
-DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_bytes)
+DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_bytes, int only = -1)
 {
     struct Cost { double start, step, stream, store, tile; };
     static const Cost cost[2][2][DENSE_TILES] =
@@ -413,7 +417,7 @@ DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_byt
     const int planes = bits > 8 ? 2 : 1, cols = row_bytes * (r4 ? 2 : 1), chunks = (K + MC_CHUNK - 1) / MC_CHUNK;
     DensePlan best = {-1, 1e30};
     for (int tile = 0; tile < DENSE_TILES; ++tile) {
-        if (t_dense.tile >= 0 && tile != t_dense.tile) continue;
+        if (only >= 0 && tile != only) continue;
         const Cost &c = cost[planes - 1][r4][tile];
         const int rows = dense_tile_rows(tile, planes), turn = dense_tile_turn(tile), share = dense_tile_share(tile);
         const int at_once = tile == 5 ? 4 : tile == 3 || (tile == 2 && planes == 1) ? 2 : 1; // workgroups of a compute unit
@@ -661,7 +665,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         const int rows = (lhs_bits == 4 || lhs_bits == 8) ? 16 : 8, group = rows / V;
         mc_merged_layout ml;
         if (group >= 2 && mc_merged_query(M, K, V, lhs_bits, row_ptr, col_idx, group, &ml) == MC_OK && ml.nvec > 0 &&
-            (t_options.spmm_merge == 1 || merged_worth_building(lay, ml))) {
+            (t_options.spmm_merge == 1 || t_options.spmm_merge >= MC_SPMM_DENSE || merged_worth_building(lay, ml))) {
             std::vector<int32_t> m_row_ptr, m_col_idx;
             std::vector<uint8_t> m_values;
             const int64_t vb = (int64_t)V * (lhs_bits == 12 ? 16 : lhs_bits) / 8;
@@ -689,7 +693,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         }
     }
     // (a thread that pins or forbids the other copies gets those and no others)
-    const bool dense_allowed = t_dense.mode == 1 || (t_dense.mode == 0 && t_options.spmm_merge == 0 && t_options.spmm_slab == 0);
+    const bool dense_allowed = dense_mode(t_options) == 1 || (dense_mode(t_options) == 0 && t_options.spmm_slab == 0);
     const bool dense_rival = dense_allowed && dense_possible(M, K, lhs_bits);
     // LDS-ordered copy for the SpMM that keeps rows of B resident in LDS, where that form is expected to be the fastest one
     // for some width of B (the merged copy's forms included), unless the thread's options rule that kernel out (1: built whatever the shape, so that the
@@ -736,7 +740,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         }
     }
     // The operand with all its columns, where that form is expected to be the fastest for some width of B
-    const bool dense = !child && dense_rival && lay.nvec > 0 && (t_dense.mode == 1 || dense_worth_building(A));
+    const bool dense = !child && dense_rival && lay.nvec > 0 && (dense_mode(t_options) == 1 || dense_worth_building(A));
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define MC_TRY(call) (ok = ok && hip_ok((call), #call))
     bool ok = true;
@@ -919,16 +923,16 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, in
     const bool merged_possible = A->merged && A->merged_valid && o.spmm_merge != -1 && !(flags != 0 && A->merged->V > 8);
     SpmmForm f = {A, false, {}, -1};
     double best = 1e30;
-    if (A->d_dense && A->dense_valid && t_dense.mode != -1 && flags == 0 && rb != 16 && o.spmm_slab == 0 && o.spmm_merge == 0 &&
+    if (A->d_dense && A->dense_valid && dense_mode(o) != -1 && flags == 0 && rb != 16 && o.spmm_slab == 0 &&
         o.spmm_row_tile_bytes == 0 && o.spmm_waves == 0 && (A->K - 1) * ldb_bytes + row_bytes <= INT32_MAX && (A->K + 8192) * ldb_bytes <= UINT32_MAX) {
-        const DensePlan d = plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, out_bytes);
+        const DensePlan d = plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, out_bytes, dense_tile(o));
         if (d.tile >= 0) {
             f.dense = d.tile;
             // (its expected times and the others' were fitted apart.  Taken by 3 % or more: of 400 drawn operands 73 change their form and
             // run 1.22 times as fast in the mean, one in twenty of them 4 - 5 % slower; rows of less than 64 bytes by 15 %: their gather
             // is expected up to a fifth too slow)
             f.plan.us = d.us;
-            best = t_dense.mode == 1 ? 0.0 : d.us * (row_bytes < 64 ? 1.15 : 1.03);
+            best = dense_mode(o) == 1 ? 0.0 : d.us * (row_bytes < 64 ? 1.15 : 1.03);
         }
     }
     for (int m = (merged_possible && o.spmm_merge == 1) ? 1 : 0; m <= (merged_possible ? 1 : 0); ++m) {
@@ -1046,9 +1050,8 @@ extern "C" int mc_spmm_ex(const mc_mat *A, const void *B_dev, int N, int ldb, mc
 extern "C" int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_options *options)
 {
     if (!A || N <= 0 || !valid_prec((int)prec) || A->lhs_bits != lhs_bits_of(prec)) return MC_EINVAL;
-    const mc_options automatic = {};
     mc_options o;
-    if (resolve_options(options ? options : &automatic, &o) != MC_OK) return MC_EINVAL;
+    if (resolve_options(options, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
     const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, 4, 0u, o);
     return form.dense >= 0 ? 4 | (A->merged ? 2 : 0) : (form.slab ? 1 : 0) | (form.A != A ? 2 : 0);
@@ -1057,9 +1060,8 @@ extern "C" int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_optio
 extern "C" double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_bytes, const mc_options *options)
 {
     if (!A || N <= 0 || !valid_prec((int)prec) || A->lhs_bits != lhs_bits_of(prec) || (out_bytes != 2 && out_bytes != 4)) return MC_EINVAL;
-    const mc_options automatic = {};
     mc_options o;
-    if (resolve_options(options ? options : &automatic, &o) != MC_OK) return MC_EINVAL;
+    if (resolve_options(options, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
     const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, out_bytes, 0u, o);
     return form.slab || form.dense >= 0 ? form.plan.us : gather_us(form.A, N * rb / 8, rb, out_bytes, o);

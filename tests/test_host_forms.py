@@ -1,0 +1,79 @@
+"""Which form of the SpMM a call takes, by the options and copies it has: the library's host code without a GPU."""
+import threading
+
+import pytest
+
+from paper_2209_06979_amd import binding as mc
+import host_library as host
+
+# panels whose blocks of 16 rows name every column: the form on the copy with all columns, unasked
+DENSE = dict(M=2048, K=2048, V=2, empty=0.5)
+
+
+@pytest.fixture
+def A():
+    L = host.load()
+    L.mc_set_thread_options(None)
+    A = host.Mat(**DENSE)
+    yield A
+    A.close()
+    L.mc_set_thread_options(None)
+    assert L.host_live() == 0
+
+
+def test_thread_choice_of_the_copy_with_all_columns_is_an_option(A):
+    """It is seen, set and reset with the thread's other options, and calls with options of their own do not follow it."""
+    L = host.load()
+    o = mc.Options()
+    for mode, tile, want in ((1, -1, 16), (1, 0, 17), (1, 5, 22), (-1, -1, -16), (0, -1, 0)):
+        assert L.mc_set_spmm_dense(mode, tile) == 0
+        assert L.mc_get_thread_options(o) == 0 and o.spmm_merge == want
+    for mode, tile in ((2, -1), (-2, -1), (1, 6), (1, -2)):
+        assert L.mc_set_spmm_dense(mode, tile) == mc.MC_EINVAL
+    assert A.run(512)[0] == "dense" and A.form(512) == 6
+    L.mc_set_spmm_dense(-1, -1)
+    assert A.run(512)[0] != "dense" and A.form(512) < 4
+    assert A.run(512, ex=True)[0] == "dense" and A.run(512, mc.Options(), ex=True)[0] == "dense" and A.form(512, mc.Options()) == 6
+    L.mc_set_spmm_dense(1, 4)
+    assert A.run(512) == ("dense", 4)
+    assert A.run(512, ex=True) != ("dense", 4)                        # (the automatic tile is another one here)
+    assert L.mc_set_thread_options(None) == 0
+    assert A.run(512) == A.run(512, ex=True) != ("dense", 4)
+
+
+def test_every_value_of_the_option(A):
+    for tile in range(6):
+        assert A.run(512, mc.Options(spmm_merge=mc.SPMM_DENSE + 1 + tile), ex=True) == ("dense", tile)
+    assert A.run(512, mc.Options(spmm_merge=mc.SPMM_DENSE), ex=True)[0] == "dense"
+    assert A.form(512, mc.Options(spmm_merge=-mc.SPMM_DENSE)) < 4
+    assert A.form(512, mc.Options(spmm_merge=1)) in (2, 3) and A.form(512, mc.Options(spmm_merge=-1)) in (0, 1)
+    for bad in (-17, -15, -2, 2, 15, 23):
+        assert A.form(512, mc.Options(spmm_merge=bad)) == mc.MC_EINVAL
+    never = host.Mat(**DENSE, options=mc.Options(spmm_merge=-mc.SPMM_DENSE))
+    assert never.form(512) in (0, 1, 2, 3) and never.form(512, mc.Options(spmm_merge=mc.SPMM_DENSE)) < 4
+    assert never.form(512, mc.Options(spmm_merge=1)) & 2              # (the merged copy is there)
+    never.close()
+    small = host.Mat(64, 64, 8, 0.5, options=mc.Options(spmm_merge=mc.SPMM_DENSE))
+    assert small.form(64, mc.Options(spmm_merge=mc.SPMM_DENSE)) & 4   # built whatever the shape
+    small.close()
+
+
+def test_a_setter_leaves_the_pin_of_another_copy(A):
+    L = host.load()
+    o = mc.Options()
+    for pin in (1, -1):
+        for mode in (-1, 0):
+            L.mc_set_thread_options(mc.Options(spmm_merge=pin))
+            assert L.mc_set_spmm_dense(mode, -1) == 0
+            L.mc_get_thread_options(o)
+            assert o.spmm_merge == pin
+
+
+def test_another_thread_is_not_affected(A):
+    L = host.load()
+    L.mc_set_spmm_dense(-1, -1)
+    seen = []
+    t = threading.Thread(target=lambda: seen.append(A.run(512)[0]))
+    t.start()
+    t.join()
+    assert seen == ["dense"] and A.run(512)[0] != "dense"
