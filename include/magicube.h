@@ -287,8 +287,8 @@ int mc_spmm_ex(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec,
 /* Which form mc_spmm_ex would run for this operand, width and options (host only, launches nothing):
  * bit 0: 0 = rows of B gathered per stored vector, 1 = rows of B resident in LDS; bit 1 (value 2): on merged
  * panels (see mc_merge_host); bit 2 (value 4, and value 2 where the operand has merged panels): on the copy that
- * holds blocks of 16 rows with all their columns (see mc_set_spmm_dense).  options == NULL: the calling thread's
- * defaults, as mc_spmm takes them.  Negative: an error code. */
+ * holds blocks of 16 rows with all their columns (see mc_set_spmm_dense).  options == NULL: automatic, but for a
+ * choice that the calling thread has made with mc_set_spmm_dense.  Negative: an error code. */
 int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_options *options);
 /* Measurement aid: the time in us that this choice expects of the form it takes (results of out_bytes = 2 or 4
  * bytes; the options can pin each form in turn).  Negative: an error code. */

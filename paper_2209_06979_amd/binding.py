@@ -355,8 +355,8 @@ def set_attention_mode(mode: int = 0) -> None:
 
 
 def spmm_form(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> str:
-    """The form spmm would take for this operand and these options (None: the calling thread's): "gather", "lds" (rows of B
-    resident in LDS) or "dense" (the operand held with all its columns)."""
+    """The form mc_spmm_ex would take for this operand and these options (None: automatic, but for a choice made with
+    set_spmm_dense): "gather", "lds" (rows of B resident in LDS) or "dense" (the operand held with all its columns)."""
     r = lib.mc_spmm_form(A.handle, N, PREC[prec], ctypes.byref(options) if options is not None else None)
     if r < 0:
         _check(r, "mc_spmm_form")
@@ -372,7 +372,7 @@ def spmm_form_us(A: SparseMatrix, N: int, prec: str, out_bytes: int = 4, options
 
 
 def spmm_on_merged(A: SparseMatrix, N: int, prec: str, options: Options | None = None) -> bool:
-    """Whether spmm would run on the operand's merged copy (panels sharing the MFMA's 16 rows)."""
+    """Whether mc_spmm_ex would run on the operand's merged copy (panels sharing the MFMA's 16 rows)."""
     r = lib.mc_spmm_form(A.handle, N, PREC[prec], ctypes.byref(options) if options is not None else None)
     if r < 0:
         _check(r, "mc_spmm_form")

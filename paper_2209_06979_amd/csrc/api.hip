@@ -1047,11 +1047,23 @@ extern "C" int mc_spmm_ex(const mc_mat *A, const void *B_dev, int N, int ldb, mc
     return spmm_impl(A, B_dev, N, ldb, prec, flags, 0, 1.f, C_dev, ldc, options ? options : &automatic, stream);
 }
 
+namespace {
+// The options that mc_spmm_form is asked about: the caller's, else automatic ones as in mc_spmm_ex, but for a choice of the copy with all
+// columns that the thread has made (mc_set_spmm_dense).
+int form_options(const mc_options *given, mc_options *out)
+{
+    if (given) return resolve_options(given, out);
+    *out = mc_options{};
+    if (std::abs(t_options.spmm_merge) >= MC_SPMM_DENSE) out->spmm_merge = t_options.spmm_merge;
+    return MC_OK;
+}
+} // namespace
+
 extern "C" int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_options *options)
 {
     if (!A || N <= 0 || !valid_prec((int)prec) || A->lhs_bits != lhs_bits_of(prec)) return MC_EINVAL;
     mc_options o;
-    if (resolve_options(options, &o) != MC_OK) return MC_EINVAL;
+    if (form_options(options, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
     const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, 4, 0u, o);
     return form.dense >= 0 ? 4 | (A->merged ? 2 : 0) : (form.slab ? 1 : 0) | (form.A != A ? 2 : 0);
@@ -1061,7 +1073,7 @@ extern "C" double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_
 {
     if (!A || N <= 0 || !valid_prec((int)prec) || A->lhs_bits != lhs_bits_of(prec) || (out_bytes != 2 && out_bytes != 4)) return MC_EINVAL;
     mc_options o;
-    if (resolve_options(options, &o) != MC_OK) return MC_EINVAL;
+    if (form_options(options, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
     const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, out_bytes, 0u, o);
     return form.slab || form.dense >= 0 ? form.plan.us : gather_us(form.A, N * rb / 8, rb, out_bytes, o);

@@ -77,3 +77,14 @@ def test_another_thread_is_not_affected(A):
     t.start()
     t.join()
     assert seen == ["dense"] and A.run(512)[0] != "dense"
+
+
+def test_form_without_options_follows_no_other_default_of_the_thread(A):
+    """mc_spmm_form with no options is about mc_spmm_ex with none; of the thread's defaults it knows the copy with all columns only."""
+    L = host.load()
+    want = [A.form(N, mc.Options()) for N in (16, 64, 512)]
+    for o in (mc.Options(spmm_merge=-1), mc.Options(spmm_merge=1), mc.Options(spmm_slab=-1), mc.Options(spmm_waves=2)):
+        assert L.mc_set_thread_options(o) == 0
+        assert [A.form(N) for N in (16, 64, 512)] == want
+    L.mc_set_thread_options(mc.Options(spmm_merge=-mc.SPMM_DENSE, spmm_slab=-1))
+    assert [A.form(N) for N in (16, 64, 512)] == [A.form(N, mc.Options(spmm_merge=-mc.SPMM_DENSE)) for N in (16, 64, 512)]
