@@ -543,10 +543,12 @@ int mc_set_spmm_stages(int stages);
 int mc_set_spmm_splitting(int enable);
 /* The SpMM form for patterns whose blocks of 16 rows name nearly every column: mc_mat_create then also stores
  * the operand with all its columns (M * K bytes, twice that for 16- and 12-bit values), zeros where nothing is
- * stored, and calls without unsigned flags, with an 8- or 4-bit B and no other option pinned choose that form
- * where it is expected to be the fastest.  Sets spmm_merge of the thread's options: mode 1 to MC_SPMM_DENSE (tile -1)
- * or MC_SPMM_DENSE + 1 + tile (0 .. 5); -1 to -MC_SPMM_DENSE and 0 to 0, where it does not pin the merged copy or its
- * absence (the tile counts with mode 1 only).  MC_EINVAL otherwise. */
+ * stored, and calls without unsigned flags, with an 8- or 4-bit B and no other option of the SpMM pinned (spmm_stages 2
+ * and spmm_splitting 1 are no pins here) choose that form where it is expected to be the fastest; asked for, it is
+ * also taken beside spmm_stages, spmm_splitting, spmm_slab_waves and spmm_slab_panels, which it has no use for.
+ * Sets spmm_merge of the thread's options: mode 1 to MC_SPMM_DENSE (tile -1) or MC_SPMM_DENSE + 1 + tile (0 .. 5);
+ * -1 to -MC_SPMM_DENSE and 0 to 0, where it does not pin the merged copy or its absence (the tile counts with mode 1
+ * only).  MC_EINVAL otherwise. */
 int mc_set_spmm_dense(int mode, int tile);
 /* (The switch also governs the work items of mc_sddmm.  There every item writes its own outputs,
  * so a pattern-only mask is cut finer: into pieces of at most the average panel length, at least

@@ -19,6 +19,8 @@ thread_local mc_options t_options = {};
 // The SpMM form that holds an operand with all its columns, as spmm_merge asks for it: 0 automatic, -1 never (also where another
 // copy is pinned), 1 wherever it exists; then the tile shape, or -1.
 int dense_mode(const mc_options &o) { return o.spmm_merge >= MC_SPMM_DENSE ? 1 : o.spmm_merge == 0 ? 0 : -1; }
+// Whether options pin part of another form (spmm_stages = 2 and spmm_splitting = 1 are what an SpMM call does by itself).
+bool pins_other_form(const mc_options &o) { return o.spmm_stages == 1 || o.spmm_splitting == -1 || o.spmm_slab_waves != 0 || o.spmm_slab_panels != 0; }
 int dense_tile(const mc_options &o) { return o.spmm_merge > MC_SPMM_DENSE ? o.spmm_merge - MC_SPMM_DENSE - 1 : -1; }
 
 bool valid_options(const mc_options &o)
@@ -923,7 +925,8 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, in
     const bool merged_possible = A->merged && A->merged_valid && o.spmm_merge != -1 && !(flags != 0 && A->merged->V > 8);
     SpmmForm f = {A, false, {}, -1};
     double best = 1e30;
-    if (A->d_dense && A->dense_valid && dense_mode(o) != -1 && flags == 0 && rb != 16 && o.spmm_slab == 0 &&
+    const bool dense_wanted = dense_mode(o) == 1 || (dense_mode(o) == 0 && !pins_other_form(o));
+    if (A->d_dense && A->dense_valid && dense_wanted && flags == 0 && rb != 16 && o.spmm_slab == 0 &&
         o.spmm_row_tile_bytes == 0 && o.spmm_waves == 0 && (A->K - 1) * ldb_bytes + row_bytes <= INT32_MAX && (A->K + 8192) * ldb_bytes <= UINT32_MAX) {
         const DensePlan d = plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, out_bytes, dense_tile(o));
         if (d.tile >= 0) {

@@ -88,3 +88,26 @@ def test_form_without_options_follows_no_other_default_of_the_thread(A):
         assert [A.form(N) for N in (16, 64, 512)] == want
     L.mc_set_thread_options(mc.Options(spmm_merge=-mc.SPMM_DENSE, spmm_slab=-1))
     assert [A.form(N) for N in (16, 64, 512)] == [A.form(N, mc.Options(spmm_merge=-mc.SPMM_DENSE)) for N in (16, 64, 512)]
+
+
+@pytest.mark.parametrize("pin", [dict(spmm_stages=1), dict(spmm_splitting=-1), dict(spmm_slab_waves=8), dict(spmm_slab_panels=2),
+                                 dict(spmm_slab=-1), dict(spmm_row_tile_bytes=128), dict(spmm_waves=4)])
+def test_options_of_the_other_forms_rule_out_the_copy_with_all_columns(A, pin):
+    """What pins part of another form is run in one of them, unless the copy with all columns is asked for beside what it can ignore."""
+    L, o = host.load(), mc.Options(**pin)
+    kernel, detail = A.run(512, o, ex=True)
+    assert kernel != "dense" and A.form(512, o) < 4
+    assert kernel != "gather" or detail == pin.get("spmm_stages", 2)
+    L.mc_set_thread_options(o)
+    assert A.run(512)[0] == kernel
+    asked = A.run(512, mc.Options(spmm_merge=mc.SPMM_DENSE, **pin), ex=True)[0]
+    assert (asked == "dense") == (not pin.keys() & {"spmm_slab", "spmm_row_tile_bytes", "spmm_waves"})
+
+
+def test_options_that_say_what_is_automatic_are_no_pins(A):
+    """Two chunks in flight and the sharing of long panels are the defaults that the one-knob setters go back to."""
+    L = host.load()
+    assert L.mc_set_spmm_stages(1) == 0 and L.mc_set_spmm_splitting(0) == 0
+    assert A.run(512)[0] != "dense"
+    assert L.mc_set_spmm_stages(2) == 0 and L.mc_set_spmm_splitting(1) == 0
+    assert A.run(512)[0] == "dense" and A.form(512, mc.Options(spmm_stages=2, spmm_splitting=1)) == 6
