@@ -436,7 +436,7 @@ DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_byt
 // Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines; by a
 // tenth at least where the merged copy has such a copy already.  (Of 1385 drawn operands 33 then have both, with 2 %
 // 106; the forms they run in lose the same 2.0 % over the best on average.)
-bool resident_worth_building(const mc_mat *A, bool dense_rival)
+bool resident_worth_building(const mc_mat *A)
 {
     const mc_options automatic = {};
     for (int row_bytes : {1024, 512, 256, 128}) {
@@ -444,7 +444,6 @@ bool resident_worth_building(const mc_mat *A, bool dense_rival)
             SlabPlan pl;
             plan_slab(A, row_bytes, r4, 4, automatic, &pl);
             double best = 0.98 * gather_us(A, row_bytes, r4 ? 4 : 8, 4, automatic);
-            if (dense_rival) best = std::min(best, plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, 4).us);
             if (A->merged) {
                 best = std::min(best, 0.98 * gather_us(A->merged, row_bytes, r4 ? 4 : 8, 4, automatic));
                 if (A->merged->d_blk_recs) {
@@ -694,9 +693,6 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             A->merge_group = group;
         }
     }
-    // (a thread that pins or forbids the other copies gets those and no others)
-    const bool dense_allowed = dense_mode(t_options) == 1 || (dense_mode(t_options) == 0 && t_options.spmm_slab == 0);
-    const bool dense_rival = dense_allowed && dense_possible(M, K, lhs_bits);
     // LDS-ordered copy for the SpMM that keeps rows of B resident in LDS, where that form is expected to be the fastest one
     // for some width of B (the merged copy's forms included), unless the thread's options rule that kernel out (1: built whatever the shape, so that the
     // form can be forced).
@@ -707,7 +703,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         ResidentLayout rl;
         mc_resident_query(K, lay.P, row_ptr, col_idx, &rl);
         A->blk_nt = rl.nt; A->block_rows = rl.block_rows; A->nblk = rl.nblk; A->blk_chunks = rl.nchunks;
-        if (rl.nchunks * MC_CHUNK <= INT32_MAX && (t_options.spmm_slab == 1 || resident_worth_building(A, dense_rival))) {
+        if (rl.nchunks * MC_CHUNK <= INT32_MAX && (t_options.spmm_slab == 1 || resident_worth_building(A))) {
             try {
                 blk_ptr.resize((size_t)lay.P * rl.nblk + 1);
                 blk_src.resize((size_t)rl.nchunks * MC_CHUNK);
@@ -741,8 +737,11 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             A->nblk = 0; A->blk_chunks = 0;
         }
     }
-    // The operand with all its columns, where that form is expected to be the fastest for some width of B
-    const bool dense = !child && dense_rival && lay.nvec > 0 && (dense_mode(t_options) == 1 || dense_worth_building(A));
+    // The operand with all its columns, where that form is expected to be the fastest for some width of B.  Beside the other copies, not in
+    // their place: calls with options, and calls that this form does not take, run in theirs.  (A thread that pins or forbids
+    // the other copies gets those and no others.)
+    const bool dense_allowed = dense_mode(t_options) == 1 || (dense_mode(t_options) == 0 && t_options.spmm_slab == 0);
+    const bool dense = !child && dense_allowed && dense_possible(M, K, lhs_bits) && lay.nvec > 0 && (dense_mode(t_options) == 1 || dense_worth_building(A));
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define MC_TRY(call) (ok = ok && hip_ok((call), #call))
     bool ok = true;

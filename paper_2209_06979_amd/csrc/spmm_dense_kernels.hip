@@ -263,7 +263,7 @@ template <int PL, bool R4> hipError_t launch_tile(const DenseArgs &a, int tile, 
 
 // The dense copy from the panel format: a workgroup makes FILL_CHUNKS chunks of one block of 16 rows in LDS, zeros included, and
 // writes them out whole.  One byte per lane and LDS write, a slot's V rows one after the other (4096 x 4096,
-// half empty, V = 2: 41 us, beside 50 for the new values' own launch; mc_mat_create 55 -> 37 ms, the LDS-ordered copy being left out).
+// half empty, V = 2: 41 us, beside 50 for the new values' own launch).
 constexpr int FILL_CHUNKS = 16;
 __global__ __launch_bounds__(256) void dense_fill_kernel(DenseFillArgs a)
 {

@@ -111,3 +111,17 @@ def test_options_that_say_what_is_automatic_are_no_pins(A):
     assert A.run(512)[0] != "dense"
     assert L.mc_set_spmm_stages(2) == 0 and L.mc_set_spmm_splitting(1) == 0
     assert A.run(512)[0] == "dense" and A.form(512, mc.Options(spmm_stages=2, spmm_splitting=1)) == 6
+
+
+@pytest.mark.parametrize("shape", [DENSE, dict(M=4096, K=4096, V=2, empty=0.5), dict(M=1024, K=2048, V=4, empty=0.5, prec="L8R4"),
+                                   dict(M=1024, K=1024, V=2, empty=0.5, prec="L16R8")])
+def test_the_copy_with_all_columns_replaces_no_other_copy(shape):
+    """Calls that ask for another form get the one that they get from an operand built without that copy."""
+    A, without = host.Mat(**shape), host.Mat(**shape, options=mc.Options(spmm_merge=-mc.SPMM_DENSE))
+    assert any(A.form(N) & 4 for N in (128, 256, 512, 1024)) and not any(without.form(N) & 4 for N in (128, 256, 512, 1024))
+    for N in (64, 128, 256, 512, 1024):
+        for o in (dict(spmm_slab=1), dict(spmm_slab=-1), dict(spmm_merge=1), dict(spmm_merge=-1), dict(spmm_merge=1, spmm_slab=1), dict(spmm_stages=1),
+                  dict(spmm_merge=-mc.SPMM_DENSE)):
+            o = mc.Options(**o)
+            assert A.form(N, o) == without.form(N, o) and A.run(N, o, ex=True) == without.run(N, o, ex=True)
+    A.close(), without.close()
