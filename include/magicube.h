@@ -241,6 +241,10 @@ int mc_mat_create(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, con
                   const void *values, void *stream, mc_mat **out);
 /* Replaces the values from a DEVICE array in interchange order (nvec*V elements of the
  * matrix's width; e.g. the output of a softmax).  Asynchronous on `stream`.
+ * The copy with all columns (see mc_set_spmm_dense) receives them if it was asked for when the operand was created
+ * (spmm_merge = MC_SPMM_DENSE, or more) or a product has read it (which may be part of a graph and read it again):
+ * writing it takes longer than a product gains by it.  Otherwise products of the operand run in the other forms from the
+ * first new values on; a program that sets the values before the first product and then multiplies many times asks for it.
  * Device data cannot be range-checked on the host: a 16-bit value must not exceed 32639 (it is
  * split into two signed bytes) and a 12-bit operand must lie in [-2048, 2047]; values outside
  * these ranges are not detected and give a wrong product (mc_mat_create returns MC_ERANGE for

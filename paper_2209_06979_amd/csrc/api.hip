@@ -575,7 +575,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     A->d_blk_ptr = nullptr; A->d_blk_recs = nullptr; A->d_blk_ends = nullptr; A->d_blk_src = nullptr;
     A->d_class_panels = nullptr;
     A->merged = nullptr; A->merge_group = 0; A->d_merge_src = nullptr; A->d_chunk_vec = nullptr; A->merged_valid = false;
-    A->d_dense = nullptr; A->dense_valid = false;
+    A->d_dense = nullptr; A->dense_valid = false; A->dense_read = false; A->dense_asked = dense_mode(t_options) == 1;
     // Length classes of the panels (V = 8: the attention kernel gives a panel 1, 2, 4 or 8 waves)
     std::vector<int32_t> class_panels;
     for (int b = 0; b <= 4; ++b) A->class_start[b] = 0;
@@ -891,7 +891,10 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
         }
     }
     MC_HIP(launch_set_values(a, static_cast<hipStream_t>(stream)));
-    if (A->d_dense) {
+    // (The copy with all columns takes longer to write than one product gains by it, 41 us against 5 at 4096 x 4096, V = 2, half empty, N = 512: where it
+    // was neither asked for nor read, products go back to the other forms.  One that read it may be part of a graph and read it again.)
+    A->dense_valid = false;
+    if (A->d_dense && (A->dense_asked || A->dense_read.load(std::memory_order_relaxed))) {
         MC_HIP(launch_dense_fill(dense_fill_args(A), static_cast<hipStream_t>(stream)));
         A->dense_valid = true;
     }
@@ -989,6 +992,7 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
     a.C = C_dev; a.ldc = ldc; a.C_batch_stride = 0;
     a.P = A->P; a.V = A->V; a.batch = 1; a.float_out = out_mode; a.out_scale = out_mode ? scale : 1.f;
     if (form.dense >= 0) {
+        A->dense_read.store(true, std::memory_order_relaxed);
         DenseArgs da = {};
         da.A = A->d_dense; da.a_bytes = (int)dense_bytes(A->M, A->K, A->lhs_bits);
         da.nrb = (A->M + 15) / 16; da.nch = (A->K + MC_CHUNK - 1) / MC_CHUNK;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <tuple>
 
 #include "../../include/magicube.h"
@@ -71,7 +72,9 @@ struct mc_mat {
     bool merged_valid;         // false once the values were replaced in the panel format only
     // The operand with all its columns (null when not built; see spmm_dense_kernels.hip).
     uint8_t *d_dense;
-    bool dense_valid;          // false once the values were replaced in the panel format only
+    bool dense_valid;          // false once the values were replaced in other formats only
+    bool dense_asked;          // built on request
+    mutable std::atomic<bool> dense_read; // a product has read it (new values are written to it if one of the two is true)
 };
 
 // Builders that also take V = 16 (4- and 8-bit values): the library's merged copies only.

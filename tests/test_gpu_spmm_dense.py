@@ -121,3 +121,35 @@ def test_automatic_choice_and_graph():
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy(), want)
     A.close(), never.close()
+
+
+def test_new_values_of_an_unasked_copy():
+    """Not read yet, the copy is left behind and products take other forms; read by a product in a graph, it follows the values."""
+    import torch
+    from paper_2209_06979_amd import binding as mc
+    c = wl.spmm_case(2048, 2048, 512, 2, 0.5, "L8R8", 9770)
+    rolled = [np.ascontiguousarray(np.roll(c["values"], k, axis=0)) for k in (3, 11, 40)]
+    B = torch_dev(c["B"])
+    A = _operand(c, 0)
+    A.set_values(torch_dev(rolled[0]))
+    assert mc.spmm_form(A, 512, "L8R8") != "dense"
+    assert np.array_equal(mc.spmm(A, B, "L8R8").cpu().numpy(), run_spmm_oracle(dict(c, values=rolled[0])))
+    A.close()
+
+    A, out = _operand(c, 0), torch.zeros((2048, 512), dtype=torch.int32, device="cuda")
+    stream, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        mc.spmm(A, B, "L8R8", out=out)
+    torch.cuda.synchronize()
+    assert mc.spmm_form(A, 512, "L8R8") == "dense"
+    with torch.cuda.graph(g, stream=stream):
+        mc.spmm(A, B, "L8R8", out=out)
+    for new in rolled:
+        A.set_values(torch_dev(new))
+        assert mc.spmm_form(A, 512, "L8R8") == "dense"
+        out.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), run_spmm_oracle(dict(c, values=new)))
+    A.close()

@@ -125,3 +125,25 @@ def test_the_copy_with_all_columns_replaces_no_other_copy(shape):
             o = mc.Options(**o)
             assert A.form(N, o) == without.form(N, o) and A.run(N, o, ex=True) == without.run(N, o, ex=True)
     A.close(), without.close()
+
+
+@pytest.mark.parametrize("asked", [False, True])
+@pytest.mark.parametrize("used", [False, True])
+def test_new_values_refill_the_copy_with_all_columns_only_where_it_is_read(asked, used):
+    """An operand whose copy was neither asked for nor read gets its new values in the other formats, and products take their forms
+    from then on.  A product that read it may sit in a graph, which will read it again: it is kept up to date."""
+    L = host.load()
+    A = host.Mat(**DENSE, options=mc.Options(spmm_merge=mc.SPMM_DENSE) if asked else None)
+    without = host.Mat(**DENSE, options=mc.Options(spmm_merge=-mc.SPMM_DENSE))
+    other = mc.Options(spmm_merge=-mc.SPMM_DENSE)
+    assert A.form(512) == 6 and A.run(512, other, ex=True)[0] != "dense" # (neither reads the copy)
+    if used:
+        assert A.run(512)[0] == "dense"
+    for _ in range(2):
+        assert L.mc_mat_set_values_device(A.handle, A.values.ctypes.data, None) == 0
+        assert L.host_called() == (b"fill" if asked or used else b"values")
+        for N in (32, 64, 128, 512, 1024):
+            assert (A.form(N) >= 4) == (A.run(N)[0] == "dense")
+            assert asked or used or (A.run(N) == without.run(N) and A.form(N) == without.form(N))
+        assert (asked or used) == (A.run(512)[0] == "dense") == (A.run(512, mc.Options(spmm_merge=mc.SPMM_DENSE), ex=True)[0] == "dense")
+    A.close(), without.close()
