@@ -891,7 +891,7 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
         }
     }
     MC_HIP(launch_set_values(a, static_cast<hipStream_t>(stream)));
-    // (The copy with all columns takes longer to write than one product gains by it, 41 us against 5 at 4096 x 4096, V = 2, half empty, N = 512: where it
+    // (The copy with all columns takes longer to write than one product gains by it, 13 us against 7 at 4096 x 4096, V = 2, half empty, N = 512: where it
     // was neither asked for nor read, products go back to the other forms.  One that read it may be part of a graph and read it again.)
     A->dense_valid = false;
     if (A->d_dense && (A->dense_asked || A->dense_read.load(std::memory_order_relaxed))) {
