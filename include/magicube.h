@@ -235,8 +235,8 @@ int mc_merge_host(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, con
  * long as writing them: the panel format (its values, padded, and 4 bytes per slot); the merged copy (see mc_merge_host: the
  * panel format of the merged operand and 4 bytes per merged vector and panel of its group) unless it would hold more vectors
  * than the operand; and an LDS-ordered copy (the values, and 6 bytes per slot) of either, and a copy with all
- * columns (see mc_set_spmm_dense), where the SpMM form that needs it is expected to be the fastest for some width of B.  spmm_merge = -1 and spmm_slab = -1 in the creating
- * thread's options leave them out.  (4096 x 4096, V = 8, 90 % empty, 8 bits: 1.8 MB of values, 13 MB on the device.) */
+ * columns (see mc_set_spmm_dense; left out where device memory for it is short), where the SpMM form that needs it is expected to be
+ * the fastest for some width of B.  spmm_merge = -1 and spmm_slab = -1 in the creating thread's options leave them out.  (4096 x 4096, V = 8, 90 % empty, 8 bits: 1.8 MB of values, 13 MB on the device.) */
 int mc_mat_create(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
                   const void *values, void *stream, mc_mat **out);
 /* Replaces the values from a DEVICE array in interchange order (nvec*V elements of the

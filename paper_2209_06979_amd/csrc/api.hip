@@ -814,15 +814,20 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
         MC_TRY(hipMalloc(&A->d_class_panels, sizeof(int32_t) * class_panels.size()));
         MC_TRY(hipMemcpyAsync(A->d_class_panels, class_panels.data(), sizeof(int32_t) * class_panels.size(), hipMemcpyHostToDevice, s));
     }
-    if (dense) {
-        MC_TRY(hipMalloc(&A->d_dense, (size_t)dense_bytes(M, K, lhs_bits)));
-        if (ok) MC_TRY(launch_dense_fill(dense_fill_args(A), s));
-        A->dense_valid = true;
-    }
     if (A->merged) {
         MC_TRY(hipMalloc(&A->d_merge_src, sizeof(int32_t) * m_src.size()));
         MC_TRY(hipMemcpyAsync(A->d_merge_src, m_src.data(), sizeof(int32_t) * m_src.size(), hipMemcpyHostToDevice, s));
         A->merged_valid = true;
+    }
+    // (last, and left out where there is no memory for it: no call depends on it)
+    if (ok && dense) {
+        if (hipMalloc(&A->d_dense, (size_t)dense_bytes(M, K, lhs_bits)) == hipSuccess) {
+            MC_TRY(launch_dense_fill(dense_fill_args(A), s));
+            A->dense_valid = true;
+        } else {
+            A->d_dense = nullptr;
+            (void)hipGetLastError();
+        }
     }
     MC_TRY(hipStreamSynchronize(s)); // host staging buffers die at return
 #undef MC_TRY

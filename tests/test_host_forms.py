@@ -147,3 +147,27 @@ def test_new_values_refill_the_copy_with_all_columns_only_where_it_is_read(asked
             assert asked or used or (A.run(N) == without.run(N) and A.form(N) == without.form(N))
         assert (asked or used) == (A.run(512)[0] == "dense") == (A.run(512, mc.Options(spmm_merge=mc.SPMM_DENSE), ex=True)[0] == "dense")
     A.close(), without.close()
+
+
+def test_an_operand_without_memory_for_the_copy_with_all_columns():
+    """The copy is optional: an operand that is built where it does not fit runs in the other forms, and holds nothing of it."""
+    L = host.load()
+    asked = mc.Options(spmm_merge=mc.SPMM_DENSE)
+    shape = dict(M=512, K=4096, V=8, empty=0.9, options=asked)
+    with_it = host.Mat(**shape)
+    assert with_it.form(512, asked) & 4
+    full = L.host_live()
+    with_it.close()
+    L.host_limit(512 * 4096)                                          # (the copy's size; all else is smaller)
+    try:
+        A = host.Mat(**shape)
+        assert L.host_live() == full - 1
+        assert A.form(512, asked) < 4 and A.run(512, asked, ex=True)[0] != "dense"
+        assert L.mc_mat_set_values_device(A.handle, A.values.ctypes.data, None) == 0 and L.host_called() == b"values"
+        assert A.form(512, asked) < 4
+        A.close()
+        L.host_limit(1024)                                            # what the operand needs is still asked for
+        host.Mat(**shape, status=mc.MC_EHIP)
+    finally:
+        L.host_limit(2**62)
+    assert L.host_live() == 0
