@@ -159,11 +159,14 @@ __global__ __launch_bounds__(64 * W, PL == 1 && NT == 4 && RF == 2 ? 4 : 1) void
         __builtin_amdgcn_sched_barrier(0);
     }
     // (memory is fenced for the compiler only: see the loop's end)
+    auto in_order = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
     auto barrier = [&]() {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
+        in_order();
     };
     mcu::lgkm_wait();
     barrier();
@@ -174,6 +177,7 @@ __global__ __launch_bounds__(64 * W, PL == 1 && NT == 4 && RF == 2 ? 4 : 1) void
 #pragma unroll
         for (int d = 0; d < AH; ++d) {
             put((d + 3) % AH, (d + 3) % STAGES);
+            in_order();                                         // (the writes are issued first: what waits for the reads has waited for them)
             fetch((d + 1) % STAGES, bop[(d + 1) & 1]);
             load_b((d + 3) % AH);
             __builtin_amdgcn_sched_barrier(0);
@@ -185,7 +189,7 @@ __global__ __launch_bounds__(64 * W, PL == 1 && NT == 4 && RF == 2 ? 4 : 1) void
                 __builtin_amdgcn_sched_barrier(0);
             }
             // The stage that the next step overwrites held this step's rows, which every wave has consumed; the one it reads
-            // was written a step before this one, ahead of reads that have returned since (LDS works in order).
+            // was written a step before this one, ahead of that step's reads, which have returned since (LDS works in order).
             barrier();
         }
     }
