@@ -21,6 +21,7 @@
 // consumer): per chunk of 64 slots and group of 16 slots, [row v][16 slots] bytes; 16-bit codes as
 // a high and a low signed-byte plane; padded slots zero.
 #include "internal.h"
+#include "softmax_split.h"
 
 #include <type_traits>
 
@@ -385,31 +386,20 @@ template <bool C16, bool DEV> hipError_t launch_softmax_mode(const SoftmaxArgs &
     const dim3 grid((unsigned)a.P, (unsigned)a.batch), grid4((unsigned)((a.P + 3) / 4), (unsigned)a.batch);
     const int64_t longest = (int64_t)a.max_panel_chunks * MC_CHUNK * a.V; // scores of the longest panel, padding included
     const int64_t units = (int64_t)a.P * a.batch;
-    // One wave per panel up to 3072 scores, with the smallest R; workgroups of four or eight waves beyond, and from 1025 scores on
-    // also for few panels, whose launch is one chain.  us, V = 8, int8 codes, replayed from a graph, before (8 x 2 waves up to 1024
-    // panels, 16 x 1 wave beyond, 16 x 4 from 4097 scores on, all with shuffles through LDS) and as it is:
-    //   scores   256 panels   1024         4096         32768
-    //      512   4.1   2.7    4.6   2.7     6.5   4.1    35    17
-    //     1024   4.2   3.1    4.7   3.3     8.5   6.7    42    32
-    //     2048   4.4   3.2    5.0   4.0    11.1   9.9    62    63   (256 panels by single waves: 3.8; 1024 by workgroups: 4.7)
-    //     4096   4.8   3.7    8.0   7.6    17.5  15.8   124   120   (1024 panels by 8 x 2 waves: 7.4, 4096: 16.4)
-    //     8192   5.8   4.5   12.0  11.2    34.1  33.2   233   235   (by 8 x 4 waves 4.4, 10.8, 34.2, 248)
-    //    16384   8.6   8.0   18.2  17.8    68.0  68.1
-    // A workgroup's fourth piece is nearly empty just above 2048 scores, which a wave of 12 pieces skips (us, workgroups / 12 x 1):
-    //     2160   640: 4.5  4.4    1024: 5.6  4.7     4096: 13.7  11.1    16384: 41.0  34.7
-    //     2560   640: 4.6  4.5    1024: 6.0  5.1     4096: 13.7  11.7    16384: 41.5  40.2
-    //     3040   640: 5.0  4.9    1024: 6.7  6.2     4096: 14.3  12.9    16384: 46.2  47.2
-    // Beyond 3072 scores, 16 x 1 gains up to 6 % at 4096 panels and loses as much at 640 and 16384.
-    const bool few = units <= 512;
-    if (a.variant == 2 || longest > 16384) return launch_kernel(softmax_general_kernel, grid, dim3(256), 0, s, a);
-    if (longest > 8192) return launch_kernel((softmax_group_kernel<16, 4, C16, DEV>), grid, dim3(256), 0, s, a);
-    if (longest > 4096) return launch_kernel((softmax_group_kernel<4, 8, C16, DEV>), grid, dim3(512), 0, s, a);
-    if (!few && a.variant != 1 && longest > 2048 && longest <= 3072) return launch_kernel((softmax_wave_kernel<12, C16, DEV>), grid4, dim3(256), 0, s, a);
-    if (longest > 2048) return launch_kernel((softmax_group_kernel<4, 4, C16, DEV>), grid, dim3(256), 0, s, a);
-    if (a.variant == 1 || (few && longest > 1024)) return launch_kernel((softmax_group_kernel<2, 4, C16, DEV>), grid, dim3(256), 0, s, a);
-    if (longest > 1024) return launch_kernel((softmax_wave_kernel<8, C16, DEV>), grid4, dim3(256), 0, s, a);
-    if (longest > 512) return launch_kernel((softmax_wave_kernel<4, C16, DEV>), grid4, dim3(256), 0, s, a);
-    return launch_kernel((softmax_wave_kernel<2, C16, DEV>), grid4, dim3(256), 0, s, a);
+    const SoftmaxSplit split = softmax_split(longest, units, a.variant);
+    switch (split.pieces * 16 + split.waves) {
+    case 0: return launch_kernel(softmax_general_kernel, grid, dim3(256), 0, s, a);
+    case 2 * 16 + 1: return launch_kernel((softmax_wave_kernel<2, C16, DEV>), grid4, dim3(256), 0, s, a);
+    case 4 * 16 + 1: return launch_kernel((softmax_wave_kernel<4, C16, DEV>), grid4, dim3(256), 0, s, a);
+    case 8 * 16 + 1: return launch_kernel((softmax_wave_kernel<8, C16, DEV>), grid4, dim3(256), 0, s, a);
+    case 12 * 16 + 1: return launch_kernel((softmax_wave_kernel<12, C16, DEV>), grid4, dim3(256), 0, s, a);
+    case 16 * 16 + 1: return launch_kernel((softmax_wave_kernel<16, C16, DEV>), grid4, dim3(256), 0, s, a);
+    case 2 * 16 + 4: return launch_kernel((softmax_group_kernel<2, 4, C16, DEV>), grid, dim3(256), 0, s, a);
+    case 4 * 16 + 4: return launch_kernel((softmax_group_kernel<4, 4, C16, DEV>), grid, dim3(256), 0, s, a);
+    case 4 * 16 + 8: return launch_kernel((softmax_group_kernel<4, 8, C16, DEV>), grid, dim3(512), 0, s, a);
+    case 16 * 16 + 4: return launch_kernel((softmax_group_kernel<16, 4, C16, DEV>), grid, dim3(256), 0, s, a);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s)

@@ -51,3 +51,16 @@ def test_device_format_of_every_kernel(V, P, scores, bits):
         outs.append(mc.spmm(A, B, prec, options=mc.Options(spmm_slab=-1, spmm_merge=-1)).cpu().numpy())
         A.close()
     assert np.array_equal(*outs) and outs[0].any()
+
+
+@pytest.mark.parametrize("scores,units", [(3080, 1536), (3080, 1537), (4096, 1537), (4096, 20481), (4104, 768), (4104, 769), (8192, 1024), (8192, 1025),
+                                          (4104, 4097)])
+def test_numbers_of_panels_where_the_kernel_changes(scores, units):
+    """Few full panels among short ones: the launch is as large, the oracle's work is not."""
+    n = scores // 8
+    L = -(-n // 8) * 8
+    panels = L // 8
+    batch = units // panels if units % 2 == 0 else -(-units // panels) # (up to the limit, or beyond it)
+    counts = _counts(panels, [n, 0, 1, n - 1, 63], 0)
+    counts[5:] = 3
+    _check(8, L, counts, 7600, 8, batch=batch)
