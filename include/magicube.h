@@ -543,7 +543,10 @@ int mc_set_spmm_stages(int stages);
  * more than 16 chunks) get, at mc_mat_create, a list of work items that cuts long panels into
  * pieces of at most three times the average (at least 8 chunks); mc_spmm then lets several workgroups add their exact int32 partial results into the
  * (first cleared) rows of such panels.  enable = 0 turns this off (one workgroup per panel and
- * row tile, as for regular matrices); the result is the same either way. */
+ * row tile, as for regular matrices); the result is the same either way.
+ * The switch also governs the SDDMM.  There a piece writes its own outputs, so panels are cut finer, of masks and of operands with
+ * values alike: into pieces of at most the average panel length, or of as few chunks as make 512 pieces where there are fewer
+ * than 256 panels, at least 2 chunks each, as soon as one panel is longer than that. */
 int mc_set_spmm_splitting(int enable);
 /* The SpMM form for patterns whose blocks of 16 rows name nearly every column: mc_mat_create then also stores
  * the operand with all its columns (M * K bytes, twice that for 16- and 12-bit values), zeros where nothing is
@@ -554,18 +557,14 @@ int mc_set_spmm_splitting(int enable);
  * -1 to -MC_SPMM_DENSE and 0 to 0, where it does not pin the merged copy or its absence (the tile counts with mode 1
  * only).  MC_EINVAL otherwise. */
 int mc_set_spmm_dense(int mode, int tile);
-/* (The switch also governs the work items of mc_sddmm.  There every item writes its own outputs,
- * so a pattern-only mask is cut finer: into pieces of at most the average panel length, at least
- * 8 chunks, as soon as one panel is longer than that; a mask with fewer than 256 panels into
- * pieces short enough to make 256 of them, again at least 8 chunks.) */
 /* SDDMM variant: -1 = automatic, 0 = the kernel that loads operands straight from memory
  * (any row length), 1, 2, 4 or 8 = waves per panel of the kernel that stages Kmat rows in
  * LDS (used for rows of up to 1024 bytes, else
  * ignored). */
 int mc_set_sddmm_variant(int waves);
-/* Softmax variant: 0 = automatic (panels of up to 4096 scores, padding included, are kept in
- * the registers of one wave, up to 16384 in those of a workgroup: one pass over the scores),
- * 1 = a workgroup per panel also for short panels, 2 = always the kernel for panels of any
+/* Softmax variant: 0 = automatic (panels of up to 16384 scores, padding included, are kept in the registers of one wave,
+ * up to 4096 of them, or of a workgroup of four or eight waves, by length and number of panels: one pass over the
+ * scores), 1 = a workgroup per panel also for short panels, 2 = always the kernel for panels of any
  * length (three passes).  Same codes up to fp32 summation order. */
 int mc_set_softmax_variant(int variant);
 /* Attention path: 0 = automatic (a single fused kernel when dk is at most 128 and no panel holds

@@ -8,12 +8,13 @@
 // all of its waves read from LDS.
 //
 //   A   straight from memory into registers, one 1 KB fragment (16 rows x 64 columns, one byte plane) per load, requested
-//       four steps ahead; every fragment is read by one wave of the workgroup only.
+//       four steps (small tiles: eight) ahead; every fragment is read by one wave of the workgroup only.
 //   B   64 rows x NT segments of 16 columns per chunk, loaded into registers seven (small tiles: eleven) steps ahead, written to
 //       LDS three steps ahead in the image [row / 16][segment][row % 16] (positions exchanged so that neither the writes nor
 //       the transposing reads meet in a bank; nibbles widened to bytes of 16 times their value, once for all waves), read a step
 //       ahead.  One barrier per step; it need not wait for anything: what a step overwrites was consumed by the step
-//       before, and what it reads was written two steps before.
+//       before, and what it reads was written two steps before, ahead of reads that its writers have waited for since (a
+//       wave's writes of a step are issued before its reads, which the kernel sees to).
 // The waves of a workgroup are WR row groups times WK groups that take every WK-th chunk; the WK sums meet in LDS at the
 // end.  The MFMA computes the transposed tile (as in spmm_resident_kernels.hip): a lane has four neighbouring columns.
 //

@@ -110,7 +110,9 @@ template <bool TR> struct PhaseClock {
 template <int BNB, int WK, int LB, int RB, bool U = false, int NS = 1, bool TR = false>
 __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
 {
-    mcu::request_arguments(a);
+    // (Not with 128-byte tiles of two planes by two waves, one chunk in flight: the scalars that it brings forward cost a wave per
+    // SIMD, and 4624 x 3513, V = 8, 94 % empty, N = 448, unequal panels, took 13.1 us instead of 12.1.)
+    if constexpr (!(NS == 1 && BNB == 128 && WK == 2 && LB == 16 && RB == 8)) mcu::request_arguments(a);
     using Cfg = SpmmCfg<BNB, WK, LB, RB, U, NS>;
     PhaseClock<TR> clk;
     clk.stamp(0);                                        // the wave has started
@@ -208,7 +210,22 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
         return av;
     };
     // all MFMAs of one chunk whose rows sit in the stage at st
+    // (64-byte tiles by eight waves, one chunk in flight, take long panels: left to itself the compiler reads and multiplies tile by
+    // tile there, to stay at 64 registers.  All reads first: 14240 x 5056, V = 4, 91 % empty, N = 64, unequal panels 17.8 -> 16.2 us.)
+    constexpr bool READS_FIRST = NS == 1 && BNB == 64 && WK == 8 && RB == 8 && !U;
     auto compute = [&](const char *st, v4i a_cur) {
+        if constexpr (READS_FIRST) {
+            v2i d[LPR][2];
+#pragma unroll
+            for (int ct = 0; ct < LPR; ++ct)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) d[ct][h] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(st + (rd_base[h] ^ (ct * 16))));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ct = 0; ct < LPR; ++ct)
+                acc[ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_cur, (v4i){d[ct][0].x, d[ct][0].y, d[ct][1].x, d[ct][1].y}, acc[ct], 0, 0, 0);
+            return;
+        }
 #pragma unroll
         for (int ct = 0; ct < LPR; ++ct) {
             const v2i d0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i *)(st + (rd_base[0] ^ (ct * 16))));
