@@ -131,12 +131,17 @@ __device__ __forceinline__ int code_of(float x, float scale, float inv, float qm
 }
 
 // L loads of 4 elements per lane and unit, one store of their codes.  Each workgroup owns a contiguous span and keeps four units in
-// flight per lane; one test for a tie covers four elements.  The tensor is read past the caches.  The codes are what the caller's
-// next kernel reads: they are stored past the caches (STREAM, and then two loads a unit: wider stores) only where they would not stay
-// there (QUANTIZE_CACHED).  The attention layer on three tensors of 2 MB of codes takes 18.2 us after streamed stores and 16.9 after
-// ordinary ones.  int8, us against two loads a unit and a test for each element throughout: 1 MB 4.0 -> 3.2, 8 MB 4.0 -> 3.9,
-// 32 MB 9.6 -> 9.2, 128 MB 30.7 -> 28.6, 512 MB 111 both (5.9 TB/s).
-template <int BITS, bool STREAM> __global__ __launch_bounds__(256) void quantize_kernel(const float *x, int64_t n, float scale, uint8_t *q)
+// flight per lane (two of what remains); one test for a tie covers four elements.  The codes are what the caller's next kernel reads: they are
+// stored past the caches (STREAM, and then two loads a unit: wider stores) only where they would not stay there (QUANTIZE_CACHED).
+// The tensor is read past the caches unless it is small (KEEP: below QUANTIZE_KEPT), when it does not drive the codes out and a
+// tensor that is quantised again is still there.  int8, three tensors and the attention layer that reads them, replayed from a graph, tensors written
+// just before / once and for all, against stores and (up to 128 MB) loads of the respective other kind, two loads a unit and a test for each element:
+//   3 x  4 MB  26.9 -> 25.7 / 18.4 -> 17.5 us (token-major; tensors read past the caches 26.1 / 19.8)
+//   3 x  8 MB  40.1 -> 38.5 / 28.2 -> 27.0
+//   3 x 16 MB  61.6 -> 54.4 / 38.6 -> 37.0 (tensors read through the caches 59.2 / 36.1)
+// By itself, eight tensors in turn: 1 MB 2.4 both, 4 MB 3.0 -> 3.1, 16 MB 5.4 -> 6.1, 32 MB 8.7 -> 9.2, 64 MB 17.3 -> 15.7, 128 MB 30.7 -> 29.5,
+// 256 MB 59.8 -> 58.2, 512 MB 111 both (5.9 TB/s).
+template <int BITS, bool STREAM, bool KEEP> __global__ __launch_bounds__(256) void quantize_kernel(const float *x, int64_t n, float scale, uint8_t *q)
 {
     constexpr int U = 4, L = STREAM ? 2 : 1;
     typedef unsigned v2u __attribute__((ext_vector_type(2)));
@@ -169,7 +174,7 @@ template <int BITS, bool STREAM> __global__ __launch_bounds__(256) void quantize
     };
     auto load = [&](int64_t i, v4f (&v)[L]) {
 #pragma unroll
-        for (int l = 0; l < L; ++l) v[l] = __builtin_nontemporal_load(&xv[i * L + l]);
+        for (int l = 0; l < L; ++l) v[l] = KEEP ? xv[i * L + l] : __builtin_nontemporal_load(&xv[i * L + l]);
     };
     int64_t i = b + threadIdx.x;
     for (; i + (U - 1) * 256 < e; i += U * 256) {
@@ -179,7 +184,15 @@ template <int BITS, bool STREAM> __global__ __launch_bounds__(256) void quantize
 #pragma unroll
         for (int u = 0; u < U; ++u) emit(i + u * 256, v[u]);
     }
-    for (; i < e; i += 256) {
+    if (i + 256 < e) { // (two of two or three more)
+        v4f v[2][L];
+        load(i, v[0]);
+        load(i + 256, v[1]);
+        emit(i, v[0]);
+        emit(i + 256, v[1]);
+        i += 512;
+    }
+    if (i < e) {
         v4f v[L];
         load(i, v);
         emit(i, v);
@@ -197,6 +210,7 @@ template <int BITS, bool STREAM> __global__ __launch_bounds__(256) void quantize
 }
 
 constexpr int64_t QUANTIZE_CACHED = 32 << 20; // bytes of codes: an eighth of the memory-side cache
+constexpr int64_t QUANTIZE_KEPT = 8 << 20;    // bytes of the tensor
 
 // units of 256 threads' worth of work, at most `cap` workgroups
 inline unsigned grid_for(int64_t units, int64_t cap)
@@ -246,9 +260,11 @@ hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uin
     // a load per lane as long as that makes no more than 2048 workgroups, then up to eight
     const int64_t loads = n / 4 / 256;
     const dim3 grid(grid_for(n / 4, loads <= 2048 ? 2048 : loads / 8 < 2048 ? 2048 : loads / 8 < 16384 ? loads / 8 : 16384)), block(256);
-    const bool stream = n * bits / 8 > QUANTIZE_CACHED;
-    if (bits == 8 && stream) return launch_kernel((quantize_kernel<8, true>), grid, block, 0, s, x, n, scale, q);
-    if (bits == 8) return launch_kernel((quantize_kernel<8, false>), grid, block, 0, s, x, n, scale, q);
-    if (stream) return launch_kernel((quantize_kernel<4, true>), grid, block, 0, s, x, n, scale, q);
-    return launch_kernel((quantize_kernel<4, false>), grid, block, 0, s, x, n, scale, q);
+    const bool stream = n * bits / 8 > QUANTIZE_CACHED, keep = n * 4 < QUANTIZE_KEPT;
+    if (bits == 8 && stream) return launch_kernel((quantize_kernel<8, true, false>), grid, block, 0, s, x, n, scale, q);
+    if (bits == 8 && keep) return launch_kernel((quantize_kernel<8, false, true>), grid, block, 0, s, x, n, scale, q);
+    if (bits == 8) return launch_kernel((quantize_kernel<8, false, false>), grid, block, 0, s, x, n, scale, q);
+    if (stream) return launch_kernel((quantize_kernel<4, true, false>), grid, block, 0, s, x, n, scale, q);
+    if (keep) return launch_kernel((quantize_kernel<4, false, true>), grid, block, 0, s, x, n, scale, q);
+    return launch_kernel((quantize_kernel<4, false, false>), grid, block, 0, s, x, n, scale, q);
 }

@@ -6,7 +6,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("n", [2, 6, 8, 10, 254, 1022, 65536 + 2, 4 * 256 * 2048 - 2, 4 * 256 * 2048 + 6, 13 * 1024 * 1024 + 254, (32 << 20) + 4, (64 << 20) + 14])
+@pytest.mark.parametrize("n", [2, 6, 8, 10, 254, 1022, 65536 + 2, 4 * 256 * 2048 - 2, 4 * 256 * 2048 + 6, 5 * 512 * 1024 + 10, 4 * 256 * 2048 * 3 + 258, 13 * 1024 * 1024 + 254, (32 << 20) + 4, (64 << 20) + 14])
 def test_sizes(n, bits):
     import torch
     from paper_2209_06979_amd import binding as mc
