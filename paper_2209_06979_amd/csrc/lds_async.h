@@ -34,9 +34,10 @@ __device__ __forceinline__ v4h to_half4(v4f f) { return (v4h){(_Float16)f.x, (_F
 typedef __attribute__((address_space(3))) v2i lds_v2i;
 
 // Requests every 64-byte line of a kernel's arguments at once.  They lie in memory that the host writes: a line that is first read in
-// the middle of a kernel costs a round trip there and then, and the compiler requests arguments as they come to be needed.  Calls of
-// the gather form of SpMM in a row take 1.035x less with it (38 drawn calls of 3.5 - 7 us; 1.016x where they take longer), the dense
-// form 1.01x and SDDMM 1.01x.  Not in the resident form: with it 20 calls of 7 - 40 us took 1.002x as long in the mean (0.96 - 1.03x).
+// the middle of a kernel costs a round trip there and then, and the compiler requests arguments as they come to be needed.  The
+// gather form of SpMM takes 1.01x less with it (136 drawn operands replayed from graphs, up to 1.05x for those of 3 - 5 us; calls that the host's launch
+// bounds gain nothing that can be told from noise), the dense form 1.01x and SDDMM 1.01x.  What it brings forward stays in registers: not in the resident
+// form (20 calls of 7 - 40 us 1.002x as long in the mean, 0.96 - 1.03x), nor where a kernel says why.
 template <class Args> __device__ __forceinline__ void request_arguments(const Args &a)
 {
     constexpr int LAST = (int)(sizeof(Args) - 4) / 64;

@@ -423,7 +423,8 @@ __global__ __launch_bounds__(64 * WK) void sddmm_nib32_kernel(SddmmArgs a)
 template <int PB, int KC, bool DQ>
 __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_direct_kernel(SddmmArgs a)
 {
-    mcu::request_arguments(a);
+    // (Not for bytes: 512 x 2048, V = 2, 80 % empty, Kd = 1040 took 25.5 us as fp16 with it, 24.5 without; 4-bit rows 1.04x as long without.)
+    if constexpr (PB != 8) mcu::request_arguments(a);
     constexpr int STEP = StepBytes<PB>::value, LANEB = STEP / 4; // bytes per step / per lane and step
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, g = lane >> 4;
