@@ -129,8 +129,8 @@ void free_device(mc_mat *A)
 // Waves per share of the mask for SDDMM: enough to put about 3200 waves on the chip (4096 of the light ones that stage rows of 32
 // bytes, or 64 bytes of nibbles), no more than a share has units of rows (64 of up to 128 bytes, 32 of 256, 16 beyond), and
 // so many that no wave has more than 24 units.
-// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at 66, 9 % off at
-// worst (profiles/sddmm_waves.txt).
+// On 70 shapes (V = 2 .. 8, 1 .. 40 chunks per panel, rows of 32 .. 544 bytes) within 5 % of the best count at 66 or more, 5 - 12 %
+// off at worst from run to run (profiles/sddmm_waves.txt).
 int choose_sddmm_waves(const mc_mat *mask, int shares, int batch, int row_bytes, int bits, const mc_options &o)
 {
     if (o.sddmm_waves != 0) return o.sddmm_waves < 0 ? 0 : o.sddmm_waves; // 0 selects the direct-load kernel in launch_sddmm
@@ -938,8 +938,8 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, in
         const DensePlan d = plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, out_bytes, dense_tile(o));
         if (d.tile >= 0) {
             f.dense = d.tile;
-            // (its expected times and the others' were fitted apart.  Taken by 3 % or more: of 400 drawn operands 73 change their form and
-            // run 1.22 times as fast in the mean, one in twenty of them 4 - 5 % slower; rows of less than 64 bytes by 15 %: their gather
+            // (its expected times and the others' were fitted apart.  Taken by 3 % or more: of 400 drawn operands 38 take it and run
+            // 1.24 times as fast in the mean, two of them slower, 1.07 and 1.17 times; rows of less than 64 bytes by 15 %: their gather
             // is expected up to a fifth too slow)
             f.plan.us = d.us;
             best = dense_mode(o) == 1 ? 0.0 : d.us * (row_bytes < 64 ? 1.15 : 1.03);
