@@ -64,3 +64,10 @@ def test_numbers_of_panels_where_the_kernel_changes(scores, units):
     counts = _counts(panels, [n, 0, 1, n - 1, 63], 0)
     counts[5:] = 3
     _check(8, L, counts, 7600, 8, batch=batch)
+
+
+@pytest.mark.parametrize("bits", [8, 16])
+@pytest.mark.parametrize("P,scores", [(1600, 4096), (1600, 3080), (800, 4104), (4104, 8192)])
+def test_device_format_of_many_panels(P, scores, bits):
+    """The splits that only large launches take, in the panel format: single waves of 16 pieces, four waves of 16."""
+    test_device_format_of_every_kernel(8, P, scores, bits)
