@@ -306,7 +306,10 @@ namespace {
 struct SlabPlan { int nt, ntiles, groups, wpp, waves; double us; };
 
 int resident_end_words(const mc_mat *A) { return (int)((A->blk_chunks + 31) / 32 + 2); }
-int resident_rec_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V * (A->lhs_bits == 12 ? 16 : A->lhs_bits) / 8; }
+int resident_chunk_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V * (A->lhs_bits == 12 ? 16 : A->lhs_bits) / 8; }
+int rec_chunks(const mc_mat *A) { return resident_rec_chunks(A->nblk, A->V, A->lhs_bits); }
+int resident_rec_bytes(const mc_mat *A) { return rec_chunks(A) * resident_chunk_bytes(A); }
+int64_t resident_records(const mc_mat *A) { return (A->blk_chunks + rec_chunks(A) - 1) / rec_chunks(A); }
 
 // Expected times in us of the two forms of the SpMM, fitted (non-negative least squares on the relative error) to 1600 operands drawn
 // as in profiles/spmm_forms.txt, which holds the first of them: all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192
@@ -317,12 +320,16 @@ int resident_rec_bytes(const mc_mat *A) { return 2 * MC_CHUNK + MC_CHUNK * A->V 
 // 2.8 %, 11 %, 62 %, and on the 168 points of profiles/sweep_spmm_sddmm_grid.txt, one operand over and over, 5.5 % and 54 % against
 // 2 % and 30 %).
 // Resident, all of B's rows at once: launch and start; the fill, a line of B per row, by how many workgroups there are to fill; per
-// step of a wave one part per MFMA and one per byte of a record, both by how many of the sixteen waves have panels; the epilogues; the stores;
+// step of a wave one part per MFMA and one per byte of a chunk's part of a record, both by how many of the sixteen waves have panels; the epilogues; the stores;
+// by the width of B and by whether the two chunks of a record share a request;
 // waves that share a panel meet; and the steps that the longest panel's waves still have when an even share would be done.
 // In blocks: per block and pass the fill, per step of a wave its own reads, and per panel of a wave a start in each block.
 // (A: the operand's layout figures are enough, its copies need not exist yet)
 void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_options &o, SlabPlan *pl)
 {
+    struct Cost { double start, store, meet, fill, mfma, record, panel, late; };
+    static const Cost cost[2][2] = {{{4.5, 1.47e-7, 0.45, 9.0e-4, 0.0567, 1.10e-4, 0.0055, 0.059}, {4.43, 1.03e-7, 0.05, 7.5e-4, 0.0586, 5.9e-5, 0.0047, 0.072}},
+                                    {{5.06, 9.8e-8, 0.16, 8.6e-4, 0.085, 2.3e-5, 0.0031, 0.148}, {4.91, 8.1e-8, 0.01, 6.9e-4, 0.0672, 7.8e-5, 0.0073, 0.16}}};
     pl->us = 1e30;
     const double lists = (double)A->blk_chunks / A->P;               // chunks of a panel over all its blocks
     const double store = (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes;
@@ -350,10 +357,10 @@ void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_
         if (A->nblk == 1) {
             const double filling = std::min(256, q.groups * q.ntiles) / 256.0, busy = std::min(1.0, (double)in_group * q.wpp / q.waves);
             const double late = std::max(0.0, (double)A->max_panel_chunks / q.wpp - steps);
-            q.us = (r4 ? 4.7 : 4.55) + store * (r4 ? 9.1e-8 : 1.2e-7) + (q.wpp > 1 ? (r4 ? 0.39 : 0.22) : 0.0) +
-                   rounds * (A->block_rows * filling * (r4 ? 8.6e-4 : 9.9e-4) + steps * busy * mfma * (r4 ? 0.072 : 0.056) +
-                             steps * busy * filling * resident_rec_bytes(A) * (r4 ? 7.8e-5 : 1.04e-4) + in_group * mfma * (r4 ? 0.0042 : 0.0038) +
-                             late * (r4 ? 0.16 : 0.067));
+            const Cost &c = cost[r4][resident_half(A->V, A->lhs_bits)];
+            q.us = c.start + store * c.store + (q.wpp > 1 ? c.meet : 0.0) +
+                   rounds * (A->block_rows * filling * c.fill + steps * busy * mfma * c.mfma + steps * busy * filling * resident_chunk_bytes(A) * c.record +
+                             in_group * mfma * c.panel + late * c.late);
         } else {
             q.us = 3.1 + store * 1.5e-7 + rounds * (passes * A->nblk * (2.1 + A->block_rows * 0.65e-3) + steps * (r4 ? 0.17 : 0.21) +
                                                     (in_group + q.waves - 1) / q.waves * 3.2);
@@ -436,7 +443,8 @@ DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_byt
 // Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines; by a
 // tenth at least where the merged copy has such a copy already.  (Of 1385 drawn operands 33 then have both, with 2 %
 // 106; the forms they run in lose the same 2.0 % over the best on average.)
-bool resident_worth_building(const mc_mat *A)
+// of: the operand whose merged copy A is (else null); the same holds against the copy that it could have.
+bool resident_worth_building(const mc_mat *A, const mc_mat *of)
 {
     const mc_options automatic = {};
     for (int row_bytes : {1024, 512, 256, 128}) {
@@ -451,6 +459,11 @@ bool resident_worth_building(const mc_mat *A)
                     plan_slab(A->merged, row_bytes, r4, 4, automatic, &m);
                     best = std::min(best, 0.9 * m.us);
                 }
+            }
+            if (of && of->blk_chunks) {
+                SlabPlan given;
+                plan_slab(of, row_bytes, r4, 4, automatic, &given);
+                best = std::min(best, 0.9 * given.us);
             }
             if (pl.us < best) return true;
         }
@@ -528,14 +541,23 @@ DenseFillArgs dense_fill_args(const mc_mat *A)
 // ml.nvec * rows values; which of the two a call uses is decided per call (spmm_form).
 bool merged_worth_building(const mc_layout &lay, const mc_merged_layout &ml) { return ml.nvec <= lay.nvec; }
 
-// child: the merged copy of another operand (V up to 16, never merged again)
+// The layout of A's LDS-ordered copy, whether it is built or not (no chunks: it cannot be)
+void resident_layout(mc_mat *A, const int32_t *row_ptr, const int32_t *col_idx)
+{
+    ResidentLayout rl;
+    mc_resident_query(A->K, A->P, row_ptr, col_idx, &rl);
+    if (rl.nchunks * MC_CHUNK > INT32_MAX) return;
+    A->blk_nt = rl.nt; A->block_rows = rl.block_rows; A->nblk = rl.nblk; A->blk_chunks = rl.nchunks;
+}
+
+// of: the operand whose merged copy this is (V up to 16, never merged again), else null
 int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
-                    void *stream, bool child, mc_mat **out)
+                    void *stream, const mc_mat *of, mc_mat **out)
 {
     if (!out) return MC_EINVAL;
     *out = nullptr;
     if (!values) lhs_bits = 0;
-    if (!child && V == 16) return MC_EINVAL;
+    if (!of && V == 16) return MC_EINVAL;
     mc_layout lay;
     int rc = mc_layout_query_wide(M, K, V, lhs_bits, row_ptr, &lay);
     if (rc != MC_OK) return rc;
@@ -648,7 +670,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     }
     // Shares of the SDDMM: every share writes its own outputs, nothing is added up
     std::vector<int32_t> shares;
-    if (!child && lay.P > 0) {
+    if (!of && lay.P > 0) {
         try {
             shares.reserve((size_t)lay.P * 4);
             for (int p = 0; p < lay.P; ++p) shares.insert(shares.end(), {panel_ptr[2 * (size_t)p], row_ptr[p + 1] - row_ptr[p], p, row_ptr[p]});
@@ -662,7 +684,8 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     // 8-bit values) or 8 rows (two byte planes), see mc_merge_host.  Not for operands without vectors, and not
     // when the thread's options rule it out.
     std::vector<int32_t> m_src;
-    if (!child && lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_merge != -1) {
+    if (lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_slab != -1) resident_layout(A, row_ptr, col_idx);
+    if (!of && lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_merge != -1) {
         const int rows = (lhs_bits == 4 || lhs_bits == 8) ? 16 : 8, group = rows / V;
         mc_merged_layout ml;
         if (group >= 2 && mc_merged_query(M, K, V, lhs_bits, row_ptr, col_idx, group, &ml) == MC_OK && ml.nvec > 0 &&
@@ -683,7 +706,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
             rc = mc_merge_host(M, K, V, lhs_bits, row_ptr, col_idx, values, group, m_row_ptr.data(), m_col_idx.data(), m_values.data(),
                                m_src.data());
             if (rc == MC_OK)
-                rc = mat_create_impl(ml.P * rows, K, rows, lhs_bits, m_row_ptr.data(), m_col_idx.data(), m_values.data(), stream, true,
+                rc = mat_create_impl(ml.P * rows, K, rows, lhs_bits, m_row_ptr.data(), m_col_idx.data(), m_values.data(), stream, A,
                                      &A->merged);
             if (rc != MC_OK) {
                 free_device(A);
@@ -700,15 +723,13 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     std::vector<uint8_t> blk_recs;
     std::vector<uint32_t> blk_ends;
     if (lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_slab != -1) {
-        ResidentLayout rl;
-        mc_resident_query(K, lay.P, row_ptr, col_idx, &rl);
-        A->blk_nt = rl.nt; A->block_rows = rl.block_rows; A->nblk = rl.nblk; A->blk_chunks = rl.nchunks;
-        if (rl.nchunks * MC_CHUNK <= INT32_MAX && (t_options.spmm_slab == 1 || resident_worth_building(A))) {
+        const ResidentLayout rl = {A->blk_nt, A->block_rows, A->nblk, A->blk_chunks};
+        if (rl.nchunks != 0 && (t_options.spmm_slab == 1 || resident_worth_building(A, of))) {
             try {
                 blk_ptr.resize((size_t)lay.P * rl.nblk + 1);
                 blk_src.resize((size_t)rl.nchunks * MC_CHUNK);
                 blk_ends.resize((size_t)resident_end_words(A));
-                blk_recs.resize((size_t)((rl.nchunks + RESIDENT_PADDING) * resident_rec_bytes(A))); // (readers run ahead of the end)
+                blk_recs.resize((size_t)((resident_records(A) + RESIDENT_PADDING) * resident_rec_bytes(A))); // (readers run ahead of the end)
                 if (A->uniform_chunks == 0 && rl.nblk > 1) {
                     order.resize((size_t)lay.P);
                     for (int p = 0; p < lay.P; ++p) order[(size_t)p] = p;
@@ -741,7 +762,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     // their place: calls with options, and calls that this form does not take, run in theirs.  (A thread that pins or forbids
     // the other copies gets those and no others.)
     const bool dense_allowed = dense_mode(t_options) == 1 || (dense_mode(t_options) == 0 && t_options.spmm_slab == 0);
-    const bool dense = !child && dense_allowed && dense_possible(M, K, lhs_bits) && lay.nvec > 0 && (dense_mode(t_options) == 1 || dense_worth_building(A));
+    const bool dense = !of && dense_allowed && dense_possible(M, K, lhs_bits) && lay.nvec > 0 && (dense_mode(t_options) == 1 || dense_worth_building(A));
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define MC_TRY(call) (ok = ok && hip_ok((call), #call))
     bool ok = true;
@@ -844,7 +865,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
 extern "C" int mc_mat_create(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
                              const void *values, void *stream, mc_mat **out)
 {
-    return mat_create_impl(M, K, V, lhs_bits, row_ptr, col_idx, values, stream, false, out);
+    return mat_create_impl(M, K, V, lhs_bits, row_ptr, col_idx, values, stream, nullptr, out);
 }
 
 extern "C" int mc_mat_merged_info(const mc_mat *A, int *group, int64_t *nvec)
@@ -889,10 +910,10 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
         const int32_t *merge_src = X == A ? nullptr : A->d_merge_src;
         const int chunk_bytes = MC_CHUNK * X->V * a.bits / 8;
         ValuesJob &panels = a.job[a.njobs++];
-        panels = {X->d_chunk_vec, nullptr, merge_src, static_cast<uint8_t *>(X->d_vals), X->nslots / MC_CHUNK, chunk_bytes, 0, X->V, 0};
+        panels = {X->d_chunk_vec, nullptr, merge_src, static_cast<uint8_t *>(X->d_vals), X->nslots / MC_CHUNK, chunk_bytes, 0, X->V, 0, 1};
         if (X->d_blk_recs) { // the LDS-ordered copy follows
             ValuesJob &copy = a.job[a.njobs++];
-            copy = {nullptr, X->d_blk_src, merge_src, X->d_blk_recs, X->blk_chunks, resident_rec_bytes(X), 2 * MC_CHUNK, X->V, 0};
+            copy = {nullptr, X->d_blk_src, merge_src, X->d_blk_recs, X->blk_chunks, resident_rec_bytes(X), rec_chunks(X) * 2 * MC_CHUNK, X->V, 0, rec_chunks(X)};
         }
     }
     MC_HIP(launch_set_values(a, static_cast<hipStream_t>(stream)));
@@ -1011,7 +1032,7 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
         SlabArgs sa = {};
         sa.blk_ptr = A->d_blk_ptr; sa.recs = A->d_blk_recs; sa.ends = A->d_blk_ends; sa.end_words = resident_end_words(A);
         sa.order = A->d_order; sa.splits = A->d_splits;
-        sa.uniform_chunks = A->uniform_chunks; sa.rec_bytes = resident_rec_bytes(A); sa.nchunks = A->blk_chunks;
+        sa.uniform_chunks = A->uniform_chunks; sa.rec_bytes = resident_rec_bytes(A); sa.nrecs = resident_records(A);
         sa.B = a.B; sa.ldb_bytes = a.ldb_bytes; sa.row_bytes = a.row_bytes; sa.K = A->K;
         sa.C = C_dev; sa.ldc = ldc;
         sa.P = A->P; sa.V = A->V; sa.nblk = A->nblk; sa.block_rows = A->block_rows; sa.nt = A->blk_nt; sa.rows = rows;

@@ -340,7 +340,8 @@ void mc_resident_query(int K, int P, const int32_t *row_ptr, const int32_t *col_
 int mc_resident_pack(int K, int V, int lhs_bits, int P, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                      const ResidentLayout &lay, int32_t *ptr, uint8_t *recs, int32_t *src, uint32_t *ends)
 {
-    const int64_t rbytes = 2 * MC_CHUNK + chunk_value_bytes(V, lhs_bits);
+    const int64_t cbytes = chunk_value_bytes(V, lhs_bits), rec_chunks = resident_rec_chunks(lay.nblk, V, lhs_bits), rbytes = rec_chunks * (2 * MC_CHUNK + cbytes);
+    const bool pairs = rec_chunks == 2;
     return with_put_vector(V, lhs_bits, [&](auto put) -> int {
         std::vector<int32_t> place;                 // interchange vector of each place of a list, -1: empty
         std::vector<int32_t> extra[16];             // vectors whose residue has more of them than the list has sets
@@ -386,17 +387,19 @@ int mc_resident_pack(int K, int V, int lhs_bits, int P, const int32_t *row_ptr, 
                     }
                 }
                 for (int st = 0; st < nsets; ++st) {
-                    const int64_t c = chunk + st / 4;
+                    const int64_t c = chunk + st / 4, second = pairs ? c & 1 : 0; // (second chunk of its record)
+                    uint8_t *rec = recs + (pairs ? c >> 1 : c) * rbytes, *vals = rec + (pairs ? 4 * MC_CHUNK : 2 * MC_CHUNK) + second * (cbytes / 4);
                     const int pair = (st % 4) / 2, h = st % 2;   // lane groups 2*pair, 2*pair + 1; slots 8h .. 8h + 7 of each
                     for (int t = 0; t < 16; ++t) {
                         const int slot = (2 * pair + t / 8) * 16 + 8 * h + t % 8;
                         const int32_t from = place[(size_t)st * 16 + t];
                         const int row = from >= 0 ? col_idx[from] - row0 : (t < nrows ? t : 0);
-                        uint8_t *rec = recs + c * rbytes;
-                        reinterpret_cast<uint16_t *>(rec)[row_position(slot)] = (uint16_t)((row >> 4) * 16 * lay.nt + (row & 15));
+                        const int at = row_position(slot);
+                        reinterpret_cast<uint16_t *>(rec)[pairs ? (at / 2 * 2 + second) * 2 + at % 2 : at] = (uint16_t)((row >> 4) * 16 * lay.nt + (row & 15));
                         src[c * MC_CHUNK + slot] = from;
                         if (from >= 0) {
-                            const int rc = put(rec + 2 * MC_CHUNK, slot, values, from);
+                            // (two chunks: a group of 16 slots of the other one after each of this one's)
+                            const int rc = put(vals + (pairs ? slot / 16 * (cbytes / 4) : 0), slot, values, from);
                             if (rc != MC_OK) return rc;
                         }
                     }

@@ -49,7 +49,7 @@ struct mc_mat {
     int nblk;                  // K-blocks
     int64_t blk_chunks;        // chunks over all (panel, block) lists
     int32_t *d_blk_ptr;        // P*nblk + 1
-    uint8_t *d_blk_recs;       // blk_chunks records (and RESIDENT_PADDING of zeros)
+    uint8_t *d_blk_recs;       // records of one or two chunks (and RESIDENT_PADDING of zeros)
     uint32_t *d_blk_ends;      // nblk == 1: a bit per chunk, set where a panel ends (and two words of zeros)
     int32_t *d_blk_src;        // blk_chunks * 64: interchange vector of each slot, -1 for padding
     int32_t *d_order;          // nblk > 1: P panel numbers by falling length (null: all panels have the same number of chunks)
@@ -86,8 +86,13 @@ int mc_pack_host_wide(int M, int K, int V, int lhs_bits, const int32_t *row_ptr,
 // a block's image being [row / 16][segment of 16 bytes][row % 16] with nt segments; the vectors of a (panel, block) list
 // (never empty: at least one chunk) are dealt into chunks of 64 such that the 16 rows which one LDS read addresses differ modulo 16 where possible.
 //   ptr    P*nblk + 1: first chunk of (panel p, block b) at [p*nblk + b]
-//   recs   nchunks records: 64 codes (uint16: (row / 16)*16*nt + row % 16, the place of the row's segment 0 in 16 bytes; the
-//          code of slot s at position (s/16)*16 + (s%8)*2 + (s%16)/8; padded slots name some row of the block), then the values in the layout of a chunk of mc_pack_host's slot_vals.  Zeroed by the caller.
+//   recs   a record per chunk: 64 codes (uint16: (row / 16)*16*nt + row % 16, the place of the row's segment 0 in 16 bytes; the
+//          code of slot s at position (s/16)*16 + (s%8)*2 + (s%16)/8; padded slots name some row of the block), then the values in the layout of a chunk
+//          of mc_pack_host's slot_vals.
+//          resident_half, one block (one plane of at most 8 rows, half of what a request of the MFMA's operand brings): a record per two
+//          chunks, whichever panels they belong to.  Word w of the first chunk's codes is word 2w of the record, that of the second 2w + 1;
+//          then the values of both by lane groups: 16 slots of the first, 16 of the second.
+//          Zeroed by the caller.
 //   src    nchunks*64: interchange vector of each slot, -1 for padding
 constexpr int RESIDENT_AHEAD = 8;     // records that a reader has requested ahead of its step, at most
 // A reader of n records requests `ahead` of them before its first step and one in every step, and takes whole turns of `ahead`
@@ -102,6 +107,8 @@ constexpr bool resident_padding_suffices(int ahead)
         if (resident_requests(n, ahead) > n + RESIDENT_PADDING) return false;
     return true;
 }
+constexpr bool resident_half(int V, int lhs_bits) { return V <= 8 && lhs_bits <= 8; }
+constexpr int resident_rec_chunks(int nblk, int V, int lhs_bits) { return nblk == 1 && resident_half(V, lhs_bits) ? 2 : 1; }
 constexpr int RESIDENT_SPLITS = 4096; // an operand with unequal panels has the first panel of every 1/4096 of its chunks listed
 struct ResidentLayout { int nt, block_rows, nblk; int64_t nchunks; };
 void mc_resident_query(int K, int P, const int32_t *row_ptr, const int32_t *col_idx, ResidentLayout *out);
@@ -151,7 +158,7 @@ struct SlabArgs {
     const int32_t *order, *splits; // see mc_mat
     int uniform_chunks;        // > 0: every panel has this many chunks (nblk == 1)
     int rec_bytes;             // bytes of a record
-    int64_t nchunks;           // records (RESIDENT_PADDING more follow)
+    int64_t nrecs;             // records (RESIDENT_PADDING more follow)
     const uint8_t *B;
     int64_t ldb_bytes;
     int row_bytes, K;
@@ -253,9 +260,10 @@ struct ValuesJob {
     const int32_t *chunk_vec;  // panels: first stored vector and number of vectors of each chunk
     const int32_t *blk_src;    // LDS-ordered copy (else null): the stored vector of each slot, -1 for padding
     const int32_t *merge_src;  // merged copy (else null): the operand's own vector behind each share of a merged vector, -1: zeros
-    uint8_t *dst;              // chunk c's values at c * rec_bytes + head_bytes
+    uint8_t *dst;              // record r's values at r * rec_bytes + head_bytes
     int64_t nchunks;
     int rec_bytes, head_bytes, V, first_block;
+    int rec_chunks;            // chunks of a record, 1 or 2 (2: their values by lane groups, see mc_resident_pack)
 };
 struct ValuesArgs {
     const uint8_t *src;        // interchange order, V values of `bits` per vector

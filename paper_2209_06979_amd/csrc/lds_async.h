@@ -94,4 +94,14 @@ template <int N, class F> __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
 }
 
+// ... f(0), f(1), ... up to N - 1 or to the first that returns false
+template <class F, int... I> __device__ __forceinline__ void static_while_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (void)(f(std::integral_constant<int, I>{}) && ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_while(F &&f)
+{
+    static_while_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
+}
+
 } // namespace mcu

@@ -8,16 +8,25 @@
 // other, each step reading the rows of one chunk of 64 vectors at the addresses that the operand's LDS-ordered copy
 // names.  B is fetched from L2 once per workgroup instead of once per stored vector.
 //
-// What bounds it: instruction issue.  A chunk of 64 vectors and 32 bytes of B is 2 KB of LDS reads, 0.6 - 1.2 KB of A operand
-// from L2 (each column tile reads all of A again) and two MFMAs, but its step is 17 instructions of each of four waves on a
-// SIMD, about 70 clocks; before the first step comes the fill, one line of 128 bytes per row of B whatever the tile's width
-// (3 - 5 us for 4096 rows), and the stores queue up in front of a wave's later loads (5 us of the first case below).
-// Whole calls, against the faster of the gather form and of the form with blocks of 1024 rows and separate filling waves that
-// this one replaced, and the kernel by itself in its two and the gather form on the operand as given / merged:
-//   16384 x 4096, 90 % empty, V = 8, N = 1024, fp16 out   58.0 -> 33.3 us    34.4 / 33.9 against 57.8 / 55.9
-//   4096 x 4096, half empty, V = 2, N = 512               22.6 -> 20.5       50.6 / 20.3 against 103.8 / 30.1   (calls now take the form of
-//                                                         spmm_dense_kernels.hip there, 15.4)
-//   3004 x 2900, 85 % empty, unequal panels, 16 x 8 bit   16.2 -> 10.3       10.1 - 11.1 / 10.1 - 10.6 against 11.9 / 12.2
+// What bounds it: no one unit.  A step is a chunk of 64 vectors and 32 bytes of B: 2 KB of LDS reads (11 clocks of a compute unit, measured), two
+// MFMAs (32 clocks of a SIMD), some 21 clocks of its other instructions, and the loads of its record.  A load takes a compute unit 16 clocks
+// where a lane asks for 8 or 16 bytes and 4.6 where it asks for 4, whatever the addresses and however many lanes are masked off; with a record
+// per chunk that is 20.6 clocks a step of each of four SIMDs, the longest part, half of it for operand rows that a panel of 8 rows does not
+// have.  Such panels have two chunks in a record, whose values come with one request and whose codes with one of 4 bytes: 10.3.  More chunks
+// cost 65 clocks a step then; the rest is fixed: launch, the fill before the first step, one line of 128 bytes per row of B whatever
+// the tile's width (2.4 clocks a row, 4.6 us for 4096 rows; which lanes fetch which pieces makes no difference), and per panel an epilogue of some 130 clocks
+// and stores that a wave's later loads queue up behind.
+// 16384 x 4096, V = 8, N = 1024, three operands in turn, replayed from a graph (us; a record per chunk and whole turns -> as it is):
+//   90 % empty, fp16 / int32            38.1 -> 32.4 / 41.2 -> 34.9     on merged panels, whose requests are full, 37.7 -> 36.6
+//   80 % empty, fp16                    54.2 -> 45.5
+//   4-bit values and B                  32.3 -> 31.4
+//   4096 rows instead of 16384          18.4 -> 16.2
+//   2048 columns (64-byte tiles)        21.9 -> 21.5, merged 22.1 -> 21.2
+// 10844 x 838, V = 4, L16-R4, N = 128 (short streams): 10.6 -> 8.7; whole calls of the first case 33.2 -> 29.9.
+// (8-byte stores by all lanes in the fp16 epilogue: 34.2; rows of B requested two or three steps ahead, sixteen chunks' records
+// ahead, ordinary stores instead of streaming ones: within 2 % either way; records of two chunks for full requests: up to 1.05x as long.)
+// Against the gather form, on the operand as given / merged: 4096 x 4096, half empty, V = 2, N = 512 50.6 / 20.3 against 103.8 / 30.1 (calls take
+// the form of spmm_dense_kernels.hip there, 15.4); 3004 x 2900, 85 % empty, V = 4, unequal panels, 16 x 8 bit 10.1 - 11.1 / 10.1 - 10.6 against 11.9 / 12.2.
 // Three things keep the LDS reads at their full rate (190 bytes per clock and compute
 // unit measured, random rows reach 81):
 //   - the LDS image is [row / 16][16-byte segment][row % 16]: a segment of 16 consecutive rows covers all banks once,
@@ -44,12 +53,12 @@ using mcu::lds_v2i;
 typedef __attribute__((address_space(1))) const void gptr_t;
 typedef __attribute__((address_space(3))) void lptr_t;
 
-// Operands of a chunk (A values and row codes) are requested this many chunks ahead: they come from L2 or beyond, one
-// chunk step is far shorter than that latency, and the stores of a finished panel, which a wave's later loads queue up
-// behind, take longer still.  (As many as the registers allow.  The last turn's surplus requests go beyond the wave's chunks,
+// Records (A values and row codes of a chunk, or of two) are requested this many ahead: they come from L2 or beyond, a
+// step is far shorter than that latency, and the stores of a finished panel, which a wave's later loads queue up
+// behind, take longer still.  (As many as the registers allow.  The last turn's surplus requests go beyond the wave's records,
 // at the end of the copy into its padding: resident_requests in internal.h counts them.)
-template <int LB, bool R4, int NT> constexpr int ahead = (R4 && NT == 4) ? (LB == 16 ? 2 : 4) : RESIDENT_AHEAD;
-constexpr int PFB = 3; // in the K-blocked form, whose accumulators need the registers
+template <int LB, bool R4, int NT, bool HALF> constexpr int ahead = HALF ? (R4 && NT == 4 ? 2 : 4) : (R4 && NT == 4) ? (LB == 16 ? 2 : 4) : RESIDENT_AHEAD;
+constexpr int PFB = 3; // (records of one chunk) in the K-blocked form, whose accumulators need the registers
 
 // How a wave walks through its panels.
 //   STREAM  all of K is resident: consecutive panels, whose chunks are one stream in memory; the last chunk of a panel
@@ -59,14 +68,18 @@ constexpr int PFB = 3; // in the K-blocked form, whose accumulators need the reg
 enum Walk { STREAM, SHARED, BLOCKS };
 
 // NT: 16-byte segments of the column tile.  OUT: type of the result (SlabArgs::float_out), -1: decided at run time.
-template <int LB, bool R4, int NT, Walk WALK, int OUT>
+// HALF: panels of at most 8 rows and one plane (resident_half), two chunks in a record, whose values share one request.
+template <int LB, bool R4, int NT, Walk WALK, int OUT, bool HALF>
 __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
 {
     constexpr bool L16 = (LB == 16);
     constexpr int NACC = NT * (R4 ? 2 : 1);              // accumulators (v4i) of one panel
     constexpr int SH = R4 ? (LB == 4 ? 8 : 4) : 0;       // scale carried by widened nibbles
-    constexpr int PF = ahead<LB, R4, NT>, PPW = R4 ? 4 : 8;
+    constexpr int PF = ahead<LB, R4, NT, HALF>, PPW = R4 ? 4 : 8;
+    constexpr int CH = HALF ? 2 : 1;                     // chunks of a record, each with accumulators of its own
+    static_assert(!HALF || (LB != 16 && WALK != BLOCKS), "records of two chunks: one plane, all of B's rows at once");
     static_assert(resident_padding_suffices(PF), "the walk stays inside the copy and its padding");
+    static_assert(PF >= 2, "the next record's codes are read before this record's set is refilled");
     const int float_out = OUT < 0 ? a.float_out : OUT;
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
@@ -104,27 +117,40 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
     };
 
     // ---- one chunk ---------------------------------------------------------------------------------------
-    // A record of the copy is a chunk's codes followed by its values.  A lane's word of codes: the LDS places (in 16 bytes)
-    // of the rows in slots g*16 + ii (low half) and g*16 + 8 + ii.
+    // A record of the copy is the codes of one chunk, or of two, followed by the values.  A word of codes: the LDS places (in 16 bytes)
+    // of the rows in slots g*16 + ii (low half) and g*16 + 8 + ii.  Two lanes need the same word; with two chunks in a record
+    // even lanes load the first chunk's and odd lanes the second's, and hand them over (HANDED; not with tiles of 64 bytes, whose
+    // steps have more to do for the VALU: within 2 % there).
+    // HALF: the values of both chunks in one request, the first chunk's rows in columns 0 .. 7 of the MFMA's operand, the second's in
+    // columns 8 .. 15 (the other columns of each product are not looked at).
     // Records are read through a buffer descriptor: a scalar offset moves from record to record, the lanes' offsets stay.
     // (The descriptor's range check leaves the scalar offset out: what keeps a stream inside the copy is its padding.)
-    const unsigned lane_r = (g * 8 + ii) * 4;
-    const int v_of_j = (L16 ? (j & 7) : j) < a.V ? (L16 ? (j & 7) : j) : 0; // (columns beyond the panel's rows get a copy of row 0)
-    const unsigned lane_a = 2 * MC_CHUNK + (L16 ? g * 32 * a.V + (j >> 3) * 16 * a.V + v_of_j * 16
-                                                : (LB == 4 ? g * 8 * a.V + v_of_j * 8 : g * 16 * a.V + v_of_j * 16));
-    auto records_from = [&](int64_t chunk) {              // descriptor of the records from this one on
-        const int64_t left = (a.nchunks + RESIDENT_PADDING - chunk) * a.rec_bytes;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.recs) + chunk * a.rec_bytes, 0, (int)(left < 0x7fffffff ? left : 0x7fffffff),
+    constexpr bool HANDED = HALF && NT == 2;
+    constexpr int WORDS = HALF && !HANDED ? 2 : 1;        // of codes of a record that a lane loads
+    constexpr int VALUES = CH * 2 * MC_CHUNK;             // where they begin
+    const unsigned lane_r = HANDED ? lane * 4 : (g * 8 + ii) * 4 * CH;
+    const int j8 = L16 || HALF ? (j & 7) : j, v_of_j = j8 < a.V ? j8 : 0; // (columns beyond the panel's rows get a copy of row 0)
+    constexpr int PIECE = LB == 4 ? 8 : 16;               // bytes of a lane
+    const unsigned lane_a = VALUES + (L16 || HALF ? (g * 2 + (j >> 3)) * PIECE * a.V + v_of_j * PIECE : g * PIECE * a.V + v_of_j * PIECE);
+    auto records_from = [&](int64_t record) {             // descriptor of the records from this one on
+        const int64_t left = (a.nrecs + RESIDENT_PADDING - record) * a.rec_bytes;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.recs) + record * a.rec_bytes, 0, (int)(left < 0x7fffffff ? left : 0x7fffffff),
                                                  0x00020000);
     };
-    auto load_rec = [&](__amdgpu_buffer_rsrc_t recs, int offset, v4i &va, int &r) { // offset: wave-uniform
-        r = __builtin_amdgcn_raw_buffer_load_b32(recs, lane_r, offset, 0);
+    auto load_rec = [&](__amdgpu_buffer_rsrc_t recs, int offset, v4i &va, int (&r)[WORDS]) { // offset: wave-uniform
+        r[0] = __builtin_amdgcn_raw_buffer_load_b32(recs, lane_r, offset, 0);
+        if (WORDS == 2) r[WORDS - 1] = __builtin_amdgcn_raw_buffer_load_b32(recs, lane_r + 4, offset, 0);
         if (LB == 4) {
             const v2i x = __builtin_amdgcn_raw_buffer_load_b64(recs, lane_a, offset, 0);
             va = (v4i){x.x, x.y, 0, 0};
         } else {
             va = __builtin_amdgcn_raw_buffer_load_b128(recs, lane_a, offset, 0);
         }
+    };
+    // the word of codes of chunk h of a record
+    auto codes_of = [&](const int (&word)[WORDS], auto H) -> int {
+        if (!HANDED) return word[WORDS == 2 ? decltype(H)::value : 0];
+        return __builtin_amdgcn_mov_dpp(word[0], decltype(H)::value ? 0xF5 : 0xA0, 0xF, 0xF, true); // quad_perm [1,1,3,3] / [0,0,2,2]
     };
     // the dense operand of a chunk: NT segments of the 64 rows its codes name, transposed
     // (one instruction per address: half of r * 16 + h8.  The kernel has no other LDS, so the image starts at address 0.)
@@ -158,9 +184,12 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
     // in j < 8, low plane in j >= 8); a byte column of nibbles is two output columns.  Everything that does not change
     // from panel to panel is worked out here: the epilogue is a good part of a short panel's instructions.
     const int ncols = R4 ? a.row_bytes * 2 : a.row_bytes, es = float_out == 2 ? 2 : 4;
-    constexpr bool PAIRS = !R4 && NT % 2 == 0;            // fp16: two accumulators become 8 neighbouring columns of a lane
-    const int col0 = R4 ? 2 * (nb0 + 4 * g) : ((PAIRS && float_out == 2) ? nb0 + (g & 1) * 16 + (g >> 1) * 8 : nb0 + 4 * g);
-    uint8_t *const out0 = static_cast<uint8_t *>(a.C) + ((int64_t)j * a.ldc + col0) * es;
+    // HALF: what a panel's rows have in columns 0 .. 7 of segment ct stays there, those of segment ct + 1 go to columns 8 .. 15 (`whole`).
+    constexpr int NOUT = HALF ? NACC / 2 : NACC;
+    const int jrow = HALF ? (j & 7) : j;
+    const int col0 = HALF ? (R4 ? 2 : 1) * (nb0 + 16 * (j >> 3) + 4 * g)
+                          : R4 ? 2 * (nb0 + 4 * g) : (float_out == 2 ? nb0 + (g & 1) * 16 + (g >> 1) * 8 : nb0 + 4 * g);
+    uint8_t *const out0 = static_cast<uint8_t *>(a.C) + ((int64_t)jrow * a.ldc + col0) * es;
     const int64_t panel_bytes = (int64_t)a.V * a.ldc * es;
     auto finish = [&](v4i s) -> v4i {   // every plane sum is exact in int32 (4-bit B: after its shift); the recombination wraps
         if (R4) s = s >> SH;
@@ -179,30 +208,41 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
         return f;
     };
     // o: out0 of the panel; rows_left: rows of C from the panel's first on (a merged panel may run past the last row)
-    auto store_panel = [&](const v4i (&acc)[NACC], uint8_t *o, int rows_left) {
-        v4i fin[NACC];
+    constexpr int PER = HALF ? 2 : 1, NSEG = NT / PER;    // segments of an accumulator; steps of that many
+    auto store_panel = [&](const v4i (&acc)[NOUT], uint8_t *o, int rows_left) {
+        v4i fin[NOUT];
 #pragma unroll
-        for (int t = 0; t < NACC; ++t) fin[t] = finish(acc[t]);
-        const bool live = j < (rows_left < a.V ? rows_left : a.V);
+        for (int t = 0; t < NOUT; ++t) fin[t] = finish(acc[t]);
+        const bool live = jrow < (rows_left < a.V ? rows_left : a.V);
         if constexpr (R4) {
 #pragma unroll
-            for (int ct = 0; ct < NT; ++ct) {
+            for (int ct = 0; ct < NSEG; ++ct) {
                 const v4i e = fin[2 * ct], d = fin[2 * ct + 1];
                 const v4i s0 = {e.x, d.x, e.y, d.y}, s1 = {e.z, d.z, e.w, d.w};
                 if (float_out == 2) {
                     const mcu::v4h h0 = mcu::to_half4(scaled(s0)), h1 = mcu::to_half4(scaled(s1));
-                    if (live && col0 + 32 * ct < ncols) __builtin_nontemporal_store((mcu::v8h){h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w}, reinterpret_cast<mcu::v8h *>(o + ct * 64));
+                    if (live && col0 + 32 * PER * ct < ncols) __builtin_nontemporal_store((mcu::v8h){h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w}, reinterpret_cast<mcu::v8h *>(o + ct * 64 * PER));
                 } else {
                     const v4i t0 = float_out ? __builtin_bit_cast(v4i, scaled(s0)) : s0, t1 = float_out ? __builtin_bit_cast(v4i, scaled(s1)) : s1;
-                    if (live && col0 + 32 * ct < ncols) {
-                        __builtin_nontemporal_store(t0, reinterpret_cast<v4i *>(o + ct * 128));
-                        __builtin_nontemporal_store(t1, reinterpret_cast<v4i *>(o + ct * 128 + 16));
+                    if (live && col0 + 32 * PER * ct < ncols) {
+                        __builtin_nontemporal_store(t0, reinterpret_cast<v4i *>(o + ct * 128 * PER));
+                        __builtin_nontemporal_store(t1, reinterpret_cast<v4i *>(o + ct * 128 * PER + 16));
                     }
                 }
             }
+        } else if (HALF && float_out == 2) {
+#pragma unroll
+            for (int ct = 0; ct < NSEG; ++ct) {
+                // the columns of odd lane groups beside those of even ones (stores of 8 bytes by all lanes: 34.2 us where 16 by half of them take 32.5)
+                const v2i x = __builtin_bit_cast(v2i, mcu::to_half4(scaled(fin[ct])));
+                const auto s0 = __builtin_amdgcn_permlane16_swap((unsigned)x.x, (unsigned)x.x, false, false);
+                const auto s1 = __builtin_amdgcn_permlane16_swap((unsigned)x.y, (unsigned)x.y, false, false);
+                if (live && !(g & 1) && col0 + 32 * ct < ncols)
+                    __builtin_nontemporal_store((v4i){(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]}, reinterpret_cast<v4i *>(o + ct * 64));
+            }
         } else if (float_out == 2) {
 #pragma unroll
-            for (int ct = 0; ct < NT; ct += 2) {
+            for (int ct = 0; ct < (HALF ? 0 : NT); ct += 2) {
                 // lane groups hold columns 4g .. 4g+3 of segments ct and ct + 1; after the exchange of odd groups of the one
                 // with even groups of the other, groups 0 .. 3 hold columns 0-7, 16-23, 8-15, 24-31
                 v2i x = __builtin_bit_cast(v2i, mcu::to_half4(scaled(fin[ct]))), y = __builtin_bit_cast(v2i, mcu::to_half4(scaled(fin[ct + 1])));
@@ -213,9 +253,9 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
             }
         } else {
 #pragma unroll
-            for (int ct = 0; ct < NT; ++ct) {
+            for (int ct = 0; ct < NSEG; ++ct) {
                 const v4i t = float_out ? __builtin_bit_cast(v4i, scaled(fin[ct])) : fin[ct];
-                if (live && col0 + 16 * ct < ncols) __builtin_nontemporal_store(t, reinterpret_cast<v4i *>(o + ct * 64));
+                if (live && col0 + 16 * PER * ct < ncols) __builtin_nontemporal_store(t, reinterpret_cast<v4i *>(o + ct * 64 * PER));
             }
         }
     };
@@ -230,7 +270,7 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
             p = __builtin_amdgcn_readfirstlane(a.splits[(int)((int64_t)RESIDENT_SPLITS * at / streams)]);
             p_end = __builtin_amdgcn_readfirstlane(a.splits[(int)((int64_t)RESIDENT_SPLITS * (at + 1) / streams)]);
         }
-        int c0 = 0, n = 0;                                // the wave's chunks: n from c0 on
+        int c0 = 0, n = 0, before = 0;                    // the wave's chunks: n from c0 on; and one before them if c0 is the second of its record
         if (p < p_end) {
             c0 = a.uniform_chunks > 0 ? p * a.uniform_chunks : __builtin_amdgcn_readfirstlane(a.blk_ptr[p]);
             n = (a.uniform_chunks > 0 ? p_end * a.uniform_chunks : __builtin_amdgcn_readfirstlane(a.blk_ptr[p_end])) - c0;
@@ -239,6 +279,9 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
                 c0 += all * k / a.wpp;
                 n = all * (k + 1) / a.wpp - all * k / a.wpp;
             }
+            if (HALF && n > 0) before = c0 & 1;
+            c0 -= before;
+            n += before;
         }
         // lane l: which of the chunks 8 l .. 8 l + 7 after chunk c end their panel
         auto load_ends = [&](int c) -> unsigned {
@@ -246,10 +289,10 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
             return __builtin_amdgcn_alignbit(a.ends[word + 1], a.ends[word], bit & 31);
         };
         unsigned ends = WALK == STREAM ? load_ends(c0) : 0u;
-        const __amdgpu_buffer_rsrc_t recs = records_from(c0);
+        const __amdgpu_buffer_rsrc_t recs = records_from(c0 / CH);
         int offset = 0;
         v4i ring_a[PF];
-        int ring_r[PF];
+        int ring_r[PF][WORDS];
 #pragma unroll
         for (int d = 0; d < PF; ++d) {
             load_rec(recs, offset, ring_a[d], ring_r[d]);
@@ -258,52 +301,93 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
         fill(0);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();                                  // the tile is complete
-        v4i acc[NACC];
+        v4i acc[CH][NACC];
+        auto clear = [&]() {
 #pragma unroll
-        for (int i = 0; i < NACC; ++i) acc[i] = (v4i){0, 0, 0, 0};
+            for (int h = 0; h < CH; ++h)
+#pragma unroll
+                for (int i = 0; i < NACC; ++i) acc[h][i] = (v4i){0, 0, 0, 0};
+        };
+        // HALF: a panel's rows are the sum of columns 0 .. 7 of the first chunks' products and 8 .. 15 of the second ones'; two segments
+        // come out of it side by side, so that all lanes have something to finish and to store
+        auto whole = [&](v4i (&sum)[NOUT]) {
+            if constexpr (!HALF) {
+#pragma unroll
+                for (int i = 0; i < NACC; ++i) sum[i] = acc[0][i];
+            } else {
+                constexpr int Q = R4 ? 2 : 1;
+                const bool low = j < 8;
+#pragma unroll
+                for (int i = 0; i < NOUT; ++i) {
+                    const v4i &x0 = acc[0][i / Q * 2 * Q + i % Q], &x1 = acc[CH - 1][i / Q * 2 * Q + i % Q], &y0 = acc[0][i / Q * 2 * Q + Q + i % Q], &y1 = acc[CH - 1][i / Q * 2 * Q + Q + i % Q];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int mine = low ? x0[r] : y1[r], other = low ? y0[r] : x1[r];
+                        sum[i][r] = mine + __builtin_amdgcn_update_dpp(0, other, 0x128, 0xF, 0xF, false); // row_ror:8: lane j + 8
+                    }
+                }
+            }
+        };
+        clear();
         if (n > 0) {
-            // Step d multiplies the chunk of register set d, whose rows of B were requested a step before, requests the
-            // rows of the next chunk and refills the set with the operands of the chunk PF further on: compile-time set
-            // numbers and unconditional loads, so the compiler's own counted waits are exact.  Every instruction counts
-            // (a SIMD issues about one every four clocks over its four waves): the loop has no exit but its end -- surplus
-            // steps run into the next stream's chunks and nothing of theirs is stored (SHARED, where they would spoil the
-            // sum: counted) -- and a panel's end is one bit test.
+            // A step multiplies a chunk whose rows of B were requested a step before and requests the rows of the next
+            // chunk; after the last chunk of register set d the set is refilled with the record PF further on: compile-time set
+            // numbers and unconditional loads, so the compiler's own counted waits are exact.  Every instruction counts:
+            // the loop runs whole turns, only the last one ends after the record that is the last -- the first step may belong to the stream
+            // before, one at the end to the next, and nothing of theirs is stored (SHARED, where they would spoil the sum: counted) --
+            // and a panel's end is one bit test.  (Surplus steps up to a whole turn: 1.05x as long at 16384 x 2048 on merged
+            // panels; an exit after every record of every turn 1.05x at 80 % empty, 4096 columns.)
             v4i bop[2][NT];
+            p -= WALK == STREAM ? before : 0;
+            const int p_first = p + before;
             uint8_t *o = out0 + p * panel_bytes;
             int rows_left = a.rows - p * a.V;
-            read_b(ring_r[0], bop[0]);
-            for (int i = 0; i < n; i += PF) {
+            read_b(codes_of(ring_r[0], std::integral_constant<int, 0>{}), bop[0]);
+            // STEPS steps from step i on (Last: as many as are left, in whole records)
+            constexpr int STEPS = CH * PF;
+            auto turn = [&](int i, auto Last) {
                 const unsigned mask = WALK == STREAM ? __builtin_amdgcn_readlane(ends, (i >> 3) & 63) >> (i & 7) : 0u;
-#pragma unroll
-                for (int d = 0; d < PF; ++d) {
-                    read_b(ring_r[(d + 1) % PF], bop[(d + 1) & 1]);
-                    if (WALK == STREAM || i + d < n) multiply(acc, ring_a[d], bop[d & 1]);
-                    load_rec(recs, offset, ring_a[d], ring_r[d]);
-                    offset += a.rec_bytes;
-                    if (WALK == STREAM && (mask & (1u << d))) {
-                        if (p < p_end) store_panel(acc, o, rows_left);
+                mcu::static_while<STEPS>([&](auto Dc) -> bool {
+                    constexpr int c = decltype(Dc)::value, d = c / CH, h = c % CH, next = (c + 1) % STEPS;
+                    read_b(codes_of(ring_r[next / CH], std::integral_constant<int, next % CH>{}), bop[(c + 1) & 1]);
+                    if (WALK == STREAM || (i + c < n && (c > 0 || i >= before))) multiply(acc[h], ring_a[d], bop[c & 1]);
+                    if (h == CH - 1) {
+                        load_rec(recs, offset, ring_a[d], ring_r[d]);
+                        offset += a.rec_bytes;
+                    }
+                    if (WALK == STREAM && (mask & (1u << c))) {
+                        if ((unsigned)(p - p_first) < (unsigned)(p_end - p_first)) {
+                            v4i sum[NOUT];
+                            whole(sum);
+                            store_panel(sum, o, rows_left);
+                        }
                         ++p;
                         o += panel_bytes;
                         rows_left -= a.V;
-#pragma unroll
-                        for (int q = 0; q < NACC; ++q) acc[q] = (v4i){0, 0, 0, 0};
+                        clear();
                     }
-                }
-                if (WALK == STREAM && ((i + PF) & 511) == 0 && i + PF < n) ends = load_ends(c0 + i + PF);
-            }
+                    return !decltype(Last)::value || h < CH - 1 || i + c + 1 < n;
+                });
+                if (WALK == STREAM && ((i + STEPS) & 511) == 0 && i + STEPS < n) ends = load_ends(c0 + i + STEPS);
+            };
+            int i = 0;
+            for (; i + (WALK == STREAM ? STEPS : 1) <= n; i += STEPS) turn(i, std::false_type{});
+            if (WALK == STREAM && i < n) turn(i, std::true_type{});
         }
         if constexpr (WALK == SHARED) {
             // few panels: the waves that share one add up their tiles in LDS (B is no longer needed)
             __syncthreads();
-            v4i *part = reinterpret_cast<v4i *>(lds) + (int64_t)w * (NACC * 64) + lane;
+            v4i mine[NOUT];
+            whole(mine);
+            v4i *part = reinterpret_cast<v4i *>(lds) + (int64_t)w * (NOUT * 64) + lane;
 #pragma unroll
-            for (int i = 0; i < NACC; ++i) part[i * 64] = acc[i];
+            for (int i = 0; i < NOUT; ++i) part[i * 64] = mine[i];
             __syncthreads();
             if (k == 0 && p < p_end) {
                 for (int o = 1; o < a.wpp; ++o)
 #pragma unroll
-                    for (int i = 0; i < NACC; ++i) acc[i] += part[(o * NACC + i) * 64];
-                store_panel(acc, out0 + p * panel_bytes, a.rows - p * a.V);
+                    for (int i = 0; i < NOUT; ++i) mine[i] += part[(o * NOUT + i) * 64];
+                store_panel(mine, out0 + p * panel_bytes, a.rows - p * a.V);
             }
         }
     } else {
@@ -311,8 +395,8 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
         // A list of n chunks is walked in max(1, ceil(n / PFB)) groups of PFB steps whose surplus steps do nothing; step d
         // of a group refills register set d with the operands of step d of the next group, of this list or the next one.
         v4i ring_a[PFB];
-        int ring_r[PFB];
-        auto load_chunk = [&](int c, v4i &va, int &r) { load_rec(records_from(c), 0, va, r); };
+        int ring_r[PFB][WORDS];
+        auto load_chunk = [&](int c, v4i &va, int (&r)[WORDS]) { load_rec(records_from(c), 0, va, r); };
         auto start_ring = [&](int first, int len) {
 #pragma unroll
             for (int d = 0; d < PFB; ++d) load_chunk(len > 0 ? first + (d < len ? d : len - 1) : 0, ring_a[d], ring_r[d]);
@@ -326,7 +410,7 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
                     const int pos = gi * PFB + d;
                     if (pos < len) {
                         v4i bop[NT];
-                        read_b(ring_r[d], bop);
+                        read_b(ring_r[d][0], bop);
                         multiply(acc, ring_a[d], bop);
                     }
                     int c;
@@ -379,9 +463,9 @@ __global__ __launch_bounds__(1024) void spmm_resident_kernel(SlabArgs a)
     }
 }
 
-template <int LB, bool R4, int NT, Walk WALK, int OUT> hipError_t launch_one(const SlabArgs &a, hipStream_t s)
+template <int LB, bool R4, int NT, Walk WALK, int OUT, bool HALF = false> hipError_t launch_one(const SlabArgs &a, hipStream_t s)
 {
-    auto kern = spmm_resident_kernel<LB, R4, NT, WALK, OUT>;
+    auto kern = spmm_resident_kernel<LB, R4, NT, WALK, OUT, HALF>;
     const int units = ((a.block_rows + 15) / 16 * a.nt + 3) / 4;
     int lds = units * 1024;
     if (WALK == SHARED) { // the tiles of the waves that share a panel meet in the same memory
@@ -398,20 +482,28 @@ template <int LB, bool R4, int NT, Walk WALK, int OUT> hipError_t launch_one(con
     return launch_kernel(kern, grid, block, lds, s, a);
 }
 
-template <int LB, bool R4, int NT> hipError_t launch_walk(const SlabArgs &a, hipStream_t s)
+template <int LB, bool R4, int NT, bool HALF> hipError_t launch_walk(const SlabArgs &a, hipStream_t s)
 {
-    if (a.wpp > 1) return launch_one<LB, R4, NT, SHARED, -1>(a, s);
+    if (a.wpp > 1) return launch_one<LB, R4, NT, SHARED, -1, HALF>(a, s);
     // (the epilogue is part of every step of the unrolled loop: one output type per kernel keeps it small)
-    if (a.float_out == 0) return launch_one<LB, R4, NT, STREAM, 0>(a, s);
-    if (a.float_out == 1) return launch_one<LB, R4, NT, STREAM, 1>(a, s);
-    return launch_one<LB, R4, NT, STREAM, 2>(a, s);
+    if (a.float_out == 0) return launch_one<LB, R4, NT, STREAM, 0, HALF>(a, s);
+    if (a.float_out == 1) return launch_one<LB, R4, NT, STREAM, 1, HALF>(a, s);
+    return launch_one<LB, R4, NT, STREAM, 2, HALF>(a, s);
+}
+
+template <int LB, bool R4, bool HALF> hipError_t launch_tile(const SlabArgs &a, int nt, hipStream_t s)
+{
+    if (nt == 4) return launch_walk<LB, R4, 4, HALF>(a, s);
+    return launch_walk<LB, R4, 2, HALF>(a, s);
 }
 
 template <int LB, bool R4> hipError_t launch_nt(const SlabArgs &a, int nt, hipStream_t s)
 {
     if (a.nblk > 1) return launch_one<LB, R4, 2, BLOCKS, -1>(a, s);
-    if (nt == 4) return launch_walk<LB, R4, 4>(a, s);
-    return launch_walk<LB, R4, 2>(a, s);
+    if constexpr (LB != 16) {
+        if (resident_half(a.V, LB)) return launch_tile<LB, R4, true>(a, nt, s);
+    }
+    return launch_tile<LB, R4, false>(a, nt, s);
 }
 
 } // namespace

@@ -57,7 +57,11 @@ template <int BITS, int V> __global__ __launch_bounds__(256) void set_values_ker
     }
     const int rows = job.V, shares = rows / V;                   // a merged vector's rows come from `shares` vectors
     const int octets = rows > 8 ? 2 : 1, per = shares / octets;  // rows are handled eight at a time
-    uint8_t *const dst = job.dst + chunk * job.rec_bytes + job.head_bytes;
+    // (two chunks in a record: a group of 16 slots of each in turn)
+    constexpr int GROUP = BITS == 4 ? 8 : 16 * PL;               // bytes of a row's 16 slots
+    const int per_rec = job.rec_chunks;
+    uint8_t *const dst = job.dst + (per_rec == 2 ? chunk >> 1 : chunk) * job.rec_bytes + job.head_bytes +
+                         (g * per_rec + (per_rec == 2 ? (int)chunk & 1 : 0)) * (GROUP * rows);
     for (int o = 0; o < octets; ++o) {
         // all sources, then all values: each a round trip to memory
         int64_t from[MOST];
@@ -93,16 +97,16 @@ template <int BITS, int V> __global__ __launch_bounds__(256) void set_values_ker
         mcu::lgkm_wait();                                        // (LDS executes a wave's instructions in order: for the compiler)
         __builtin_amdgcn_wave_barrier();
         // lane l of a group of 16 slots: row l % 8 of the octet, slots 0 .. 7 (l < 8) or 8 .. 15
-        const int row = o * 8 + (l & 7), half = l >> 3;
+        const int row = o * 8 + (l & 7), up = l >> 3;
 #pragma unroll
         for (int p = 0; p < PL; ++p) {
             v2i d = mcu::lds_read_tr8(&stage[w][p][g * 16 + (l >> 1) + 8 * (l & 1)]);
             if constexpr (BITS == 4) {                           // byte b: slots b and b + 8
-                const v2i up = {__builtin_amdgcn_update_dpp(0, d.x, 0x128, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, d.y, 0x128, 0xF, 0xF, false)};
-                d = (v2i){d.x | up.x << 4, d.y | up.y << 4};
-                if (row < rows && half == 0) *reinterpret_cast<v2i *>(dst + (g * rows + row) * 8) = d;
+                const v2i odd = {__builtin_amdgcn_update_dpp(0, d.x, 0x128, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, d.y, 0x128, 0xF, 0xF, false)};
+                d = (v2i){d.x | odd.x << 4, d.y | odd.y << 4};
+                if (row < rows && up == 0) *reinterpret_cast<v2i *>(dst + row * 8) = d;
             } else if (row < rows) {
-                *reinterpret_cast<v2i *>(dst + ((g * PL + p) * rows + row) * 16 + half * 8) = d;
+                *reinterpret_cast<v2i *>(dst + (p * rows + row) * 16 + up * 8) = d;
             }
         }
         mcu::lgkm_wait();                                        // the next octet goes to the same place
