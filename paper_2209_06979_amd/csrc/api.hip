@@ -443,7 +443,8 @@ DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_byt
 // Whether the LDS-ordered copy is built: the form is expected to be the fastest for wide rows of B, or for rows of two lines; by a
 // tenth at least where the merged copy has such a copy already.  (Of 1385 drawn operands 33 then have both, with 2 %
 // 106; the forms they run in lose the same 2.0 % over the best on average.)
-// of: the operand whose merged copy A is (else null); the same holds against the copy that it could have.
+// of: the operand whose merged copy A is (else null); the same holds against the copy that it could have, where that has the shorter
+// records of panels of 8 rows (otherwise the merged copy's is nearly always the faster one).
 bool resident_worth_building(const mc_mat *A, const mc_mat *of)
 {
     const mc_options automatic = {};
@@ -460,7 +461,7 @@ bool resident_worth_building(const mc_mat *A, const mc_mat *of)
                     best = std::min(best, 0.9 * m.us);
                 }
             }
-            if (of && of->blk_chunks) {
+            if (of && of->blk_chunks && resident_half(of->V, of->lhs_bits)) {
                 SlabPlan given;
                 plan_slab(of, row_bytes, r4, 4, automatic, &given);
                 best = std::min(best, 0.9 * given.us);
