@@ -934,11 +934,14 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
 }
 
 namespace {
+// (the forms with 32-bit lane offsets work out a lane's offset into B with one 24-bit multiplication)
+inline bool spmm_short_b(int K, int64_t ldb_bytes, int row_bytes)
+{
+    return (int64_t)(K - 1) * ldb_bytes + row_bytes < ((int64_t)1 << 32) && K <= (1 << 24) && ldb_bytes < (1 << 24);
+}
 inline int spmm_stages_for(const mc_options &o, int K, int64_t ldb_bytes, int row_bytes)
 {
-    // (the two-chunk form works out a lane's offset into B with one 24-bit multiply-add)
-    return (o.spmm_stages != 1 && (int64_t)(K - 1) * ldb_bytes + row_bytes < ((int64_t)1 << 32) && K <= (1 << 24) &&
-            ldb_bytes < (1 << 24)) ? 2 : 1;
+    return o.spmm_stages != 1 && spmm_short_b(K, ldb_bytes, row_bytes) ? 2 : 1;
 }
 
 // The form one SpMM call takes: the operand or its merged copy, and whether rows of B are resident in LDS (then plan is
@@ -1043,6 +1046,7 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
         return MC_OK;
     }
     a.stages = spmm_stages_for(o, A->K, a.ldb_bytes, a.row_bytes);
+    a.short_b = spmm_short_b(A->K, a.ldb_bytes, a.row_bytes);
     a.uniform_chunks = A->uniform_chunks;
     a.max_unit_chunks = A->max_panel_chunks;
     const bool use_items = A->n_items && o.spmm_splitting != -1 && out_mode == 0;
@@ -1171,7 +1175,7 @@ extern "C" int mc_probe_spmm_phases(const mc_mat *A, const void *B_dev, int N, i
     a.B = static_cast<const uint8_t *>(B_dev); a.ldb_bytes = ldb; a.row_bytes = N;
     a.C = C_dev; a.ldc = ldc;
     a.P = A->P; a.V = A->V; a.rows = A->M; a.batch = 1; a.out_scale = 1.f;
-    a.stages = 2; a.max_unit_chunks = A->max_panel_chunks; a.uniform_chunks = A->uniform_chunks;
+    a.stages = 2; a.short_b = 1; a.max_unit_chunks = A->max_panel_chunks; a.uniform_chunks = A->uniform_chunks;
     a.trace = reinterpret_cast<long long *>(trace_dev);
     MC_HIP(launch_spmm_phase_probe(a, static_cast<hipStream_t>(stream)));
     return MC_OK;
@@ -1437,6 +1441,7 @@ int attention_pipeline(const uint8_t *Q, const uint8_t *Km, const uint8_t *Vm, i
     m.row_bytes = row_bytes; m.C = O; m.ldc = o_token_stride; m.C_batch_stride = o_head_stride;
     m.P = mask->P; m.V = 8; m.rows = mask->M; m.batch = heads; m.float_out = out_f16 ? 2 : 1; m.out_scale = s_p * s_v;
     m.stages = spmm_stages_for(o, mask->K, m.ldb_bytes, m.row_bytes);
+    m.short_b = spmm_short_b(mask->K, m.ldb_bytes, m.row_bytes);
     m.uniform_chunks = mask->uniform_chunks;
     m.max_unit_chunks = mask->max_panel_chunks;
     if (split_panels) {

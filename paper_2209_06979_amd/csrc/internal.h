@@ -138,7 +138,8 @@ struct SpmmArgs {
     // add their int32 results into C with atomics; C's rows of those panels are cleared first.
     const int32_t *items;
     int n_units;               // items, or P
-    int stages;                // chunks in flight per wave: 1 or 2 (2 needs B to span less than 4 GiB)
+    int stages;                // chunks in flight per wave: 1 or 2 (2 needs short_b)
+    int short_b;               // B spans less than 4 GiB, its rows and their length fit 24 bits
     int uniform_chunks;        // > 0: every panel has this many chunks and starts at panel * uniform_chunks * 64 (panel_ptr is not read)
     int ntiles, tile_shift;    // filled by the launcher: column tiles (workgroups) per unit, and their log2 (-1: not a power of two)
     int max_unit_chunks;       // chunks of the longest unit of work (panel or work item)

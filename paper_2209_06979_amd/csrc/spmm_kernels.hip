@@ -51,16 +51,16 @@ using mcu::load_a;
 typedef __attribute__((address_space(1))) const void gptr_t;
 typedef __attribute__((address_space(3))) void lptr_t;
 
-// NS: chunks in flight per wave.  1: the copies are issued through the compiler's builtin, which
-// makes it wait for all of them before the first LDS read (any extent of B, any panel length).
-// 2: the copies are issued from inline assembly into two alternating stages and only the older
-// chunk is waited for (counted s_waitcnt); for waves with at most SPMM_PIPE_CHUNKS chunks; lane
-// offsets are 32 bits, so B must span less than 4 GiB.
+// NS: chunks in flight per wave.  0 and 1: one (any panel length).  0: the copies are issued through the compiler's builtin, with
+// lane offsets of 64 bits (any extent of B); 1: from inline assembly with offsets of 32 bits, so B must span less than 4 GiB, its rows
+// and their length fit 24 bits (a 64-bit product per copy stood between a chunk's indices and its copies).
+// 2: the same into two alternating stages, and only the older
+// chunk is waited for (counted s_waitcnt); for waves with at most SPMM_PIPE_CHUNKS chunks.
 constexpr int SPMM_PIPE_CHUNKS = 4;
 
 // Makes the compiler treat x as used and redefined here: a load into x that is still in flight is
 // waited for at this point (and at no later one).
-__device__ __forceinline__ void pin(v4i &x) { asm volatile("" : "+v"(x)); }
+template <class T> __device__ __forceinline__ void pin(T &x) { asm volatile("" : "+v"(x)); }
 template <int BNB, int WK, int LB, int RB, bool U = false, int NS = 1> struct SpmmCfg {
     static constexpr bool R4 = (RB == 4), R16 = (RB == 16), L16 = (LB == 16);
     static_assert(!U || (!R16 && !L16), "unsigned operands: 4 and 8 bits");
@@ -76,7 +76,8 @@ template <int BNB, int WK, int LB, int RB, bool U = false, int NS = 1> struct Sp
     static constexpr int OROWS = L16 ? 16 : (U ? 12 : 8); // rows of a partial tile (U: row 8 holds column sums of B)
     static constexpr int TST = COLS + 4;                 // row stride (ints) of a partial tile: +4 keeps rows 4 apart in different banks
     static constexpr int OTILE = OROWS * TST * 4;        // bytes of one wave's partial tile
-    static constexpr int PERWAVE = (NS * STAGE > OTILE) ? NS * STAGE : OTILE;
+    static constexpr int STAGES = NS == 2 ? 2 : 1;
+    static constexpr int PERWAVE = (STAGES * STAGE > OTILE) ? STAGES * STAGE : OTILE;
     static constexpr int LDS = WK * PERWAVE;
     // Which LDS row (within the RPI rows a load instruction writes) holds slot group r (slots r*NI .. r*NI+NI-1), and
     // back.  A transposing read's lane groups g and g + 1 (32 lanes, 256 bytes of banks) ask for slot groups 2g + h and
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
 {
     // (Not with 128-byte tiles of two planes by two waves, one chunk in flight: the scalars that it brings forward cost a wave per
     // SIMD, and 4624 x 3513, V = 8, 94 % empty, N = 448, unequal panels, took 13.1 us instead of 12.1.)
-    if constexpr (!(NS == 1 && BNB == 128 && WK == 2 && LB == 16 && RB == 8)) mcu::request_arguments(a);
+    if constexpr (!(NS < 2 && BNB == 128 && WK == 2 && LB == 16 && RB == 8)) mcu::request_arguments(a);
     using Cfg = SpmmCfg<BNB, WK, LB, RB, U, NS>;
     PhaseClock<TR> clk;
     clk.stamp(0);                                        // the wave has started
@@ -167,12 +168,19 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
 
     // Load instruction i of a chunk: lane (rg, seg) copies segment seg ^ (i & SWZ) of the
     // row in slot group_of_row(rg)*NI + i to LDS byte i*1024 + lane*16, i.e. LDS row i*RPI + rg.  The NI
-    // column indices a lane needs are consecutive slots: NI/4 128-bit index loads.
+    // column indices a lane needs are consecutive slots, the same for the lanes of a row: each of four neighbours loads every fourth
+    // one, and copy i takes its index from neighbour i % 4.  (A compute unit's loads take 4.6 clocks where a lane
+    // asks for 4 bytes and 16 where it asks for 8 or 16, whatever the addresses, as long as a copy of 1 KB.  Loaded whole by every
+    // lane, the indices of a chunk were a quarter of its copies.)
     // A segment beyond the row end is replaced by segment 0 (its columns are never stored),
     // so that every chunk issues exactly the same number of memory instructions.
-    auto load_idx = [&](int c, v4i (&dst)[NI / 4]) {
+    constexpr int NX = NI / 4;
+    auto load_idx = [&](int c, int (&dst)[NX]) {
 #pragma unroll
-        for (int t = 0; t < NI / 4; ++t) dst[t] = *reinterpret_cast<const v4i *>(idx + c * MC_CHUNK + Cfg::group_of_row(rg) * NI + 4 * t);
+        for (int t = 0; t < NX; ++t) dst[t] = idx[c * MC_CHUNK + Cfg::group_of_row(rg) * NI + (lane & 3) + 4 * t];
+    };
+    auto from_neighbour = [&](auto I, int x) -> int { // (with all lanes active)
+        return __builtin_amdgcn_mov_dpp(x, decltype(I)::value % 4 * 0x55, 0xF, 0xF, true); // quad_perm [q,q,q,q]
     };
     int segoff[NI];
 #pragma unroll
@@ -212,7 +220,7 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
     // all MFMAs of one chunk whose rows sit in the stage at st
     // (64-byte tiles by eight waves, one chunk in flight, take long panels: left to itself the compiler reads and multiplies tile by
     // tile there, to stay at 64 registers.  All reads first: 14240 x 5056, V = 4, 91 % empty, N = 64, unequal panels 17.8 -> 16.2 us.)
-    constexpr bool READS_FIRST = NS == 1 && BNB == 64 && WK == 8 && RB == 8 && !U;
+    constexpr bool READS_FIRST = NS < 2 && BNB == 64 && WK == 8 && RB == 8 && !U;
     auto compute = [&](const char *st, v4i a_cur) {
         if constexpr (READS_FIRST) {
             v2i d[LPR][2];
@@ -249,15 +257,32 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
             acc[XACC] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_cur, ones, acc[XACC], 0, 0, 0); // every column: sum over the chunk of A's row
         }
     };
-    if (NS == 1) {
-        v4i idxv[NI / 4];
+    // the copies of one chunk into the stage at `to`, lane offsets of 32 bits
+    const unsigned ldb32 = (unsigned)a.ldb_bytes;
+    auto issue = [&](unsigned to, const int (&ixs)[NX]) {
+        int at[NX];                                      // (multiplied by the lane that holds it, handed over in the sum)
+#pragma unroll
+        for (int t = 0; t < NX; ++t) at[t] = (int)__umul24((unsigned)ixs[t], ldb32);
+        mcu::static_for<NI>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            mcu::copy16_to_lds(Bb, (unsigned)from_neighbour(I, at[i / 4]) + (unsigned)segoff[i], to + i * 1024);
+        });
+    };
+    const unsigned stage_u = mcu::lds_addr_uniform(stage);
+    if (NS < 2) {
+        int idxv[NX];
         if (nmy > 0) load_idx(w, idxv);
         for (int k = 0; k < nmy; ++k) {
             const int c = w + k * WK;
-#pragma unroll
-            for (int i = 0; i < NI; ++i)
-                __builtin_amdgcn_global_load_lds((gptr_t *)(Bb + (int64_t)idxv[i >> 2][i & 3] * a.ldb_bytes + segoff[i]),
-                                                 (lptr_t *)(stage + i * 1024), 16, 0, 0);
+            if constexpr (NS == 1) {
+                issue(stage_u, idxv);
+            } else {
+                mcu::static_for<NI>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    __builtin_amdgcn_global_load_lds((gptr_t *)(Bb + (int64_t)from_neighbour(I, idxv[i / 4]) * a.ldb_bytes + segoff[i]),
+                                                     (lptr_t *)(stage + i * 1024), 16, 0, 0);
+                });
+            }
             const v4i a_cur = load_a_op(c);
             if (k + 1 < nmy) load_idx(c + WK, idxv); // the copies above have consumed the old indices
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -278,13 +303,12 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
         // the NI copies of chunk k+1 means that chunk k has arrived.  (Row numbers and row strides are
         // below 2^24 here -- the launcher checks it -- so a lane's offset is one 24-bit multiply-add.)
         constexpr int MAXL = SPMM_PIPE_CHUNKS;
-        const unsigned stage_u = mcu::lds_addr_uniform(stage);
-        const unsigned ldb32 = (unsigned)a.ldb_bytes;
-        v4i ix[MAXL][NI / 4], av[MAXL];
+        int ix[MAXL][NX];
+        v4i av[MAXL];
         mcu::static_for<MAXL>([&](auto Lc) {
             constexpr int l = decltype(Lc)::value;
 #pragma unroll
-            for (int t = 0; t < NI / 4; ++t) ix[l][t] = (v4i){0, 0, 0, 0};
+            for (int t = 0; t < NX; ++t) ix[l][t] = 0;
             av[l] = (v4i){0, 0, 0, 0};
             if (l < nmy) {
                 load_idx(w + l * WK, ix[l]);
@@ -294,22 +318,17 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
         mcu::static_for<MAXL>([&](auto Lc) {
             constexpr int l = decltype(Lc)::value;
 #pragma unroll
-            for (int t = 0; t < NI / 4; ++t) pin(ix[l][t]);
+            for (int t = 0; t < NX; ++t) pin(ix[l][t]);
             pin(av[l]);
         });
-        auto issue = [&](int st, const v4i (&ixs)[NI / 4]) {
-#pragma unroll
-            for (int i = 0; i < NI; ++i)
-                mcu::copy16_to_lds(Bb, __umul24((unsigned)ixs[i >> 2][i & 3], ldb32) + (unsigned)segoff[i], stage_u + st * Cfg::STAGE + i * 1024);
-        };
         clk.stamp(2);                                    // column indices and A operands have arrived
         if (nmy == 0) clk.stamp(3);                      // (a wave without chunks waits for no rows)
-        if (nmy > 0) issue(0, ix[0]);
+        if (nmy > 0) issue(stage_u, ix[0]);
         mcu::static_for<MAXL>([&](auto Lc) {
             constexpr int l = decltype(Lc)::value;
             if (l < nmy) {
                 if (l + 1 < MAXL && l + 1 < nmy) {
-                    issue((l + 1) & 1, ix[(l + 1 < MAXL) ? l + 1 : l]);
+                    issue(stage_u + ((l + 1) & 1) * Cfg::STAGE, ix[(l + 1 < MAXL) ? l + 1 : l]);
                     mcu::vm_wait<NI>();
                 } else {
                     mcu::vm_wait<0>();
@@ -472,15 +491,14 @@ template <int BNB, int LB, int RB, bool U, int NS> hipError_t launch_ns(const Sp
 
 template <int BNB, int LB, int RB, bool U = false> hipError_t launch_wk(const SpmmArgs &a, int waves, hipStream_t s)
 {
-    // two chunks in flight per wave whenever the lane offsets into B fit 32 bits (unsigned
-    // operands keep to the one-chunk form to bound the number of kernels)
-    // ... and no wave has more than SPMM_PIPE_CHUNKS chunks
+    // two chunks in flight per wave (unsigned operands keep to the one-chunk form to bound the number of kernels)
+    // ... where no wave has more than SPMM_PIPE_CHUNKS chunks
     if constexpr (!U) if (a.stages == 2) {
         constexpr int MAXW2 = (SpmmCfg<BNB, 8, LB, RB, U, 2>::LDS <= 65536) ? 8 : ((SpmmCfg<BNB, 4, LB, RB, U, 2>::LDS <= 65536) ? 4 : ((SpmmCfg<BNB, 2, LB, RB, U, 2>::LDS <= 65536) ? 2 : 1));
         const int wv = waves > MAXW2 ? MAXW2 : (waves == 4 && MAXW2 < 4 ? MAXW2 : waves);
         if ((a.max_unit_chunks + wv - 1) / wv <= SPMM_PIPE_CHUNKS) return launch_ns<BNB, LB, RB, U, 2>(a, waves, s);
     }
-    return launch_ns<BNB, LB, RB, U, 1>(a, waves, s);
+    return a.short_b ? launch_ns<BNB, LB, RB, U, 1>(a, waves, s) : launch_ns<BNB, LB, RB, U, 0>(a, waves, s);
 }
 
 // unsigned operands: tiles of 64 or 128 bytes
