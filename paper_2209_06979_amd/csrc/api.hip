@@ -386,7 +386,7 @@ double gather_us(const mc_mat *A, int row_bytes, int rb, int out_bytes, const mc
     const int longest = items ? A->max_item_chunks : A->max_panel_chunks;
     int bnb, waves;
     choose_variant(A, A->lhs_bits, row_bytes, rb == 4, 1, longest, o, &bnb, &waves);
-    const int wave_lds = std::max(MC_CHUNK * bnb, (A->lhs_bits > 8 ? 16 : 8) * ((rb == 4 ? 2 * bnb : bnb) + 4) * 4); // (as in SpmmCfg)
+    const int wave_lds = std::max(MC_CHUNK * bnb, 8 * ((rb == 4 ? 2 * bnb : bnb) + 4) * 4); // (as in SpmmCfg)
     while (waves > 1 && waves * wave_lds > 65536) waves /= 2;
     int unit = bnb;                                       // rows start at multiples of this, tiles too
     while (row_bytes % unit || unit > 128) unit /= 2;

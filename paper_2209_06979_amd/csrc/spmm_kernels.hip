@@ -73,7 +73,7 @@ template <int BNB, int WK, int LB, int RB, bool U = false, int NS = 1> struct Sp
     static constexpr int STAGE = 64 * BNB;               // LDS bytes of one staged chunk
     static constexpr int COLS = BNB * (R4 ? 2 : 1);      // columns of the partial tile (byte columns for R16)
     static constexpr int OUTC = R16 ? BNB / 2 : COLS;    // output columns of the tile
-    static constexpr int OROWS = L16 ? 16 : (U ? 12 : 8); // rows of a partial tile (U: row 8 holds column sums of B)
+    static constexpr int OROWS = U ? 12 : 8;             // rows of a partial tile (U: row 8 holds column sums of B)
     static constexpr int TST = COLS + 4;                 // row stride (ints) of a partial tile: +4 keeps rows 4 apart in different banks
     static constexpr int OTILE = OROWS * TST * 4;        // bytes of one wave's partial tile
     static constexpr int STAGES = NS == 2 ? 2 : 1;
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
     }
 
     // ---- partial tiles -> LDS (each wave into its own region), row-major int32 ----------
-    // accumulator register r of lane (j, g) is output row 4g + r; MFMA ct covers tile bytes
+    // accumulator register r of lane (j, g) is row 4g + r of the result; MFMA ct covers tile bytes
     // 16*ct .. 16*ct+15, i.e. column 16*ct + j (R8) or columns 32*ct + 2j, 2j+1 (R4).
     // A one-plane operand of 16 rows (the merged copy of an operand) passes through the tile in two
     // halves of 8 rows: lane groups 0, 1 first, then 2, 3.
@@ -351,21 +351,46 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
     constexpr int OROWS = Cfg::OROWS;
     constexpr int SH = R4 ? (LB == 4 ? 8 : 4) : 0;       // scale carried by widened nibbles
     const int nhalf = (!L16 && !U && a.V > 8) ? 2 : 1;
+    if constexpr (L16) {
+        // Two planes: their rows are 32 lanes apart.  They are put together here, before the tiles of the waves meet (every
+        // plane's sum is a multiple of a nibble's 16, and from there on all is modulo 2^32): the lower half of the wave ends up with column tile ct,
+        // the upper half with ct + 1.  A tile of 16 rows took as long again to write and to add up, and its LDS left a
+        // workgroup four waves (rows of 128 bytes, two of nibbles).
+        constexpr int Q = R4 ? 2 : 1;
+#pragma unroll
+        for (int ct = 0; ct < LPR; ct += 2)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const auto x = __builtin_amdgcn_permlane32_swap((unsigned)(acc[ct * Q + q][r] >> SH), (unsigned)(acc[(ct + 1) * Q + q][r] >> SH), false, false);
+                    acc[ct * Q + q][r] = (int)((x[0] << 8) + x[1]);
+                }
+        if (R16) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const auto x = __builtin_amdgcn_permlane32_swap((unsigned)acc[XACC][r], (unsigned)acc[XACC][r], false, false);
+                acc[XACC][r] = (int)((x[0] << 8) + x[1]);
+            }
+        }
+    }
     for (int hf = 0; hf < nhalf; ++hf) {
         if (hf) __syncthreads();                         // the first half's tiles have been read
-        const int gg = g - 2 * hf;
-        if (gg >= 0 && 4 * gg < OROWS) {
+        const int gg = L16 ? (g & 1) : g - 2 * hf;
+        if (L16 || (gg >= 0 && 4 * gg < OROWS)) {
 #pragma unroll
-            for (int ct = 0; ct < LPR; ++ct)
+            for (int ct = 0; ct < LPR; ct += L16 ? 2 : 1) {
+                const int at = L16 ? ct + (g >> 1) : ct; // this lane's column tile
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     if (!R4) {
-                        tile_w[(4 * gg + r) * TST + ct * 16 + j] = acc[ct][r];
+                        tile_w[(4 * gg + r) * TST + at * 16 + j] = acc[ct][r];
                     } else {
-                        *reinterpret_cast<v2i *>(&tile_w[(4 * gg + r) * TST + ct * 32 + 2 * j]) = (v2i){acc[2 * ct][r], acc[2 * ct + 1][r]};
+                        *reinterpret_cast<v2i *>(&tile_w[(4 * gg + r) * TST + at * 32 + 2 * j]) = (v2i){acc[2 * ct][r], acc[2 * ct + 1][r]};
                     }
                 }
-            if ((R16 || U) && j == 0) { // the row sums ride in the padding column of the tile
+            }
+            if ((R16 || U) && j == 0 && (!L16 || g < 2)) { // the row sums ride in the padding column of the tile
 #pragma unroll
                 for (int r = 0; r < 4; ++r) tile_w[(4 * gg + r) * TST + COLS] = acc[XACC][r];
             }
@@ -383,13 +408,12 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
             const int pc = (tid + q * 64 * WK < PIECES) ? tid + q * 64 * WK : PIECES - 1;
             const int row = pc / (OUTC / 4), col = (pc % (OUTC / 4)) * 4;
             const int tcol = R16 ? 2 * col : col;            // first column in the partial tile
-            v4i s = {0, 0, 0, 0}, lo = {0, 0, 0, 0}, s2 = {0, 0, 0, 0}, lo2 = {0, 0, 0, 0}, cs = {0, 0, 0, 0};
-            int rs = 0, rs_lo = 0;
+            v4i s = {0, 0, 0, 0}, s2 = {0, 0, 0, 0}, cs = {0, 0, 0, 0};
+            int rs = 0;
 #pragma unroll
             for (int ww = 0; ww < WK; ++ww) {
                 const int *t = reinterpret_cast<const int *>(lds + ww * Cfg::PERWAVE);
                 s += *reinterpret_cast<const v4i *>(&t[row * TST + tcol]);
-                if (L16) lo += *reinterpret_cast<const v4i *>(&t[(row + 8) * TST + tcol]);
                 if (U) {
                     cs += *reinterpret_cast<const v4i *>(&t[8 * TST + tcol]);
                     rs += t[row * TST + COLS];
@@ -397,10 +421,6 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
                 if (R16) {
                     s2 += *reinterpret_cast<const v4i *>(&t[row * TST + tcol + 4]);
                     rs += t[row * TST + COLS];
-                    if (L16) {
-                        lo2 += *reinterpret_cast<const v4i *>(&t[(row + 8) * TST + tcol + 4]);
-                        rs_lo += t[(row + 8) * TST + COLS];
-                    }
                 }
             }
             if (U) {
@@ -409,12 +429,11 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
                 if (a.rhs_unsigned) s += (v4i){rs << 7, rs << 7, rs << 7, rs << 7};
                 if (a.lhs_unsigned) s += cs << 7;
             }
-            if (R4) { s = s >> SH; lo = lo >> SH; }
+            if (R4 && !L16) s = s >> SH;
             if (U && a.lhs_unsigned && a.rhs_unsigned) {
                 const int cc = (LB == 4 ? 8 : 128) * (RB == 4 ? 8 : 128) * (nch * MC_CHUNK); // ca * cb * slots (padded ones included: their a' is -ca)
                 s += (v4i){cc, cc, cc, cc};
             }
-            if (L16) { s = (s << 8) + lo; s2 = (s2 << 8) + lo2; rs = (rs << 8) + rs_lo; }
             if (R16) {
                 // byte columns (low, high) of four B elements: A*b = (A*hi << 8) + A*(low ^ 0x80) + 128 * rowsum(A)
                 const int fix = rs << 7;
