@@ -89,8 +89,9 @@ __device__ __forceinline__ void store_scores(const SddmmArgs &a, int64_t out0, i
 // Two int16 operands: the tile's accumulators hold Qh.Kh (rows 0 .. 7) and Ql.Kh (rows 8 .. 15, 32 lanes further up) in acc, the same with
 // Kl in acc2; S = (QhKh << 16) + ((QhKl + QlKh) << 8) + QlKl.  Each half of the wave adds up the two terms that it has after one
 // exchange of halves (lower lanes those of acc, upper lanes those of acc2), a second exchange brings the halves' sums together and leaves
-// lane (j, g) rows 4 (g & 1) + 2 (g >> 1) and the next of vector j: every lane has a pair of rows to store.
-__device__ __forceinline__ v2i combine16(v4i acc, v4i acc2, int lower_shift)
+// lane (j, g) rows 4 (g & 1) + 2 (g >> 1) and the next of vector j: every lane has a pair of rows to store.  Of two tiles the exchange
+// leaves four rows of one in the lower and of the other in the upper half.
+__device__ __forceinline__ v4i halves16(v4i acc, v4i acc2, int lower_shift)
 {
     v4i z;
 #pragma unroll
@@ -98,6 +99,20 @@ __device__ __forceinline__ v2i combine16(v4i acc, v4i acc2, int lower_shift)
         const auto s = __builtin_amdgcn_permlane32_swap((unsigned)acc[r], (unsigned)acc2[r], false, false);
         z[r] = (int)(((s[0] << 8) + s[1]) << lower_shift);   // lower: QhKh << 16 + QlKh << 8; upper: QhKl << 8 + QlKl
     }
+    return z;
+}
+__device__ __forceinline__ v4i two_tiles(v4i z, v4i y)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const auto s = __builtin_amdgcn_permlane32_swap((unsigned)z[r], (unsigned)y[r], false, false);
+        z[r] = (int)(s[0] + s[1]);
+    }
+    return z;
+}
+__device__ __forceinline__ v2i combine16(v4i acc, v4i acc2, int lower_shift)
+{
+    const v4i z = halves16(acc, acc2, lower_shift);
     v2i out;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
@@ -168,6 +183,10 @@ __device__ __forceinline__ void store_pair(const SddmmArgs &a, int64_t out0, int
 // With int16 operands it is the instructions, too (the same rows as int8: 6.9 us where int16 took 8.9, equal panels): Kmat's bytes
 // are taken apart without a carry, halves of the wave combine a tile's four sums by two exchanges in registers, and offsets are 32
 // bits wide where they can be: 8.9 -> 7.9; with rows above 512 bytes (5760 x 2546, V = 8, 71 %, Kd = 280) 43.6 -> 32.7.
+// Loads and stores take a compute unit 16 clocks where a lane has 8 or 16 bytes, also where half of the lanes have nothing, and 4.6
+// where it has 4: the indices are shared by the lanes of a row, and where a unit has several tiles two of them are stored at once.  54 drawn masks, three
+// operands in turn from a graph, 1.027x in the mean (4096 x 4096, 90 % sparse, Kd = 256 5.9 -> 5.6 us; 758 x 5997, V = 2, Kd = 128 13.2 -> 11.4; L16-R16,
+// 4360 x 6043, V = 8, Kd = 72 31.5 -> 28.7); 16-bit ones of 3 us 1 % slower.
 // SHORT: Kmat spans less than 4 GiB, its rows and their length fit 24 bits.
 template <int PB, int LPR, bool DQ, bool U, bool SHORT>
 __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
@@ -191,12 +210,18 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
     const int nunits = (n_all + UNIT - 1) / UNIT;
     const int nmy = (nunits > w) ? (nunits - w + nw - 1) / nw : 0;
     if (nmy == 0) return;
-    // piece i of a unit: lane (rg, seg) fetches piece seg of the row in slot rg*NI + i
-    const int32_t *idx = a.slot_idx + s0 + rg * NI;
-    v4i ixn[NI / 4];
+    // piece i of a unit: lane (rg, seg) fetches piece seg of the row in slot rg*NI + i.  The lanes of a row need the same indices: each of
+    // four neighbours loads every fourth one, and copy i takes its index from neighbour i % 4.  (A load of 4 bytes a lane takes a compute
+    // unit 4.6 clocks, one of 16 as long as a copy of 1 KB, 16: loaded whole by every lane, the indices were up to a quarter of the copies.)
+    constexpr int NX = NI / 4;
+    const int32_t *idx = a.slot_idx + s0 + rg * NI + (lane & 3);
+    int ixn[NX];
     auto load_idx = [&](int u) {
 #pragma unroll
-        for (int t = 0; t < NI / 4; ++t) ixn[t] = *reinterpret_cast<const v4i *>(idx + u * UNIT + 4 * t);
+        for (int t = 0; t < NX; ++t) ixn[t] = idx[u * UNIT + 4 * t];
+    };
+    auto from_neighbour = [&](auto I, int x) -> int { // (with all lanes active)
+        return __builtin_amdgcn_mov_dpp(x, decltype(I)::value % 4 * 0x55, 0xF, 0xF, true); // quad_perm [q,q,q,q]
     };
     load_idx(w);
     const int64_t out0 = (int64_t)batch * a.S_batch_stride + (int64_t)share.w * a.V;
@@ -227,12 +252,19 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
     auto request = [&]() {
         unsigned to = stage_u;
         if (U && LPR == 64) asm("" : "+s"(to)); // (sixteen places kept in scalar registers would be spilled)
-        if constexpr (SHORT) { // one multiply-add per piece, and eight registers less
+        if constexpr (SHORT) { // (multiplied by the lane that holds an index, handed over in the sum)
+            int at[NX];
 #pragma unroll
-            for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km, __umul24(ixn[i >> 2][i & 3], (unsigned)a.ldk_bytes) + off[i], to + i * 1024);
+            for (int t = 0; t < NX; ++t) at[t] = (int)__umul24((unsigned)ixn[t], (unsigned)a.ldk_bytes);
+            mcu::static_for<NI>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                mcu::copy16_to_lds(Km, (unsigned)from_neighbour(I, at[i / 4]) + (unsigned)off[i], to + i * 1024);
+            });
         } else {
-#pragma unroll
-            for (int i = 0; i < NI; ++i) mcu::copy16_to_lds(Km + ((int64_t)ixn[i >> 2][i & 3] * a.ldk_bytes + off[i]), to + i * 1024);
+            mcu::static_for<NI>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                mcu::copy16_to_lds(Km + ((int64_t)from_neighbour(I, ixn[i / 4]) * a.ldk_bytes + off[i]), to + i * 1024);
+            });
         }
     };
     request();
@@ -270,10 +302,12 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
 
     for (int k = 0; k < nmy; ++k) {
         const int u = w + k * nw;
-        // This unit's rows have landed.  (Integer outputs: the TILES stores of the unit before were issued after this
+        // This unit's rows have landed.  (Integer outputs: the stores of the unit before, one for two tiles or for one, were issued after this
         // unit's copies -- only the last unit can have tiles without a store -- and need not be waited for.)
+        constexpr bool IN_TWOS = !U && TILES > 1;
+        constexpr int STORES = IN_TWOS ? TILES / 2 : TILES;
         if (k == 0 || DQ) mcu::vm_wait<0>();
-        else mcu::vm_wait<TILES>();
+        else mcu::vm_wait<STORES>();
         // The operands of the whole unit first, so that the stage is free for the next unit's rows before the MFMAs (rows
         // of 1024 bytes: their operands are more than the registers hold, they are read one by one).
         constexpr int OPS = (PB == 16) ? 2 * KC : KC;
@@ -299,6 +333,7 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
                 for (int kc = 0; kc < OPS; ++kc) kt[tl][kc] = read_op(tl, kc);
             next_unit();
         }
+        v4i even = {0, 0, 0, 0};
 #pragma unroll
         for (int tl = 0; tl < TILES; ++tl) {
             // (int16: the low bytes of Kmat enter as u - 128, and 128 times the sum of Q goes in here)
@@ -324,7 +359,22 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
             }
             if (!EARLY) next_unit();                // (a unit of these is one tile)
             const int slot = u * UNIT + tl * 16 + j;
-            if (PB == 16) {
+            if (IN_TWOS) {
+                // two tiles' rows 0 .. 7 side by side, so that all lanes have four rows to store: a store takes a compute unit as long for half the lanes
+                const v4i z = PB == 16 ? halves16(acc, acc2, lower_shift) : finish_tile<PB>(acc, acc2);
+                if (tl % 2 == 0) {
+                    even = z;
+                } else {
+                    v4i both;
+                    if (PB == 16) {
+                        both = two_tiles(even, z);
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) both[r] = (int)__builtin_amdgcn_permlane32_swap((unsigned)even[r], (unsigned)z[r], false, false)[0];
+                    }
+                    store_scores<DQ>(a, out0, s0, slot - 16 + 16 * (g >> 1), n, g & 1, both);
+                }
+            } else if (PB == 16) {
                 store_pair<DQ>(a, out0, s0, slot, n, g, combine16(acc, acc2, lower_shift));
             } else if (!U) {
                 store_scores<DQ>(a, out0, s0, slot, n, g, finish_tile<PB>(acc, acc2));

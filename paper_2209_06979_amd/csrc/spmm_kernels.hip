@@ -171,7 +171,10 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
     // column indices a lane needs are consecutive slots, the same for the lanes of a row: each of four neighbours loads every fourth
     // one, and copy i takes its index from neighbour i % 4.  (A compute unit's loads take 4.6 clocks where a lane
     // asks for 4 bytes and 16 where it asks for 8 or 16, whatever the addresses, as long as a copy of 1 KB.  Loaded whole by every
-    // lane, the indices of a chunk were a quarter of its copies.)
+    // lane, the indices of a chunk were a quarter of its copies.  With the offsets of 32 bits below,
+    // 36 drawn operands, three in turn from a graph: 1.035x in the mean, none slower by more than 0.7 %; 3788 x 4401, V = 2, unequal panels, L4-R4,
+    // N = 96 32.0 -> 27.2 us, 9584 x 1627, V = 8, L8-R8, N = 576 20.0 -> 18.2.  The same for A, two chunks' operands of a panel of 8 rows in one
+    // request: 0.98x.)
     // A segment beyond the row end is replaced by segment 0 (its columns are never stored),
     // so that every chunk issues exactly the same number of memory instructions.
     constexpr int NX = NI / 4;
@@ -355,7 +358,8 @@ __global__ __launch_bounds__(64 * WK) void spmm_kernel(SpmmArgs a)
         // Two planes: their rows are 32 lanes apart.  They are put together here, before the tiles of the waves meet (every
         // plane's sum is a multiple of a nibble's 16, and from there on all is modulo 2^32): the lower half of the wave ends up with column tile ct,
         // the upper half with ct + 1.  A tile of 16 rows took as long again to write and to add up, and its LDS left a
-        // workgroup four waves (rows of 128 bytes, two of nibbles).
+        // workgroup four waves (rows of 128 bytes, two of nibbles).  36 drawn 16-bit operands 1.076x in the mean; 760 x 6497, V = 8, 56 %
+        // empty, L16-R4, N = 160 19.3 -> 12.7 us, 4210 x 5059, V = 2, unequal panels, L12-R4, N = 320 101.5 -> 81.1.
         constexpr int Q = R4 ? 2 : 1;
 #pragma unroll
         for (int ct = 0; ct < LPR; ct += 2)
