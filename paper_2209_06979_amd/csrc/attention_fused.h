@@ -243,11 +243,14 @@ void attention_fused_kernel(AttnArgs a)
     // long arrived by the time they are needed: a vm_wait<0>() lies in between).
     ixv_t ixn = {};
     auto issue = [&](const uint8_t *base, int c, int st) {
+        ixv_t row;                             // (multiplied by the lane that holds an index, handed over in the sum)
+#pragma unroll
+        for (int q = 0; q < NIX; ++q) row[q] = (int)__umul24((unsigned)ixn[q], tstride);
         static_for<NITW>([&](auto I) {
             constexpr int i = decltype(I)::value;
             unsigned off = segoff[i];
             if (PAD) asm("" : "+v"(off)); // (sixteen conditions kept would be more than the scalar registers)
-            const unsigned at = __umul24(index_of(I, ixn), tstride) + off; // (the exchange with all lanes active)
+            const unsigned at = index_of(I, row) + off; // (the exchange with all lanes active)
             if (!PAD || (int)off >= 0) copy16_to_lds(base, at, stage_u + st * STG + (NITW * w + i) * 1024);
         });
         ixn = load_idx((c + KS < nch) ? c + KS : c);
@@ -296,7 +299,16 @@ void attention_fused_kernel(AttnArgs a)
         if (QB == 8) return raw;
         return (raw ^ flip) & half;
     };
-    v4i first = {0, 0, 0, 0};                  // what the sums start with: -8 x 16 x the row's even elements
+    // What the sums start with: the bit pattern of 1.5 * 2^23 -- as a float a sum then is that much more than its value, exactly, and no conversion
+    // is needed -- and, 4 bit, -8 x 16 x the row's even elements.  (Scores stay below 2^22: 192 x 128 x 128.)
+    static_assert(DK * 128 * 128 < 1 << 22, "scores are exact beside 1.5 * 2^23");
+    // (A conversion takes a SIMD 4.3 clocks, as a byte permutation, a multiply-add of integers or an exchange of neighbours; a sum or product of floats 2.3 -
+    // 2.7, an exponential 8.9.  With one product per index instead of per copy and codes by one multiply-add and permutations, 40
+    // layers replayed from graphs 1.010x in the mean, 8 x 4 heads x 8192 with 16-bit codes 1.02, 0.99 - 1.05x: it is the gather that takes the time.
+    // Not where four more registers are too many.)
+    constexpr bool BIASED = !(HPW == 2 && KS > 1 && PB == 16);
+    constexpr int FLOAT0 = BIASED ? 0x4B400000 : 0;
+    v4i first = {FLOAT0, FLOAT0, FLOAT0, FLOAT0};
     if (QB == 4) {
         const int minus8 = g < 2 ? (int)0xF8F8F8F8 : 0;
 #pragma unroll
@@ -343,10 +355,10 @@ void attention_fused_kernel(AttnArgs a)
     // all Kmat rows are consumed: start copying V rows while the softmax runs
     start_pipeline(Vg);
 
-    // ---- softmax over row 4*(g&1) + r, in base 2: exp(x - max) = 2^((s - smax) * scale2) -----
+    // ---- softmax over row 4*(g&1) + r, in base 2: exp(x - max) = 2^((s - smax) * scale2), the difference exact -----
     constexpr float LOG2E = 1.4426950408889634f;
     const float scale2 = a.score_scale * LOG2E * (QB == 4 ? 0.0625f : 1.f);
-    float m2[4], srow[4] = {0.f, 0.f, 0.f, 0.f};
+    float top[4], srow[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         unsigned lo, hi;
@@ -365,7 +377,7 @@ void attention_fused_kernel(AttnArgs a)
             for (int k = 0; k < KS; ++k) imax[r] = max(imax[r], xch[0][w][k][4 * (g & 1) + r]);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) m2[r] = (float)imax[r] * scale2;
+    for (int r = 0; r < 4; ++r) top[r] = BIASED ? __builtin_bit_cast(float, imax[r]) : (float)imax[r] * scale2;
     float x[NPR][4];
     static_for<MAXCH>([&](auto C) {
         constexpr int c = C;
@@ -373,8 +385,10 @@ void attention_fused_kernel(AttnArgs a)
 #pragma unroll
             for (int pr = 0; pr < 2; ++pr)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    x[2 * c + pr][r] = __builtin_amdgcn_exp2f(__builtin_fmaf((float)sc[2 * c + pr][r], scale2, -m2[r]));
+                for (int r = 0; r < 4; ++r) {
+                    const int sum = sc[2 * c + pr][r]; // (a bit cast of a vector's element takes the first one)
+                    x[2 * c + pr][r] = __builtin_amdgcn_exp2f(BIASED ? (__builtin_bit_cast(float, sum) - top[r]) * scale2 : __builtin_fmaf((float)sum, scale2, -top[r]));
+                }
             if (ks + c * KS == nch - 1) {
                 // the panel's last chunk: padded slots count for nothing.  (The empty statement keeps
                 // this a branch taken once per wave instead of selects in every chunk.)
@@ -453,33 +467,24 @@ void attention_fused_kernel(AttnArgs a)
                 constexpr bool CAP = decltype(Cap)::value;
 #pragma unroll
                 for (int pr = 0; pr < 2; ++pr) {
-                    float y[4];
+                    // code = rint(x * rinv), ties to even: added to 1.5 * 2^23 the product becomes an integer in the low half of the word.
+                    // 16 bit, plus 128: code = 256 * hi + lo with hi = (code + 128) >> 8 in [0, 127] then is the second byte and lo, in [-128, 127],
+                    // the first one with its top bit flipped.
+                    constexpr float INTEGER = PB == 8 ? 12582912.f : 12582912.f + 128.f;
+                    unsigned u[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        y[r] = x[2 * c + pr][r] * rinv[r];
-                        if (CAP) y[r] = fminf(y[r], PB == 8 ? 127.f : 32639.f);
+                        const float e = x[2 * c + pr][r];
+                        u[r] = __builtin_bit_cast(unsigned, CAP ? fminf(e * rinv[r], PB == 8 ? 127.f : 32639.f) + INTEGER : __builtin_fmaf(e, rinv[r], INTEGER));
                     }
                     char *to = code_at + pr * 256;
+                    const unsigned c01 = __builtin_amdgcn_perm(u[1], u[0], 0x05010400), c23 = __builtin_amdgcn_perm(u[3], u[2], 0x05010400);
+                    const unsigned low = __builtin_amdgcn_perm(c23, c01, 0x05040100);
                     if (PB == 8) {
-                        // v_cvt_pk_u8_f32 rounds to nearest even and drops the byte into place
-                        unsigned packed = 0;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) packed = __builtin_amdgcn_cvt_pk_u8_f32(y[r], r, packed);
-                        *reinterpret_cast<unsigned *>(to) = packed;
+                        *reinterpret_cast<unsigned *>(to) = low;
                     } else {
-                        // code = rint(y), ties to even, hi = (code + 128) >> 8 in [0, 127], lo = code - 256 * hi in [-128, 127]:
-                        // the code's low byte as it is.  Adding 1.5 * 2^23 rounds to an integer and leaves it in the low
-                        // half of the word; four codes are then split two at a time.  (18 instructions for four codes, it
-                        // was 36.  By itself: 8 x 4 heads x 8192, (L, heads, dk), 190.5 -> 184.5 us, (heads, L, dk) 227.5 -> 225.5.)
-                        unsigned u[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            asm("" : "+v"(y[r])); // (the product is rounded before the sum is)
-                            u[r] = __builtin_bit_cast(unsigned, y[r] + 12582912.f);
-                        }
-                        const unsigned c01 = __builtin_amdgcn_perm(u[1], u[0], 0x05040100), c23 = __builtin_amdgcn_perm(u[3], u[2], 0x05040100);
-                        *reinterpret_cast<unsigned *>(to) = __builtin_amdgcn_perm(c23 + 0x00800080u, c01 + 0x00800080u, 0x07050301);
-                        *reinterpret_cast<unsigned *>(to + PSTRIDE) = __builtin_amdgcn_perm(c23, c01, 0x06040200);
+                        *reinterpret_cast<unsigned *>(to) = __builtin_amdgcn_perm(c23, c01, 0x07060302);
+                        *reinterpret_cast<unsigned *>(to + PSTRIDE) = low ^ 0x80808080u;
                     }
                 }
             };
