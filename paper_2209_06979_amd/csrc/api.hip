@@ -145,60 +145,88 @@ int choose_sddmm_waves(const mc_mat *mask, int shares, int batch, int row_bytes,
     return w;
 }
 
-// SpMM tile variant for a problem (from sweeps on MI355X).  Rows are cut into 128-byte tiles, into
-// 256-byte tiles when panels are long, into 64-byte tiles when rows or panels are short; the chunks
-// of a panel are shared by as many waves as it takes to put about 2048 waves on the chip, but
-// never more waves than a panel has chunks.
-// max_unit: chunks of the longest unit of work (panel or work item) of this launch.
-// lhs_bits: width of the sparse operand's values in this launch (a mask carries none of its own).
-void choose_variant(const mc_mat *A, int lhs_bits, int row_bytes, bool r4, int batch, int max_unit, const mc_options &o, int *bnb,
-                    int *waves)
+// The tile (bytes of a row of B) and the waves per panel of a gathered SpMM, and its expected time in us.
+struct GatherPlan { int bnb, waves; double us; };
+
+// Workgroups of one gathered launch that the chip holds at once, by LDS (as in SpmmCfg) and wave slots; 0: more than the 64 KB that the
+// launcher gives a workgroup.
+constexpr int gather_at_once(int bnb, bool r4, int stages, int waves)
 {
-    int b = o.spmm_row_tile_bytes, w = o.spmm_waves;
-    const double avg = A->P ? (double)(A->nslots / MC_CHUNK) / A->P : 0.0;
-    if (b == 0) {
-        if (r4) {
-            // a 64-byte tile of nibbles already yields 128 output columns
-            // (rows of 128 bytes: the wider tile only for long panels, and not with a two-plane A and V = 8,
-            // i.e. 16 output rows per tile: L16-R4, N=256, 70 % sparse 13.4 us on 128-byte, 11.2 us on 64-byte tiles)
-            const bool two_planes = (lhs_bits != 8 && lhs_bits != 4 && A->V == 8) || A->V == 16; // 16 output rows per tile
-            b = ((row_bytes >= 256 && avg >= 2.0) || (row_bytes >= 128 && avg >= 16.0 && !two_planes)) ? 128 : 64;
-        } else {
-            b = 128;
-            if (row_bytes < 128 || (row_bytes == 128 && avg < 4.0) || (row_bytes < 512 && avg < 2.0) || avg < 3.0) b = 64;
-            // wide tiles for panels of 8 chunks and more; with a two-plane A and V = 8 (16 output rows per
-            // tile) only for long rows
-            if (row_bytes >= 256 && avg >= 8.0 && ((lhs_bits == 8 && A->V <= 8) || A->V < 8 || row_bytes >= 512)) b = 256;
-            if (row_bytes >= 1024 && avg >= 6.0) b = 256; // eight and more 128-byte tiles would each re-read A
+    const int tile = 8 * ((r4 ? 2 * bnb : bnb) + 4) * 4, lds = waves * std::max(stages * MC_CHUNK * bnb, tile);
+    return lds > 65536 ? 0 : 256 * std::min({163840 / lds, 32 / waves, 16});
+}
+struct GatherAtOnce { int n[2][3][2][4]; };
+constexpr GatherAtOnce gather_at_once_all()
+{
+    GatherAtOnce g = {};
+    for (int r4 = 0; r4 < 2; ++r4)
+        for (int t = 0; t < 3; ++t)
+            for (int st = 0; st < 2; ++st)
+                for (int w = 0; w < 4; ++w) g.n[r4][t][st][w] = gather_at_once(64 << t, r4, st + 1, 1 << w);
+    return g;
+}
+
+// Gathered: the tile and the waves with the least expected time.  Launch and start; the 128-byte lines that rows touch, each tile by itself,
+// with rows at all multiples of their length; the stores; the waves; the chunks of a wave, one after the other, at an even share; those that
+// the longest unit's waves still have then; the launch that clears rows when panels are cut into items; and a last turn of workgroups that
+// leaves compute units idle.  What a line, a wave or a chunk costs goes by the width of B, by the tile, and by whether A has two planes or
+// panels of 16 rows.  Fitted (non-negative least squares on the relative error) to every tile and number of waves on 2700 drawn operands
+// (sizes as at plan_slab), given and merged, three copies of everything in turn; then scaled to the times of the variants picked (the least
+// of several expected times is 3 - 6 % too low).  On 900 others: off by 8 % in the median and by 22 % in nine cases of ten; the variant
+// picked is 2.2 % slower than the fastest of the eight to twelve on average, by 9 % or less in nine cases of ten, by 30 % at worst.  Thresholds
+// on the rows' length and the panels' (64 bytes for short ones, 256 for long ones, waves until 2048 of them are on the chip) were 5.3 %, 18 % and
+// 81 % slower: 3004 x 2900, V = 4, 85 % empty, L16-R8, N = 208 13.5 -> 9.8 us; 10336 x 3053, V = 8, L4-R4, N = 288 52 -> 30 us (64-byte
+// tiles: with 128 bytes of nibbles half as many waves fit).
+// lhs_bits: width of the sparse operand's values in this launch (a mask carries none of its own).  items: the launch takes the operand's
+// work items.  wide: 256-byte tiles exist (they don't for unsigned operands and for rows of nibbles).
+GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int out_bytes, int batch, bool items, bool wide,
+                       const mc_options &o)
+{
+    struct Cost { double start, line, store, wave, chunk, late, items, last; };
+    static const Cost cost[7][3] = {
+        {{2.54, 2.94e-8, 7.57e-8, 0.00032, 0.405, 0.47, 1.68, 0.523}, {2.77, 4.08e-8, 6.51e-8, 0.000654, 0.675, 0.766, 1.18, 0.972}},
+        {{3.17, 3.3e-8, 0, 0.000525, 0.495, 0.479, 0, 0.991}, {3.64, 4.39e-8, 1.19e-9, 0.000961, 0.839, 0.757, 0, 1.52}},
+        {{2.48, 3.07e-8, 1.19e-7, 0.000329, 0.376, 0.394, 1.72, 0.414}, {2.64, 2.81e-8, 1.19e-7, 0.00071, 0.75, 0.698, 1.35, 1.25}},
+        {{2.34, 3.03e-8, 1.93e-8, 0.000252, 0.23, 0.29, 2.18, 0.343}, {2.3, 2.6e-8, 3.65e-8, 0.000546, 0.445, 0.493, 1.75, 0.863}, {2.63, 2.74e-8, 6.08e-8, 0.00101, 0.686, 0.721, 2.28, 1.98}},
+        {{2.8, 3.7e-8, 0, 0.000352, 0.282, 0.316, 2.87, 0.862}, {2.85, 3.42e-8, 0, 0.00066, 0.551, 0.52, 2.57, 1.55}, {3.61, 2.9e-8, 0, 0.00145, 0.868, 0.722, 0, 3.31}},
+        {{2.29, 3.43e-8, 3.14e-8, 0.000249, 0.263, 0.324, 1.66, 0.512}, {2.16, 2.94e-8, 6.68e-8, 0.000514, 0.536, 0.54, 1.64, 0.764}, {2.26, 2.54e-8, 6.63e-8, 0.00119, 0.832, 0.791, 1.05, 1.85}},
+        {{2.53, 3.15e-8, 0, 0.000314, 0.376, 0.463, 2.08, 0.855}, {2.47, 2.78e-8, 6.96e-8, 0.000606, 0.612, 0.678, 2.28, 1.17}, {2.67, 2.41e-8, 9e-8, 0.00123, 0.954, 0.941, 1.57, 2.7}}
+    };
+    static constexpr GatherAtOnce at_once = gather_at_once_all();
+    const bool r4 = rb == 4;
+    const Cost *costs = cost[rb == 16 ? 6 : (r4 ? 0 : 3) + (lhs_bits > 8 ? 2 : A->V == 16 ? 1 : 0)];
+    const double chunks = (double)(A->nslots / MC_CHUNK) * batch, units = (double)(items ? A->n_items : A->P) * batch;
+    const double lines = (double)A->nvec * batch, stored = (double)A->M * batch * (row_bytes * 8 / rb) * out_bytes;
+    const int longest = items ? A->max_item_chunks : A->max_panel_chunks;
+    GatherPlan best = {64, 1, 1e30};
+    for (int t = 0; t < (wide && !r4 ? 3 : 2); ++t) {
+        const int bnb = 64 << t;
+        if (o.spmm_row_tile_bytes ? std::min(o.spmm_row_tile_bytes, wide && !r4 ? 256 : 128) != bnb : bnb > 64 && bnb >= 2 * row_bytes) continue;
+        const Cost &c = costs[t];
+        int unit = bnb;                                   // rows start at multiples of this, tiles too
+        while (row_bytes % unit || unit > 128) unit /= 2;
+        const int tiles = (row_bytes + bnb - 1) / bnb;
+        const double groups = std::max(1.0, units * tiles), steps = chunks * tiles;
+        const double fixed = c.start + lines * (row_bytes + tiles * (128 - unit)) * c.line + stored * c.store + (items ? c.items : 0.0);
+        for (int w = 0; w < 4; ++w) {
+            const int waves = 1 << w;
+            if (o.spmm_waves && o.spmm_waves != waves) continue;
+            const int *fits = at_once.n[r4][t][0];
+            if (!o.spmm_waves && !fits[w]) break;
+            // two chunks in flight where no wave has more (the launcher's rule, with the waves it then allows)
+            const int *two = at_once.n[r4][t][1];
+            int w1 = w, w2 = w;
+            while (!fits[w1]) --w1;
+            while (!two[w2]) --w2;
+            const bool pipe = o.spmm_stages != 1 && (longest + (1 << w2) - 1) >> w2 <= SPMM_PIPE_CHUNKS;
+            const int wk = pipe ? w2 : w1;
+            const double fit = (pipe ? two : fits)[wk], held = std::min(groups, fit), turns = groups / held;
+            const double share = steps / (held * (1 << wk)), late = std::max(0.0, (double)longest / (1 << wk) - share);
+            const double us = fixed + groups * (1 << wk) * c.wave + share * c.chunk + late * c.late + (std::ceil(turns) - turns) * c.last;
+            if (us < best.us) best = {bnb, waves, us};
         }
     }
-    if (b == 256 && r4) b = 128;
-    // few panels: narrower tiles until there is a workgroup for every compute unit (a 256 x 2304 matrix
-    // with rows of 512 bytes: 5.7 us on 256-byte tiles, 3.3 us on 64-byte ones)
-    // (rows of nibbles, fewer than 512 panels: until the panels' chunks can occupy 4096 of the light waves)
-    if (o.spmm_row_tile_bytes == 0) {
-        const double nb = (batch > 0 ? batch : 1), per_group = std::min(8.0, std::max(1.0, avg));
-        while (b > 64 && (double)A->P * ((row_bytes + b - 1) / b) * nb < 256.0) b /= 2;
-        if (r4 && A->P < 512)
-            while (b > 64 && (double)A->P * ((row_bytes + b - 1) / b) * nb * per_group < 4096.0) b /= 2;
-    }
-    if (w == 0) {
-        const double groups = (double)A->P * ((row_bytes + b - 1) / b) * (batch > 0 ? batch : 1);
-        // about 2048 waves on the chip; 4096 of the lighter ones that gather 64-byte pieces of nibbles
-        const double target = (r4 && b == 64) ? 4096.0 : 2048.0;
-        w = 1;
-        while (w < 8 && groups * w * 2 <= target && w * 2 <= avg) w *= 2;
-        // long panels on the narrower tiles: at most 16 chunks per wave (8 with a two-plane A and V = 8)
-        if (!r4 && b != 256) {
-            const double per_wave = ((lhs_bits != 8 && A->V == 8) || A->V == 16) ? 8.0 : 16.0;
-            while (w < 8 && avg > per_wave * w) w *= 2;
-        }
-        // unequal panels (longest unit above twice the average): the longest unit sets the time of the
-        // launch; no wave gets more than 8 chunks of it
-        while (w < 8 && max_unit > 2.0 * avg && max_unit > 8 * w) w *= 2;
-    }
-    *bnb = b;
-    *waves = w;
+    return best;
 }
 
 } // namespace
@@ -311,14 +339,12 @@ int rec_chunks(const mc_mat *A) { return resident_rec_chunks(A->nblk, A->V, A->l
 int resident_rec_bytes(const mc_mat *A) { return rec_chunks(A) * resident_chunk_bytes(A); }
 int64_t resident_records(const mc_mat *A) { return (A->blk_chunks + rec_chunks(A) - 1) / rec_chunks(A); }
 
-// Expected times in us of the two forms of the SpMM, fitted (non-negative least squares on the relative error) to 1600 operands drawn
-// as in profiles/spmm_forms.txt, which holds the first of them: all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192
-// columns, rows of B of 32 .. 1024 bytes, two in three of them of round length, half to 97 % empty, a quarter with panels of unequal length.
-// Timed with three copies of everything in turn, as a program's operands alternate.  An expected time is off by 8 - 10 % in the median and by
-// up to 28 % in nine cases of ten; the form picked is slower than the fastest of the four (merged or not, resident or gathered) by 1.5 % on
-// average, by 6 % or less in nine cases of ten, by half at worst, on equal and on unequal panels alike (with the constants before:
-// 2.8 %, 11 %, 62 %, and on the 168 points of profiles/sweep_spmm_sddmm_grid.txt, one operand over and over, 5.5 % and 54 % against
-// 2 % and 30 %).
+// Expected times in us of the two forms of the SpMM, fitted (non-negative least squares on the relative error) to 2700 drawn operands:
+// all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B of 32 .. 1024 bytes and more, two in three of them of
+// round length, half to 97 % empty, a quarter with panels of unequal length.  Timed with three copies of everything in turn, as a
+// program's operands alternate.  On 900 others a resident time is off by 6 % in the median and by 18 % in nine cases of ten (in blocks:
+// 14 %, 38 %), and the form picked (merged or not, resident, gathered or with all columns) is 1.8 % slower than the fastest on average, by 7 % or
+// less in nine cases of ten, by half at worst (with the constants before: 2.9 %, 11 %, 62 %; form, tile and waves together 2.7 % where 5.2 %).
 // Resident, all of B's rows at once: launch and start; the fill, a line of B per row, by how many workgroups there are to fill; per
 // step of a wave one part per MFMA and one per byte of a chunk's part of a record, both by how many of the sixteen waves have panels; the epilogues; the stores;
 // by the width of B and by whether the two chunks of a record share a request;
@@ -328,8 +354,8 @@ int64_t resident_records(const mc_mat *A) { return (A->blk_chunks + rec_chunks(A
 void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_options &o, SlabPlan *pl)
 {
     struct Cost { double start, store, meet, fill, mfma, record, panel, late; };
-    static const Cost cost[2][2] = {{{4.5, 1.47e-7, 0.45, 9.0e-4, 0.0567, 1.10e-4, 0.0055, 0.059}, {4.43, 1.03e-7, 0.05, 7.5e-4, 0.0586, 5.9e-5, 0.0047, 0.072}},
-                                    {{5.06, 9.8e-8, 0.16, 8.6e-4, 0.085, 2.3e-5, 0.0031, 0.148}, {4.91, 8.1e-8, 0.01, 6.9e-4, 0.0672, 7.8e-5, 0.0073, 0.16}}};
+    static const Cost cost[2][2] = {{{3.93, 9.09e-8, 1.18, 0.000936, 0.0687, 9.07e-5, 0.00477, 0.0442}, {3.9, 9.7e-8, 0.76, 0.000832, 0.0618, 3.49e-5, 0.0029, 0.0414}},
+                                    {{3.99, 1.13e-7, 1.3, 0.000711, 0.0813, 5.36e-5, 0.00234, 0.108}, {4.31, 7.34e-8, 1.11, 0.000489, 0.0763, 0, 0.00458, 0.154}}};
     pl->us = 1e30;
     const double lists = (double)A->blk_chunks / A->P;               // chunks of a panel over all its blocks
     const double store = (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes;
@@ -369,34 +395,13 @@ void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_
     }
 }
 
-// Gathered, in the tiles and waves that choose_variant and the launcher give it: launch and start; the staged bytes (padded slots and
-// the unused part of a last tile included); the 128-byte lines that rows touch, each tile by itself, with rows at all multiples of their
-// length; the stores; the waves; the launch that clears rows when panels are cut into items; the chunks of a wave, one after the other,
-// at an even share; and those that the longest unit's waves still have then.  The constants go by the width of B and by the rows of the
-// MFMA's result that a panel fills (merged panels and two planes of V = 8: all sixteen).
-double gather_us(const mc_mat *A, int row_bytes, int rb, int out_bytes, const mc_options &o)
+// Whether a gathered call takes the operand's work items (out_mode as in spmm_impl)
+bool takes_items(const mc_mat *A, int out_mode, const mc_options &o) { return A->n_items && o.spmm_splitting != -1 && out_mode == 0; }
+
+// Gathered, with int32 results
+double gather_us(const mc_mat *A, int row_bytes, int rb, const mc_options &o)
 {
-    struct Cost { double start, byte, line, store, wave, chunk, late; };
-    static const Cost cost[3][2] = {{{2.55, 7.9e-8, 0.0, 9.8e-8, 5.5e-5, 0.30, 0.48}, {2.65, 6.3e-8, 6.3e-7, 1.0e-7, 1.75e-4, 0.50, 0.45}},
-                                    {{2.37, 4.8e-8, 7.5e-7, 4.7e-8, 5.6e-5, 0.21, 0.29}, {2.22, 4.6e-8, 1.3e-6, 4.5e-8, 1.23e-4, 0.44, 0.26}},
-                                    {{2.40, 5.2e-8, 3.7e-7, 0.0, 2.3e-4, 0.23, 0.33}, {2.40, 4.1e-8, 2.2e-6, 1.3e-7, 0.0, 0.41, 0.42}}};
-    constexpr double second_launch = 3.1;
-    const Cost &c = cost[rb == 4 ? 0 : rb == 8 ? 1 : 2][A->V == 16 || (A->V == 8 && A->lhs_bits > 8)];
-    const bool items = A->n_items && out_bytes == 4;
-    const int longest = items ? A->max_item_chunks : A->max_panel_chunks;
-    int bnb, waves;
-    choose_variant(A, A->lhs_bits, row_bytes, rb == 4, 1, longest, o, &bnb, &waves);
-    const int wave_lds = std::max(MC_CHUNK * bnb, 8 * ((rb == 4 ? 2 * bnb : bnb) + 4) * 4); // (as in SpmmCfg)
-    while (waves > 1 && waves * wave_lds > 65536) waves /= 2;
-    int unit = bnb;                                       // rows start at multiples of this, tiles too
-    while (row_bytes % unit || unit > 128) unit /= 2;
-    const double tiles = (row_bytes + bnb - 1) / bnb, chunks = (double)(A->nslots / MC_CHUNK), groups = A->P * tiles;
-    const double lines = (row_bytes + tiles * (128 - unit)) / 128;
-    const double at_once = 256.0 * std::max(1, std::min(163840 / (waves * wave_lds), 32 / waves)); // workgroups, by LDS and wave slots
-    const double share = chunks * tiles / (std::min(groups, at_once) * waves), longest_share = (double)longest / waves;
-    return c.start + chunks * MC_CHUNK * tiles * bnb * c.byte + A->nvec * lines * c.line +
-           (double)A->M * (row_bytes * 8.0 / rb) * out_bytes * c.store + groups * waves * c.wave + (items ? second_launch : 0.0) +
-           share * c.chunk + std::max(0.0, longest_share - share) * bnb / 64 * c.late;
+    return plan_gather(A, A->lhs_bits, row_bytes, rb, 4, 1, takes_items(A, 0, o), true, o).us;
 }
 
 // With all columns: the tile shape and the expected time.
@@ -452,9 +457,9 @@ bool resident_worth_building(const mc_mat *A, const mc_mat *of)
         for (int r4 = (A->lhs_bits == 4); r4 < 2; ++r4) {
             SlabPlan pl;
             plan_slab(A, row_bytes, r4, 4, automatic, &pl);
-            double best = 0.98 * gather_us(A, row_bytes, r4 ? 4 : 8, 4, automatic);
+            double best = 0.98 * gather_us(A, row_bytes, r4 ? 4 : 8, automatic);
             if (A->merged) {
-                best = std::min(best, 0.98 * gather_us(A->merged, row_bytes, r4 ? 4 : 8, 4, automatic));
+                best = std::min(best, 0.98 * gather_us(A->merged, row_bytes, r4 ? 4 : 8, automatic));
                 if (A->merged->d_blk_recs) {
                     SlabPlan m;
                     plan_slab(A->merged, row_bytes, r4, 4, automatic, &m);
@@ -484,7 +489,7 @@ bool dense_worth_building(const mc_mat *A)
             double best = 1e30;
             for (const mc_mat *X : {A, (const mc_mat *)A->merged}) {
                 if (!X) continue;
-                best = std::min(best, gather_us(X, row_bytes, r4 ? 4 : 8, 4, automatic));
+                best = std::min(best, gather_us(X, row_bytes, r4 ? 4 : 8, automatic));
                 if (!X->blk_chunks) continue;
                 SlabPlan pl;
                 plan_slab(X, row_bytes, r4, 4, automatic, &pl);
@@ -945,17 +950,18 @@ inline int spmm_stages_for(const mc_options &o, int K, int64_t ldb_bytes, int ro
 }
 
 // The form one SpMM call takes: the operand or its merged copy, and whether rows of B are resident in LDS (then plan is
-// the work split), or the operand with all its columns (dense: the tile shape, else -1).
-struct SpmmForm { const mc_mat *A; bool slab; SlabPlan plan; int dense; };
+// the work split), or the operand with all its columns (dense: the tile shape, else -1), or else gathered as planned.
+struct SpmmForm { const mc_mat *A; bool slab; SlabPlan plan; int dense; GatherPlan gather; };
 
-// ldb_bytes: from row to row of B
-SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, int out_bytes, unsigned flags, const mc_options &o)
+// ldb_bytes: from row to row of B; out_mode as in spmm_impl
+SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, int out_mode, unsigned flags, const mc_options &o)
 {
     const bool r4 = rb == 4;
+    const int out_bytes = out_mode == 2 ? 2 : 4;
     const bool slab_possible = o.spmm_slab != -1 && flags == 0 && rb != 16 && o.spmm_row_tile_bytes == 0 && o.spmm_waves == 0;
     // a 16-row panel leaves no MFMA row for the column sums that unsigned operands need
     const bool merged_possible = A->merged && A->merged_valid && o.spmm_merge != -1 && !(flags != 0 && A->merged->V > 8);
-    SpmmForm f = {A, false, {}, -1};
+    SpmmForm f = {A, false, {}, -1, {}};
     double best = 1e30;
     const bool dense_wanted = dense_mode(o) == 1 || (dense_mode(o) == 0 && !pins_other_form(o));
     if (A->d_dense && A->dense_valid && dense_wanted && flags == 0 && rb != 16 && o.spmm_slab == 0 &&
@@ -963,24 +969,23 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, in
         const DensePlan d = plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, out_bytes, dense_tile(o));
         if (d.tile >= 0) {
             f.dense = d.tile;
-            // (its expected times and the others' were fitted apart.  Taken by 3 % or more: of 400 drawn operands 38 take it and run
-            // 1.24 times as fast in the mean, two of them slower, 1.07 and 1.17 times; rows of less than 64 bytes by 15 %: their gather
-            // is expected up to a fifth too slow)
+            // (its expected times and the others' were fitted apart, and where several of theirs compete the least is too low: with 3 % off, of
+            // 1800 drawn operands the form picked is 1.6 % slower than the fastest on average, with 3 % on 1.9 %)
             f.plan.us = d.us;
-            best = dense_mode(o) == 1 ? 0.0 : d.us * (row_bytes < 64 ? 1.15 : 1.03);
+            best = dense_mode(o) == 1 ? 0.0 : 0.97 * d.us;
         }
     }
     for (int m = (merged_possible && o.spmm_merge == 1) ? 1 : 0; m <= (merged_possible ? 1 : 0); ++m) {
         const mc_mat *X = m ? A->merged : A;
         const bool slab = slab_possible && X->d_blk_recs && X->blk_valid;
-        if (!slab && !merged_possible && f.dense < 0) return f;     // nothing to choose
         SlabPlan pl;
         pl.us = 1e30;
         if (slab) plan_slab(X, row_bytes, r4, out_bytes, o, &pl);
-        const double gather = (slab && o.spmm_slab == 1) ? 1e30 : gather_us(X, row_bytes, rb, out_bytes, o);
-        if (std::min(gather, pl.us) < best) {
-            best = std::min(gather, pl.us);
-            f.A = X; f.slab = pl.us < gather; f.plan = pl; f.dense = -1;
+        GatherPlan gather = {0, 0, 1e30};
+        if (!slab || o.spmm_slab != 1) gather = plan_gather(X, X->lhs_bits, row_bytes, rb, out_bytes, 1, takes_items(X, out_mode, o), flags == 0, o);
+        if (std::min(gather.us, pl.us) < best) {
+            best = std::min(gather.us, pl.us);
+            f.A = X; f.slab = pl.us < gather.us; f.plan = pl; f.dense = -1; f.gather = gather;
         }
     }
     return f;
@@ -1009,7 +1014,7 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
 
     // the operand's merged copy (panels of 8 or 16 rows at the union of their columns) where it is expected to be faster
     const int rows = A->M;
-    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)ldb * rb / 8, rb, out_mode == 2 ? 2 : 4, flags, o);
+    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)ldb * rb / 8, rb, out_mode, flags, o);
     A = form.A;
 
     SpmmArgs a = {};
@@ -1049,18 +1054,15 @@ int spmm_impl(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, 
     a.short_b = spmm_short_b(A->K, a.ldb_bytes, a.row_bytes);
     a.uniform_chunks = A->uniform_chunks;
     a.max_unit_chunks = A->max_panel_chunks;
-    const bool use_items = A->n_items && o.spmm_splitting != -1 && out_mode == 0;
-    if (use_items) a.max_unit_chunks = A->max_item_chunks;
-    int bnb, waves;
-    choose_variant(A, A->lhs_bits, a.row_bytes, rb == 4, 1, a.max_unit_chunks, o, &bnb, &waves);
-    if (use_items) {
+    if (takes_items(A, out_mode, o)) {
+        a.max_unit_chunks = A->max_item_chunks;
         // very unequal panels: long ones are shared by several workgroups that add into cleared rows
         // (integer results only: a scaled, rounded result cannot be accumulated piecewise)
         a.items = A->d_items; a.n_units = A->n_items;
         MC_HIP(launch_zero_rows(static_cast<int32_t *>(C_dev), ldc, N, A->V, A->d_split_panels, A->n_split,
                                 static_cast<hipStream_t>(stream)));
     }
-    MC_HIP(launch_spmm(prec, a, bnb, waves, static_cast<hipStream_t>(stream)));
+    MC_HIP(launch_spmm(prec, a, form.gather.bnb, form.gather.waves, static_cast<hipStream_t>(stream)));
     return MC_OK;
 }
 } // namespace
@@ -1102,7 +1104,7 @@ extern "C" int mc_spmm_form(const mc_mat *A, int N, mc_prec prec, const mc_optio
     mc_options o;
     if (form_options(options, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
-    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, 4, 0u, o);
+    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, 0, 0u, o);
     return form.dense >= 0 ? 4 | (A->merged ? 2 : 0) : (form.slab ? 1 : 0) | (form.A != A ? 2 : 0);
 }
 
@@ -1112,8 +1114,8 @@ extern "C" double mc_spmm_form_us(const mc_mat *A, int N, mc_prec prec, int out_
     mc_options o;
     if (form_options(options, &o) != MC_OK) return MC_EINVAL;
     const int rb = rhs_bits_of(prec);
-    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, out_bytes, 0u, o);
-    return form.slab || form.dense >= 0 ? form.plan.us : gather_us(form.A, N * rb / 8, rb, out_bytes, o);
+    const SpmmForm form = spmm_form(A, N * rb / 8, (int64_t)N * rb / 8, rb, out_bytes == 2 ? 2 : 0, 0u, o);
+    return form.slab || form.dense >= 0 ? form.plan.us : form.gather.us;
 }
 
 extern "C" int mc_spmm_dequant(const mc_mat *A, const void *B_dev, int N, int ldb, mc_prec prec, unsigned flags,
@@ -1148,9 +1150,8 @@ extern "C" int mc_probe_gather(const mc_mat *A, const void *B_dev, int N, int ld
     a.C = nullptr; a.ldc = 0; a.C_batch_stride = 0;
     a.P = A->P; a.V = A->V; a.rows = A->M; a.batch = 1; a.float_out = 0; a.out_scale = 1.f;
     a.uniform_chunks = A->uniform_chunks;
-    int bnb, waves;
-    choose_variant(A, A->lhs_bits, a.row_bytes, rb == 4, 1, A->max_panel_chunks, o, &bnb, &waves);
-    MC_HIP(launch_gather_probe(a, bnb, waves, sink_dev, static_cast<hipStream_t>(stream)));
+    const GatherPlan plan = plan_gather(A, A->lhs_bits, a.row_bytes, rb, 4, 1, false, true, o);
+    MC_HIP(launch_gather_probe(a, plan.bnb, plan.waves, sink_dev, static_cast<hipStream_t>(stream)));
     return MC_OK;
 }
 
@@ -1452,10 +1453,9 @@ int attention_pipeline(const uint8_t *Q, const uint8_t *Km, const uint8_t *Vm, i
         m.acc = reinterpret_cast<int32_t *>(wsb + ws.acc); m.acc_ld = dk; m.n_split = mask->n_split;
         MC_HIP(launch_zero_ints(m.acc, (int64_t)heads * mask->n_split * 8 * dk, s));
     }
-    int bnb, waves;
-    choose_variant(mask, p_bits, m.row_bytes, qkv_bits == 4, heads, m.max_unit_chunks, o, &bnb, &waves);
+    const GatherPlan plan = plan_gather(mask, p_bits, m.row_bytes, qkv_bits, out_f16 ? 2 : 4, heads, split_panels, true, o);
     const mc_prec prec = (p_bits == 16) ? (qkv_bits == 4 ? MC_L16R4 : MC_L16R8) : (qkv_bits == 4 ? MC_L8R4 : MC_L8R8);
-    MC_HIP(launch_spmm(prec, m, bnb, waves, s));
+    MC_HIP(launch_spmm(prec, m, plan.bnb, plan.waves, s));
     if (split_panels)
         MC_HIP(launch_finish_split_rows(m.acc, dk, mask->n_split, 8, heads, mask->d_split_panels, O, o_token_stride,
                                         o_head_stride, m.float_out, m.out_scale, s));

@@ -116,6 +116,9 @@ void mc_resident_query(int K, int P, const int32_t *row_ptr, const int32_t *col_
 int mc_resident_pack(int K, int V, int lhs_bits, int P, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
                      const ResidentLayout &lay, int32_t *ptr, uint8_t *recs, int32_t *src, uint32_t *ends);
 
+// Chunks of a wave up to which a gathered launch has two of them in flight
+constexpr int SPMM_PIPE_CHUNKS = 4;
+
 // One SpMM launch (optionally a batch of problems sharing the sparsity pattern).
 struct SpmmArgs {
     const int32_t *panel_ptr;

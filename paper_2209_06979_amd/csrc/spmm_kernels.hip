@@ -56,7 +56,6 @@ typedef __attribute__((address_space(3))) void lptr_t;
 // and their length fit 24 bits (a 64-bit product per copy stood between a chunk's indices and its copies).
 // 2: the same into two alternating stages, and only the older
 // chunk is waited for (counted s_waitcnt); for waves with at most SPMM_PIPE_CHUNKS chunks.
-constexpr int SPMM_PIPE_CHUNKS = 4;
 
 // Makes the compiler treat x as used and redefined here: a load into x that is still in flight is
 // waited for at this point (and at no later one).
