@@ -570,7 +570,9 @@ int mc_set_softmax_variant(int variant);
 /* Attention path: 0 = automatic (a single fused kernel when dk is at most 128 and no panel holds
  * more than 4096 vectors -- one, two, four or eight waves per (panel, head) for panels of up to 512,
  * 1024, 2048, 4096 vectors, more waves than that when the launch is small; two neighbouring heads per
- * workgroup for token-major tensors once the launch has 2048 (panel, head) units, 4096 where dk is below 64 -- or when dk is at
+ * workgroup for token-major tensors once the launch has 2048 (panel, head) units, or 1024 of them and 12500 chunks of 64 vectors;
+ * where dk is below 64 with those chunks alone, in tokens of at least 96 bytes and rows of more than 32 or panels of up to 1024 vectors,
+ * and any from 4096 units and 10000 chunks on -- or when dk is at
  * most 192, no panel holds more than 2048 vectors and spmm_splitting does not ask for the sharing of
  * long panels, which only the pipeline has; else the pipeline of kernels), 1 = always the pipeline: one kernel that computes the scores of a panel,
  * keeps them in on-chip memory, takes the softmax and writes the integer codes in the SpMM's operand

@@ -1556,14 +1556,24 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 // Halving the gather requests pays once the launch fills the chip (2048 (panel, head) units and
                 // more: 13.3 against 15.6 us for 4096 of them; 5.0 against 4.7 us for 128).  Smaller launches get
                 // more waves per unit instead, until about 2048 waves are in flight and while every wave still
-                // has a chunk (256 units of 7 chunks: 5.9 us with one wave each, 4.5 us with four).
+                // has a chunk (256 units of 7 chunks: 5.9 us with one wave each, 4.5 us with four; of 3 chunks, dk = 80 - 96, 170 to 438
+                // units 6.0 - 6.9 with two, 5.5 - 6.3 with four, dk = 64 2 % less).
                 const int64_t units = (int64_t)n_panels * heads * batch;
-                // (Shorter heads from 4096 units on: 8 x 8 heads x 1584, dk = 48, 84 % empty 40.9 -> 33.7 us, 8 heads x 4896, 83 % 72.1 -> 46.4,
-                // 8 x 8 x 1888, dk = 32 48.1 -> 43.0; 2048 to 4096 units 0.94 - 1.2 times as fast.)
-                hpg = (pairs && units >= (fills ? 2048 : 4096) && wpp < 8) ? 2 : 1;
+                // Two heads, by 240 drawn layers in each form: from 1024 units on where they have 12500 chunks (dk = 64, 1300 to 1700 units of
+                // 13 to 18 chunks 1.03 - 1.16 times as fast, below that 0.9 - 1.06), and shorter heads there, too (8 heads x 3384, dk = 48, 9 chunks 35.7 -> 24.2 us,
+                // 4 x 3992, 12 chunks 24.3 -> 17.3; 64 layers of 1024 to 4096 units 1.07 in the mean), but for tokens of less than 96 bytes, whose
+                // line holds both heads already (0.92 - 1.03), and rows of up to 32 bytes by four waves each (0.94 - 1.08).  Short heads
+                // of 4096 units and more from 10000 chunks on (fewer: 0.95 - 1.0).
+                const double work = (double)units * std::min(avg, (double)max_chunks);
+                const int64_t head_bytes = (int64_t)dk * qkv_bits / 8;
+                const bool long_enough = units >= 1024 && work >= 12500.0;
+                const bool two = fills ? units >= 2048 || long_enough
+                                       : units >= 4096 ? work >= 10000.0
+                                                       : long_enough && f.in_token_stride >= 96 && (head_bytes > 32 || wpp < 4);
+                hpg = (pairs && two && wpp < 8) ? 2 : 1;
                 // (Rows of 256 bytes, too, where four waves' stages take half a compute unit's LDS: against 1024 waves in flight 46 drawn layers of
                 // dk = 144 - 192 1.03 times as fast in the mean, up to 1.23.  4096 waves: 0.98, down to 0.73.)
-                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp * 2 <= avg) wpp *= 2;
+                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp + 1 <= avg) wpp *= 2;
             } else {
                 if (o.attention_mode == 3 && wpp < 2) wpp = 2;
                 if (o.attention_mode == 4 && wpp < 4) wpp = 4;
