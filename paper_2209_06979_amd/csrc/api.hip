@@ -1574,6 +1574,9 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 // (Rows of 256 bytes, too, where four waves' stages take half a compute unit's LDS: against 1024 waves in flight 46 drawn layers of
                 // dk = 144 - 192 1.03 times as fast in the mean, up to 1.23.  4096 waves: 0.98, down to 0.73.)
                 if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp + 1 <= avg) wpp *= 2;
+                // (Eight waves for nine chunks: 225 to 253 units of 9 or 10 1.04 times as fast; 8-bit inputs with 5 to 8 chunks 0.93 - 1.0, nibbles, whose
+                // rows take longer to multiply than to fetch, 1.0 - 1.07 from 5 chunks on.)
+                if (hpg == 1 && wpp == 4 && tile <= 128 && units * 8 <= 2048 && std::min(avg, (double)max_chunks) >= (qkv_bits == 4 ? 5.0 : 9.0)) wpp = 8;
             } else {
                 if (o.attention_mode == 3 && wpp < 2) wpp = 2;
                 if (o.attention_mode == 4 && wpp < 4) wpp = 4;

@@ -24,6 +24,8 @@ pytestmark = pytest.mark.gpu
     (32, 8, 8, 8, 4, 1032, 0.8),      # ... of 4 chunks: two heads
     (64, 8, 8, 1, 4, 520, 0.7), (96, 16, 8, 1, 3, 520, 0.7), (128, 8, 4, 1, 2, 520, 0.7), (160, 8, 8, 1, 2, 520, 0.7),  # 3 chunks, four waves
     (80, 8, 8, 2, 4, 520, 0.7),       # 520 units of 3 chunks: two waves
+    (64, 16, 8, 1, 2, 1024, 0.4), (112, 8, 8, 1, 1, 1032, 0.42), (128, 8, 4, 1, 1, 520, 0.38), (32, 16, 4, 1, 3, 520, 0.38),  # eight waves
+    (64, 8, 8, 1, 2, 1032, 0.42),     # 258 units of 10 chunks: four (panels beyond 8 chunks: at least two)
 ])
 @pytest.mark.parametrize("token_major", [True, False])
 def test_automatic_heads_and_waves(dk, p_bits, qkv_bits, batch, heads, L, sparsity, token_major):
