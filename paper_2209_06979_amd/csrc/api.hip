@@ -155,14 +155,20 @@ constexpr int gather_at_once(int bnb, bool r4, int stages, int waves)
     const int tile = 8 * ((r4 ? 2 * bnb : bnb) + 4) * 4, lds = waves * std::max(stages * MC_CHUNK * bnb, tile);
     return lds > 65536 ? 0 : 256 * std::min({163840 / lds, 32 / waves, 16});
 }
-struct GatherAtOnce { int n[2][3][2][4]; };
+// waves: log2 of the most waves up to 1 << w that fit; n, part: workgroups at once with these, and its reciprocal
+struct GatherAtOnce { struct { int waves; double n, part; } with[2][3][2][4]; };
 constexpr GatherAtOnce gather_at_once_all()
 {
     GatherAtOnce g = {};
     for (int r4 = 0; r4 < 2; ++r4)
         for (int t = 0; t < 3; ++t)
             for (int st = 0; st < 2; ++st)
-                for (int w = 0; w < 4; ++w) g.n[r4][t][st][w] = gather_at_once(64 << t, r4, st + 1, 1 << w);
+                for (int w = 0; w < 4; ++w) {
+                    int fits = w;
+                    while (gather_at_once(64 << t, r4, st + 1, 1 << fits) == 0) --fits;
+                    const double n = gather_at_once(64 << t, r4, st + 1, 1 << fits);
+                    g.with[r4][t][st][w] = {fits, n, 1.0 / n};
+                }
     return g;
 }
 
@@ -196,34 +202,37 @@ GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int
     const bool r4 = rb == 4;
     const Cost *costs = cost[rb == 16 ? 6 : (r4 ? 0 : 3) + (lhs_bits > 8 ? 2 : A->V == 16 ? 1 : 0)];
     const double chunks = (double)(A->nslots / MC_CHUNK) * batch, units = (double)(items ? A->n_items : A->P) * batch;
-    const double lines = (double)A->nvec * batch, stored = (double)A->M * batch * (row_bytes * 8 / rb) * out_bytes;
+    const double lines = (double)A->nvec * batch, stored = (double)A->M * batch * ((row_bytes << 3 >> (rb == 4 ? 2 : rb == 8 ? 3 : 4)) * out_bytes);
+    const double per_unit = chunks / std::max(1.0, units);
     const int longest = items ? A->max_item_chunks : A->max_panel_chunks;
+    // (every call works this out: no division from here on)
+    static constexpr double PART[4] = {1.0, 0.5, 0.25, 0.125};
     GatherPlan best = {64, 1, 1e30};
     for (int t = 0; t < (wide && !r4 ? 3 : 2); ++t) {
         const int bnb = 64 << t;
         if (o.spmm_row_tile_bytes ? std::min(o.spmm_row_tile_bytes, wide && !r4 ? 256 : 128) != bnb : bnb > 64 && bnb >= 2 * row_bytes) continue;
         const Cost &c = costs[t];
-        int unit = bnb;                                   // rows start at multiples of this, tiles too
-        while (row_bytes % unit || unit > 128) unit /= 2;
-        const int tiles = (row_bytes + bnb - 1) / bnb;
+        int unit = std::min(bnb, 128);                    // rows start at multiples of this, tiles too
+        while (row_bytes & (unit - 1)) unit >>= 1;
+        const int tiles = (row_bytes + bnb - 1) >> (6 + t);
         const double groups = std::max(1.0, units * tiles), steps = chunks * tiles;
         const double fixed = c.start + lines * (row_bytes + tiles * (128 - unit)) * c.line + stored * c.store + (items ? c.items : 0.0);
         for (int w = 0; w < 4; ++w) {
-            const int waves = 1 << w;
-            if (o.spmm_waves && o.spmm_waves != waves) continue;
-            const int *fits = at_once.n[r4][t][0];
-            if (!o.spmm_waves && !fits[w]) break;
+            if (o.spmm_waves && o.spmm_waves != 1 << w) continue;
+            const auto *fits = at_once.with[r4][t][0] + w, *two = at_once.with[r4][t][1] + w;
+            if (!o.spmm_waves && fits->waves != w) break;
             // two chunks in flight where no wave has more (the launcher's rule, with the waves it then allows)
-            const int *two = at_once.n[r4][t][1];
-            int w1 = w, w2 = w;
-            while (!fits[w1]) --w1;
-            while (!two[w2]) --w2;
-            const bool pipe = o.spmm_stages != 1 && (longest + (1 << w2) - 1) >> w2 <= SPMM_PIPE_CHUNKS;
-            const int wk = pipe ? w2 : w1;
-            const double fit = (pipe ? two : fits)[wk], held = std::min(groups, fit), turns = groups / held;
-            const double share = steps / (held * (1 << wk)), late = std::max(0.0, (double)longest / (1 << wk) - share);
-            const double us = fixed + groups * (1 << wk) * c.wave + share * c.chunk + late * c.late + (std::ceil(turns) - turns) * c.last;
-            if (us < best.us) best = {bnb, waves, us};
+            if (o.spmm_stages != 1 && (longest + (1 << two->waves) - 1) >> two->waves <= SPMM_PIPE_CHUNKS) fits = two;
+            const double part = PART[fits->waves];
+            double us = fixed + groups * (1 << w) * c.wave, share = per_unit * part;
+            if (groups > fits->n) {
+                const double turns = groups * fits->part;
+                const int64_t whole = (int64_t)turns;
+                share = steps * fits->part * part;
+                if (turns > (double)whole) us += ((double)(whole + 1) - turns) * c.last;
+            }
+            us += share * c.chunk + std::max(0.0, longest * part - share) * c.late;
+            if (us < best.us) best = {bnb, 1 << w, us};
         }
     }
     return best;
