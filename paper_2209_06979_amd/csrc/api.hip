@@ -1586,6 +1586,9 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 // (Eight waves for nine chunks: 225 to 253 units of 9 or 10 1.04 times as fast; 8-bit inputs with 5 to 8 chunks 0.93 - 1.0, nibbles, whose
                 // rows take longer to multiply than to fetch, 1.0 - 1.07 from 5 chunks on.)
                 if (hpg == 1 && wpp == 4 && tile <= 128 && units * 8 <= 2048 && std::min(avg, (double)max_chunks) >= (qkv_bits == 4 ? 5.0 : 9.0)) wpp = 8;
+                // (A few more units than SIMDs, 1024, give some of them two waves and most one; of six chunks on, two waves each: 40 layers of 1026 to 1264 units of 6 to 8
+                // chunks 1.0 - 1.18 times as fast, 3 x 3352, dk = 80, 6 chunks 13.9 -> 12.5 us.  Of 3 to 5 chunks 0.95 - 1.08; from 1326 units on 0.8 - 1.04.)
+                if (hpg == 1 && wpp == 1 && tile <= 128 && units <= 1280 && std::min(avg, (double)max_chunks) >= 6.0) wpp = 2;
             } else {
                 if (o.attention_mode == 3 && wpp < 2) wpp = 2;
                 if (o.attention_mode == 4 && wpp < 4) wpp = 4;

@@ -25,6 +25,7 @@ pytestmark = pytest.mark.gpu
     (64, 8, 8, 1, 4, 520, 0.7), (96, 16, 8, 1, 3, 520, 0.7), (128, 8, 4, 1, 2, 520, 0.7), (160, 8, 8, 1, 2, 520, 0.7),  # 3 chunks, four waves
     (80, 8, 8, 2, 4, 520, 0.7),       # 520 units of 3 chunks: two waves
     (64, 16, 8, 1, 2, 1024, 0.4), (112, 8, 8, 1, 1, 1032, 0.42), (128, 8, 4, 1, 1, 520, 0.38), (32, 16, 4, 1, 3, 520, 0.38),  # eight waves
+    (80, 16, 8, 1, 3, 2736, 0.87), (64, 8, 4, 1, 3, 2736, 0.87), (112, 8, 8, 1, 5, 2048, 0.8),  # 1026 and 1280 units of 6 and 7 chunks: two waves
     (64, 8, 8, 1, 2, 1032, 0.42),     # 258 units of 10 chunks: four (panels beyond 8 chunks: at least two)
 ])
 @pytest.mark.parametrize("token_major", [True, False])
