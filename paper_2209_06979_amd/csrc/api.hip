@@ -454,38 +454,42 @@ DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_byt
     return best;
 }
 
-// Whether the LDS-ordered copy is built: the form is expected to be faster by a twentieth for wide rows of B, or for rows of two lines; by a
-// tenth at least where the merged copy has such a copy already.  (Of 1385 drawn operands 33 then have both, with 2 %
-// 106; the forms they run in lose the same 2.0 % over the best on average.  A twentieth, an expected time's own error: with 2 % operands of
-// 1000 to 2000 rows had the copy for what is no gain, mc_mat_create 1.16 instead of 0.78 ms at 2048 x 2048, 90 % empty, and new values to
-// write there; the expected times of 120 drawn calls are the same, 5.74 us in the mean.)
-// of: the operand whose merged copy A is (else null); the same holds against the copy that it could have, where that has the shorter
-// records of panels of 8 rows (otherwise the merged copy's is nearly always the faster one).
-bool resident_worth_building(const mc_mat *A, const mc_mat *of)
+// Which of an operand and its merged copy (null: none) get an LDS-ordered copy.  One does where its form is expected to be faster than either gather
+// by a twentieth for some width of B, rows of 128 to 1024 bytes; of two that do, the one that takes more off over these widths, and the other where it is
+// expected to be faster than that one, too, by a tenth for some width.  Both are decided at once: with the merged copy decided first, giving way to what
+// the given operand could have, that one failed its own test at times, and of 10731 operands of 4- and 8-bit values 253 had neither (14952 x 531, V = 8,
+// L4-R4 gathered where it had run resident).
+// (Of 1385 drawn operands 33 had both copies with a tenth, with 2 % 106; the forms they run in lose the same 2.0 % over the best on average.  A
+// twentieth is an expected time's own error: with 2 % operands of 1000 to 2000 rows had the copy for what is no gain, mc_mat_create 1.16 instead of
+// 0.78 ms at 2048 x 2048, 90 % empty, and new values to write there.)
+struct ResidentCopies { bool given, merged; };
+ResidentCopies resident_worth_building(const mc_mat *A, const mc_mat *merged)
 {
     const mc_options automatic = {};
+    const mc_mat *const of[2] = {A, merged};
+    bool worth[2] = {}, beside[2] = {};                   // (a copy beside the other one)
+    double taken_off[2] = {};                             // of the faster gather's logarithm
     for (int row_bytes : {1024, 512, 256, 128}) {
         for (int r4 = (A->lhs_bits == 4); r4 < 2; ++r4) {
-            SlabPlan pl;
-            plan_slab(A, row_bytes, r4, 4, automatic, &pl);
-            double best = 0.95 * gather_us(A, row_bytes, r4 ? 4 : 8, automatic);
-            if (A->merged) {
-                best = std::min(best, 0.95 * gather_us(A->merged, row_bytes, r4 ? 4 : 8, automatic));
-                if (A->merged->d_blk_recs) {
-                    SlabPlan m;
-                    plan_slab(A->merged, row_bytes, r4, 4, automatic, &m);
-                    best = std::min(best, 0.9 * m.us);
-                }
+            double gather = 1e30, us[2] = {1e30, 1e30};
+            for (int i = 0; i < 2; ++i) {
+                if (!of[i]) continue;
+                gather = std::min(gather, gather_us(of[i], row_bytes, r4 ? 4 : 8, automatic));
+                if (!of[i]->blk_chunks) continue;
+                SlabPlan pl;
+                plan_slab(of[i], row_bytes, r4, 4, automatic, &pl);
+                us[i] = pl.us;
             }
-            if (of && of->blk_chunks && resident_half(of->V, of->lhs_bits)) {
-                SlabPlan given;
-                plan_slab(of, row_bytes, r4, 4, automatic, &given);
-                best = std::min(best, 0.9 * given.us);
+            for (int i = 0; i < 2; ++i) {
+                worth[i] |= us[i] < 0.95 * gather;
+                beside[i] |= us[i] < std::min(0.95 * gather, 0.9 * us[1 - i]);
+                taken_off[i] += std::log(gather / std::min(gather, us[i]));
             }
-            if (pl.us < best) return true;
         }
     }
-    return false;
+    if (!worth[0] || !worth[1]) return {worth[0], worth[1]};
+    const bool merged_first = taken_off[1] >= taken_off[0];
+    return {!merged_first || beside[0], merged_first || beside[1]};
 }
 
 } // namespace
@@ -567,9 +571,9 @@ void resident_layout(mc_mat *A, const int32_t *row_ptr, const int32_t *col_idx)
     A->blk_nt = rl.nt; A->block_rows = rl.block_rows; A->nblk = rl.nblk; A->blk_chunks = rl.nchunks;
 }
 
-// of: the operand whose merged copy this is (V up to 16, never merged again), else null
+// of: the operand whose merged copy this is (V up to 16, never merged again), else null; of_resident: whether that one gets an LDS-ordered copy
 int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx, const void *values,
-                    void *stream, const mc_mat *of, mc_mat **out)
+                    void *stream, const mc_mat *of, bool *of_resident, mc_mat **out)
 {
     if (!out) return MC_EINVAL;
     *out = nullptr;
@@ -701,6 +705,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     // 8-bit values) or 8 rows (two byte planes), see mc_merge_host.  Not for operands without vectors, and not
     // when the thread's options rule it out.
     std::vector<int32_t> m_src;
+    bool resident = false;                                // (decided with the merged copy's, where there is one)
     if (lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_slab != -1) resident_layout(A, row_ptr, col_idx);
     if (!of && lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_merge != -1) {
         const int rows = (lhs_bits == 4 || lhs_bits == 8) ? 16 : 8, group = rows / V;
@@ -724,7 +729,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
                                m_src.data());
             if (rc == MC_OK)
                 rc = mat_create_impl(ml.P * rows, K, rows, lhs_bits, m_row_ptr.data(), m_col_idx.data(), m_values.data(), stream, A,
-                                     &A->merged);
+                                     &resident, &A->merged);
             if (rc != MC_OK) {
                 free_device(A);
                 delete A;
@@ -741,7 +746,14 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     std::vector<uint32_t> blk_ends;
     if (lhs_bits != 0 && lay.nvec > 0 && t_options.spmm_slab != -1) {
         const ResidentLayout rl = {A->blk_nt, A->block_rows, A->nblk, A->blk_chunks};
-        if (rl.nchunks != 0 && (t_options.spmm_slab == 1 || resident_worth_building(A, of))) {
+        if (of) {
+            const ResidentCopies copies = resident_worth_building(of, A);
+            *of_resident = copies.given;
+            resident = copies.merged;
+        } else if (!A->merged) {
+            resident = resident_worth_building(A, nullptr).given;
+        }
+        if (rl.nchunks != 0 && (t_options.spmm_slab == 1 || resident)) {
             try {
                 blk_ptr.resize((size_t)lay.P * rl.nblk + 1);
                 blk_src.resize((size_t)rl.nchunks * MC_CHUNK);
@@ -882,7 +894,7 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
 extern "C" int mc_mat_create(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, const int32_t *col_idx,
                              const void *values, void *stream, mc_mat **out)
 {
-    return mat_create_impl(M, K, V, lhs_bits, row_ptr, col_idx, values, stream, nullptr, out);
+    return mat_create_impl(M, K, V, lhs_bits, row_ptr, col_idx, values, stream, nullptr, nullptr, out);
 }
 
 extern "C" int mc_mat_merged_info(const mc_mat *A, int *group, int64_t *nvec)

@@ -86,8 +86,9 @@ def load():
         _lib.host_limit.argtypes = [ctypes.c_size_t]
         _lib.mc_mat_create.argtypes, _lib.mc_mat_destroy.argtypes = mc.lib.mc_mat_create.argtypes, [ctypes.c_void_p]
         _lib.mc_mat_destroy.restype = None
-        for name in ("mc_spmm", "mc_spmm_ex", "mc_spmm_form", "mc_mat_set_values_device"):
+        for name in ("mc_spmm", "mc_spmm_ex", "mc_spmm_form", "mc_spmm_form_us", "mc_mat_set_values_device"):
             getattr(_lib, name).argtypes = getattr(mc.lib, name).argtypes
+        _lib.mc_spmm_form_us.restype = ctypes.c_double
         _lib.mc_set_thread_options.argtypes = _lib.mc_get_thread_options.argtypes = [ctypes.POINTER(mc.Options)]
     return _lib
 
@@ -115,6 +116,10 @@ class Mat:
     def form(self, N, options=None):
         """4: with all columns, else 1 (in LDS) and 2 (merged) added up."""
         return load().mc_spmm_form(self.handle, N, self.prec, options)
+
+    def us(self, N, options=None):
+        """The time expected of the form that a call takes."""
+        return load().mc_spmm_form_us(self.handle, N, self.prec, 4, options)
 
     def run(self, N, options=None, ex=False, flags=0, ld=None):
         """The kernel that a call launches, and its detail: chunks in flight, segments or tile."""
