@@ -145,29 +145,41 @@ int choose_sddmm_waves(const mc_mat *mask, int shares, int batch, int row_bytes,
     return w;
 }
 
+// (the forms with 32-bit lane offsets work out a lane's offset into B with one 24-bit multiplication)
+inline bool spmm_short_b(int K, int64_t ldb_bytes, int row_bytes)
+{
+    return (int64_t)(K - 1) * ldb_bytes + row_bytes < ((int64_t)1 << 32) && K <= (1 << 24) && ldb_bytes < (1 << 24);
+}
+inline int spmm_stages_for(const mc_options &o, int K, int64_t ldb_bytes, int row_bytes)
+{
+    return o.spmm_stages != 1 && spmm_short_b(K, ldb_bytes, row_bytes) ? 2 : 1;
+}
+
 // The tile (bytes of a row of B) and the waves per panel of a gathered SpMM, and its expected time in us.
 struct GatherPlan { int bnb, waves; double us; };
 
 // Workgroups of one gathered launch that the chip holds at once, by LDS (as in SpmmCfg) and wave slots; 0: more than the 64 KB that the
 // launcher gives a workgroup.
-constexpr int gather_at_once(int bnb, bool r4, int stages, int waves)
+constexpr int gather_at_once(int bnb, bool r4, int stages, int rows, int waves)
 {
-    const int tile = 8 * ((r4 ? 2 * bnb : bnb) + 4) * 4, lds = waves * std::max(stages * MC_CHUNK * bnb, tile);
+    const int tile = rows * ((r4 ? 2 * bnb : bnb) + 4) * 4, lds = waves * std::max(stages * MC_CHUNK * bnb, tile);
     return lds > 65536 ? 0 : 256 * std::min({163840 / lds, 32 / waves, 16});
 }
-// waves: log2 of the most waves up to 1 << w that fit; n, part: workgroups at once with these, and its reciprocal
-struct GatherAtOnce { struct { int waves; double n, part; } with[2][3][2][4]; };
+// waves: log2 of the most waves up to 1 << w that fit; n, part: workgroups at once with these, and its reciprocal; of the kernels with one and two
+// chunks in flight, and of the one for unsigned operands (one chunk, twelve rows in a tile)
+struct GatherAtOnce { struct { int waves; double n, part; } with[2][3][3][4]; };
 constexpr GatherAtOnce gather_at_once_all()
 {
     GatherAtOnce g = {};
     for (int r4 = 0; r4 < 2; ++r4)
         for (int t = 0; t < 3; ++t)
-            for (int st = 0; st < 2; ++st)
+            for (int kind = 0; kind < 3; ++kind)
                 for (int w = 0; w < 4; ++w) {
+                    const int stages = kind == 1 ? 2 : 1, rows = kind == 2 ? 12 : 8;
                     int fits = w;
-                    while (gather_at_once(64 << t, r4, st + 1, 1 << fits) == 0) --fits;
-                    const double n = gather_at_once(64 << t, r4, st + 1, 1 << fits);
-                    g.with[r4][t][st][w] = {fits, n, 1.0 / n};
+                    while (gather_at_once(64 << t, r4, stages, rows, 1 << fits) == 0) --fits;
+                    const double n = gather_at_once(64 << t, r4, stages, rows, 1 << fits);
+                    g.with[r4][t][kind][w] = {fits, n, 1.0 / n};
                 }
     return g;
 }
@@ -184,8 +196,9 @@ constexpr GatherAtOnce gather_at_once_all()
 // 81 % slower: 3004 x 2900, V = 4, 85 % empty, L16-R8, N = 208 13.5 -> 9.8 us; 10336 x 3053, V = 8, L4-R4, N = 288 52 -> 30 us (64-byte
 // tiles: with 128 bytes of nibbles half as many waves fit).
 // lhs_bits: width of the sparse operand's values in this launch (a mask carries none of its own).  items: the launch takes the operand's
-// work items.  wide: 256-byte tiles exist (they don't for unsigned operands and for rows of nibbles).
-GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int out_bytes, int batch, bool items, bool wide,
+// work items.  stages: chunks that the launch may have in flight (SpmmArgs).  unsigned_ops: the kernel for unsigned operands, which has one in flight and no
+// tiles of 256 bytes.
+GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int out_bytes, int batch, bool items, int stages, bool unsigned_ops,
                        const mc_options &o)
 {
     struct Cost { double start, line, store, wave, chunk, late, items, last; };
@@ -199,7 +212,7 @@ GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int
         {{2.53, 3.15e-8, 0, 0.000314, 0.376, 0.463, 2.08, 0.855}, {2.47, 2.78e-8, 6.96e-8, 0.000606, 0.612, 0.678, 2.28, 1.17}, {2.67, 2.41e-8, 9e-8, 0.00123, 0.954, 0.941, 1.57, 2.7}}
     };
     static constexpr GatherAtOnce at_once = gather_at_once_all();
-    const bool r4 = rb == 4;
+    const bool r4 = rb == 4, wide = !r4 && !unsigned_ops, two_stages = stages == 2 && !unsigned_ops;
     const Cost *costs = cost[rb == 16 ? 6 : (r4 ? 0 : 3) + (lhs_bits > 8 ? 2 : A->V == 16 ? 1 : 0)];
     const double chunks = (double)(A->nslots / MC_CHUNK) * batch, units = (double)(items ? A->n_items : A->P) * batch;
     const double lines = (double)A->nvec * batch, stored = (double)A->M * batch * ((row_bytes << 3 >> (rb == 4 ? 2 : rb == 8 ? 3 : 4)) * out_bytes);
@@ -208,9 +221,9 @@ GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int
     // (every call works this out: no division from here on)
     static constexpr double PART[4] = {1.0, 0.5, 0.25, 0.125};
     GatherPlan best = {64, 1, 1e30};
-    for (int t = 0; t < (wide && !r4 ? 3 : 2); ++t) {
+    for (int t = 0; t < (wide ? 3 : 2); ++t) {
         const int bnb = 64 << t;
-        if (o.spmm_row_tile_bytes ? std::min(o.spmm_row_tile_bytes, wide && !r4 ? 256 : 128) != bnb : bnb > 64 && bnb >= 2 * row_bytes) continue;
+        if (o.spmm_row_tile_bytes ? std::min(o.spmm_row_tile_bytes, wide ? 256 : 128) != bnb : bnb > 64 && bnb >= 2 * row_bytes) continue;
         const Cost &c = costs[t];
         int unit = std::min(bnb, 128);                    // rows start at multiples of this, tiles too
         while (row_bytes & (unit - 1)) unit >>= 1;
@@ -219,10 +232,10 @@ GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int
         const double fixed = c.start + lines * (row_bytes + tiles * (128 - unit)) * c.line + stored * c.store + (items ? c.items : 0.0);
         for (int w = 0; w < 4; ++w) {
             if (o.spmm_waves && o.spmm_waves != 1 << w) continue;
-            const auto *fits = at_once.with[r4][t][0] + w, *two = at_once.with[r4][t][1] + w;
+            const auto *fits = at_once.with[r4][t][unsigned_ops ? 2 : 0] + w, *two = at_once.with[r4][t][1] + w;
             if (!o.spmm_waves && fits->waves != w) break;
             // two chunks in flight where no wave has more (the launcher's rule, with the waves it then allows)
-            if (o.spmm_stages != 1 && (longest + (1 << two->waves) - 1) >> two->waves <= SPMM_PIPE_CHUNKS) fits = two;
+            if (two_stages && (longest + (1 << two->waves) - 1) >> two->waves <= SPMM_PIPE_CHUNKS) fits = two;
             const double part = PART[fits->waves];
             double us = fixed + groups * (1 << w) * c.wave, share = per_unit * part;
             if (groups > fits->n) {
@@ -407,10 +420,10 @@ void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_
 // Whether a gathered call takes the operand's work items (out_mode as in spmm_impl)
 bool takes_items(const mc_mat *A, int out_mode, const mc_options &o) { return A->n_items && o.spmm_splitting != -1 && out_mode == 0; }
 
-// Gathered, with int32 results
+// Gathered, with signed operands, int32 results and B's rows one after the other
 double gather_us(const mc_mat *A, int row_bytes, int rb, const mc_options &o)
 {
-    return plan_gather(A, A->lhs_bits, row_bytes, rb, 4, 1, takes_items(A, 0, o), true, o).us;
+    return plan_gather(A, A->lhs_bits, row_bytes, rb, 4, 1, takes_items(A, 0, o), spmm_stages_for(o, A->K, row_bytes, row_bytes), false, o).us;
 }
 
 // With all columns: the tile shape and the expected time.
@@ -962,16 +975,6 @@ extern "C" int mc_mat_set_values_device(mc_mat *A, const void *values_dev, void 
 }
 
 namespace {
-// (the forms with 32-bit lane offsets work out a lane's offset into B with one 24-bit multiplication)
-inline bool spmm_short_b(int K, int64_t ldb_bytes, int row_bytes)
-{
-    return (int64_t)(K - 1) * ldb_bytes + row_bytes < ((int64_t)1 << 32) && K <= (1 << 24) && ldb_bytes < (1 << 24);
-}
-inline int spmm_stages_for(const mc_options &o, int K, int64_t ldb_bytes, int row_bytes)
-{
-    return o.spmm_stages != 1 && spmm_short_b(K, ldb_bytes, row_bytes) ? 2 : 1;
-}
-
 // The form one SpMM call takes: the operand or its merged copy, and whether rows of B are resident in LDS (then plan is
 // the work split), or the operand with all its columns (dense: the tile shape, else -1), or else gathered as planned.
 struct SpmmForm { const mc_mat *A; bool slab; SlabPlan plan; int dense; GatherPlan gather; };
@@ -1005,7 +1008,10 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, in
         pl.us = 1e30;
         if (slab) plan_slab(X, row_bytes, r4, out_bytes, o, &pl);
         GatherPlan gather = {0, 0, 1e30};
-        if (!slab || o.spmm_slab != 1) gather = plan_gather(X, X->lhs_bits, row_bytes, rb, out_bytes, 1, takes_items(X, out_mode, o), flags == 0, o);
+        if (!slab || o.spmm_slab != 1) {
+            gather = plan_gather(X, X->lhs_bits, row_bytes, rb, out_bytes, 1, takes_items(X, out_mode, o), spmm_stages_for(o, X->K, ldb_bytes, row_bytes),
+                                 flags != 0, o);
+        }
         if (std::min(gather.us, pl.us) < best) {
             best = std::min(gather.us, pl.us);
             f.A = X; f.slab = pl.us < gather.us; f.plan = pl; f.dense = -1; f.gather = gather;
@@ -1173,7 +1179,7 @@ extern "C" int mc_probe_gather(const mc_mat *A, const void *B_dev, int N, int ld
     a.C = nullptr; a.ldc = 0; a.C_batch_stride = 0;
     a.P = A->P; a.V = A->V; a.rows = A->M; a.batch = 1; a.float_out = 0; a.out_scale = 1.f;
     a.uniform_chunks = A->uniform_chunks;
-    const GatherPlan plan = plan_gather(A, A->lhs_bits, a.row_bytes, rb, 4, 1, false, true, o);
+    const GatherPlan plan = plan_gather(A, A->lhs_bits, a.row_bytes, rb, 4, 1, false, spmm_stages_for(o, A->K, a.ldb_bytes, a.row_bytes), false, o);
     MC_HIP(launch_gather_probe(a, plan.bnb, plan.waves, sink_dev, static_cast<hipStream_t>(stream)));
     return MC_OK;
 }
@@ -1476,7 +1482,7 @@ int attention_pipeline(const uint8_t *Q, const uint8_t *Km, const uint8_t *Vm, i
         m.acc = reinterpret_cast<int32_t *>(wsb + ws.acc); m.acc_ld = dk; m.n_split = mask->n_split;
         MC_HIP(launch_zero_ints(m.acc, (int64_t)heads * mask->n_split * 8 * dk, s));
     }
-    const GatherPlan plan = plan_gather(mask, p_bits, m.row_bytes, qkv_bits, out_f16 ? 2 : 4, heads, split_panels, true, o);
+    const GatherPlan plan = plan_gather(mask, p_bits, m.row_bytes, qkv_bits, out_f16 ? 2 : 4, heads, split_panels, m.stages, false, o);
     const mc_prec prec = (p_bits == 16) ? (qkv_bits == 4 ? MC_L16R4 : MC_L16R8) : (qkv_bits == 4 ? MC_L8R4 : MC_L8R8);
     MC_HIP(launch_spmm(prec, m, plan.bnb, plan.waves, s));
     if (split_panels)

@@ -21,13 +21,14 @@ STUBS = r"""
 static std::atomic<size_t> limit{~(size_t)0};
 static std::atomic<long> allocations{0};
 static thread_local char called[64] = "";
-static thread_local int detail = 0;
+static thread_local int detail = 0, variant[2] = {0, 0};
 static hipError_t note(const char *what, int d = 0) { strcpy(called, what); detail = d; return hipSuccess; }
 extern "C" {
 void host_limit(size_t bytes) { limit = bytes; }
 long host_live() { return allocations; }
 const char *host_called() { return called; }
 int host_detail() { return detail; }
+int host_variant(int i) { return variant[i]; }
 hipError_t hipMalloc(void **p, size_t n)
 {
     if (n >= limit) return *p = nullptr, hipErrorOutOfMemory;
@@ -42,7 +43,11 @@ hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorInvalidVa
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { return memcpy(d, s, n), hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 }
-hipError_t launch_spmm(mc_prec, const SpmmArgs &a, int, int, hipStream_t) { return note("gather", a.stages); }
+hipError_t launch_spmm(mc_prec, const SpmmArgs &a, int bnb, int waves, hipStream_t)
+{
+    variant[0] = bnb; variant[1] = waves;
+    return note("gather", a.stages);
+}
 hipError_t launch_spmm_slab(mc_prec, const SlabArgs &, int nt, hipStream_t) { return note("lds", nt); }
 hipError_t launch_spmm_dense(mc_prec, const DenseArgs &, int tile, hipStream_t) { return note("dense", tile); }
 hipError_t launch_dense_fill(const DenseFillArgs &, hipStream_t) { return note("fill"); }
@@ -130,6 +135,11 @@ class Mat:
               L.mc_spmm(self.handle, at, N, ld, self.prec, at, N, None))
         assert rc == 0
         return L.host_called().decode(), L.host_detail()
+
+    def variant(self, N, options=None, **kw):
+        """The tile and the waves of the gathered kernel that a call launches."""
+        assert self.run(N, options, ex=True, **kw)[0] == "gather"
+        return load().host_variant(0), load().host_variant(1)
 
     def close(self):
         load().mc_mat_destroy(self.handle)

@@ -1,0 +1,35 @@
+"""The tile and waves that a gathered SpMM is given: the library's host code without a GPU."""
+import pytest
+
+from paper_2209_06979_amd import binding as mc
+import host_library as host
+
+SHAPES = [(2048, 4096, 8, 0.9), (4096, 2048, 8, 0.95), (1024, 3000, 4, 0.85), (8192, 4096, 2, 0.97), (256, 2304, 8, 0.7), (512, 700, 8, 0.5), (640, 5000, 4, 0.6)]
+
+
+@pytest.mark.parametrize("prec", ["L8R8", "L8R4", "L4R4"])
+@pytest.mark.parametrize("flags", [1, 2, 3])
+def test_unsigned_operands_have_one_chunk_in_flight(prec, flags):
+    """Their kernel never has two: what is picked for it does not depend on whether others may, nor is it a pair whose tiles do not fit."""
+    for M, K, V, empty in SHAPES:
+        A = host.Mat(M, K, V, empty, prec)
+        for N in (64, 96, 128, 256, 512, 1024):
+            got = A.variant(N, flags=flags)
+            assert got == A.variant(N, mc.Options(spmm_stages=1), flags=flags), (M, K, N)
+            tile = 12 * (got[0] * (2 if prec != "L8R8" else 1) + 4) * 4
+            assert got[0] < 256 and got[1] * max(64 * got[0], tile) <= 65536
+        A.close()
+
+
+@pytest.mark.parametrize("prec", ["L8R8", "L4R4", "L16R8", "L16R16"])
+def test_a_dense_operand_beyond_32_bit_offsets_has_one_chunk_in_flight(prec):
+    """Rows of B 16 MB and more apart: the launch has one chunk in flight, and its tile and waves are those of that kernel."""
+    for M, K, V, empty in SHAPES:
+        A = host.Mat(M, K, V, empty, prec)
+        gather = mc.Options(spmm_slab=-1, spmm_merge=-1)
+        one = mc.Options(spmm_slab=-1, spmm_merge=-1, spmm_stages=1)
+        far = (1 << 24) * 8 // A.rhs
+        for N in (64, 128, 256, 512):
+            assert A.run(N, gather, ex=True)[1] == 2 and A.run(N, gather, ex=True, ld=far)[1] == 1
+            assert A.variant(N, gather, ld=far) == A.variant(N, one) == A.variant(N, one, ld=far)
+        A.close()
