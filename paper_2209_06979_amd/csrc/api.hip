@@ -184,39 +184,42 @@ constexpr GatherAtOnce gather_at_once_all()
     return g;
 }
 
-// Gathered: the tile and the waves with the least expected time.  Launch and start; the 128-byte lines that rows touch, each tile by itself,
-// with rows at all multiples of their length; the stores; the waves; the chunks of a wave, one after the other, at an even share; those that
+// Gathered: the tile and the waves with the least expected time.  Launch and start; the staged bytes (padded slots and the unused part of a last tile
+// included); the 128-byte lines that rows touch, each tile by itself, with rows at all multiples of their length; B, which every XCD fetches for itself,
+// and the operand's values, which every tile reads again; the stores; the waves; the chunks of a wave, one after the other, at an even share; those that
 // the longest unit's waves still have then; the launch that clears rows when panels are cut into items; and a last turn of workgroups that
-// leaves compute units idle.  What a line, a wave or a chunk costs goes by the width of B, by the tile, and by whether A has two planes or
-// panels of 16 rows.  Fitted (non-negative least squares on the relative error) to every tile and number of waves on 2700 drawn operands
-// (sizes as at plan_slab), given and merged, three copies of everything in turn; then scaled to the times of the variants picked (the least
-// of several expected times is 3 - 6 % too low).  On 900 others: off by 8 % in the median and by 22 % in nine cases of ten; the variant
-// picked is 2.2 % slower than the fastest of the eight to twelve on average, by 9 % or less in nine cases of ten, by 30 % at worst.  Thresholds
-// on the rows' length and the panels' (64 bytes for short ones, 256 for long ones, waves until 2048 of them are on the chip) were 5.3 %, 18 % and
-// 81 % slower: 3004 x 2900, V = 4, 85 % empty, L16-R8, N = 208 13.5 -> 9.8 us; 10336 x 3053, V = 8, L4-R4, N = 288 52 -> 30 us (64-byte
-// tiles: with 128 bytes of nibbles half as many waves fit).
+// leaves compute units idle.  What each costs goes by the width of B, by the tile, by whether A has two planes or panels of 16 rows, and for
+// unsigned operands by the width of B.  Fitted (non-negative least squares on the relative error, a variant counting by how near it is to the
+// fastest of its operand) to every tile and number of waves on 4888 drawn operands (sizes as at plan_slab), given and merged, three copies of
+// everything in turn; then scaled to the times of the variants picked (the least of several expected times is 3 - 5 % too low).
+// On 843 others, given / merged: the time of the variant picked is off by 7.0 / 6.4 % in the median and by 17 % in nine cases of ten, and that
+// variant is 2.7 / 3.1 % slower than the fastest of the eight to twelve on average, by 11 % or less in nine cases of ten, by 57 % at worst (without the staged
+// bytes, B and the operand's values, as fitted before, 9.7 / 8.5 %, 24 % and 2.9 / 3.7 %; L12-R4, 1184 x 5592, unequal panels, gathered in 21 us where 15 were
+// expected).  Unsigned ones, 820 of both sets: 2.4 %.
 // lhs_bits: width of the sparse operand's values in this launch (a mask carries none of its own).  items: the launch takes the operand's
 // work items.  stages: chunks that the launch may have in flight (SpmmArgs).  unsigned_ops: the kernel for unsigned operands, which has one in flight and no
 // tiles of 256 bytes.
 GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int out_bytes, int batch, bool items, int stages, bool unsigned_ops,
                        const mc_options &o)
 {
-    struct Cost { double start, line, store, wave, chunk, late, items, last; };
-    static const Cost cost[7][3] = {
-        {{2.54, 2.94e-8, 7.57e-8, 0.00032, 0.405, 0.47, 1.68, 0.523}, {2.77, 4.08e-8, 6.51e-8, 0.000654, 0.675, 0.766, 1.18, 0.972}},
-        {{3.17, 3.3e-8, 0, 0.000525, 0.495, 0.479, 0, 0.991}, {3.64, 4.39e-8, 1.19e-9, 0.000961, 0.839, 0.757, 0, 1.52}},
-        {{2.48, 3.07e-8, 1.19e-7, 0.000329, 0.376, 0.394, 1.72, 0.414}, {2.64, 2.81e-8, 1.19e-7, 0.00071, 0.75, 0.698, 1.35, 1.25}},
-        {{2.34, 3.03e-8, 1.93e-8, 0.000252, 0.23, 0.29, 2.18, 0.343}, {2.3, 2.6e-8, 3.65e-8, 0.000546, 0.445, 0.493, 1.75, 0.863}, {2.63, 2.74e-8, 6.08e-8, 0.00101, 0.686, 0.721, 2.28, 1.98}},
-        {{2.8, 3.7e-8, 0, 0.000352, 0.282, 0.316, 2.87, 0.862}, {2.85, 3.42e-8, 0, 0.00066, 0.551, 0.52, 2.57, 1.55}, {3.61, 2.9e-8, 0, 0.00145, 0.868, 0.722, 0, 3.31}},
-        {{2.29, 3.43e-8, 3.14e-8, 0.000249, 0.263, 0.324, 1.66, 0.512}, {2.16, 2.94e-8, 6.68e-8, 0.000514, 0.536, 0.54, 1.64, 0.764}, {2.26, 2.54e-8, 6.63e-8, 0.00119, 0.832, 0.791, 1.05, 1.85}},
-        {{2.53, 3.15e-8, 0, 0.000314, 0.376, 0.463, 2.08, 0.855}, {2.47, 2.78e-8, 6.96e-8, 0.000606, 0.612, 0.678, 2.28, 1.17}, {2.67, 2.41e-8, 9e-8, 0.00123, 0.954, 0.941, 1.57, 2.7}}
+    struct Cost { double start, byte, line, store, wave, chunk, late, items, last, fetch, operand; };
+    static const Cost cost[9][3] = {
+        {{2.44, 1.26e-08, 2.43e-08, 4.84e-08, 0.00028, 0.349, 0.456, 1.44, 0.557, 2.84e-07, 1.76e-08}, {2.83, 5.73e-08, 1.27e-08, 1.13e-07, 0.000235, 0.461, 0.786, 1.15, 1.24, 7.64e-08, 0}},
+        {{3.07, 2.47e-08, 2.3e-08, 8.29e-09, 0.000466, 0.453, 0.468, 0, 1.38, 2.93e-07, 0}, {3.53, 5.44e-08, 1.49e-08, 8.77e-08, 0.000326, 0.734, 0.798, 0, 2.39, 1.06e-07, 0}},
+        {{2.4, 0, 2.29e-08, 6.51e-09, 0.000325, 0.368, 0.456, 1.68, 0.558, 3.76e-07, 1.03e-07}, {2.7, 3.08e-08, 1.13e-08, 1.14e-07, 0.000332, 0.675, 0.774, 1.48, 1.47, 1.9e-07, 4.52e-08}},
+        {{2.13, 0, 2.38e-08, 0, 0.000208, 0.201, 0.304, 2.01, 0.405, 3.87e-07, 1.35e-07}, {2.15, 1.87e-08, 1.6e-08, 1.89e-08, 0.000282, 0.364, 0.547, 1.68, 1.03, 2.81e-07, 1.76e-07}, {2.35, 2.69e-08, 6e-09, 1.05e-07, 0.00022, 0.565, 0.807, 2.22, 2.62, 3.92e-07, 2.57e-07}},
+        {{2.59, 3.8e-09, 3.38e-08, 0, 0.000324, 0.276, 0.317, 0, 1.07, 4.07e-07, 0}, {2.59, 0, 1.75e-08, 5.72e-09, 0.0003, 0.539, 0.608, 0, 2.33, 4.04e-07, 2.48e-07}, {3.38, 2.14e-08, 1.54e-08, 4.55e-08, 0.000297, 0.811, 0.793, 0, 4.96, 5.02e-07, 0}},
+        {{2.12, 0, 2.37e-08, 0, 0.000204, 0.226, 0.313, 2.17, 0.491, 4.17e-07, 9.92e-08}, {2.08, 1.25e-08, 1.87e-08, 5.6e-08, 0.000247, 0.448, 0.617, 3.11, 1.19, 3e-07, 1.09e-07}, {2.48, 1.55e-08, 1.51e-08, 9.49e-08, 0.000216, 0.649, 0.831, 3.12, 3.24, 3.56e-07, 1.33e-07}},
+        {{2.27, 0, 2.32e-08, 0, 0.000262, 0.29, 0.394, 2.22, 0.685, 3.07e-07, 9.67e-08}, {2.26, 1.31e-08, 1.86e-08, 4.02e-08, 0.000308, 0.526, 0.665, 1.72, 1.48, 2.76e-07, 1.03e-07}, {2.47, 1.87e-08, 1.15e-08, 1.89e-07, 0.000306, 0.845, 0.974, 0.388, 3.43, 3.82e-07, 8.31e-08}},
+        {{2.68, 1.1e-08, 2.35e-08, 5.4e-08, 0.000292, 0.398, 0.48, 1.63, 0.363, 3.67e-07, 2.66e-08}, {3.12, 3.23e-08, 1.2e-08, 1.25e-07, 0.000264, 0.737, 0.801, 0.938, 2.17, 1.73e-07, 0}},
+        {{2.49, 0, 2.38e-08, 0, 0.000174, 0.27, 0.348, 1.98, 0.272, 4.89e-07, 1.44e-07}, {2.43, 1.58e-08, 1.36e-08, 0, 0.00042, 0.561, 0.606, 1.47, 0.74, 4.07e-07, 1.74e-07}}
     };
     static constexpr GatherAtOnce at_once = gather_at_once_all();
     const bool r4 = rb == 4, wide = !r4 && !unsigned_ops, two_stages = stages == 2 && !unsigned_ops;
-    const Cost *costs = cost[rb == 16 ? 6 : (r4 ? 0 : 3) + (lhs_bits > 8 ? 2 : A->V == 16 ? 1 : 0)];
+    const Cost *costs = cost[unsigned_ops ? (r4 ? 7 : 8) : rb == 16 ? 6 : (r4 ? 0 : 3) + (lhs_bits > 8 ? 2 : A->V == 16 ? 1 : 0)];
     const double chunks = (double)(A->nslots / MC_CHUNK) * batch, units = (double)(items ? A->n_items : A->P) * batch;
     const double lines = (double)A->nvec * batch, stored = (double)A->M * batch * ((row_bytes << 3 >> (rb == 4 ? 2 : rb == 8 ? 3 : 4)) * out_bytes);
-    const double per_unit = chunks / std::max(1.0, units);
+    const double per_unit = chunks / std::max(1.0, units), fetch = (double)A->K * batch * row_bytes, slot_bytes = (lhs_bits == 12 ? 16 : lhs_bits) * A->V / 8.0;
     const int longest = items ? A->max_item_chunks : A->max_panel_chunks;
     // (every call works this out: no division from here on)
     static constexpr double PART[4] = {1.0, 0.5, 0.25, 0.125};
@@ -229,7 +232,8 @@ GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int
         while (row_bytes & (unit - 1)) unit >>= 1;
         const int tiles = (row_bytes + bnb - 1) >> (6 + t);
         const double groups = std::max(1.0, units * tiles), steps = chunks * tiles;
-        const double fixed = c.start + lines * (row_bytes + tiles * (128 - unit)) * c.line + stored * c.store + (items ? c.items : 0.0);
+        const double fixed = c.start + steps * MC_CHUNK * (bnb * c.byte + slot_bytes * c.operand) + lines * (row_bytes + tiles * (128 - unit)) * c.line +
+                             stored * c.store + fetch * c.fetch + (items ? c.items : 0.0);
         for (int w = 0; w < 4; ++w) {
             if (o.spmm_waves && o.spmm_waves != 1 << w) continue;
             const auto *fits = at_once.with[r4][t][unsigned_ops ? 2 : 0] + w, *two = at_once.with[r4][t][1] + w;
@@ -361,23 +365,35 @@ int rec_chunks(const mc_mat *A) { return resident_rec_chunks(A->nblk, A->V, A->l
 int resident_rec_bytes(const mc_mat *A) { return rec_chunks(A) * resident_chunk_bytes(A); }
 int64_t resident_records(const mc_mat *A) { return (A->blk_chunks + rec_chunks(A) - 1) / rec_chunks(A); }
 
-// Expected times in us of the two forms of the SpMM, fitted (non-negative least squares on the relative error) to 2700 drawn operands:
-// all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B of 32 .. 1024 bytes and more, two in three of them of
-// round length, half to 97 % empty, a quarter with panels of unequal length.  Timed with three copies of everything in turn, as a
-// program's operands alternate.  On 900 others a resident time is off by 6 % in the median and by 18 % in nine cases of ten (in blocks:
-// 14 %, 38 %), and the form picked (merged or not, resident, gathered or with all columns) is 1.8 % slower than the fastest on average, by 7 % or
-// less in nine cases of ten, by half at worst (with the constants before: 2.9 %, 11 %, 62 %; form, tile and waves together 2.7 % where 5.2 %).
+// Expected times in us of the resident form, fitted (least squares on the relative error, no constant below zero, a byte of a record above it: left
+// free, it came out as nothing for records of two chunks and nibbles of B, and of 88 drawn operands of panels of 8 rows seven ran as given, 1.07 - 1.25 times
+// as long as merged) to 4888 drawn operands: all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B of 32 .. 1024 bytes,
+// two in three of them of round length, half to 97 % empty, a quarter with panels of unequal length.  Timed with three copies of everything in turn, as a
+// program's operands alternate.  On 843 others a resident time is off by 6 % in the median and by 16 % in nine cases of ten (in blocks: 13 %, 30 %), and
+// the form, tile and waves picked together are 3.1 % slower than the fastest of all on average, by 10 % or less in nine cases of ten, by 81 % at worst
+// (with the constants and the copies before: 4.1 %, 14 %, 81 %).
 // Resident, all of B's rows at once: launch and start; the fill, a line of B per row, by how many workgroups there are to fill; per
 // step of a wave one part per MFMA and one per byte of a chunk's part of a record, both by how many of the sixteen waves have panels; the epilogues; the stores;
-// by the width of B and by whether the two chunks of a record share a request;
-// waves that share a panel meet; and the steps that the longest panel's waves still have when an even share would be done.
+// B, which every XCD fetches for itself; waves that share a panel meet; and the steps that the longest panel's waves still have when an even share would be
+// done.  By the width of B, by the tile that the copy is made for, and by what a request for operands brings: two planes of 8 rows or fewer, the 8 rows of two chunks, 16 rows.
 // In blocks: per block and pass the fill, per step of a wave its own reads, and per panel of a wave a start in each block.
 // (A: the operand's layout figures are enough, its copies need not exist yet)
 void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_options &o, SlabPlan *pl)
 {
-    struct Cost { double start, store, meet, fill, mfma, record, panel, late; };
-    static const Cost cost[2][2] = {{{3.93, 9.09e-8, 1.18, 0.000936, 0.0687, 9.07e-5, 0.00477, 0.0442}, {3.9, 9.7e-8, 0.76, 0.000832, 0.0618, 3.49e-5, 0.0029, 0.0414}},
-                                    {{3.99, 1.13e-7, 1.3, 0.000711, 0.0813, 5.36e-5, 0.00234, 0.108}, {4.31, 7.34e-8, 1.11, 0.000489, 0.0763, 0, 0.00458, 0.154}}};
+    struct Cost { double start, store, meet, fill, mfma, record, panel, late, fetch, uneven; };
+    // (two planes of 8 rows; half requests; panels of 16 rows; two planes of fewer rows; each in tiles of 32 and of 64 bytes)
+    static const Cost cost[2][4][2] = {
+        {{{3.72, 1.07e-7, 0.503, 0.000767, 0.0552, 6.77e-5, 0, 0.0414, 1.3e-6, 0.0203}, {3.77, 8.37e-8, 1.02, 0.00109, 0.056, 3.19e-5, 0.00528, 0.00978, 1.27e-6, 0.0212}},
+         {{3.79, 3.01e-8, 0.215, 0.000461, 0.0443, 6.68e-5, 0.00807, 0.0411, 1.43e-6, 0.0224}, {3.34, 7.28e-8, 0.853, 0.00103, 0.0567, 2e-5, 0.00598, 0.0404, 1.16e-6, 0.0217}},
+         {{3.77, 9.42e-8, 0.625, 0.000746, 0.074, 4.17e-5, 0, 0.0323, 1.27e-6, 0.012}, {3.61, 1.03e-7, 1.25, 0.00125, 0.0752, 2.64e-5, 0, 0.0631, 1.04e-6, 0.00624}},
+         {{3.07, 1.15e-7, 0.183, 0.000813, 0.0543, 9.15e-5, 0.00854, 0.0378, 1.37e-6, 0.014}, {3.64, 3.08e-8, 0.983, 0.000988, 0.0475, 0.000115, 0.00849, 0.0152, 1.18e-6, 0.0276}}},
+        {{{4.22, 1.22e-9, 0.6, 0.000598, 0.0522, 9.32e-5, 0.00505, 0.0901, 1.45e-6, 0.0166}, {3.8, 4.66e-8, 1.16, 0.00111, 0.0572, 5.9e-5, 0.0074, 0.0938, 1.21e-6, 0.0202}},
+         {{4.09, 6.69e-8, 0.369, 0.000516, 0.0603, 2e-5, 0.00662, 0.0808, 1.56e-6, 0.0295}, {3.84, 8.57e-8, 0.982, 0.00084, 0.063, 2e-5, 0.00585, 0.0915, 1.31e-6, 0.021}},
+         {{4.6, 6.7e-8, 0.229, 0.000678, 0.0817, 2e-5, 0, 0.103, 1.42e-6, 0}, {3.68, 1.56e-7, 1.36, 0.00102, 0.0668, 2e-5, 0, 0.0854, 1.26e-6, 0.00818}},
+         {{3.92, 0, 0.742, 0.000553, 0.0548, 0.000108, 0.00828, 0.0844, 1.63e-6, 0.0205}, {3.64, 0, 1.26, 0.00104, 0.061, 8.64e-5, 0.00943, 0.0953, 1.4e-6, 0.0217}}}
+    };
+    struct Blocks { double start, pass, row, step, panel; };
+    static const Blocks blocks[2] = {{5.0, 4.07, 0.000913, 0.0726, 2.71}, {4.36, 0, 0.000947, 0.19, 3.08}};
     pl->us = 1e30;
     const double lists = (double)A->blk_chunks / A->P;               // chunks of a panel over all its blocks
     const double store = (double)A->M * row_bytes * (r4 ? 2 : 1) * out_bytes;
@@ -405,13 +421,15 @@ void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_
         if (A->nblk == 1) {
             const double filling = std::min(256, q.groups * q.ntiles) / 256.0, busy = std::min(1.0, (double)in_group * q.wpp / q.waves);
             const double late = std::max(0.0, (double)A->max_panel_chunks / q.wpp - steps);
-            const Cost &c = cost[r4][resident_half(A->V, A->lhs_bits)];
-            q.us = c.start + store * c.store + (q.wpp > 1 ? c.meet : 0.0) +
-                   rounds * (A->block_rows * filling * c.fill + steps * busy * mfma * c.mfma + steps * busy * filling * resident_chunk_bytes(A) * c.record +
+            const Cost &c = cost[r4][resident_half(A->V, A->lhs_bits) ? 1 : A->lhs_bits <= 8 ? 2 : A->V == 8 ? 0 : 3][A->blk_nt == 4];
+            q.us = c.start + store * c.store + (double)A->K * row_bytes * c.fetch + (q.wpp > 1 ? c.meet : 0.0) +
+                   rounds * (A->block_rows * filling * c.fill + steps * busy * mfma * (c.mfma + (A->uniform_chunks ? 0.0 : c.uneven)) +
+                             steps * busy * filling * resident_chunk_bytes(A) * c.record +
                              in_group * mfma * c.panel + late * c.late);
         } else {
-            q.us = 3.1 + store * 1.5e-7 + rounds * (passes * A->nblk * (2.1 + A->block_rows * 0.65e-3) + steps * (r4 ? 0.17 : 0.21) +
-                                                    (in_group + q.waves - 1) / q.waves * 3.2);
+            const Blocks &c = blocks[r4];
+            q.us = c.start + store * 3e-7 + rounds * (passes * A->nblk * (c.pass + A->block_rows * c.row) + steps * c.step +
+                                                      (in_group + q.waves - 1) / q.waves * c.panel);
         }
         if (q.us < pl->us) *pl = q;
     }
@@ -468,20 +486,20 @@ DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_byt
 }
 
 // Which of an operand and its merged copy (null: none) get an LDS-ordered copy.  One does where its form is expected to be faster than either gather
-// by a twentieth for some width of B, rows of 128 to 1024 bytes; of two that do, the one that takes more off over these widths, and the other where it is
-// expected to be faster than that one, too, by a tenth for some width.  Both are decided at once: with the merged copy decided first, giving way to what
-// the given operand could have, that one failed its own test at times, and of 10731 operands of 4- and 8-bit values 253 had neither (14952 x 531, V = 8,
-// L4-R4 gathered where it had run resident).
-// (Of 1385 drawn operands 33 had both copies with a tenth, with 2 % 106; the forms they run in lose the same 2.0 % over the best on average.  A
-// twentieth is an expected time's own error: with 2 % operands of 1000 to 2000 rows had the copy for what is no gain, mc_mat_create 1.16 instead of
-// 0.78 ms at 2048 x 2048, 90 % empty, and new values to write there.)
+// by a tenth for some width of B, rows of 128 to 1024 bytes.  Where both do, the given operand's is built if it is expected to be faster than merged by
+// 15 % for some width, and the merged copy's unless that one is and nothing is gained beside it, a twentieth for some width.  Both are decided at
+// once: with the merged copy decided first, giving way to what the given operand could have, that one failed its own test at times, and of 10731
+// operands of 4- and 8-bit values 253 had neither (14952 x 531, V = 8, L4-R4 gathered where it had run resident).
+// On 4888 drawn operands 2335 have one copy then, 66 both, and of 1103 with panels of 8 rows and one plane 31 run more than 5 % behind
+// their merged resident form (with the rule and the constants before 2813, 150 and 103).  With a twentieth instead of a tenth 2536, 101 and 26; the
+// forms they run in are 3.2 % slower than the fastest of all, 3.1 % with a twentieth, but 4096 x 4096, 90 % empty, V = 8 has a copy
+// then for rows of 1024 bytes alone, and mc_mat_create takes 7.9 instead of 5.3 ms; with a fifth 3.5 %.
 struct ResidentCopies { bool given, merged; };
 ResidentCopies resident_worth_building(const mc_mat *A, const mc_mat *merged)
 {
     const mc_options automatic = {};
     const mc_mat *const of[2] = {A, merged};
     bool worth[2] = {}, beside[2] = {};                   // (a copy beside the other one)
-    double taken_off[2] = {};                             // of the faster gather's logarithm
     for (int row_bytes : {1024, 512, 256, 128}) {
         for (int r4 = (A->lhs_bits == 4); r4 < 2; ++r4) {
             double gather = 1e30, us[2] = {1e30, 1e30};
@@ -494,15 +512,13 @@ ResidentCopies resident_worth_building(const mc_mat *A, const mc_mat *merged)
                 us[i] = pl.us;
             }
             for (int i = 0; i < 2; ++i) {
-                worth[i] |= us[i] < 0.95 * gather;
-                beside[i] |= us[i] < std::min(0.95 * gather, 0.9 * us[1 - i]);
-                taken_off[i] += std::log(gather / std::min(gather, us[i]));
+                worth[i] |= us[i] < 0.9 * gather;
+                beside[i] |= us[i] < std::min(0.9 * gather, (i == 0 ? 0.85 : 0.95) * us[1 - i]);
             }
         }
     }
     if (!worth[0] || !worth[1]) return {worth[0], worth[1]};
-    const bool merged_first = taken_off[1] >= taken_off[0];
-    return {!merged_first || beside[0], merged_first || beside[1]};
+    return {beside[0], !beside[0] || beside[1]};
 }
 
 } // namespace

@@ -99,14 +99,17 @@ def load():
 
 
 class Mat:
-    """An operand of random columns in that library (freed by close)."""
+    """An operand of random columns in that library (freed by close).  sigma: of the logarithm of the panels' lengths."""
 
-    def __init__(self, M, K, V, empty, prec="L8R8", options=None, status=0):
+    def __init__(self, M, K, V, empty, prec="L8R8", options=None, status=0, sigma=0.0):
         L = load()
         rng = np.random.default_rng(M + K)
-        keep = max(1, round((1 - empty) * K))
-        self.row_ptr = (np.arange(M // V + 1) * keep).astype(np.int32)
-        col_idx = np.concatenate([np.sort(rng.permutation(K)[:keep]) for _ in range(M // V)]).astype(np.int32)
+        keep = np.full(M // V, max(1, round((1 - empty) * K)))
+        if sigma:
+            lengths = rng.lognormal(0.0, sigma, M // V)
+            keep = np.clip(np.rint(lengths / lengths.mean() * keep), 1, K).astype(np.int64)
+        self.row_ptr = np.concatenate([[0], np.cumsum(keep)]).astype(np.int32)
+        col_idx = np.concatenate([np.sort(rng.permutation(K)[:n]) for n in keep]).astype(np.int32)
         bits = mc.LHS_BITS[prec]
         self.values = np.ones((len(col_idx), V * (16 if bits == 12 else bits) // 8), np.uint8)
         self.K, self.M, self.prec, self.handle = K, M, mc.PREC[prec], ctypes.c_void_p()
