@@ -651,13 +651,18 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     // Length classes of the panels (V = 8: the attention kernel gives a panel 1, 2, 4 or 8 waves)
     std::vector<int32_t> class_panels;
     for (int b = 0; b <= 4; ++b) A->class_start[b] = 0;
+    for (int b = 0; b < 4; ++b) A->class_chunks[b] = 0;
     if (V == 8 && lay.P > 0) {
+        auto chunks_of = [&](int p) { return (row_ptr[p + 1] - row_ptr[p] + MC_CHUNK - 1) / MC_CHUNK; };
         auto class_of = [&](int p) {
-            const int c = (row_ptr[p + 1] - row_ptr[p] + MC_CHUNK - 1) / MC_CHUNK;
+            const int c = chunks_of(p);
             return c <= 8 ? 0 : (c <= 16 ? 1 : (c <= 32 ? 2 : 3));
         };
         int count[4] = {0, 0, 0, 0};
-        for (int p = 0; p < lay.P; ++p) ++count[class_of(p)];
+        for (int p = 0; p < lay.P; ++p) {
+            ++count[class_of(p)];
+            A->class_chunks[class_of(p)] += chunks_of(p);
+        }
         if ((count[0] > 0) + (count[1] > 0) + (count[2] > 0) + (count[3] > 0) > 1) {
             try {
                 class_panels.resize((size_t)lay.P);
@@ -1588,8 +1593,8 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         const bool fills = dk == tile && tile <= 128; // (the tile of 192 is a padded one)
         const bool pairs = ((fills && short_rows) || tile == 64) && head_stride == dk && heads % 2 == 0 && !(p_bits == 16 && qkv_bits == 4);
         const double avg = mask->P ? (double)(mask->nslots / MC_CHUNK) / mask->P : 0.0;
-        // One launch for the panels in `list` (null: all), none of which has more than max_chunks chunks.
-        auto launch = [&](const int32_t *list, int n_panels, int max_chunks) -> hipError_t {
+        // One launch for the panels in `list` (null: all), none of which has more than max_chunks chunks; mean: of theirs.
+        auto launch = [&](const int32_t *list, int n_panels, int max_chunks, double mean) -> hipError_t {
             f.panel_list = list; f.P = n_panels;
             f.index_bytes = 4 * std::min(mask->nslots, (int64_t)n_panels * max_chunks * MC_CHUNK);
             // a wave keeps at most 8 chunks of scores in registers: longer panels are shared by 2, 4 or 8 waves
@@ -1598,16 +1603,18 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
             if (o.attention_mode == 0) {
                 // Halving the gather requests pays once the launch fills the chip (2048 (panel, head) units and
                 // more: 13.3 against 15.6 us for 4096 of them; 5.0 against 4.7 us for 128).  Smaller launches get
-                // more waves per unit instead, until about 2048 waves are in flight and while every wave still
-                // has a chunk (256 units of 7 chunks: 5.9 us with one wave each, 4.5 us with four; of 3 chunks, dk = 80 - 96, 170 to 438
-                // units 6.0 - 6.9 with two, 5.5 - 6.3 with four, dk = 64 2 % less).
+                // more waves per unit instead, until about 2048 waves are in flight and while at most one of a unit's waves is
+                // without a chunk (256 units of 7 chunks: 5.9 us with one wave each, 4.5 us with four; of 3 chunks, dk = 80 - 96, 170 to 438
+                // units 6.0 - 6.9 with two, 5.5 - 6.3 with four, dk = 64 2 % less).  All by the chunks of this launch's panels: by the mean of all
+                // panels of an unequal mask, whose classes are launched apart, panels of one chunk had four or eight waves and long ones too few.  160 drawn
+                // layers on such masks 1.06x in the mean, 0.95 - 1.38 (2 x 2 heads x 1136, dk = 96, nibbles 15.4 -> 11.1 us).
                 const int64_t units = (int64_t)n_panels * heads * batch;
                 // Two heads, by 240 drawn layers in each form: from 1024 units on where they have 12500 chunks (dk = 64, 1300 to 1700 units of
                 // 13 to 18 chunks 1.03 - 1.16 times as fast, below that 0.9 - 1.06), and shorter heads there, too (8 heads x 3384, dk = 48, 9 chunks 35.7 -> 24.2 us,
                 // 4 x 3992, 12 chunks 24.3 -> 17.3; 64 layers of 1024 to 4096 units 1.07 in the mean), but for tokens of less than 96 bytes, whose
                 // line holds both heads already (0.92 - 1.03), and rows of up to 32 bytes by four waves each (0.94 - 1.08).  Short heads
                 // of 4096 units and more from 10000 chunks on (fewer: 0.95 - 1.0).
-                const double work = (double)units * std::min(avg, (double)max_chunks);
+                const double work = (double)units * mean;
                 const int64_t head_bytes = (int64_t)dk * qkv_bits / 8;
                 const bool long_enough = units >= 1024 && work >= 12500.0;
                 const bool two = fills ? units >= 2048 || long_enough
@@ -1616,13 +1623,13 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 hpg = (pairs && two && wpp < 8) ? 2 : 1;
                 // (Rows of 256 bytes, too, where four waves' stages take half a compute unit's LDS: against 1024 waves in flight 46 drawn layers of
                 // dk = 144 - 192 1.03 times as fast in the mean, up to 1.23.  4096 waves: 0.98, down to 0.73.)
-                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp + 1 <= avg) wpp *= 2;
+                if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp + 1 <= mean) wpp *= 2;
                 // (Eight waves for nine chunks: 225 to 253 units of 9 or 10 1.04 times as fast; 8-bit inputs with 5 to 8 chunks 0.93 - 1.0, nibbles, whose
-                // rows take longer to multiply than to fetch, 1.0 - 1.07 from 5 chunks on.)
-                if (hpg == 1 && wpp == 4 && tile <= 128 && units * 8 <= 2048 && std::min(avg, (double)max_chunks) >= (qkv_bits == 4 ? 5.0 : 9.0)) wpp = 8;
+                // rows take longer to multiply than to fetch, 1.0 - 1.07 from 5 chunks on: three waves without one, too.)
+                if (hpg == 1 && wpp == 4 && tile <= 128 && units * 8 <= 2048 && mean >= (qkv_bits == 4 ? 5.0 : 9.0)) wpp = 8;
                 // (A few more units than SIMDs, 1024, give some of them two waves and most one; of six chunks on, two waves each: 40 layers of 1026 to 1264 units of 6 to 8
                 // chunks 1.0 - 1.18 times as fast, 3 x 3352, dk = 80, 6 chunks 13.9 -> 12.5 us.  Of 3 to 5 chunks 0.95 - 1.08; from 1326 units on 0.8 - 1.04.)
-                if (hpg == 1 && wpp == 1 && tile <= 128 && units <= 1280 && std::min(avg, (double)max_chunks) >= 6.0) wpp = 2;
+                if (hpg == 1 && wpp == 1 && tile <= 128 && units <= 1280 && mean >= 6.0) wpp = 2;
             } else {
                 if (o.attention_mode == 3 && wpp < 2) wpp = 2;
                 if (o.attention_mode == 4 && wpp < 4) wpp = 4;
@@ -1637,10 +1644,10 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         if (o.attention_mode == 0 && mask->d_class_panels && mask->max_panel_chunks > 8 && mask->max_panel_chunks >= 2.0 * avg) {
             for (int b = 0; b < 4; ++b) {
                 const int n = mask->class_start[b + 1] - mask->class_start[b];
-                if (n > 0) MC_HIP(launch(mask->d_class_panels + mask->class_start[b], n, b == 3 ? mask->max_panel_chunks : (8 << b)));
+                if (n > 0) MC_HIP(launch(mask->d_class_panels + mask->class_start[b], n, b == 3 ? mask->max_panel_chunks : (8 << b), (double)mask->class_chunks[b] / n));
             }
         } else {
-            MC_HIP(launch(nullptr, mask->P, mask->max_panel_chunks));
+            MC_HIP(launch(nullptr, mask->P, mask->max_panel_chunks, avg));
         }
         return MC_OK;
     };

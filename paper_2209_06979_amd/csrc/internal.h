@@ -61,6 +61,7 @@ struct mc_mat {
     // hold; class 3 also takes what is longer still.
     int32_t *d_class_panels;   // P panel numbers, class after class
     int class_start[5];        // first entry of each class in d_class_panels; [4] = P
+    int64_t class_chunks[4];   // chunks of each class's panels
     // Merged copy for the SpMM (null when not built): `merge_group` consecutive panels as one panel of
     // V * merge_group rows at the union of their columns (see mc_merge_host); a complete operand of its own
     // (work items, LDS-ordered copy), never merged again.  Its rows may run past M: launches on it pass M as the

@@ -22,13 +22,22 @@ static std::atomic<size_t> limit{~(size_t)0};
 static std::atomic<long> allocations{0};
 static thread_local char called[64] = "";
 static thread_local int detail = 0, variant[2] = {0, 0};
+static thread_local int heads_waves[8][2], n_attention = 0;
 static hipError_t note(const char *what, int d = 0) { strcpy(called, what); detail = d; return hipSuccess; }
+static hipError_t attention(int heads, int waves)
+{
+    if (n_attention < 8) { heads_waves[n_attention][0] = heads; heads_waves[n_attention][1] = waves; }
+    ++n_attention;
+    return note("attention", 10 * heads + waves);
+}
 extern "C" {
 void host_limit(size_t bytes) { limit = bytes; }
 long host_live() { return allocations; }
 const char *host_called() { return called; }
 int host_detail() { return detail; }
 int host_variant(int i) { return variant[i]; }
+int host_attention(int i, int what) { return heads_waves[i][what]; }
+int host_attentions() { const int n = n_attention; n_attention = 0; return n; }
 hipError_t hipMalloc(void **p, size_t n)
 {
     if (n >= limit) return *p = nullptr, hipErrorOutOfMemory;
@@ -64,8 +73,8 @@ hipError_t launch_scores_softmax(const ScoresArgs &, int, int, int, hipStream_t)
 int scores_softmax_max_npad(int, int) { return 4096; }
 hipError_t launch_absmax(const float *, int64_t, float *, hipStream_t) { return note("absmax"); }
 hipError_t launch_quantize(const float *, int64_t, float, int, uint8_t *, hipStream_t) { return note("quantize"); }
-hipError_t launch_attention_fused(const AttnArgs &, int, int, int, int, int, hipStream_t) { return note("attention"); }
-hipError_t launch_attention_fused_padded(const AttnArgs &, int, int, int, int, int, hipStream_t) { return note("attention"); }
+hipError_t launch_attention_fused(const AttnArgs &, int heads, int waves, int, int, int, hipStream_t) { return attention(heads, waves); }
+hipError_t launch_attention_fused_padded(const AttnArgs &, int heads, int waves, int, int, int, hipStream_t) { return attention(heads, waves); }
 int attention_fused_max_vectors() { return 4096; }
 """
 _lib = None
@@ -91,7 +100,7 @@ def load():
         _lib.host_limit.argtypes = [ctypes.c_size_t]
         _lib.mc_mat_create.argtypes, _lib.mc_mat_destroy.argtypes = mc.lib.mc_mat_create.argtypes, [ctypes.c_void_p]
         _lib.mc_mat_destroy.restype = None
-        for name in ("mc_spmm", "mc_spmm_ex", "mc_spmm_form", "mc_spmm_form_us", "mc_mat_set_values_device"):
+        for name in ("mc_spmm", "mc_spmm_ex", "mc_spmm_form", "mc_spmm_form_us", "mc_mat_set_values_device", "mc_sparse_attention_ex"):
             getattr(_lib, name).argtypes = getattr(mc.lib, name).argtypes
         _lib.mc_spmm_form_us.restype = ctypes.c_double
         _lib.mc_set_thread_options.argtypes = _lib.mc_get_thread_options.argtypes = [ctypes.POINTER(mc.Options)]
@@ -143,6 +152,30 @@ class Mat:
         """The tile and the waves of the gathered kernel that a call launches."""
         assert self.run(N, options, ex=True, **kw)[0] == "gather"
         return load().host_variant(0), load().host_variant(1)
+
+    def close(self):
+        load().mc_mat_destroy(self.handle)
+
+
+class Mask:
+    """A mask of panels of 8 rows with `lengths` stored vectors each in that library."""
+
+    def __init__(self, L, lengths):
+        lib = load()
+        self.L, self.handle = L, ctypes.c_void_p()
+        row_ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+        col_idx = np.concatenate([np.arange(n) for n in lengths]).astype(np.int32)
+        assert lib.mc_mat_create(L, L, 8, 0, mc._p32(row_ptr), mc._p32(col_idx), None, None, ctypes.byref(self.handle)) == 0
+
+    def attention(self, batch, heads, dk, p_bits=8, qkv_bits=8, token_major=True, options=None):
+        """(heads, waves) of every fused launch of a layer on this mask."""
+        lib, one = load(), np.zeros(64, np.uint8)
+        at = one.ctypes.data + -one.ctypes.data % 16
+        lib.host_attentions()
+        strides = (heads * self.L * dk, dk, heads * dk) if token_major else (heads * self.L * dk, self.L * dk, dk)
+        assert lib.mc_sparse_attention_ex(at, at, at, batch, heads, self.L, dk, *strides, self.handle, p_bits, qkv_bits, 0.1, 0.1, 0.1, 0.1,
+                                          0, options, at, None, 0, None) == 0
+        return [(lib.host_attention(i, 0), lib.host_attention(i, 1)) for i in range(lib.host_attentions())]
 
     def close(self):
         load().mc_mat_destroy(self.handle)
