@@ -356,8 +356,11 @@ void attention_fused_kernel(AttnArgs a)
     start_pipeline(Vg);
 
     // ---- softmax over row 4*(g&1) + r, in base 2: exp(x - max) = 2^((s - smax) * scale2), the difference exact -----
+    // (Not BIASED: s * scale2 - m2 by one multiply-add, exact but for its rounding and for what m2 = smax * scale2 was rounded by, the same for the
+    // whole row; that is a factor of 2^64 at most, which the sum takes off again, because a scale of 256 leaves the largest scores alone as any larger
+    // one does: without that bound scales from 3e38 / smax on had no probabilities at all.)
     constexpr float LOG2E = 1.4426950408889634f;
-    const float scale2 = a.score_scale * LOG2E * (QB == 4 ? 0.0625f : 1.f);
+    const float scale2 = fminf(a.score_scale * LOG2E * (QB == 4 ? 0.0625f : 1.f), 256.f);
     float top[4], srow[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
