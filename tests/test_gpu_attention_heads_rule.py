@@ -1,5 +1,6 @@
 """The automatic choice of heads per workgroup and waves per head, on both sides of its lines (units of (panel, head), chunks of a
-launch, bytes of a token and of a row; three chunks by four waves), against the CPU oracle and against one head per workgroup."""
+launch, bytes of a token and of a row; three chunks by four waves), against the CPU oracle and against one head per workgroup.  (That a launch has
+the heads and waves that stand beside its sizes is shown on the host, in test_host_attention_rule.)"""
 import numpy as np
 import pytest
 

@@ -40,3 +40,19 @@ def test_a_small_product_of_two_planes():
     A = host.Mat(512, 512, 8, 0.8, "L16R8")
     assert A.variant(128) == (64, 4)
     A.close()
+
+
+@pytest.mark.parametrize("prec", ["L8R8", "L8R4", "L4R4", "L16R8", "L16R4", "L12R4", "L16R16"])
+@pytest.mark.parametrize("merge", [-1, 1])
+def test_the_launch_is_the_pair_with_the_least_expected_time(prec, merge):
+    for M, K, V, empty in SHAPES:
+        A = host.Mat(M, K, V, empty, prec, options=mc.Options(spmm_merge=merge))
+        for row_bytes in (16, 64, 208, 512, 1040):
+            N = row_bytes * 8 // A.rhs
+            us = {}
+            for tile in (64, 128, 256):
+                for waves in (1, 2, 4, 8):
+                    if (tile == 64 or tile < 2 * row_bytes) and not (tile == 256 and A.rhs == 4):  # (256 bytes of nibbles run as 128)
+                        us[tile, waves] = A.us(N, mc.Options(spmm_slab=-1, spmm_merge=merge, spmm_row_tile_bytes=tile, spmm_waves=waves))
+            assert us[A.variant(N, mc.Options(spmm_slab=-1, spmm_merge=merge))] == min(us.values())
+        A.close()
