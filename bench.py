@@ -133,10 +133,14 @@ def main():
     ap.add_argument("--forms", type=int, default=0, metavar="N",
                     help="instead of the step: the SpMM on N drawn operands (all precisions, all sizes, equal and "
                          "unequal panels) in each of its five forms, beside the time that the library's choice expects of it")
+    ap.add_argument("--variants", type=int, default=0, metavar="N",
+                    help="instead of the step: the gathered SpMM on N drawn operands in every tile and number of waves, beside the pair that the library picks")
+    ap.add_argument("--layers", type=int, default=0, metavar="N",
+                    help="instead of the step: the fused attention layer on N drawn layers, automatic and in every mode that pins a form")
     ap.add_argument("--waves", action="store_true",
                     help="instead of the step: the SDDMM's automatic number of waves per panel against every pinned one")
     ap.add_argument("--table", action="store_true",
-                    help="with --sweep / --skew / --shapes / --forms / --waves: print a plain-text table instead of the JSON object")
+                    help="with --sweep / --skew / --shapes / --forms / --variants / --layers / --waves: print a plain-text table instead of the JSON object")
     ap.add_argument("--point", default="",
                     help="instead of the step: one SpMM configuration 'prec:V:sparsity:N:form' (form: gather, lds, merged, merged-lds or auto) at "
                          "4096 x 4096, launched --steps times one by one (for counter and trace collection), e.g. L8R8:2:0.5:512:lds")
@@ -159,9 +163,10 @@ def main():
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
 
-    if args.sweep or args.skew or args.shapes or args.phases or args.forms or args.waves:
+    if args.sweep or args.skew or args.shapes or args.phases or args.forms or args.variants or args.layers or args.waves:
         result = (run_sweep(mc, torch) if args.sweep else run_skew(mc, torch) if args.skew else
                   run_shapes(mc, torch) if args.shapes else run_forms(mc, torch, args.forms) if args.forms else
+                  run_variants(mc, torch, args.variants) if args.variants else run_layers(mc, torch, args.layers) if args.layers else
                   run_waves(mc, torch) if args.waves else run_phases(mc, torch))
         print(as_table(result) if args.table else json.dumps(result))
         return
@@ -634,13 +639,27 @@ def draw_operand(rng):
             return prec, Vv, Ms, Ks, row_bytes, s, sigma, (4, 2)[rng.integers(2)]
 
 
+def drawn_pattern(P, Ks, s, sigma, rng):
+    """Row pointers and columns of P panels."""
+    lengths = np.maximum(1, lognormal_counts(P, max(8, round(Ks * (1 - s))), sigma, Ks, rng))
+    score = rng.random((P, Ks), dtype=np.float32)
+    rank = np.argsort(score, axis=1) if sigma else np.argpartition(score, int(lengths[0]) - 1, axis=1)
+    return (np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32),
+            np.concatenate([np.sort(rank[p, :lengths[p]]) for p in range(P)]).astype(np.int32))
+
+
+def drawn_values(bits, n, Vv, seed):
+    from paper_2209_06979_amd import workloads as wl
+    return (wl.uniform_packed_int4((n, Vv // 2), seed) if bits == 4 else wl.uniform_int8((n, Vv), seed) if bits == 8 else
+            wl.uniform_int16((n, Vv), seed, -2048, 2047))
+
+
 def run_forms(mc, torch, count):
     """The SpMM on drawn operands: each of its five forms -- rows of B gathered per stored vector or resident in LDS, on
     the operand as given or on its merged copy, and the operand with all its columns -- timed beside the time that the library's choice expects of it, and what the
     choice loses over the fastest.  Three copies of everything are visited in turn, as a program's operands alternate (an XCD's L2
     then holds small ones only).  `chunks` / `longest` and their merged counterparts are the operand's chunks of 64 vectors
     and those of its longest panel."""
-    from paper_2209_06979_amd import workloads as wl
     rng = np.random.default_rng(470)
     stream = torch.cuda.Stream()
     pins = {"gather": mc.Options(spmm_slab=-1, spmm_merge=-1), "lds": mc.Options(spmm_slab=1, spmm_merge=-1),
@@ -651,16 +670,11 @@ def run_forms(mc, torch, count):
     with torch.cuda.stream(stream):
         for i in range(count):
             prec, Vv, Ms, Ks, row_bytes, s, sigma, out = draw_operand(rng)
-            P, lhs, rhs = Ms // Vv, mc.LHS_BITS[prec], mc.RHS_BITS[prec]
+            lhs, rhs = mc.LHS_BITS[prec], mc.RHS_BITS[prec]
             N = row_bytes * 8 // rhs
-            lengths = np.maximum(1, lognormal_counts(P, max(8, round(Ks * (1 - s))), sigma, Ks, rng))
-            score = rng.random((P, Ks), dtype=np.float32)
-            rank = np.argsort(score, axis=1) if sigma else np.argpartition(score, int(lengths[0]) - 1, axis=1)
-            rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
-            ci = np.concatenate([np.sort(rank[p, :lengths[p]]) for p in range(P)]).astype(np.int32)
+            rp, ci = drawn_pattern(Ms // Vv, Ks, s, sigma, rng)
             n = len(ci)
-            vals = (wl.uniform_packed_int4((n, Vv // 2), i) if lhs == 4 else wl.uniform_int8((n, Vv), i) if lhs == 8 else
-                    wl.uniform_int16((n, Vv), i, -2048, 2047))
+            vals = drawn_values(lhs, n, Vv, i)
             mc.set_thread_options(mc.Options(spmm_slab=1, spmm_merge=mc.SPMM_DENSE)) # (all copies, whether they would be built or not)
             As = [mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs) for _ in range(3)]
             A = As[0]
@@ -716,6 +730,115 @@ def run_forms(mc, torch, count):
             "library": mc.lib.mc_version().decode(),
             "columns": "<form>_error: median / 9 in 10 / largest error of the expected time, per cent; auto_over_best: mean / 9 in 10 / largest",
             "summary": [dict(panels=k, **summary(v)) for k, v in groups.items() if v], "rows": rows}
+
+
+def run_variants(mc, torch, count):
+    """The gathered SpMM on drawn operands, as given and merged, a third of the 4- and 8-bit ones also with unsigned operands: every tile (bytes of a
+    row of B) by every number of waves per panel, and what the pair that the library picks loses over the fastest and was expected to take."""
+    rng = np.random.default_rng(471)
+    stream = torch.cuda.Stream()
+    rows = []
+    with torch.cuda.stream(stream):
+        for i in range(count):
+            prec, Vv, Ms, Ks, row_bytes, s, sigma, _ = draw_operand(rng)
+            lhs, rhs = mc.LHS_BITS[prec], mc.RHS_BITS[prec]
+            N = row_bytes * 8 // rhs
+            rp, ci = drawn_pattern(Ms // Vv, Ks, s, sigma, rng)
+            vals = drawn_values(lhs, len(ci), Vv, i)
+            mc.set_thread_options(mc.Options(spmm_slab=-1, spmm_merge=1))
+            As = [mc.SparseMatrix(Ms, Ks, Vv, rp, ci, vals, lhs) for _ in range(3)]
+            mc.set_thread_options(None)
+            Bs = [torch.randint(0, 256, (Ks, row_bytes), device="cuda", dtype=torch.uint8) for _ in As]
+            Bs = Bs if rhs == 4 else [B.view(torch.int8 if rhs == 8 else torch.int16) for B in Bs]
+            Cs = [torch.empty((Ms, N), dtype=torch.int32, device="cuda") for _ in As]
+            reps = 45 if len(ci) * row_bytes < 100e6 else 18
+            signs = (False, True) if prec in ("L8R8", "L8R4", "L4R4") and rng.integers(3) == 0 else (False,)
+            for merge, unsigned in [(m, u) for m in (-1, 1) for u in signs]:
+                if merge == 1 and (not As[0].merge_group or (unsigned and As[0].merge_group * Vv > 8)):
+                    continue
+
+                def time_of(o):
+                    return time_graph(torch, stream, [(lambda k=r % 3: mc.spmm(As[k], Bs[k], prec, out=Cs[k], lhs_unsigned=unsigned, rhs_unsigned=unsigned,
+                                                                              options=o)) for r in range(reps)], rounds=3, warm_ms=5.0)
+                us = {}
+                for tile in (64, 128, 256):
+                    for waves in (1, 2, 4, 8):
+                        exists = (tile == 64 or tile < 2 * row_bytes) and not (tile == 256 and (rhs == 4 or unsigned))
+                        us[f"{tile}x{waves}"] = round(time_of(mc.Options(spmm_slab=-1, spmm_merge=merge, spmm_row_tile_bytes=tile, spmm_waves=waves)), 2) if exists else None
+                auto = mc.Options(spmm_slab=-1, spmm_merge=merge)
+                picked = round(time_of(auto), 2)
+                rows.append(dict(prec=prec, V=Vv, M=Ms, K=Ks, row_bytes=row_bytes, empty=s, sigma=sigma, merged=int(merge == 1), unsigned=int(unsigned), **us,
+                                 picked=picked, expected=None if unsigned else round(mc.spmm_form_us(As[0], N, prec, 4, auto), 2),
+                                 over_best=round(picked / min(v for v in us.values() if v), 3)))
+            for X in As:
+                X.close()
+            if i % 20 == 19:
+                print(f"{i + 1} of {count} operands", file=sys.stderr, flush=True)
+
+    def summary(name, some):
+        a = np.sort([x["over_best"] for x in some])
+        e = np.sort([abs(np.log(x["expected"] / x["picked"])) for x in some if x["expected"]])
+        return dict(products=name, count=len(some), over_best=f"{a.mean():.3f} / {a[int(0.9 * (len(a) - 1))]:.3f} / {a[-1]:.3f}",
+                    error=" / ".join(f"{100 * (np.exp(e[int(q * (len(e) - 1))]) - 1):.0f}" for q in (0.5, 0.9, 1.0)) if len(e) else None)
+    groups = {"given": lambda x: not x["merged"] and not x["unsigned"], "merged": lambda x: x["merged"] and not x["unsigned"], "unsigned": lambda x: x["unsigned"]}
+    return {"variants": "gathered SpMM on drawn operands, three copies in turn, back-to-back launches in a graph (median of 3), us; tile x waves",
+            "library": mc.lib.mc_version().decode(), "columns": "over_best: mean / 9 in 10 / largest; error: of the time expected of the pair picked, per cent",
+            "summary": [summary(k, some) for k, f in groups.items() if (some := [x for x in rows if f(x)])], "rows": rows}
+
+
+def run_layers(mc, torch, count):
+    """The fused attention layer on drawn layers, equal and unequal panels: the automatic heads per workgroup and waves per head against the forms that
+    the modes pin, in both layouts (2: one head, waves by the panels' length; 3, 4: at least two, four waves; 5: waves by length; 3 to 5 with
+    two heads per workgroup where tokens hold neighbouring heads)."""
+    rng = np.random.default_rng(472)
+    stream = torch.cuda.Stream()
+    rows = []
+    with torch.cuda.stream(stream):
+        while len(rows) < count:
+            batch, heads = int(rng.choice((1, 1, 1, 2, 4))), int(rng.choice((1, 2, 3, 4, 8)))
+            L = int(np.exp(rng.uniform(np.log(256), np.log(8192))) / 8) * 8
+            qkv_bits = int(rng.choice((8, 8, 8, 4)))
+            dk = int(rng.choice((64, 64, 128, 32, 96) if qkv_bits == 4 else (64, 64, 128, 32, 48, 80, 96)))
+            p_bits, s = int(rng.choice((8, 16))), round(float(rng.uniform(0.5, 0.97)), 3)
+            sigma = round(float(rng.uniform(0.4, 1.4)), 2) if rng.integers(3) == 0 else 0.0
+            if L // 8 * L * (1 - s) * heads * batch * dk * qkv_bits / 8 > 1e9:
+                continue
+            rp, ci = drawn_pattern(L // 8, L, s, sigma, rng)
+            chunks = (np.diff(rp) + 63) // 64
+            if chunks.max() > 64:
+                continue
+            mask = mc.SparseMatrix(L, L, 8, rp, ci)
+            row = dict(batch=batch, heads=heads, L=L, dk=dk, qkv=qkv_bits, p=p_bits, empty=s, sigma=sigma, units=L // 8 * heads * batch,
+                       chunks=round(float(chunks.mean()), 1), longest=int(chunks.max()))
+            for layout in ("token", "head"):
+                w = dk * qkv_bits // 8
+                q, k, v = (torch.randint(-127, 128, (batch, L, heads, w) if layout == "token" else (batch, heads, L, w), device="cuda", dtype=torch.int8) for _ in range(3))
+                if layout == "token":
+                    q, k, v = (t.permute(0, 2, 1, 3) for t in (q, k, v))
+                if qkv_bits == 4:
+                    q, k, v = (t.view(torch.uint8) for t in (q, k, v))
+                out = mc.sparse_attention(q, k, v, mask, 0.02, 0.02, 0.02, 1 / 127, p_bits=p_bits, qkv_bits=qkv_bits)
+                times = {mode: [] for mode in (0, 2, 3, 4, 5)}       # in turn: the form that is timed first reads up to 5 % above the others
+                for _ in range(3):
+                    for mode, t in times.items():
+                        o = mc.Options(attention_mode=mode)
+                        t.append(time_graph(torch, stream, [lambda: mc.sparse_attention(q, k, v, mask, 0.02, 0.02, 0.02, 1 / 127, out=out, p_bits=p_bits,
+                                                                                        qkv_bits=qkv_bits, options=o)] * 20, rounds=3, warm_ms=2.0))
+                us = {mode: float(np.median(t)) for mode, t in times.items()}
+                row.update({f"{layout}_{'auto' if m == 0 else f'mode{m}'}": round(t, 2) for m, t in us.items()})
+                row[f"{layout}_over_best"] = round(us[0] / min(us.values()), 3)
+            rows.append(row)
+            mask.close()
+            if len(rows) % 20 == 0:
+                print(f"{len(rows)} of {count} layers", file=sys.stderr, flush=True)
+    r = {"layers": "fused attention on drawn layers, 20 back-to-back launches in a graph, the forms in turn (median of 3 of 3), us", "library": mc.lib.mc_version().decode()}
+    for layout in ("token", "head"):
+        for name, some in (("equal", [x for x in rows if not x["sigma"]]), ("unequal", [x for x in rows if x["sigma"]])):
+            a = np.sort([x[f"{layout}_over_best"] for x in some])
+            if len(a):
+                r[f"{layout}-major, {name} panels"] = f"{len(a)} layers, over the fastest of the modes: mean {a.mean():.3f}, nine in ten {a[int(0.9 * (len(a) - 1))]:.3f}, largest {a[-1]:.3f}"
+    r["rows"] = rows
+    return r
 
 
 def run_waves(mc, torch):

@@ -583,7 +583,7 @@ int mc_set_softmax_variant(int variant);
  * length alone; 3 / 4 = the fused kernel with at least two / with four waves per (panel, head)
  * whatever the panel length, 5 = waves by panel length alone -- 3, 4 and 5 with two heads per
  * workgroup wherever the layout allows it, whatever the size of the launch.  All give the same
- * result up to fp32 summation order in the softmax.  MC_EINVAL for other values. */
+ * result up to fp32 rounding and summation order in the softmax.  MC_EINVAL for other values. */
 int mc_set_attention_mode(int mode);
 
 #ifdef __cplusplus

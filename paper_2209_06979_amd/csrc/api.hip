@@ -194,8 +194,8 @@ constexpr GatherAtOnce gather_at_once_all()
 // everything in turn; then scaled to the times of the variants picked (the least of several expected times is 3 - 5 % too low).
 // On 843 others, given / merged: the time of the variant picked is off by 7.0 / 6.4 % in the median and by 17 % in nine cases of ten, and that
 // variant is 2.7 / 3.1 % slower than the fastest of the eight to twelve on average, by 11 % or less in nine cases of ten, by 57 % at worst (without the staged
-// bytes, B and the operand's values, as fitted before, 9.7 / 8.5 %, 24 % and 2.9 / 3.7 %; L12-R4, 1184 x 5592, unequal panels, gathered in 21 us where 15 were
-// expected).  Unsigned ones, 820 of both sets: 2.4 %.
+// bytes, B and the operand's values, as fitted before, 9.7 / 8.5 %, 24 % and 2.9 / 3.7 %); unsigned ones, 820 of both sets, 2.4 %.  (bench.py --variants times them all.)
+// Still too low where a few long panels gather from all over B: L12-R4, 1184 x 5592, lengths from 1 to 88 chunks, rows of 208 bytes 21 us where 16 are expected.
 // lhs_bits: width of the sparse operand's values in this launch (a mask carries none of its own).  items: the launch takes the operand's
 // work items.  stages: chunks that the launch may have in flight (SpmmArgs).  unsigned_ops: the kernel for unsigned operands, which has one in flight and no
 // tiles of 256 bytes.
@@ -1016,8 +1016,8 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, in
         const DensePlan d = plan_dense(A->M, A->K, A->lhs_bits, row_bytes, r4, out_bytes, dense_tile(o));
         if (d.tile >= 0) {
             f.dense = d.tile;
-            // (its expected times and the others' were fitted apart, and where several of theirs compete the least is too low: with 3 % off, of
-            // 1800 drawn operands the form picked is 1.6 % slower than the fastest on average, with 3 % on 1.9 %)
+            // (its expected times and the others' were fitted apart, and where several of theirs compete the least is too low: with 3 % off the form and
+            // variant picked for 843 drawn operands are 3.25 % slower than the fastest on average, with nothing 3.28 %, with 3 % on 3.36 %)
             f.plan.us = d.us;
             best = dense_mode(o) == 1 ? 0.0 : 0.97 * d.us;
         }
@@ -1607,7 +1607,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 // without a chunk (256 units of 7 chunks: 5.9 us with one wave each, 4.5 us with four; of 3 chunks, dk = 80 - 96, 170 to 438
                 // units 6.0 - 6.9 with two, 5.5 - 6.3 with four, dk = 64 2 % less).  All by the chunks of this launch's panels: by the mean of all
                 // panels of an unequal mask, whose classes are launched apart, panels of one chunk had four or eight waves and long ones too few.  160 drawn
-                // layers on such masks 1.06x in the mean, 0.95 - 1.38 (2 x 2 heads x 1136, dk = 96, nibbles 15.4 -> 11.1 us).
+                // layers on such masks 1.06x in the mean, 0.95 - 1.38 (2 x 2 heads x 1136, dk = 96, nibbles 15.4 -> 11.1 us).  (bench.py --layers times the forms.)
                 const int64_t units = (int64_t)n_panels * heads * batch;
                 // Two heads, by 240 drawn layers in each form: from 1024 units on where they have 12500 chunks (dk = 64, 1300 to 1700 units of
                 // 13 to 18 chunks 1.03 - 1.16 times as fast, below that 0.9 - 1.06), and shorter heads there, too (8 heads x 3384, dk = 48, 9 chunks 35.7 -> 24.2 us,

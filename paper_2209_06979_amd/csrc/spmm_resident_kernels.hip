@@ -25,8 +25,10 @@
 // 10844 x 838, V = 4, L16-R4, N = 128 (short streams): 10.6 -> 8.7; whole calls of the first case 33.2 -> 29.9.
 // (8-byte stores by all lanes in the fp16 epilogue: 34.2; rows of B requested two or three steps ahead, sixteen chunks' records
 // ahead, ordinary stores instead of streaming ones: within 2 % either way; records of two chunks for full requests: up to 1.05x as long.)
-// Against the gather form, on the operand as given / merged: 4096 x 4096, half empty, V = 2, N = 512 50.6 / 20.3 against 103.8 / 30.1 (calls take
-// the form of spmm_dense_kernels.hip there, 15.4); 3004 x 2900, 85 % empty, V = 4, unequal panels, 16 x 8 bit 10.1 - 11.1 / 10.1 - 10.6 against 11.9 / 12.2.
+// Against the gather form, on the operand as given / merged: 4096 x 4096, half empty, V = 2, N = 512 42.4 / 20.7 against 104.8 / 28.4 (calls take
+// the form of spmm_dense_kernels.hip there, 15.4); 3004 x 2900, 85 % empty, V = 4, unequal panels, 16 x 8 bit 9.8 / 10.2 against 12.6 / 14.3.
+// Against a record per chunk and whole turns, the calls that lost: L4-R4, 15240 x 592, V = 8, unequal panels, N = 1024, fp16 26.6 -> 29.0 (its gather 24.4); L16-R8,
+// 12822 x 988, V = 2, N = 128 13.1 -> 13.5 (on all columns 10.3).
 // Three things keep the LDS reads at their full rate (190 bytes per clock and compute
 // unit measured, random rows reach 81):
 //   - the LDS image is [row / 16][16-byte segment][row % 16]: a segment of 16 consecutive rows covers all banks once,
