@@ -184,17 +184,20 @@ constexpr GatherAtOnce gather_at_once_all()
     return g;
 }
 
-// Gathered: the tile and the waves with the least expected time.  Launch and start; the staged bytes (padded slots and the unused part of a last tile
-// included); the 128-byte lines that rows touch, each tile by itself, with rows at all multiples of their length; B, which every XCD fetches for itself,
-// and the operand's values, which every tile reads again; the stores; the waves; the chunks of a wave, one after the other, at an even share; those that
-// the longest unit's waves still have then; the launch that clears rows when panels are cut into items; and a last turn of workgroups that
-// leaves compute units idle.  What each costs goes by the width of B, by the tile, by whether A has two planes or panels of 16 rows, and for
-// unsigned operands by the width of B.  Fitted (non-negative least squares on the relative error, a variant counting by how near it is to the
-// fastest of its operand) to every tile and number of waves on 4888 drawn operands (sizes as at plan_slab), given and merged, three copies of
-// everything in turn; then scaled to the times of the variants picked (the least of several expected times is 3 - 5 % too low).
-// On 843 others, given / merged: the time of the variant picked is off by 7.0 / 6.4 % in the median and by 17 % in nine cases of ten, and that
-// variant is 2.7 / 3.1 % slower than the fastest of the eight to twelve on average, by 11 % or less in nine cases of ten, by 57 % at worst (without the staged
-// bytes, B and the operand's values, as fitted before, 9.7 / 8.5 %, 24 % and 2.9 / 3.7 %); unsigned ones, 820 of both sets, 2.4 %.  (bench.py --variants times them all.)
+// Gathered: the tile and the waves with the least expected time.  Launch and start, later with one chunk in flight; the launch that clears rows when panels
+// are cut into items; the staged bytes (padded slots and the unused part of a last tile included); the 128-byte lines that rows touch, each tile by
+// itself, with rows at all multiples of their length; B, which every XCD fetches for itself, and the operand's values, which every tile reads again; the
+// stores; the waves, each by itself and as one of a workgroup's that meet; the chunks of a wave, one after the other, at an even share; those that
+// the longest unit's waves still have then; and a last turn of workgroups that leaves compute units idle.  What each costs goes by the width of B, by the
+// tile, by whether A has two planes or panels of 16 rows, and for unsigned operands by the width of B.  Fitted (least squares on the logarithm, nothing
+// below zero, a variant counting by how near it is to the fastest of its operand) to every tile and number of waves on 7888 drawn operands (sizes
+// as at plan_slab), given and merged, three copies of everything in turn; then scaled to the times of the variants picked (the least of
+// several expected times is 1 - 3 % too low).
+// On 2280 others, given / merged: the time of the variant picked is off by 6.8 / 6.0 % in the median and by 16 % in nine cases of ten, and that variant is
+// 2.6 % slower than the fastest of the eight to twelve on average, 0.9 % below 3.6 us and up to 64 panels, by 10 % or less in nine cases of ten, by
+// 62 % at worst; unsigned ones 2.0 %.  Without the waves that meet and the one chunk in flight 2.7 / 3.1 %, 1.5 and 1.5 %; without the staged bytes, B and
+// the operand's values either, as fitted before, 2.9 / 3.7 %, and off by 9.7 / 8.5 % and 24 %.  (bench.py --variants times them all.)
+// As the root of the sum of the squares of what is moved and what a wave waits for 1.9 / 2.1 %, 0.9 and 1.1 %, but a call takes 20 ns longer to decide.
 // Still too low where a few long panels gather from all over B: L12-R4, 1184 x 5592, lengths from 1 to 88 chunks, rows of 208 bytes 21 us where 16 are expected.
 // lhs_bits: width of the sparse operand's values in this launch (a mask carries none of its own).  items: the launch takes the operand's
 // work items.  stages: chunks that the launch may have in flight (SpmmArgs).  unsigned_ops: the kernel for unsigned operands, which has one in flight and no
@@ -202,17 +205,17 @@ constexpr GatherAtOnce gather_at_once_all()
 GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int out_bytes, int batch, bool items, int stages, bool unsigned_ops,
                        const mc_options &o)
 {
-    struct Cost { double start, byte, line, store, wave, chunk, late, items, last, fetch, operand; };
+    struct Cost { double start, items, meet, one, last, byte, line, store, wave, fetch, operand, chunk, late; };
     static const Cost cost[9][3] = {
-        {{2.44, 1.26e-08, 2.43e-08, 4.84e-08, 0.00028, 0.349, 0.456, 1.44, 0.557, 2.84e-07, 1.76e-08}, {2.83, 5.73e-08, 1.27e-08, 1.13e-07, 0.000235, 0.461, 0.786, 1.15, 1.24, 7.64e-08, 0}},
-        {{3.07, 2.47e-08, 2.3e-08, 8.29e-09, 0.000466, 0.453, 0.468, 0, 1.38, 2.93e-07, 0}, {3.53, 5.44e-08, 1.49e-08, 8.77e-08, 0.000326, 0.734, 0.798, 0, 2.39, 1.06e-07, 0}},
-        {{2.4, 0, 2.29e-08, 6.51e-09, 0.000325, 0.368, 0.456, 1.68, 0.558, 3.76e-07, 1.03e-07}, {2.7, 3.08e-08, 1.13e-08, 1.14e-07, 0.000332, 0.675, 0.774, 1.48, 1.47, 1.9e-07, 4.52e-08}},
-        {{2.13, 0, 2.38e-08, 0, 0.000208, 0.201, 0.304, 2.01, 0.405, 3.87e-07, 1.35e-07}, {2.15, 1.87e-08, 1.6e-08, 1.89e-08, 0.000282, 0.364, 0.547, 1.68, 1.03, 2.81e-07, 1.76e-07}, {2.35, 2.69e-08, 6e-09, 1.05e-07, 0.00022, 0.565, 0.807, 2.22, 2.62, 3.92e-07, 2.57e-07}},
-        {{2.59, 3.8e-09, 3.38e-08, 0, 0.000324, 0.276, 0.317, 0, 1.07, 4.07e-07, 0}, {2.59, 0, 1.75e-08, 5.72e-09, 0.0003, 0.539, 0.608, 0, 2.33, 4.04e-07, 2.48e-07}, {3.38, 2.14e-08, 1.54e-08, 4.55e-08, 0.000297, 0.811, 0.793, 0, 4.96, 5.02e-07, 0}},
-        {{2.12, 0, 2.37e-08, 0, 0.000204, 0.226, 0.313, 2.17, 0.491, 4.17e-07, 9.92e-08}, {2.08, 1.25e-08, 1.87e-08, 5.6e-08, 0.000247, 0.448, 0.617, 3.11, 1.19, 3e-07, 1.09e-07}, {2.48, 1.55e-08, 1.51e-08, 9.49e-08, 0.000216, 0.649, 0.831, 3.12, 3.24, 3.56e-07, 1.33e-07}},
-        {{2.27, 0, 2.32e-08, 0, 0.000262, 0.29, 0.394, 2.22, 0.685, 3.07e-07, 9.67e-08}, {2.26, 1.31e-08, 1.86e-08, 4.02e-08, 0.000308, 0.526, 0.665, 1.72, 1.48, 2.76e-07, 1.03e-07}, {2.47, 1.87e-08, 1.15e-08, 1.89e-07, 0.000306, 0.845, 0.974, 0.388, 3.43, 3.82e-07, 8.31e-08}},
-        {{2.68, 1.1e-08, 2.35e-08, 5.4e-08, 0.000292, 0.398, 0.48, 1.63, 0.363, 3.67e-07, 2.66e-08}, {3.12, 3.23e-08, 1.2e-08, 1.25e-07, 0.000264, 0.737, 0.801, 0.938, 2.17, 1.73e-07, 0}},
-        {{2.49, 0, 2.38e-08, 0, 0.000174, 0.27, 0.348, 1.98, 0.272, 4.89e-07, 1.44e-07}, {2.43, 1.58e-08, 1.36e-08, 0, 0.00042, 0.561, 0.606, 1.47, 0.74, 4.07e-07, 1.74e-07}}
+        {{2.15, 1.61, 0.0416, 0.00629, 0.473, 1.42e-8, 2.16e-8, 6.16e-8, 0.000289, 4e-7, 6.04e-9, 0.401, 0.473}, {2.68, 1.29, 0, 0.744, 1.24, 5.78e-8, 8.86e-9, 1.2e-7, 0.000294, 1.16e-7, 0, 0.516, 0.72}},
+        {{2.48, 1.04, 0.0861, 0, 1.25, 2.4e-8, 2.15e-8, 3.53e-8, 0.000418, 4.25e-7, 0, 0.485, 0.475}, {3.36, 2.35, 0, 0.104, 2.25, 6.11e-8, 6.39e-9, 9.03e-8, 0.000325, 2.63e-7, 0, 0.766, 0.756}},
+        {{2.18, 1.63, 0.0296, 0, 0.448, 0, 2.17e-8, 2e-8, 0.000321, 4.96e-7, 1.03e-7, 0.39, 0.447}, {2.61, 1.54, 0, 0.364, 1.52, 2.93e-8, 1.02e-8, 1.25e-7, 0.000365, 2.57e-7, 3.77e-8, 0.687, 0.73}},
+        {{1.82, 1.97, 0.0489, 0, 0.285, 0, 2.37e-8, 0, 0.000224, 5.37e-7, 1.16e-7, 0.242, 0.309}, {2.05, 1.57, 0, 0.412, 1.02, 1.7e-8, 1.47e-8, 5.38e-8, 0.000306, 4.41e-7, 1.44e-7, 0.375, 0.508}, {2.17, 1.51, 0, 0.809, 2.87, 2.26e-8, 7.97e-9, 1.82e-7, 0.000242, 4.77e-7, 1.26e-7, 0.591, 0.718}},
+        {{1.98, 4.67, 0.092, 0.000356, 0.858, 1.45e-8, 2.73e-8, 5.89e-10, 0.000312, 5.82e-7, 0, 0.309, 0.319}, {2.19, 2.61, 0.0375, 0.45, 2.23, 2.07e-8, 1.58e-8, 5.05e-8, 0.000303, 6.42e-7, 4.13e-8, 0.546, 0.514}, {2.95, 2.34, 0, 0.64, 4.47, 1.66e-8, 1.12e-8, 6.9e-8, 0.000365, 7.49e-7, 6.05e-8, 0.787, 0.712}},
+        {{1.75, 2.51, 0.0552, 0, 0.396, 0, 2.34e-8, 0, 0.000218, 5.93e-7, 9.71e-8, 0.27, 0.331}, {1.93, 2.27, 0, 0.586, 1.15, 1.01e-8, 1.8e-8, 5.82e-8, 0.000284, 5.39e-7, 9.84e-8, 0.459, 0.565}, {2.26, 2.59, 0, 0.816, 3.12, 1.74e-8, 1.08e-8, 1.15e-7, 0.000247, 4.51e-7, 9.92e-8, 0.664, 0.769}},
+        {{1.85, 1.76, 0.0719, 0, 0.393, 0, 2.26e-8, 0, 0.000279, 5.21e-7, 8.87e-8, 0.334, 0.411}, {2.16, 1.44, 0, 0.489, 1.34, 1.06e-8, 1.78e-8, 7.51e-8, 0.000367, 4.33e-7, 8.67e-8, 0.529, 0.618}, {2.34, 0.921, 0, 0.717, 3.3, 2.02e-8, 9.4e-9, 3.05e-7, 0.00034, 3.37e-7, 2.17e-8, 0.844, 0.876}},
+        {{2.45, 1.49, 0.0343, 0, 0.323, 1.26e-8, 2.19e-8, 6.71e-8, 0.000287, 4.53e-7, 1.23e-8, 0.436, 0.484}, {3.09, 0.878, 0, 0, 2.12, 3.18e-8, 1.11e-8, 1.23e-7, 0.000282, 2.13e-7, 0, 0.77, 0.792}},
+        {{2.09, 1.85, 0.0729, 0, 0.179, 0, 2.43e-8, 0, 0.000183, 5.84e-7, 1.21e-7, 0.322, 0.367}, {2.29, 1.54, 0.0251, 0, 0.615, 1.44e-8, 1.4e-8, 0, 0.000431, 5.8e-7, 1.57e-7, 0.58, 0.603}}
     };
     static constexpr GatherAtOnce at_once = gather_at_once_all();
     const bool r4 = rb == 4, wide = !r4 && !unsigned_ops, two_stages = stages == 2 && !unsigned_ops;
@@ -228,20 +231,21 @@ GatherPlan plan_gather(const mc_mat *A, int lhs_bits, int row_bytes, int rb, int
         const int bnb = 64 << t;
         if (o.spmm_row_tile_bytes ? std::min(o.spmm_row_tile_bytes, wide ? 256 : 128) != bnb : bnb > 64 && bnb >= 2 * row_bytes) continue;
         const Cost &c = costs[t];
-        int unit = std::min(bnb, 128);                    // rows start at multiples of this, tiles too
-        while (row_bytes & (unit - 1)) unit >>= 1;
+        const int unit = std::min({bnb, 128, row_bytes & -row_bytes}); // rows start at multiples of this, tiles too
         const int tiles = (row_bytes + bnb - 1) >> (6 + t);
         const double groups = std::max(1.0, units * tiles), steps = chunks * tiles;
         const double fixed = c.start + steps * MC_CHUNK * (bnb * c.byte + slot_bytes * c.operand) + lines * (row_bytes + tiles * (128 - unit)) * c.line +
                              stored * c.store + fetch * c.fetch + (items ? c.items : 0.0);
+        const double wave = groups * c.wave + c.meet;
         for (int w = 0; w < 4; ++w) {
             if (o.spmm_waves && o.spmm_waves != 1 << w) continue;
             const auto *fits = at_once.with[r4][t][unsigned_ops ? 2 : 0] + w, *two = at_once.with[r4][t][1] + w;
             if (!o.spmm_waves && fits->waves != w) break;
             // two chunks in flight where no wave has more (the launcher's rule, with the waves it then allows)
-            if (two_stages && (longest + (1 << two->waves) - 1) >> two->waves <= SPMM_PIPE_CHUNKS) fits = two;
+            const bool pipelined = two_stages && (longest + (1 << two->waves) - 1) >> two->waves <= SPMM_PIPE_CHUNKS;
+            if (pipelined) fits = two;
             const double part = PART[fits->waves];
-            double us = fixed + groups * (1 << w) * c.wave, share = per_unit * part;
+            double us = fixed + (1 << w) * wave + (pipelined ? 0.0 : c.one), share = per_unit * part;
             if (groups > fits->n) {
                 const double turns = groups * fits->part;
                 const int64_t whole = (int64_t)turns;
@@ -367,11 +371,11 @@ int64_t resident_records(const mc_mat *A) { return (A->blk_chunks + rec_chunks(A
 
 // Expected times in us of the resident form, fitted (least squares on the relative error, no constant below zero, a byte of a record above it: left
 // free, it came out as nothing for records of two chunks and nibbles of B, and of 88 drawn operands of panels of 8 rows seven ran as given, 1.07 - 1.25 times
-// as long as merged) to 4888 drawn operands: all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B of 32 .. 1024 bytes,
-// two in three of them of round length, half to 97 % empty, a quarter with panels of unequal length.  Timed with three copies of everything in turn, as a
-// program's operands alternate.  On 843 others a resident time is off by 6 % in the median and by 16 % in nine cases of ten (in blocks: 13 %, 30 %), and
-// the form, tile and waves picked together are 3.1 % slower than the fastest of all on average, by 10 % or less in nine cases of ten, by 81 % at worst
-// (with the constants and the copies before: 4.1 %, 14 %, 81 %).
+// as long as merged) to 7888 drawn operands: all precisions, V = 2 / 4 / 8 and merged, 256 .. 16000 rows, 512 .. 8192 columns, rows of B of 32 .. 1024 bytes
+// and more, two in five of them of round length, half to 98 % empty, a quarter with panels of unequal length.  Timed with three copies of everything in turn, as a
+// program's operands alternate.  On 2280 others a resident time is off by 6 % in the median and by 14 % in nine cases of ten (in blocks: 12 %, 30 %), and
+// the form, tile and waves picked together are 2.8 % slower than the fastest of all on average, by 10 % or less in nine cases of ten, by 81 % at worst
+// (with the constants and the copies before: 3.5 %, 12 %, 81 %).
 // Resident, all of B's rows at once: launch and start; the fill, a line of B per row, by how many workgroups there are to fill; per
 // step of a wave one part per MFMA and one per byte of a chunk's part of a record, both by how many of the sixteen waves have panels; the epilogues; the stores;
 // B, which every XCD fetches for itself; waves that share a panel meet; and the steps that the longest panel's waves still have when an even share would be
@@ -383,14 +387,14 @@ void plan_slab(const mc_mat *A, int row_bytes, bool r4, int out_bytes, const mc_
     struct Cost { double start, store, meet, fill, mfma, record, panel, late, fetch, uneven; };
     // (two planes of 8 rows; half requests; panels of 16 rows; two planes of fewer rows; each in tiles of 32 and of 64 bytes)
     static const Cost cost[2][4][2] = {
-        {{{3.72, 1.07e-7, 0.503, 0.000767, 0.0552, 6.77e-5, 0, 0.0414, 1.3e-6, 0.0203}, {3.77, 8.37e-8, 1.02, 0.00109, 0.056, 3.19e-5, 0.00528, 0.00978, 1.27e-6, 0.0212}},
-         {{3.79, 3.01e-8, 0.215, 0.000461, 0.0443, 6.68e-5, 0.00807, 0.0411, 1.43e-6, 0.0224}, {3.34, 7.28e-8, 0.853, 0.00103, 0.0567, 2e-5, 0.00598, 0.0404, 1.16e-6, 0.0217}},
-         {{3.77, 9.42e-8, 0.625, 0.000746, 0.074, 4.17e-5, 0, 0.0323, 1.27e-6, 0.012}, {3.61, 1.03e-7, 1.25, 0.00125, 0.0752, 2.64e-5, 0, 0.0631, 1.04e-6, 0.00624}},
-         {{3.07, 1.15e-7, 0.183, 0.000813, 0.0543, 9.15e-5, 0.00854, 0.0378, 1.37e-6, 0.014}, {3.64, 3.08e-8, 0.983, 0.000988, 0.0475, 0.000115, 0.00849, 0.0152, 1.18e-6, 0.0276}}},
-        {{{4.22, 1.22e-9, 0.6, 0.000598, 0.0522, 9.32e-5, 0.00505, 0.0901, 1.45e-6, 0.0166}, {3.8, 4.66e-8, 1.16, 0.00111, 0.0572, 5.9e-5, 0.0074, 0.0938, 1.21e-6, 0.0202}},
-         {{4.09, 6.69e-8, 0.369, 0.000516, 0.0603, 2e-5, 0.00662, 0.0808, 1.56e-6, 0.0295}, {3.84, 8.57e-8, 0.982, 0.00084, 0.063, 2e-5, 0.00585, 0.0915, 1.31e-6, 0.021}},
-         {{4.6, 6.7e-8, 0.229, 0.000678, 0.0817, 2e-5, 0, 0.103, 1.42e-6, 0}, {3.68, 1.56e-7, 1.36, 0.00102, 0.0668, 2e-5, 0, 0.0854, 1.26e-6, 0.00818}},
-         {{3.92, 0, 0.742, 0.000553, 0.0548, 0.000108, 0.00828, 0.0844, 1.63e-6, 0.0205}, {3.64, 0, 1.26, 0.00104, 0.061, 8.64e-5, 0.00943, 0.0953, 1.4e-6, 0.0217}}}
+        {{{3.51, 1.03e-7, 0.714, 0.000757, 0.0558, 6.69e-5, 0.00322, 0.0443, 1.31e-6, 0.0203}, {3.7, 6.19e-8, 1.05, 0.00104, 0.0562, 4.71e-5, 0.00708, 0.0204, 1.07e-6, 0.0152}},
+         {{3.56, 1.16e-8, 0.266, 0.000547, 0.0428, 8.36e-5, 0.00798, 0.0398, 1.4e-6, 0.0213}, {3.36, 5.59e-8, 0.884, 0.000968, 0.053, 4.41e-5, 0.00563, 0.027, 1.07e-6, 0.02}},
+         {{3.68, 7.89e-8, 0.598, 0.000786, 0.0805, 2.65e-5, 0, 0.0367, 1.24e-6, 0.016}, {3.71, 1.09e-7, 1.16, 0.00106, 0.0628, 4.71e-5, 0, 0.0365, 9.17e-7, 0.0107}},
+         {{3.33, 1.12e-7, 0.402, 0.000676, 0.0616, 7.5e-5, 0.00823, 0.046, 1.33e-6, 0.0128}, {3.62, 0, 0.991, 0.000934, 0.0408, 0.000148, 0.00946, 0.0253, 1.11e-6, 0.0198}}},
+        {{{4.39, 3.88e-8, 0.355, 0.000621, 0.0533, 8.35e-5, 0.00178, 0.088, 1.5e-6, 0.0173}, {3.76, 4.69e-8, 1.2, 0.000944, 0.0603, 6.15e-5, 0.00677, 0.104, 1.35e-6, 0.0189}},
+         {{3.95, 7.55e-8, 0.407, 0.000489, 0.0621, 2.4e-5, 0.00484, 0.0772, 1.73e-6, 0.0328}, {3.86, 8.29e-8, 1.02, 0.000662, 0.0641, 2e-5, 0.00585, 0.0876, 1.41e-6, 0.0217}},
+         {{4.49, 6.56e-8, 0.218, 0.000625, 0.0851, 2e-5, 0, 0.0929, 1.59e-6, 0}, {3.77, 1.48e-7, 1.29, 0.000839, 0.0686, 2e-5, 0, 0.0881, 1.4e-6, 0.00798}},
+         {{3.76, 0, 0.775, 0.00056, 0.0549, 0.000101, 0.0084, 0.082, 1.75e-6, 0.0243}, {3.59, 0, 1.33, 0.000837, 0.0624, 8.89e-5, 0.00898, 0.0974, 1.67e-6, 0.0243}}}
     };
     struct Blocks { double start, pass, row, step, panel; };
     static const Blocks blocks[2] = {{5.0, 4.07, 0.000913, 0.0726, 2.71}, {4.36, 0, 0.000947, 0.19, 3.08}};
@@ -486,14 +490,14 @@ DensePlan plan_dense(int M, int K, int bits, int row_bytes, bool r4, int out_byt
 }
 
 // Which of an operand and its merged copy (null: none) get an LDS-ordered copy.  One does where its form is expected to be faster than either gather
-// by a tenth for some width of B, rows of 128 to 1024 bytes.  Where both do, the given operand's is built if it is expected to be faster than merged by
-// 15 % for some width, and the merged copy's unless that one is and nothing is gained beside it, a twentieth for some width.  Both are decided at
-// once: with the merged copy decided first, giving way to what the given operand could have, that one failed its own test at times, and of 10731
-// operands of 4- and 8-bit values 253 had neither (14952 x 531, V = 8, L4-R4 gathered where it had run resident).
-// On 4888 drawn operands 2335 have one copy then, 66 both, and of 1103 with panels of 8 rows and one plane 31 run more than 5 % behind
-// their merged resident form (with the rule and the constants before 2813, 150 and 103).  With a twentieth instead of a tenth 2536, 101 and 26; the
-// forms they run in are 3.2 % slower than the fastest of all, 3.1 % with a twentieth, but 4096 x 4096, 90 % empty, V = 8 has a copy
-// then for rows of 1024 bytes alone, and mc_mat_create takes 7.9 instead of 5.3 ms; with a fifth 3.5 %.
+// by a twentieth, an expected time's own error, for some width of B, rows of 128 to 1024 bytes.  Where both do, the given operand's is built if it is
+// expected to be faster than merged by 15 % for some width, and the merged copy's unless that one is and nothing is gained beside it, a twentieth for
+// some width.  Both are decided at once: with the merged copy decided first, giving way to what the given operand could have, that one failed its
+// own test at times, and of 10731 operands of 4- and 8-bit values 253 had neither (14952 x 531, V = 8, L4-R4 gathered where it had run resident).
+// Of 2280 drawn operands 1225 have one copy then, 38 both, and of 518 with panels of 8 rows and one plane 14 run more than 5 % behind
+// their merged resident form (with the rule and the constants before 1338, 70 and 34).
+// (2 % over the gathers: operands of 1000 to 2000 rows had the copy for what is no gain, mc_mat_create 1.16 instead of 0.78 ms at
+// 2048 x 2048, 90 % empty, and new values to write there.)
 struct ResidentCopies { bool given, merged; };
 ResidentCopies resident_worth_building(const mc_mat *A, const mc_mat *merged)
 {
@@ -512,8 +516,8 @@ ResidentCopies resident_worth_building(const mc_mat *A, const mc_mat *merged)
                 us[i] = pl.us;
             }
             for (int i = 0; i < 2; ++i) {
-                worth[i] |= us[i] < 0.9 * gather;
-                beside[i] |= us[i] < std::min(0.9 * gather, (i == 0 ? 0.85 : 0.95) * us[1 - i]);
+                worth[i] |= us[i] < 0.95 * gather;
+                beside[i] |= us[i] < std::min(0.95 * gather, (i == 0 ? 0.85 : 0.95) * us[1 - i]);
             }
         }
     }
@@ -1017,7 +1021,7 @@ SpmmForm spmm_form(const mc_mat *A, int row_bytes, int64_t ldb_bytes, int rb, in
         if (d.tile >= 0) {
             f.dense = d.tile;
             // (its expected times and the others' were fitted apart, and where several of theirs compete the least is too low: with 3 % off the form and
-            // variant picked for 843 drawn operands are 3.25 % slower than the fastest on average, with nothing 3.28 %, with 3 % on 3.36 %)
+            // variant picked for 1437 drawn operands are 2.82 % slower than the fastest on average, with nothing 2.89 %, with 3 % on 2.93 %)
             f.plan.us = d.us;
             best = dense_mode(o) == 1 ? 0.0 : 0.97 * d.us;
         }

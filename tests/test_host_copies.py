@@ -12,7 +12,7 @@ LDS, MERGED_LDS = mc.Options(spmm_slab=1, spmm_merge=-1), mc.Options(spmm_slab=1
                                               (16384, 4096, 8, 0.9, "L8R8"), (9608, 4339, 8, 0.68, "L8R8"), (520, 700, 8, 0.9, "L8R8"), (4096, 640, 8, 0.5, "L16R8"),
                                               (4096, 640, 4, 0.5, "L16R8"), (9600, 6400, 8, 0.7, "L4R4"), (6000, 7000, 8, 0.6, "L8R8"), (4800, 5600, 4, 0.7, "L8R8")])
 def test_a_resident_form_that_is_worth_a_copy_has_one(M, K, V, empty, prec):
-    """One of the two copies is there where one of them is expected to be a tenth faster than both gathers at some width, none otherwise,
+    """One of the two copies is there where one of them is expected to be a twentieth faster than both gathers at some width, none otherwise,
     and of two the given operand's where it gains 15 % over the merged one, the merged one unless nothing is gained beside that."""
     bits = mc.LHS_BITS[prec]
     rhs = (4,) if bits == 4 else (8, 4)
@@ -28,8 +28,8 @@ def test_a_resident_form_that_is_worth_a_copy_has_one(M, K, V, empty, prec):
             us = [full.us(N, LDS), full.us(N, MERGED_LDS) if merged else 1e30]
             gather = min(full.us(N, GATHER), full.us(N, MERGED_GATHER) if merged else 1e30)
             for i in (0, 1):
-                worth[i] |= us[i] < 0.9 * gather
-                beside[i] |= us[i] < min(0.9 * gather, (0.85, 0.95)[i] * us[1 - i])
+                worth[i] |= us[i] < 0.95 * gather
+                beside[i] |= us[i] < min(0.95 * gather, (0.85, 0.95)[i] * us[1 - i])
     has = [own.form(128, LDS) == 1, bool(own.form(128, MERGED_GATHER) & 2) and own.form(128, MERGED_LDS) == 3]
     own.close(), full.close()
     assert host.load().host_live() == 0

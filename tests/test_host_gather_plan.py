@@ -36,9 +36,9 @@ def test_a_dense_operand_beyond_32_bit_offsets_has_one_chunk_in_flight(prec):
 
 
 def test_a_small_product_of_two_planes():
-    """512 x 512, N = 128: 2.57 us in these tiles and waves, 2.92 in tiles of 128 bytes."""
+    """512 x 512, N = 128: 2.53 - 2.57 us in tiles of 64 bytes by two or four waves, 2.92 in tiles of 128 bytes."""
     A = host.Mat(512, 512, 8, 0.8, "L16R8")
-    assert A.variant(128) == (64, 4)
+    assert A.variant(128) in ((64, 2), (64, 4))
     A.close()
 
 
