@@ -496,7 +496,7 @@ def run_phases(mc, torch):
     B = torch.from_numpy(c["B"]).cuda()
     ref = mc.spmm(A, B, "L8R8", options=mc.Options(spmm_merge=-1, spmm_slab=-1))
     stream = torch.cuda.Stream()
-    names = ["wave started", "kernel arguments and panel pointers arrived", "column indices and A operands arrived",
+    names = ["wave started", "kernel arguments arrived (panels of equal length: no pointers)", "column indices and A operands arrived",
              "rows of the first chunk landed", "all chunks in the accumulators", "partial tile written",
              "workgroup barrier passed", "output pieces summed", "stores issued", "stores acknowledged"]
     samples = []
