@@ -50,3 +50,18 @@ def test_the_faster_of_the_resident_forms(M, K, V, empty, sigma, prec, N, form):
     A = host.Mat(M, K, V, empty, prec, sigma=sigma)
     assert A.form(N) == form
     A.close()
+
+
+@pytest.mark.parametrize("prec,V,s", [("L8R8", 8, 0.8), ("L8R8", 4, 0.9), ("L8R4", 8, 0.7), ("L16R8", 4, 0.8)])
+def test_the_resident_form_runs_where_it_is_expected_three_percent_faster(prec, V, s):
+    given = {"spmm_merge": -1}
+    with_copy = mc.Options(spmm_slab=1, **given)
+    A = host.Mat(4096, 4096, V, s, prec, options=with_copy)
+    seen = set()
+    for row_bytes in range(32, 1040, 16):
+        N = row_bytes * 8 // A.rhs
+        gathered, resident = A.us(N, mc.Options(spmm_slab=-1, **given)), A.us(N, with_copy)
+        assert A.form(N, mc.Options(**given)) == int(1.03 * resident < gathered)
+        seen.add(1.03 * resident < gathered)
+    A.close()
+    assert seen == {False, True}
