@@ -581,6 +581,7 @@ void take_shares(const mc_mat *A, bool cut, SddmmArgs *a)
     const bool pieces = cut && A->n_cut > 0;
     a->shares = A->d_shares + (pieces ? 4 * (int64_t)A->P : 0);
     a->n_shares = pieces ? A->n_cut : A->P;
+    a->uniform_vectors = pieces ? 0 : A->uniform_vectors;
     a->kmat_rows = A->K;
 }
 
@@ -636,7 +637,9 @@ int mat_create_impl(int M, int K, int V, int lhs_bits, const int32_t *row_ptr, c
     A->nvec = lay.nvec; A->nslots = lay.nslots; A->vals_bytes = lay.vals_bytes;
     A->max_panel_chunks = 0;
     int min_panel_chunks = INT32_MAX;
+    A->uniform_vectors = lay.P > 0 ? row_ptr[1] - row_ptr[0] : 0;
     for (int p = 0; p < lay.P; ++p) {
+        if (row_ptr[p + 1] - row_ptr[p] != A->uniform_vectors) A->uniform_vectors = 0;
         const int c = (row_ptr[p + 1] - row_ptr[p] + MC_CHUNK - 1) / MC_CHUNK;
         if (c > A->max_panel_chunks) A->max_panel_chunks = c;
         if (c < min_panel_chunks) min_panel_chunks = c;
@@ -1584,7 +1587,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
     auto fused = [&](int tile) -> int {           // tile: the kernel's head dimension
         AttnArgs f = {};
         f.real_pieces = dk * qkv_bits / 8 / 16; f.out_cols = dk;
-        f.panel_ptr = mask->d_panel_ptr; f.slot_idx = mask->d_slot_idx;
+        f.panel_ptr = mask->d_panel_ptr; f.slot_idx = mask->d_slot_idx; f.uniform_vectors = mask->uniform_vectors;
         f.Q = static_cast<const uint8_t *>(Q_dev); f.Km = static_cast<const uint8_t *>(Km_dev);
         f.Vm = static_cast<const uint8_t *>(Vm_dev); f.O = static_cast<float *>(O_dev); f.out_f16 = out_f16;
         f.head_stride = head_stride; f.token_stride = token_stride; f.batch_stride = batch_stride;

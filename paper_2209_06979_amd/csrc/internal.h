@@ -25,6 +25,7 @@ struct mc_mat {
     int64_t nvec, nslots, vals_bytes;
     int max_panel_chunks;      // longest panel, in chunks of 64 vectors
     int uniform_chunks;        // chunks of every panel when all panels have the same number (and at least one), else 0
+    int uniform_vectors;       // the same of their vectors
     int device;                // HIP device the buffers live on
     int32_t *d_panel_ptr;      // 2*P: chunk-aligned first slot, real end slot
     int32_t *d_row_ptr;        // P+1: interchange row pointers (vector offsets)
@@ -212,6 +213,7 @@ struct DenseFillArgs {
 struct SddmmArgs {
     const int32_t *shares;     // n_shares x 4 (see mc_mat)
     int n_shares;
+    int uniform_vectors;       // > 0: the shares are the panels and each has this many vectors (shares is not read)
     const int32_t *slot_idx;
     const uint8_t *Q;
     int64_t ldq_bytes, Q_batch_stride;
@@ -288,6 +290,7 @@ struct AttnArgs {
     const uint8_t *Km;
     int64_t in_token_stride, in_head_stride; // bytes of Q, Km, Vm
     const uint8_t *Q, *Vm;
+    int64_t uniform_vectors;                 // > 0: every panel has this many vectors and starts behind the chunks of those before (panel_ptr is not read)
     int64_t in_batch_stride;                 // between batch items: bytes of Q, Km, Vm
     float *O;                                // fp32, or half when out_f16 is set
     int64_t head_stride, token_stride;       // elements of O
