@@ -83,8 +83,12 @@ constexpr unsigned PAIR_ROWS_Y = 32768; // rows of the grid along y, the rest of
 
 // MAXCH: longest panel in chunks of 64 vectors.  HPW: heads (= waves) per workgroup.
 // PB: bits of the re-quantised softmax output.  16 ("16b-8b" layer): the code c <= 32639 is split
-// into signed bytes c = 256*hi + lo (Section 4.4); the hi codes feed MFMA rows 0..7 and the lo
-// codes rows 8..15 of the same instruction, and the output is (O_hi << 8) + O_lo.
+// into signed bytes c = 256*hi + lo (Section 4.4); the lo codes of row r feed MFMA row 2r and the hi
+// codes row 2r + 1 of the same instruction, and the output is (O_hi << 8) + O_lo.  The two sums of an output lie in neighbouring registers
+// of a lane, a code's two bytes stay together from the rounded product to LDS, and the output tile has 8 rows.  (With a plane of
+// its own for each, 8 rows apart: eight more byte permutations and stores of LDS a chunk, a tile of 16 rows to write, to add up between the waves and to
+// put together; replayed from a graph 8 x 4 heads x 8192, (L, heads, dk) 169.3 -> 167.6 us, 1 x 368 x 112 4.37 -> 4.20, 1 x 1368 x 64 of nibbles
+// 4.26 -> 4.06, 2 x 12 x 1016 x 80 14.4 -> 14.2.)
 // QB: bits of Q, Kmat and V.  4 ("8b-4b" layer): rows are 32 bytes of packed nibbles, whose bytes are widened in registers (Section 4.4
 // without an int4 matrix unit): the even elements of a 16-byte piece in lane groups 0 and 1, the odd ones in groups 2 and 3.  An
 // odd element stays in the upper half of its byte, worth 16 x its value; an even one in the lower half as value + 8, which one
@@ -118,13 +122,13 @@ void attention_fused_kernel(AttnArgs a)
     static_assert(QB == 8 || QB == 4, "Q, K, V are 8-bit or packed 4-bit");
     static_assert(DK == 64 || (DK == 128 && (QB == 4 || HPW == 1)) || (DK == 192 && PAD), "rows of 128 bytes: one head per workgroup");
     constexpr int NW = HPW * KS;         // waves per workgroup
-    constexpr int OTILE = (PB == 16 ? 16 : 8) * (DK + 4) * 4;                       // a wave's output tile, staged where the gathered rows were
-    // The code area holds ONE chunk, [plane][slot][8 rows] (codes are written right before they are read; an area for all chunks and
+    constexpr int OTILE = 8 * (DK + 4) * 4;                                         // a wave's output tile, staged where the gathered rows were
+    // The code area holds ONE chunk, [slot][8 rows][1 or 2 bytes] (codes are written right before they are read; an area for all chunks and
     // the output tile took 3.5 - 14 KB more of LDS per wave): a workgroup of two heads stays below 20 KB, eight of them, i.e. all 2048 of a 8 x 4096
     // layer, are resident at once; four waves of a dk of 144 - 192 take 68 KB instead of 82, two workgroups a compute unit instead of
     // one (12 heads x 5568, dk = 144, 77 % empty 489 -> 296 us, 3 x 2264, dk = 160 28.5 -> 19.1); with 16-bit codes 16 waves are resident instead of
     // 13 (8 heads x 5008, dk = 96, 95 % 29.1 -> 25.3; 12 x 2 x 2336, dk = 64, 4-bit inputs 35.8 -> 33.7).
-    constexpr int PSTRIDE = 512, PLB = 512 * (PB / 8);                              // from the high to the low plane of the codes; bytes of that area
+    constexpr int SLOTB = PB, PLB = 64 * SLOTB;                                     // bytes of a slot's codes; of that area
     constexpr int DKB = DK * QB / 8; // bytes of one head's row
     constexpr int KK = DK / 64;      // MFMA steps along the head dimension
     constexpr int NO = DK / 16;      // column tiles of the output
@@ -141,7 +145,7 @@ void attention_fused_kernel(AttnArgs a)
     constexpr int WSTG = (HPW == 1 && OTILE > STG) ? OTILE : NST * STG;               // ... of the stages of one share of the chunks
     static_assert(HPW == 1 || OTILE <= STG, "with two heads per workgroup a wave's output tile is staged in one gather stage");
     __shared__ __attribute__((aligned(16))) char stage_all[WSTG * KS];       // chunks of gathered rows (KS > 1: one stage per wave)
-    __shared__ __attribute__((aligned(16))) char Pl_all[NW * PLB]; // codes, [plane][slot][8 rows], per wave
+    __shared__ __attribute__((aligned(16))) char Pl_all[NW * PLB]; // codes of a chunk, per wave
     __shared__ __attribute__((aligned(8))) char zeros[72];                     // row operand of the MFMA rows that carry no codes
     __shared__ int xch[2][HPW][KS][8];                                        // row maxima / row sums of the KS waves of a head
 
@@ -458,9 +462,9 @@ void attention_fused_kernel(AttnArgs a)
     for (int ct = 0; ct < NCT; ++ct)
         vaddr[ct] = stage + (slot0 % NIT) * 1024 + (slot0 / NIT) * ROWB + (((NITW * w + ct) ^ (slot0 % NIT)) * 16) + 8 * (src & 1);
     // lanes 2t and 2t+1 supply the 8-byte pieces that end up in MFMA rows 0..7 and 8..15: the
-    // codes and 8 zero bytes (PB 8; they do not move from chunk to chunk), or the high and the low plane of the codes (PB 16)
-    const char *paddr = (PB == 8 && (src & 1)) ? zeros : Pl + slot0 * 8 + (src & 1) * PSTRIDE;
-    char *const code_at = Pl + ((g >> 1) * 16 + j) * 8 + 4 * (g & 1); // codes of tile pair pr: 256 * pr on
+    // codes and 8 zero bytes (PB 8; they do not move from chunk to chunk), or the low and high bytes of rows 0..3 and 4..7 (PB 16)
+    const char *paddr = (PB == 8 && (src & 1)) ? zeros : Pl + slot0 * SLOTB + (PB == 8 ? 0 : (src & 1) * 8);
+    char *const code_at = Pl + ((g >> 1) * 16 + j) * SLOTB + SLOTB / 2 * (g & 1); // codes of tile pair pr: 32 slots * pr on
     // p / s_p stays within the largest code unless s_p is below its reciprocal
     const bool cap = a.inv_s_p > (PB == 8 ? 127.f : 32639.f);
     static_for<MAXCH>([&](auto C) {
@@ -472,7 +476,7 @@ void attention_fused_kernel(AttnArgs a)
         }
         if (c < nloc) {
             // Codes of this chunk's slots (tile*16 + j), rows 4*(g&1) .. +3: one 32-bit LDS write
-            // per tile and plane.  Done here, chunk by chunk, so that this ALU work overlaps the V copies in flight.
+            // (PB 16: one of 64 bits) per tile.  Done here, chunk by chunk, so that this ALU work overlaps the V copies in flight.
             auto make_codes = [&](auto Cap) {
                 constexpr bool CAP = decltype(Cap)::value;
 #pragma unroll
@@ -487,14 +491,13 @@ void attention_fused_kernel(AttnArgs a)
                         const float e = x[2 * c + pr][r];
                         u[r] = __builtin_bit_cast(unsigned, CAP ? fminf(e * rinv[r], PB == 8 ? 127.f : 32639.f) + INTEGER : __builtin_fmaf(e, rinv[r], INTEGER));
                     }
-                    char *to = code_at + pr * 256;
-                    const unsigned c01 = __builtin_amdgcn_perm(u[1], u[0], 0x05010400), c23 = __builtin_amdgcn_perm(u[3], u[2], 0x05010400);
-                    const unsigned low = __builtin_amdgcn_perm(c23, c01, 0x05040100);
+                    char *to = code_at + pr * 32 * SLOTB;
                     if (PB == 8) {
-                        *reinterpret_cast<unsigned *>(to) = low;
+                        const unsigned c01 = __builtin_amdgcn_perm(u[1], u[0], 0x05010400), c23 = __builtin_amdgcn_perm(u[3], u[2], 0x05010400);
+                        *reinterpret_cast<unsigned *>(to) = __builtin_amdgcn_perm(c23, c01, 0x05040100);
                     } else {
-                        *reinterpret_cast<unsigned *>(to) = __builtin_amdgcn_perm(c23, c01, 0x07060302);
-                        *reinterpret_cast<unsigned *>(to + PSTRIDE) = low ^ 0x80808080u;
+                        *reinterpret_cast<v2i *>(to) = (v2i){(int)(__builtin_amdgcn_perm(u[1], u[0], 0x05040100) ^ 0x00800080u),
+                                                             (int)(__builtin_amdgcn_perm(u[3], u[2], 0x05040100) ^ 0x00800080u)};
                     }
                 }
             };
@@ -502,7 +505,7 @@ void attention_fused_kernel(AttnArgs a)
             else make_codes(std::false_type{});
             acquire(Vg, gc, (c + 1) % NST);
             // the codes, transposed to the MFMA row operand: row j < 8, slots g*16 .. +15
-            const v2i p0 = lds_read_tr8(paddr), p1 = lds_read_tr8(paddr + 64);
+            const v2i p0 = lds_read_tr8(paddr), p1 = lds_read_tr8(paddr + (PB == 8 ? 64 : 128));
             v2i d[NCT][2];
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
@@ -534,15 +537,17 @@ void attention_fused_kernel(AttnArgs a)
         __builtin_amdgcn_s_barrier(); // nobody reads the stages any more: each wave takes one for its tile
     }
     int *Ol = reinterpret_cast<int *>(stage_all + ks * WSTG + w * STG); // (HPW 2: as many stages as waves)
+    // lane (j, g) has rows 4g .. 4g+3, or (PB 16) the low and the high plane's sums of rows 2g and 2g + 1
     if (g < 2 || PB == 16) {
+        constexpr int ROWS = PB == 8 ? 4 : 2;
 #pragma unroll
-        for (int ct = 0; ct < NO; ++ct)
+        for (int ct = 0; ct < NO; ++ct) {
+            // nibbles: low ones were 8 too large, high ones carry a factor 16; each plane's sum for itself
+            auto sum = [&](int r) -> int { return QB == 8 ? o[ct][r] : (ct & 1) ? o[ct][r] >> 4 : o[ct][r] - 8 * ocodes[r]; };
+            const int col = QB == 8 ? ct * 16 + j : (ct >> 1) * 32 + 2 * j + (ct & 1);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                // nibbles: low ones were 8 too large, high ones carry a factor 16; each plane's sum for itself
-                if (QB == 8) Ol[(4 * g + r) * (DK + 4) + ct * 16 + j] = o[ct][r];
-                else Ol[(4 * g + r) * (DK + 4) + (ct >> 1) * 32 + 2 * j + (ct & 1)] = (ct & 1) ? o[ct][r] >> 4 : o[ct][r] - 8 * ocodes[r];
-            }
+            for (int r = 0; r < ROWS; ++r) Ol[(ROWS * g + r) * (DK + 4) + col] = PB == 8 ? sum(r) : (sum(2 * r + 1) << 8) + sum(2 * r);
+        }
     }
     lgkm_wait();
     if (KS > 1) __syncthreads(); else __builtin_amdgcn_wave_barrier();
@@ -562,14 +567,12 @@ void attention_fused_kernel(AttnArgs a)
             v4h hv[2];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                v4i sres = {0, 0, 0, 0}, slo = {0, 0, 0, 0};
+                v4i sres = {0, 0, 0, 0};
 #pragma unroll
                 for (int k = 0; k < KS; ++k) {
                     const int *Ok = (KS > 1) ? partial_tile(k) : Ol;
                     sres += *reinterpret_cast<const v4i *>(&Ok[row * (DK + 4) + col + 4 * q]);
-                    if (PB == 16) slo += *reinterpret_cast<const v4i *>(&Ok[(row + 8) * (DK + 4) + col + 4 * q]);
                 }
-                if (PB == 16) sres = (sres << 8) + slo;
                 hv[q] = to_half4((v4f){sres.x * a.out_scale, sres.y * a.out_scale, sres.z * a.out_scale, sres.w * a.out_scale});
             }
             typedef _Float16 v8h __attribute__((ext_vector_type(8)));
@@ -586,14 +589,12 @@ void attention_fused_kernel(AttnArgs a)
         if (piece >= 2 * DK) continue;
         const int row = piece / (DK / 4), col = (piece % (DK / 4)) * 4;
         if (PAD && col >= a.out_cols) continue;
-        v4i sres = {0, 0, 0, 0}, slo = {0, 0, 0, 0};
+        v4i sres = {0, 0, 0, 0};
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
             const int *Ok = (KS > 1) ? partial_tile(k) : Ol;
             sres += *reinterpret_cast<const v4i *>(&Ok[row * (DK + 4) + col]);
-            if (PB == 16) slo += *reinterpret_cast<const v4i *>(&Ok[(row + 8) * (DK + 4) + col]);
         }
-        if (PB == 16) sres = (sres << 8) + slo;
         const v4f f = {sres.x * a.out_scale, sres.y * a.out_scale, sres.z * a.out_scale, sres.w * a.out_scale};
         __builtin_nontemporal_store(f, reinterpret_cast<v4f *>(Oh + (int64_t)row * a.token_stride + col));
     }
