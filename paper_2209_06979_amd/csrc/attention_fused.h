@@ -315,10 +315,12 @@ void attention_fused_kernel(AttnArgs a)
     static_assert(DK * 128 * 128 < 1 << 22, "scores are exact beside 1.5 * 2^23");
     // (A conversion takes a SIMD 4.3 clocks, as a byte permutation, a multiply-add of integers or an exchange of neighbours; a sum or product of floats 2.3 -
     // 2.7, an exponential 8.9.  With one product per index instead of per copy and codes by one multiply-add and permutations, 40
-    // layers replayed from graphs 1.010x in the mean, 8 x 4 heads x 8192 with 16-bit codes 1.02, 0.99 - 1.05x: it is the gather that takes the time.
-    // Not where four more registers are too many.)
-    constexpr bool BIASED = !(HPW == 2 && KS > 1 && PB == 16);
-    constexpr int FLOAT0 = BIASED ? 0x4B400000 : 0;
+    // layers replayed from graphs 1.010x in the mean, 8 x 4 heads x 8192 with 16-bit codes 1.02, 0.99 - 1.05x: it is the gather that takes the time.)
+    // FOLDED: subtraction and product of the softmax in one multiply-add (below): the pairs by several waves with 16-bit codes, which the instructions
+    // bound, too (three operations a score with conversions 169.7 us at 8 x 4 heads x 8192, subtraction and product 172, folded 168.2).  Elsewhere the exact
+    // difference gives the largest term of a row exactly, at up to 0.5 % of the time.
+    constexpr bool FOLDED = HPW == 2 && KS > 1 && PB == 16 && QB == 8;
+    constexpr int FLOAT0 = 0x4B400000;
     v4i first = {FLOAT0, FLOAT0, FLOAT0, FLOAT0};
     if (QB == 4) {
         const int minus8 = g < 2 ? (int)0xF8F8F8F8 : 0;
@@ -367,11 +369,12 @@ void attention_fused_kernel(AttnArgs a)
     start_pipeline(Vg);
 
     // ---- softmax over row 4*(g&1) + r, in base 2: exp(x - max) = 2^((s - smax) * scale2), the difference exact -----
-    // (Not BIASED: s * scale2 - m2 by one multiply-add, exact but for its rounding and for what m2 = smax * scale2 was rounded by, the same for the
-    // whole row; that is a factor of 2^64 at most, which the sum takes off again, because a scale of 256 leaves the largest scores alone as any larger
-    // one does: without that bound scales from 3e38 / smax on had no probabilities at all.)
+    // (FOLDED: s * scale2 - m2 by one multiply-add, exact but for its rounding and for what m2 = smax * scale2, both with their 1.5 * 2^23, was rounded
+    // by.  That is the same for the whole row, a factor of 2^32 at most, which the sum takes off again, because a scale of 64 leaves the largest scores
+    // alone as any larger one does: what is one less is 2^-64 of them, which no sum of 4096 holds and no code shows.  Error against 64 bits, six layers of 2000 - 3400
+    // tokens: 2.86e-5, 2.89e-5 with conversions.)
     constexpr float LOG2E = 1.4426950408889634f;
-    const float scale2 = fminf(a.score_scale * LOG2E * (QB == 4 ? 0.0625f : 1.f), 256.f);
+    const float scale2 = fminf(a.score_scale * LOG2E * (QB == 4 ? 0.0625f : 1.f), FOLDED ? 64.f : 256.f);
     float top[4], srow[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -391,7 +394,7 @@ void attention_fused_kernel(AttnArgs a)
             for (int k = 0; k < KS; ++k) imax[r] = max(imax[r], xch[0][w][k][4 * (g & 1) + r]);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) top[r] = BIASED ? __builtin_bit_cast(float, imax[r]) : (float)imax[r] * scale2;
+    for (int r = 0; r < 4; ++r) top[r] = FOLDED ? __builtin_bit_cast(float, imax[r]) * scale2 : __builtin_bit_cast(float, imax[r]);
     float x[NPR][4];
     static_for<MAXCH>([&](auto C) {
         constexpr int c = C;
@@ -401,7 +404,7 @@ void attention_fused_kernel(AttnArgs a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int sum = sc[2 * c + pr][r]; // (a bit cast of a vector's element takes the first one)
-                    x[2 * c + pr][r] = __builtin_amdgcn_exp2f(BIASED ? (__builtin_bit_cast(float, sum) - top[r]) * scale2 : __builtin_fmaf((float)sum, scale2, -top[r]));
+                    x[2 * c + pr][r] = __builtin_amdgcn_exp2f(FOLDED ? __builtin_fmaf(__builtin_bit_cast(float, sum), scale2, -top[r]) : (__builtin_bit_cast(float, sum) - top[r]) * scale2);
                 }
             if (ks + c * KS == nch - 1) {
                 // the panel's last chunk: padded slots count for nothing.  (The empty statement keeps
