@@ -1596,11 +1596,10 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         f.score_scale = s_q * s_k / std::sqrt((float)dk); f.inv_s_p = 1.f / s_p; f.out_scale = s_p * s_v;
         f.heads = heads; f.batch = batch; f.tokens = L;
         // neighbouring heads contiguous inside a token, rows of at most 64 bytes (less than 64 elements where they do not fill the tile): two
-        // heads per workgroup can gather 128 bytes per token (not for 16-bit codes with 4-bit inputs, whose output tile does not fit
-        // that kernel's stages)
+        // heads per workgroup can gather 128 bytes per token
         const bool short_rows = dk == 64 || qkv_bits == 4;
         const bool fills = dk == tile && tile <= 128; // (the tile of 192 is a padded one)
-        const bool pairs = ((fills && short_rows) || tile == 64) && head_stride == dk && heads % 2 == 0 && !(p_bits == 16 && qkv_bits == 4);
+        const bool pairs = ((fills && short_rows) || tile == 64) && head_stride == dk && heads % 2 == 0;
         const double avg = mask->P ? (double)(mask->nslots / MC_CHUNK) / mask->P : 0.0;
         // One launch for the panels in `list` (null: all), none of which has more than max_chunks chunks; mean: of theirs.
         auto launch = [&](const int32_t *list, int n_panels, int max_chunks, double mean) -> hipError_t {
@@ -1629,7 +1628,9 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 const bool two = fills ? units >= 2048 || long_enough
                                        : units >= 4096 ? work >= 10000.0
                                                        : long_enough && f.in_token_stride >= 96 && (head_bytes > 32 || wpp < 4);
-                hpg = (pairs && two && wpp < 8) ? 2 : 1;
+                // (Not 128 nibbles by four waves each: eight waves of 152 registers are one workgroup a compute unit, a third of its places empty.
+                // 2 x 2 heads x 7496, 74 % empty 103 -> 73 us, 8 x 4800, 75 % 96 -> 62.)
+                hpg = (pairs && two && wpp < 8 && !(fills && tile == 128 && wpp == 4)) ? 2 : 1;
                 // (Rows of 256 bytes, too, where four waves' stages take half a compute unit's LDS: against 1024 waves in flight 46 drawn layers of
                 // dk = 144 - 192 1.03 times as fast in the mean, up to 1.23.  4096 waves: 0.98, down to 0.73.)
                 if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp + 1 <= mean) wpp *= 2;

@@ -114,7 +114,7 @@ constexpr unsigned PAIR_ROWS_Y = 32768; // rows of the grid along y, the rest of
 // nothing to a score and give zero output columns, which are not stored.  Two heads per workgroup (DK 64 only): the places of both heads' pieces,
 // which are contiguous in memory, side by side as if the rows were full.
 template <int MAXCH, int HPW, int PB, int QB, int KS, int DK, bool PAD = false>
-__global__ __launch_bounds__(64 * HPW * KS, (((HPW == 1 && PB == 8 && KS == 1 && DK == 64) || (HPW == 2 && DK == 64 && QB == 8)) ? 4 : ((KS == 8 || DK == 192) ? 2 : 3)))
+__global__ __launch_bounds__(64 * HPW * KS, (((HPW == 1 && PB == 8 && KS == 1 && DK == 64) || (HPW == 2 && DK == 64)) ? 4 : ((KS == 8 || DK == 192) ? 2 : 3)))
 void attention_fused_kernel(AttnArgs a)
 {
     static_assert(!PAD || HPW == 1 || DK == 64, "shorter rows of more than 64 elements: one head per workgroup");

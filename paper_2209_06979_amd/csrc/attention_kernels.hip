@@ -7,9 +7,8 @@ template <int PB, int QB, int DK> hipError_t launch_pq(const AttnArgs &a, int he
 {
     if (heads_per_group == 2 && waves_per_panel == 8) return hipErrorInvalidValue;
     if (heads_per_group == 2) {
-        // (16-bit codes with 4-bit Q/K/V: the two-plane output tile does not fit the stage; rows of 128
-        // bytes: one head per workgroup)
-        if constexpr ((PB == 16 && QB == 4) || (DK == 128 && QB == 8)) return hipErrorInvalidValue;
+        // (rows of 128 bytes: one head per workgroup)
+        if constexpr (DK == 128 && QB == 8) return hipErrorInvalidValue;
         else {
             if (waves_per_panel == 4) return launch_pairs<2, PB, QB, 4, DK, false>(a, s);
             if (waves_per_panel == 2) return launch_pairs<2, PB, QB, 2, DK, false>(a, s);

@@ -19,13 +19,10 @@ template <int PB, int QB, int DK> hipError_t launch_padded(const AttnArgs &a, in
 template <int PB, int QB> hipError_t launch_padded_64(const AttnArgs &a, int heads_per_group, int waves_per_panel, hipStream_t s)
 {
     if (heads_per_group == 1) return launch_padded<PB, QB, 64>(a, waves_per_panel, s);
-    if constexpr (PB == 16 && QB == 4) return hipErrorInvalidValue; // (the two-plane output tile does not fit the stage)
-    else {
-        if (waves_per_panel == 8) return hipErrorInvalidValue;
-        if (waves_per_panel == 4) return launch_pairs<2, PB, QB, 4, 64, true>(a, s);
-        if (waves_per_panel == 2) return launch_pairs<2, PB, QB, 2, 64, true>(a, s);
-        return launch_pairs<2, PB, QB, 1, 64, true>(a, s);
-    }
+    if (waves_per_panel == 8) return hipErrorInvalidValue;
+    if (waves_per_panel == 4) return launch_pairs<2, PB, QB, 4, 64, true>(a, s);
+    if (waves_per_panel == 2) return launch_pairs<2, PB, QB, 2, 64, true>(a, s);
+    return launch_pairs<2, PB, QB, 1, 64, true>(a, s);
 }
 } // namespace
 

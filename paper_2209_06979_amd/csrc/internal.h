@@ -336,7 +336,7 @@ int scores_softmax_max_npad(int row_bytes, int waves);
 hipError_t launch_absmax(const float *x, int64_t n, float *result, hipStream_t s);
 hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uint8_t *q, hipStream_t s);
 // dk is 64 or 128.  heads_per_group 2 needs head_stride == dk (token-major layout), rows of at most 64
-// bytes and an even head count, and is not available for 16-bit codes with 4-bit inputs
+// bytes and an even head count
 hipError_t launch_attention_fused(const AttnArgs &a, int heads_per_group, int waves_per_panel, int p_bits, int qkv_bits,
                                   int dk, hipStream_t s);
 // the same kernel for head dimensions below its tile (64 or 128), and up to its tile of 192: one head per workgroup; a.real_pieces, a.out_cols set
