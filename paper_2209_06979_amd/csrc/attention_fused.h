@@ -162,8 +162,10 @@ void attention_fused_kernel(AttnArgs a)
     // empty, 8-bit codes and inputs, dk = 32 36.6 -> 33.9 us, 48 60.2 -> 41.6, 80 61.8 -> 55.4, 96 63.1 -> 59.0, 128 52.4 -> 50.3.)
     const int groups = a.heads / HPW;
     // (all of the first line of arguments in one round trip, not one by one as they come to be needed)
+    constexpr bool COMPUTED = !(HPW == 2 && KS > 1 && PB == 8 && QB == 8 && !PAD); // (see below)
+    if constexpr (COMPUTED) asm volatile("" ::"s"(a.uniform_vectors), "s"(a.Q));
     asm volatile("" ::"s"(a.panel_ptr), "s"(a.slot_idx), "s"(a.panel_list), "s"(a.heads), "s"(a.batch), "s"(a.pair_shift), "s"(a.pair_rows),
-                 "s"(a.Km), "s"(a.in_token_stride), "s"(a.in_head_stride), "s"(a.Q), "s"(a.uniform_vectors));
+                 "s"(a.Km), "s"(a.in_token_stride), "s"(a.in_head_stride), "s"(a.Q));
     const int grid_row = (int)(blockIdx.z * PAIR_ROWS_Y + blockIdx.y);
     if (grid_row >= a.pair_rows) return;
     const int pair = (int)(blockIdx.x & ((1u << a.pair_shift) - 1)) * a.pair_rows + grid_row;
@@ -175,9 +177,10 @@ void attention_fused_kernel(AttnArgs a)
     const int panel = a.panel_list ? a.panel_list[blockIdx.x >> a.pair_shift] : (int)(blockIdx.x >> a.pair_shift);
     const int head = hgrp * HPW + w;
     // (panels of equal length: first slot and length without a trip to memory that the column indices wait for.  Replayed from a graph, three layers
-    // in turn: 4 heads x 1000 4.46 -> 4.40 us, 8 x 4 heads x 8192, 16-bit codes, (L, heads, dk) 170.5 -> 169.3.)
-    int s0, n = (int)a.uniform_vectors;
-    if (n > 0) s0 = panel * ((n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK);
+    // in turn: 4 heads x 1000 4.46 -> 4.40 us, 8 x 4 heads x 8192, 16-bit codes, (L, heads, dk) 170.5 -> 169.3.
+    // Not where several waves share the 8-bit codes of a pair: all 128 registers are taken there, and one more would be spilled.)
+    int s0, n = COMPUTED ? (int)a.uniform_vectors : 0;
+    if (COMPUTED && n > 0) s0 = panel * ((n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK);
     else {
         s0 = a.panel_ptr[2 * panel];
         n = a.panel_ptr[2 * panel + 1] - s0;
