@@ -1600,6 +1600,9 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         const bool short_rows = dk == 64 || qkv_bits == 4;
         const bool fills = dk == tile && tile <= 128; // (the tile of 192 is a padded one)
         const bool pairs = ((fills && short_rows) || tile == 64) && head_stride == dk && heads % 2 == 0;
+        // Pairs by several waves with 16-bit codes take the exponential of entries down to 2^-64 of a row's largest only (FOLDED in the kernel): below that
+        // scale of the probabilities, where such entries have codes, one head per workgroup.
+        const bool faint = p_bits == 16 && qkv_bits == 8 && !(f.inv_s_p <= FOLDED_MAX_INV_S_P);
         const double avg = mask->P ? (double)(mask->nslots / MC_CHUNK) / mask->P : 0.0;
         // One launch for the panels in `list` (null: all), none of which has more than max_chunks chunks; mean: of theirs.
         auto launch = [&](const int32_t *list, int n_panels, int max_chunks, double mean) -> hipError_t {
@@ -1633,7 +1636,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                                                              (head_bytes > 32 && units >= 1152 && mean > 2.0);
                 // (Not 128 nibbles by four waves each: eight waves of 152 registers are one workgroup a compute unit, a third of its places empty.
                 // 2 x 2 heads x 7496, 74 % empty 103 -> 73 us, 8 x 4800, 75 % 96 -> 62.)
-                hpg = (pairs && two && wpp < 8 && !(fills && tile == 128 && wpp == 4)) ? 2 : 1;
+                hpg = (pairs && two && wpp < 8 && !(fills && tile == 128 && wpp == 4) && !(faint && wpp > 1)) ? 2 : 1;
                 // (Rows of 256 bytes, too, where four waves' stages take half a compute unit's LDS: against 1024 waves in flight 46 drawn layers of
                 // dk = 144 - 192 1.03 times as fast in the mean, up to 1.23.  4096 waves: 0.98, down to 0.73.)
                 if (hpg == 1) while (wpp < 4 && units * wpp * 2 <= 2048 && wpp + 1 <= mean) wpp *= 2;
@@ -1646,7 +1649,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
             } else {
                 if (o.attention_mode == 3 && wpp < 2) wpp = 2;
                 if (o.attention_mode == 4 && wpp < 4) wpp = 4;
-                hpg = (o.attention_mode != 2 && pairs && wpp < 8) ? 2 : 1;
+                hpg = (o.attention_mode != 2 && pairs && wpp < 8 && !(faint && wpp > 1)) ? 2 : 1;
             }
             if (fills) return launch_attention_fused(f, hpg, wpp, p_bits, qkv_bits, dk, s);
             return launch_attention_fused_padded(f, hpg, wpp, p_bits, qkv_bits, tile, s);

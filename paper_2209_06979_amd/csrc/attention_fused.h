@@ -374,7 +374,8 @@ void attention_fused_kernel(AttnArgs a)
     // ---- softmax over row 4*(g&1) + r, in base 2: exp(x - max) = 2^((s - smax) * scale2), the difference exact -----
     // (FOLDED: s * scale2 - m2 by one multiply-add, exact but for its rounding and for what m2 = smax * scale2, both with their 1.5 * 2^23, was rounded
     // by.  That is the same for the whole row, a factor of 2^32 at most, which the sum takes off again, because a scale of 64 leaves the largest scores
-    // alone as any larger one does: what is one less is 2^-64 of them, which no sum of 4096 holds and no code shows.  Error against 64 bits, six layers of 2000 - 3400
+    // alone as any larger one does: what is one less is 2^-64 of them, which no sum of 4096 holds, and no code shows it while inv_s_p is at most
+    // FOLDED_MAX_INV_S_P, nor what the factor of 2^-32 takes from entries below 2^-94: larger ones are not launched here.  Error against 64 bits, six layers of 2000 - 3400
     // tokens: 2.86e-5, 2.89e-5 with conversions.)
     constexpr float LOG2E = 1.4426950408889634f;
     const float scale2 = fminf(a.score_scale * LOG2E * (QB == 4 ? 0.0625f : 1.f), FOLDED ? 64.f : 256.f);
@@ -681,6 +682,7 @@ inline int pairs_at_a_time(int64_t pairs, double row_bytes, double index_bytes, 
 
 template <int HPW, int PB, int QB, int KS, int DK, bool PAD> hipError_t launch_pairs(AttnArgs a, hipStream_t s)
 {
+    if (HPW == 2 && KS > 1 && PB == 16 && QB == 8 && !(a.inv_s_p <= FOLDED_MAX_INV_S_P)) return hipErrorInvalidValue;
     const unsigned pairs = (unsigned)(a.heads / HPW) * (unsigned)a.batch;
     const int row = HPW * (PAD ? a.real_pieces * 16 : DK * QB / 8), lines = (row + 127) / 128 * 128; // (the L2 holds lines of 128 bytes)
     PairLines asked;

@@ -335,6 +335,9 @@ hipError_t launch_scores_softmax(const ScoresArgs &a, int qkv_bits, int code_bit
 int scores_softmax_max_npad(int row_bytes, int waves);
 hipError_t launch_absmax(const float *x, int64_t n, float *result, hipStream_t s);
 hipError_t launch_quantize(const float *x, int64_t n, float scale, int bits, uint8_t *q, hipStream_t s);
+// Largest inv_s_p for two heads per workgroup by several waves each with 16-bit codes and 8-bit inputs: what is 2^-64 of a row's largest entry has
+// no code then (a quarter of a step), and less is all that those kernels may get wrong.
+constexpr float FOLDED_MAX_INV_S_P = 0x1p62f;
 // dk is 64 or 128.  heads_per_group 2 needs head_stride == dk (token-major layout), rows of at most 64
 // bytes and an even head count
 hipError_t launch_attention_fused(const AttnArgs &a, int heads_per_group, int waves_per_panel, int p_bits, int qkv_bits,

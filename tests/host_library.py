@@ -167,13 +167,13 @@ class Mask:
         col_idx = np.concatenate([np.arange(n) for n in lengths]).astype(np.int32)
         assert lib.mc_mat_create(L, L, 8, 0, mc._p32(row_ptr), mc._p32(col_idx), None, None, ctypes.byref(self.handle)) == 0
 
-    def attention(self, batch, heads, dk, p_bits=8, qkv_bits=8, token_major=True, options=None):
+    def attention(self, batch, heads, dk, p_bits=8, qkv_bits=8, token_major=True, options=None, s_p=0.1):
         """(heads, waves) of every fused launch of a layer on this mask."""
         lib, one = load(), np.zeros(64, np.uint8)
         at = one.ctypes.data + -one.ctypes.data % 16
         lib.host_attentions()
         strides = (heads * self.L * dk, dk, heads * dk) if token_major else (heads * self.L * dk, self.L * dk, dk)
-        assert lib.mc_sparse_attention_ex(at, at, at, batch, heads, self.L, dk, *strides, self.handle, p_bits, qkv_bits, 0.1, 0.1, 0.1, 0.1,
+        assert lib.mc_sparse_attention_ex(at, at, at, batch, heads, self.L, dk, *strides, self.handle, p_bits, qkv_bits, 0.1, 0.1, 0.1, s_p,
                                           0, options, at, None, 0, None) == 0
         return [(lib.host_attention(i, 0), lib.host_attention(i, 1)) for i in range(lib.host_attentions())]
 

@@ -48,3 +48,22 @@ def test_classes_of_unequal_panels_go_by_their_own_chunks(short, long, n, batch,
     mask = host.Mask(2048, lengths)
     assert mask.attention(batch, heads, dk, qkv_bits=qkv_bits) == want
     mask.close()
+
+
+# Pairs by several waves with 16-bit codes: down to a scale of the probabilities of 2^-62, where entries 2^-64 of a row's largest have no codes
+@pytest.mark.parametrize("dk,p_bits,qkv_bits,s_p,mode,want", [
+    (64, 16, 8, 2.0 ** -62, 0, (2, 2)), (64, 16, 8, 2.0 ** -63, 0, (1, 2)), (48, 16, 8, 2.0 ** -63, 0, (1, 2)),
+    (64, 16, 8, 2.0 ** -63, 4, (1, 4)), (64, 16, 8, 2.0 ** -62, 4, (2, 4)), (64, 16, 8, 1e-40, 3, (1, 2)),
+    (64, 16, 4, 2.0 ** -63, 0, (2, 2)), (64, 8, 8, 2.0 ** -63, 0, (2, 2)),      # the other kernels' exponents have no such bound
+])
+def test_scales_of_probabilities_that_pairs_by_several_waves_do_not_take(dk, p_bits, qkv_bits, s_p, mode, want):
+    mask = host.Mask(2056, np.full(257, 822))         # 1028 units of 13 chunks
+    options = host.mc.Options(attention_mode=mode)
+    assert mask.attention(1, 4, dk, p_bits, qkv_bits, options=options, s_p=s_p) == [want]
+    mask.close()
+
+
+def test_pairs_by_one_wave_take_any_scale_of_probabilities():
+    mask = host.Mask(2056, np.full(257, 500))         # 4112 units of 8 chunks
+    assert mask.attention(2, 8, 64, 16, 8, s_p=2.0 ** -63) == [(2, 1)]
+    mask.close()
