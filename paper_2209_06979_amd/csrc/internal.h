@@ -213,7 +213,7 @@ struct DenseFillArgs {
 struct SddmmArgs {
     const int32_t *shares;     // n_shares x 4 (see mc_mat)
     int n_shares;
-    int uniform_vectors;       // > 0: the shares are the panels and each has this many vectors (shares is not read)
+    int uniform_vectors;       // > 0: the shares are the panels and each has this many vectors (shares need not be read)
     const int32_t *slot_idx;
     const uint8_t *Q;
     int64_t ldq_bytes, Q_batch_stride;

@@ -30,14 +30,23 @@ using namespace mcs;
 // four fp32 values rounded to fp16 (to nearest even; beyond the fp16 range: infinity)
 __device__ __forceinline__ v4h to_half4(v4f f) { return (v4h){(_Float16)f.x, (_Float16)f.y, (_Float16)f.z, (_Float16)f.w}; }
 
-// The workgroup's share: first slot, vectors, panel, first output vector; computed where all panels are equally long, which saves the one of a
-// wave's three dependent trips to memory that comes before its indices and rows of Q.  (Three operands in turn, replayed from a graph: 4096 x 4096,
-// 90 % empty, Kd = 256 5.57 -> 5.40 us; masks that are cut, or whose panels differ, read their shares as before: 9.01 -> 9.05.)
-__device__ __forceinline__ v4i share_of(const SddmmArgs &a)
+// The workgroup's share: first slot, vectors, panel, first output vector.  COMPUTED: worked out where all panels are equally long, which saves the one
+// of a wave's three dependent trips to memory that comes before its indices and rows of Q.  SCALAR: read through the scalar cache; the compiler reads
+// through the vector caches once a volatile statement comes before (request_arguments), and merged with what is worked out the values stay in vector registers: four
+// to nine more of them, a wave less per SIMD in nine of the kernels with float results.
+// Which kernels do which is measured, three operands in turn replayed from a graph, as before either / worked out or read through the vector caches / now:
+//   staged (both): 4096 x 4096, 90 % empty, Kd = 256 5.67 / 5.46 / 5.51 us, fp32 6.15 / 5.98 / 5.97; unequal panels 6.37 / 6.30 / 6.38; L16-R16, 2000 x 3100, V = 4,
+//     Kd = 200, unequal 8.95 / 8.91 / 8.91
+//   nib32 (scalar): 4096 x 4096, 90 %, unsigned, fp32 5.01 / 5.23 / 4.99; int32, unequal panels 4.46 / 4.57 / 4.49
+//   direct, 2048 x 2048: 16 bits (both), Kd = 640, 90 % 31.5 / 31.0 / 30.8; bytes with float results (both), Kd = 1040, 80 % 42.5 / 41.6 / 41.6; with int32 results
+//     (scalar) 42.0 / 42.9 / 42.05; nibbles (neither), Kd = 2112, 90 % 29.5 / 29.7 / 29.5, fp16 30.0 / 31.5 / 30.0 (scalar alone 29.95, both 31.2 and 30.3)
+//   unsigned (both), bytes, 2048 x 2048, 90 %, Kd = 1040 33.0 / 31.9 / 32.0
+template <bool COMPUTED, bool SCALAR> __device__ __forceinline__ v4i share_of(const SddmmArgs &a)
 {
-    const int p = (int)blockIdx.x, n = a.uniform_vectors;
-    if (n > 0) return (v4i){p * ((n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK), n, p, p * n};
-    return *reinterpret_cast<const v4i *>(a.shares + 4 * p);
+    const int p = (int)blockIdx.x, n = COMPUTED ? a.uniform_vectors : 0;
+    if (COMPUTED && n > 0) return (v4i){p * ((n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK), n, p, p * n};
+    if constexpr (SCALAR) return *(__attribute__((address_space(4))) const v4i *)(uintptr_t)(a.shares + 4 * p);
+    else return *reinterpret_cast<const v4i *>(a.shares + 4 * p);
 }
 
 // DQ: fused dequantisation (Section 5.3).  A compile-time switch: the integer path keeps its
@@ -213,7 +222,7 @@ __global__ __launch_bounds__(512) void sddmm_staged_kernel(SddmmArgs a)
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
     const int batch = blockIdx.y;
-    const v4i share = share_of(a);
+    const v4i share = share_of<true, true>(a);
     const int s0 = share.x, n = share.y, panel = share.z;
     // (codes written into an operand's device format also cover the padded slots, with zeros)
     const int n_all = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK : n;
@@ -418,7 +427,7 @@ __global__ __launch_bounds__(64 * WK) void sddmm_nib32_kernel(SddmmArgs a)
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane >> 1, seg = lane & 1;
     const int batch = blockIdx.y;
-    const v4i share = share_of(a);
+    const v4i share = share_of<false, true>(a);
     const int s0 = share.x, n = share.y, panel = share.z;
     const int nch = (n + MC_CHUNK - 1) / MC_CHUNK;
     const int32_t *idx = a.slot_idx + s0;
@@ -489,7 +498,7 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_direct_kernel(SddmmArg
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, g = lane >> 4;
     const int batch = blockIdx.y;
-    const v4i share = share_of(a);
+    const v4i share = share_of<PB == 16 || (PB == 8 && DQ), PB != 4>(a);
     const int s0 = share.x, n = share.y, panel = share.z;
     // (codes written into an operand's device format also cover the padded slots of the last chunk, with zeros)
     const int ntile = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * 4 : (n + 15) / 16;
@@ -557,7 +566,7 @@ __global__ __launch_bounds__(64 * SDDMM_WAVES) void sddmm_unsigned_kernel(SddmmA
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, g = lane >> 4;
     const int batch = blockIdx.y;
-    const v4i share = share_of(a);
+    const v4i share = share_of<true, true>(a);
     const int s0 = share.x, n = share.y, panel = share.z;
     // (codes written into an operand's device format also cover the padded slots of the last chunk, with zeros)
     const int ntile = (DQ && a.float_out == 3) ? (n + MC_CHUNK - 1) / MC_CHUNK * 4 : (n + 15) / 16;
