@@ -1591,7 +1591,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         f.Q = static_cast<const uint8_t *>(Q_dev); f.Km = static_cast<const uint8_t *>(Km_dev);
         f.Vm = static_cast<const uint8_t *>(Vm_dev); f.O = static_cast<float *>(O_dev); f.out_f16 = out_f16;
         f.head_stride = head_stride; f.token_stride = token_stride; f.batch_stride = batch_stride;
-        f.in_head_stride = head_stride * qkv_bits / 8; f.in_token_stride = token_stride * qkv_bits / 8;
+        f.in_head_stride = head_stride * qkv_bits / 8; f.in_token_stride = (int)(token_stride * qkv_bits / 8);
         f.in_batch_stride = batch_stride * qkv_bits / 8;
         f.score_scale = s_q * s_k / std::sqrt((float)dk); f.inv_s_p = 1.f / s_p; f.out_scale = s_p * s_v;
         f.heads = heads; f.batch = batch; f.tokens = L;

@@ -161,9 +161,11 @@ void attention_fused_kernel(AttnArgs a)
     // otherwise fetch while another XCD fetches it, too.  (By itself, neighbouring pairs at the same time and as it is: 8 x 8 heads x 1800, 87 %
     // empty, 8-bit codes and inputs, dk = 32 36.6 -> 33.9 us, 48 60.2 -> 41.6, 80 61.8 -> 55.4, 96 63.1 -> 59.0, 128 52.4 -> 50.3.)
     const int groups = a.heads / HPW;
-    // (all of the first line of arguments in one round trip, not one by one as they come to be needed)
+    // (all that a wave needs first in one round trip, not one by one as it comes to be needed: the first line of arguments and what follows it, which no
+    // argument that only some kernels read may part.  With the panels' length among the pointers behind that line the kernels that do not read it waited
+    // a second and a third time; 4 heads x 1000 4.31 -> 4.18 us, 2 heads x 520 3.65 -> 3.53, 8 x 4 heads x 8192 of any kind 0.994 - 1.002x.)
     constexpr bool COMPUTED = !(HPW == 2 && KS > 1 && PB == 8 && QB == 8 && !PAD); // (see below)
-    if constexpr (COMPUTED) asm volatile("" ::"s"(a.uniform_vectors), "s"(a.Q));
+    if constexpr (COMPUTED) asm volatile("" ::"s"(a.uniform_vectors));
     asm volatile("" ::"s"(a.panel_ptr), "s"(a.slot_idx), "s"(a.panel_list), "s"(a.heads), "s"(a.batch), "s"(a.pair_shift), "s"(a.pair_rows),
                  "s"(a.Km), "s"(a.in_token_stride), "s"(a.in_head_stride), "s"(a.Q));
     const int grid_row = (int)(blockIdx.z * PAIR_ROWS_Y + blockIdx.y);
@@ -177,9 +179,9 @@ void attention_fused_kernel(AttnArgs a)
     const int panel = a.panel_list ? a.panel_list[blockIdx.x >> a.pair_shift] : (int)(blockIdx.x >> a.pair_shift);
     const int head = hgrp * HPW + w;
     // (panels of equal length: first slot and length without a trip to memory that the column indices wait for.  Replayed from a graph, three layers
-    // in turn: 4 heads x 1000 4.46 -> 4.40 us, 8 x 4 heads x 8192, 16-bit codes, (L, heads, dk) 170.5 -> 169.3.
+    // in turn: 4 heads x 1000 4.46 -> 4.40 us, 8 x 4 heads x 8192, 16-bit codes, (L, heads, dk) 170.5 -> 169.3; as single calls the same, the host issues them.
     // Not where several waves share the 8-bit codes of a pair: all 128 registers are taken there, and one more would be spilled.)
-    int s0, n = COMPUTED ? (int)a.uniform_vectors : 0;
+    int s0, n = COMPUTED ? a.uniform_vectors : 0;
     if (COMPUTED && n > 0) s0 = panel * ((n + MC_CHUNK - 1) / MC_CHUNK * MC_CHUNK);
     else {
         s0 = a.panel_ptr[2 * panel];

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <atomic>
@@ -288,9 +289,11 @@ struct AttnArgs {
     int heads, batch;
     int pair_shift, pair_rows;               // set by the launcher: log2 of the (head group, batch item) pairs of a grid row; rows of the grid
     const uint8_t *Km;
-    int64_t in_token_stride, in_head_stride; // bytes of Q, Km, Vm
+    int in_token_stride;                     // bytes of Q, Km, Vm, below 2^24
+    int uniform_vectors;                     // > 0: every panel has this many vectors and starts behind the chunks of those before (panel_ptr need not be read)
+    int64_t in_head_stride;                  // bytes of Q, Km, Vm
+    // (these follow: kernels that do not read uniform_vectors ask for everything from Km to in_batch_stride at once)
     const uint8_t *Q, *Vm;
-    int64_t uniform_vectors;                 // > 0: every panel has this many vectors and starts behind the chunks of those before (panel_ptr is not read)
     int64_t in_batch_stride;                 // between batch items: bytes of Q, Km, Vm
     float *O;                                // fp32, or half when out_f16 is set
     int64_t head_stride, token_stride;       // elements of O
@@ -304,6 +307,7 @@ struct AttnArgs {
     int P, tokens;
     int64_t index_bytes;
 };
+static_assert(offsetof(AttnArgs, Q) == 64 && offsetof(AttnArgs, in_batch_stride) == 80, "a line of 64 bytes; one request from Km on");
 
 hipError_t launch_spmm(mc_prec prec, const SpmmArgs &a, int bnb, int waves, hipStream_t s);
 // the L8-R8 SpMM (128-byte tiles, 2 waves per panel, two chunks in flight; every panel at most 8 chunks, whole panels,
