@@ -1628,12 +1628,12 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                 const double work = (double)units * mean;
                 const int64_t head_bytes = (int64_t)dk * qkv_bits / 8;
                 const bool long_enough = units >= 1024 && work >= 12500.0;
-                // (Of 1152 to 4095 units, heads of 48 bytes take three chunks a panel: of 1690 layers in every form 22 change, 1.08 times as fast in the
-                // mean, 20 of them by more than 2 %, none slower by as much; 8 heads x 2680, 2.5 chunks 11.8 -> 9.4 us.  With two chunks 0.89 - 1.03.)
+                // (From 1152 units on, heads of 48 bytes take more than two chunks a panel: of 1690 layers in every form 22 change, 1.08 times as fast in the
+                // mean, 20 of them by more than 2 %, none slower by as much; 8 heads x 2680, 2.5 chunks 11.8 -> 9.4 us; 20 layers of 4160 to 4860 units and 2.0 to
+                // 2.33 chunks, less than 10000 in all, 0.98 - 1.13, 1.05 in the mean.  With two chunks and 1152 to 2000 units 0.89 - 1.03.)
                 const bool two = fills ? units >= 2048 || long_enough
-                                       : units >= 4096 ? work >= 10000.0
-                                                       : (long_enough && f.in_token_stride >= 96 && (head_bytes > 32 || wpp < 4)) ||
-                                                             (head_bytes > 32 && units >= 1152 && mean > 2.0);
+                                       : (units >= 4096 ? work >= 10000.0 : long_enough && f.in_token_stride >= 96 && (head_bytes > 32 || wpp < 4)) ||
+                                             (head_bytes > 32 && units >= 1152 && mean > 2.0);
                 // (Not 128 nibbles by four waves each: eight waves of 152 registers are one workgroup a compute unit, a third of its places empty.
                 // 2 x 2 heads x 7496, 74 % empty 103 -> 73 us, 8 x 4800, 75 % 96 -> 62.)
                 hpg = (pairs && two && wpp < 8 && !(fills && tile == 128 && wpp == 4) && !(faint && wpp > 1)) ? 2 : 1;

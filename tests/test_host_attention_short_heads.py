@@ -20,3 +20,18 @@ def test_pairs(batch, heads, L, n, want):
     assert mask.attention(batch, heads, 48, 16, 8) == [want]
     assert mask.attention(batch, heads, 48, 8, 8, token_major=False)[0][0] == 1
     mask.close()
+
+
+@pytest.mark.parametrize("heads,L,three,want", [
+    (8, 4088, 26, (2, 1)),            # 4088 units of 2.05 chunks in the mean
+    (8, 4104, 26, (2, 1)), (8, 4944, 6, (2, 1)),     # 4104, and 4944 of 2.01: less than 10000 in all
+    (8, 4104, 0, (1, 1)),             # two chunks in every panel
+    (8, 1144, 26, (1, 1)),            # 1144 units
+])
+def test_pairs_of_more_than_two_chunks_in_the_mean(heads, L, three, want):
+    lengths = np.full(L // 8, 128)
+    lengths[:three] = 150
+    mask = host.Mask(L, lengths)
+    assert mask.attention(1, heads, 48, 8, 8) == [want]
+    assert mask.attention(1, heads, 32, 8, 8)[0][0] == 1          # heads of 32 bytes as before
+    mask.close()
