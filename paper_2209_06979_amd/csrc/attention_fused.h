@@ -33,6 +33,7 @@
 // per chunk, so that the column indices a lane needs are consecutive) and its 16-byte segments are
 // XOR-swizzled with s % NIT so that rows read together fall into different banks.
 #pragma once
+#include "attention_order.h"
 #include "internal.h"
 #include "lds_async.h"
 #include <type_traits>
@@ -156,7 +157,7 @@ void attention_fused_kernel(AttnArgs a)
     const int j = lane & 15, g = lane >> 4;
     const int rg = lane / LPR, seg = lane % LPR;
     // Workgroups are handed to the 8 XCDs round-robin by linear id.  1, 2, 4 or 8 (head group, batch item) pairs are worked on
-    // at a time, a row of the grid (pairs_at_a_time): an XCD then sees one pair at a time, and neighbouring ones one after the other.
+    // at a time, a row of the grid (attention_pair_shift): an XCD then sees one pair at a time, and neighbouring ones one after the other.
     // In (L, heads, dk) tensors neighbouring heads share lines unless their rows are whole ones: an XCD finds in its L2 what it would
     // otherwise fetch while another XCD fetches it, too.  (By itself, neighbouring pairs at the same time and as it is: 8 x 8 heads x 1800, 87 %
     // empty, 8-bit codes and inputs, dk = 32 36.6 -> 33.9 us, 48 60.2 -> 41.6, 80 61.8 -> 55.4, 96 63.1 -> 59.0, 128 52.4 -> 50.3.)
@@ -609,88 +610,11 @@ void attention_fused_kernel(AttnArgs a)
     }
 }
 
-// Lines of 128 bytes that the rows of the busiest of 1, 2, 4, 8 runs of neighbouring pairs touch, against the mean: a gather asks for lines, and an XCD
-// that has one head of (L, heads, dk) tensors to itself takes as long as that head's rows cross lines (48 bytes at 96 of 128 do, at 0 do not).
-// False: no pair differs from the others.  (offset: of a pair's first row within a line, of 16-byte pieces; a pattern of eight of them comes round
-// again after eight pairs, so that more than 64 pairs even it out by themselves.)
-struct PairLines {
-    double mean = 0.0, busiest[4] = {1.0, 1.0, 1.0, 1.0};
-    bool find(const AttnArgs &a, int pairs, int groups, int row, int64_t group_stride)
-    {
-        if (128 % row == 0 && a.in_token_stride % row == 0) return false;
-        if (row % 128 == 0 || pairs > 64 || a.in_token_stride % 128 % 32 != 0) return false; // (the last: every row of a pair in turn at every place)
-        double at[8];
-        bool equal = true;
-        for (int o = 0; o < 8; ++o) {
-            int lines = 0;
-            for (int t = 0; t < 4; ++t) lines += ((int)((o * 16 + t * a.in_token_stride) % 128) + row + 127) / 128;
-            at[o] = lines / 4.0;
-            equal = equal && at[o] == at[0];
-        }
-        if (equal) return false;
-        double run[8] = {};
-        for (int p = 0; p < pairs; ++p) {
-            const int64_t off = (int64_t)(p / groups) * a.in_batch_stride + (int64_t)(p % groups) * group_stride;
-            const double lines = (at[((uintptr_t)a.Km + off) / 16 % 8] + at[((uintptr_t)a.Vm + off) / 16 % 8]) / 2;
-            mean += lines;
-            run[(int64_t)p * 8 / pairs] += lines; // (eight runs are whole where they are asked for)
-        }
-        mean /= pairs;
-        for (int s = 3; s >= 0; --s) {
-            double most = 0.0;
-            for (int k = 0; k < 1 << s; ++k) most = run[k] > most ? run[k] : most;
-            busiest[s] = most / (mean * pairs / (1 << s));
-            for (int k = 0; k < 1 << s >> 1; ++k) run[k] = run[2 * k] + run[2 * k + 1];
-        }
-        return true;
-    }
-};
-
-// log2 of the pairs worked on at a time, 2^s of them: the s at which the XCDs fetch least from beyond their L2s and the lines they ask L2 for are shared
-// out best.  The 8 >> s XCDs of
-// a pair fetch its K and V rows (row_bytes), and each its share of the column indices; the share is still there for
-// the XCD's next pair if it fits beside a pair's rows into three of L2's four megabytes, or is fetched again for every pair.
-// 2^s must divide the number of pairs.  Measured at 1, 2, 4, 8 pairs at a time, 90 % empty, dk = 64, 8-bit codes and inputs:
-//   8 x 4 heads x 8192, (heads, L, dk)   217  213  212 (taken)  215 us        16-bit codes 227  219  220 (taken)  226; 4-bit inputs 194  193  191 (taken)  197
-//   8 x 4 heads x 8192, (L, heads, dk)   180  179  178.5        177.5 (taken)     4-bit inputs 165  170  168  167.5 (taken)
-//   8 x 8 heads x 4096, (heads, L, dk)   122  112  109          108 (taken)   (L, heads, dk) 95.5  92.5  91.5  90 (taken)
-//   2 heads x 4096, batch 32             122  113  108          108 (taken)   8 heads x 4096 x 128  27  25  22.1  22.1 (taken)
-// and of (L, heads, dk) tensors whose rows cross lines, 8 heads x 3072, 90 % empty:
-//   nibbles, dk = 96   15.3  14.7 (taken)  17.1  20.6;   8 bits, dk = 80  18.2  17.0  17.05 (taken)  19.9;   96  19.5  17.9  18.4 (taken)  21.2;
-//   112  21.4  20.2 (taken)  21.5  21.6;   48 (four pairs)  12.2  11.9 (taken)  12.7
-// A byte more to fetch costs 0.02 - 0.065 ns per kB, since the gather goes on meanwhile; L2 serves 200 lines a ns to this kernel.
-inline int pairs_at_a_time(int64_t pairs, double row_bytes, double index_bytes, const PairLines *lines)
-{
-    constexpr double US_PER_BYTE = 4e-8, LINES_PER_US = 2e5;
-    const double asked = lines ? pairs * lines->mean * 2.0 * index_bytes / 4.0 / LINES_PER_US : 0.0;
-    int best = 0, plain = 0;
-    double least = 0.0, bytes = 0.0, us_plain = 0.0;
-    for (int s = 0; s <= 3 && pairs % (1 << s) == 0; ++s) {
-        const double share = index_bytes * (1 << s) / 8;
-        const double fetched = pairs * row_bytes * (8 >> s) + (row_bytes + share <= 3.0 * (1 << 20) ? 8 * share : pairs * index_bytes);
-        const double us = fetched * US_PER_BYTE + (lines ? asked * lines->busiest[s] : 0.0);
-        if (s == 0 || us <= least) {
-            best = s;
-            least = us;
-        }
-        if (s == 0 || fetched <= bytes) {
-            plain = s;
-            bytes = fetched;
-            us_plain = us;
-        }
-    }
-    return least < us_plain - 0.04 * asked ? best : plain; // (for less than that the estimate is too coarse)
-}
-
 template <int HPW, int PB, int QB, int KS, int DK, bool PAD> hipError_t launch_pairs(AttnArgs a, hipStream_t s)
 {
     if (HPW == 2 && KS > 1 && PB == 16 && QB == 8 && !(a.inv_s_p <= FOLDED_MAX_INV_S_P)) return hipErrorInvalidValue;
     const unsigned pairs = (unsigned)(a.heads / HPW) * (unsigned)a.batch;
-    const int row = HPW * (PAD ? a.real_pieces * 16 : DK * QB / 8), lines = (row + 127) / 128 * 128; // (the L2 holds lines of 128 bytes)
-    PairLines asked;
-    const bool differ = asked.find(a, (int)pairs, a.heads / HPW, row, HPW * a.in_head_stride);
-    a.pair_shift = pairs_at_a_time(pairs, 2.0 * a.tokens * (a.in_token_stride < lines ? (double)a.in_token_stride : lines), (double)a.index_bytes,
-                                   differ ? &asked : nullptr);
+    a.pair_shift = attention_pair_shift(a, HPW, PAD ? a.real_pieces * 16 : DK * QB / 8);
     a.pair_rows = (int)(pairs >> a.pair_shift);
     const unsigned rows = (unsigned)a.pair_rows, y = rows < PAIR_ROWS_Y ? rows : PAIR_ROWS_Y;
     return launch_kernel((attention_fused_kernel<8, HPW, PB, QB, KS, DK, PAD>), dim3((unsigned)a.P << a.pair_shift, y, (rows + y - 1) / y),

@@ -14,6 +14,7 @@ from paper_2209_06979_amd import binding as mc
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2209_06979_amd", "csrc")
 STUBS = r"""
+#include "attention_order.h"
 #include "internal.h"
 #include <atomic>
 #include <cstdlib>
@@ -22,11 +23,14 @@ static std::atomic<size_t> limit{~(size_t)0};
 static std::atomic<long> allocations{0};
 static thread_local char called[64] = "";
 static thread_local int detail = 0, variant[2] = {0, 0};
-static thread_local int heads_waves[8][2], n_attention = 0;
+static thread_local int heads_waves[8][3], n_attention = 0;
 static hipError_t note(const char *what, int d = 0) { strcpy(called, what); detail = d; return hipSuccess; }
-static hipError_t attention(int heads, int waves)
+static hipError_t attention(const AttnArgs &a, int heads, int waves, int head_bytes)
 {
-    if (n_attention < 8) { heads_waves[n_attention][0] = heads; heads_waves[n_attention][1] = waves; }
+    if (n_attention < 8) {
+        heads_waves[n_attention][0] = heads; heads_waves[n_attention][1] = waves;
+        heads_waves[n_attention][2] = attention_pair_shift(a, heads, head_bytes);
+    }
     ++n_attention;
     return note("attention", 10 * heads + waves);
 }
@@ -73,8 +77,8 @@ hipError_t launch_scores_softmax(const ScoresArgs &, int, int, int, hipStream_t)
 int scores_softmax_max_npad(int, int) { return 4096; }
 hipError_t launch_absmax(const float *, int64_t, float *, hipStream_t) { return note("absmax"); }
 hipError_t launch_quantize(const float *, int64_t, float, int, uint8_t *, hipStream_t) { return note("quantize"); }
-hipError_t launch_attention_fused(const AttnArgs &, int heads, int waves, int, int, int, hipStream_t) { return attention(heads, waves); }
-hipError_t launch_attention_fused_padded(const AttnArgs &, int heads, int waves, int, int, int, hipStream_t) { return attention(heads, waves); }
+hipError_t launch_attention_fused(const AttnArgs &a, int heads, int waves, int, int bits, int dk, hipStream_t) { return attention(a, heads, waves, dk * bits / 8); }
+hipError_t launch_attention_fused_padded(const AttnArgs &a, int heads, int waves, int, int, int, hipStream_t) { return attention(a, heads, waves, a.real_pieces * 16); }
 int attention_fused_max_vectors() { return 4096; }
 """
 _lib = None
@@ -169,13 +173,18 @@ class Mask:
 
     def attention(self, batch, heads, dk, p_bits=8, qkv_bits=8, token_major=True, options=None, s_p=0.1):
         """(heads, waves) of every fused launch of a layer on this mask."""
-        lib, one = load(), np.zeros(64, np.uint8)
-        at = one.ctypes.data + -one.ctypes.data % 16
+        return [(h, w) for h, w, _ in self.launches(batch, heads, dk, p_bits, qkv_bits, token_major, options, s_p)]
+
+    def launches(self, batch, heads, dk, p_bits=8, qkv_bits=8, token_major=True, options=None, s_p=0.1, places=(0, 0), wider=0):
+        """The same with log2 of the pairs worked on at a time.  places: of K and V, 16-byte pieces from the start of a line; wider: elements that tokens are longer by."""
+        lib, one = load(), np.zeros(512, np.uint8)
+        at = one.ctypes.data + -one.ctypes.data % 128
         lib.host_attentions()
-        strides = (heads * self.L * dk, dk, heads * dk) if token_major else (heads * self.L * dk, self.L * dk, dk)
-        assert lib.mc_sparse_attention_ex(at, at, at, batch, heads, self.L, dk, *strides, self.handle, p_bits, qkv_bits, 0.1, 0.1, 0.1, s_p,
+        token = heads * dk + wider
+        strides = (token * self.L, dk, token) if token_major else (heads * self.L * dk, self.L * dk, dk)
+        assert lib.mc_sparse_attention_ex(at, at + 16 * places[0], at + 16 * places[1], batch, heads, self.L, dk, *strides, self.handle, p_bits, qkv_bits, 0.1, 0.1, 0.1, s_p,
                                           0, options, at, None, 0, None) == 0
-        return [(lib.host_attention(i, 0), lib.host_attention(i, 1)) for i in range(lib.host_attentions())]
+        return [tuple(lib.host_attention(i, what) for what in range(3)) for i in range(lib.host_attentions())]
 
     def close(self):
         load().mc_mat_destroy(self.handle)
