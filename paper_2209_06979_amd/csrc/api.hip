@@ -1635,7 +1635,7 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
                                        : (units >= 4096 ? work >= 10000.0 : long_enough && f.in_token_stride >= 96 && (head_bytes > 32 || wpp < 4)) ||
                                              (head_bytes > 32 && units >= 1152 && mean > 2.0);
                 // (Not 128 nibbles by four waves each: eight waves of 152 registers are one workgroup a compute unit, a third of its places empty.
-                // 2 x 2 heads x 7496, 74 % empty 103 -> 73 us, 8 x 4800, 75 % 96 -> 62.)
+                // 2 x 2 heads x 7496, 74 % empty 101.8 -> 74.4 us, 8 x 4800, 75 % 94.7 -> 64.0.)
                 hpg = (pairs && two && wpp < 8 && !(fills && tile == 128 && wpp == 4) && !(faint && wpp > 1)) ? 2 : 1;
                 // (Rows of 256 bytes, too, where four waves' stages take half a compute unit's LDS: against 1024 waves in flight 46 drawn layers of
                 // dk = 144 - 192 1.03 times as fast in the mean, up to 1.23.  4096 waves: 0.98, down to 0.73.)

@@ -22,6 +22,10 @@ EQUAL = [
     (64, 16, 8, 1, 2, 1024, 0.4, (1, 8), (1, 8)), (128, 8, 4, 1, 1, 520, 0.38, (1, 8), (1, 8)),  # 10 chunks; 6 of nibbles
     (80, 16, 8, 1, 3, 2736, 0.87, (1, 2), (1, 2)), (112, 8, 8, 1, 5, 2048, 0.8, (1, 2), (1, 2)),  # 1026 and 1280 units of 6 and 7 chunks
     (64, 8, 8, 1, 2, 1032, 0.42, (1, 4), (1, 4)),     # 258 units of 10 chunks
+    # 128 nibbles: pairs by one and two waves, single heads by four (19 chunks, 4800 units); shorter rows in pairs by four, too
+    (128, 8, 4, 1, 8, 4800, 0.75, (1, 4), (1, 4)), (128, 16, 4, 1, 8, 4800, 0.75, (1, 4), (1, 4)), (128, 16, 4, 1, 8, 4800, 0.8, (2, 2), (1, 2)),
+    (128, 8, 4, 1, 8, 4800, 0.9, (2, 1), (1, 1)), (64, 8, 4, 1, 8, 4800, 0.75, (2, 4), (1, 4)), (96, 8, 4, 1, 8, 4800, 0.75, (1, 4), (1, 4)),
+    (48, 8, 8, 1, 8, 4800, 0.75, (2, 4), (1, 4)),
 ]
 
 
