@@ -1661,8 +1661,8 @@ int attention_impl(const void *Q_dev, const void *Km_dev, const void *Vm_dev, in
         // costs nothing there.  With panels in three classes and more up to 3000 (panel, head) units, or 1400 where the longest panel takes eight waves and
         // heads are longer than 64 elements; with panels of up to 16 chunks, in two classes, up to 1400.  Of 340 drawn masks both ways, replayed from a
         // graph, the 150 below the lines run 1.5 times as fast in one launch in the mean, 0.99 - 2.55 (2 heads x 1128, 2.1 chunks of up to 18 15.1 -> 6.0 us; 1800 units, dk = 128,
-        // 2.4 of up to 19 1.65); of those above one launch takes longer the larger they are, up to 3.4 times (27648 units, dk = 128, 9 of up to 54 chunks 217 us in classes, 478
-        // in one), some of up to 5000 units in less time, down to 0.61.  Two classes far apart are on either side, 0.67 - 1.57 below 1500 units.
+        // 2.4 of up to 19 1.65); of those above one launch takes longer the larger they are (27648 units, dk = 128, 9 of up to 54 chunks 217 us in classes, 478
+        // in one), up to 3.4 times, some of up to 5000 units in less time, down to 0.61.  Two classes far apart are on either side, 0.67 - 1.57 below 1500 units.
         const int classes = (mask->class_start[1] > 0) + (mask->class_start[2] > mask->class_start[1]) + (mask->class_start[3] > mask->class_start[2]) +
                             (mask->class_start[4] > mask->class_start[3]);
         const int64_t all_units = (int64_t)mask->P * heads * batch;

@@ -1,6 +1,6 @@
-"""Masks whose panels are all equally long: first slot, length and first output of a panel are computed, not read.  SDDMM against the
-oracle in every kernel; the attention layer against the same mask with one vector less in its last panel, whose other rows have to be
-the same to the last bit."""
+"""Masks whose panels are all equally long: most kernels compute a panel's first slot, length and first output instead of reading them.  SDDMM
+against the oracle in every kernel; the attention layer (the fused kernel; its tile of 192 in automatic mode, which alone takes it) against the same
+mask with one vector less in its last panel, whose other rows have to be the same to the last bit."""
 import numpy as np
 import pytest
 
@@ -44,6 +44,8 @@ def test_attention(n, heads, dk, p_bits, mode):
     rp, ci = wl.ragged_pattern(L, L, 8, [n] * P, 9711)
     shorter = np.concatenate([rp[:-1], rp[-1:] - 1]).astype(rp.dtype)
     equal, other = mc.SparseMatrix(L, L, 8, rp, ci), mc.SparseMatrix(L, L, 8, shorter, ci[:-1])
+    mode = mode if dk <= 128 else 0
+    assert all(mc.attention_form(m, dk, options=mc.Options(attention_mode=mode)) == "fused" for m in (equal, other))
     mc.set_attention_mode(mode)
     try:
         args = (0.02, 0.02, 0.02, 1.0 / (127 if p_bits == 8 else 32639))
